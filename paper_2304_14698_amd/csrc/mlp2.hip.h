@@ -12,7 +12,7 @@
 // registers), so layer 1's accumulator layout (lane = row, registers = features) is, after ReLU
 // and conversion, the B-operand layout of layer 2; layer 2's accumulators have lane = row as
 // well, so a row leaves as register quads and the per-receiver sum runs across adjacent lanes.
-// Weights are pre-arranged on the host in the per-lane fragment order (see swizzle_* in the
+// Weights are pre-arranged in the per-lane fragment order (arrange_weights_kernel in the
 // runtime), so every weight fragment is one coalesced 1 KB load per wave.
 #pragma once
 #include "mma.hip.h"

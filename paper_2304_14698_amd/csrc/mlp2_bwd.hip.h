@@ -29,7 +29,7 @@
 struct Mlp2BwdArgs {
   int64_t n_rows, n_blocks;
   const void *W1s, *W2s;     // forward fragment order
-  const void *W2bt, *W1bt;   // contraction over the weight's columns (see swizzle_chain)
+  const void *W2bt, *W1bt;   // contraction over the weight's columns (SWZ_CHAIN order)
   const float *b1, *b2;
   int nslab1;
   const void *h, *agg;       // forward inputs, operand type

@@ -21,7 +21,7 @@
 
 struct Mlp2BwdzArgs {
   int64_t n_rows, n_blocks;
-  const void *W2bt, *W1bt;     // contraction over the weight's columns (see swizzle_chain)
+  const void *W2bt, *W1bt;     // contraction over the weight's columns (SWZ_CHAIN order)
   const void *dy;              // upstream gradient [N, H] bf16 (EDGE: indexed by receiver); kernels instantiated
                                // with GIVEN: dz2 itself, already masked by [y > 0] (then ymask and dz2 are unused)
   const int32_t *dy_index;     // NODE, EMBED, optional: row n reads dy[dy_index[n]] (the gradient of the
