@@ -1,6 +1,7 @@
 // Device side of the library: context, weight upload, workspace, kernel sequencing.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -184,6 +185,8 @@ struct xrl_ctx {
   char *bws = nullptr;          // backward scratch
   size_t bws_bytes = 0;
   // buffers of the last encode (inside ws)
+  uint64_t id = 0;              // unique per context
+  std::shared_ptr<DevicePool> blocks;
   uint64_t enc_batch = 0;
   bool enc_saved = false;
   float *pool = nullptr, *carry = nullptr, *ro_act[2] = {nullptr, nullptr};
@@ -242,9 +245,185 @@ int static_scratch(int dev, char **out) {
 }
 }  // namespace
 
+// ---- memory of packed batches ----------------------------------------------------------------
+// Pinned host blocks and device blocks are kept when a batch is freed: pinning and unpinning, hipMalloc
+// and hipFree (which waits for the whole device) and the page faults of fresh memory took most of
+// packing and uploading a state of a few hundred thousand nodes. Both pools are bounded and are given
+// back with the last context (host) or their context (device).
+namespace {
+constexpr size_t kMaxPinnedBlock = (size_t)128 << 20;    // larger batches stay in ordinary memory
+constexpr size_t kMaxPinnedTotal = (size_t)1 << 30;      // pinned by all batches together
+constexpr size_t kMaxIdlePinned = (size_t)256 << 20, kMaxIdleDevice = (size_t)1 << 30;
+constexpr size_t kMaxIdleBlocks = 4;
+
+// capacity classes: four per power of two, so that batches of about one size share blocks
+size_t block_capacity(size_t bytes) {
+  size_t step = 16384;
+  while (step * 8 < bytes) step *= 2;
+  return (bytes + step - 1) / step * step;
+}
+
+struct HostPool {
+  std::mutex mu;
+  std::vector<HostBlock> idle;      // oldest first
+  size_t idle_bytes = 0, pinned_bytes = 0;
+  int contexts = 0;
+};
+HostPool &host_pool() {
+  static HostPool *p = new HostPool;   // (never destroyed: a batch may be freed by a static destructor)
+  return *p;
+}
+// Blocks change hands in calls that touch no stream: they must not disturb a capture that this or another
+// thread has under way.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+void host_block_release(HostBlock &b) {
+  if (!b.pinned) {
+    free(b.p);
+    b = HostBlock();
+    return;
+  }
+  RelaxedCapture relaxed;
+  if (b.copied) {
+    (void)hipEventSynchronize((hipEvent_t)b.copied);
+    (void)hipEventDestroy((hipEvent_t)b.copied);
+  }
+  (void)hipHostFree(b.p);
+  b = HostBlock();
+}
+void host_pool_context(int change) {
+  HostPool &hp = host_pool();
+  std::vector<HostBlock> drop;
+  {
+    std::lock_guard<std::mutex> lk(hp.mu);
+    hp.contexts += change;
+    if (hp.contexts == 0) {
+      drop.swap(hp.idle);
+      hp.pinned_bytes -= hp.idle_bytes;
+      hp.idle_bytes = 0;
+    }
+  }
+  for (HostBlock &b : drop) host_block_release(b);
+}
+}  // namespace
+
+HostBlock host_block_take(size_t bytes) {
+  HostPool &hp = host_pool();
+  HostBlock b;
+  const size_t cap = block_capacity(bytes);
+  bool pin = false;
+  std::unique_lock<std::mutex> lk(hp.mu);
+  if (hp.contexts > 0 && cap <= kMaxPinnedBlock) {
+    RelaxedCapture relaxed;
+    // the oldest idle block of a fitting class whose last transfer is over; one still being read by a
+    // transfer only if no other block may be added
+    int pick = -1, busy = -1;
+    for (size_t i = 0; i < hp.idle.size() && pick < 0; ++i) {
+      const HostBlock &x = hp.idle[i];
+      if (x.cap < bytes || x.cap > 2 * cap) continue;
+      if (!x.copied || hipEventQuery((hipEvent_t)x.copied) == hipSuccess) pick = (int)i;
+      else if (busy < 0) busy = (int)i;
+    }
+    if (busy >= 0) (void)hipGetLastError();              // (hipErrorNotReady is no error here)
+    if (pick < 0 && hp.idle.size() >= kMaxIdleBlocks) pick = busy;
+    if (pick >= 0) {
+      b = hp.idle[pick];
+      hp.idle.erase(hp.idle.begin() + pick);
+      hp.idle_bytes -= b.cap;
+    } else if (hp.pinned_bytes + cap <= kMaxPinnedTotal) {
+      pin = true;
+      hp.pinned_bytes += cap;
+    }
+  }
+  lk.unlock();
+  if (b.p) {
+    RelaxedCapture relaxed;
+    if (b.copied) (void)hipEventSynchronize((hipEvent_t)b.copied);
+    return b;
+  }
+  b.cap = cap;
+  if (pin) {
+    RelaxedCapture relaxed;
+    if (hipHostMalloc((void **)&b.p, cap, hipHostMallocPortable) == hipSuccess) {
+      b.pinned = true;
+      return b;
+    }
+    (void)hipGetLastError();
+    b.p = nullptr;
+    lk.lock();
+    hp.pinned_bytes -= cap;
+    lk.unlock();
+  }
+  b.p = (char *)aligned_alloc(4096, (cap + 4095) / 4096 * 4096);
+  return b;
+}
+
+void host_block_give(HostBlock &b) {
+  if (!b.p) return;
+  if (b.pinned) {
+    HostPool &hp = host_pool();
+    std::lock_guard<std::mutex> lk(hp.mu);
+    if (hp.contexts > 0 && hp.idle.size() < kMaxIdleBlocks && hp.idle_bytes + b.cap <= kMaxIdlePinned) {
+      hp.idle.push_back(b);
+      hp.idle_bytes += b.cap;
+      b = HostBlock();
+      return;
+    }
+    hp.pinned_bytes -= b.cap;
+  }
+  host_block_release(b);
+}
+
+// Idle device blocks of one context, reused by its later uploads: these are queued on the same stream
+// behind everything that has used the block.
+struct DevicePool {
+  std::mutex mu;
+  std::vector<std::pair<void *, size_t>> idle;
+  size_t idle_bytes = 0;
+  bool closed = false;
+  hipError_t take(size_t bytes, void **p, size_t *cap) {
+    *cap = block_capacity(bytes);
+    {
+      std::lock_guard<std::mutex> lk(mu);
+      for (size_t i = 0; i < idle.size(); ++i)
+        if (idle[i].second >= bytes && idle[i].second <= 2 * *cap) {
+          *p = idle[i].first;
+          *cap = idle[i].second;
+          idle_bytes -= *cap;
+          idle.erase(idle.begin() + i);
+          return hipSuccess;
+        }
+    }
+    return hipMalloc(p, *cap);
+  }
+  void give(void *p, size_t cap) {
+    {
+      std::lock_guard<std::mutex> lk(mu);
+      if (!closed && idle.size() < kMaxIdleBlocks && idle_bytes + cap <= kMaxIdleDevice) {
+        idle.push_back({p, cap});
+        idle_bytes += cap;
+        return;
+      }
+    }
+    (void)hipFree(p);
+  }
+  void close() {
+    std::lock_guard<std::mutex> lk(mu);
+    closed = true;
+    for (auto &x : idle) (void)hipFree(x.first);
+    idle.clear();
+    idle_bytes = 0;
+  }
+};
+
 extern "C" void xrl_batch_release_device(xrl_batch *b) {
   if (b && b->dev.block) {
-    (void)hipFree(b->dev.block);
+    if (b->pool && !b->shared) b->pool->give(b->dev.block, b->dev.bytes);
+    else (void)hipFree(b->dev.block);
+    b->pool.reset();
     b->dev = xrl_batch_device();
     b->uploaded = false;
   }
@@ -496,6 +675,13 @@ int check_batch(const xrl_ctx *c, const xrl_batch *b, const char *who) {
   if (x.n_op_types != y.n_op_types || x.n_node_dense != y.n_node_dense || x.d_edge != y.d_edge ||
       x.d_global != y.d_global)
     return fail(XRL_ERR_SHAPE, "%s: batch was packed for different feature widths", who);
+  if (b->owner != c->id) {               // uploaded by another context, perhaps on another stream
+    const_cast<xrl_batch *>(b)->shared = true;
+    if (b->mem.copied) HIP_TRY(hipEventSynchronize((hipEvent_t)b->mem.copied));
+  }
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (!b->shared && hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
+    const_cast<xrl_batch *>(b)->shared = true;   // (replays may run on any stream)
   return XRL_OK;
 }
 
@@ -1240,7 +1426,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   Mlp2BwdzArgs za;
   memset(&za, 0, sizeof(za));
   za.in_dst = d.in_dst; za.dz1 = dz1; za.dz2 = dz2;
-  za.tile_ptr = d.tile_ptr; za.n_tiles = (int64_t)b->tile_ptr.size() - 1;
+  za.tile_ptr = d.tile_ptr; za.n_tiles = b->n_tiles;
   bool dz2_given = false;
   auto mlp_bwd = [&](int kind, const EncMlp &e, const uint16_t *z1mask, const uint16_t *ymask) -> int {
     if constexpr (sizeof(T) == 2) {
@@ -1363,7 +1549,7 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   const xrl_model_desc &m = c->m;
   const int H = m.hidden, R = m.rounds, De = m.d_edge;
   const int64_t N = b->N, E = b->E, G = b->G;
-  const int64_t n_tiles = (int64_t)b->tile_ptr.size() - 1;
+  const int64_t n_tiles = b->n_tiles;
   // ---- workspace plan
   const int nh = save ? R + 1 : (R > 0 ? 2 : 1), nagg = save ? R : (R > 0 ? 1 : 0);
   size_t need = 0;
@@ -1638,6 +1824,10 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   }
   xrl_ctx *c = new (std::nothrow) xrl_ctx();
   if (!c) return fail(XRL_ERR_OOM, "xrl_create: out of host memory");
+  static std::atomic<uint64_t> next_ctx{1};
+  c->id = next_ctx++;
+  c->blocks = std::make_shared<DevicePool>();
+  host_pool_context(1);
   c->m = *model;
   c->L = L;
   c->single_layer = single_layer;
@@ -1678,7 +1868,7 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   const size_t tail_bytes = 1024 + sizeof(int32_t) * kMaxFusedSlots + sizeof(unsigned) * kClusterMaxGraphs;
   e = hipMalloc((void **)&c->d_w, w_bytes + tail_bytes);
   if (e != hipSuccess) {
-    delete c;
+    xrl_destroy(c);
     return fail(XRL_ERR_OOM, "device weights: %s", hipGetErrorString(e));
   }
   c->zero_row = (char *)c->d_w + w_bytes;
@@ -1741,6 +1931,8 @@ int xrl_destroy(xrl_ctx *c) {
   if (c->bws) (void)hipFree(c->bws);
   for (auto &sp : c->spans) { (void)hipEventDestroy(sp.a); (void)hipEventDestroy(sp.b); }
   for (auto &e : c->free_events) (void)hipEventDestroy(e);
+  c->blocks->close();
+  host_pool_context(-1);
   delete c;
   return XRL_OK;
 }
@@ -1768,97 +1960,89 @@ __global__ void agg_src_kernel(const int32_t *in_ptr, int64_t n, int32_t *agg_sr
 int xrl_batch_upload(xrl_ctx *c, xrl_batch *b) {
   if (!c || !b) return fail(XRL_ERR_NULL, "xrl_batch_upload: NULL argument");
   if (b->uploaded) return XRL_OK;
-  const int Dd = b->model.n_node_dense, De = b->model.d_edge, Dg = b->model.d_global;
-  const int64_t S = b->S, G = b->G, N = b->N, E = b->E;
-  size_t off = 0;
+  const int Dd = b->model.n_node_dense, De = b->model.d_edge;
+  const int64_t N = b->N, E = b->E;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();             // (a replay would read the host copy again, which may be gone)
+    return fail(XRL_ERR_HIP, "xrl_batch_upload: the stream is being captured");
+  }
+  // the device block: what the host sends, then what the device writes itself
+  size_t off = b->send_bytes;
   auto plan = [&](size_t bytes) { size_t o = off; off += align_up(bytes + 16); return o; };
-  const size_t o_sgp = plan((S + 1) * 4), o_gnp = plan((G + 1) * 4), o_op = plan(N * 4),
-               o_inp = plan((N + 1) * 4), o_ins = plan(E * 4), o_ind = plan(E * 4),
-               o_outp = plan((N + 1) * 4), o_outpos = plan(E * 4), o_ng = plan(N * 4),
-               o_nd = plan((size_t)N * Dd * 4), o_ef = plan((size_t)E * De * 4),
-               o_gg = plan((size_t)G * Dg * 4), o_mask = plan(G),
-               o_tile = plan(b->tile_ptr.size() * 4), o_gtile = plan(b->gtile_ptr.size() * 4),
-               o_gtp = plan(b->graph_tile_ptr.size() * 4), o_as = plan(N * 4);
-  // packed from edits: the attribute arrays are filled on the device from these
   const bool ed = b->from_edits;
-  const size_t o_nf = ed ? plan(N * 4) : 0, o_ef2 = ed ? plan(E * 4) : 0,
-               o_bop = ed ? plan(b->base_node_op.size() * 4) : 0, o_nop = ed ? plan(b->new_node_op.size() * 4) : 0,
-               o_bnd = ed ? plan(b->base_node_dense.size() * 4) : 0, o_nnd = ed ? plan(b->new_node_dense.size() * 4) : 0,
-               o_bef = ed ? plan(b->base_edge_feat.size() * 4) : 0, o_nef = ed ? plan(b->new_edge_feat.size() * 4) : 0;
+  const size_t o_as = plan(N * 4), o_op = ed ? plan(N * 4) : b->o_node_op, o_nd = ed ? plan((size_t)N * Dd * 4) : b->o_node_dense,
+               o_ef = ed ? plan((size_t)E * De * 4) : b->o_edge_feat;
+  xrl_batch_release_device(b);           // (of an upload that failed)
   char *blk = nullptr;
-  hipError_t e = hipMalloc((void **)&blk, off);
+  xrl_batch_device &d = b->dev;
+  hipError_t e = c->blocks->take(off, (void **)&blk, &d.bytes);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return fail(XRL_ERR_OOM, "device copy of the batch (%zu bytes): %s", off, hipGetErrorString(e));
   }
-  xrl_batch_device &d = b->dev;
   d.block = blk;
-  d.bytes = off;
-  // the host vectors live as long as the batch; wait for the copies anyway so that freeing the
-  // batch right after this call is safe
-  auto cp = [&](size_t o, const void *src, size_t bytes) -> hipError_t {
-    return bytes ? hipMemcpyAsync(blk + o, src, bytes, hipMemcpyHostToDevice, c->stream) : hipSuccess;
+  b->pool = c->blocks;
+  b->owner = c->id;
+  b->shared = false;
+  auto queue = [&]() -> int {
+    HIP_TRY(hipMemcpyAsync(blk, b->mem.p, b->send_bytes, hipMemcpyHostToDevice, c->stream));
+    if (N > 0)
+      agg_src_kernel<<<dim3((unsigned)((N + 255) / 256)), dim3(256), 0, c->stream>>>((const int32_t *)(blk + b->o_in_ptr), N,
+                                                                                    (int32_t *)(blk + o_as));
+    if (ed) {
+      auto expand = [&](size_t o_from, int64_t n, int width, size_t o_base, size_t o_new, size_t o_out) {
+        const int64_t total = n * width;
+        if (total > 0)
+          expand_rows_kernel<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, c->stream>>>(
+              (const int32_t *)(blk + o_from), n, width, (const uint32_t *)(blk + o_base), (const uint32_t *)(blk + o_new),
+              (uint32_t *)(blk + o_out));
+      };
+      expand(b->o_node_from, N, 1, b->o_base_op, b->o_new_op, o_op);
+      expand(b->o_node_from, N, Dd, b->o_base_dense, b->o_new_dense, o_nd);
+      expand(b->o_edge_from, E, De, b->o_base_feat, b->o_new_feat, o_ef);
+    }
+    HIP_TRY(hipGetLastError());
+    if (!b->mem.pinned) {                // (read while this call runs, or soon after: wait for it)
+      HIP_TRY(hipStreamSynchronize(c->stream));
+      return XRL_OK;
+    }
+    // A pinned block is read after this call returns: an event marks the end of it (and of the kernels
+    // above), which the block's next user waits for, and other contexts that are given the batch.
+    if (b->mem.copied && b->mem.device != c->device) {
+      (void)hipEventDestroy((hipEvent_t)b->mem.copied);
+      b->mem.copied = nullptr;
+    }
+    if (!b->mem.copied) {
+      hipEvent_t ev = nullptr;
+      HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+      b->mem.copied = ev;
+      b->mem.device = c->device;
+    }
+    HIP_TRY(hipEventRecord((hipEvent_t)b->mem.copied, c->stream));
+    return XRL_OK;
   };
-  HIP_TRY(cp(o_sgp, b->state_graph_ptr.data(), (S + 1) * 4));
-  HIP_TRY(cp(o_gnp, b->graph_node_ptr.data(), (G + 1) * 4));
-  if (!ed) HIP_TRY(cp(o_op, b->node_op.data(), N * 4));
-  HIP_TRY(cp(o_inp, b->in_ptr.data(), (N + 1) * 4));
-  if (N > 0) {
-    agg_src_kernel<<<dim3((unsigned)((N + 255) / 256)), dim3(256), 0, c->stream>>>((const int32_t *)(blk + o_inp), N,
-                                                                                  (int32_t *)(blk + o_as));
-    HIP_TRY(hipGetLastError());
+  const int rc = queue();
+  if (rc) {
+    (void)hipStreamSynchronize(c->stream);
+    return rc;
   }
-  HIP_TRY(cp(o_ins, b->in_src.data(), E * 4));
-  HIP_TRY(cp(o_ind, b->in_dst.data(), E * 4));
-  HIP_TRY(cp(o_outp, b->out_ptr.data(), (N + 1) * 4));
-  HIP_TRY(cp(o_outpos, b->out_pos.data(), E * 4));
-  HIP_TRY(cp(o_ng, b->node_graph.data(), N * 4));
-  if (!ed) {
-    HIP_TRY(cp(o_nd, b->node_dense.data(), (size_t)N * Dd * 4));
-    HIP_TRY(cp(o_ef, b->edge_feat.data(), (size_t)E * De * 4));
-  } else {
-    HIP_TRY(cp(o_nf, b->node_from.data(), N * 4));
-    HIP_TRY(cp(o_ef2, b->edge_from.data(), E * 4));
-    HIP_TRY(cp(o_bop, b->base_node_op.data(), b->base_node_op.size() * 4));
-    HIP_TRY(cp(o_nop, b->new_node_op.data(), b->new_node_op.size() * 4));
-    HIP_TRY(cp(o_bnd, b->base_node_dense.data(), b->base_node_dense.size() * 4));
-    HIP_TRY(cp(o_nnd, b->new_node_dense.data(), b->new_node_dense.size() * 4));
-    HIP_TRY(cp(o_bef, b->base_edge_feat.data(), b->base_edge_feat.size() * 4));
-    HIP_TRY(cp(o_nef, b->new_edge_feat.data(), b->new_edge_feat.size() * 4));
-    auto expand = [&](size_t o_from, int64_t n, int width, size_t o_base, size_t o_new, size_t o_out) {
-      const int64_t total = n * width;
-      if (total > 0)
-        expand_rows_kernel<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, c->stream>>>(
-            (const int32_t *)(blk + o_from), n, width, (const uint32_t *)(blk + o_base), (const uint32_t *)(blk + o_new),
-            (uint32_t *)(blk + o_out));
-    };
-    expand(o_nf, N, 1, o_bop, o_nop, o_op);
-    expand(o_nf, N, Dd, o_bnd, o_nnd, o_nd);
-    expand(o_ef2, E, De, o_bef, o_nef, o_ef);
-    HIP_TRY(hipGetLastError());
-  }
-  HIP_TRY(cp(o_gg, b->graph_global.data(), (size_t)G * Dg * 4));
-  HIP_TRY(cp(o_mask, b->mask.data(), G));
-  HIP_TRY(cp(o_tile, b->tile_ptr.data(), b->tile_ptr.size() * 4));
-  HIP_TRY(cp(o_gtile, b->gtile_ptr.data(), b->gtile_ptr.size() * 4));
-  HIP_TRY(cp(o_gtp, b->graph_tile_ptr.data(), b->graph_tile_ptr.size() * 4));
-  HIP_TRY(hipStreamSynchronize(c->stream));
-  d.state_graph_ptr = (int32_t *)(blk + o_sgp);
-  d.graph_node_ptr = (int32_t *)(blk + o_gnp);
+  d.state_graph_ptr = (int32_t *)(blk + b->o_state_graph_ptr);
+  d.graph_node_ptr = (int32_t *)(blk + b->o_graph_node_ptr);
   d.node_op = (int32_t *)(blk + o_op);
-  d.in_ptr = (int32_t *)(blk + o_inp);
-  d.in_src = (int32_t *)(blk + o_ins);
-  d.in_dst = (int32_t *)(blk + o_ind);
-  d.out_ptr = (int32_t *)(blk + o_outp);
-  d.out_pos = (int32_t *)(blk + o_outpos);
-  d.node_graph = (int32_t *)(blk + o_ng);
+  d.in_ptr = (int32_t *)(blk + b->o_in_ptr);
+  d.in_src = (int32_t *)(blk + b->o_in_src);
+  d.in_dst = (int32_t *)(blk + b->o_in_dst);
+  d.out_ptr = (int32_t *)(blk + b->o_out_ptr);
+  d.out_pos = (int32_t *)(blk + b->o_out_pos);
+  d.node_graph = (int32_t *)(blk + b->o_node_graph);
   d.node_dense = (float *)(blk + o_nd);
   d.edge_feat = (float *)(blk + o_ef);
-  d.graph_global = (float *)(blk + o_gg);
-  d.mask = (uint8_t *)(blk + o_mask);
-  d.tile_ptr = (int32_t *)(blk + o_tile);
-  d.gtile_ptr = b->graph_tile_ptr.empty() ? nullptr : (int32_t *)(blk + o_gtile);
-  d.graph_tile_ptr = b->graph_tile_ptr.empty() ? nullptr : (int32_t *)(blk + o_gtp);
+  d.graph_global = (float *)(blk + b->o_graph_global);
+  d.mask = (uint8_t *)(blk + b->o_mask);
+  d.tile_ptr = (int32_t *)(blk + b->o_tile);
+  d.gtile_ptr = b->has_graph_tiles ? (int32_t *)(blk + b->o_gtile) : nullptr;
+  d.graph_tile_ptr = b->has_graph_tiles ? (int32_t *)(blk + b->o_graph_tile) : nullptr;
   d.agg_src = (int32_t *)(blk + o_as);
   b->uploaded = true;
   return XRL_OK;

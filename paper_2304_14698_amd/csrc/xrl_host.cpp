@@ -123,9 +123,13 @@ int pack_thread_count(int64_t work) {
   }
   int hw = (int)std::thread::hardware_concurrency();
   if (hw < 1) hw = 1;
-  if (hw > 16) hw = 16;
-  int64_t t = work / 65536;
-  return (int)(t < 1 ? 1 : (t > hw ? hw : t));
+  // About 4.5 ns per node or edge against 12 us to start a thread: the best number is the square root of
+  // their quotient. Measured, one thread / the best number / what this picks, us: 36 k nodes and edges
+  // 154 / 125 / 125, 152 k 451 / 163 / 163, 620 k 3640 / 822 / 880; at 1.4 M (8.3 / 1.9 / 1.9 ms) eight
+  // threads already take what the memory gives.
+  if (hw > 12) hw = 12;
+  const int t = (int)std::sqrt((double)work / 4096.0);
+  return t < 1 ? 1 : (t > hw ? hw : t);
 }
 
 // graph range boundaries [T + 1], balanced by nodes + edges
@@ -171,66 +175,173 @@ bool run_ranges(const std::vector<int64_t> &cut, F fn) {
   return ok;
 }
 
-// Edge tiles of the message kernels and the per-graph tiles of the one-launch encoder, from the
-// packed in_ptr / graph_node_ptr (serial: a tile boundary depends on the ones before it).
-void build_tile_tables(xrl_batch *b) {
-  const int64_t N = b->N, E = b->E, G = b->G;
-  {  // Edge tiles of the message kernels: consecutive receiver-order edges, at most 32 per tile,
-       // cut at receiver boundaries so that a receiver's in-edges share a tile. Only a receiver
-       // with more than 32 in-edges is split (into full tiles plus a remainder that later
-       // receivers may join); its pieces are recombined by the carry fix-up.
-      b->tile_ptr.clear();
-      b->tile_ptr.push_back(0);
-      b->n_split_tiles = 0;
-      int32_t fill = 0;                 // edges in the open tile
-      for (int64_t n = 0; n < N; ++n) {
-        int32_t d = b->in_ptr[n + 1] - b->in_ptr[n];
-        if (d == 0) continue;
-        if (fill + d > 32 && fill > 0) {
-          b->tile_ptr.push_back(b->in_ptr[n]);
-          fill = 0;
-        }
-        while (d > 32) {                // fill == 0 here
-          b->tile_ptr.push_back(b->tile_ptr.back() + 32);
-          b->n_split_tiles++;
-          d -= 32;
-        }
-        fill += d;
-      }
-      if (fill > 0) b->tile_ptr.push_back((int32_t)E);
+// Edge tiles of the message kernels: consecutive receiver-order edges, at most 32 per tile, cut at
+// receiver boundaries so that a receiver's in-edges share a tile. Only a receiver with more than
+// 32 in-edges is split (into full tiles plus a remainder that later receivers may join); its
+// pieces are recombined by the carry fix-up. cut_tiles goes over the receivers
+// [n0, n1), whose edges begin at `first`, with `fill` edges in the open tile, appends the first edge of
+// every tile it opens and returns the edges in the tile open at the end.
+struct TileCut {
+  std::vector<int32_t> starts;
+  int64_t n_split = 0;
+  int32_t fill = 0;
+};
+int32_t cut_tiles(const int32_t *in_ptr, int64_t n0, int64_t n1, int32_t first, int32_t fill, TileCut &out) {
+  for (int64_t n = n0; n < n1; ++n) {
+    const int32_t end = in_ptr[n + 1];
+    if (first == end) continue;
+    if (fill == 0 || fill + (end - first) > 32) {
+      out.starts.push_back(first);
+      fill = 0;
     }
-    b->max_graph_nodes = 0;
-    for (int64_t g = 0; g < G; ++g)
-      b->max_graph_nodes = std::max(b->max_graph_nodes, b->graph_node_ptr[g + 1] - b->graph_node_ptr[g]);
-    b->gtile_ptr.clear();
-    b->graph_tile_ptr.clear();
+    while (end - first > 32) {          // fill == 0 here
+      first += 32;
+      out.starts.push_back(first);
+      out.n_split++;
+    }
+    fill += end - first;
+    first = end;
+  }
+  return fill;
+}
+
+// Ranges of nodes are cut on separate threads, each as if a tile began with it (spec). The real entry
+// state of a range is known once the ranges before it are joined: they are cut again from there until a
+// tile begins where one of the speculative cut does -- usually a few tiles in -- and from that tile
+// on the two are the same.
+void join_tiles(const int32_t *in_ptr, int64_t n0, int64_t n1, const TileCut &spec, int32_t *tiles, int64_t &nt,
+                int32_t &fill, int64_t &n_split) {
+  size_t k = 0;                          // next speculative start not passed yet
+  for (int64_t n = n0; n < n1; ++n) {
+    const int32_t first = in_ptr[n], end = in_ptr[n + 1];
+    if (first == end) continue;
+    const bool opens = fill == 0 || fill + (end - first) > 32;
+    if (opens) {
+      while (k < spec.starts.size() && spec.starts[k] < first) ++k;
+      if (k < spec.starts.size() && spec.starts[k] == first) {
+        // (a split receiver's pieces begin at its first edge in both, so its splits lie on one side)
+        const size_t rest = spec.starts.size() - k;
+        memcpy(tiles + nt, spec.starts.data() + k, sizeof(int32_t) * rest);
+        nt += (int64_t)rest;
+        for (int64_t q = n; spec.n_split > 0 && q < n1; ++q)
+          if (in_ptr[q + 1] - in_ptr[q] > 32) n_split += (in_ptr[q + 1] - in_ptr[q] - 1) / 32;
+        fill = spec.fill;
+        return;
+      }
+    }
+    TileCut one;
+    fill = cut_tiles(in_ptr, n, n + 1, first, fill, one);
+    for (int32_t st : one.starts) tiles[nt++] = st;
+    n_split += one.n_split;
+  }
+}
+
+inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
+
+// Offsets of the packed arrays; every array is followed by at least 16 bytes of slack (the
+// kernels' 16-byte loads of a last, partial piece). Upper bounds for the tile tables: two neighbouring
+// tiles hold more than 32 edges together.
+struct BlockPlan {
+  size_t off = 0;
+  size_t take(size_t bytes) {
+    const size_t o = off;
+    off += align_up(bytes + 16);
+    return o;
+  }
+};
+bool plan_block(xrl_batch *b, int64_t Nc = 0, int64_t Ec = 0, int64_t n_an = 0, int64_t n_ae = 0) {
+  const size_t S = b->S, G = b->G, N = b->N, E = b->E;
+  const size_t Dd = b->model.n_node_dense, De = b->model.d_edge, Dg = b->model.d_global;
+  const bool ed = b->from_edits;
+  BlockPlan p;
+  b->o_state_graph_ptr = p.take((S + 1) * 4);
+  b->o_graph_node_ptr = p.take((G + 1) * 4);
+  b->o_in_ptr = p.take((N + 1) * 4);
+  b->o_in_src = p.take(E * 4);
+  b->o_in_dst = p.take(E * 4);
+  b->o_out_ptr = p.take((N + 1) * 4);
+  b->o_out_pos = p.take(E * 4);
+  b->o_node_graph = p.take(N * 4);
+  b->o_graph_global = p.take(G * Dg * 4);
+  b->o_mask = p.take(G);
+  if (ed) {
+    b->o_node_from = p.take(N * 4);
+    b->o_edge_from = p.take(E * 4);
+    b->o_base_op = p.take((size_t)Nc * 4);
+    b->o_new_op = p.take((size_t)n_an * 4);
+    b->o_base_dense = p.take((size_t)Nc * Dd * 4);
+    b->o_new_dense = p.take((size_t)n_an * Dd * 4);
+    b->o_base_feat = p.take((size_t)Ec * De * 4);
+    b->o_new_feat = p.take((size_t)n_ae * De * 4);
+  } else {
+    b->o_node_op = p.take(N * 4);
+    b->o_node_dense = p.take(N * Dd * 4);
+    b->o_edge_feat = p.take(E * De * 4);
+  }
+  const bool gt = b->G <= kGraphTileMaxGraphs;
+  b->o_tile = p.take((E / 16 + 4) * 4);
+  b->o_gtile = p.take(gt ? (E / 16 + 2 * G + 4) * 4 : 0);
+  b->o_graph_tile = p.take(gt ? (G + 1) * 4 : 0);
+  b->send_bytes = p.off;
+  b->o_in_eid = p.take(E * 4);
+  b->mem = host_block_take(p.off);
+  return b->mem.p != nullptr;
+}
+
+// What the packing threads find out about their graphs, besides the arrays they write.
+struct RangeTiles {
+  TileCut cut;                           // edge tiles of the range's nodes
+  TileCut graphs;                        // per-graph edge tiles, one graph after the other
+  std::vector<int32_t> graph_end;        // tiles of the range up to and with each of its graphs
+  int32_t max_nodes = 0, max_tiles = 0;
+};
+// (the entries of in_ptr past gnp[g0] are written; that one is another thread's, so its value is given)
+void range_tiles(const int32_t *in_ptr, const int32_t *gnp, int64_t g0, int64_t g1, int32_t first, bool per_graph,
+                 RangeTiles &r) {
+  r.cut.fill = cut_tiles(in_ptr, gnp[g0], gnp[g1], first, 0, r.cut);
+  for (int64_t g = g0; g < g1; ++g) {
+    r.max_nodes = std::max(r.max_nodes, gnp[g + 1] - gnp[g]);
+    if (!per_graph) continue;
+    const size_t before = r.graphs.starts.size();
+    cut_tiles(in_ptr, gnp[g], gnp[g + 1], first, 0, r.graphs);
+    if (gnp[g + 1] > gnp[g]) first = in_ptr[gnp[g + 1]];
+    r.max_tiles = std::max(r.max_tiles, (int32_t)(r.graphs.starts.size() - before));
+    r.graph_end.push_back((int32_t)r.graphs.starts.size());
+  }
+}
+void join_range_tiles(xrl_batch *b, const std::vector<int64_t> &cut, const std::vector<RangeTiles> &rt) {
+  const int32_t *in_ptr = b->at<int32_t>(b->o_in_ptr), *gnp = b->at<int32_t>(b->o_graph_node_ptr);
+  int32_t *tiles = b->at<int32_t>(b->o_tile);
+  int64_t nt = 0;
+  int32_t fill = 0;
+  b->n_split_tiles = 0;
+  for (size_t t = 0; t < rt.size(); ++t)
+    join_tiles(in_ptr, gnp[cut[t]], gnp[cut[t + 1]], rt[t].cut, tiles, nt, fill, b->n_split_tiles);
+  b->n_tiles = nt;
+  if (nt == 0) tiles[0] = 0;             // (no edges: one entry, no tile)
+  else tiles[nt] = (int32_t)b->E;
+  b->max_graph_nodes = 0;
+  b->max_graph_tiles = 0;
+  for (const RangeTiles &r : rt) {
+    b->max_graph_nodes = std::max(b->max_graph_nodes, r.max_nodes);
+    b->max_graph_tiles = std::max(b->max_graph_tiles, r.max_tiles);
+  }
+  b->has_graph_tiles = b->G <= kGraphTileMaxGraphs && b->n_split_tiles == 0;
+  b->n_graph_tiles = 0;
+  if (!b->has_graph_tiles) {
     b->max_graph_tiles = 0;
-    if (G <= kGraphTileMaxGraphs) {   // the same rule graph by graph (see xrl_batch)
-      bool ok = true;
-      b->graph_tile_ptr.push_back(0);
-      for (int64_t g = 0; g < G && ok; ++g) {
-        int32_t fill = 0;
-        const int32_t n1 = b->graph_node_ptr[g + 1];
-        for (int32_t n = b->graph_node_ptr[g]; n < n1; ++n) {
-          const int32_t d = b->in_ptr[n + 1] - b->in_ptr[n];
-          if (d == 0) continue;
-          if (d > 32) { ok = false; break; }
-          if (fill + d > 32 || fill == 0) {
-            b->gtile_ptr.push_back(b->in_ptr[n]);
-            fill = 0;
-          }
-          fill += d;
-        }
-        b->max_graph_tiles = std::max(b->max_graph_tiles, (int32_t)b->gtile_ptr.size() - b->graph_tile_ptr.back());
-        b->graph_tile_ptr.push_back((int32_t)b->gtile_ptr.size());
-      }
-      if (ok) {
-        b->gtile_ptr.push_back((int32_t)E);
-      } else {
-        b->gtile_ptr.clear();
-        b->graph_tile_ptr.clear();
-      }
-    }
+    return;
+  }
+  int32_t *gt = b->at<int32_t>(b->o_gtile), *gtp = b->at<int32_t>(b->o_graph_tile);
+  int64_t n = 0, g = 0;
+  gtp[g++] = 0;
+  for (const RangeTiles &r : rt) {
+    if (!r.graphs.starts.empty()) memcpy(gt + n, r.graphs.starts.data(), sizeof(int32_t) * r.graphs.starts.size());
+    for (int32_t e : r.graph_end) gtp[g++] = (int32_t)n + e;
+    n += (int64_t)r.graphs.starts.size();
+  }
+  b->n_graph_tiles = n;
+  gt[n] = (int32_t)b->E;
 }
 }  // namespace
 
@@ -283,12 +394,31 @@ static int check_ptr(const int32_t *p, int64_t n, const char *what) {
 }
 
 static bool all_finite(const float *p, int64_t n, int64_t *where) {
-  for (int64_t i = 0; i < n; ++i)
-    if (!std::isfinite(p[i])) {
-      *where = i;
-      return false;
+  constexpr int64_t kPiece = 4096;                   // (no early exit inside a piece: vector code)
+  for (int64_t i = 0; i < n; i += kPiece) {
+    const int64_t k = std::min(kPiece, n - i);
+    uint32_t bad = 0;
+    for (int64_t j = 0; j < k; ++j) {
+      uint32_t u;
+      memcpy(&u, p + i + j, 4);
+      bad |= (uint32_t)((u & 0x7f800000u) == 0x7f800000u);
     }
+    if (!bad) continue;
+    *where = i;
+    while (std::isfinite(p[*where])) ++*where;
+    return false;
+  }
   return true;
+}
+
+// The first of n operator ids outside [0, limit), or n.
+static int64_t first_outside(const int32_t *p, int64_t n, int32_t limit) {
+  uint32_t bad = 0;
+  for (int64_t i = 0; i < n; ++i) bad |= (uint32_t)((uint32_t)p[i] >= (uint32_t)limit);
+  if (!bad) return n;
+  int64_t i = 0;
+  while ((uint32_t)p[i] < (uint32_t)limit) ++i;
+  return i;
 }
 
 int xrl_pack_state(const xrl_model_desc *model, const xrl_state_desc *st, xrl_batch **out) {
@@ -317,107 +447,116 @@ int xrl_pack_state(const xrl_model_desc *model, const xrl_state_desc *st, xrl_ba
   for (int64_t s = 0; s < S; ++s)
     if (st->slot_mask[st->state_graph_ptr[s]] == 0)
       return fail(XRL_ERR_MASK, "state %lld masks its No-Op slot (its first graph)", (long long)s);
-  // per-range checks, reported in the order a serial pass would find them: operator ids, edge
-  // endpoints, node attributes, edge attributes; within a kind, the lowest range first
-  const int T = pack_thread_count(N + E);
-  const std::vector<int64_t> cut = graph_ranges(st, G, T);
-  {
+  xrl_batch *b = new (std::nothrow) xrl_batch();
+  if (!b) return fail(XRL_ERR_OOM, "xrl_pack_state: out of host memory");
+  // One pass of the packing threads over their graphs. Checks first, reported in the order a serial pass
+  // would find them: operator ids, edge endpoints, node attributes, edge attributes; within a
+  // kind, the lowest range first.
+  try {
+    static std::atomic<uint64_t> next_id{1};
+    b->id = next_id++;
+    b->model = *model;
+    b->S = S; b->G = G; b->N = N; b->E = E;
+    if (!plan_block(b)) throw std::bad_alloc();
+    int32_t *gnp = b->at<int32_t>(b->o_graph_node_ptr), *in_ptr = b->at<int32_t>(b->o_in_ptr), *out_ptr = b->at<int32_t>(b->o_out_ptr);
+    int32_t *node_op = b->at<int32_t>(b->o_node_op), *node_graph = b->at<int32_t>(b->o_node_graph);
+    int32_t *in_src = b->at<int32_t>(b->o_in_src), *in_dst = b->at<int32_t>(b->o_in_dst), *in_eid = b->at<int32_t>(b->o_in_eid);
+    int32_t *out_pos = b->at<int32_t>(b->o_out_pos);
+    float *node_dense = b->at<float>(b->o_node_dense), *edge_feat = b->at<float>(b->o_edge_feat);
+    memcpy(b->at<int32_t>(b->o_state_graph_ptr), st->state_graph_ptr, sizeof(int32_t) * (S + 1));
+    memcpy(gnp, st->graph_node_ptr, sizeof(int32_t) * (G + 1));
+    in_ptr[0] = out_ptr[0] = 0;
+    const int T = pack_thread_count(N + E);
+    const std::vector<int64_t> cut = graph_ranges(st, G, T);
     std::vector<PackIssue> issue((size_t)4 * T);
-    const bool ok = run_ranges(cut, [&](int t, int64_t g0, int64_t g1) {
+    std::vector<RangeTiles> rt(T);
+    const bool done = run_ranges(cut, [&](int t, int64_t g0, int64_t g1) {
       const int64_t n0 = st->graph_node_ptr[g0], n1 = st->graph_node_ptr[g1];
       const int64_t e0 = st->graph_edge_ptr[g0], e1 = st->graph_edge_ptr[g1];
-      for (int64_t i = n0; i < n1; ++i)
-        if (st->node_op[i] < 0 || st->node_op[i] >= model->n_op_types) {
-          issue[0 * T + t].set(XRL_ERR_INDEX, "node %lld: op id %d outside [0, %d)", (long long)i,
-                               st->node_op[i], model->n_op_types);
-          break;
-        }
+      const int64_t op = n1 > n0 ? n0 + first_outside(st->node_op + n0, n1 - n0, model->n_op_types) : n1;
+      if (op < n1)
+        issue[0 * T + t].set(XRL_ERR_INDEX, "node %lld: op id %d outside [0, %d)", (long long)op, st->node_op[op],
+                             model->n_op_types);
       for (int64_t g = g0; g < g1 && !issue[1 * T + t].code; ++g) {
         const int32_t n = st->graph_node_ptr[g + 1] - st->graph_node_ptr[g];
-        for (int64_t e = st->graph_edge_ptr[g]; e < st->graph_edge_ptr[g + 1]; ++e)
-          if (st->edge_src[e] < 0 || st->edge_src[e] >= n || st->edge_dst[e] < 0 || st->edge_dst[e] >= n) {
-            issue[1 * T + t].set(XRL_ERR_INDEX, "edge %lld of graph %lld: endpoint (%d -> %d) outside [0, %d)",
-                                 (long long)e, (long long)g, st->edge_src[e], st->edge_dst[e], n);
-            break;
-          }
+        const int64_t a = st->graph_edge_ptr[g], z = st->graph_edge_ptr[g + 1];
+        if (a == z) continue;
+        const int64_t e = a + std::min(first_outside(st->edge_src + a, z - a, n), first_outside(st->edge_dst + a, z - a, n));
+        if (e < z)
+          issue[1 * T + t].set(XRL_ERR_INDEX, "edge %lld of graph %lld: endpoint (%d -> %d) outside [0, %d)",
+                               (long long)e, (long long)g, st->edge_src[e], st->edge_dst[e], n);
       }
       int64_t where = 0;
       if (Dd > 0 && !all_finite(st->node_dense + n0 * Dd, (n1 - n0) * Dd, &where))
         issue[2 * T + t].set(XRL_ERR_VALUE, "node_dense[%lld] is not finite", (long long)(n0 * Dd + where));
       if (!all_finite(st->edge_feat + e0 * De, (e1 - e0) * De, &where))
         issue[3 * T + t].set(XRL_ERR_VALUE, "edge_feat[%lld] is not finite", (long long)(e0 * De + where));
-    });
-    if (!ok) return fail(XRL_ERR_OOM, "xrl_pack_state: out of host memory");
-    for (const PackIssue &is : issue)
-      if (is.code) return fail(is.code, "%s", is.msg);
-  }
-  int64_t bad = 0;
-  if (st->graph_global && !all_finite(st->graph_global, G * Dg, &bad))
-    return fail(XRL_ERR_VALUE, "graph_global[%lld] is not finite", (long long)bad);
-
-  xrl_batch *b = new (std::nothrow) xrl_batch();
-  if (!b) return fail(XRL_ERR_OOM, "xrl_pack_state: out of host memory");
-  try {
-    static std::atomic<uint64_t> next_id{1};
-    b->id = next_id++;
-    b->model = *model;
-    b->S = S; b->G = G; b->N = N; b->E = E;
-    b->state_graph_ptr.assign(st->state_graph_ptr, st->state_graph_ptr + S + 1);
-    b->graph_node_ptr.assign(st->graph_node_ptr, st->graph_node_ptr + G + 1);
-    b->node_op.resize(N);                            // (copied by the packing threads below)
-    b->node_dense.resize(Dd > 0 ? (size_t)N * Dd : 0);
-    b->mask.resize(G);
-    for (int64_t g = 0; g < G; ++g) b->mask[g] = st->slot_mask[g] ? 1 : 0;
-    if (st->graph_global)
-      b->graph_global.assign(st->graph_global, st->graph_global + G * Dg);
-    else
-      b->graph_global.assign((size_t)(G * Dg), 0.0f);
-    for (int64_t s = 0; s < S; ++s) {
-      int32_t c = st->state_graph_ptr[s + 1] - st->state_graph_ptr[s];
-      if (c > b->max_slots) b->max_slots = c;
-    }
-    b->node_graph.resize(N);
-    b->in_ptr.assign(N + 1, 0);
-    b->out_ptr.assign(N + 1, 0);
-    b->in_src.resize(E); b->in_dst.resize(E); b->in_eid.resize(E); b->out_pos.resize(E);
-    b->edge_feat.resize((size_t)E * De);
-    // Receiver order: stable counting sort of each graph's edges by receiver; then the sender-side
-    // index (receiver-order positions grouped by sender, ascending position). A graph's edges
-    // keep the index range they came with, so the graph ranges are independent.
-    const bool sorted = run_ranges(cut, [&](int, int64_t g0, int64_t g1) {
+      for (int k = 0; k < 4; ++k)
+        if (issue[k * T + t].code) return;
+      if (n1 > n0) {
+        memcpy(node_op + n0, st->node_op + n0, sizeof(int32_t) * (n1 - n0));
+        if (Dd > 0) memcpy(node_dense + n0 * Dd, st->node_dense + n0 * Dd, sizeof(float) * (n1 - n0) * Dd);
+        memset(in_ptr + n0 + 1, 0, sizeof(int32_t) * (n1 - n0));
+        memset(out_ptr + n0 + 1, 0, sizeof(int32_t) * (n1 - n0));
+      }
+      // Receiver order: stable counting sort of each graph's edges by receiver; then the sender-side
+      // index (receiver-order positions grouped by sender, ascending position). A graph's edges
+      // keep the index range they came with, so the graph ranges are independent.
       std::vector<int32_t> cur;
       for (int64_t g = g0; g < g1; ++g) {
         const int32_t base = st->graph_node_ptr[g], n = st->graph_node_ptr[g + 1] - base;
-        const int64_t e0 = st->graph_edge_ptr[g], e1 = st->graph_edge_ptr[g + 1];
-        for (int32_t i = 0; i < n; ++i) b->node_graph[base + i] = (int32_t)g;
-        if (n > 0) {
-          memcpy(&b->node_op[base], st->node_op + base, sizeof(int32_t) * n);
-          if (Dd > 0) memcpy(&b->node_dense[(size_t)base * Dd], st->node_dense + (size_t)base * Dd, sizeof(float) * n * Dd);
-        }
-        int32_t *inp = b->in_ptr.data() + base + 1, *outp = b->out_ptr.data() + base + 1;   // counts, then ends
-        for (int64_t e = e0; e < e1; ++e) {
+        const int64_t a = st->graph_edge_ptr[g], z = st->graph_edge_ptr[g + 1];
+        for (int32_t i = 0; i < n; ++i) node_graph[base + i] = (int32_t)g;
+        int32_t *inp = in_ptr + base + 1, *outp = out_ptr + base + 1;   // counts, then ends
+        for (int64_t e = a; e < z; ++e) {
           inp[st->edge_dst[e]]++;
           outp[st->edge_src[e]]++;
         }
-        cur.assign((size_t)2 * n, 0);
-        int32_t ri = (int32_t)e0, ro = (int32_t)e0;
+        if (cur.size() < (size_t)2 * n) cur.resize((size_t)2 * n);
+        int32_t ri = (int32_t)a, ro = (int32_t)a;
         for (int32_t i = 0; i < n; ++i) {
           cur[i] = ri; cur[n + i] = ro;                   // first position of node i's in- / out-edges
           ri += inp[i]; ro += outp[i];
           inp[i] = ri; outp[i] = ro;
         }
-        for (int64_t e = e0; e < e1; ++e) {
-          const int32_t p = cur[st->edge_dst[e]]++;
-          b->in_src[p] = base + st->edge_src[e];
-          b->in_dst[p] = base + st->edge_dst[e];
-          b->in_eid[p] = (int32_t)e;
-          memcpy(&b->edge_feat[(size_t)p * De], &st->edge_feat[(size_t)e * De], sizeof(float) * De);
-        }
-        for (int64_t p = e0; p < e1; ++p) b->out_pos[cur[n + (b->in_src[p] - base)]++] = (int32_t)p;
+        auto place = [&](auto width) {
+          constexpr size_t kRow = sizeof(float) * decltype(width)::value;      // 0: any width
+          for (int64_t e = a; e < z; ++e) {
+            const int32_t p = cur[st->edge_dst[e]]++;
+            in_src[p] = base + st->edge_src[e];
+            in_dst[p] = base + st->edge_dst[e];
+            in_eid[p] = (int32_t)e;
+            memcpy(edge_feat + (size_t)p * De, st->edge_feat + (size_t)e * De, kRow ? kRow : sizeof(float) * De);
+          }
+        };
+        if (De == 8) place(std::integral_constant<int, 8>());
+        else if (De == 4) place(std::integral_constant<int, 4>());
+        else place(std::integral_constant<int, 0>());
+        for (int64_t p = a; p < z; ++p) out_pos[cur[n + (in_src[p] - base)]++] = (int32_t)p;
       }
+      range_tiles(in_ptr, gnp, g0, g1, (int32_t)e0, G <= kGraphTileMaxGraphs, rt[t]);
     });
-    if (!sorted) throw std::bad_alloc();
-    build_tile_tables(b);
+    if (!done) throw std::bad_alloc();
+    int code = 0;
+    for (const PackIssue &is : issue)
+      if (is.code && !code) code = fail(is.code, "%s", is.msg);
+    int64_t bad = 0;
+    if (!code && st->graph_global && !all_finite(st->graph_global, G * Dg, &bad))
+      code = fail(XRL_ERR_VALUE, "graph_global[%lld] is not finite", (long long)bad);
+    if (code) {
+      delete b;
+      return code;
+    }
+    uint8_t *mask = b->at<uint8_t>(b->o_mask);
+    for (int64_t g = 0; g < G; ++g) mask[g] = st->slot_mask[g] ? 1 : 0;
+    float *gg = b->at<float>(b->o_graph_global);
+    if (st->graph_global && G * Dg > 0) memcpy(gg, st->graph_global, sizeof(float) * G * Dg);
+    else memset(gg, 0, sizeof(float) * (size_t)(G * Dg));
+    for (int64_t s = 0; s < S; ++s) {
+      int32_t c = st->state_graph_ptr[s + 1] - st->state_graph_ptr[s];
+      if (c > b->max_slots) b->max_slots = c;
+    }
+    join_range_tiles(b, cut, rt);
   } catch (const std::bad_alloc &) {
     delete b;
     return fail(XRL_ERR_OOM, "xrl_pack_state: out of host memory");
@@ -465,12 +604,10 @@ int xrl_pack_state_edits(const xrl_model_desc *model, const xrl_edit_state_desc 
   for (int64_t s = 0; s < S; ++s)
     if (st->slot_mask[sgp[s]] == 0) return fail(XRL_ERR_MASK, "state %lld masks its No-Op slot (its first graph)", (long long)s);
   // ---- the current graphs and the new items (what is validated; everything else is copied from them)
-  for (int64_t i = 0; i < Nc; ++i)
-    if (st->node_op[i] < 0 || st->node_op[i] >= model->n_op_types)
-      return fail(XRL_ERR_INDEX, "node %lld: op id %d outside [0, %d)", (long long)i, st->node_op[i], model->n_op_types);
-  for (int64_t i = 0; i < n_an; ++i)
-    if (st->add_node_op[i] < 0 || st->add_node_op[i] >= model->n_op_types)
-      return fail(XRL_ERR_INDEX, "new node %lld: op id %d outside [0, %d)", (long long)i, st->add_node_op[i], model->n_op_types);
+  const int64_t op = first_outside(st->node_op, Nc, model->n_op_types), new_op = first_outside(st->add_node_op, n_an, model->n_op_types);
+  if (op < Nc) return fail(XRL_ERR_INDEX, "node %lld: op id %d outside [0, %d)", (long long)op, st->node_op[op], model->n_op_types);
+  if (new_op < n_an)
+    return fail(XRL_ERR_INDEX, "new node %lld: op id %d outside [0, %d)", (long long)new_op, st->add_node_op[new_op], model->n_op_types);
   for (int64_t s = 0; s < S; ++s) {
     const int32_t n = st->cur_node_ptr[s + 1] - st->cur_node_ptr[s];
     for (int64_t e = st->cur_edge_ptr[s]; e < st->cur_edge_ptr[s + 1]; ++e)
@@ -484,40 +621,63 @@ int xrl_pack_state_edits(const xrl_model_desc *model, const xrl_edit_state_desc 
   if (!all_finite(st->edge_feat, Ec * De, &where)) return fail(XRL_ERR_VALUE, "edge_feat[%lld] is not finite", (long long)where);
   if (!all_finite(st->add_edge_feat, n_ae * De, &where)) return fail(XRL_ERR_VALUE, "add_edge_feat[%lld] is not finite", (long long)where);
   if (st->graph_global && !all_finite(st->graph_global, G * Dg, &where)) return fail(XRL_ERR_VALUE, "graph_global[%lld] is not finite", (long long)where);
-  // ---- the edits, and the size of every graph
+  // ---- the current graph of every state in receiver order once: its in-edge lists (edge ids
+  // ascending inside a receiver's list, i.e. the stable order); and its out-edge lists
+  std::vector<int32_t> bin_ptr(Nc + S + 1, 0), bin_eid(Ec), bout_ptr(Nc + S + 1, 0), bout_eid(Ec), cursor;
+  for (int64_t s = 0; s < S; ++s) {
+    const int32_t nb = st->cur_node_ptr[s], n = st->cur_node_ptr[s + 1] - nb;
+    const int64_t e0 = st->cur_edge_ptr[s], e1 = st->cur_edge_ptr[s + 1];
+    auto lists = [&](const int32_t *end, int32_t *ip, int32_t *eid) {      // ip: [n + 1] of this state
+      for (int64_t e = e0; e < e1; ++e) ip[end[e] + 1]++;
+      for (int32_t i = 0; i < n; ++i) ip[i + 1] += ip[i];
+      cursor.assign(ip, ip + n);
+      for (int64_t e = e0; e < e1; ++e) eid[e0 + cursor[end[e]]++] = (int32_t)(e - e0);
+    };
+    lists(st->edge_dst, bin_ptr.data() + nb + s, bin_eid.data());
+    lists(st->edge_src, bout_ptr.data() + nb + s, bout_eid.data());
+  }
+  // ---- the edits, and the size of every graph: an edge is gone if it is deleted or at a deleted node,
+  // so only the lists of the deleted nodes are gone over
   std::vector<int32_t> gnp(G + 1, 0), gep(G + 1, 0);
   {
-    std::vector<uint8_t> dead;                     // per node of the state's current graph
+    int32_t n_max = 0;
+    for (int64_t s = 0; s < S; ++s) n_max = std::max(n_max, st->cur_node_ptr[s + 1] - st->cur_node_ptr[s]);
+    std::vector<uint8_t> dead(n_max, 0);           // per node of the state's current graph; cleared after each candidate
     for (int64_t g = 0; g < G; ++g) {
       const int64_t s = g_state[g];
       const int32_t n = st->cur_node_ptr[s + 1] - st->cur_node_ptr[s];
       const int64_t e0 = st->cur_edge_ptr[s], e1 = st->cur_edge_ptr[s + 1];
       if (g_cand[g] < 0) { gnp[g + 1] = n; gep[g + 1] = (int32_t)(e1 - e0); continue; }
       const int64_t c = g_cand[g];
-      dead.assign(n, 0);
       for (int32_t k = st->del_node_ptr[c]; k < st->del_node_ptr[c + 1]; ++k) {
         const int32_t v = st->del_node[k];
         if (v < 0 || v >= n || (k > st->del_node_ptr[c] && v <= st->del_node[k - 1]))
           return fail(XRL_ERR_INDEX, "candidate %lld: del_node[%d] = %d out of range or not ascending", (long long)c, k, v);
         dead[v] = 1;
       }
-      int32_t kept = 0;
-      int32_t kd = st->del_edge_ptr[c];
-      const int32_t kd1 = st->del_edge_ptr[c + 1];
+      const int32_t kd = st->del_edge_ptr[c], kd1 = st->del_edge_ptr[c + 1];
+      int32_t kept = (int32_t)(e1 - e0) - (kd1 - kd);
       for (int32_t k = kd; k < kd1; ++k) {
         const int32_t v = st->del_edge[k];
         if (v < 0 || v >= e1 - e0 || (k > kd && v <= st->del_edge[k - 1]))
           return fail(XRL_ERR_INDEX, "candidate %lld: del_edge[%d] = %d out of range or not ascending", (long long)c, k, v);
       }
-      for (int64_t e = e0; e < e1; ++e) {
-        if (kd < kd1 && st->del_edge[kd] == e - e0) { ++kd; continue; }
-        if (!dead[st->edge_src[e]] && !dead[st->edge_dst[e]]) ++kept;
+      const int32_t *ip = bin_ptr.data() + st->cur_node_ptr[s] + s, *op = bout_ptr.data() + st->cur_node_ptr[s] + s;
+      auto deleted = [&](int32_t el) { return kd < kd1 && std::binary_search(st->del_edge + kd, st->del_edge + kd1, el); };
+      for (int32_t k = st->del_node_ptr[c]; k < st->del_node_ptr[c + 1]; ++k) {
+        const int32_t v = st->del_node[k];
+        for (int32_t q = ip[v]; q < ip[v + 1]; ++q) kept -= !deleted(bin_eid[e0 + q]);
+        for (int32_t q = op[v]; q < op[v + 1]; ++q) {
+          const int32_t el = bout_eid[e0 + q];
+          kept -= !dead[st->edge_dst[e0 + el]] && !deleted(el);    // (else counted above)
+        }
       }
       const int32_t n_new = st->add_node_ptr[c + 1] - st->add_node_ptr[c];
       for (int32_t k = st->add_edge_ptr[c]; k < st->add_edge_ptr[c + 1]; ++k)
         for (const int32_t v : {st->add_edge_src[k], st->add_edge_dst[k]})
           if (v < 0 || v >= n + n_new || (v < n && dead[v]))
             return fail(XRL_ERR_INDEX, "candidate %lld: new edge %d has endpoint %d outside its graph or on a deleted node", (long long)c, k, v);
+      for (int32_t k = st->del_node_ptr[c]; k < st->del_node_ptr[c + 1]; ++k) dead[st->del_node[k]] = 0;
       gnp[g + 1] = n - (st->del_node_ptr[c + 1] - st->del_node_ptr[c]) + n_new;
       gep[g + 1] = kept + (st->add_edge_ptr[c + 1] - st->add_edge_ptr[c]);
     }
@@ -538,37 +698,31 @@ int xrl_pack_state_edits(const xrl_model_desc *model, const xrl_edit_state_desc 
     b->model = *model;
     b->S = S; b->G = G; b->N = N; b->E = E;
     b->from_edits = true;
-    b->state_graph_ptr = sgp;
-    b->graph_node_ptr = gnp;
-    b->mask.resize(G);
-    for (int64_t g = 0; g < G; ++g) b->mask[g] = st->slot_mask[g] ? 1 : 0;
-    if (st->graph_global) b->graph_global.assign(st->graph_global, st->graph_global + G * Dg);
-    else b->graph_global.assign((size_t)(G * Dg), 0.0f);
+    if (!plan_block(b, Nc, Ec, n_an, n_ae)) throw std::bad_alloc();
+    memcpy(b->at<int32_t>(b->o_state_graph_ptr), sgp.data(), sizeof(int32_t) * (S + 1));
+    memcpy(b->at<int32_t>(b->o_graph_node_ptr), gnp.data(), sizeof(int32_t) * (G + 1));
+    uint8_t *mask = b->at<uint8_t>(b->o_mask);
+    for (int64_t g = 0; g < G; ++g) mask[g] = st->slot_mask[g] ? 1 : 0;
+    float *gg = b->at<float>(b->o_graph_global);
+    if (st->graph_global && G * Dg > 0) memcpy(gg, st->graph_global, sizeof(float) * G * Dg);
+    else memset(gg, 0, sizeof(float) * (size_t)(G * Dg));
     for (int64_t s = 0; s < S; ++s) b->max_slots = std::max(b->max_slots, sgp[s + 1] - sgp[s]);
     // (node_op, node_dense and edge_feat of the batch are not written here: the device fills its
-    // copies from node_from / edge_from, and xrl_batch_host_view fills the host's on demand)
-    b->node_graph.resize(N);
-    b->in_ptr.assign(N + 1, 0); b->out_ptr.assign(N + 1, 0);
-    b->in_src.resize(E); b->in_dst.resize(E); b->in_eid.resize(E); b->out_pos.resize(E);
-    b->node_from.resize(N); b->edge_from.resize(E);
-    b->base_node_op.assign(st->node_op, st->node_op + Nc);
-    b->base_node_dense.assign(st->node_dense, st->node_dense + (Dd > 0 ? Nc * Dd : 0));
-    b->base_edge_feat.assign(st->edge_feat, st->edge_feat + Ec * De);
-    b->new_node_op.assign(st->add_node_op, st->add_node_op + n_an);
-    b->new_node_dense.assign(st->add_node_dense, st->add_node_dense + (Dd > 0 ? n_an * Dd : 0));
-    b->new_edge_feat.assign(st->add_edge_feat, st->add_edge_feat + n_ae * De);
-    // ---- the current graph of every state in receiver order once: its in-edge lists (edge ids
-    // ascending inside a receiver's list, i.e. the stable order)
-    std::vector<int32_t> bin_ptr(Nc + S + 1, 0), bin_eid(Ec);
-    for (int64_t s = 0; s < S; ++s) {
-      const int32_t nb = st->cur_node_ptr[s], n = st->cur_node_ptr[s + 1] - nb;
-      const int64_t e0 = st->cur_edge_ptr[s], e1 = st->cur_edge_ptr[s + 1];
-      int32_t *ip = bin_ptr.data() + nb + s;          // [n + 1] of this state
-      for (int64_t e = e0; e < e1; ++e) ip[st->edge_dst[e] + 1]++;
-      for (int32_t i = 0; i < n; ++i) ip[i + 1] += ip[i];
-      std::vector<int32_t> cur(ip, ip + n);
-      for (int64_t e = e0; e < e1; ++e) bin_eid[e0 + cur[st->edge_dst[e]]++] = (int32_t)(e - e0);
-    }
+    // copies from node_from / edge_from, and xrl_batch_host_view writes edge_feat on demand)
+    int32_t *in_ptr = b->at<int32_t>(b->o_in_ptr), *out_ptr = b->at<int32_t>(b->o_out_ptr);
+    int32_t *node_graph = b->at<int32_t>(b->o_node_graph), *out_pos = b->at<int32_t>(b->o_out_pos);
+    int32_t *in_src = b->at<int32_t>(b->o_in_src), *in_dst = b->at<int32_t>(b->o_in_dst), *in_eid = b->at<int32_t>(b->o_in_eid);
+    int32_t *node_from = b->at<int32_t>(b->o_node_from), *edge_from = b->at<int32_t>(b->o_edge_from);
+    in_ptr[0] = out_ptr[0] = 0;
+    auto put = [&](size_t off, const void *src, int64_t bytes) {
+      if (bytes > 0) memcpy(b->mem.p + off, src, (size_t)bytes);
+    };
+    put(b->o_base_op, st->node_op, Nc * 4);
+    put(b->o_base_dense, st->node_dense, Nc * Dd * 4);
+    put(b->o_base_feat, st->edge_feat, Ec * De * 4);
+    put(b->o_new_op, st->add_node_op, n_an * 4);
+    put(b->o_new_dense, st->add_node_dense, n_an * Dd * 4);
+    put(b->o_new_feat, st->add_edge_feat, n_ae * De * 4);
     // ---- every graph by merging; graph ranges on separate threads
     const int T = pack_thread_count(N + E);
     std::vector<int64_t> cut(T + 1, G);
@@ -578,7 +732,8 @@ int xrl_pack_state_edits(const xrl_model_desc *model, const xrl_edit_state_desc 
       while (g < G && (int64_t)gnp[g] + gep[g] < want) ++g;
       cut[t] = g;
     }
-    const bool merged = run_ranges(cut, [&](int, int64_t g0, int64_t g1) {
+    std::vector<RangeTiles> rt(T);
+    const bool merged = run_ranges(cut, [&](int t, int64_t g0, int64_t g1) {
       std::vector<int32_t> newid, erank, cur, add_order;
       std::vector<uint8_t> dead;
       for (int64_t g = g0; g < g1; ++g) {
@@ -618,17 +773,17 @@ int xrl_pack_state_edits(const xrl_model_desc *model, const xrl_edit_state_desc 
         for (int32_t i = 0; i < n; ++i) {
           if (dead[i]) continue;
           const int32_t v = base + newid[i];
-          b->node_graph[v] = (int32_t)g;
-          b->node_from[v] = nb + i;
+          node_graph[v] = (int32_t)g;
+          node_from[v] = nb + i;
         }
         for (int32_t k = 0; k < n_new; ++k) {
           const int32_t v = base + nk + k;
-          b->node_graph[v] = (int32_t)g;
-          b->node_from[v] = -1 - (an0 + k);
+          node_graph[v] = (int32_t)g;
+          node_from[v] = -1 - (an0 + k);
         }
         // receiver order: per receiver its surviving in-edges (edge ids ascending), then its new ones
         int32_t p = eb, ka = 0;
-        int32_t *inp = b->in_ptr.data() + base + 1, *outp = b->out_ptr.data() + base + 1;
+        int32_t *inp = in_ptr + base + 1, *outp = out_ptr + base + 1;
         int32_t vcur = 0;
         for (int32_t i = 0; i < n + n_new; ++i) {
           if (i < n && dead[i]) continue;
@@ -638,34 +793,35 @@ int xrl_pack_state_edits(const xrl_model_desc *model, const xrl_edit_state_desc 
               const int32_t el = bin_eid[e0 + q];
               if (erank[el] < 0) continue;
               const int64_t e = e0 + el;
-              b->in_src[p] = base + newid[st->edge_src[e]];
-              b->in_dst[p] = base + v;
-              b->in_eid[p] = eb + erank[el];
-              b->edge_from[p] = (int32_t)e;
+              in_src[p] = base + newid[st->edge_src[e]];
+              in_dst[p] = base + v;
+              in_eid[p] = eb + erank[el];
+              edge_from[p] = (int32_t)e;
               ++p;
             }
           }
           for (; ka < n_ae_c && newid[st->add_edge_dst[ae0 + add_order[ka]]] == v; ++ka) {
             const int32_t k = ae0 + add_order[ka];
-            b->in_src[p] = base + newid[st->add_edge_src[k]];
-            b->in_dst[p] = base + v;
-            b->in_eid[p] = eb + ek + add_order[ka];
-            b->edge_from[p] = -1 - k;
+            in_src[p] = base + newid[st->add_edge_src[k]];
+            in_dst[p] = base + v;
+            in_eid[p] = eb + ek + add_order[ka];
+            edge_from[p] = -1 - k;
             ++p;
           }
           inp[v] = p;                                // end of v's in-edges
         }
         // sender-side index: receiver-order positions grouped by sender, ascending position
         for (int32_t v = 0; v < ng; ++v) outp[v] = 0;
-        for (int32_t q = eb; q < p; ++q) outp[b->in_src[q] - base]++;
+        for (int32_t q = eb; q < p; ++q) outp[in_src[q] - base]++;
         cur.assign(ng, 0);
         int32_t ro = eb;
         for (int32_t v = 0; v < ng; ++v) { cur[v] = ro; ro += outp[v]; outp[v] = ro; }
-        for (int32_t q = eb; q < p; ++q) b->out_pos[cur[b->in_src[q] - base]++] = q;
+        for (int32_t q = eb; q < p; ++q) out_pos[cur[in_src[q] - base]++] = q;
       }
+      range_tiles(in_ptr, gnp.data(), g0, g1, gep[g0], G <= kGraphTileMaxGraphs, rt[t]);
     });
     if (!merged) throw std::bad_alloc();
-    build_tile_tables(b);
+    join_range_tiles(b, cut, rt);
   } catch (const std::bad_alloc &) {
     delete b;
     return fail(XRL_ERR_OOM, "xrl_pack_state_edits: out of host memory");
@@ -709,36 +865,39 @@ int xrl_batch_dims(const xrl_batch *b, int64_t *S, int64_t *G, int64_t *N, int64
 int xrl_batch_host_view(const xrl_batch *cb, xrl_packed_view *v) {
   if (!cb || !v) return fail(XRL_ERR_NULL, "xrl_batch_host_view: NULL argument");
   xrl_batch *b = const_cast<xrl_batch *>(cb);
-  if (b->from_edits && b->edge_feat.size() != (size_t)b->E * b->model.d_edge) {
+  const int De = b->model.d_edge;
+  const float *edge_feat = b->from_edits ? b->view_edge_feat.data() : b->at<float>(b->o_edge_feat);
+  if (b->from_edits && b->view_edge_feat.size() != (size_t)b->E * De) {
     // packed from edits: the per-edge attribute rows are written out on first request
-    const int De = b->model.d_edge;
     try {
-      b->edge_feat.resize((size_t)b->E * De);
+      b->view_edge_feat.resize((size_t)b->E * De);
     } catch (const std::bad_alloc &) {
       return fail(XRL_ERR_OOM, "xrl_batch_host_view: out of host memory");
     }
+    const int32_t *edge_from = b->at<int32_t>(b->o_edge_from);
     for (int64_t p = 0; p < b->E; ++p) {
-      const int32_t f = b->edge_from[p];
-      const float *src = f >= 0 ? &b->base_edge_feat[(size_t)f * De] : &b->new_edge_feat[(size_t)(-1 - f) * De];
-      memcpy(&b->edge_feat[(size_t)p * De], src, sizeof(float) * De);
+      const int32_t f = edge_from[p];
+      const float *src = f >= 0 ? b->at<float>(b->o_base_feat) + (size_t)f * De : b->at<float>(b->o_new_feat) + (size_t)(-1 - f) * De;
+      memcpy(&b->view_edge_feat[(size_t)p * De], src, sizeof(float) * De);
     }
+    edge_feat = b->view_edge_feat.data();
   }
   v->S = b->S; v->G = b->G; v->N = b->N; v->E = b->E;
-  v->state_graph_ptr = b->state_graph_ptr.data();
-  v->graph_node_ptr = b->graph_node_ptr.data();
-  v->in_ptr = b->in_ptr.data();
-  v->in_src = b->in_src.data();
-  v->in_dst = b->in_dst.data();
-  v->in_eid = b->in_eid.data();
-  v->out_ptr = b->out_ptr.data();
-  v->out_pos = b->out_pos.data();
-  v->node_graph = b->node_graph.data();
-  v->edge_feat = b->edge_feat.data();
-  v->n_tiles = (int64_t)b->tile_ptr.size() - 1;
-  v->tile_ptr = b->tile_ptr.data();
-  v->n_graph_tiles = b->gtile_ptr.empty() ? 0 : (int64_t)b->gtile_ptr.size() - 1;
-  v->graph_tile_ptr = b->graph_tile_ptr.empty() ? nullptr : b->graph_tile_ptr.data();
-  v->gtile_ptr = b->gtile_ptr.empty() ? nullptr : b->gtile_ptr.data();
+  v->state_graph_ptr = b->at<int32_t>(b->o_state_graph_ptr);
+  v->graph_node_ptr = b->at<int32_t>(b->o_graph_node_ptr);
+  v->in_ptr = b->at<int32_t>(b->o_in_ptr);
+  v->in_src = b->at<int32_t>(b->o_in_src);
+  v->in_dst = b->at<int32_t>(b->o_in_dst);
+  v->in_eid = b->at<int32_t>(b->o_in_eid);
+  v->out_ptr = b->at<int32_t>(b->o_out_ptr);
+  v->out_pos = b->at<int32_t>(b->o_out_pos);
+  v->node_graph = b->at<int32_t>(b->o_node_graph);
+  v->edge_feat = edge_feat;
+  v->n_tiles = b->n_tiles;
+  v->tile_ptr = b->at<int32_t>(b->o_tile);
+  v->n_graph_tiles = b->n_graph_tiles;
+  v->graph_tile_ptr = b->has_graph_tiles ? b->at<int32_t>(b->o_graph_tile) : nullptr;
+  v->gtile_ptr = b->has_graph_tiles ? b->at<int32_t>(b->o_gtile) : nullptr;
   return XRL_OK;
 }
 

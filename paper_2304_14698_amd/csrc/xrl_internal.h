@@ -1,5 +1,6 @@
 // Internal declarations shared by the host-side packer and the device-side runtime.
 #pragma once
+#include <atomic>
 #include <cstdarg>
 #include <cstdint>
 #include <cstdio>
@@ -67,37 +68,67 @@ struct xrl_batch_device {
   uint8_t *mask = nullptr;
 };
 
+// Host memory of one packed batch. While a context is alive it is pinned (the upload is then one
+// transfer at the link's rate) and comes from a bounded pool, so that a program that packs a state
+// per step pays neither for page faults nor for pinning; otherwise it is ordinary memory.
+struct HostBlock {
+  char *p = nullptr;
+  size_t cap = 0;
+  bool pinned = false;
+  int device = -1;          // device of `copied`
+  void *copied = nullptr;   // event behind the last transfer out of the block (pinned blocks)
+};
+// Implemented in the device translation unit. host_block_take leaves p null when memory ran out.
+HostBlock host_block_take(size_t bytes);
+void host_block_give(HostBlock &b);
+
+struct DevicePool;          // idle device blocks of one context (device translation unit)
+
+// The packed arrays lie in one host block, those the device needs first and in the device's layout:
+// array i of the device block is at the same offset in both. Behind them, in the host block, in_eid;
+// in the device block, the arrays that the device writes itself.
 struct xrl_batch {
   xrl_model_desc model;
   int64_t S = 0, G = 0, N = 0, E = 0;
   int32_t max_slots = 0;  // largest number of slots in one state
-  std::vector<int32_t> state_graph_ptr, graph_node_ptr, in_ptr, out_ptr;
-  RawVec<int32_t> node_op, in_src, in_dst, in_eid, out_pos, node_graph;
-  std::vector<int32_t> tile_ptr;  // [n_tiles + 1] edge tiles of the message kernels (see the packer)
+  HostBlock mem;
+  size_t send_bytes = 0;  // transferred to the device
+  size_t o_state_graph_ptr = 0, o_graph_node_ptr = 0, o_in_ptr = 0, o_out_ptr = 0, o_node_op = 0, o_in_src = 0,
+         o_in_dst = 0, o_out_pos = 0, o_node_graph = 0, o_node_dense = 0, o_edge_feat = 0, o_graph_global = 0,
+         o_mask = 0, o_tile = 0, o_gtile = 0, o_graph_tile = 0, o_in_eid = 0;
+  template <typename T> T *at(size_t off) const { return (T *)(mem.p + off); }
+  int64_t n_tiles = 0;            // edge tiles of the message kernels (see the packer): [n_tiles + 1] at o_tile
   int64_t n_split_tiles = 0;      // tiles that end inside a receiver's in-edge range
   // Per-graph edge tiles for the one-launch encoder of small batches: the same cutting rule, but
   // a tile never spans two graphs; graph g owns tiles [graph_tile_ptr[g], graph_tile_ptr[g + 1])
-  // of gtile_ptr. Both empty when the batch has more than kGraphTileMaxGraphs graphs or a node
+  // of gtile_ptr. Absent when the batch has more than kGraphTileMaxGraphs graphs or a node
   // with more than 32 in-edges.
-  std::vector<int32_t> gtile_ptr, graph_tile_ptr;
+  bool has_graph_tiles = false;
+  int64_t n_graph_tiles = 0;
   int32_t max_graph_nodes = 0;    // nodes of the largest graph
   int32_t max_graph_tiles = 0;    // most per-graph edge tiles of one graph
-  RawVec<float> node_dense, edge_feat;
-  std::vector<float> graph_global;
-  std::vector<uint8_t> mask;
   // Batches packed from edits (xrl_pack_state_edits): where each node's and each receiver-order
   // edge's attributes come from -- an index into the current graphs' arrays (>= 0) or, as -1 - k,
-  // into the new nodes' / edges' arrays -- and those compact attribute arrays. Empty otherwise.
-  RawVec<int32_t> node_from, edge_from;
-  RawVec<int32_t> base_node_op, new_node_op;
-  RawVec<float> base_node_dense, new_node_dense, base_edge_feat, new_edge_feat;
+  // into the new nodes' / edges' arrays -- and those compact attribute arrays. Such a batch has no
+  // node_op, node_dense and edge_feat on the host (xrl_batch_host_view writes the last on demand).
   bool from_edits = false;
+  size_t o_node_from = 0, o_edge_from = 0, o_base_op = 0, o_new_op = 0, o_base_dense = 0, o_new_dense = 0,
+         o_base_feat = 0, o_new_feat = 0;
+  RawVec<float> view_edge_feat;
   xrl_batch_device dev;
   bool uploaded = false;
+  // the context that uploaded it: its other users wait for its transfer, and a device block that only it
+  // has used goes back to its pool (reuse on the same stream is ordered), any other is freed
+  uint64_t owner = 0;
+  std::shared_ptr<DevicePool> pool;
+  std::atomic<bool> shared{false};
   uint64_t id = 0;  // unique per packed batch; ties saved activations to their batch
+  xrl_batch() = default;
+  xrl_batch(const xrl_batch &) = delete;
+  ~xrl_batch() { host_block_give(mem); }
 };
 
 constexpr int64_t kGraphTileMaxGraphs = 4096;
 
-// Implemented in the device translation unit; frees dev.block if any.
+// Implemented in the device translation unit; gives dev.block back if there is one.
 extern "C" void xrl_batch_release_device(xrl_batch *b);

@@ -1,0 +1,65 @@
+"""Packed batches take their host and device memory from pools: a block that changes hands while the
+queue still holds work on its last owner must not disturb that work, whatever the sizes, contexts
+and order of frees."""
+import numpy as np
+import pytest
+
+import paper_2304_14698_amd as xrl
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _setup(sizes):
+    import torch
+    model, _ = synth.make_config(1)
+    rng = np.random.Generator(np.random.PCG64(11))
+    weights = synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1)
+    states = []
+    for blocks, cand in sizes:
+        graphs, mask = synth.make_state(rng, synth.resnet_dag(rng, blocks), cand, by_block=True)
+        states.append(synth.concat_states([(graphs, mask)]))
+    return torch, model, weights, states
+
+
+@pytest.mark.parametrize("sizes", [[(2, 3)] * 6, [(2, 3), (8, 40), (2, 5), (8, 41), (16, 90), (2, 3)], [(16, 500), (16, 400)]])
+def test_blocks_change_hands_behind_the_queue(sizes):
+    torch, model, weights, states = _setup(sizes)
+    enc = xrl.Encoder(model, weights)
+    want = []
+    for st in states:                               # one at a time, waited for
+        b = enc.pack(st)
+        want.append(enc.encode(b).cpu())
+        b.free()
+    for _ in range(3):                              # queued back to back, each batch freed at once
+        got = []
+        for st in states:
+            b = enc.pack(st)
+            got.append(enc.encode(b))
+            b.free()
+        torch.cuda.synchronize()
+        for g, w in zip(got, want):
+            assert torch.equal(g.cpu(), w)
+
+
+def test_batch_outlives_its_context_and_serves_another():
+    torch, model, weights, states = _setup([(8, 40), (8, 40)])
+    side = torch.cuda.Stream()
+    a, b = xrl.Encoder(model, weights), xrl.Encoder(model, weights, stream=side)
+    first, second = a.pack(states[0]), a.pack(states[1])
+    on_a = a.encode(first)
+    torch.cuda.synchronize()
+    out = torch.empty_like(on_a)
+    third = a.pack(states[0])
+    torch.cuda.current_stream().wait_stream(side)
+    on_b = b.encode(third, out=out)                 # another stream than the upload's, right behind it
+    third.free()                                    # (in use on both streams: not recycled)
+    again = a.encode(a.pack(states[1]))
+    torch.cuda.synchronize()
+    assert torch.equal(on_a.cpu(), on_b.cpu())
+    a.close()
+    late = b.encode(second)
+    torch.cuda.synchronize()
+    assert torch.equal(late.cpu(), again.cpu())
+    first.free()
+    second.free()
