@@ -38,13 +38,6 @@ TRAFFIC = {
                               bytes_per_launch=(89442.7 * 2.000 + 70572.0 * 1.000) * 1024),
     (4, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h"), sha256_16="b61a512bcdbfb016",
                               bytes_per_launch=(118742.4 * 2.000 + 162434.5 * 1.000) * 1024),
-    # configuration 5 (profiles/step_config5_bf16_hbm_traffic.md): backward through the node / edge MLP
-    (5, "bf16", "bwd_node"): dict(sources=("mma.hip.h", "mlp2_bwd.hip.h", "mlp2_bwdz.hip.h"), sha256_16="4137d3e1b408b425",
-                                  # mean of the five launches: four with dz2 given by the gradient gather, the topmost round's
-                                  bytes_per_launch=(0.8 * (4635006.5 * 2.000 + 20977475.7 * 1.000) +
-                                                    0.2 * (947049.9 * 2.000 + 29040546.5 * 1.000)) * 1024),
-    (5, "bf16", "bwd_edge"): dict(sources=("mma.hip.h", "mlp2_bwd.hip.h", "mlp2_bwdz.hip.h"), sha256_16="4137d3e1b408b425",
-                                  bytes_per_launch=(3545704.0 * 2.000 + 31035381.9 * 1.000) * 1024),
 }
 
 
@@ -244,69 +237,76 @@ def main():
     peak = PEAK_BF16_TFLOPS if bf16 else PEAK_FP32_TFLOPS
     b = 2 if bf16 else 4
     hv = batch.host_view()
-    n_recv = int((np.diff(hv["in_ptr"]) > 0).sum())
-    n_tiles = len(hv["tile_ptr"]) - 1
+    # what a round computes: the batch's nodes and edges, or (a batch reduced to its distinct nodes) the
+    # mean over the rounds; the node-update layer's below
+    levels = [enc.batch_level(batch, r) for r in range(R + 1)]
+    n_node, n_edge, n_recv, n_tiles = (sum(lv[i] for lv in levels[1:]) / max(R, 1) for i in range(4))
+    n_node0, n_edge0 = levels[0][:2]
+    n_below = sum(lv[0] for lv in levels[:-1]) / max(R, 1)
+    reduced = n_node0 < N
     Tn = model["n_op_types"]
     # Large bf16 batches run on the forward kernels that keep relu(z1) and the ReLU mask bits of z1
     # and y for the backward pass, and on the backward kernels that start from the bits.
     kept = (backward and bf16 and args.round_kind == "mlp" and kern["resident"]["launches_per_step"] == 0
-            and min(N, E) >= int(os.environ.get("XRL_PERSISTENT_MIN_ROWS", 8192)))
+            and (reduced or min(N, E) >= int(os.environ.get("XRL_PERSISTENT_MIN_ROWS", 8192))))
     zk = 1 if kept else 0
     # Algorithmic work per launch of each kernel (multiply-add = 2 flop; b = bytes per stored
     # activation): flops of the products the kernel is there for, and the bytes of its inputs read
     # once and its outputs written once (rows gathered several times count once). A kernel whose
     # flops / bytes lies below the ridge of the two peaks is rated against HBM, else against the
     # matrix cores.
-    NH, EH = N * H * b, E * H * b
-    idx_e = 4 * (2 * E + n_tiles)
+    NH, EH, NH0 = n_node * H * b, n_edge * H * b, n_node0 * H * b
+    idx_e = 4 * (2 * n_edge + n_tiles)
     # the kept forward's mask bits of one MLP's z1 or y: 16 bits per lane, 32-feature block and wave tile
-    mask_e, mask_n = n_tiles * (H // 32) * 128, ((N + 31) // 32) * (H // 32) * 128
+    mask_e, mask_n, mask_n0 = (t * (H // 32) * 128 for t in (n_tiles, (n_node + 31) // 32, (n_node0 + 31) // 32))
     work = {
         "embed": dict(kernel="node-update layer: sum of incoming edge attributes + embed MLP",
-                      flops=2.0 * N * H * (De + Dd + H),
-                      bytes=E * De * 4 + N * (4 + 4 * Dd) + 4 * (N + 1) + NH * (1 + zk) + zk * 2 * mask_n),
+                      flops=2.0 * n_node0 * H * (De + Dd + H),
+                      bytes=n_edge0 * De * 4 + n_node0 * (4 + 4 * Dd) + 4 * (n_node0 + 1) + NH0 * (1 + zk) + zk * 2 * mask_n0),
         "edge": dict(kernel="edge MLP + per-receiver sum (one launch per round)",
-                     flops=2.0 * E * H * (3 * H + De),
-                     bytes=NH + E * De * 4 + idx_e + n_recv * H * b + zk * (EH + 2 * mask_e)),
-        "node": dict(kernel="node MLP (one launch per round)", flops=2.0 * N * H * 3 * H,
-                     bytes=(2 + zk) * NH + n_recv * H * b + 4 * N + zk * 2 * mask_n),   # received sums: nodes with in-edges only
+                     flops=2.0 * n_edge * H * (3 * H + De),
+                     bytes=NH + n_edge * De * 4 + idx_e + n_recv * H * b + zk * (EH + 2 * mask_e)),
+        "node": dict(kernel="node MLP (one launch per round)", flops=2.0 * n_node * H * 3 * H,
+                     bytes=(2 + zk) * NH + n_recv * H * b + 4 * n_node + zk * 2 * mask_n),   # received sums: nodes with in-edges only
         "pool": dict(kernel="per-graph readout sum (fused with the readout MLP)", flops=0.0,
-                     bytes=NH + 4 * (G + 1) + G * H * 4),
+                     bytes=levels[R][0] * H * b + (4 * N if reduced else 0) + 4 * (G + 1) + G * H * 4),
         "grad_gather": dict(kernel="per-node sum of the per-edge gradients (receiver and sender side)", flops=0.0,
-                            bytes=(EH + n_recv * H * b + mask_n if kept else 2 * EH) + 2 * NH + 4 * (2 * N + E)),
+                            # (reduced: then summed per distinct node of the round below, in fp32 first)
+                            bytes=(EH + n_recv * H * b + mask_n if kept else 2 * EH) + 2 * NH + 4 * (2 * n_node + n_edge)
+                            + (NH + n_below * H * (8 + b) if reduced else 0)),
     }
     if kept:
         work.update({
             "bwd_edge": dict(kernel="backward through the edge MLP from the kept forward (one launch per round)",
-                             flops=2.0 * E * H * 3 * H,
-                             bytes=n_recv * H * b + 2 * mask_e + 4 * (E + n_tiles) + 3 * EH + n_recv * H * b),
+                             flops=2.0 * n_edge * H * 3 * H,
+                             bytes=n_recv * H * b + 2 * mask_e + 4 * (n_edge + n_tiles) + 3 * EH + n_recv * H * b),
             "bwd_node": dict(kernel="backward through the node MLP from the kept forward (one launch per round)",
                              # dz2 arrives masked from the gradient gather and is read (NH) instead of stored; the
                              # topmost round reads the per-graph table and stores dz2 itself (NH either way);
                              # dz1, dh, and the dagg rows of the nodes with in-edges are written
-                             flops=2.0 * N * H * 3 * H,
-                             bytes=3 * NH + n_recv * H * b + mask_n * (1 + 1 / max(R, 1)) + 4 * N),
-            "bwd_embed": dict(kernel="backward through the embed MLP from the kept forward", flops=2.0 * N * H * H,
-                              bytes=2 * NH + mask_n),
+                             flops=2.0 * n_node * H * 3 * H,
+                             bytes=3 * NH + n_recv * H * b + mask_n * (1 + 1 / max(R, 1)) + 4 * n_node),
+            "bwd_embed": dict(kernel="backward through the embed MLP from the kept forward", flops=2.0 * n_node0 * H * H,
+                              bytes=2 * NH0 + mask_n0),
             "wgrad_edge": dict(kernel="weight gradients of one edge MLP, both layers",
-                               flops=2.0 * E * H * (3 * H + De + 2), bytes=NH + 4 * EH + E * De * 4 + 8 * E),
+                               flops=2.0 * n_edge * H * (3 * H + De + 2), bytes=NH + 4 * EH + n_edge * De * 4 + 8 * n_edge),
             "wgrad_node": dict(kernel="weight gradients of one node MLP, both layers",
-                               flops=2.0 * N * H * (3 * H + 2), bytes=4 * NH + n_recv * H * b + 4 * N),
+                               flops=2.0 * n_node * H * (3 * H + 2), bytes=4 * NH + n_recv * H * b + 4 * n_node),
             "wgrad_embed": dict(kernel="weight gradients of the embed MLP, both layers",
-                                flops=2.0 * N * H * (De + Tn + Dd + H + 2), bytes=3 * NH + E * De * 4 + N * (8 + 4 * Dd)),
+                                flops=2.0 * n_node0 * H * (De + Tn + Dd + H + 2), bytes=3 * NH0 + n_edge0 * De * 4 + n_node0 * (8 + 4 * Dd)),
         })
     else:
         # small batches and fp32: the backward kernels recompute the first layer (and, for the edge
         # kind, the second) of the forward on the matrix cores; that recomputation is counted
         work.update({
-            "bwd_edge": dict(kernel="backward through the edge MLP (one launch per round)", flops=2.0 * E * H * (6 * H + De),
+            "bwd_edge": dict(kernel="backward through the edge MLP (one launch per round)", flops=2.0 * n_edge * H * (6 * H + De),
                              bytes=None),
-            "bwd_node": dict(kernel="backward through the node MLP (one launch per round)", flops=2.0 * N * H * 5 * H, bytes=None),
-            "bwd_embed": dict(kernel="backward through the embed MLP", flops=2.0 * N * H * (De + Dd + 2 * H), bytes=None),
-            "wgrad_edge": dict(kernel="weight gradients of one edge MLP, both layers", flops=2.0 * E * H * (3 * H + De + 2), bytes=None),
-            "wgrad_node": dict(kernel="weight gradients of one node MLP, both layers", flops=2.0 * N * H * (3 * H + 2), bytes=None),
+            "bwd_node": dict(kernel="backward through the node MLP (one launch per round)", flops=2.0 * n_node * H * 5 * H, bytes=None),
+            "bwd_embed": dict(kernel="backward through the embed MLP", flops=2.0 * n_node0 * H * (De + Dd + 2 * H), bytes=None),
+            "wgrad_edge": dict(kernel="weight gradients of one edge MLP, both layers", flops=2.0 * n_edge * H * (3 * H + De + 2), bytes=None),
+            "wgrad_node": dict(kernel="weight gradients of one node MLP, both layers", flops=2.0 * n_node * H * (3 * H + 2), bytes=None),
             "wgrad_embed": dict(kernel="weight gradients of the embed MLP, both layers",
-                                flops=2.0 * N * H * (De + Tn + Dd + H + 2), bytes=None),
+                                flops=2.0 * n_node0 * H * (De + Tn + Dd + H + 2), bytes=None),
         })
     ridge = peak * 1e12 / (PEAK_HBM_GBS * 1e9)           # flop per byte at which the two peaks meet
     report = {}
@@ -341,6 +341,8 @@ def main():
         edges_per_s=E * R / (ms * 1e-3),
         pack_upload_ms=t_pack * 1e3,              # host packing + H2D copies, outside the timed region
         kernels_us=kern,
+        # nodes and edges the rounds are computed for: equal histories once (node-update layer first)
+        computed=dict(nodes=[lv[0] for lv in levels], edges=[lv[1] for lv in levels]),
     )
     if report:
         # the roofline entry rates the kernel that takes the largest share of the step

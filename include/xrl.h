@@ -210,21 +210,37 @@ int xrl_batch_free(xrl_batch *b);   /* frees host and device copies; NULL is acc
  * step, Section 4.2; same results). Its blocks wait for each other; XRL_CLUSTER_SPIN_LIMIT =
  * polls after which such a wait gives up (default 2^21, about two seconds): the launch then
  * finishes with invalid embeddings, and the next xrl_encode on the context returns XRL_ERR_HIP
- * (once), after which the context works again. */
+ * (once), after which the context works again;
+ * XRL_DISTINCT_MIN_US = smallest batch, as the estimated time of its encode in microseconds, that
+ * is reduced to its distinct nodes (default 300; 0 = every batch that can be; -1 = none; see
+ * xrl_encode). */
 int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip_stream,
                xrl_ctx **out);
 int xrl_set_weights(xrl_ctx *ctx, const float *weights_host);
 int xrl_destroy(xrl_ctx *ctx);
-/* Copies the packed arrays to the GPU (async on the ctx stream). Must precede the calls below. */
+/* Copies the packed arrays to the GPU (async on the ctx stream; not while it is being captured). Must
+ * precede the calls below. */
 int xrl_batch_upload(xrl_ctx *ctx, xrl_batch *b);
 
 /* ---- forward --------------------------------------------------------------------------------
  * xrl_encode: the GNN of Section 3.4 on every graph of the batch. d_emb: device [G, hidden]
  * fp32, the graph representations. save_for_backward != 0 keeps the per-round node states and
  * received sums inside ctx for xrl_encode_backward (overwritten by the next xrl_encode).
+ * Nodes of different graphs with the same history -- the same attributes and, over the rounds so far,
+ * the same senders' histories, edge by edge -- have the same state, bit for bit. A large batch of
+ * rewrites of a few graphs (message-passing rounds of the MLP kind, at most 15; no receiver of more
+ * than 32 in-edges) is reduced to its distinct nodes by the context that uploaded it when it is
+ * first saved for the backward pass, or encoded a second time: that one call waits for the stream
+ * twice, later calls compute every round once per distinct node. States and embeddings are
+ * the same bits; gradients are summed in another, equally fixed order.
  * Errors: NULL, SHAPE, OOM, HIP (also: an earlier one-launch encode on this context did not
  * complete, see XRL_CLUSTER_SPIN_LIMIT). */
 int xrl_encode(xrl_ctx *ctx, const xrl_batch *b, float *d_emb, int save_for_backward);
+
+/* What xrl_encode computes of the batch in round `level` (0: the node-update layer): nodes, edges, nodes
+ * with in-edges and edge tiles -- the batch's own, or its distinct ones once it has been reduced.
+ * Errors: NULL, STATE, INDEX. */
+int xrl_batch_level(xrl_ctx *ctx, const xrl_batch *b, int32_t level, int64_t counts[4]);
 
 /* xrl_policy_value: heads of Section 3.3.2 on the embeddings. Per slot j: logit = policy MLP of
  * emb[j]; per state, over its valid slots only (invalid-action masking): d_logp [G] = log

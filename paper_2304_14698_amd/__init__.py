@@ -60,7 +60,7 @@ class PackedView(C.Structure):
 
 
 EXPORTS = ["xrl_weight_count", "xrl_weight_tensor_count", "xrl_weight_tensor", "xrl_pack_state", "xrl_pack_state_edits",
-           "xrl_batch_dims", "xrl_batch_host_view", "xrl_batch_free", "xrl_create",
+           "xrl_batch_dims", "xrl_batch_level", "xrl_batch_host_view", "xrl_batch_free", "xrl_create",
            "xrl_set_weights", "xrl_destroy", "xrl_batch_upload", "xrl_encode", "xrl_policy_value",
            "xrl_policy_value_static",
            "xrl_policy_value_backward", "xrl_encode_backward", "xrl_ppo_objective", "xrl_segment_sum",
@@ -86,6 +86,7 @@ def load_library():
     lib.xrl_pack_state.argtypes = [C.POINTER(ModelDesc), C.POINTER(StateDesc), C.POINTER(vp)]
     lib.xrl_pack_state_edits.argtypes = [C.POINTER(ModelDesc), C.POINTER(EditStateDesc), C.POINTER(vp)]
     lib.xrl_batch_dims.argtypes = [vp] + [C.POINTER(i64)] * 4
+    lib.xrl_batch_level.argtypes = [vp, vp, i32, C.POINTER(i64)]
     lib.xrl_batch_host_view.argtypes = [vp, C.POINTER(PackedView)]
     lib.xrl_batch_free.argtypes = [vp]
     lib.xrl_create.argtypes = [C.POINTER(ModelDesc), vp, vp, C.POINTER(vp)]
@@ -279,6 +280,12 @@ class Encoder:
 
     def pack_edits(self, edit_state):
         return self.upload(Batch(self.model, edit_state, edits=True))
+
+    def batch_level(self, batch, level):
+        """(nodes, edges, nodes with in-edges, edge tiles) computed in round `level` (0: node-update layer)."""
+        v = (C.c_int64 * 4)()
+        _check(self.lib.xrl_batch_level(self.handle, batch.handle, level, v))
+        return tuple(int(x) for x in v)
 
     def _empty(self, shape, dtype=None):
         t = self.torch

@@ -1,0 +1,440 @@
+// Distinct nodes of a batch, level by level. The candidates of a state are local rewrites of its current
+// graph, so most of their nodes have, for the first rounds, exactly the history of a node of another
+// graph: the same operator, attributes and incoming edge attributes (level 0), and at level l + 1 the
+// same level-l class and, edge by edge in the batch's receiver order, senders of the same level-l
+// classes. Nodes of one class at level l have the same state after l rounds, bit for bit, so a round
+// is computed once per class, on the graph of one representative per class (its smallest node) and
+// the representatives' in-edges.
+//
+// Classes are found by hashing a node's key into an open-addressing table (32-bit tag, smallest node
+// that has it) and then comparing the key itself with that node's, word by word: a node whose tag
+// is another key's too becomes a class of its own, so equality never rests on the hash.
+// Class numbers ascend with their representatives, whatever order the hardware ran in.
+//
+// What it saves, a kept minibatch's update step: 4.3 M nodes, H = 256: 88.0 -> 14.4 ms (20 % of the edges are
+// left over five rounds); 354 k nodes, H = 128: 4.3 -> 1.85 ms (40 %); 73 k nodes re-evaluated in fp32:
+// 1.19 -> 0.66 ms. The attention rounds keep to the whole batch: their backward gathers per sender, and a
+// sender shared by thousands of graphs made that pass 8 times slower than what the rest gained.
+//
+// Bound by gathers of 4-byte class numbers and by table probes: one pass of each over the nodes and
+// edges per level, against two matrix products per edge and node and round for what it saves.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+#include "mma.hip.h"
+
+constexpr int kMaxLevels = 16;            // levels 0 .. rounds
+constexpr unsigned long long kEmptySlot = ~0ull;
+constexpr int kScanItems = 1024;          // nodes per block of the class kernels (four per thread)
+
+struct ClassArgs {
+  int64_t N;
+  const int32_t *in_ptr, *in_src, *node_op;
+  const uint32_t *edge_feat, *node_dense;  // bit patterns
+  int De, Dd;
+  const int32_t *prev;                     // class of each node one level below; nullptr: level 0
+  unsigned long long *table;               // [mask + 1] tag << 32 | smallest node, kEmptySlot
+  uint32_t mask;
+  const int32_t *state_graph_ptr, *graph_node_ptr;
+  int32_t *slot;                           // [N] table slot, then (representatives) the class number
+  int32_t *rep;                            // [N]
+  int2 *block_sum;                         // [blocks] classes and their in-edges, then exclusive sums
+  int32_t *totals;                         // [2] classes and in-edges of the level
+  int32_t *receivers;                      // [1] set to zero for level_fill_kernel
+  int32_t *reps;                           // [classes] representative of each class
+  int32_t *ptr;                            // [classes + 1] in-edges of the representatives
+  int32_t *cls;                            // [N] class of each node
+};
+
+__device__ __forceinline__ uint64_t mix64(uint64_t h, uint64_t v) {   // (order-sensitive)
+  h = (h ^ v) * 0x9E3779B97F4A7C15ull;
+  return h ^ (h >> 29);
+}
+
+__global__ __launch_bounds__(256) void class_clear_kernel(unsigned long long *table, uint32_t n) {
+  const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+  if (i < n) table[i] = kEmptySlot;
+}
+
+__device__ __forceinline__ void class_insert(const ClassArgs &a, int64_t n) {
+  const int e0 = a.in_ptr[n], e1 = a.in_ptr[n + 1];
+  uint64_t h;
+  if (a.prev) {
+    h = mix64(0x51ED270B27B4F3CFull, (uint32_t)a.prev[n]);
+    for (int e = e0; e < e1; ++e) h = mix64(h, (uint32_t)a.prev[a.in_src[e]]);
+  } else {
+    h = mix64((uint32_t)a.node_op[n], (uint32_t)(e1 - e0));
+    for (int k = 0; k < a.Dd; ++k) h = mix64(h, a.node_dense[(size_t)n * a.Dd + k]);
+    for (size_t w = (size_t)e0 * a.De; w < (size_t)e1 * a.De; ++w) h = mix64(h, a.edge_feat[w]);
+  }
+  h = mix64(h, h >> 32);
+  const unsigned long long tag = (h >> 32) % 0xffffffffull;           // (not that of an empty slot)
+  const unsigned long long mine = tag << 32 | (uint32_t)n;
+  uint32_t s = (uint32_t)h & a.mask;
+  for (uint32_t i = 0; i <= a.mask; ++i, s = (s + 1) & a.mask) {      // (the table has more slots than there are nodes)
+    // (a slot's tag is written once and its node only falls: most nodes find themselves above it)
+    unsigned long long w = __hip_atomic_load(a.table + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (w == kEmptySlot) {
+      w = atomicCAS(a.table + s, kEmptySlot, mine);
+      if (w == kEmptySlot) w = mine;
+    }
+    if (w >> 32 != tag) continue;
+    if (w > mine) atomicMin(a.table + s, mine);
+    a.slot[n] = (int32_t)s;
+    break;
+  }
+}
+// The nodes of every state's first graph, a block each, before all nodes: they are the smallest of most
+// classes, so the others find their class in place and leave the table alone (all at once, thousands
+// of nodes would go for the same slots: 98 against 17 us per level at 703 k nodes of 2080 graphs).
+__global__ __launch_bounds__(256) void class_insert_first_kernel(const ClassArgs a) {
+  const int g = a.state_graph_ptr[blockIdx.x], n1 = a.graph_node_ptr[g + 1];
+  for (int n = a.graph_node_ptr[g] + threadIdx.x; n < n1; n += 256) class_insert(a, n);
+}
+__global__ __launch_bounds__(256) void class_insert_kernel(const ClassArgs a) {
+  const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (n < a.N) class_insert(a, n);
+}
+
+__device__ __forceinline__ bool same_key(const ClassArgs &a, int64_t n, int64_t r) {
+  const int e0 = a.in_ptr[n], d = a.in_ptr[n + 1] - e0, f0 = a.in_ptr[r];
+  if (a.in_ptr[r + 1] - f0 != d) return false;
+  if (a.prev) {
+    bool same = a.prev[n] == a.prev[r];
+    for (int k = 0; k < d; ++k) same &= a.prev[a.in_src[e0 + k]] == a.prev[a.in_src[f0 + k]];
+    return same;
+  }
+  bool same = a.node_op[n] == a.node_op[r];
+  for (int k = 0; k < a.Dd; ++k) same &= a.node_dense[(size_t)n * a.Dd + k] == a.node_dense[(size_t)r * a.Dd + k];
+  for (int64_t w = 0; w < (int64_t)d * a.De; ++w) same &= a.edge_feat[(size_t)e0 * a.De + w] == a.edge_feat[(size_t)f0 * a.De + w];
+  return same;
+}
+
+// exclusive sums over the 256 threads of a block; total of all in `sum`
+__device__ __forceinline__ int2 block_scan_pair(int2 v, int2 *wave_sum, int2 &sum) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int2 x = v;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int px = __shfl_up(x.x, o), py = __shfl_up(x.y, o);
+    if (lane >= o) { x.x += px; x.y += py; }
+  }
+  if (lane == 63) wave_sum[w] = x;
+  __syncthreads();
+  int2 before = make_int2(0, 0);
+  sum = make_int2(0, 0);
+  for (int k = 0; k < (int)blockDim.x / 64; ++k) {
+    if (k < w) { before.x += wave_sum[k].x; before.y += wave_sum[k].y; }
+    sum.x += wave_sum[k].x; sum.y += wave_sum[k].y;
+  }
+  __syncthreads();
+  return make_int2(before.x + x.x - v.x, before.y + x.y - v.y);
+}
+
+__global__ __launch_bounds__(256) void class_verify_kernel(const ClassArgs a) {
+  __shared__ int2 ws[4];
+  int2 v = make_int2(0, 0), sum;
+  for (int i = 0; i < kScanItems / 256; ++i) {
+    const int64_t n = (int64_t)blockIdx.x * kScanItems + i * 256 + threadIdx.x;
+    if (n >= a.N) break;
+    int32_t r = (int32_t)(uint32_t)a.table[a.slot[n]];
+    if (r != (int32_t)n && !same_key(a, n, r)) r = (int32_t)n;
+    a.rep[n] = r;
+    if (r == (int32_t)n) { ++v.x; v.y += a.in_ptr[n + 1] - a.in_ptr[n]; }
+  }
+  (void)block_scan_pair(v, ws, sum);
+  if (threadIdx.x == 0) a.block_sum[blockIdx.x] = sum;
+}
+
+__global__ __launch_bounds__(256) void class_scan_kernel(const ClassArgs a, int n_blocks) {
+  __shared__ int2 ws[4];
+  int2 base = make_int2(0, 0);
+  for (int i0 = 0; i0 < n_blocks; i0 += 256) {
+    const int i = i0 + threadIdx.x;
+    const int2 v = i < n_blocks ? a.block_sum[i] : make_int2(0, 0);
+    int2 sum;
+    const int2 x = block_scan_pair(v, ws, sum);
+    if (i < n_blocks) a.block_sum[i] = make_int2(base.x + x.x, base.y + x.y);
+    base.x += sum.x; base.y += sum.y;
+  }
+  if (threadIdx.x == 0) {
+    a.totals[0] = base.x;
+    a.totals[1] = base.y;
+    *a.receivers = 0;
+    a.ptr[base.x] = base.y;
+  }
+}
+
+__global__ __launch_bounds__(256) void class_number_kernel(const ClassArgs a) {
+  __shared__ int2 ws[4];
+  int2 base = a.block_sum[blockIdx.x];
+  for (int i = 0; i < kScanItems / 256; ++i) {
+    const int64_t n = (int64_t)blockIdx.x * kScanItems + i * 256 + threadIdx.x;
+    const bool is_rep = n < a.N && a.rep[n] == (int32_t)n;
+    const int2 v = is_rep ? make_int2(1, a.in_ptr[n + 1] - a.in_ptr[n]) : make_int2(0, 0);
+    int2 sum;
+    const int2 x = block_scan_pair(v, ws, sum);
+    if (is_rep) {
+      a.slot[n] = base.x + x.x;
+      a.reps[base.x + x.x] = (int32_t)n;
+      a.ptr[base.x + x.x] = base.y + x.y;
+    }
+    base.x += sum.x; base.y += sum.y;
+  }
+}
+
+__global__ __launch_bounds__(256) void class_of_kernel(const ClassArgs a) {
+  const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (n < a.N) a.cls[n] = a.slot[a.rep[n]];
+}
+
+// The graph of a level's representatives: receiver-order arrays like the batch's own.
+struct LevelFillArgs {
+  int64_t n_cls, n_edges;
+  const int32_t *reps, *ptr, *cls, *prev;   // classes of this level and of the one below (nullptr: level 0)
+  const int32_t *in_ptr, *in_src, *node_op;
+  const float *edge_feat, *node_dense;
+  int De, Dd;
+  int32_t *o_ptr, *o_src, *o_dst, *o_agg_src, *o_self, *o_op;
+  float *o_feat, *o_dense;
+  int32_t *receivers;                       // classes with in-edges, counted
+};
+__global__ __launch_bounds__(256) void level_fill_kernel(const LevelFillArgs a) {
+  const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (c >= a.n_cls) return;
+  const int32_t r = a.reps[c], e0 = a.in_ptr[r], d = a.in_ptr[r + 1] - e0, p0 = a.ptr[c];
+  const unsigned long long with = __ballot(d > 0);
+  if ((threadIdx.x & 63) == 0 && with) atomicAdd(a.receivers, __popcll(with));
+  a.o_ptr[c] = p0;
+  if (c == a.n_cls - 1) a.o_ptr[a.n_cls] = p0 + d;
+  a.o_agg_src[c] = d > 0 ? (int32_t)c : -1;
+  if (a.prev) {
+    a.o_self[c] = a.prev[r];
+    for (int k = 0; k < d; ++k) {
+      a.o_src[p0 + k] = a.cls[a.in_src[e0 + k]];
+      a.o_dst[p0 + k] = (int32_t)c;
+    }
+  } else {
+    a.o_op[c] = a.node_op[r];
+    for (int k = 0; k < a.Dd; ++k) a.o_dense[(size_t)c * a.Dd + k] = a.node_dense[(size_t)r * a.Dd + k];
+  }
+  const f32x4 *src = (const f32x4 *)(a.edge_feat + (size_t)e0 * a.De);      // (De is a multiple of 4)
+  f32x4 *dst = (f32x4 *)(a.o_feat + (size_t)p0 * a.De);
+  for (int k = 0; k < d * (a.De / 4); ++k) dst[k] = src[k];
+}
+
+// Edge tiles of the levels 1 .. rounds: at most 32 edges, cut at receiver boundaries (no receiver of such a
+// batch has more than 32). The cut starts afresh every kTileChunk edges, so a block cuts a chunk by
+// itself: at one unfilled tile in about 66, where a cut of the whole level is one serial chain.
+constexpr int kTileChunk = 2048, kTileChunkMax = 2 * (kTileChunk + 32) / 33 + 2;   // tiles of a chunk at most
+struct TileLevels {
+  int n_levels;                             // entries below
+  int chunk0[kMaxLevels + 1];               // first chunk of each level
+  int32_t n_edges[kMaxLevels];
+  const int32_t *ptr[kMaxLevels], *dst[kMaxLevels];
+  int32_t *tile_ptr[kMaxLevels];
+  int32_t *cuts;                            // [chunks][kTileChunkMax]
+  int32_t *count;                           // [chunks] tiles, then the first tile of each chunk
+  int32_t *totals;                          // [n_levels] tiles of each level
+};
+__device__ __forceinline__ int tile_level(const TileLevels &a, int chunk) {
+  int l = 0;
+  while (l + 1 < a.n_levels && chunk >= a.chunk0[l + 1]) ++l;
+  return l;
+}
+__global__ __launch_bounds__(256) void tile_cut_kernel(const TileLevels a) {
+  __shared__ int32_t start[kTileChunk + 64];   // first edge of the receiver of edge e0 + j, less e0
+  const int l = tile_level(a, blockIdx.x);
+  const int32_t E = a.n_edges[l], k = (int)blockIdx.x - a.chunk0[l];
+  const int32_t *ptr = a.ptr[l], *dst = a.dst[l];
+  // the chunk: from the first receiver boundary at or after k * kTileChunk to the next chunk's
+  auto boundary = [&](int64_t e) -> int32_t {
+    if (e >= E) return E;
+    const int32_t r = dst[e];
+    return ptr[r] == (int32_t)e ? (int32_t)e : ptr[r + 1];
+  };
+  const int32_t e0 = boundary((int64_t)k * kTileChunk), e1 = boundary((int64_t)(k + 1) * kTileChunk);
+  const int32_t n = e1 - e0;                   // <= kTileChunk + 31
+  for (int j = threadIdx.x; j < n; j += 256) start[j] = ptr[dst[e0 + j]] - e0;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  int32_t *cuts = a.cuts + (size_t)blockIdx.x * kTileChunkMax;
+  int c = 0;
+  for (int s = 0; s < n && c < kTileChunkMax;) {
+    cuts[c++] = e0 + s;
+    s = s + 32 >= n ? n : start[s + 32];       // the receiver of edge s + 32 starts the next tile (after s: in-degrees <= 32)
+  }
+  a.count[blockIdx.x] = c;
+}
+__global__ __launch_bounds__(256) void tile_scan_kernel(const TileLevels a) {
+  __shared__ int2 ws[4];
+  const int l = blockIdx.x, c0 = a.chunk0[l], c1 = a.chunk0[l + 1];
+  int base = 0;
+  for (int i0 = c0; i0 < c1; i0 += 256) {
+    const int i = i0 + threadIdx.x;
+    const int2 v = make_int2(i < c1 ? a.count[i] : 0, 0);
+    int2 sum;
+    const int2 x = block_scan_pair(v, ws, sum);
+    if (i < c1) a.count[i] = base + x.x;
+    base += sum.x;
+  }
+  if (threadIdx.x == 0) {
+    a.totals[l] = base;
+    a.tile_ptr[l][base] = a.n_edges[l];
+  }
+}
+__global__ __launch_bounds__(256) void tile_write_kernel(const TileLevels a) {
+  const int l = tile_level(a, blockIdx.x);
+  const int32_t first = a.count[blockIdx.x];
+  const int32_t last = (int)blockIdx.x + 1 < a.chunk0[l + 1] ? a.count[blockIdx.x + 1] : a.totals[l];
+  for (int i = threadIdx.x; i < last - first; i += 256)
+    a.tile_ptr[l][first + i] = a.cuts[(size_t)blockIdx.x * kTileChunkMax + i];
+}
+
+// ---- groupings for the backward pass. What a class receives from the level above: the gradients of the
+// level's classes that split it and those of the level's edges whose sender's class it is, rows of one
+// list [edges | classes]; and the classes of the last level, the pool's gradient for each of their
+// nodes. All groupings are made in one stable radix sort: each owns a range of items and a
+// range of keys, in the same order. (A sender may have thousands of edges here, one from every
+// graph it is shared by: a sum per segment cut into 16-row pieces, not a loop per node.)
+constexpr int kMaxGroupings = kMaxLevels;
+struct GroupArgs {
+  int n;                                       // groupings
+  int64_t item0[kMaxGroupings + 1];            // first item of each
+  uint32_t key0[kMaxGroupings + 1];            // first key of each
+  int64_t n_edges[kMaxGroupings];              // level groupings: the items below it are edges, the others classes
+  const int32_t *src[kMaxGroupings];           // level groupings: senders of the edges
+  const int32_t *key[kMaxGroupings];           // key of each class, or (members) of each node
+  const int32_t *val[kMaxGroupings];           // value of each item; nullptr: the item's index
+  int32_t *ptr[kMaxGroupings];                 // [keys + 1] out: first sorted item of each key
+  int32_t *seg[kMaxGroupings];                 // [items] out: key of each sorted item
+  int32_t *out[kMaxGroupings];                 // [items] out: sorted values
+};
+__device__ __forceinline__ int grouping_of(const GroupArgs &a, int64_t i) {
+  int lo = 0, hi = a.n;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (a.item0[mid] <= i) lo = mid; else hi = mid;
+  }
+  return lo;
+}
+__global__ __launch_bounds__(256) void group_items_kernel(const GroupArgs a, uint2 *items) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= a.item0[a.n]) return;
+  const int g = grouping_of(a, i);
+  const int64_t j = i - a.item0[g];
+  const int64_t c = j < a.n_edges[g] ? a.src[g][j] : j - a.n_edges[g];
+  items[i] = make_uint2(a.key0[g] + (uint32_t)a.key[g][c], (uint32_t)(a.val[g] ? a.val[g][j] : (int32_t)j));
+}
+constexpr int kSortItems = 4096;               // items per block: four waves of 1024 consecutive ones
+__global__ __launch_bounds__(256) void sort_count_kernel(const uint2 *items, int64_t n, int shift, int32_t *hist, int n_blocks) {
+  __shared__ int cnt[256];
+  cnt[threadIdx.x] = 0;
+  __syncthreads();
+  const int64_t i0 = (int64_t)blockIdx.x * kSortItems;
+  for (int k = threadIdx.x; k < kSortItems; k += 256)
+    if (i0 + k < n) atomicAdd(&cnt[(items[i0 + k].x >> shift) & 255], 1);
+  __syncthreads();
+  hist[(size_t)threadIdx.x * n_blocks + blockIdx.x] = cnt[threadIdx.x];
+}
+// one block per digit: exclusive sums over the blocks, the digit's total to digit_total
+__global__ __launch_bounds__(256) void sort_scan_kernel(int32_t *hist, int n_blocks, int32_t *digit_total) {
+  __shared__ int2 ws[4];
+  int32_t *h = hist + (size_t)blockIdx.x * n_blocks;
+  int base = 0;
+  for (int i0 = 0; i0 < n_blocks; i0 += 256) {
+    const int i = i0 + threadIdx.x;
+    int2 sum;
+    const int2 x = block_scan_pair(make_int2(i < n_blocks ? h[i] : 0, 0), ws, sum);
+    if (i < n_blocks) h[i] = base + x.x;
+    base += sum.x;
+  }
+  if (threadIdx.x == 0) digit_total[blockIdx.x] = base;
+}
+__global__ __launch_bounds__(256) void sort_scatter_kernel(const uint2 *items, int64_t n, int shift, const int32_t *hist,
+                                                           int n_blocks, const int32_t *digit_total, uint2 *out) {
+  __shared__ int off[4][256];
+  __shared__ int2 ws[4];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  for (int k = 0; k < 4; ++k) off[k][t] = 0;
+  __syncthreads();
+  const int64_t w0 = (int64_t)blockIdx.x * kSortItems + w * (kSortItems / 4);
+  for (int k = lane; k < kSortItems / 4; k += 64)
+    if (w0 + k < n) atomicAdd(&off[w][(items[w0 + k].x >> shift) & 255], 1);
+  __syncthreads();
+  int2 sum;
+  int base = block_scan_pair(make_int2(digit_total[t], 0), ws, sum).x + hist[(size_t)t * n_blocks + blockIdx.x];
+  for (int k = 0; k < 4; ++k) {                // thread t: digit t's first place for each wave
+    const int c = off[k][t];
+    off[k][t] = base;
+    base += c;
+  }
+  __syncthreads();
+  volatile int *mine = off[w];
+  for (int k = 0; k < kSortItems / 4; k += 64) {
+    const int64_t i = w0 + k + lane;
+    const bool in = i < n;
+    const uint2 x = in ? items[i] : make_uint2(0, 0);
+    const int d = (x.x >> shift) & 255;
+    unsigned long long same = __ballot(in);
+    for (int b = 0; b < 8; ++b) {
+      const unsigned long long m = __ballot((d >> b) & 1);
+      same &= (d >> b) & 1 ? m : ~m;
+    }
+    const int rank = __popcll(same & ((1ull << lane) - 1));
+    const int place = mine[d] + rank;
+    __builtin_amdgcn_wave_barrier();
+    if (in && rank == 0) mine[d] = place + __popcll(same);
+    __builtin_amdgcn_wave_barrier();
+    if (in) out[place] = x;
+  }
+}
+__global__ __launch_bounds__(256) void group_write_kernel(const GroupArgs a, const uint2 *items) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= a.item0[a.n]) return;
+  const int g = grouping_of(a, i);
+  const int64_t j = i - a.item0[g];
+  const int32_t k = (int32_t)(items[i].x - a.key0[g]);
+  const int32_t before = j > 0 ? (int32_t)(items[i - 1].x - a.key0[g]) : -1;
+  for (int32_t q = before + 1; q <= k; ++q) a.ptr[g][q] = (int32_t)j;
+  if (i + 1 == a.item0[g + 1])
+    for (int32_t q = k + 1; q <= (int32_t)(a.key0[g + 1] - a.key0[g]); ++q) a.ptr[g][q] = (int32_t)j + 1;
+  a.seg[g][j] = k;
+  a.out[g][j] = (int32_t)items[i].y;
+}
+
+// out[c, :] = in[from[c], :], rows of `pieces` 16-byte pieces: the states of a level's classes, which
+// split the classes of the level below
+__global__ __launch_bounds__(256) void expand_states_kernel(const f32x4 *in, const int32_t *from, int64_t n, int pieces,
+                                                            f32x4 *out) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n * pieces) return;
+  const int64_t c = i / pieces;
+  out[i] = in[(size_t)from[c] * pieces + (i - c * pieces)];
+}
+
+// The sum of a level's gradients per class of the level below (fp32), stored in the operand type; with
+// ymask (bf16) multiplied by the ReLU mask of the layer that produced those states, as
+// node_grad_gather_kernel does. One thread per eight columns.
+template <typename T>
+__global__ __launch_bounds__(256) void store_summed_kernel(const float *sum, int64_t n_rows, int D, const uint16_t *ymask, T *out) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n_rows * (D / 8)) return;
+  const int64_t n = i / (D / 8);
+  const int c = (int)(i - n * (D / 8)) * 8;
+  const f32x4 *p = (const f32x4 *)(sum + (size_t)n * D + c);
+  const f32x4 lo4 = p[0], hi4 = p[1];
+  float v[8];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) { v[j] = lo4[j]; v[4 + j] = hi4[j]; }
+  if (ymask) {
+    const size_t w = ((size_t)(n / 32) * (D / 32) + c / 32) * 64 + (size_t)(n % 32);
+    const unsigned lo = ymask[w] >> (4 * (c % 32 / 8)), hi = ymask[w + 32] >> (4 * (c % 32 / 8));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      v[j] = (lo >> j) & 1u ? v[j] : 0.f;
+      v[4 + j] = (hi >> j) & 1u ? v[4 + j] : 0.f;
+    }
+  }
+  store4<T>(out + (size_t)n * D + c, v);
+  store4<T>(out + (size_t)n * D + c + 4, v + 4);
+}

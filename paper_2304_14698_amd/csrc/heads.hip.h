@@ -189,11 +189,13 @@ __global__ __launch_bounds__(256) void rowmlp_kernel(const RowMlpArgs a) {
 // sums are added in group order, so the result does not depend on timing. pool [G, H] is also
 // stored (it is an input of the backward pass). Meant for batches of many graphs of moderate
 // size; a few huge graphs go through the generic segment-sum kernels instead.
+// MAPPED: row_of[n] is the row of h that holds node n's state (else row n).
 // (sm: (256 * VEC + 2 * widest layer) floats of LDS; all 256 threads of the block call it together.
 // UF = loads a thread keeps in flight: a thread adds its rows in the same order whatever UF is.)
-template <typename T, int VEC, int UF = 8>
+template <typename T, int VEC, int UF = 8, bool MAPPED = false>
 __device__ __forceinline__ void graph_readout_block(const T *h, const int n0, const int n1, const int g, int H,
-                                                    int mean, float *pool, const RowMlpArgs &mlp, float *sm) {
+                                                    int mean, float *pool, const RowMlpArgs &mlp, float *sm,
+                                                    const int32_t *row_of = nullptr) {
   const int t = threadIdx.x;
   const int tpr = H / VEC, ng = 256 / tpr, c0 = (t % tpr) * VEC, q = t / tpr;
   float acc[VEC];
@@ -203,7 +205,10 @@ __device__ __forceinline__ void graph_readout_block(const T *h, const int n0, co
   for (; n + (UF - 1) * ng < n1; n += UF * ng) {
     float v[UF][VEC];
 #pragma unroll
-    for (int i = 0; i < UF; ++i) RowVec<T, VEC>::load(h + (size_t)(n + i * ng) * H + c0, v[i]);
+    for (int i = 0; i < UF; ++i) {
+      const int r = n + i * ng;
+      RowVec<T, VEC>::load(h + (size_t)(MAPPED ? row_of[r] : r) * H + c0, v[i]);
+    }
 #pragma unroll
     for (int i = 0; i < UF; ++i)
 #pragma unroll
@@ -216,7 +221,8 @@ __device__ __forceinline__ void graph_readout_block(const T *h, const int n0, co
 #pragma unroll
     for (int i = 0; i < UF; ++i) {
       const int r = n + i * ng;
-      RowVec<T, VEC>::load(h + (size_t)(r < n1 ? r : n1 - 1) * H + c0, v[i]);
+      const int rc = r < n1 ? r : n1 - 1;
+      RowVec<T, VEC>::load(h + (size_t)(MAPPED ? row_of[rc] : rc) * H + c0, v[i]);
     }
 #pragma unroll
     for (int i = 0; i < UF; ++i)
@@ -242,12 +248,13 @@ __device__ __forceinline__ void graph_readout_block(const T *h, const int n0, co
   block_row_mlp(mlp, cur, nxt, part, g);
 }
 
-template <typename T, int VEC, int UF>
+template <typename T, int VEC, int UF, bool MAPPED>
 __global__ __launch_bounds__(256) void graph_readout_kernel(const T *h, const int32_t *graph_node_ptr, int H,
-                                                            int mean, float *pool, const RowMlpArgs mlp) {
+                                                            int mean, float *pool, const RowMlpArgs mlp,
+                                                            const int32_t *row_of) {
   extern __shared__ __align__(16) float sm[];   // [256 * VEC] partial sums, then the MLP's buffers
   const int g = blockIdx.x;
-  graph_readout_block<T, VEC, UF>(h, graph_node_ptr[g], graph_node_ptr[g + 1], g, H, mean, pool, mlp, sm);
+  graph_readout_block<T, VEC, UF, MAPPED>(h, graph_node_ptr[g], graph_node_ptr[g + 1], g, H, mean, pool, mlp, sm, row_of);
 }
 
 // pool[g, :] /= max(n_g, 1)  (mean readout)

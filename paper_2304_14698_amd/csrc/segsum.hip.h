@@ -58,6 +58,7 @@ struct SegsumArgs {
   const int32_t *perm;  // nullable: row r of the reduction reads vals row perm[r]
   const int32_t *ptr;   // [n_seg + 1]
   const int32_t *row_seg;  // nullable: segment of vals row i (saves the search for a sub-tile's first segment)
+  const int32_t *pos_seg;  // nullable: segment of row r of the reduction
   int64_t n_rows, n_seg;
   int D, RT;
   void *out;            // [n_seg, D], type TOut
@@ -83,7 +84,7 @@ __global__ __launch_bounds__(256) void segsum_kernel(const SegsumArgs a) {
       RowVec<TIn, VEC>::load(vals + (size_t)r * a.D + c, v[i]);
     }
   }
-  int seg = a.row_seg ? a.row_seg[a.perm ? (int64_t)a.perm[r0] : r0] : seg_of_row(a.ptr, a.n_seg, r0);
+  int seg = a.pos_seg ? a.pos_seg[r0] : a.row_seg ? a.row_seg[a.perm ? (int64_t)a.perm[r0] : r0] : seg_of_row(a.ptr, a.n_seg, r0);
   if (Put::kZeroEmpty && st == 0)                               // empty segments before row 0
     for (int s = 0; s < seg; ++s)
 #pragma unroll
@@ -201,7 +202,7 @@ __global__ __launch_bounds__(256) void edge_tile_fixup(const int32_t *tile_ptr, 
 // group of D / VEC lanes per node, each lane a 16-byte column slice; the edges are taken in index
 // order and summed in fp32, so the result is run-to-run identical. One pass over dh instead of
 // one per direction. recv_summed: d_recv is [n_nodes, D], already summed per receiver (rows of nodes
-// without in-edges hold nothing and are not read).
+// without in-edges hold nothing and are not read). out_ptr nullptr: the in-edges' part only.
 // masked_out (or nullptr: the sum replaces dh): the sum goes there instead, multiplied by the ReLU
 // mask of the layer that produced h -- ymask, the mask bits a forward kernel kept for its output
 // (see Mlp2Args: [tiles of 32 nodes][D / 32][64 lanes] words; VEC must be 8) -- which is the dz2 the
@@ -217,7 +218,7 @@ __global__ __launch_bounds__(256) void node_grad_gather_kernel(const T *d_recv, 
   const int64_t n = gt / lpr;
   if (n >= n_nodes) return;
   const int c = (int)(gt - n * lpr) * VEC;
-  const int e0 = in_ptr[n], e1 = in_ptr[n + 1], k0 = out_ptr[n], k1 = out_ptr[n + 1];
+  const int e0 = in_ptr[n], e1 = in_ptr[n + 1], k0 = out_ptr ? out_ptr[n] : 0, k1 = out_ptr ? out_ptr[n + 1] : 0;
   T *o = dh + (size_t)n * D + c;
   float acc[VEC], v[VEC];
   RowVec<T, VEC>::load(o, acc);

@@ -20,6 +20,7 @@
 #include "gat.hip.h"
 #include "wgrad.hip.h"
 #include "segsum.hip.h"
+#include "distinct.hip.h"
 #include "xrl_internal.h"
 
 using namespace xrl;
@@ -117,6 +118,8 @@ static const char *const kTimedNames[TK_COUNT] = {"embed", "edge", "edge_fixup",
                                                   "wgrad_edge", "wgrad_node", "wgrad_embed"};
 
 constexpr int64_t kMaxFusedSlots = 4096;   // largest G the single-launch heads kernel takes
+constexpr int kCounts = 3 * kMaxLevels;
+constexpr int64_t kPersistentMinRows = 8192;   // rows from which the persistent kernels replace the streaming one
 constexpr int64_t kClusterMaxGraphs = 256; // largest G of the one-launch encoder with several blocks per graph
 
 // Scratch of xrl_policy_value_static, the entry point that allocates nothing: per-state counters,
@@ -186,6 +189,12 @@ struct xrl_ctx {
   size_t bws_bytes = 0;
   // buffers of the last encode (inside ws)
   uint64_t id = 0;              // unique per context
+  int32_t *d_counts = nullptr;  // class and tile counts of the levels of a batch, and their copy in pinned memory
+  int32_t *h_counts = nullptr;
+  int64_t distinct_min_us = 300;   // smallest estimated encode that is reduced to distinct nodes (XRL_DISTINCT_MIN_US;
+                                   // 0 = every batch that can be, -1 = none)
+  int64_t min_rows_now = 0;     // p_min_rows, or 1 for the levels of a reduced batch
+  std::vector<void *> hx;       // last encode of a reduced batch: h of the level below, per class
   std::shared_ptr<DevicePool> blocks;
   uint64_t enc_batch = 0;
   bool enc_saved = false;
@@ -419,10 +428,38 @@ struct DevicePool {
   }
 };
 
+// A graph in receiver order as the message kernels take it: the batch's own, or that of the
+// representatives of one level (see distinct.hip.h).
+struct LevelGraph {
+  int64_t N = 0, E = 0, n_tiles = 0, receivers = 0;   // (receivers: nodes with in-edges, of a level)
+  const int32_t *in_ptr = nullptr, *in_src = nullptr, *in_dst = nullptr, *out_ptr = nullptr, *out_pos = nullptr;
+  const int32_t *tile_ptr = nullptr, *agg_src = nullptr, *node_op = nullptr;
+  const float *edge_feat = nullptr, *node_dense = nullptr;
+  // level l > 0: each class's class one level below, and the rows [edges | classes] grouped by the class
+  // one level below that their gradients go to
+  int32_t *self = nullptr, *down_ptr = nullptr, *down = nullptr, *down_seg = nullptr;
+};
+struct Distinct {
+  int levels = 0;                          // rounds + 1
+  LevelGraph lv[kMaxLevels];
+  int32_t *cls[kMaxLevels] = {};           // [N] class of each node at each level
+  int32_t *mem_ptr = nullptr, *mem_graph = nullptr, *mem_seg = nullptr;   // the batch's nodes by class at the last level
+  bool grouped = false;                    // the groupings the backward pass needs have been made
+  void *block[2] = {nullptr, nullptr};
+  size_t bytes[2] = {0, 0};
+};
+
 extern "C" void xrl_batch_release_device(xrl_batch *b) {
   if (b && b->dev.block) {
-    if (b->pool && !b->shared) b->pool->give(b->dev.block, b->dev.bytes);
-    else (void)hipFree(b->dev.block);
+    auto give = [&](void *p, size_t cap) {
+      if (!p) return;
+      if (b->pool && !b->shared) b->pool->give(p, cap);
+      else (void)hipFree(p);
+    };
+    if (b->distinct)
+      for (int i = 0; i < 2; ++i) give(b->distinct->block[i], b->distinct->bytes[i]);
+    b->distinct.reset();
+    give(b->dev.block, b->dev.bytes);
     b->pool.reset();
     b->dev = xrl_batch_device();
     b->uploaded = false;
@@ -689,7 +726,7 @@ int check_batch(const xrl_ctx *c, const xrl_batch *b, const char *who) {
 template <typename TIn, typename TOut, int VEC, int RT>
 int launch_segsum_rt(xrl_ctx *c, const void *vals, const int32_t *perm, const int32_t *ptr,
                      const int32_t *row_seg, int64_t n_rows, int64_t n_seg, int D, void *out,
-                     float *carry, const int32_t *vals_seg = nullptr) {
+                     float *carry, const int32_t *pos_seg = nullptr) {
   if (n_seg == 0) return XRL_OK;
   if (n_rows == 0) {
     static_assert(sizeof(TOut) == 4, "zero fill below writes fp32 words");
@@ -700,7 +737,8 @@ int launch_segsum_rt(xrl_ctx *c, const void *vals, const int32_t *perm, const in
   }
   SegsumArgs a;
   a.vals = vals; a.perm = perm; a.ptr = ptr; a.n_rows = n_rows; a.n_seg = n_seg;
-  a.row_seg = vals_seg ? vals_seg : (perm ? nullptr : row_seg);
+  a.row_seg = perm ? nullptr : row_seg;
+  a.pos_seg = pos_seg;
   a.D = D; a.RT = RT; a.out = out; a.carry = carry;
   const int64_t nsub = (n_rows + RT - 1) / RT;
   const int64_t threads = nsub * (D / VEC);
@@ -815,7 +853,7 @@ int launch_embedp(xrl_ctx *c, Mlp2Args &a) {
 inline bool mlp2p_applies(const xrl_ctx *c, int kind, const Mlp2Args &a) {
   const int H = c->m.hidden;
   if (c->elem != 2 || a.n_rows <= 0) return false;
-  if (a.n_rows < c->p_min_rows) return false;
+  if (a.n_rows < c->min_rows_now) return false;
   if (kind == KIND_EMBED) {
     const int pieces = 4 * 64 * embedp_waves(H);             // see embedp_kernel
     return a.nslabx <= 2 && a.nslabx * (H / 32) * 64 <= pieces && (H > 128 || a.Tn * (H / 4) <= pieces) &&
@@ -863,7 +901,7 @@ inline bool mlp2r_applies(const xrl_ctx *c, int kind, const Mlp2Args &a) {
   // barriers, and that kernel (mlp2p) measured faster (the template itself covers 64 and 128)
   const int H = c->m.hidden;
   if (c->elem != 2 || H != 256 || kind == KIND_EMBED || a.n_rows <= 0) return false;
-  if (a.n_rows < c->p_min_rows) return false;
+  if (a.n_rows < c->min_rows_now) return false;
   if (kind == KIND_EDGE && (a.De > 8 || a.nslab1 != 2 * (H / 16) + 1)) return false;   // edge attrs: half a slab
   return RTile<256, KIND_EDGE>::BYTES <= c->max_lds;
 }
@@ -951,15 +989,16 @@ int launch_heads(xrl_ctx *c, const xrl_batch *b, const float *d_emb, float *logi
   return XRL_OK;
 }
 
-// row_src (or nullptr): the row of src to export for each row, -1 = a row of zeros
+// row_src (or nullptr): the row of src to export for each row, -1 = a row of zeros; cls (or nullptr): the
+// row instead, where row_src does not say zeros
 template <typename T>
-__global__ void export_rows_kernel(const T *src, int64_t n_rows, int D, const int32_t *row_src, float *dst) {
+__global__ void export_rows_kernel(const T *src, int64_t n_rows, int D, const int32_t *row_src, const int32_t *cls, float *dst) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_rows * D) return;
-  if (row_src) {
+  if (row_src || cls) {
     const int64_t r = i / D;
-    const int32_t s = row_src[r];
-    dst[i] = s < 0 ? 0.f : (float)src[(int64_t)s * D + (i - r * D)];
+    const int64_t s = row_src && row_src[r] < 0 ? -1 : (cls ? cls[r] : row_src[r]);
+    dst[i] = s < 0 ? 0.f : (float)src[s * D + (i - r * D)];
     return;
   }
   dst[i] = (float)src[i];
@@ -1328,13 +1367,241 @@ __global__ void embed_input_rows_kernel(const float *edge_feat, const int32_t *i
   *(bf16x8 *)(X + (size_t)n * Kp + k0) = pack_bf16x8(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]);
 }
 
+// ---- batches reduced to distinct nodes (distinct.hip.h)
+LevelGraph batch_graph(const xrl_batch *b) {
+  const xrl_batch_device &d = b->dev;
+  LevelGraph g;
+  g.N = b->N; g.E = b->E; g.n_tiles = b->n_tiles;
+  g.in_ptr = d.in_ptr; g.in_src = d.in_src; g.in_dst = d.in_dst; g.out_ptr = d.out_ptr; g.out_pos = d.out_pos;
+  g.tile_ptr = d.tile_ptr; g.agg_src = d.agg_src; g.node_op = d.node_op; g.edge_feat = d.edge_feat; g.node_dense = d.node_dense;
+  return g;
+}
+Distinct *distinct_of(const xrl_ctx *c, const xrl_batch *b) {
+  return b->distinct && b->owner == c->id ? b->distinct.get() : nullptr;   // (levels and groupings are on its stream)
+}
+
+// The groupings of a reduced batch that the backward pass goes by.
+GroupArgs groupings(const xrl_batch *b, Distinct *q) {
+  GroupArgs a;
+  memset(&a, 0, sizeof(a));
+  int64_t item = 0, key = 0;
+  auto add = [&](int64_t items, int64_t keys, int64_t n_edges, const int32_t *src, const int32_t *k, const int32_t *val,
+                 int32_t *ptr, int32_t *seg, int32_t *out) {
+    a.item0[a.n] = item; a.key0[a.n] = (uint32_t)key;
+    a.n_edges[a.n] = n_edges; a.src[a.n] = src; a.key[a.n] = k; a.val[a.n] = val;
+    a.ptr[a.n] = ptr; a.seg[a.n] = seg; a.out[a.n] = out;
+    item += items; key += keys;
+    ++a.n;
+    a.item0[a.n] = item; a.key0[a.n] = (uint32_t)key;
+  };
+  const int R = q->levels - 1;
+  for (int l = 1; l <= R; ++l) {
+    LevelGraph &g = q->lv[l];
+    add(g.E + g.N, q->lv[l - 1].N, g.E, g.in_src, g.self, nullptr, g.down_ptr, g.down_seg, g.down);
+  }
+  add(b->N, q->lv[R].N, 0, nullptr, q->cls[R], b->dev.node_graph, q->mem_ptr, q->mem_seg, q->mem_graph);
+  return a;
+}
+size_t grouping_bytes(const xrl_batch *b, Distinct *q) {
+  const GroupArgs a = groupings(b, q);
+  const int64_t n = a.item0[a.n], nb = (n + kSortItems - 1) / kSortItems;
+  return 2 * align_up((size_t)n * 8) + align_up((size_t)nb * 256 * 4) + 1024;
+}
+int make_groupings(xrl_ctx *c, const xrl_batch *b, Distinct *q) {
+  const GroupArgs a = groupings(b, q);
+  const int64_t n = a.item0[a.n];
+  const int nb = (int)((n + kSortItems - 1) / kSortItems);
+  Bump bump{c->bws};
+  uint2 *x = bump.take<uint2>((size_t)n), *y = bump.take<uint2>((size_t)n);
+  int32_t *hist = bump.take<int32_t>((size_t)nb * 256), *total = bump.take<int32_t>(256);
+  const dim3 per_item((unsigned)((n + 255) / 256));
+  group_items_kernel<<<per_item, dim3(256), 0, c->stream>>>(a, x);
+  for (int shift = 0; shift < 32 && (a.key0[a.n] - 1) >> shift; shift += 8) {
+    sort_count_kernel<<<dim3((unsigned)nb), dim3(256), 0, c->stream>>>(x, n, shift, hist, nb);
+    sort_scan_kernel<<<dim3(256), dim3(256), 0, c->stream>>>(hist, nb, total);
+    sort_scatter_kernel<<<dim3((unsigned)nb), dim3(256), 0, c->stream>>>(x, n, shift, hist, nb, total, y);
+    std::swap(x, y);
+  }
+  group_write_kernel<<<per_item, dim3(256), 0, c->stream>>>(a, x);
+  HIP_TRY(hipGetLastError());
+  // (while a stream is being captured nothing runs: eager calls make them for themselves)
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  q->grouped = hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+  return XRL_OK;
+}
+
+// Whether a batch's levels are worth finding: its encode is estimated from the products' flops, and its
+// graphs have to look like rewrites of their state's first (half of the first 64 operators of a sample of
+// graphs the same, place by place). Finding the levels and the groupings takes 0.4 to 0.6 ms (70 k to
+// 700 k nodes), two waits included. Measured, us per step without / with, by the estimate (update
+// with a fresh minibatch, so that every step pays for it; 5 rounds, H = 128): 30 us 1008 / 1410, 108 us
+// 1912 / 1721, 216 us 3115 / 3874, 430 us 5380 / 3779; fp32 200 us 2265 / 2587. A batch kept over
+// the steps pays once: 430 us 622 / 337 forward only.
+bool distinct_pays(const xrl_ctx *c, const xrl_batch *b) {
+  const int H = c->m.hidden, R = c->m.rounds, De = c->m.d_edge;
+  if (c->distinct_min_us < 0 || c->m.round_kind != XRL_ROUND_MLP || R < 1 || R + 1 > kMaxLevels || b->G <= b->S || b->N < 1 || b->E < 1 || b->n_split_tiles > 0) return false;
+  const double flops = 2.0 * R * H * ((double)b->N * 3 * H + (double)b->E * (3 * H + De));
+  const double us = flops / (c->elem == 2 ? 7e8 : 7e7);                                 // (flops per us measured)
+  if (us < (double)c->distinct_min_us) return false;
+  if (b->from_edits || c->distinct_min_us == 0) return true;
+  const int32_t *sgp = b->at<int32_t>(b->o_state_graph_ptr), *gnp = b->at<int32_t>(b->o_graph_node_ptr), *op = b->at<int32_t>(b->o_node_op);
+  const int64_t step = std::max<int64_t>(1, b->G / 64);
+  int64_t same = 0, seen = 0, s = 0;
+  for (int64_t g = 0; g < b->G; g += step) {
+    while (sgp[s + 1] <= g) ++s;
+    const int64_t f = sgp[s];
+    if (g == f) continue;
+    const int n = std::min(64, std::min(gnp[g + 1] - gnp[g], gnp[f + 1] - gnp[f]));
+    for (int i = 0; i < n; ++i) same += op[gnp[g] + i] == op[gnp[f] + i];
+    seen += 64;
+  }
+  return 2 * same >= seen;
+}
+
+// Finds the levels' classes, reads back how many there are, and, if that is few enough, makes the levels'
+// graphs. Two waits for the stream (the counts of classes, then of tiles).
+int find_distinct(xrl_ctx *c, xrl_batch *b) {
+  const int R = c->m.rounds, L = R + 1, De = c->m.d_edge, Dd = c->m.n_node_dense;
+  const int64_t N = b->N, E = b->E;
+  const xrl_batch_device &d = b->dev;
+  uint32_t slots = 1024;
+  while (slots < (uint64_t)N + N / 2) slots *= 2;
+  const int nb = (int)((N + kScanItems - 1) / kScanItems);
+  auto q = std::make_shared<Distinct>();
+  q->levels = L;
+  auto take = [&](int i, size_t bytes) -> char * {
+    if (c->blocks->take(bytes, &q->block[i], &q->bytes[i]) == hipSuccess) return (char *)q->block[i];
+    (void)hipGetLastError();
+    q->block[i] = nullptr;
+    return nullptr;
+  };
+  auto drop = [&]() {
+    for (int i = 0; i < 2; ++i)
+      if (q->block[i]) c->blocks->give(q->block[i], q->bytes[i]);
+  };
+  const size_t n_bytes = align_up((size_t)N * 4);
+  char *cls_block = take(0, n_bytes * L);
+  if (!cls_block) return XRL_OK;                            // (no memory for it: the batch is used as it is)
+  const size_t scratch = align_up((size_t)slots * 8) + 2 * n_bytes + align_up((size_t)nb * 8) +
+                         (n_bytes + align_up((size_t)(N + 1) * 4)) * L;
+  int rc = ensure_bws(c, scratch);
+  if (rc) { drop(); return rc == XRL_ERR_OOM ? XRL_OK : rc; }
+  Bump bump{c->bws};
+  ClassArgs a;
+  memset(&a, 0, sizeof(a));
+  a.N = N; a.in_ptr = d.in_ptr; a.in_src = d.in_src; a.node_op = d.node_op;
+  a.edge_feat = (const uint32_t *)d.edge_feat; a.node_dense = (const uint32_t *)d.node_dense; a.De = De; a.Dd = Dd;
+  a.table = bump.take<unsigned long long>(slots); a.mask = slots - 1;
+  a.state_graph_ptr = d.state_graph_ptr; a.graph_node_ptr = d.graph_node_ptr;
+  a.slot = bump.take<int32_t>((size_t)N); a.rep = bump.take<int32_t>((size_t)N); a.block_sum = bump.take<int2>((size_t)nb);
+  std::vector<int32_t *> reps(L), ptr(L);
+  const dim3 per_node((unsigned)((N + 255) / 256)), per_block((unsigned)nb), b256(256);
+  for (int l = 0; l < L; ++l) {
+    a.prev = l > 0 ? q->cls[l - 1] : nullptr;
+    a.cls = q->cls[l] = (int32_t *)(cls_block + n_bytes * l);
+    a.reps = reps[l] = bump.take<int32_t>((size_t)N);
+    a.ptr = ptr[l] = bump.take<int32_t>((size_t)N + 1);
+    a.totals = c->d_counts + 2 * l;
+    a.receivers = c->d_counts + 2 * kMaxLevels + l;
+    class_clear_kernel<<<dim3((slots + 255) / 256), b256, 0, c->stream>>>(a.table, slots);
+    class_insert_first_kernel<<<dim3((unsigned)b->S), b256, 0, c->stream>>>(a);
+    class_insert_kernel<<<per_node, b256, 0, c->stream>>>(a);
+    class_verify_kernel<<<per_block, b256, 0, c->stream>>>(a);
+    class_scan_kernel<<<dim3(1), b256, 0, c->stream>>>(a, nb);
+    class_number_kernel<<<per_block, b256, 0, c->stream>>>(a);
+    class_of_kernel<<<per_node, b256, 0, c->stream>>>(a);
+  }
+  auto read_counts = [&](int n) -> int {
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipMemcpyAsync(c->h_counts, c->d_counts, sizeof(int32_t) * n, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    return XRL_OK;
+  };
+  if ((rc = read_counts(2 * L))) { drop(); return rc; }
+  int64_t sumE = 0, sumN = 0;
+  for (int l = 0; l < L; ++l) {
+    q->lv[l].N = c->h_counts[2 * l];
+    q->lv[l].E = c->h_counts[2 * l + 1];
+    if (l > 0) { sumE += q->lv[l].E; sumN += q->lv[l].N; }
+  }
+  // (a level costs a copy of its states more, so a quarter of the edges has to go)
+  if (4 * (sumE + sumN) > 3 * R * (E + N) && c->distinct_min_us != 0) { drop(); return XRL_OK; }
+  // ---- the levels' graphs
+  size_t off = 0;
+  auto plan = [&](size_t bytes) { const size_t o = off; off += align_up(bytes + 16); return o; };
+  struct Off { size_t ptr, src, dst, agg, self, op, dense, feat, tile, dptr, down, dseg; } o[kMaxLevels];
+  TileLevels tl;
+  memset(&tl, 0, sizeof(tl));
+  tl.n_levels = R;
+  int chunks = 0;
+  for (int l = 0; l < L; ++l) {
+    const int64_t n = q->lv[l].N, e = q->lv[l].E;
+    o[l].ptr = plan((n + 1) * 4);
+    o[l].agg = plan(n * 4);
+    o[l].feat = plan((size_t)e * De * 4);
+    if (l == 0) {
+      o[l].op = plan(n * 4);
+      o[l].dense = plan((size_t)n * Dd * 4);
+      continue;
+    }
+    const int nc = (int)((e + kTileChunk - 1) / kTileChunk);
+    tl.chunk0[l - 1] = chunks;
+    tl.n_edges[l - 1] = (int32_t)e;
+    chunks += nc;
+    tl.chunk0[l] = chunks;
+    o[l].src = plan(e * 4); o[l].dst = plan(e * 4); o[l].self = plan(n * 4);
+    o[l].tile = plan((e / 16 + 2 * nc + 4) * 4);
+    o[l].dptr = plan((q->lv[l - 1].N + 1) * 4); o[l].down = plan((e + n) * 4); o[l].dseg = plan((e + n) * 4);
+  }
+  const size_t o_mptr = plan((q->lv[R].N + 1) * 4), o_mgraph = plan(N * 4), o_mseg = plan(N * 4);
+  const size_t o_cuts = plan((size_t)chunks * kTileChunkMax * 4), o_count = plan((size_t)(chunks + 1) * 4);
+  char *blk = take(1, off);
+  if (!blk) { drop(); return XRL_OK; }
+  for (int l = 0; l < L; ++l) {
+    LevelGraph &g = q->lv[l];
+    LevelFillArgs f;
+    memset(&f, 0, sizeof(f));
+    auto at = [&](size_t x) { return (int32_t *)(blk + x); };
+    f.n_cls = g.N; f.n_edges = g.E; f.reps = reps[l]; f.ptr = ptr[l]; f.cls = q->cls[l]; f.prev = l > 0 ? q->cls[l - 1] : nullptr;
+    f.in_ptr = d.in_ptr; f.in_src = d.in_src; f.node_op = d.node_op; f.edge_feat = d.edge_feat; f.node_dense = d.node_dense;
+    f.De = De; f.Dd = Dd; f.receivers = c->d_counts + 2 * kMaxLevels + l;
+    f.o_ptr = at(o[l].ptr); f.o_agg_src = at(o[l].agg); f.o_feat = (float *)(blk + o[l].feat);
+    if (l == 0) { f.o_op = at(o[l].op); f.o_dense = (float *)(blk + o[l].dense); }
+    else { f.o_src = at(o[l].src); f.o_dst = at(o[l].dst); f.o_self = at(o[l].self); }
+    level_fill_kernel<<<dim3((unsigned)((g.N + 255) / 256)), b256, 0, c->stream>>>(f);
+    g.in_ptr = f.o_ptr; g.in_src = f.o_src; g.in_dst = f.o_dst; g.agg_src = f.o_agg_src; g.edge_feat = f.o_feat;
+    g.node_op = f.o_op; g.node_dense = f.o_dense; g.self = f.o_self;
+    if (l == 0) continue;
+    g.down_ptr = at(o[l].dptr); g.down = at(o[l].down); g.down_seg = at(o[l].dseg);
+    g.tile_ptr = at(o[l].tile);
+    tl.ptr[l - 1] = g.in_ptr; tl.dst[l - 1] = g.in_dst; tl.tile_ptr[l - 1] = at(o[l].tile);
+  }
+  q->mem_ptr = (int32_t *)(blk + o_mptr); q->mem_graph = (int32_t *)(blk + o_mgraph); q->mem_seg = (int32_t *)(blk + o_mseg);
+  tl.cuts = (int32_t *)(blk + o_cuts); tl.count = (int32_t *)(blk + o_count); tl.totals = c->d_counts;
+  tile_cut_kernel<<<dim3((unsigned)chunks), b256, 0, c->stream>>>(tl);
+  tile_scan_kernel<<<dim3((unsigned)R), b256, 0, c->stream>>>(tl);
+  tile_write_kernel<<<dim3((unsigned)chunks), b256, 0, c->stream>>>(tl);
+  if ((rc = read_counts(kCounts))) { drop(); return rc; }
+  for (int l = 0; l < L; ++l) {
+    if (l > 0) q->lv[l].n_tiles = c->h_counts[l - 1];
+    q->lv[l].receivers = c->h_counts[2 * kMaxLevels + l];
+  }
+  b->distinct = q;
+  return XRL_OK;
+}
+
 template <typename T>
 int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, float *dweights) {
   const xrl_model_desc &m = c->m;
   const int H = m.hidden, R = m.rounds, De = m.d_edge, Dg = m.d_global;
   const int64_t N = b->N, E = b->E, G = b->G;
-  const int64_t M = N > E ? N : E;
   const xrl_batch_device &d = b->dev;
+  Distinct *q = distinct_of(c, b);
+  const LevelGraph whole = batch_graph(b);
+  auto lev = [&](int l) -> const LevelGraph & { return q ? q->lv[l] : whole; };
+  int64_t maxN = 0, maxE = 0;
+  for (int l = 0; l <= R; ++l) { maxN = std::max(maxN, lev(l).N); maxE = std::max(maxE, lev(l).E); }
+  const int64_t M = std::max(maxN, maxE), N0 = lev(0).N;
   // ---- scratch plan
   size_t need = 0;
   auto acc = [&](size_t bytes) { need += align_up(bytes); };
@@ -1343,39 +1610,67 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   // (edge tiles end at receiver boundaries unless a receiver has more than 32 in-edges)
   const bool fold = kept && b->n_split_tiles == 0;
   for (int i = 0; i < (kept ? 2 : 3); ++i) acc((size_t)M * H * sizeof(T));      // (z1,) dz1, dz2
-  acc((size_t)E * H * sizeof(T));                                  // per-edge d h_sender
+  acc((size_t)(maxE + (q ? maxN : 0)) * H * sizeof(T));            // per-edge d h_sender; a reduced batch: dh behind it
   acc((size_t)M * H * sizeof(T));                                  // d h_receiver: per edge, or summed per receiver
-  for (int i = 0; i < 3; ++i) acc((size_t)N * H * sizeof(T));      // dh (two buffers), dagg
+  for (int i = 0; i < 3; ++i) acc((size_t)maxN * H * sizeof(T));   // dh (two buffers), dagg
   // bf16: the node-update layer's input rows are written out for its weight gradient, Kp columns
   const int Kx = De + m.n_op_types + m.n_node_dense, Kp = (Kx + 7) / 8 * 8;
   const bool embed_rows = sizeof(T) == 2 && N > 0;
-  if (embed_rows) acc((size_t)N * Kp * 2);
+  if (embed_rows) acc((size_t)N0 * Kp * 2);
   const size_t part = std::max(wgrad_partial_floats(M, 2 * H + De, H, c->n_cu), wgrad_partial_floats(M, H, H, c->n_cu));
   acc(part * 4);
   acc((size_t)G * H * 4); acc((size_t)G * H * 4); acc((size_t)G * (H + Dg) * 4);
   const bool gat = m.round_kind == XRL_ROUND_GAT;
   if (gat) {                                                       // softmax weights and score gradients
-    for (int i = 0; i < 2; ++i) acc((size_t)E * 4);
-    for (int i = 0; i < 4; ++i) acc((size_t)N * 4);
+    for (int i = 0; i < 2; ++i) acc((size_t)maxE * 4);
+    for (int i = 0; i < 4; ++i) acc((size_t)maxN * 4);
+  }
+  // a reduced batch: fp32 sums per class, their carries, the pool's gradient per graph; and, the first
+  // time, the sort that makes the groupings these sums go by (in the same place)
+  size_t sort_bytes = 0;
+  const size_t o_reduced = need;
+  if (q) {
+    acc((size_t)maxN * H * 4);
+    acc((size_t)((std::max(N, maxE + maxN) + 15) / 16) * 2 * H * 4);
+    acc((size_t)G * H * 4);
+    sort_bytes = q->grouped ? 0 : grouping_bytes(b, q);
+    need = std::max(need, sort_bytes);
   }
   int rc = ensure_bws(c, need);
   if (rc) return rc;
+  if (q && !q->grouped && (rc = make_groupings(c, b, q))) return rc;
   Bump bump{c->bws};
   T *z1 = kept ? nullptr : bump.take<T>((size_t)M * H);
   T *dz1 = bump.take<T>((size_t)M * H), *dz2 = bump.take<T>((size_t)M * H);
-  T *dsrc = bump.take<T>((size_t)E * H), *ddst = bump.take<T>((size_t)M * H);
-  T *dhA = bump.take<T>((size_t)N * H), *dhB = bump.take<T>((size_t)N * H);
-  T *dagg = bump.take<T>((size_t)N * H);
-  bf16_t *xrows = embed_rows ? bump.take<bf16_t>((size_t)N * Kp) : nullptr;
+  T *dsrc = bump.take<T>((size_t)(maxE + (q ? maxN : 0)) * H), *ddst = bump.take<T>((size_t)M * H);
+  T *dhA = bump.take<T>((size_t)maxN * H), *dhB = bump.take<T>((size_t)maxN * H);
+  T *dagg = bump.take<T>((size_t)maxN * H);
+  bf16_t *xrows = embed_rows ? bump.take<bf16_t>((size_t)N0 * Kp) : nullptr;
   float *partial = bump.take<float>(part);
   float *rdz[3] = {bump.take<float>((size_t)G * H), bump.take<float>((size_t)G * H), nullptr};
   float *rdx = bump.take<float>((size_t)G * (H + Dg));
   float *g_ale = nullptr, *g_due = nullptr, *g_als = nullptr, *g_dus = nullptr, *g_dss = nullptr, *g_dsd = nullptr;
   if (gat) {
-    g_ale = bump.take<float>((size_t)E); g_due = bump.take<float>((size_t)E);
-    g_als = bump.take<float>((size_t)N); g_dus = bump.take<float>((size_t)N);
-    g_dss = bump.take<float>((size_t)N); g_dsd = bump.take<float>((size_t)N);
+    g_ale = bump.take<float>((size_t)maxE); g_due = bump.take<float>((size_t)maxE);
+    g_als = bump.take<float>((size_t)maxN); g_dus = bump.take<float>((size_t)maxN);
+    g_dss = bump.take<float>((size_t)maxN); g_dsd = bump.take<float>((size_t)maxN);
   }
+  bump.off = o_reduced;
+  float *csum = q ? bump.take<float>((size_t)maxN * H) : nullptr;
+  float *ccarry = q ? bump.take<float>((size_t)((std::max(N, maxE + maxN) + 15) / 16) * 2 * H) : nullptr;
+  float *dpool_rows = q ? bump.take<float>((size_t)G * H) : nullptr;
+  constexpr int PV = 16 / sizeof(T);
+  // the gradients of the rows `vals`, summed per segment (fp32) and stored: masked, as the dz2 of the layer
+  // that produced the segments' states, or as their dh
+  auto contract = [&](auto tag, const void *vals, const int32_t *perm, const int32_t *ptr, const int32_t *seg, int64_t rows,
+                      int64_t n_seg, const uint16_t *ymask, T *out) -> int {
+    using TIn = decltype(tag);
+    const int rc2 = launch_segsum_rt<TIn, float, 16 / sizeof(TIn), 16>(c, vals, perm, ptr, seg, rows, n_seg, H, csum, ccarry, seg);
+    if (rc2) return rc2;
+    store_summed_kernel<T><<<dim3((unsigned)((n_seg * (H / 8) + 255) / 256)), dim3(256), 0, c->stream>>>(csum, n_seg, H, ymask, out);
+    HIP_TRY(hipGetLastError());
+    return XRL_OK;
+  };
 
   // ---- global-update layer backward
   float *ract[3] = {c->ro_act[0], c->ro_act[1], nullptr};
@@ -1384,8 +1679,16 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   // The gradient w.r.t. the last node states is the pool's, the same row for every node of a graph.
   // From the kept forward, the first backward kernel reads it through the nodes' graph ids from a
   // [G, H] table (the kernel below with the graphs as its "nodes"); otherwise it is written out per node.
-  const bool dpool_table = kept && !gat;
-  if (N > 0) {
+  const bool dpool_table = kept && !gat && !q;
+  bool dz2_given = false;                  // dz2 of the next node-side layer down is in place already
+  if (q) {
+    // (a reduced batch: summed over each class's nodes of all graphs)
+    broadcast_dpool_kernel<float><<<dim3((unsigned)((G * (H / 4) + 255) / 256)), dim3(256), 0, c->stream>>>(
+        rdx, H + Dg, nullptr, d.graph_node_ptr, m.readout == XRL_READOUT_MEAN, G, H, dpool_rows);
+    const uint16_t *mask = kept ? c->ym_node[R - 1] : nullptr;
+    dz2_given = mask != nullptr;
+    if ((rc = contract(float(), dpool_rows, q->mem_graph, q->mem_ptr, q->mem_seg, N, lev(R).N, mask, mask ? dz2 : dhA))) return rc;
+  } else if (N > 0) {
     if (dpool_table)
       broadcast_dpool_kernel<T><<<dim3((unsigned)((G * (H / 4) + 255) / 256)), dim3(256), 0, c->stream>>>(
           rdx, H + Dg, nullptr, d.graph_node_ptr, m.readout == XRL_READOUT_MEAN, G, H, dhA);
@@ -1398,17 +1701,12 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   Mlp2BwdArgs a;
   memset(&a, 0, sizeof(a));
   a.De = De; a.Tn = m.n_op_types; a.Dd = m.n_node_dense;
-  a.in_ptr = d.in_ptr; a.in_src = d.in_src; a.in_dst = d.in_dst;
-  a.edge_feat = d.edge_feat; a.node_op = d.node_op; a.node_dense = d.node_dense;
   a.z1 = z1; a.dz1 = dz1; a.dz2 = dz2;
   WgradArgs wa;
   memset(&wa, 0, sizeof(wa));
-  wa.in_ptr = d.in_ptr; wa.in_src = d.in_src; wa.in_dst = d.in_dst; wa.edge_feat = d.edge_feat;
   // (after a forward of one launch per layer the received sums of nodes without in-edges were never written)
   a.zero_row = wa.zero_row = c->zero_row;
-  wa.agg_src = d.agg_src;
-  if (c->agg_skip) a.agg_src = d.agg_src;
-  wa.node_op = d.node_op; wa.node_dense = d.node_dense; wa.De = De; wa.Tn = m.n_op_types; wa.Dd = m.n_node_dense;
+  wa.De = De; wa.Tn = m.n_op_types; wa.Dd = m.n_node_dense;
   wa.partial = partial;
   auto set_w = [&](const EncMlp &e) {
     a.W1s = e.W1s; a.W2s = e.W2s; a.W2bt = e.W2bt; a.W1bt = e.W1bt; a.b1 = e.b1; a.b2 = e.b2; a.nslab1 = e.nslab1;
@@ -1425,14 +1723,19 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   // gradients through one fused MLP: from what the forward kept, else with its first layer recomputed
   Mlp2BwdzArgs za;
   memset(&za, 0, sizeof(za));
-  za.in_dst = d.in_dst; za.dz1 = dz1; za.dz2 = dz2;
-  za.tile_ptr = d.tile_ptr; za.n_tiles = b->n_tiles;
-  bool dz2_given = false;
+  za.dz1 = dz1; za.dz2 = dz2;
+  auto set_graph = [&](const LevelGraph &g) {
+    a.in_ptr = wa.in_ptr = g.in_ptr; a.in_src = wa.in_src = g.in_src; a.in_dst = wa.in_dst = za.in_dst = g.in_dst;
+    a.edge_feat = wa.edge_feat = g.edge_feat; a.node_op = wa.node_op = g.node_op; a.node_dense = wa.node_dense = g.node_dense;
+    wa.agg_src = za.agg_src = g.agg_src;
+    a.agg_src = c->agg_skip ? g.agg_src : nullptr;
+    za.tile_ptr = g.tile_ptr; za.n_tiles = g.n_tiles;
+  };
   auto mlp_bwd = [&](int kind, const EncMlp &e, const uint16_t *z1mask, const uint16_t *ymask) -> int {
     if constexpr (sizeof(T) == 2) {
       if (kept) {
         za.n_rows = a.n_rows; za.W2bt = e.W2bt; za.W1bt = e.W1bt; za.dy = a.dy;
-        za.z1mask = z1mask; za.ymask = ymask; za.dx_a = a.dx_a; za.dx_b = a.dx_b; za.agg_src = d.agg_src;
+        za.z1mask = z1mask; za.ymask = ymask; za.dx_a = a.dx_a; za.dx_b = a.dx_b;
         za.dy_index = (dy_by_graph && kind != KIND_EDGE) ? d.node_graph : nullptr;
         dy_by_graph = false;
         const bool given = dz2_given && kind != KIND_EDGE;   // (the gather of the round above left dz2 in place)
@@ -1443,7 +1746,6 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
     }
     return launch_mlp2_bwd<T>(c, kind, a);
   };
-  constexpr int PV = 16 / sizeof(T);
   for (int r = R - 1; r >= 0 && gat; --r) {
     // attention round r+1: input h[r], saved z (in the agg slot) and scores, output h[r+1]; upstream dhA
     if (N == 0) break;
@@ -1489,23 +1791,29 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   }
   for (int r = R - 1; r >= 0 && !gat; --r) {
     // node MLP of round r+1: inputs h[r], agg[r+1]; output h[r+1]; upstream dhA
+    const LevelGraph &g = lev(r + 1);
+    const int64_t N = g.N, E = g.E;
+    const void *h_in = q ? c->hx[r + 1] : c->h[r];
+    set_graph(g);
+    if (q) dhB = dsrc + (size_t)E * H;
     set_w(c->node[r]);
-    a.n_rows = N; a.h = c->h[r]; a.agg = c->agg[r + 1]; a.y = c->h[r + 1]; a.dy = dhA;
+    a.n_rows = N; a.h = h_in; a.agg = c->agg[r + 1]; a.y = c->h[r + 1]; a.dy = dhA;
     a.dx_a = dhB; a.dx_b = dagg;
     { Timed t(c, TK_BWD_NODE); rc = mlp_bwd(KIND_NODE, c->node[r], kept ? c->zm_node[r] : nullptr, kept ? c->ym_node[r] : nullptr); }
     if (rc) return rc;
-    wa.h = c->h[r]; wa.agg = c->agg[r + 1];
+    wa.h = h_in; wa.agg = c->agg[r + 1];
     if ((rc = wgrads(WG_NODE, N, 2 * H, c->L.node[r], kept ? c->z1_node[r] : nullptr))) return rc;
     // edge MLP of round r+1: upstream = dagg gathered by receiver
     set_w(c->edge[r]);
-    a.n_rows = E; a.h = c->h[r]; a.agg = nullptr; a.y = nullptr; a.dy = dagg;
+    a.n_rows = E; a.h = h_in; a.agg = nullptr; a.y = nullptr; a.dy = dagg;
     a.dx_a = dsrc; a.dx_b = ddst;
     { Timed t(c, TK_BWD_EDGE); rc = mlp_bwd(KIND_EDGE, c->edge[r], kept ? c->zm_edge[r] : nullptr, kept ? c->ym_edge[r] : nullptr); }
     if (rc) return rc;
     if ((rc = wgrads(WG_EDGE, E, 2 * H + De, c->L.edge[r], kept ? c->z1_edge[r] : nullptr))) return rc;
     // dh[r] = d(node MLP)/dh + sum over in-edges of d h_receiver + sum over out-edges of d h_sender
+    const uint16_t *below = kept ? (r > 0 ? c->ym_node[r - 1] : c->ym_embed) : nullptr;
+    Timed timed(c, TK_GRAD_GATHER);
     if (E > 0) {
-      Timed t(c, TK_GRAD_GATHER);
       const int64_t threads = N * (H / PV);
       // from the kept forward: the sum leaves multiplied by the output mask of the layer that
       // produced h[r] (the node MLP of the round below, or the node-update layer), as that layer's
@@ -1513,32 +1821,40 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
       T *masked_out = nullptr;
       const uint16_t *mask = nullptr;
       if constexpr (sizeof(T) == 2) {
-        if (kept) { masked_out = dz2; mask = r > 0 ? c->ym_node[r - 1] : c->ym_embed; }
+        if (kept && !q) { masked_out = dz2; mask = below; }
       }
       node_grad_gather_kernel<T, PV><<<dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, c->stream>>>(
-          ddst, dsrc, d.in_ptr, d.out_ptr, d.out_pos, N, H, dhB, fold ? 1 : 0, masked_out, mask);
+          ddst, dsrc, g.in_ptr, g.out_ptr, g.out_pos, N, H, dhB, fold ? 1 : 0, masked_out, mask);
       dz2_given = masked_out != nullptr;
     }
-    std::swap(dhA, dhB);
+    if (q) {
+      // ... and on to the classes of the level below, masked as above
+      dz2_given = below != nullptr;
+      if ((rc = contract(T(), dsrc, g.down, g.down_ptr, g.down_seg, E + N, lev(r).N, below, below ? dz2 : dhA))) return rc;
+    } else {
+      std::swap(dhA, dhB);
+    }
   }
   // ---- node-update layer backward (weights only: its inputs are data)
+  const LevelGraph &g0 = lev(0);
+  set_graph(g0);
   set_w(c->embed);
-  a.n_rows = N; a.h = nullptr; a.agg = nullptr; a.y = c->h[0]; a.dy = dhA; a.dx_a = nullptr; a.dx_b = nullptr;
+  a.n_rows = N0; a.h = nullptr; a.agg = nullptr; a.y = c->h[0]; a.dy = dhA; a.dx_a = nullptr; a.dx_b = nullptr;
   { Timed t(c, TK_BWD_EMBED); rc = mlp_bwd(KIND_EMBED, c->embed, kept ? c->zm_embed : nullptr, kept ? c->ym_embed : nullptr); }
   if (rc) return rc;
   if constexpr (sizeof(T) == 2) {
     // first layer: dW1 = X^T dz1 on the transpose-read kernel, X written out once; its Kx real rows
     // and the bias row (row Kp of the slices' partial tiles) are reduced separately
     Timed t(c, TK_WGRAD_EMBED);
-    const int64_t threads = N * (Kp / 8);
+    const int64_t threads = N0 * (Kp / 8);
     embed_input_rows_kernel<<<dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, c->stream>>>(
-        d.edge_feat, d.in_ptr, d.node_op, d.node_dense, N, De, m.n_op_types, m.n_node_dense, Kp, xrows);
-    wa.n_rows = N; wa.Ka = Kp; wa.dZ = dz1; wa.A = xrows;
+        g0.edge_feat, g0.in_ptr, g0.node_op, g0.node_dense, N0, De, m.n_op_types, m.n_node_dense, Kp, xrows);
+    wa.n_rows = N0; wa.Ka = Kp; wa.dZ = dz1; wa.A = xrows;
     if ((rc = launch_wgrad_embed_rows<T>(c, wa, Kx, dweights + c->L.embed.w[0], dweights + c->L.embed.b[0]))) return rc;
     wa.Ka = H; wa.dZ = dz2; wa.A = kept ? c->z1_embed : z1;
     if ((rc = launch_wgrad<T>(c, WG_PLAIN, wa, dweights + c->L.embed.w[1], dweights + c->L.embed.b[1]))) return rc;
   } else {
-    if ((rc = wgrads(WG_EMBED, N, Kx, c->L.embed, nullptr))) return rc;
+    if ((rc = wgrads(WG_EMBED, N0, Kx, c->L.embed, nullptr))) return rc;
   }
   HIP_TRY(hipGetLastError());
   return XRL_OK;
@@ -1549,16 +1865,25 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   const xrl_model_desc &m = c->m;
   const int H = m.hidden, R = m.rounds, De = m.d_edge;
   const int64_t N = b->N, E = b->E, G = b->G;
-  const int64_t n_tiles = b->n_tiles;
+  const Distinct *q = distinct_of(c, b);
+  const LevelGraph whole = batch_graph(b);
+  auto lev = [&](int l) -> const LevelGraph & { return q ? q->lv[l] : whole; };
+  c->min_rows_now = q && c->p_min_rows <= kPersistentMinRows ? 1 : c->p_min_rows;
   // ---- workspace plan
   const int nh = save ? R + 1 : (R > 0 ? 2 : 1), nagg = save ? R : (R > 0 ? 1 : 0);
+  int64_t maxN = 0, max_tiles = 0;
+  for (int l = 0; l <= R; ++l) { maxN = std::max(maxN, lev(l).N); max_tiles = std::max(max_tiles, lev(l).n_tiles); }
+  auto h_rows = [&](int i) { return (size_t)(save ? lev(i).N : maxN); };         // i-th buffer of h
+  auto a_rows = [&](int i) { return (size_t)(save ? lev(i + 1).N : maxN); };     // ... of the received sums and of hx
   size_t need = 0;
   auto acc = [&](size_t bytes) { need += align_up(bytes); };
   constexpr int PV = 16 / sizeof(T);
   const bool gat = m.round_kind == XRL_ROUND_GAT;
-  for (int i = 0; i < nh + nagg; ++i) acc((size_t)N * H * sizeof(T));   // (GAT: the agg slot holds z)
+  for (int i = 0; i < nh; ++i) acc(h_rows(i) * H * sizeof(T));
+  for (int i = 0; i < nagg; ++i) acc(a_rows(i) * H * sizeof(T));        // (GAT: the agg slot holds z)
+  for (int i = 0; q && i < nagg; ++i) acc(a_rows(i) * H * sizeof(T));
   const xrl_batch_device &d = b->dev;
-  const bool resident_ok = !gat && H * sizeof(T) <= 256 && d.graph_tile_ptr && R <= kResidentMaxRounds;
+  const bool resident_ok = !gat && !q && H * sizeof(T) <= 256 && d.graph_tile_ptr && R <= kResidentMaxRounds;
   const int64_t graph_tiles = std::max<int64_t>((b->max_graph_nodes + 31) / 32, b->max_graph_tiles);
   // blocks per graph of the one-launch encoder: one while a graph's phase is a single pass of a
   // block's four waves; otherwise as many as give every tile of a phase a wave of its own, if
@@ -1581,27 +1906,30 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
       Mlp2Args t;
       memset(&t, 0, sizeof(t));
       t.De = De; t.Tn = m.n_op_types; t.Dd = m.n_node_dense;
-      t.n_rows = N; t.nslabx = c->embed.nslabx;
+      t.n_rows = lev(0).N; t.nslabx = c->embed.nslabx;
       keep = mlp2p_applies(c, KIND_EMBED, t);
       for (int r = 0; r < R && keep; ++r) {
-        t.n_rows = E; t.nslab1 = c->edge[r].nslab1;
+        t.n_rows = lev(r + 1).E; t.nslab1 = c->edge[r].nslab1;
         keep = keep && (mlp2r_applies(c, KIND_EDGE, t) || mlp2p_applies(c, KIND_EDGE, t));
-        t.n_rows = N; t.nslab1 = c->node[r].nslab1;
+        t.n_rows = lev(r + 1).N; t.nslab1 = c->node[r].nslab1;
         keep = keep && (mlp2r_applies(c, KIND_NODE, t) || mlp2p_applies(c, KIND_NODE, t));
       }
     }
   }
-  const size_t ym_words = (size_t)n_tiles * (H / 32) * 64;            // 16-bit words of one edge MLP's mask bits (z1 or y)
-  const size_t nm_words = (size_t)((N + 31) / 32) * (H / 32) * 64;    // ... of a node-side MLP's
+  auto ym_words = [&](int l) { return (size_t)lev(l).n_tiles * (H / 32) * 64; };          // 16-bit words of one edge MLP's mask bits (z1 or y)
+  auto nm_words = [&](int l) { return (size_t)((lev(l).N + 31) / 32) * (H / 32) * 64; };  // ... of a node-side MLP's
   if (keep) {
-    for (int i = 0; i < R + 1; ++i) acc((size_t)N * H * sizeof(T));
-    for (int i = 0; i < R; ++i) { acc((size_t)E * H * sizeof(T)); acc(ym_words * 2); acc(ym_words * 2); }
-    for (int i = 0; i < 2 * (R + 1); ++i) acc(nm_words * 2);
+    for (int l = 0; l <= R; ++l) {
+      acc((size_t)lev(l).N * H * sizeof(T));
+      acc(nm_words(l) * 2); acc(nm_words(l) * 2);
+      if (l > 0) { acc((size_t)lev(l).E * H * sizeof(T)); acc(ym_words(l) * 2); acc(ym_words(l) * 2); }
+    }
   }
   const int n_gs = gat ? (save ? R : 1) : 0;                            // saved per round for the backward
-  for (int i = 0; i < 2 * n_gs; ++i) acc((size_t)N * 4);
-  const size_t carry_floats = std::max(std::max(segsum_carry_floats(E, De), segsum_carry_floats(N, H)),
-                                       (size_t)n_tiles * 2 * H);
+  for (int i = 0; i < 2 * n_gs; ++i) acc(a_rows(i / 2) * 4);
+  // (a reduced batch has few huge graphs at most: the carries of the readout's segment sum are not needed)
+  const size_t carry_floats = std::max(std::max(segsum_carry_floats(E, De), q && N <= 4096 * G ? 0 : segsum_carry_floats(N, H)),
+                                       (size_t)max_tiles * 2 * H);
   acc(carry_floats * 4);
   acc((size_t)G * H * 4);
   acc((size_t)G * H * 4);
@@ -1612,13 +1940,16 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   c->h.assign(R + 1, nullptr);
   c->agg.assign(R + 1, nullptr);
   std::vector<T *> hb(nh), ab(std::max(nagg, 1), nullptr);
-  for (int i = 0; i < nh; ++i) hb[i] = bump.take<T>((size_t)N * H);
-  for (int i = 0; i < nagg; ++i) ab[i] = bump.take<T>((size_t)N * H);
+  std::vector<T *> xb(std::max(nagg, 1), nullptr);
+  c->hx.assign(R + 1, nullptr);
+  for (int i = 0; i < nh; ++i) hb[i] = bump.take<T>(h_rows(i) * H);
+  for (int i = 0; i < nagg; ++i) ab[i] = bump.take<T>(a_rows(i) * H);
+  for (int i = 0; q && i < nagg; ++i) xb[i] = bump.take<T>(a_rows(i) * H);
   c->gat_ss.assign(R, nullptr);
   c->gat_sd.assign(R, nullptr);
   for (int i = 0; i < n_gs; ++i) {
-    c->gat_ss[i] = bump.take<float>((size_t)N);
-    c->gat_sd[i] = bump.take<float>((size_t)N);
+    c->gat_ss[i] = bump.take<float>(a_rows(i));
+    c->gat_sd[i] = bump.take<float>(a_rows(i));
   }
   c->carry = bump.take<float>(carry_floats);
   c->pool = bump.take<float>((size_t)G * H);
@@ -1630,16 +1961,16 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   c->ym_node.assign(R, nullptr); c->zm_node.assign(R, nullptr);
   c->z1_embed = nullptr; c->ym_embed = c->zm_embed = nullptr;
   if (keep) {
-    c->z1_embed = bump.take<T>((size_t)N * H);
-    c->zm_embed = bump.take<uint16_t>(nm_words);
-    c->ym_embed = bump.take<uint16_t>(nm_words);
+    c->z1_embed = bump.take<T>((size_t)lev(0).N * H);
+    c->zm_embed = bump.take<uint16_t>(nm_words(0));
+    c->ym_embed = bump.take<uint16_t>(nm_words(0));
     for (int r = 0; r < R; ++r) {
-      c->z1_node[r] = bump.take<T>((size_t)N * H);
-      c->z1_edge[r] = bump.take<T>((size_t)E * H);
-      c->zm_edge[r] = bump.take<uint16_t>(ym_words);
-      c->ym_edge[r] = bump.take<uint16_t>(ym_words);
-      c->zm_node[r] = bump.take<uint16_t>(nm_words);
-      c->ym_node[r] = bump.take<uint16_t>(nm_words);
+      c->z1_node[r] = bump.take<T>((size_t)lev(r + 1).N * H);
+      c->z1_edge[r] = bump.take<T>((size_t)lev(r + 1).E * H);
+      c->zm_edge[r] = bump.take<uint16_t>(ym_words(r + 1));
+      c->ym_edge[r] = bump.take<uint16_t>(ym_words(r + 1));
+      c->zm_node[r] = bump.take<uint16_t>(nm_words(r + 1));
+      c->ym_node[r] = bump.take<uint16_t>(nm_words(r + 1));
     }
   }
   c->enc_batch = b->id;
@@ -1649,15 +1980,19 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   Mlp2Args a;
   memset(&a, 0, sizeof(a));
   a.De = De; a.Tn = m.n_op_types; a.Dd = m.n_node_dense;
-  a.in_ptr = d.in_ptr; a.in_src = d.in_src; a.in_dst = d.in_dst;
-  a.edge_feat = d.edge_feat; a.node_op = d.node_op; a.node_dense = d.node_dense;
-  a.carry = c->carry; a.tile_ptr = d.tile_ptr; a.n_tiles = n_tiles; a.zero_row = c->zero_row;
+  auto set_graph = [&](const LevelGraph &g) {
+    a.in_ptr = g.in_ptr; a.in_src = g.in_src; a.in_dst = g.in_dst;
+    a.edge_feat = g.edge_feat; a.node_op = g.node_op; a.node_dense = g.node_dense;
+    a.tile_ptr = g.tile_ptr; a.n_tiles = g.n_tiles;
+  };
+  set_graph(lev(0));
+  a.carry = c->carry; a.zero_row = c->zero_row;
   auto set_w = [&](const EncMlp &e) {
     a.W1s = e.W1s; a.W2s = e.W2s; a.b1 = e.b1; a.b2 = e.b2; a.nslab1 = e.nslab1;
     a.W1x = e.W1x; a.nslabx = e.nslabx; a.table = e.table;
   };
   set_w(c->embed);
-  a.n_rows = N; a.out = hb[0];
+  a.n_rows = lev(0).N; a.out = hb[0];
   a.agg0 = ab[0]; a.n_agg = gat ? 0 : nagg; a.agg_stride = nagg > 1 ? (size_t)((char *)ab[1] - (char *)ab[0]) : 0;
   if (resident_batch) {
     // small batch: the whole encoder in one launch, one block per graph (rows of at most 256
@@ -1710,7 +2045,7 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   }
   // one launch per layer: the node MLPs (and whatever reads the received sums afterwards) take
   // zeros for nodes without in-edges through agg_src, so nobody has to write those rows
-  a.n_agg = 0; a.agg_src = d.agg_src;
+  a.n_agg = 0; a.agg_src = lev(0).agg_src;
   c->agg_skip = !gat;
   a.z1 = c->z1_embed; a.z1mask = c->zm_embed; a.ymask = c->ym_embed;
   { Timed t(c, TK_EMBED); rc = launch_mlp2<T>(c, KIND_EMBED, a); }
@@ -1721,6 +2056,16 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   for (int r = 0; r < R; ++r) {
     T *aggb = save ? ab[r] : ab[0];
     T *hnext = save ? hb[r + 1] : hb[(r + 1) & 1];
+    const LevelGraph &g = lev(r + 1);
+    const int64_t N = g.N, E = g.E;
+    if (q) {                           // the level's classes split those of the level below: a copy of the state each
+      T *x = save ? xb[r] : xb[0];
+      const int pieces = H / PV;
+      expand_states_kernel<<<dim3((unsigned)((N * pieces + 255) / 256)), dim3(256), 0, c->stream>>>(
+          (const f32x4 *)hcur, g.self, N, pieces, (f32x4 *)x);
+      c->hx[r + 1] = x;
+      hcur = x;
+    }
     if (gat) {                         // graph-attention reading of the round
       if (N > 0) {
         GatArgs ga;
@@ -1746,6 +2091,8 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
       hcur = hnext;
       continue;
     }
+    set_graph(g);
+    a.agg_src = g.agg_src;
     set_w(c->edge[r]);
     a.n_rows = E; a.h = hcur; a.out = aggb;
     a.z1 = c->z1_edge[r]; a.z1mask = c->zm_edge[r]; a.ymask = c->ym_edge[r];
@@ -1753,7 +2100,7 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
     if (rc) return rc;
     if (b->n_split_tiles > 0) {         // only a receiver with more than 32 in-edges spans tiles
       Timed t(c, TK_EDGE_FIXUP);
-      const int64_t fthreads = n_tiles * (H / 4);
+      const int64_t n_tiles = g.n_tiles, fthreads = n_tiles * (H / 4);
       edge_tile_fixup<T><<<dim3((unsigned)((fthreads + 255) / 256)), dim3(256), 0, c->stream>>>(
           d.tile_ptr, n_tiles, d.in_ptr, d.in_dst, H, c->carry, aggb);
     }
@@ -1774,13 +2121,18 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
     const RowMlpArgs ra = rowmlp_args(c, c->L.readout, true, c->pool, H, d.graph_global, m.d_global, G, d_emb,
                                       c->ro_act, &dmax);
     const size_t lds = (size_t)(256 * PV + 2 * dmax) * sizeof(float);
-    graph_readout_kernel<T, PV, 8><<<dim3((unsigned)G), dim3(256), lds, c->stream>>>(
-        hcur, d.graph_node_ptr, H, m.readout == XRL_READOUT_MEAN ? 1 : 0, c->pool, ra);
+    const int mean = m.readout == XRL_READOUT_MEAN ? 1 : 0;
+    if (q)
+      graph_readout_kernel<T, PV, 8, true><<<dim3((unsigned)G), dim3(256), lds, c->stream>>>(
+          hcur, d.graph_node_ptr, H, mean, c->pool, ra, q->cls[R]);
+    else
+      graph_readout_kernel<T, PV, 8, false><<<dim3((unsigned)G), dim3(256), lds, c->stream>>>(
+          hcur, d.graph_node_ptr, H, mean, c->pool, ra, nullptr);
     HIP_TRY(hipGetLastError());
     return XRL_OK;
   }
   { Timed t(c, TK_POOL);
-    rc = launch_segsum<T, float, PV>(c, hcur, nullptr, d.graph_node_ptr, d.node_graph, N, G, H, c->pool, c->carry); }
+    rc = launch_segsum<T, float, PV>(c, hcur, q ? q->cls[R] : nullptr, d.graph_node_ptr, d.node_graph, N, G, H, c->pool, c->carry); }
   if (rc) return rc;
   if (m.readout == XRL_READOUT_MEAN && G > 0)
     mean_scale_kernel<<<dim3((unsigned)((G * H + 255) / 256)), dim3(256), 0, c->stream>>>(c->pool, d.graph_node_ptr, G, H, 0);
@@ -1836,7 +2188,8 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   c->elem = model->precision == XRL_PREC_BF16 ? 2 : 4;
   // Row count from which the persistent kernels replace the streaming one (tuning knob; the
   // default is where they start to win; 0 = always, a huge value = never)
-  c->p_min_rows = 8192;
+  c->p_min_rows = kPersistentMinRows;
+  if (const char *e = getenv("XRL_DISTINCT_MIN_US")) c->distinct_min_us = atoll(e);
   if (const char *e = getenv("XRL_PERSISTENT_MIN_ROWS")) c->p_min_rows = atoll(e);
   // (measured: at H = 256 the 256-column tiles win from about 300 k rows on, at H = 128 from 1 M)
   c->wide_min_rows = model->hidden >= 256 ? (1 << 18) : (1 << 20);
@@ -1865,7 +2218,7 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   // the weights, followed by 1 KB of zeros (16-byte aligned) that kernels read in place of absent rows
   const size_t w_bytes = align_up(sizeof(float) * L.total);
   // zero row, heads' counters, the one-launch encoder's counters
-  const size_t tail_bytes = 1024 + sizeof(int32_t) * kMaxFusedSlots + sizeof(unsigned) * kClusterMaxGraphs;
+  const size_t tail_bytes = 1024 + sizeof(int32_t) * kMaxFusedSlots + sizeof(unsigned) * kClusterMaxGraphs + sizeof(int32_t) * kCounts;
   e = hipMalloc((void **)&c->d_w, w_bytes + tail_bytes);
   if (e != hipSuccess) {
     xrl_destroy(c);
@@ -1874,12 +2227,14 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   c->zero_row = (char *)c->d_w + w_bytes;
   c->d_counter = (int32_t *)((char *)c->zero_row + 1024);
   c->d_arrived = (unsigned *)(c->d_counter + kMaxFusedSlots);
+  c->d_counts = (int32_t *)(c->d_arrived + kClusterMaxGraphs);
   e = hipMemset(c->zero_row, 0, tail_bytes);
   if (e != hipSuccess) {
     xrl_destroy(c);
     return fail(XRL_ERR_HIP, "hipMemset: %s", hipGetErrorString(e));
   }
-  e = hipHostMalloc((void **)&c->h_fault, sizeof(unsigned), hipHostMallocMapped);
+  e = hipHostMalloc((void **)&c->h_counts, sizeof(int32_t) * kCounts, hipHostMallocDefault);
+  if (e == hipSuccess) e = hipHostMalloc((void **)&c->h_fault, sizeof(unsigned), hipHostMallocMapped);
   if (e == hipSuccess) {
     *c->h_fault = 0;
     e = hipHostGetDevicePointer((void **)&c->d_fault, c->h_fault, 0);
@@ -1920,6 +2275,7 @@ int xrl_destroy(xrl_ctx *c) {
   (void)hipStreamSynchronize(c->stream);
   if (c->d_w) (void)hipFree(c->d_w);
   if (c->h_fault) (void)hipHostFree(c->h_fault);
+  if (c->h_counts) (void)hipHostFree(c->h_counts);
   if (c->d_dw_int) (void)hipFree(c->d_dw_int);
   if (c->d_wmap) (void)hipFree(c->d_wmap);
   if (c->d_swz) (void)hipFree(c->d_swz);
@@ -2044,6 +2400,7 @@ int xrl_batch_upload(xrl_ctx *c, xrl_batch *b) {
   d.gtile_ptr = b->has_graph_tiles ? (int32_t *)(blk + b->o_gtile) : nullptr;
   d.graph_tile_ptr = b->has_graph_tiles ? (int32_t *)(blk + b->o_graph_tile) : nullptr;
   d.agg_src = (int32_t *)(blk + o_as);
+  b->encodes = 0;
   b->uploaded = true;
   return XRL_OK;
 }
@@ -2062,8 +2419,35 @@ int xrl_encode(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save_for_backwa
     return fail(XRL_ERR_HIP, "xrl_encode: an earlier xrl_encode on this context did not complete (a wait between the "
                              "blocks of its one-launch form ran out); its embeddings are invalid");
   }
+  if (b->owner == c->id && b->encodes >= 0) {
+    // Reduced to its distinct nodes when it is first saved for a backward pass, or encoded again: a batch
+    // encoded once and forward only would not earn back what finding them takes.
+    xrl_batch *mb = const_cast<xrl_batch *>(b);
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if ((save_for_backward || ++mb->encodes > 1) && distinct_pays(c, b) &&
+        hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
+      mb->encodes = -1;
+      if ((rc = find_distinct(c, mb))) return rc;
+    }
+  }
   return c->elem == 2 ? encode_impl<bf16_t>(c, b, d_emb, save_for_backward)
                       : encode_impl<float>(c, b, d_emb, save_for_backward);
+}
+
+int xrl_batch_level(xrl_ctx *c, const xrl_batch *b, int32_t level, int64_t counts[4]) {
+  const int rc = check_batch(c, b, "xrl_batch_level");
+  if (rc) return rc;
+  if (!counts) return fail(XRL_ERR_NULL, "xrl_batch_level: counts is NULL");
+  if (level < 0 || level > c->m.rounds) return fail(XRL_ERR_INDEX, "xrl_batch_level: level %d outside [0, %d]", level, c->m.rounds);
+  if (const Distinct *q = distinct_of(c, b)) {
+    const LevelGraph &g = q->lv[level];
+    counts[0] = g.N; counts[1] = g.E; counts[2] = g.receivers; counts[3] = g.n_tiles;
+    return XRL_OK;
+  }
+  const int32_t *in_ptr = b->at<int32_t>(b->o_in_ptr);
+  counts[0] = b->N; counts[1] = b->E; counts[2] = 0; counts[3] = b->n_tiles;
+  for (int64_t n = 0; n < b->N; ++n) counts[2] += in_ptr[n + 1] > in_ptr[n];
+  return XRL_OK;
 }
 
 int xrl_policy_value(xrl_ctx *c, const xrl_batch *b, const float *d_emb, float *d_logp,
@@ -2425,7 +2809,8 @@ int xrl_get_activation(xrl_ctx *c, const xrl_batch *b, const char *what, int32_t
   int64_t rows = N;
   int D = H;
   bool typed = true;
-  const int32_t *row_src = nullptr;
+  const int32_t *row_src = nullptr, *cls = nullptr;   // (a reduced batch: the node's class at the level)
+  const Distinct *q = distinct_of(c, b);
   if (!strcmp(what, "a0")) {   // not kept by the forward pass: recomputed with the segment-sum kernel
     return launch_segsum<float, float, 4>(c, b->dev.edge_feat, nullptr, b->dev.in_ptr, b->dev.in_dst, b->E, N,
                                           c->m.d_edge, d_out, c->carry);
@@ -2434,19 +2819,21 @@ int xrl_get_activation(xrl_ctx *c, const xrl_batch *b, const char *what, int32_t
   else if (!strcmp(what, "h")) {
     if (round < 0 || round > R) return fail(XRL_ERR_INDEX, "h: round %d outside [0, %d]", round, R);
     src = c->h[round];
+    if (q) cls = q->cls[round];
   } else if (!strcmp(what, "agg")) {
     if (round < 1 || round > R) return fail(XRL_ERR_INDEX, "agg: round %d outside [1, %d]", round, R);
     if (c->m.round_kind == XRL_ROUND_GAT)
       return fail(XRL_ERR_UNSUPPORTED, "agg: the graph-attention rounds keep no received sums");
     src = c->agg[round];
+    if (q) cls = q->cls[round];
     if (c->agg_skip) row_src = b->dev.agg_src;   // rows of nodes without in-edges were never written
   } else return fail(XRL_ERR_INDEX, "xrl_get_activation: unknown tensor '%s'", what);
   if (rows * D == 0) return XRL_OK;
   const unsigned blocks = (unsigned)((rows * D + 255) / 256);
   if (typed && c->elem == 2)
-    export_rows_kernel<bf16_t><<<dim3(blocks), dim3(256), 0, c->stream>>>((const bf16_t *)src, rows, D, row_src, d_out);
+    export_rows_kernel<bf16_t><<<dim3(blocks), dim3(256), 0, c->stream>>>((const bf16_t *)src, rows, D, row_src, cls, d_out);
   else
-    export_rows_kernel<float><<<dim3(blocks), dim3(256), 0, c->stream>>>((const float *)src, rows, D, row_src, d_out);
+    export_rows_kernel<float><<<dim3(blocks), dim3(256), 0, c->stream>>>((const float *)src, rows, D, row_src, cls, d_out);
   HIP_TRY(hipGetLastError());
   return XRL_OK;
 }

@@ -82,6 +82,7 @@ struct HostBlock {
 HostBlock host_block_take(size_t bytes);
 void host_block_give(HostBlock &b);
 
+struct Distinct;            // the batch's graphs reduced to distinct nodes (device translation unit)
 struct DevicePool;          // idle device blocks of one context (device translation unit)
 
 // The packed arrays lie in one host block, those the device needs first and in the device's layout:
@@ -121,6 +122,8 @@ struct xrl_batch {
   // has used goes back to its pool (reuse on the same stream is ordered), any other is freed
   uint64_t owner = 0;
   std::shared_ptr<DevicePool> pool;
+  std::shared_ptr<Distinct> distinct;      // used by the owner only
+  int encodes = 0;                         // the owner's calls of xrl_encode, until the batch is looked at for it
   std::atomic<bool> shared{false};
   uint64_t id = 0;  // unique per packed batch; ties saved activations to their batch
   xrl_batch() = default;

@@ -1,0 +1,111 @@
+"""Batches reduced to distinct nodes: classes of nodes with equal histories are encoded once. Every state,
+received sum and embedding has to be the same bits as without the reduction; gradients, whose sums
+are taken in another order, agree to rounding and with the oracle."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import paper_2304_14698_amd as xrl
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _edge_cases(rng, model):
+    """Graphs that are the same but for one edge attribute's last bit, a node's last attribute, the order
+    of a receiver's in-edges, a sender five hops up; empty and edgeless graphs; a repeated edge; a
+    graph twice; receivers of 32 in-edges."""
+    base = synth.layered_dag(rng, 40)
+    n, e = base.n_nodes, base.n_edges
+
+    def bump(a, i):
+        a = a.copy()
+        a.reshape(-1)[i] = np.nextafter(a.reshape(-1)[i], np.float32(100))
+        return a
+
+    def variant(**kw):
+        return dataclasses.replace(base, **kw)
+    back = np.arange(e)[::-1]
+    indeg_32 = np.concatenate([np.where(base.dst == n - 1, n - 2, base.dst), np.full(32, n - 1)]).astype(np.int32)
+    hub = variant(src=np.concatenate([base.src, np.arange(32) % (n - 1)]).astype(np.int32), dst=indeg_32,
+                  efeat=np.concatenate([base.efeat, base.efeat[:32]]))
+    assert np.bincount(hub.dst).max() == 32
+    graphs = [base, base, variant(efeat=bump(base.efeat, 0)), variant(efeat=bump(base.efeat, base.efeat.size - 1)),
+              variant(dense=bump(base.dense, base.dense.size - 1)),
+              variant(op=np.concatenate([[(base.op[0] + 1) % 32], base.op[1:]]).astype(np.int32)),
+              variant(src=base.src[back], dst=base.dst[back], efeat=base.efeat[back]),
+              variant(src=base.src[:0], dst=base.dst[:0], efeat=base.efeat[:0]), hub, hub,
+              variant(op=base.op[:0], dense=base.dense[:0], layer=base.layer[:0], block=base.block[:0], src=base.src[:0],
+                      dst=base.dst[:0], efeat=base.efeat[:0])]
+    return synth.concat_states([(graphs, np.ones(len(graphs), np.uint8))])
+
+
+def _state(kind, rng, model):
+    if kind == "edges":
+        return _edge_cases(rng, model), False
+    if kind == "edits":
+        base = synth.shuffle_edges(rng, synth.resnet_dag(rng, 3))
+        return synth.make_edit_states(rng, [base, base], [9, 17], by_block=True)[0], True
+    base = synth.transformer_dag(rng, 3) if kind == "transformer" else synth.resnet_dag(rng, 4)
+    states = [synth.make_state(rng, base, n, by_block=True) for n in ((24,) if kind == "transformer" else (5, 60, 1))]
+    return synth.concat_states(states), False
+
+
+def _run(enc, batch, up, rounds):
+    import torch
+    out = {"emb": enc.encode(batch, save_for_backward=True)}
+    for r in range(rounds + 1):
+        out[f"h{r}"] = enc.get_activation(batch, "h", r)
+        if r:
+            out[f"agg{r}"] = enc.get_activation(batch, "agg", r)
+    dw = torch.zeros(enc.n_weights, dtype=torch.float32, device="cuda")
+    enc.encode_backward(batch, up, dw)
+    plain = enc.encode(batch)
+    again = torch.zeros_like(dw)
+    enc.encode(batch, save_for_backward=True)
+    enc.encode_backward(batch, up, again)
+    assert torch.equal(plain, out["emb"]) and torch.equal(dw, again)
+    return {k: v.cpu().numpy() for k, v in out.items()}, dw.cpu().numpy().astype(np.float64)
+
+
+@pytest.mark.parametrize("kind", ["edges", "resnet", "transformer", "edits"])
+@pytest.mark.parametrize("hidden,precision,layers,readout", [
+    (64, "fp32", 2, "sum"), (128, "bf16", 2, "mean"), (256, "bf16", 2, "sum"),
+    (128, "fp32", 1, "mean")])
+def test_reduction_changes_nothing(kind, hidden, precision, layers, readout, monkeypatch):
+    import torch
+    rng = np.random.Generator(np.random.PCG64(5))
+    model, _ = synth.make_config(1)
+    model.update(hidden=hidden, precision=precision, mlp_layers=layers, readout=readout, rounds=3)
+    state, edits = _state(kind, rng, model)
+    w = synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1)
+    got = {}
+    for min_us in ("-1", "0"):                      # never, always
+        monkeypatch.setenv("XRL_DISTINCT_MIN_US", min_us)
+        monkeypatch.setenv("XRL_RESIDENT_MAX_GRAPHS", "0")
+        if precision == "bf16":                     # gradients from the kept forward on both sides
+            monkeypatch.setenv("XRL_PERSISTENT_MIN_ROWS", "0")
+        enc = xrl.Encoder(model, w)
+        batch = enc.pack_edits(state) if edits else enc.pack(state)
+        up = torch.tensor(np.random.default_rng(3).standard_normal((batch.G, hidden)), dtype=torch.float32, device="cuda")
+        got[min_us] = _run(enc, batch, up, model["rounds"])
+        batch.free()
+        enc.close()
+    (a, da), (b, db) = got["-1"], got["0"]
+    for k in a:
+        assert np.array_equal(a[k], b[k]), k
+    # fp32: sums of thousands of products in another order; bf16: every stored gradient row is rounded to
+    # 2^-9, here per node, there per class (measured: 2e-7 to 1e-6 and 1e-3 to 5e-3)
+    assert np.linalg.norm(da - db) <= (1e-5 if precision == "fp32" else 2e-2) * np.linalg.norm(da)
+
+
+def test_reduced_batch_against_the_oracle(monkeypatch):
+    from test_gpu_backward import run_backward_case
+    monkeypatch.setenv("XRL_DISTINCT_MIN_US", "0")
+    monkeypatch.setenv("XRL_RESIDENT_MAX_GRAPHS", "0")
+    model, _ = synth.make_config(1)
+    rng = np.random.Generator(np.random.PCG64(9))
+    state = synth.concat_states([synth.make_state(rng, synth.resnet_dag(rng, 2), n, by_block=True) for n in (12, 3)])
+    w = synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1)
+    run_backward_case(xrl, model, state, w, seed=4)
