@@ -511,7 +511,7 @@ __global__ __launch_bounds__(256) void state_policy_bwd_kernel(
   if (t == 0) inv_nvalid[s] = 1.f / nvalid;
 }
 
-// Backward of rowmlp_kernel for up to three layers, one block per ROWMLP_ROWS rows:
+// Backward of rowmlp_kernel for up to three layers, a block for ROWMLP_ROWS rows:
 // given dout [n_rows, d_out[last]] and the saved post-activation outputs act[l], computes the
 // pre-activation gradients dz[l] (stored, for the weight-gradient pass) and dx [n_rows, d_in[0]].
 struct RowMlpBwdArgs {
@@ -526,12 +526,11 @@ struct RowMlpBwdArgs {
 };
 
 template <int ROWMLP_ROWS>
-__global__ __launch_bounds__(256) void rowmlp_bwd_kernel(const RowMlpBwdArgs a) {
-  extern __shared__ float sm[];
+__device__ __forceinline__ void rowmlp_bwd_block(const RowMlpBwdArgs &a, int block, float *sm) {
   int dmax = a.d_in[0];
   for (int l = 0; l < a.n_layers; ++l) dmax = a.d_out[l] > dmax ? a.d_out[l] : dmax;
   float *cur = sm, *nxt = sm + ROWMLP_ROWS * dmax;
-  const int64_t row0 = (int64_t)blockIdx.x * ROWMLP_ROWS;
+  const int64_t row0 = (int64_t)block * ROWMLP_ROWS;
   const int L = a.n_layers;
   // dz of the last layer
   {
@@ -586,39 +585,128 @@ __global__ __launch_bounds__(256) void rowmlp_bwd_kernel(const RowMlpBwdArgs a) 
   }
 }
 
-// Weight gradient of one affine layer over a modest number of rows, deterministic:
+// The rows of one MLP, ROWMLP_ROWS per block, and behind them those of a second one (other == 0 rows: none):
+// the two heads' backward passes do not depend on each other. Every block reads all the weights from L2,
+// which bounds the launch: several rows per block as soon as that leaves a block per compute unit
+// (1040 rows of the policy head, H = 128: 32 us with a block per row and 14 us for the value head
+// after it, 23 us together with four rows per block). A row's sums do not depend on it.
+template <int ROWMLP_ROWS>
+__global__ __launch_bounds__(256) void rowmlp_bwd_kernel(const RowMlpBwdArgs a, const RowMlpBwdArgs other) {
+  extern __shared__ float sm[];
+  const int blocks = (int)((a.n_rows + ROWMLP_ROWS - 1) / ROWMLP_ROWS);
+  if ((int)blockIdx.x < blocks) rowmlp_bwd_block<ROWMLP_ROWS>(a, blockIdx.x, sm);
+  else rowmlp_bwd_block<ROWMLP_ROWS>(other, (int)blockIdx.x - blocks, sm);
+}
+
+// Weight gradients of a few affine layers over G or S rows each, one launch for all of them:
 //   dW[k, f] += sum_rows x[row, k] dz[row, f],  db[f] += sum_rows dz[row, f]
-// x = [x1 | x2] (x2 nullable). One thread per (k, f) walks a chunk of rows in order (blockIdx.y =
-// chunk). With one chunk the sums are added to dW / db directly; with several, chunk c writes
-// partial[c][k][f] (k = din is the bias row) and the fixed-order reduction of the weight-gradient
-// kernels adds them up.
-__global__ void small_wgrad_kernel(const float *x1, int w1, const float *x2, int w2,
-                                   const float *dz, int64_t n_rows, int rows_per_chunk, int din, int dout,
-                                   float *dW, float *db, float *partial) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)(din + 1) * dout) return;
-  const int k = (int)(i / dout), f = (int)(i - (int64_t)k * dout);
-  const int64_t r0 = (int64_t)blockIdx.y * rows_per_chunk;
-  const int64_t r1 = r0 + rows_per_chunk < n_rows ? r0 + rows_per_chunk : n_rows;
-  // rows are added in order, eight requested at a time (a plain loop waits for every row's loads)
-  const float *xp = k < w1 ? x1 + k : (k < din ? x2 + (k - w1) : nullptr);
-  const int xs = k < w1 ? w1 : w2;
-  float acc = 0.f;
-  for (int64_t r = r0; r < r1; r += 8) {
-    float xv[8], dv[8];
+// x = [x1 | x2] (x2 nullable); k = d_in is the bias row (x = 1). A block owns a 64 x 64 tile of one layer's
+// [d_in + 1, d_out] and one chunk of its rows; rows go through LDS sixteen at a time (the next sixteen
+// requested before the products of these), and a thread holds 4 x 4 sums: two 16-byte LDS reads for
+// sixteen products, where one thread per entry waited for two loads per product (H = 128, 1040 rows,
+// 16 states: 250 us for the eight layers of heads and readout, a launch and a reduction each; here 32 us
+// in four launches; 4624 rows, H = 256: 760 -> 81 us). With one chunk the sums
+// are added to dW / db directly; with several, chunk c writes partial[c][k][f], which
+// small_wgrad_reduce_kernel adds up in a fixed order.
+constexpr int kWgradJobs = 6, kWgradTile = 64, kWgradStage = 16;
+struct SmallWgradJob {
+  const float *x1, *x2, *dz;
+  int w1, w2, d_in, d_out;       // w1 + w2 == d_in
+  int64_t n_rows;
+  int rows_per_chunk, n_chunks, tiles_k, tiles_f;
+  int block0, entry0;            // the launch's first block / the reduction's first block of this layer
+  float *dW, *db, *partial;      // partial: nullptr with one chunk
+};
+struct SmallWgradArgs {
+  int n_jobs;
+  SmallWgradJob job[kWgradJobs];
+};
+__global__ __launch_bounds__(256) void small_wgrad_kernel(const SmallWgradArgs a) {
+  __shared__ __align__(16) float xs[kWgradStage][kWgradTile], zs[kWgradStage][kWgradTile];
+  int ji = 0;
+  while (ji + 1 < a.n_jobs && (int)blockIdx.x >= a.job[ji + 1].block0) ++ji;
+  const SmallWgradJob &j = a.job[ji];
+  int q = (int)blockIdx.x - j.block0;
+  const int f0 = (q % j.tiles_f) * kWgradTile;
+  q /= j.tiles_f;
+  const int k0 = (q % j.tiles_k) * kWgradTile, chunk = q / j.tiles_k;
+  const int64_t r0 = (int64_t)chunk * j.rows_per_chunk;
+  const int64_t r1 = r0 + j.rows_per_chunk < j.n_rows ? r0 + j.rows_per_chunk : j.n_rows;
+  const int t = threadIdx.x, tk = 4 * (t >> 4), tf = 4 * (t & 15);
+  const int col = t & 63, row4 = t >> 6;                    // staging: column `col` of rows row4, row4 + 4, ..
+  const int k = k0 + col, f = f0 + col;
+  const bool in_x = k < j.d_in, in_f = f < j.d_out;
+  const float *xp = k < j.w1 ? j.x1 + k : (in_x ? j.x2 + (k - j.w1) : j.x1);
+  const int xstride = k < j.w1 ? j.w1 : j.w2;
+  const float xelse = k == j.d_in ? 1.f : 0.f;
+  float xv[kWgradStage / 4], zv[kWgradStage / 4];
+  auto request = [&](int64_t r) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int64_t ri = r + i < r1 ? r + i : r1 - 1;
-      dv[i] = dz[ri * dout + f];
-      xv[i] = xp ? xp[ri * xs] : 1.f;
+    for (int i = 0; i < kWgradStage / 4; ++i) {
+      const int64_t ri = r + row4 + 4 * i;
+      const bool on = ri < r1;
+      const int64_t rc = on ? ri : r1 - 1;
+      const float x = in_x ? xp[rc * xstride] : xelse;
+      const float z = in_f ? j.dz[rc * j.d_out + f] : 0.f;
+      xv[i] = on ? x : 0.f;
+      zv[i] = on ? z : 0.f;
     }
+  };
+  float acc[4][4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if (r + i < r1) acc = xp ? fmaf(xv[i], dv[i], acc) : acc + dv[i];
+  for (int m = 0; m < 4; ++m)
+#pragma unroll
+    for (int n = 0; n < 4; ++n) acc[m][n] = 0.f;
+  request(r0);
+  for (int64_t r = r0; r < r1; r += kWgradStage) {
+#pragma unroll
+    for (int i = 0; i < kWgradStage / 4; ++i) {
+      xs[row4 + 4 * i][col] = xv[i];
+      zs[row4 + 4 * i][col] = zv[i];
+    }
+    __syncthreads();
+    if (r + kWgradStage < r1) request(r + kWgradStage);
+#pragma unroll
+    for (int i = 0; i < kWgradStage; ++i) {
+      const f32x4 x = *(const f32x4 *)&xs[i][tk], z = *(const f32x4 *)&zs[i][tf];
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int n = 0; n < 4; ++n) acc[m][n] = fmaf(x[m], z[n], acc[m][n]);
+    }
+    __syncthreads();
   }
-  if (partial) partial[(size_t)blockIdx.y * (din + 1) * dout + i] = acc;
-  else if (k == din) db[f] += acc;
-  else dW[(size_t)k * dout + f] += acc;
+#pragma unroll
+  for (int m = 0; m < 4; ++m)
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      const int ko = k0 + tk + m, fo = f0 + tf + n;
+      if (ko > j.d_in || fo >= j.d_out) continue;
+      if (j.partial) j.partial[((size_t)chunk * (j.d_in + 1) + ko) * j.d_out + fo] = acc[m][n];
+      else if (ko == j.d_in) j.db[fo] += acc[m][n];
+      else j.dW[(size_t)ko * j.d_out + fo] += acc[m][n];
+    }
+}
+// dW / db += the chunks' sums, every entry in chunk order (eight loads in flight); layers of one chunk have no blocks
+__global__ __launch_bounds__(256) void small_wgrad_reduce_kernel(const SmallWgradArgs a) {
+  int ji = 0;
+  while (ji + 1 < a.n_jobs && (int)blockIdx.x >= a.job[ji + 1].entry0) ++ji;
+  const SmallWgradJob &j = a.job[ji];
+  const int64_t i = (int64_t)((int)blockIdx.x - j.entry0) * 256 + threadIdx.x, n = (int64_t)(j.d_in + 1) * j.d_out;
+  if (i >= n) return;
+  float sum = 0.f;
+  int c = 0;
+  for (; c + 8 <= j.n_chunks; c += 8) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = j.partial[(size_t)(c + u) * n + i];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) sum += v[u];
+  }
+  for (; c < j.n_chunks; ++c) sum += j.partial[(size_t)c * n + i];
+  const int64_t nw = (int64_t)j.d_in * j.d_out;
+  if (i < nw) j.dW[i] += sum;
+  else j.db[i - nw] += sum;
 }
 
 // Clipped-surrogate objective of Section 3.3.4 and its derivatives w.r.t. the heads' outputs, one

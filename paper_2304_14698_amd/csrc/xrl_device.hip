@@ -1223,65 +1223,104 @@ int launch_wgrad_embed_rows(xrl_ctx *c, WgradArgs &a, int Kx, float *dW, float *
   return fail(XRL_ERR_UNSUPPORTED, "launch_wgrad_embed_rows: bf16 contexts only");
 }
 
-int launch_rowmlp_bwd(xrl_ctx *c, const MlpRef &r, bool relu_last, float *const *act, const float *dout,
-                      int64_t n_rows, float *const *dz, float *dx) {
-  if (n_rows <= 0) return XRL_OK;
+RowMlpBwdArgs rowmlp_bwd_args(xrl_ctx *c, const MlpRef &r, bool relu_last, float *const *act, const float *dout,
+                              int64_t n_rows, float *const *dz, float *dx) {
   RowMlpBwdArgs a;
   memset(&a, 0, sizeof(a));
   a.n_layers = r.n_layers;
   a.relu_last = relu_last ? 1 : 0;
-  int dmax = r.d_in[0];
   for (int l = 0; l < r.n_layers; ++l) {
     a.W[l] = c->d_w + r.w[l];
     a.d_in[l] = r.d_in[l];
     a.d_out[l] = r.d_out[l];
     a.act[l] = act[l];
     a.dz[l] = dz[l];
-    if (r.d_out[l] > dmax) dmax = r.d_out[l];
   }
   a.dout = dout; a.n_rows = n_rows; a.dx = dx;
-  if (n_rows <= 4096) {
-    rowmlp_bwd_kernel<1><<<dim3((unsigned)n_rows), dim3(256), (size_t)2 * dmax * sizeof(float), c->stream>>>(a);
-  } else {
-    const unsigned blocks = (unsigned)((n_rows + 7) / 8);
-    rowmlp_bwd_kernel<8><<<dim3(blocks), dim3(256), (size_t)2 * 8 * dmax * sizeof(float), c->stream>>>(a);
-  }
-  HIP_TRY(hipGetLastError());
-  return XRL_OK;
+  return a;
+}
+// a's rows and, if given, b's in one launch (see rowmlp_bwd_kernel for the rows per block)
+int launch_rowmlp_bwd(xrl_ctx *c, const RowMlpBwdArgs &a, const RowMlpBwdArgs *b = nullptr) {
+  RowMlpBwdArgs other;
+  memset(&other, 0, sizeof(other));
+  if (b) other = *b;
+  if (a.n_rows + other.n_rows <= 0) return XRL_OK;
+  int dmax = 1;
+  for (const RowMlpBwdArgs *m : {&a, (const RowMlpBwdArgs *)&other})
+    for (int l = 0; l < m->n_layers; ++l) dmax = std::max(dmax, std::max(m->d_in[l], m->d_out[l]));
+  auto go = [&](auto rows) -> int {
+    constexpr int ROWS = decltype(rows)::value;
+    const int64_t blocks = (a.n_rows + ROWS - 1) / ROWS + (other.n_rows + ROWS - 1) / ROWS;
+    rowmlp_bwd_kernel<ROWS><<<dim3((unsigned)blocks), dim3(256), (size_t)2 * ROWS * dmax * sizeof(float), c->stream>>>(a, other);
+    HIP_TRY(hipGetLastError());
+    return XRL_OK;
+  };
+  if (a.n_rows < 2 * c->n_cu) return go(std::integral_constant<int, 1>());
+  if (a.n_rows < 4 * c->n_cu) return go(std::integral_constant<int, 2>());
+  if (a.n_rows < 8 * c->n_cu) return go(std::integral_constant<int, 4>());
+  return go(std::integral_constant<int, 8>());
 }
 
-// dW, db of every layer of a small row-MLP: x of layer 0 is [x1 | x2], of layer l > 0 act[l-1].
-// Above kSmallWgradRows rows the rows are cut into chunks of that size (as many as `partial`,
-// partial_floats long, has room for) whose partial sums are reduced in chunk order.
-constexpr int kSmallWgradRows = 512;
-inline size_t small_wgrad_partial_floats(const MlpRef &r, int64_t n_rows) {
-  size_t big = 0;
-  for (int l = 0; l < r.n_layers; ++l) big = std::max(big, (size_t)(r.d_in[l] + 1) * r.d_out[l]);
-  const int64_t nc = (n_rows + kSmallWgradRows - 1) / kSmallWgradRows;
-  return nc > 1 ? big * (size_t)nc : 0;
+// dW, db of every layer of one or two small row-MLPs in one launch (and one reduction): x of layer 0 is
+// [x1 | x2], of layer l > 0 act[l-1]. Rows are cut into chunks of kSmallWgradRows, fewer and larger ones
+// where `partial` (partial_floats long) has no room for as many.
+constexpr int kSmallWgradRows = 64;
+struct SmallWgradMlp {
+  const MlpRef *r;
+  const float *x1, *x2;
+  int w1, w2;
+  float *const *act, *const *dz;
+  int64_t n_rows;
+};
+inline int64_t small_wgrad_chunks(int64_t n_rows) {
+  return std::min<int64_t>((n_rows + kSmallWgradRows - 1) / kSmallWgradRows, 64);
 }
-int launch_small_wgrads(xrl_ctx *c, const MlpRef &r, const float *x1, int w1, const float *x2, int w2,
-                        float *const *act, float *const *dz, int64_t n_rows, float *dweights,
-                        float *partial, size_t partial_floats) {
-  if (n_rows <= 0) return XRL_OK;
-  for (int l = 0; l < r.n_layers; ++l) {
-    const int64_t n = (int64_t)(r.d_in[l] + 1) * r.d_out[l];
-    const float *a1 = l == 0 ? x1 : act[l - 1];
-    const int aw1 = l == 0 ? w1 : r.d_in[l];
-    int64_t nc = (n_rows + kSmallWgradRows - 1) / kSmallWgradRows;
-    if (partial && (size_t)nc * n > partial_floats) nc = (int64_t)(partial_floats / n);
-    if (!partial || nc < 2) nc = 1;
-    if (nc > 65535) nc = 65535;
-    const int64_t rpc = (n_rows + nc - 1) / nc;
-    nc = (n_rows + rpc - 1) / rpc;
-    float *dW = dweights + r.w[l], *db = dweights + r.b[l];
-    small_wgrad_kernel<<<dim3((unsigned)((n + 255) / 256), (unsigned)nc), dim3(256), 0, c->stream>>>(
-        a1, aw1, l == 0 ? x2 : nullptr, l == 0 ? w2 : 0, dz[l], n_rows, (int)rpc, r.d_in[l], r.d_out[l], dW, db,
-        nc > 1 ? partial : nullptr);
-    if (nc > 1)
-      wgrad_reduce_kernel<<<dim3((unsigned)((n + 31) / 32)), dim3(256), 0, c->stream>>>(
-          partial, (int)nc, r.d_in[l] + 1, r.d_in[l], r.d_out[l], dW, db);
+inline size_t small_wgrad_partial_floats(const MlpRef &r, int64_t n_rows) {
+  size_t n = 0;
+  for (int l = 0; l < r.n_layers; ++l) n += (size_t)(r.d_in[l] + 1) * r.d_out[l];
+  const int64_t nc = small_wgrad_chunks(n_rows);
+  return nc > 1 ? n * (size_t)nc : 0;
+}
+int launch_small_wgrads(xrl_ctx *c, const SmallWgradMlp *mlps, int n_mlps, float *dweights, float *partial, size_t partial_floats) {
+  SmallWgradArgs a;
+  memset(&a, 0, sizeof(a));
+  int blocks = 0, entries = 0;
+  size_t used = 0;
+  for (int i = 0; i < n_mlps; ++i) {
+    const SmallWgradMlp &m = mlps[i];
+    if (m.n_rows <= 0) continue;
+    for (int l = 0; l < m.r->n_layers; ++l) {
+      SmallWgradJob &j = a.job[a.n_jobs++];
+      j.d_in = m.r->d_in[l]; j.d_out = m.r->d_out[l];
+      j.x1 = l == 0 ? m.x1 : m.act[l - 1];
+      j.w1 = l == 0 ? m.w1 : j.d_in;
+      j.x2 = l == 0 ? m.x2 : nullptr;
+      j.w2 = l == 0 ? m.w2 : 0;
+      j.dz = m.dz[l];
+      j.n_rows = m.n_rows;
+      const size_t n = (size_t)(j.d_in + 1) * j.d_out;
+      int64_t nc = small_wgrad_chunks(m.n_rows);
+      if (partial && used + (size_t)nc * n > partial_floats) nc = (int64_t)((partial_floats - used) / n);
+      if (!partial || nc < 2) nc = 1;
+      j.rows_per_chunk = (int)((m.n_rows + nc - 1) / nc);
+      j.n_chunks = (int)((m.n_rows + j.rows_per_chunk - 1) / j.rows_per_chunk);
+      j.tiles_k = (j.d_in + 1 + kWgradTile - 1) / kWgradTile;
+      j.tiles_f = (j.d_out + kWgradTile - 1) / kWgradTile;
+      j.block0 = blocks;
+      j.entry0 = entries;
+      j.dW = dweights + m.r->w[l];
+      j.db = dweights + m.r->b[l];
+      blocks += j.tiles_k * j.tiles_f * j.n_chunks;
+      if (j.n_chunks > 1) {
+        j.partial = partial + used;
+        used += (size_t)j.n_chunks * n;
+        entries += (int)((n + 255) / 256);
+      }
+    }
   }
+  if (blocks == 0) return XRL_OK;
+  small_wgrad_kernel<<<dim3((unsigned)blocks), dim3(256), 0, c->stream>>>(a);
+  if (entries > 0) small_wgrad_reduce_kernel<<<dim3((unsigned)entries), dim3(256), 0, c->stream>>>(a);
   HIP_TRY(hipGetLastError());
   return XRL_OK;
 }
@@ -1617,7 +1656,8 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   const int Kx = De + m.n_op_types + m.n_node_dense, Kp = (Kx + 7) / 8 * 8;
   const bool embed_rows = sizeof(T) == 2 && N > 0;
   if (embed_rows) acc((size_t)N0 * Kp * 2);
-  const size_t part = std::max(wgrad_partial_floats(M, 2 * H + De, H, c->n_cu), wgrad_partial_floats(M, H, H, c->n_cu));
+  const size_t part = std::max(std::max(wgrad_partial_floats(M, 2 * H + De, H, c->n_cu), wgrad_partial_floats(M, H, H, c->n_cu)),
+                               small_wgrad_partial_floats(c->L.readout, G));
   acc(part * 4);
   acc((size_t)G * H * 4); acc((size_t)G * H * 4); acc((size_t)G * (H + Dg) * 4);
   const bool gat = m.round_kind == XRL_ROUND_GAT;
@@ -1674,8 +1714,9 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
 
   // ---- global-update layer backward
   float *ract[3] = {c->ro_act[0], c->ro_act[1], nullptr};
-  if ((rc = launch_rowmlp_bwd(c, c->L.readout, true, ract, d_demb, G, rdz, rdx))) return rc;
-  if ((rc = launch_small_wgrads(c, c->L.readout, c->pool, H, d.graph_global, Dg, ract, rdz, G, dweights, partial, part))) return rc;
+  if ((rc = launch_rowmlp_bwd(c, rowmlp_bwd_args(c, c->L.readout, true, ract, d_demb, G, rdz, rdx)))) return rc;
+  const SmallWgradMlp readout = {&c->L.readout, c->pool, d.graph_global, H, Dg, ract, rdz, G};
+  if ((rc = launch_small_wgrads(c, &readout, 1, dweights, partial, part))) return rc;
   // The gradient w.r.t. the last node states is the pool's, the same row for every node of a graph.
   // From the kept forward, the first backward kernel reads it through the nodes' graph ids from a
   // [G, H] table (the kernel below with the graphs as its "nodes"); otherwise it is written out per node.
@@ -2576,7 +2617,7 @@ int policy_value_backward_run(xrl_ctx *c, const xrl_batch *b, const float *d_emb
   acc(G); acc(S);                                                     // dlogit, 1/|valid|
   acc(G * h0); acc(G * h1); acc(G);                                   // policy dz
   acc(S * h0); acc(S * h1); acc(S); acc(S * H);                       // value dz, dz_mean
-  const size_t spart_floats = std::max(small_wgrad_partial_floats(c->L.policy, G), small_wgrad_partial_floats(c->L.value, S));
+  const size_t spart_floats = small_wgrad_partial_floats(c->L.policy, G) + small_wgrad_partial_floats(c->L.value, S);
   acc(spart_floats);                                                  // chunk partials of the heads' weight gradients
   if ((rc = ensure_hws(c, need))) return rc;
   Bump bump{c->hws};
@@ -2597,12 +2638,12 @@ int policy_value_backward_run(xrl_ctx *c, const xrl_batch *b, const float *d_emb
   // backward
   state_policy_bwd_kernel<<<dim3((unsigned)S), dim3(256), 0, c->stream>>>(logp, ent, d.mask, d.state_graph_ptr,
                                                                         d_dlogp, d_dentropy, dlogit, inv_n);
-  if ((rc = launch_rowmlp_bwd(c, c->L.policy, false, pact, dlogit, G, pdz, d_demb))) return rc;
-  if ((rc = launch_rowmlp_bwd(c, c->L.value, false, vact, d_dvalue, S, vdz, dzs))) return rc;
+  const RowMlpBwdArgs value_rows = rowmlp_bwd_args(c, c->L.value, false, vact, d_dvalue, S, vdz, dzs);
+  if ((rc = launch_rowmlp_bwd(c, rowmlp_bwd_args(c, c->L.policy, false, pact, dlogit, G, pdz, d_demb), &value_rows))) return rc;
   demb_combine_kernel<<<dim3((unsigned)G), dim3(H < 256 ? H : 256), 0, c->stream>>>(d_demb, dzs, inv_n, d.mask,
                                                                                  d.state_graph_ptr, (int)S, H);
-  if ((rc = launch_small_wgrads(c, c->L.policy, d_emb, H, nullptr, 0, pact, pdz, G, d_dweights, spart, spart_floats))) return rc;
-  if ((rc = launch_small_wgrads(c, c->L.value, zmean, H, nullptr, 0, vact, vdz, S, d_dweights, spart, spart_floats))) return rc;
+  const SmallWgradMlp heads[2] = {{&c->L.policy, d_emb, nullptr, H, 0, pact, pdz, G}, {&c->L.value, zmean, nullptr, H, 0, vact, vdz, S}};
+  if ((rc = launch_small_wgrads(c, heads, 2, d_dweights, spart, spart_floats))) return rc;
   HIP_TRY(hipGetLastError());
   return XRL_OK;
 }
