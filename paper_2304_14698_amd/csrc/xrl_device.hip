@@ -196,6 +196,7 @@ struct xrl_ctx {
   int64_t min_rows_now = 0;     // p_min_rows, or 1 for the levels of a reduced batch
   std::vector<void *> hx;       // last encode of a reduced batch: h of the level below, per class
   std::shared_ptr<DevicePool> blocks;
+  hipStream_t copy_stream = nullptr;   // uploads of kCopyStreamBytes and more
   uint64_t enc_batch = 0;
   bool enc_saved = false;
   float *pool = nullptr, *carry = nullptr, *ro_act[2] = {nullptr, nullptr};
@@ -264,6 +265,7 @@ constexpr size_t kMaxPinnedBlock = (size_t)128 << 20;    // larger batches stay 
 constexpr size_t kMaxPinnedTotal = (size_t)1 << 30;      // pinned by all batches together
 constexpr size_t kMaxIdlePinned = (size_t)256 << 20, kMaxIdleDevice = (size_t)1 << 30;
 constexpr size_t kMaxIdleBlocks = 4;
+constexpr size_t kCopyStreamBytes = (size_t)8 << 20;     // uploads from this size on leave on the copy stream
 
 // capacity classes: four per power of two, so that batches of about one size share blocks
 size_t block_capacity(size_t bytes) {
@@ -386,43 +388,71 @@ void host_block_give(HostBlock &b) {
   host_block_release(b);
 }
 
-// Idle device blocks of one context, reused by its later uploads: these are queued on the same stream
-// behind everything that has used the block.
+// Idle device blocks of one context, reused by its later uploads. A block comes with an event behind its
+// last use on the context's stream, for users on another stream (the copy stream).
+struct DeviceBlock {
+  void *p = nullptr;
+  size_t cap = 0;
+  hipEvent_t used = nullptr;         // nullptr: never used
+};
 struct DevicePool {
   std::mutex mu;
-  std::vector<std::pair<void *, size_t>> idle;
+  std::vector<DeviceBlock> idle;     // oldest first
   size_t idle_bytes = 0;
+  hipStream_t stream = nullptr;      // the context's
   bool closed = false;
-  hipError_t take(size_t bytes, void **p, size_t *cap) {
-    *cap = block_capacity(bytes);
+  // on_stream: the block will be used on the context's own stream, where its last use is over by then; else
+  // a block whose last use is over already is preferred, and a new one to waiting
+  hipError_t take(size_t bytes, bool on_stream, DeviceBlock *out) {
+    const size_t cap = block_capacity(bytes);
     {
       std::lock_guard<std::mutex> lk(mu);
-      for (size_t i = 0; i < idle.size(); ++i)
-        if (idle[i].second >= bytes && idle[i].second <= 2 * *cap) {
-          *p = idle[i].first;
-          *cap = idle[i].second;
-          idle_bytes -= *cap;
-          idle.erase(idle.begin() + i);
-          return hipSuccess;
-        }
+      int pick = -1, busy = -1;
+      for (size_t i = 0; i < idle.size() && pick < 0; ++i) {
+        if (idle[i].cap < bytes || idle[i].cap > 2 * cap) continue;
+        if (on_stream || hipEventQuery(idle[i].used) == hipSuccess) pick = (int)i;
+        else if (busy < 0) busy = (int)i;
+      }
+      if (busy >= 0) (void)hipGetLastError();            // (hipErrorNotReady is no error here)
+      if (pick < 0 && idle.size() >= kMaxIdleBlocks) pick = busy;
+      if (pick >= 0) {
+        *out = idle[pick];
+        idle_bytes -= out->cap;
+        idle.erase(idle.begin() + pick);
+        return hipSuccess;
+      }
     }
-    return hipMalloc(p, *cap);
+    *out = DeviceBlock();
+    out->cap = cap;
+    return hipMalloc(&out->p, cap);
   }
-  void give(void *p, size_t cap) {
+  void give(DeviceBlock &b) {
+    if (!b.p) return;
     {
       std::lock_guard<std::mutex> lk(mu);
-      if (!closed && idle.size() < kMaxIdleBlocks && idle_bytes + cap <= kMaxIdleDevice) {
-        idle.push_back({p, cap});
-        idle_bytes += cap;
+      hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+      if (!closed && idle.size() < kMaxIdleBlocks && idle_bytes + b.cap <= kMaxIdleDevice &&
+          hipStreamIsCapturing(stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone &&
+          (b.used || hipEventCreateWithFlags(&b.used, hipEventDisableTiming) == hipSuccess) &&
+          hipEventRecord(b.used, stream) == hipSuccess) {
+        idle.push_back(b);
+        idle_bytes += b.cap;
+        b = DeviceBlock();
         return;
       }
     }
-    (void)hipFree(p);
+    release(b);
+  }
+  static void release(DeviceBlock &b) {
+    RelaxedCapture relaxed;
+    if (b.p) (void)hipFree(b.p);     // (waits for the device)
+    if (b.used) (void)hipEventDestroy(b.used);
+    b = DeviceBlock();
   }
   void close() {
     std::lock_guard<std::mutex> lk(mu);
     closed = true;
-    for (auto &x : idle) (void)hipFree(x.first);
+    for (DeviceBlock &x : idle) release(x);
     idle.clear();
     idle_bytes = 0;
   }
@@ -445,21 +475,21 @@ struct Distinct {
   int32_t *cls[kMaxLevels] = {};           // [N] class of each node at each level
   int32_t *mem_ptr = nullptr, *mem_graph = nullptr, *mem_seg = nullptr;   // the batch's nodes by class at the last level
   bool grouped = false;                    // the groupings the backward pass needs have been made
-  void *block[2] = {nullptr, nullptr};
-  size_t bytes[2] = {0, 0};
+  DeviceBlock block[2];
 };
 
 extern "C" void xrl_batch_release_device(xrl_batch *b) {
   if (b && b->dev.block) {
-    auto give = [&](void *p, size_t cap) {
-      if (!p) return;
-      if (b->pool && !b->shared) b->pool->give(p, cap);
-      else (void)hipFree(p);
+    auto give = [&](DeviceBlock &x) {
+      if (b->pool && !b->shared) b->pool->give(x);
+      else DevicePool::release(x);
     };
     if (b->distinct)
-      for (int i = 0; i < 2; ++i) give(b->distinct->block[i], b->distinct->bytes[i]);
+      for (DeviceBlock &x : b->distinct->block) give(x);
     b->distinct.reset();
-    give(b->dev.block, b->dev.bytes);
+    DeviceBlock x;
+    x.p = b->dev.block; x.cap = b->dev.bytes; x.used = (hipEvent_t)b->dev.used;
+    give(x);
     b->pool.reset();
     b->dev = xrl_batch_device();
     b->uploaded = false;
@@ -1509,14 +1539,13 @@ int find_distinct(xrl_ctx *c, xrl_batch *b) {
   auto q = std::make_shared<Distinct>();
   q->levels = L;
   auto take = [&](int i, size_t bytes) -> char * {
-    if (c->blocks->take(bytes, &q->block[i], &q->bytes[i]) == hipSuccess) return (char *)q->block[i];
+    if (c->blocks->take(bytes, true, &q->block[i]) == hipSuccess) return (char *)q->block[i].p;
     (void)hipGetLastError();
-    q->block[i] = nullptr;
+    q->block[i] = DeviceBlock();
     return nullptr;
   };
   auto drop = [&]() {
-    for (int i = 0; i < 2; ++i)
-      if (q->block[i]) c->blocks->give(q->block[i], q->bytes[i]);
+    for (DeviceBlock &x : q->block) c->blocks->give(x);
   };
   const size_t n_bytes = align_up((size_t)N * 4);
   char *cls_block = take(0, n_bytes * L);
@@ -2220,6 +2249,7 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   static std::atomic<uint64_t> next_ctx{1};
   c->id = next_ctx++;
   c->blocks = std::make_shared<DevicePool>();
+  c->blocks->stream = (hipStream_t)hip_stream;
   host_pool_context(1);
   c->m = *model;
   c->L = L;
@@ -2329,6 +2359,10 @@ int xrl_destroy(xrl_ctx *c) {
   for (auto &sp : c->spans) { (void)hipEventDestroy(sp.a); (void)hipEventDestroy(sp.b); }
   for (auto &e : c->free_events) (void)hipEventDestroy(e);
   c->blocks->close();
+  if (c->copy_stream) {
+    (void)hipStreamSynchronize(c->copy_stream);
+    (void)hipStreamDestroy(c->copy_stream);
+  }
   host_pool_context(-1);
   delete c;
   return XRL_OK;
@@ -2373,25 +2407,39 @@ int xrl_batch_upload(xrl_ctx *c, xrl_batch *b) {
   xrl_batch_release_device(b);           // (of an upload that failed)
   char *blk = nullptr;
   xrl_batch_device &d = b->dev;
-  hipError_t e = c->blocks->take(off, (void **)&blk, &d.bytes);
+  // A large batch travels on a stream of its own, so that it arrives while the context's stream is still at
+  // work on the batch before. us per step, one stream / two, calls queued back to back: 55 MB 2199 / 1713,
+  // 24 MB 2012 / 1496, 14 MB 1768 / 1561; but 6.6 MB 341 / 470 and 4 MB 391 / 536: below 8 MB the hand-over
+  // between the streams and the further blocks in rotation cost more than the transfer.
+  hipStream_t up = c->stream;
+  if (b->mem.pinned && b->send_bytes >= kCopyStreamBytes) {
+    if (!c->copy_stream) HIP_TRY(hipStreamCreateWithFlags(&c->copy_stream, hipStreamNonBlocking));
+    up = c->copy_stream;
+  }
+  DeviceBlock got;
+  hipError_t e = c->blocks->take(off, up == c->stream, &got);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return fail(XRL_ERR_OOM, "device copy of the batch (%zu bytes): %s", off, hipGetErrorString(e));
   }
+  blk = (char *)got.p;
   d.block = blk;
+  d.bytes = got.cap;
+  d.used = got.used;
   b->pool = c->blocks;
   b->owner = c->id;
   b->shared = false;
   auto queue = [&]() -> int {
-    HIP_TRY(hipMemcpyAsync(blk, b->mem.p, b->send_bytes, hipMemcpyHostToDevice, c->stream));
+    if (up != c->stream && got.used) HIP_TRY(hipStreamWaitEvent(up, got.used, 0));
+    HIP_TRY(hipMemcpyAsync(blk, b->mem.p, b->send_bytes, hipMemcpyHostToDevice, up));
     if (N > 0)
-      agg_src_kernel<<<dim3((unsigned)((N + 255) / 256)), dim3(256), 0, c->stream>>>((const int32_t *)(blk + b->o_in_ptr), N,
+      agg_src_kernel<<<dim3((unsigned)((N + 255) / 256)), dim3(256), 0, up>>>((const int32_t *)(blk + b->o_in_ptr), N,
                                                                                     (int32_t *)(blk + o_as));
     if (ed) {
       auto expand = [&](size_t o_from, int64_t n, int width, size_t o_base, size_t o_new, size_t o_out) {
         const int64_t total = n * width;
         if (total > 0)
-          expand_rows_kernel<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, c->stream>>>(
+          expand_rows_kernel<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, up>>>(
               (const int32_t *)(blk + o_from), n, width, (const uint32_t *)(blk + o_base), (const uint32_t *)(blk + o_new),
               (uint32_t *)(blk + o_out));
       };
@@ -2416,12 +2464,13 @@ int xrl_batch_upload(xrl_ctx *c, xrl_batch *b) {
       b->mem.copied = ev;
       b->mem.device = c->device;
     }
-    HIP_TRY(hipEventRecord((hipEvent_t)b->mem.copied, c->stream));
+    HIP_TRY(hipEventRecord((hipEvent_t)b->mem.copied, up));
+    if (up != c->stream) HIP_TRY(hipStreamWaitEvent(c->stream, (hipEvent_t)b->mem.copied, 0));
     return XRL_OK;
   };
   const int rc = queue();
   if (rc) {
-    (void)hipStreamSynchronize(c->stream);
+    (void)hipStreamSynchronize(up);
     return rc;
   }
   d.state_graph_ptr = (int32_t *)(blk + b->o_state_graph_ptr);

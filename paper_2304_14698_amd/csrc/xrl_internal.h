@@ -59,6 +59,7 @@ template <typename T> using RawVec = std::vector<T, RawAlloc<T>>;
 struct xrl_batch_device {
   void *block = nullptr;
   size_t bytes = 0;
+  void *used = nullptr;   // event behind the block's last use before this batch
   int32_t *state_graph_ptr = nullptr, *graph_node_ptr = nullptr, *node_op = nullptr;
   int32_t *in_ptr = nullptr, *in_src = nullptr, *in_dst = nullptr;
   int32_t *out_ptr = nullptr, *out_pos = nullptr, *node_graph = nullptr, *tile_ptr = nullptr;
