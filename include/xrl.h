@@ -197,7 +197,7 @@ int xrl_batch_free(xrl_batch *b);   /* frees host and device copies; NULL is acc
  * with an identity second layer, which changes no result; weights and gradients keep the one-layer
  * layout of xrl_weight_tensor.
  * Environment, read here: XRL_PERSISTENT_MIN_ROWS = row count from which the persistent MLP
- * kernels replace the streaming one (default 8192; 0 = always; results agree within rounding);
+ * kernels replace the others (default 8192 when saving for the backward pass and at hidden = 256, else 32768; 0 = always; results agree within rounding);
  * XRL_WGRAD_WIDE_MIN_ROWS = row count from which the weight-gradient kernel uses 256-column
  * tiles (default 2^18 at hidden = 256, else 2^20; same sums in a different, equally fixed order);
  * XRL_RESIDENT_MAX_GRAPHS (default 256; 0 = never) and XRL_RESIDENT_MAX_TILES (default 4) =

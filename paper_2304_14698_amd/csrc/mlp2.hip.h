@@ -144,11 +144,13 @@ __device__ __forceinline__ uint16_t lane_mask_bits(const f32x16 &acc) {
 // carry[wt][0] when it began before the tile, to carry[wt][1] when it goes on after it (a run
 // covering the whole tile and open on both sides counts as begun before); segsum_fixup adds the
 // carried pieces in tile order.
-template <typename T, int H>
-__device__ __forceinline__ void edge_tile_sum(f32x16 (&acc)[H / 32], const EdgeTileMeta &m, int64_t wt, int nv,
-                                               int lane, T *out, float *carry, char *stage) {
-  constexpr int MB = H / 32;
-  const int l32 = lane & 31, g = lane >> 5;
+struct EdgeRoute {
+  int dsel;             // row this lane's total goes to, -1 = none
+  bool to_c0, to_c1;    // ... or the carry it goes to
+};
+template <int NB>
+__device__ __forceinline__ EdgeRoute edge_run_sums(f32x16 (&acc)[NB], const EdgeTileMeta &m, int nv, int lane) {
+  const int l32 = lane & 31;
   const bool valid = l32 < nv;                                  // nv >= 1
   const int up = __shfl_up(m.dst, 1);                           // lane 32 reads lane 31, but is a head anyway
   const bool head = valid && (l32 == 0 || up != m.dst);
@@ -156,7 +158,7 @@ __device__ __forceinline__ void edge_tile_sum(f32x16 (&acc)[H / 32], const EdgeT
   // number of edges after this one that have the same receiver and lie in the tile
   const int rem = valid ? __builtin_ctzll(heads >> (l32 + 1)) : 0;
 #pragma unroll
-  for (int nb = 0; nb < MB; ++nb)
+  for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[nb][r] = relu_f32(acc[nb][r]);
   // (the lane's partner value enters through a product with 0 or 1: one fused multiply-add per
@@ -166,7 +168,7 @@ __device__ __forceinline__ void edge_tile_sum(f32x16 (&acc)[H / 32], const EdgeT
     // wave-wide shift (no LDS traffic)
     const float takef = rem >= 1 ? 1.f : 0.f;
 #pragma unroll
-    for (int nb = 0; nb < MB; ++nb)
+    for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         // (a copy first: bit-casting the vector-element lvalue itself reads element 0)
@@ -179,30 +181,37 @@ __device__ __forceinline__ void edge_tile_sum(f32x16 (&acc)[H / 32], const EdgeT
     const float takef = rem >= d ? 1.f : 0.f;
     const int from = ((lane + d) & 63) << 2;
 #pragma unroll
-    for (int nb = 0; nb < MB; ++nb) {
+    for (int nb = 0; nb < NB; ++nb) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const float v = acc[nb][r];
         const float t = __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(v)));
         acc[nb][r] = fmaf(t, takef, v);
       }
-      // one block's exchanges at a time: all of them in flight at once would hold 16 * MB more
+      // one block's exchanges at a time: all of them in flight at once would hold 16 * NB more
       // registers than the callers that keep a next tile's rows in flight can spare
       __builtin_amdgcn_sched_barrier(0);
     }
   }
   const bool ends_tile = l32 + rem == nv - 1;
-  const bool to_c0 = head && l32 == 0 && m.prev_d == m.dst;
-  const bool to_c1 = head && !to_c0 && ends_tile && m.next_d == m.dst;
-  const int dsel = (head && !to_c0 && !to_c1) ? m.dst : -1;      // row this lane's total goes to
+  EdgeRoute e;
+  e.to_c0 = head && l32 == 0 && m.prev_d == m.dst;
+  e.to_c1 = head && !e.to_c0 && ends_tile && m.next_d == m.dst;
+  e.dsel = (head && !e.to_c0 && !e.to_c1) ? m.dst : -1;
+  return e;
+}
+template <typename T, int H>
+__device__ __forceinline__ void edge_tile_sum(f32x16 (&acc)[H / 32], const EdgeTileMeta &m, int64_t wt, int nv,
+                                               int lane, T *out, float *carry, char *stage) {
+  const EdgeRoute e = edge_run_sums<H / 32>(acc, m, nv, lane);
   store_rows_via_lds<T, H, false>(acc, stage, lane, [&](int r) -> T * {
-    const int d = __shfl(dsel, r);
+    const int d = __shfl(e.dsel, r);
     return d >= 0 ? out + (size_t)d * H : nullptr;
   });
-  if (to_c0 || to_c1) {
-    const int64_t crow = wt * 2 + (to_c1 ? 1 : 0);
+  if (e.to_c0 || e.to_c1) {
+    const int64_t crow = wt * 2 + (e.to_c1 ? 1 : 0);
 #pragma unroll
-    for (int nb = 0; nb < MB; ++nb) store_tile_rows<float, H>(carry, crow, true, nb, g, acc[nb]);
+    for (int nb = 0; nb < H / 32; ++nb) store_tile_rows<float, H>(carry, crow, true, nb, lane >> 5, acc[nb]);
   }
 }
 
@@ -283,7 +292,7 @@ __device__ __forceinline__ void zero_source_rows(const Mlp2Args &a, int64_t row0
 }
 
 // One wave tile: rows [row0, row0 + nv) (nv in 1..32; for EDGE the edges of tile `wt` of the
-// tile table in use), staged out through `stage` (RowStage<T, H>::BYTES, private to the wave).
+// tile table in use), on one wave (the one-launch encoders), staged out through `stage` (RowStage<T, H>::BYTES, private to the wave).
 // T1 = operand type of layer 1 (its input rows and W1), T = operand type of layer 2 and of the
 // stored activations. They differ only for EMBED in bf16 mode, whose first layer stays in fp32:
 // its inputs (log2 shape attributes up to 12, sums of edge attributes) are large enough for bf16
@@ -421,27 +430,139 @@ __device__ __forceinline__ void mlp2_wave_tile(const Mlp2Args &a, const int64_t 
   }
 }
 
-// Streaming form: one block of four waves per 128 rows (four edge tiles), weights read from
-// memory (L2) as they are needed.
+// Split form, one launch per layer where the persistent kernels do not apply (fp32, small batches): a block of H / 32 waves takes one
+// tile, wave w the 32 output features of block w in both layers. The tile's input rows are gathered
+// once, as operand fragments, each wave its share, and shared through LDS, as is relu(z1); a wave
+// streams only its own slices of the weights, eight fragments ahead. A tile's chain of dependent
+// matrix instructions is H / 32 times shorter: with a wave per tile a launch took 37 us and more in fp32
+// at H = 128 however few tiles there were (768 matrix instructions of 64 cycles are 23 us by
+// themselves). Same operations in the same order per output: the same bits. Edge kernel, us, a wave
+// per tile / split: fp32 H = 128: 158 tiles 39.7 / 14.1, 2278 105 / 88, 13.7 k 479 / 458; H = 256: 158 tiles
+// 171 / 35, 2278 514 / 275; H = 64: 200 tiles 16.4 / 12.6, 2278 35.2 / 35.0; bf16 H = 256: 158 tiles 40.8 / 11.6.
+template <typename T, int H>
+struct SplitTile {
+  static constexpr int V = Operand<T>::V, HS = H / (2 * V), MB = H / 32, QB = 32 / (2 * V);
+  static constexpr int XBYTES = 2 * HS * 1024, ZBYTES = MB * QB * 1024, SBYTES = MB * BlockStage<T>::BYTES;
+  // input fragments; then, in their place, relu(z1) and behind it the waves' output staging
+  static constexpr int BYTES = XBYTES > ZBYTES + SBYTES ? XBYTES : ZBYTES + SBYTES;
+};
 template <typename T1, typename T, int H, int KIND>
-__global__ __launch_bounds__(256) void mlp2_kernel(const Mlp2Args a) {
-  __shared__ __align__(16) char stage[4][RowStage<T, H>::BYTES];  // per-wave staging of output rows
-  // consecutive tiles stay on one XCD (blocks are dealt round-robin to the 8 XCDs), so the rows
-  // a tile gathers are mostly in that XCD's L2 already
-  const int64_t per_xcd = (a.n_blocks + 7) / 8;
-  const int64_t tile = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (tile >= a.n_blocks) return;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t wt = tile * 4 + wave;                           // wave tile: 32 rows, or an edge tile
+__global__ __launch_bounds__(2 * H) void mlp2_split_kernel(const Mlp2Args a) {
+  using S = SplitTile<T, H>;
+  using Opd = Operand<T>;
+  using vec = typename Opd::vec;
+  constexpr int V = Opd::V, SL = 2 * V, HS = S::HS, MB = S::MB, QB = S::QB, NC2 = MB * QB;
+  constexpr int RING = 8;                                       // weight fragments in flight
+  extern __shared__ __align__(16) char smem[];
+  const int64_t n_tiles = a.n_blocks, per_xcd = (n_tiles + 7) / 8;
+  // consecutive tiles stay on one XCD (blocks are dealt round-robin to the 8 XCDs), so the rows a tile
+  // gathers are mostly in that XCD's L2 already
+  const int64_t wt = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if ((int64_t)(blockIdx.x / 8) >= per_xcd || wt >= n_tiles) return;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int64_t row0 = wt * 32;
   int nv;
   if constexpr (KIND == KIND_EDGE) {
-    if (wt >= a.n_tiles) return;
     row0 = a.tile_ptr[wt];
     nv = a.tile_ptr[wt + 1] - (int)row0;
   } else {
-    if (row0 >= a.n_rows) return;
     nv = a.n_rows - row0 < 32 ? (int)(a.n_rows - row0) : 32;
   }
-  mlp2_wave_tile<T1, T, H, KIND>(a, row0, nv, wt, stage[wave], lane);
+  const int64_t row = row0 + (l32 < nv ? l32 : nv - 1);         // clamp loads; stores are guarded
+  f32x16 acc;
+  // ---------------- layer 1
+  if constexpr (KIND != KIND_EMBED) {
+    const vec *W1 = (const vec *)a.W1s + (size_t)w * 64 + lane;
+    const T *pa, *pb;
+    if constexpr (KIND == KIND_EDGE) {
+      pa = (const T *)a.h + (size_t)a.in_src[row] * H + g * V;
+      pb = (const T *)a.h + (size_t)a.in_dst[row] * H + g * V;
+    } else {
+      pa = (const T *)a.h + (size_t)row * H + g * V;
+      const int64_t ar = a.agg_src ? (int64_t)a.agg_src[row] : row;
+      pb = ar < 0 ? (const T *)a.zero_row + g * V : (const T *)a.agg + (size_t)ar * H + g * V;
+    }
+    vec wq[RING];
+#pragma unroll
+    for (int s = 0; s < RING; ++s) wq[s] = W1[(size_t)s * MB * 64];
+    constexpr int MINE = 2 * HS / MB;                           // consecutive slabs of the row this wave fetches
+    static_assert(MINE * MB == 2 * HS && HS % MINE == 0 && 2 * HS >= RING, "");
+    const int s0 = w * MINE;
+    const T *px = s0 < HS ? pa + s0 * SL : pb + (s0 - HS) * SL;
+    vec x[MINE];
+#pragma unroll
+    for (int i = 0; i < MINE; ++i) x[i] = *(const vec *)(px + i * SL);
+    [[maybe_unused]] TailRaw<V> xt;
+    if constexpr (KIND == KIND_EDGE) xt = load_tail<V>(a.edge_feat + (size_t)row * a.De, a.De, 0, g);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = a.b1[32 * w + acc_row(r, g)];
+    vec *xs = (vec *)smem;                                      // [2 HS][64]
+#pragma unroll
+    for (int i = 0; i < MINE; ++i) xs[(s0 + i) * 64 + lane] = x[i];
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < 2 * HS; ++s) {
+      Opd::mma(wq[s % RING], xs[s * 64 + lane], acc);
+      if (s + RING < 2 * HS || (KIND == KIND_EDGE && s + RING == 2 * HS)) wq[s % RING] = W1[(size_t)(s + RING) * MB * 64];
+    }
+    if constexpr (KIND == KIND_EDGE) {
+      const float *xe = a.edge_feat + (size_t)row * a.De;
+      for (int s = 2 * HS; s < a.nslab1; ++s) {                 // edge attributes
+        const vec xv = tail_to_operand<T>(s == 2 * HS ? xt : load_tail<V>(xe, a.De, s - 2 * HS, g));
+        const vec wv = s == 2 * HS ? wq[(2 * HS) % RING] : W1[(size_t)s * MB * 64];
+        Opd::mma(wv, xv, acc);
+      }
+    }
+  } else {
+    // (see mlp2_wave_tile: the op type's row of W1 and the bias, then the fp32 columns)
+    const f32x4 *W1 = (const f32x4 *)a.W1x + (size_t)w * 64 + lane;
+    const EmbedRow er = load_embed_row(a.node_op, a.in_ptr, a.node_dense, a.Dd, row);
+    const float *trow = a.table + (size_t)er.op * H + 32 * w + 4 * g;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 t = *(const f32x4 *)(trow + 8 * q);
+      const f32x4 b = *(const f32x4 *)(a.b1 + 32 * w + 8 * q + 4 * g);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[4 * q + j] = t[j] + b[j];
+    }
+    for (int s = 0; s < a.nslabx; ++s) {
+      const f32x4 xv = embed_columns(er, a.edge_feat, a.De, a.Dd, s * 8 + g * 4);
+      Operand<float>::mma(W1[(size_t)s * MB * 64], xv, acc);
+    }
+  }
+  // ---------------- layer 2
+  const vec *W2 = (const vec *)a.W2s + (size_t)w * 64 + lane;
+  constexpr int RING2 = NC2 < RING ? NC2 : RING;
+  vec wq[RING2];
+#pragma unroll
+  for (int c = 0; c < RING2; ++c) wq[c] = W2[(size_t)c * MB * 64];
+  vec *zs = (vec *)smem;                                        // [NC2][64]
+  if constexpr (KIND != KIND_EMBED) __syncthreads();            // (every wave has read its input fragments)
+#pragma unroll
+  for (int q = 0; q < QB; ++q) zs[(w * QB + q) * 64 + lane] = relu_operand<T>(acc, q);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = a.b2[32 * w + acc_row(r, g)];
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < NC2; ++c) {
+    Opd::mma(wq[c % RING2], zs[c * 64 + lane], acc);
+    if (c + RING2 < NC2) wq[c % RING2] = W2[(size_t)(c + RING2) * MB * 64];
+  }
+  // ---------------- epilogue on this wave's 32 features
+  T *out = (T *)a.out;
+  char *stage = smem + S::ZBYTES + w * BlockStage<T>::BYTES;
+  if constexpr (KIND != KIND_EDGE) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = relu_f32(acc[r]);
+    store_block_via_lds<T, H>(out, row0, nv, w, lane, acc, stage);
+    if constexpr (KIND == KIND_EMBED)
+      if (w == 0) zero_source_rows<T, H>(a, row0, nv, a.in_ptr[row + 1] == a.in_ptr[row], lane);
+  } else {
+    const EdgeTileMeta m = load_edge_meta(a.in_dst, a.n_rows, row0, nv, l32);
+    f32x16 one[1] = {acc};
+    const EdgeRoute e = edge_run_sums<1>(one, m, nv, lane);
+    store_block_rows_via_lds<T, H>(out, e.dsel, w, lane, one[0], stage);
+    if (e.to_c0 || e.to_c1) store_tile_rows<float, H>(a.carry, wt * 2 + (e.to_c1 ? 1 : 0), true, w, g, one[0]);
+  }
 }

@@ -141,7 +141,8 @@ struct xrl_ctx {
   int elem = 4;                 // bytes per stored activation / operand
   int n_cu = 256;               // compute units of the device
   int max_lds = 65536;          // LDS bytes one block may use
-  int64_t p_min_rows = 8192;    // smallest row count for the persistent kernels (XRL_PERSISTENT_MIN_ROWS)
+  int64_t p_min_rows = 8192;    // smallest row count for the persistent kernels (XRL_PERSISTENT_MIN_ROWS) when saving
+  int64_t p_min_rows_forward = 8192;   // for the backward pass, and when not
   int64_t wide_min_rows = 1 << 20;   // ... for the 256-column weight-gradient tiles (XRL_WGRAD_WIDE_MIN_ROWS)
   int64_t resident_max_graphs = 0;   // largest batch (graphs) for the one-launch encoder (XRL_RESIDENT_MAX_GRAPHS)
   int64_t resident_max_tiles = 0;    // ... and the most 32-row tiles (nodes, or edges) of one graph (XRL_RESIDENT_MAX_TILES)
@@ -193,7 +194,7 @@ struct xrl_ctx {
   int32_t *h_counts = nullptr;
   int64_t distinct_min_us = 300;   // smallest estimated encode that is reduced to distinct nodes (XRL_DISTINCT_MIN_US;
                                    // 0 = every batch that can be, -1 = none)
-  int64_t min_rows_now = 0;     // p_min_rows, or 1 for the levels of a reduced batch
+  int64_t min_rows_now = 0;     // the one in force, or 1 for the levels of a reduced batch that is saved
   std::vector<void *> hx;       // last encode of a reduced batch: h of the level below, per class
   std::shared_ptr<DevicePool> blocks;
   hipStream_t copy_stream = nullptr;   // uploads of kCopyStreamBytes and more
@@ -796,15 +797,26 @@ int launch_segsum(xrl_ctx *c, const void *vals, const int32_t *perm, const int32
 
 size_t segsum_carry_floats(int64_t n_rows, int D) { return (size_t)((n_rows + 3) / 4) * 2 * D; }
 
+template <typename T1, typename T, int H, int KIND>
+int launch_mlp2_split(xrl_ctx *c, const Mlp2Args &a) {
+  using S = SplitTile<T, H>;
+  auto kern = mlp2_split_kernel<T1, T, H, KIND>;
+  static bool attr_set = false;          // one attribute per kernel instantiation
+  if (!attr_set) {
+    HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, S::BYTES));
+    attr_set = true;
+  }
+  kern<<<dim3((unsigned)((a.n_blocks + 7) / 8 * 8)), dim3(2 * H), S::BYTES, c->stream>>>(a);
+  HIP_TRY(hipGetLastError());
+  return XRL_OK;
+}
+
 template <typename T, int H>
 int launch_mlp2_h(xrl_ctx *c, int kind, const Mlp2Args &a) {
   if (a.n_rows <= 0) return XRL_OK;
-  const unsigned grid = (unsigned)(((a.n_blocks + 7) / 8) * 8);
-  if (kind == KIND_EMBED) mlp2_kernel<float, T, H, KIND_EMBED><<<dim3(grid), dim3(256), 0, c->stream>>>(a);
-  else if (kind == KIND_EDGE) mlp2_kernel<T, T, H, KIND_EDGE><<<dim3(grid), dim3(256), 0, c->stream>>>(a);
-  else mlp2_kernel<T, T, H, KIND_NODE><<<dim3(grid), dim3(256), 0, c->stream>>>(a);
-  HIP_TRY(hipGetLastError());
-  return XRL_OK;
+  if (kind == KIND_EMBED) return launch_mlp2_split<float, T, H, KIND_EMBED>(c, a);
+  if (kind == KIND_EDGE) return launch_mlp2_split<T, T, H, KIND_EDGE>(c, a);
+  return launch_mlp2_split<T, T, H, KIND_NODE>(c, a);
 }
 
 // Persistent LDS-resident-weights variant (bf16, H <= 128, edge and node kinds).
@@ -945,7 +957,7 @@ int launch_mlp2(xrl_ctx *c, int kind, Mlp2Args &a) {
       return c->m.hidden == 64 ? launch_embedp<64>(c, a) : c->m.hidden == 128 ? launch_embedp<128>(c, a) : launch_embedp<256>(c, a);
     return c->m.hidden == 64 ? launch_mlp2p<64>(c, kind, a) : launch_mlp2p<128>(c, kind, a);
   }
-  a.n_blocks = kind == KIND_EDGE ? (a.n_tiles + 3) / 4 : (a.n_rows + 127) / 128;
+  a.n_blocks = kind == KIND_EDGE ? a.n_tiles : (a.n_rows + 31) / 32;
   switch (c->m.hidden) {
     case 64: return launch_mlp2_h<T, 64>(c, kind, a);
     case 128: return launch_mlp2_h<T, 128>(c, kind, a);
@@ -1938,7 +1950,7 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   const Distinct *q = distinct_of(c, b);
   const LevelGraph whole = batch_graph(b);
   auto lev = [&](int l) -> const LevelGraph & { return q ? q->lv[l] : whole; };
-  c->min_rows_now = q && c->p_min_rows <= kPersistentMinRows ? 1 : c->p_min_rows;
+  c->min_rows_now = !save ? c->p_min_rows_forward : (q && c->p_min_rows <= kPersistentMinRows ? 1 : c->p_min_rows);
   // ---- workspace plan
   const int nh = save ? R + 1 : (R > 0 ? 2 : 1), nagg = save ? R : (R > 0 ? 1 : 0);
   int64_t maxN = 0, max_tiles = 0;
@@ -2257,11 +2269,15 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   if (single_layer) c->Lu = Lu;
   c->stream = (hipStream_t)hip_stream;
   c->elem = model->precision == XRL_PREC_BF16 ? 2 : 4;
-  // Row count from which the persistent kernels replace the streaming one (tuning knob; the
+  // Row count from which the persistent kernels replace the split one (tuning knob; the
   // default is where they start to win; 0 = always, a huge value = never)
   c->p_min_rows = kPersistentMinRows;
   if (const char *e = getenv("XRL_DISTINCT_MIN_US")) c->distinct_min_us = atoll(e);
-  if (const char *e = getenv("XRL_PERSISTENT_MIN_ROWS")) c->p_min_rows = atoll(e);
+  // Saving from these on keeps the forward for the backward pass. Without that, H <= 128, five rounds, us per
+  // encode, persistent / split kernels: 10.5 k nodes 120 / 74, 17.5 k 128 / 96, 34.5 k 141 / 140, 73 k 188 / 232
+  // (H = 64: 17.5 k 73 / 59, 73 k 105 / 113); H = 256: 17.5 k 194 / 215
+  c->p_min_rows_forward = model->hidden <= 128 ? 4 * kPersistentMinRows : kPersistentMinRows;
+  if (const char *e = getenv("XRL_PERSISTENT_MIN_ROWS")) c->p_min_rows = c->p_min_rows_forward = atoll(e);
   // (measured: at H = 256 the 256-column tiles win from about 300 k rows on, at H = 128 from 1 M)
   c->wide_min_rows = model->hidden >= 256 ? (1 << 18) : (1 << 20);
   if (const char *e = getenv("XRL_WGRAD_WIDE_MIN_ROWS")) c->wide_min_rows = atoll(e);
