@@ -203,7 +203,9 @@ int xrl_batch_free(xrl_batch *b);   /* frees host and device copies; NULL is acc
  * XRL_RESIDENT_MAX_GRAPHS (default 256; 0 = never) and XRL_RESIDENT_MAX_TILES (default 4) =
  * largest batch, in graphs and in 32-row tiles of nodes or edges per graph, that xrl_encode runs
  * as one launch with a block per graph (message-passing rounds of the MLP kind, rows of at most
- * 256 bytes, no receiver of more than 32 in-edges; results identical to the other path's);
+ * 256 bytes, no receiver of more than 32 in-edges; results identical to the other path's) when it
+ * saves for the backward pass -- and otherwise too if one of these four variables is set: forward
+ * only, a launch per layer is the faster way;
  * XRL_CLUSTER_MAX_GRAPHS (default 48; 0 = never) = largest batch of graphs of more tiles than
  * that which xrl_encode runs as one launch with several blocks per graph, used when a block per
  * four tiles of the largest graph fits the GPU at once (the few dozen candidates of one rewriting

@@ -161,6 +161,7 @@ struct xrl_ctx {
   Layout Lu;                      // the caller's layout (single_layer)
   float *d_dw_int = nullptr;      // [L.total] internal gradient vector (single_layer)
   int32_t *d_wmap = nullptr;      // [Lu.total] index in the internal vector of each of the caller's weights
+  bool one_launch_forward = false; // forward-only encodes of small batches take the one-launch forms too
   int64_t cluster_max_graphs = 0; // largest batch (graphs) for the one-launch encoder with several blocks per graph
   unsigned cluster_spin_limit = kClusterSpinLimit;   // polls after which one of its waits gives up (XRL_CLUSTER_SPIN_LIMIT)
   int device = 0;               // the device that was current at xrl_create
@@ -1965,7 +1966,7 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   for (int i = 0; i < nagg; ++i) acc(a_rows(i) * H * sizeof(T));        // (GAT: the agg slot holds z)
   for (int i = 0; q && i < nagg; ++i) acc(a_rows(i) * H * sizeof(T));
   const xrl_batch_device &d = b->dev;
-  const bool resident_ok = !gat && !q && H * sizeof(T) <= 256 && d.graph_tile_ptr && R <= kResidentMaxRounds;
+  const bool resident_ok = !gat && !q && (save || c->one_launch_forward) && H * sizeof(T) <= 256 && d.graph_tile_ptr && R <= kResidentMaxRounds;
   const int64_t graph_tiles = std::max<int64_t>((b->max_graph_nodes + 31) / 32, b->max_graph_tiles);
   // blocks per graph of the one-launch encoder: one while a graph's phase is a single pass of a
   // block's four waves; otherwise as many as give every tile of a phase a wave of its own, if
@@ -2281,16 +2282,20 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   // (measured: at H = 256 the 256-column tiles win from about 300 k rows on, at H = 128 from 1 M)
   c->wide_min_rows = model->hidden >= 256 ? (1 << 18) : (1 << 20);
   if (const char *e = getenv("XRL_WGRAD_WIDE_MIN_ROWS")) c->wide_min_rows = atoll(e);
-  // Batches the one-launch encoder takes: one block of four waves per graph wins while every
-  // phase of a graph is a single pass of its waves (measured: 51-node graphs, 9 to 144 of them,
-  // 49 us against 66 us; 340-node graphs 190 us against 122 us). 0 graphs = never.
+  // Batches the one-launch encoders take when saving for the backward pass (0 graphs = never). A forward-only
+  // encode takes them only in a context made with one of the variables below: since a tile of the
+  // launch-per-layer path is split over H / 32 waves that path is the faster one at every size they
+  // cover (us per encode, one launch / a launch per layer: nine 50-node graphs, fp32, H = 64, two
+  // rounds 50 / 38; bf16, H = 128, five rounds: the same graphs 79 / 57, 200 of them 81 / 76, 15 graphs of 338
+  // nodes 97 / 61, of 565 nodes 106 / 76).
+  for (const char *name : {"XRL_RESIDENT_MAX_GRAPHS", "XRL_RESIDENT_MAX_TILES", "XRL_CLUSTER_MAX_GRAPHS", "XRL_CLUSTER_SPIN_LIMIT"})
+    c->one_launch_forward |= getenv(name) != nullptr;
+  // (one block of four waves per graph while every phase of a graph is a single pass of its waves)
   c->resident_max_graphs = 256;
   c->resident_max_tiles = 4;
   if (const char *e = getenv("XRL_RESIDENT_MAX_GRAPHS")) c->resident_max_graphs = atoll(e);
   if (const char *e = getenv("XRL_RESIDENT_MAX_TILES")) c->resident_max_tiles = atoll(e);
   // ... and with several blocks per graph, for the few dozen larger graphs of one rewriting step
-  // (measured, one state of 14 / 31 / 51 graphs: 338-node graphs 97 / 107 / 125 us against
-  // 120 / 122 / 125 us for a launch per phase; 565-node graphs 105 / 128 us against 120 / 127 us)
   c->cluster_max_graphs = 48;
   if (const char *e = getenv("XRL_CLUSTER_MAX_GRAPHS")) c->cluster_max_graphs = std::min<int64_t>(atoll(e), kClusterMaxGraphs);
   if (const char *e = getenv("XRL_CLUSTER_SPIN_LIMIT")) c->cluster_spin_limit = (unsigned)std::max<long long>(0, std::min<long long>(atoll(e), kClusterSpinLimit));
