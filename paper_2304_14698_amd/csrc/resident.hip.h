@@ -1,13 +1,13 @@
 // One-launch encoder for small batches (the agent's own inference loop encodes one state of a few
 // dozen candidate graphs per step, Section 4.2): one block per graph runs the node-update layer,
 // every message-passing round and the global-update layer (Section 3.4) on its graph, with block
-// barriers where the streaming path has kernel boundaries. A graph's node states and received
-// sums live in the same global buffers as on the streaming path (a few hundred KB per graph: they
+// barriers where the other path has kernel boundaries. A graph's node states and received
+// sums live in the same global buffers as with a launch per layer (a few hundred KB per graph: they
 // stay in the CU's L1 and the XCD's L2), so both paths save the same activations for the
 // backward pass; what the launch removes is a dozen launch latencies and pipeline drains.
 //
 // Tiles, arithmetic and the order of every sum are those of mlp2_wave_tile and
-// graph_readout_block, so the embeddings equal the streaming path's bit for bit. Edge tiles
+// graph_readout_block, so the embeddings equal those of a launch per layer bit for bit. Edge tiles
 // come from the packer's per-graph table (no tile spans two graphs, no receiver spans two
 // tiles), which is why no carry fix-up is needed here.
 #pragma once
@@ -65,7 +65,7 @@ __device__ __forceinline__ void fill_lds(char *dst, const void *src, int bytes) 
 
 // LDS: [four waves' row staging | W1 of the running phase | its W2 | the embed layer's table];
 // the readout reuses it from the start. With a handful of tiles per graph a weight fragment
-// requested from L2 one slab ahead of its MFMAs (as the streaming kernel does, where other waves
+// requested from L2 one slab ahead of its MFMAs (as the split kernel does, where other waves
 // hide the wait) would cost a memory round trip per slab, so every phase first copies its two
 // matrices into LDS in one batch of loads.
 template <typename T, int H>

@@ -119,7 +119,7 @@ static const char *const kTimedNames[TK_COUNT] = {"embed", "edge", "edge_fixup",
 
 constexpr int64_t kMaxFusedSlots = 4096;   // largest G the single-launch heads kernel takes
 constexpr int kCounts = 3 * kMaxLevels;
-constexpr int64_t kPersistentMinRows = 8192;   // rows from which the persistent kernels replace the streaming one
+constexpr int64_t kPersistentMinRows = 8192;   // rows from which the persistent kernels replace the split one
 constexpr int64_t kClusterMaxGraphs = 256; // largest G of the one-launch encoder with several blocks per graph
 
 // Scratch of xrl_policy_value_static, the entry point that allocates nothing: per-state counters,
@@ -206,7 +206,7 @@ struct xrl_ctx {
   // what the forward kernels of large bf16 batches keep for the backward pass (inside ws): relu(z1)
   // of the embed MLP and of every round's edge and node MLP, and the mask bits of every round's
   // per-edge output (which is summed per receiver and never stored itself)
-  bool fwd_kept = false;
+  bool fwd_kept = false, embed_kept = false;   // (attention rounds: of the embed MLP alone)
   void *z1_embed = nullptr;
   std::vector<void *> z1_edge, z1_node;
   std::vector<uint16_t *> ym_edge, ym_node, zm_edge, zm_node;   // mask bits of y and of z1, per round
@@ -1459,7 +1459,7 @@ LevelGraph batch_graph(const xrl_batch *b) {
   return g;
 }
 Distinct *distinct_of(const xrl_ctx *c, const xrl_batch *b) {
-  return b->distinct && b->owner == c->id ? b->distinct.get() : nullptr;   // (levels and groupings are on its stream)
+  return b->owner == c->id ? b->distinct.get() : nullptr;   // (the owner's alone: it is made and used on its stream)
 }
 
 // The groupings of a reduced batch that the backward pass goes by.
@@ -1521,7 +1521,9 @@ int make_groupings(xrl_ctx *c, const xrl_batch *b, Distinct *q) {
 // the steps pays once: 430 us 622 / 337 forward only.
 bool distinct_pays(const xrl_ctx *c, const xrl_batch *b) {
   const int H = c->m.hidden, R = c->m.rounds, De = c->m.d_edge;
-  if (c->distinct_min_us < 0 || c->m.round_kind != XRL_ROUND_MLP || R < 1 || R + 1 > kMaxLevels || b->G <= b->S || b->N < 1 || b->E < 1 || b->n_split_tiles > 0) return false;
+  if (c->distinct_min_us < 0 || c->m.round_kind != XRL_ROUND_MLP || R < 1 || R + 1 > kMaxLevels || b->G <= b->S || b->N < 1 || b->E < 1 || b->n_split_tiles > 0 ||
+      b->N + b->E > (int64_t)1 << 28)                       // (table slots and sort keys are 32-bit)
+    return false;
   const double flops = 2.0 * R * H * ((double)b->N * 3 * H + (double)b->E * (3 * H + De));
   const double us = flops / (c->elem == 2 ? 7e8 : 7e7);                                 // (flops per us measured)
   if (us < (double)c->distinct_min_us) return false;
@@ -1686,11 +1688,13 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   // ---- scratch plan
   size_t need = 0;
   auto acc = [&](size_t bytes) { need += align_up(bytes); };
+  const bool gat = m.round_kind == XRL_ROUND_GAT;
   const bool kept = c->fwd_kept;                                   // the forward kept z1 and the ReLU masks
   // the per-edge gradients w.r.t. h_receiver leave the edge kernel already summed per receiver
   // (edge tiles end at receiver boundaries unless a receiver has more than 32 in-edges)
   const bool fold = kept && b->n_split_tiles == 0;
-  for (int i = 0; i < (kept ? 2 : 3); ++i) acc((size_t)M * H * sizeof(T));      // (z1,) dz1, dz2
+  const bool embed_kept = c->embed_kept, recompute = gat ? !embed_kept : !kept;
+  for (int i = 0; i < (recompute ? 3 : 2); ++i) acc((size_t)M * H * sizeof(T));   // (z1,) dz1, dz2
   acc((size_t)(maxE + (q ? maxN : 0)) * H * sizeof(T));            // per-edge d h_sender; a reduced batch: dh behind it
   acc((size_t)M * H * sizeof(T));                                  // d h_receiver: per edge, or summed per receiver
   for (int i = 0; i < 3; ++i) acc((size_t)maxN * H * sizeof(T));   // dh (two buffers), dagg
@@ -1702,7 +1706,6 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
                                small_wgrad_partial_floats(c->L.readout, G));
   acc(part * 4);
   acc((size_t)G * H * 4); acc((size_t)G * H * 4); acc((size_t)G * (H + Dg) * 4);
-  const bool gat = m.round_kind == XRL_ROUND_GAT;
   if (gat) {                                                       // softmax weights and score gradients
     for (int i = 0; i < 2; ++i) acc((size_t)maxE * 4);
     for (int i = 0; i < 4; ++i) acc((size_t)maxN * 4);
@@ -1722,7 +1725,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   if (rc) return rc;
   if (q && !q->grouped && (rc = make_groupings(c, b, q))) return rc;
   Bump bump{c->bws};
-  T *z1 = kept ? nullptr : bump.take<T>((size_t)M * H);
+  T *z1 = recompute ? bump.take<T>((size_t)M * H) : nullptr;
   T *dz1 = bump.take<T>((size_t)M * H), *dz2 = bump.take<T>((size_t)M * H);
   T *dsrc = bump.take<T>((size_t)(maxE + (q ? maxN : 0)) * H), *ddst = bump.take<T>((size_t)M * H);
   T *dhA = bump.take<T>((size_t)maxN * H), *dhB = bump.take<T>((size_t)maxN * H);
@@ -1816,7 +1819,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   };
   auto mlp_bwd = [&](int kind, const EncMlp &e, const uint16_t *z1mask, const uint16_t *ymask) -> int {
     if constexpr (sizeof(T) == 2) {
-      if (kept) {
+      if (kept || (embed_kept && kind == KIND_EMBED)) {
         za.n_rows = a.n_rows; za.W2bt = e.W2bt; za.W1bt = e.W1bt; za.dy = a.dy;
         za.z1mask = z1mask; za.ymask = ymask; za.dx_a = a.dx_a; za.dx_b = a.dx_b;
         za.dy_index = (dy_by_graph && kind != KIND_EDGE) ? d.node_graph : nullptr;
@@ -1923,7 +1926,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   set_graph(g0);
   set_w(c->embed);
   a.n_rows = N0; a.h = nullptr; a.agg = nullptr; a.y = c->h[0]; a.dy = dhA; a.dx_a = nullptr; a.dx_b = nullptr;
-  { Timed t(c, TK_BWD_EMBED); rc = mlp_bwd(KIND_EMBED, c->embed, kept ? c->zm_embed : nullptr, kept ? c->ym_embed : nullptr); }
+  { Timed t(c, TK_BWD_EMBED); rc = mlp_bwd(KIND_EMBED, c->embed, embed_kept ? c->zm_embed : nullptr, embed_kept ? c->ym_embed : nullptr); }
   if (rc) return rc;
   if constexpr (sizeof(T) == 2) {
     // first layer: dW1 = X^T dz1 on the transpose-read kernel, X written out once; its Kx real rows
@@ -1934,7 +1937,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
         g0.edge_feat, g0.in_ptr, g0.node_op, g0.node_dense, N0, De, m.n_op_types, m.n_node_dense, Kp, xrows);
     wa.n_rows = N0; wa.Ka = Kp; wa.dZ = dz1; wa.A = xrows;
     if ((rc = launch_wgrad_embed_rows<T>(c, wa, Kx, dweights + c->L.embed.w[0], dweights + c->L.embed.b[0]))) return rc;
-    wa.Ka = H; wa.dZ = dz2; wa.A = kept ? c->z1_embed : z1;
+    wa.Ka = H; wa.dZ = dz2; wa.A = embed_kept ? c->z1_embed : z1;
     if ((rc = launch_wgrad<T>(c, WG_PLAIN, wa, dweights + c->L.embed.w[1], dweights + c->L.embed.b[1]))) return rc;
   } else {
     if ((rc = wgrads(WG_EMBED, N0, Kx, c->L.embed, nullptr))) return rc;
@@ -1999,8 +2002,23 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
       }
     }
   }
+  bool keep_embed = keep;
+  if constexpr (sizeof(T) == 2) {
+    // (attention rounds: the embed MLP's backward from what its forward kept; recomputing it took 81 us at 148 k
+    // nodes, H = 128, from mask bits half of that)
+    if (save && gat && N > 0) {
+      Mlp2Args t;
+      memset(&t, 0, sizeof(t));
+      t.De = De; t.Tn = m.n_op_types; t.Dd = m.n_node_dense; t.n_rows = N; t.nslabx = c->embed.nslabx;
+      keep_embed = mlp2p_applies(c, KIND_EMBED, t);
+    }
+  }
   auto ym_words = [&](int l) { return (size_t)lev(l).n_tiles * (H / 32) * 64; };          // 16-bit words of one edge MLP's mask bits (z1 or y)
   auto nm_words = [&](int l) { return (size_t)((lev(l).N + 31) / 32) * (H / 32) * 64; };  // ... of a node-side MLP's
+  if (keep_embed && !keep) {
+    acc((size_t)N * H * sizeof(T));
+    acc(nm_words(0) * 2); acc(nm_words(0) * 2);
+  }
   if (keep) {
     for (int l = 0; l <= R; ++l) {
       acc((size_t)lev(l).N * H * sizeof(T));
@@ -2039,14 +2057,17 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   c->ro_act[0] = bump.take<float>((size_t)G * H);
   c->ro_act[1] = bump.take<float>((size_t)G * H);
   c->fwd_kept = keep;
+  c->embed_kept = keep_embed;
   c->z1_edge.assign(R, nullptr); c->z1_node.assign(R, nullptr);
   c->ym_edge.assign(R, nullptr); c->zm_edge.assign(R, nullptr);
   c->ym_node.assign(R, nullptr); c->zm_node.assign(R, nullptr);
   c->z1_embed = nullptr; c->ym_embed = c->zm_embed = nullptr;
-  if (keep) {
+  if (keep_embed) {
     c->z1_embed = bump.take<T>((size_t)lev(0).N * H);
     c->zm_embed = bump.take<uint16_t>(nm_words(0));
     c->ym_embed = bump.take<uint16_t>(nm_words(0));
+  }
+  if (keep) {
     for (int r = 0; r < R; ++r) {
       c->z1_node[r] = bump.take<T>((size_t)lev(r + 1).N * H);
       c->z1_edge[r] = bump.take<T>((size_t)lev(r + 1).E * H);
