@@ -291,9 +291,12 @@ __global__ __launch_bounds__(256) void tile_write_kernel(const TileLevels a) {
 }
 
 // ---- groupings for the backward pass. What a class receives from the level above: the gradients of the
-// level's classes that split it and those of the level's edges whose sender's class it is, rows of one
-// list [edges | classes]; and the classes of the last level, the pool's gradient for each of their
-// nodes. All groupings are made in one stable radix sort: each owns a range of items and a
+// level's edges whose sender's class it is, those of the level's classes that split it, and what these
+// received, rows of one list [edges as senders | classes | received]; and the classes of the last
+// level, the pool's gradient for each of their nodes. The three are summed in one fp32 sum and rounded
+// once, like a node's gradient in a batch that is not reduced. Received: per class, summed by the
+// edge kernel (a class without in-edges has no such row: value -1, a row of zeros), or per edge.
+// All groupings are made in one stable radix sort: each owns a range of items and a
 // range of keys, in the same order. (A sender may have thousands of edges here, one from every
 // graph it is shared by: a sum per segment cut into 16-row pieces, not a loop per node.)
 constexpr int kMaxGroupings = kMaxLevels;
@@ -301,8 +304,11 @@ struct GroupArgs {
   int n;                                       // groupings
   int64_t item0[kMaxGroupings + 1];            // first item of each
   uint32_t key0[kMaxGroupings + 1];            // first key of each
-  int64_t n_edges[kMaxGroupings];              // level groupings: the items below it are edges, the others classes
+  int64_t n_edges[kMaxGroupings];              // level groupings: the first items, edges as senders ...
+  int64_t n_cls[kMaxGroupings];                // ... then classes, then received rows (members: nodes only)
   const int32_t *src[kMaxGroupings];           // level groupings: senders of the edges
+  const int32_t *dst[kMaxGroupings];           // ... their receivers; nullptr: received rows are per class
+  const int32_t *agg_src[kMaxGroupings];       // ... -1 for a class without in-edges
   const int32_t *key[kMaxGroupings];           // key of each class, or (members) of each node
   const int32_t *val[kMaxGroupings];           // value of each item; nullptr: the item's index
   int32_t *ptr[kMaxGroupings];                 // [keys + 1] out: first sorted item of each key
@@ -322,8 +328,11 @@ __global__ __launch_bounds__(256) void group_items_kernel(const GroupArgs a, uin
   if (i >= a.item0[a.n]) return;
   const int g = grouping_of(a, i);
   const int64_t j = i - a.item0[g];
-  const int64_t c = j < a.n_edges[g] ? a.src[g][j] : j - a.n_edges[g];
-  items[i] = make_uint2(a.key0[g] + (uint32_t)a.key[g][c], (uint32_t)(a.val[g] ? a.val[g][j] : (int32_t)j));
+  const int64_t k = j - a.n_edges[g], q = k - a.n_cls[g];
+  const int64_t c = k < 0 ? a.src[g][j] : q < 0 ? k : a.dst[g] ? a.dst[g][q] : q;
+  int32_t v = a.val[g] ? a.val[g][j] : (int32_t)j;
+  if (q >= 0 && !a.dst[g] && a.agg_src[g][c] < 0) v = -1;
+  items[i] = make_uint2(a.key0[g] + (uint32_t)a.key[g][c], (uint32_t)v);
 }
 constexpr int kSortItems = 4096;               // items per block: four waves of 1024 consecutive ones
 __global__ __launch_bounds__(256) void sort_count_kernel(const uint2 *items, int64_t n, int shift, int32_t *hist, int n_blocks) {

@@ -55,7 +55,8 @@ __device__ __forceinline__ int seg_of_row(const int32_t *ptr, int64_t n_seg, int
 
 struct SegsumArgs {
   const void *vals;     // [*, D] rows, type TIn
-  const int32_t *perm;  // nullable: row r of the reduction reads vals row perm[r]
+  const int32_t *perm;  // nullable: row r of the reduction reads vals row perm[r], or zeros where that is negative
+  const void *zero_row; // D zeros of type TIn (with perm)
   const int32_t *ptr;   // [n_seg + 1]
   const int32_t *row_seg;  // nullable: segment of vals row i (saves the search for a sub-tile's first segment)
   const int32_t *pos_seg;  // nullable: segment of row r of the reduction
@@ -81,7 +82,7 @@ __global__ __launch_bounds__(256) void segsum_kernel(const SegsumArgs a) {
   for (int i = 0; i < RT; ++i) {
     if (i < nv) {
       int64_t r = a.perm ? (int64_t)a.perm[r0 + i] : (r0 + i);
-      RowVec<TIn, VEC>::load(vals + (size_t)r * a.D + c, v[i]);
+      RowVec<TIn, VEC>::load((r < 0 ? (const TIn *)a.zero_row : vals + (size_t)r * a.D) + c, v[i]);
     }
   }
   int seg = a.pos_seg ? a.pos_seg[r0] : a.row_seg ? a.row_seg[a.perm ? (int64_t)a.perm[r0] : r0] : seg_of_row(a.ptr, a.n_seg, r0);
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(256) void edge_tile_fixup(const int32_t *tile_ptr, 
 // group of D / VEC lanes per node, each lane a 16-byte column slice; the edges are taken in index
 // order and summed in fp32, so the result is run-to-run identical. One pass over dh instead of
 // one per direction. recv_summed: d_recv is [n_nodes, D], already summed per receiver (rows of nodes
-// without in-edges hold nothing and are not read). out_ptr nullptr: the in-edges' part only.
+// without in-edges hold nothing and are not read).
 // masked_out (or nullptr: the sum replaces dh): the sum goes there instead, multiplied by the ReLU
 // mask of the layer that produced h -- ymask, the mask bits a forward kernel kept for its output
 // (see Mlp2Args: [tiles of 32 nodes][D / 32][64 lanes] words; VEC must be 8) -- which is the dz2 the
@@ -218,7 +219,7 @@ __global__ __launch_bounds__(256) void node_grad_gather_kernel(const T *d_recv, 
   const int64_t n = gt / lpr;
   if (n >= n_nodes) return;
   const int c = (int)(gt - n * lpr) * VEC;
-  const int e0 = in_ptr[n], e1 = in_ptr[n + 1], k0 = out_ptr ? out_ptr[n] : 0, k1 = out_ptr ? out_ptr[n + 1] : 0;
+  const int e0 = in_ptr[n], e1 = in_ptr[n + 1], k0 = out_ptr[n], k1 = out_ptr[n + 1];
   T *o = dh + (size_t)n * D + c;
   float acc[VEC], v[VEC];
   RowVec<T, VEC>::load(o, acc);

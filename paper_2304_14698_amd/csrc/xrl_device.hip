@@ -467,8 +467,8 @@ struct LevelGraph {
   const int32_t *in_ptr = nullptr, *in_src = nullptr, *in_dst = nullptr, *out_ptr = nullptr, *out_pos = nullptr;
   const int32_t *tile_ptr = nullptr, *agg_src = nullptr, *node_op = nullptr;
   const float *edge_feat = nullptr, *node_dense = nullptr;
-  // level l > 0: each class's class one level below, and the rows [edges | classes] grouped by the class
-  // one level below that their gradients go to
+  // level l > 0: each class's class one level below, and the rows [edges | classes | received] grouped by
+  // the class one level below that their gradients go to (see GroupArgs)
   int32_t *self = nullptr, *down_ptr = nullptr, *down = nullptr, *down_seg = nullptr;
 };
 struct Distinct {
@@ -476,7 +476,8 @@ struct Distinct {
   LevelGraph lv[kMaxLevels];
   int32_t *cls[kMaxLevels] = {};           // [N] class of each node at each level
   int32_t *mem_ptr = nullptr, *mem_graph = nullptr, *mem_seg = nullptr;   // the batch's nodes by class at the last level
-  bool grouped = false;                    // the groupings the backward pass needs have been made
+  bool grouped = false;                    // the groupings the backward pass needs have been made ...
+  bool grouped_fold = false;               // ... for gradients that arrive summed per receiver
   DeviceBlock block[2];
 };
 
@@ -769,6 +770,7 @@ int launch_segsum_rt(xrl_ctx *c, const void *vals, const int32_t *perm, const in
   }
   SegsumArgs a;
   a.vals = vals; a.perm = perm; a.ptr = ptr; a.n_rows = n_rows; a.n_seg = n_seg;
+  a.zero_row = c->zero_row;
   a.row_seg = perm ? nullptr : row_seg;
   a.pos_seg = pos_seg;
   a.D = D; a.RT = RT; a.out = out; a.carry = carry;
@@ -1462,15 +1464,16 @@ Distinct *distinct_of(const xrl_ctx *c, const xrl_batch *b) {
   return b->owner == c->id ? b->distinct.get() : nullptr;   // (the owner's alone: it is made and used on its stream)
 }
 
+// Rows of a level's list [edges | classes | received]. fold: received rows are summed per class.
+int64_t level_rows(const LevelGraph &g, bool fold) { return g.E + g.N + (fold ? g.N : g.E); }
 // The groupings of a reduced batch that the backward pass goes by.
-GroupArgs groupings(const xrl_batch *b, Distinct *q) {
+GroupArgs groupings(const xrl_batch *b, Distinct *q, bool fold) {
   GroupArgs a;
   memset(&a, 0, sizeof(a));
   int64_t item = 0, key = 0;
-  auto add = [&](int64_t items, int64_t keys, int64_t n_edges, const int32_t *src, const int32_t *k, const int32_t *val,
-                 int32_t *ptr, int32_t *seg, int32_t *out) {
+  auto add = [&](int64_t items, int64_t keys, const int32_t *k, const int32_t *val, int32_t *ptr, int32_t *seg, int32_t *out) {
     a.item0[a.n] = item; a.key0[a.n] = (uint32_t)key;
-    a.n_edges[a.n] = n_edges; a.src[a.n] = src; a.key[a.n] = k; a.val[a.n] = val;
+    a.key[a.n] = k; a.val[a.n] = val;
     a.ptr[a.n] = ptr; a.seg[a.n] = seg; a.out[a.n] = out;
     item += items; key += keys;
     ++a.n;
@@ -1479,18 +1482,20 @@ GroupArgs groupings(const xrl_batch *b, Distinct *q) {
   const int R = q->levels - 1;
   for (int l = 1; l <= R; ++l) {
     LevelGraph &g = q->lv[l];
-    add(g.E + g.N, q->lv[l - 1].N, g.E, g.in_src, g.self, nullptr, g.down_ptr, g.down_seg, g.down);
+    a.n_edges[a.n] = g.E; a.n_cls[a.n] = g.N; a.src[a.n] = g.in_src; a.dst[a.n] = fold ? nullptr : g.in_dst; a.agg_src[a.n] = g.agg_src;
+    add(level_rows(g, fold), q->lv[l - 1].N, g.self, nullptr, g.down_ptr, g.down_seg, g.down);
   }
-  add(b->N, q->lv[R].N, 0, nullptr, q->cls[R], b->dev.node_graph, q->mem_ptr, q->mem_seg, q->mem_graph);
+  a.n_cls[a.n] = b->N;
+  add(b->N, q->lv[R].N, q->cls[R], b->dev.node_graph, q->mem_ptr, q->mem_seg, q->mem_graph);
   return a;
 }
-size_t grouping_bytes(const xrl_batch *b, Distinct *q) {
-  const GroupArgs a = groupings(b, q);
+size_t grouping_bytes(const xrl_batch *b, Distinct *q, bool fold) {
+  const GroupArgs a = groupings(b, q, fold);
   const int64_t n = a.item0[a.n], nb = (n + kSortItems - 1) / kSortItems;
   return 2 * align_up((size_t)n * 8) + align_up((size_t)nb * 256 * 4) + 1024;
 }
-int make_groupings(xrl_ctx *c, const xrl_batch *b, Distinct *q) {
-  const GroupArgs a = groupings(b, q);
+int make_groupings(xrl_ctx *c, const xrl_batch *b, Distinct *q, bool fold) {
+  const GroupArgs a = groupings(b, q, fold);
   const int64_t n = a.item0[a.n];
   const int nb = (int)((n + kSortItems - 1) / kSortItems);
   Bump bump{c->bws};
@@ -1508,6 +1513,7 @@ int make_groupings(xrl_ctx *c, const xrl_batch *b, Distinct *q) {
   HIP_TRY(hipGetLastError());
   // (while a stream is being captured nothing runs: eager calls make them for themselves)
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  q->grouped_fold = fold;
   q->grouped = hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
   return XRL_OK;
 }
@@ -1634,7 +1640,7 @@ int find_distinct(xrl_ctx *c, xrl_batch *b) {
     tl.chunk0[l] = chunks;
     o[l].src = plan(e * 4); o[l].dst = plan(e * 4); o[l].self = plan(n * 4);
     o[l].tile = plan((e / 16 + 2 * nc + 4) * 4);
-    o[l].dptr = plan((q->lv[l - 1].N + 1) * 4); o[l].down = plan((e + n) * 4); o[l].dseg = plan((e + n) * 4);
+    o[l].dptr = plan((q->lv[l - 1].N + 1) * 4); o[l].down = plan((e + n + std::max(e, n)) * 4); o[l].dseg = plan((e + n + std::max(e, n)) * 4);
   }
   const size_t o_mptr = plan((q->lv[R].N + 1) * 4), o_mgraph = plan(N * 4), o_mseg = plan(N * 4);
   const size_t o_cuts = plan((size_t)chunks * kTileChunkMax * 4), o_count = plan((size_t)(chunks + 1) * 4);
@@ -1695,8 +1701,12 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   const bool fold = kept && b->n_split_tiles == 0;
   const bool embed_kept = c->embed_kept, recompute = gat ? !embed_kept : !kept;
   for (int i = 0; i < (recompute ? 3 : 2); ++i) acc((size_t)M * H * sizeof(T));   // (z1,) dz1, dz2
-  acc((size_t)(maxE + (q ? maxN : 0)) * H * sizeof(T));            // per-edge d h_sender; a reduced batch: dh behind it
-  acc((size_t)M * H * sizeof(T));                                  // d h_receiver: per edge, or summed per receiver
+  // per-edge d h_sender; d h_receiver: per edge, or summed per receiver (a reduced batch: d h_sender, the
+  // classes' own dh and d h_receiver one behind the other, see GroupArgs)
+  int64_t max_rows = 0;
+  for (int l = 1; q && l <= R; ++l) max_rows = std::max(max_rows, level_rows(lev(l), fold));
+  acc((size_t)(q ? max_rows : maxE) * H * sizeof(T));
+  if (!q) acc((size_t)M * H * sizeof(T));
   for (int i = 0; i < 3; ++i) acc((size_t)maxN * H * sizeof(T));   // dh (two buffers), dagg
   // bf16: the node-update layer's input rows are written out for its weight gradient, Kp columns
   const int Kx = De + m.n_op_types + m.n_node_dense, Kp = (Kx + 7) / 8 * 8;
@@ -1716,18 +1726,18 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   const size_t o_reduced = need;
   if (q) {
     acc((size_t)maxN * H * 4);
-    acc((size_t)((std::max(N, maxE + maxN) + 15) / 16) * 2 * H * 4);
+    acc((size_t)((std::max(N, max_rows) + 15) / 16) * 2 * H * 4);
     acc((size_t)G * H * 4);
-    sort_bytes = q->grouped ? 0 : grouping_bytes(b, q);
+    sort_bytes = q->grouped && q->grouped_fold == fold ? 0 : grouping_bytes(b, q, fold);
     need = std::max(need, sort_bytes);
   }
   int rc = ensure_bws(c, need);
   if (rc) return rc;
-  if (q && !q->grouped && (rc = make_groupings(c, b, q))) return rc;
+  if (q && !(q->grouped && q->grouped_fold == fold) && (rc = make_groupings(c, b, q, fold))) return rc;
   Bump bump{c->bws};
   T *z1 = recompute ? bump.take<T>((size_t)M * H) : nullptr;
   T *dz1 = bump.take<T>((size_t)M * H), *dz2 = bump.take<T>((size_t)M * H);
-  T *dsrc = bump.take<T>((size_t)(maxE + (q ? maxN : 0)) * H), *ddst = bump.take<T>((size_t)M * H);
+  T *dsrc = bump.take<T>((size_t)(q ? max_rows : maxE) * H), *ddst = q ? nullptr : bump.take<T>((size_t)M * H);
   T *dhA = bump.take<T>((size_t)maxN * H), *dhB = bump.take<T>((size_t)maxN * H);
   T *dagg = bump.take<T>((size_t)maxN * H);
   bf16_t *xrows = embed_rows ? bump.take<bf16_t>((size_t)N0 * Kp) : nullptr;
@@ -1742,7 +1752,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   }
   bump.off = o_reduced;
   float *csum = q ? bump.take<float>((size_t)maxN * H) : nullptr;
-  float *ccarry = q ? bump.take<float>((size_t)((std::max(N, maxE + maxN) + 15) / 16) * 2 * H) : nullptr;
+  float *ccarry = q ? bump.take<float>((size_t)((std::max(N, max_rows) + 15) / 16) * 2 * H) : nullptr;
   float *dpool_rows = q ? bump.take<float>((size_t)G * H) : nullptr;
   constexpr int PV = 16 / sizeof(T);
   // the gradients of the rows `vals`, summed per segment (fp32) and stored: masked, as the dz2 of the layer
@@ -1881,7 +1891,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
     const int64_t N = g.N, E = g.E;
     const void *h_in = q ? c->hx[r + 1] : c->h[r];
     set_graph(g);
-    if (q) dhB = dsrc + (size_t)E * H;
+    if (q) { dhB = dsrc + (size_t)E * H; ddst = dhB + (size_t)N * H; }
     set_w(c->node[r]);
     a.n_rows = N; a.h = h_in; a.agg = c->agg[r + 1]; a.y = c->h[r + 1]; a.dy = dhA;
     a.dx_a = dhB; a.dx_b = dagg;
@@ -1899,6 +1909,12 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
     // dh[r] = d(node MLP)/dh + sum over in-edges of d h_receiver + sum over out-edges of d h_sender
     const uint16_t *below = kept ? (r > 0 ? c->ym_node[r - 1] : c->ym_embed) : nullptr;
     Timed timed(c, TK_GRAD_GATHER);
+    if (q) {
+      // ... of all the classes that split one of the level below, masked as below
+      dz2_given = below != nullptr;
+      if ((rc = contract(T(), dsrc, g.down, g.down_ptr, g.down_seg, level_rows(g, fold), lev(r).N, below, below ? dz2 : dhA))) return rc;
+      continue;
+    }
     if (E > 0) {
       const int64_t threads = N * (H / PV);
       // from the kept forward: the sum leaves multiplied by the output mask of the layer that
@@ -1907,19 +1923,13 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
       T *masked_out = nullptr;
       const uint16_t *mask = nullptr;
       if constexpr (sizeof(T) == 2) {
-        if (kept && !q) { masked_out = dz2; mask = below; }
+        if (kept) { masked_out = dz2; mask = below; }
       }
       node_grad_gather_kernel<T, PV><<<dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, c->stream>>>(
           ddst, dsrc, g.in_ptr, g.out_ptr, g.out_pos, N, H, dhB, fold ? 1 : 0, masked_out, mask);
       dz2_given = masked_out != nullptr;
     }
-    if (q) {
-      // ... and on to the classes of the level below, masked as above
-      dz2_given = below != nullptr;
-      if ((rc = contract(T(), dsrc, g.down, g.down_ptr, g.down_seg, E + N, lev(r).N, below, below ? dz2 : dhA))) return rc;
-    } else {
-      std::swap(dhA, dhB);
-    }
+    std::swap(dhA, dhB);
   }
   // ---- node-update layer backward (weights only: its inputs are data)
   const LevelGraph &g0 = lev(0);
