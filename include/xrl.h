@@ -193,6 +193,9 @@ int xrl_batch_free(xrl_batch *b);   /* frees host and device copies; NULL is acc
 /* ---- context --------------------------------------------------------------------------------
  * weights_host: xrl_weight_count floats. hip_stream: a hipStream_t (NULL = default stream).
  * Errors: NULL, UNSUPPORTED (hidden not in {64,128,256}, mlp_layers not 1 or 2, ...), VALUE, HIP, OOM.
+ * Neither this nor xrl_set_weights while the stream is being captured (HIP): a replay would send whatever
+ * the staging buffer holds by then. New weights queue behind the work on the stream and are what
+ * graphs recorded before compute with from then on.
  * mlp_layers = 1 (one learned matrix per layer, Section 3.4 as printed) runs on the two-layer kernels
  * with an identity second layer, which changes no result; weights and gradients keep the one-layer
  * layout of xrl_weight_tensor.

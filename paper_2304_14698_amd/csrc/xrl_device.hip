@@ -638,6 +638,14 @@ bool copy_finite(float *dst, const float *src, int64_t n) {
   return bad == 0;
 }
 
+// Calls that send host memory which may change or go away after they return: a replay would read it again.
+int refuse_capture(const xrl_ctx *c, const char *who) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) return XRL_OK;
+  (void)hipGetLastError();
+  return fail(XRL_ERR_HIP, "%s: the stream is being captured", who);
+}
+
 // New weights: copied (and checked) piece by piece into pinned memory, each piece on its way to the GPU
 // while the next is copied, then one kernel writes the flat vector and every fragment-ordered
 // copy. Queued on the context's stream; the caller's vector is free on return. A value that is not
@@ -645,6 +653,7 @@ bool copy_finite(float *dst, const float *src, int64_t n) {
 // H = 128 (2.6 MB), 0.35 ms at H = 256 (9.4 MB), of which the caller's thread is held 0.08 and 0.26 ms by
 // the copy and its check; one thread arranging the copies on the host took 2.3 and 10.5 ms.
 int upload_weights(xrl_ctx *c, const float *w_user) {
+  if (int rc = refuse_capture(c, "xrl_set_weights")) return rc;
   HIP_TRY(hipEventSynchronize(c->wstage_free));            // the pinned copy of the call before has left
   constexpr int64_t kPiece = 1 << 16;                       // floats: stays in the core's cache between copy and check
   constexpr int64_t kSend = 1 << 19;                        // floats per transfer
@@ -2445,11 +2454,7 @@ int xrl_batch_upload(xrl_ctx *c, xrl_batch *b) {
   if (b->uploaded) return XRL_OK;
   const int Dd = b->model.n_node_dense, De = b->model.d_edge;
   const int64_t N = b->N, E = b->E;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();             // (a replay would read the host copy again, which may be gone)
-    return fail(XRL_ERR_HIP, "xrl_batch_upload: the stream is being captured");
-  }
+  if (int rc = refuse_capture(c, "xrl_batch_upload")) return rc;
   // the device block: what the host sends, then what the device writes itself
   size_t off = b->send_bytes;
   auto plan = [&](size_t bytes) { size_t o = off; off += align_up(bytes + 16); return o; };

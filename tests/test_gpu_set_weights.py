@@ -52,3 +52,39 @@ def test_new_weights(hidden, precision, round_kind, layers):
         for a, b in zip(g, want[i]):
             assert torch.equal(a.cpu(), b)
     enc.close()
+
+
+def test_refused_while_the_stream_is_captured():
+    """A captured copy would send whatever the staging buffer holds at each replay. The capture goes on, and
+    new weights given afterwards are what its replays use."""
+    import torch
+    import paper_2304_14698_amd as xrl
+    model, state = synth.make_config(2, n_cand=3)
+    rng = np.random.Generator(np.random.PCG64(8))
+    w = [synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1) for _ in range(2)]
+    side = torch.cuda.Stream()
+    enc = xrl.Encoder(model, w[0], stream=side)
+    batch = enc.pack(state)
+    first = enc.encode(batch)
+    out = torch.empty_like(first)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side, capture_error_mode="relaxed"):
+        enc.encode(batch, out=out)
+        with pytest.raises(xrl.XrlError) as e:
+            enc.set_weights(w[1])
+        assert e.value.code == xrl.ERR["HIP"] and "captured" in str(e.value)
+    for _ in range(2):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, first)
+    enc.set_weights(w[1])
+    second = enc.encode(batch)
+    torch.cuda.synchronize()
+    assert not torch.equal(second, first)
+    for _ in range(2):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, second)
+    batch.free()
+    enc.close()
