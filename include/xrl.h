@@ -171,7 +171,11 @@ int32_t xrl_weight_tensor_count(const xrl_model_desc *model); /* number of tenso
 int xrl_weight_tensor(const xrl_model_desc *model, int32_t index, char *name, size_t name_cap,
                       int64_t *offset, int64_t *rows, int64_t *cols);
 
-/* ---- packing (host only; never touches the GPU) ---------------------------------------------
+/* ---- packing (host only) --------------------------------------------------------------------
+ * Needs no GPU. In a process that has a context the packed arrays lie in pinned memory from a bounded
+ * pool (allocated on the context's device; nothing is queued on a stream), else in ordinary memory. A
+ * process forked off one with a context packs, views and frees batches, its parent's included, in
+ * ordinary memory without a call to the GPU's runtime.
  * Batches current + candidate graphs into one meta-graph with its slot mask (Section 3.3.2):
  * validates, converts endpoints to global node ids, sorts edges by receiver (stable) and builds
  * the sender-side index. Errors: NULL, SHAPE, INDEX, VALUE (non-finite attribute), MASK. */

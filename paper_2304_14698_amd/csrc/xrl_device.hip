@@ -1,6 +1,9 @@
 // Device side of the library: context, weight upload, workspace, kernel sequencing.
 #include <hip/hip_runtime.h>
 
+#include <pthread.h>
+#include <sys/mman.h>
+
 #include <atomic>
 #include <cmath>
 #include <cstdlib>
@@ -281,10 +284,42 @@ struct HostPool {
   std::vector<HostBlock> idle;      // oldest first
   size_t idle_bytes = 0, pinned_bytes = 0;
   int contexts = 0;
+  int device = 0;                   // that of the last context made, where blocks are pinned
+  bool child = false;               // this process was forked off one that had a context: no HIP call from here
+  struct Live { char *p; size_t cap; void *copy; };
+  std::vector<Live> live;           // pinned blocks in the hands of batches (copy: while forking)
 };
 HostPool &host_pool() {
   static HostPool *p = new HostPool;   // (never destroyed: a batch may be freed by a static destructor)
   return *p;
+}
+// Pinned memory is not there in a forked process. It gets ordinary memory with the same contents at the same
+// addresses for the batches it inherits, and none of the pool: it packs, views and frees batches like a
+// process that never had a GPU.
+void fork_prepare() {
+  HostPool &hp = host_pool();
+  hp.mu.lock();
+  for (HostPool::Live &x : hp.live) {
+    x.copy = mmap(nullptr, x.cap, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+    if (x.copy != MAP_FAILED) memcpy(x.copy, x.p, x.cap);
+  }
+}
+void fork_parent() {
+  HostPool &hp = host_pool();
+  for (HostPool::Live &x : hp.live)
+    if (x.copy != MAP_FAILED) (void)munmap(x.copy, x.cap);
+  hp.mu.unlock();
+}
+void fork_child() {
+  HostPool &hp = host_pool();
+  for (HostPool::Live &x : hp.live)
+    if (x.copy != MAP_FAILED) (void)mremap(x.copy, x.cap, x.cap, MREMAP_MAYMOVE | MREMAP_FIXED, x.p);
+  hp.live.clear();
+  hp.idle.clear();
+  hp.idle_bytes = hp.pinned_bytes = 0;
+  hp.contexts = 0;
+  hp.child = true;
+  hp.mu.unlock();
 }
 // Blocks change hands in calls that touch no stream: they must not disturb a capture that this or another
 // thread has under way.
@@ -293,9 +328,23 @@ struct RelaxedCapture {
   RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
   ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
+// The calling thread's current device, for as long as this lives.
+struct OnDevice {
+  int before = 0;
+  bool changed = false;
+  explicit OnDevice(int device) {
+    changed = hipGetDevice(&before) == hipSuccess && before != device && hipSetDevice(device) == hipSuccess;
+  }
+  ~OnDevice() { if (changed) (void)hipSetDevice(before); }
+};
 void host_block_release(HostBlock &b) {
   if (!b.pinned) {
     free(b.p);
+    b = HostBlock();
+    return;
+  }
+  if (host_pool().child) {               // (see fork_child)
+    (void)munmap(b.p, b.cap);
     b = HostBlock();
     return;
   }
@@ -307,12 +356,16 @@ void host_block_release(HostBlock &b) {
   (void)hipHostFree(b.p);
   b = HostBlock();
 }
-void host_pool_context(int change) {
+void host_pool_context(int change, int device = 0) {
   HostPool &hp = host_pool();
+  static std::once_flag once;
+  std::call_once(once, [] { (void)pthread_atfork(fork_prepare, fork_parent, fork_child); });
   std::vector<HostBlock> drop;
   {
     std::lock_guard<std::mutex> lk(hp.mu);
+    if (hp.child) return;
     hp.contexts += change;
+    if (change > 0) hp.device = device;
     if (hp.contexts == 0) {
       drop.swap(hp.idle);
       hp.pinned_bytes -= hp.idle_bytes;
@@ -328,7 +381,9 @@ HostBlock host_block_take(size_t bytes) {
   HostBlock b;
   const size_t cap = block_capacity(bytes);
   bool pin = false;
+  int device = 0;
   std::unique_lock<std::mutex> lk(hp.mu);
+  device = hp.device;
   if (hp.contexts > 0 && cap <= kMaxPinnedBlock) {
     RelaxedCapture relaxed;
     // the oldest idle block of a fitting class whose last transfer is over; one still being read by a
@@ -346,6 +401,7 @@ HostBlock host_block_take(size_t bytes) {
       b = hp.idle[pick];
       hp.idle.erase(hp.idle.begin() + pick);
       hp.idle_bytes -= b.cap;
+      hp.live.push_back({b.p, b.cap, nullptr});
     } else if (hp.pinned_bytes + cap <= kMaxPinnedTotal) {
       pin = true;
       hp.pinned_bytes += cap;
@@ -360,15 +416,18 @@ HostBlock host_block_take(size_t bytes) {
   b.cap = cap;
   if (pin) {
     RelaxedCapture relaxed;
-    if (hipHostMalloc((void **)&b.p, cap, hipHostMallocPortable) == hipSuccess) {
+    OnDevice on(device);                 // (the packing thread may never have chosen one)
+    const hipError_t e = hipHostMalloc((void **)&b.p, cap, hipHostMallocPortable);
+    lk.lock();
+    if (e == hipSuccess) {
       b.pinned = true;
+      hp.live.push_back({b.p, cap, nullptr});
       return b;
     }
-    (void)hipGetLastError();
-    b.p = nullptr;
-    lk.lock();
     hp.pinned_bytes -= cap;
     lk.unlock();
+    (void)hipGetLastError();
+    b.p = nullptr;
   }
   b.p = (char *)aligned_alloc(4096, (cap + 4095) / 4096 * 4096);
   return b;
@@ -379,13 +438,15 @@ void host_block_give(HostBlock &b) {
   if (b.pinned) {
     HostPool &hp = host_pool();
     std::lock_guard<std::mutex> lk(hp.mu);
+    for (size_t i = 0; i < hp.live.size(); ++i)
+      if (hp.live[i].p == b.p) { hp.live.erase(hp.live.begin() + i); break; }
     if (hp.contexts > 0 && hp.idle.size() < kMaxIdleBlocks && hp.idle_bytes + b.cap <= kMaxIdlePinned) {
       hp.idle.push_back(b);
       hp.idle_bytes += b.cap;
       b = HostBlock();
       return;
     }
-    hp.pinned_bytes -= b.cap;
+    if (!hp.child) hp.pinned_bytes -= b.cap;
   }
   host_block_release(b);
 }
@@ -484,7 +545,8 @@ struct Distinct {
 extern "C" void xrl_batch_release_device(xrl_batch *b) {
   if (b && b->dev.block) {
     auto give = [&](DeviceBlock &x) {
-      if (b->pool && !b->shared) b->pool->give(x);
+      if (host_pool().child) x = DeviceBlock();        // (the device's memory is the parent's)
+      else if (b->pool && !b->shared) b->pool->give(x);
       else DevicePool::release(x);
     };
     if (b->distinct)
@@ -2303,7 +2365,8 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   c->id = next_ctx++;
   c->blocks = std::make_shared<DevicePool>();
   c->blocks->stream = (hipStream_t)hip_stream;
-  host_pool_context(1);
+  if (hipGetDevice(&c->device) != hipSuccess) (void)hipGetLastError();
+  host_pool_context(1, c->device);
   c->m = *model;
   c->L = L;
   c->single_layer = single_layer;
@@ -2340,12 +2403,9 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   if (const char *e = getenv("XRL_CLUSTER_MAX_GRAPHS")) c->cluster_max_graphs = std::min<int64_t>(atoll(e), kClusterMaxGraphs);
   if (const char *e = getenv("XRL_CLUSTER_SPIN_LIMIT")) c->cluster_spin_limit = (unsigned)std::max<long long>(0, std::min<long long>(atoll(e), kClusterSpinLimit));
   {
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) == hipSuccess) {
-      c->device = dev;
-      if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) c->n_cu = v;
-      if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > 0) c->max_lds = v;
-    }
+    int v = 0;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, c->device) == hipSuccess && v > 0) c->n_cu = v;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device) == hipSuccess && v > 0) c->max_lds = v;
   }
   // the weights, followed by 1 KB of zeros (16-byte aligned) that kernels read in place of absent rows
   const size_t w_bytes = align_up(sizeof(float) * L.total);

@@ -63,3 +63,50 @@ def test_batch_outlives_its_context_and_serves_another():
     assert torch.equal(late.cpu(), again.cpu())
     first.free()
     second.free()
+
+
+def test_forked_process_packs_views_and_frees():
+    """A worker forked off a process with a context: pinned memory and the pool are not there in it."""
+    import os
+    import signal
+    import time
+    torch, model, weights, states = _setup([(8, 40), (4, 10), (2, 3)])
+    enc = xrl.Encoder(model, weights)
+    first, second = enc.pack(states[0]), xrl.Batch(model, states[1])       # uploaded; packed only
+    want = [b.host_view() for b in (first, second)]
+    third = enc.pack(states[2])
+    want.append(third.host_view())
+    emb = enc.encode(first).cpu()
+    third.free()                                    # (its block is idle now)
+    torch.cuda.synchronize()
+
+    def same(batch, view):
+        got = batch.host_view()
+        return all(np.array_equal(got[k], view[k]) for k in view)
+
+    pid = os.fork()
+    if pid == 0:                                    # (no GPU call from here; nothing of pytest's runs either)
+        ok = 0
+        try:
+            ok += same(first, want[0]) and same(second, want[1])
+            mine = [xrl.Batch(model, s) for s in states]
+            ok += all(same(b, w) for b, w in zip(mine, want))
+            for b in mine + [first, second]:
+                b.free()
+            ok += same(xrl.Batch(model, states[2]), want[2])
+        finally:
+            os._exit(0 if ok == 3 else 1)
+    for _ in range(600):
+        done, status = os.waitpid(pid, os.WNOHANG)
+        if done:
+            break
+        time.sleep(0.05)
+    else:
+        os.kill(pid, signal.SIGKILL)
+        os.waitpid(pid, 0)
+        status = -1
+    assert status == 0
+    assert torch.equal(enc.encode(first).cpu(), emb) and same(enc.pack(states[2]), want[2])
+    first.free()
+    second.free()
+    enc.close()
