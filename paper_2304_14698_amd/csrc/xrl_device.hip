@@ -328,14 +328,20 @@ struct RelaxedCapture {
   RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
   ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
+// Whether a call made while memory changes hands went well. A failure is dealt with on the spot and must not be
+// found by the next check of a launch.
+bool went_well(hipError_t e) {
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e == hipSuccess;
+}
 // The calling thread's current device, for as long as this lives.
 struct OnDevice {
   int before = 0;
   bool changed = false;
   explicit OnDevice(int device) {
-    changed = hipGetDevice(&before) == hipSuccess && before != device && hipSetDevice(device) == hipSuccess;
+    changed = went_well(hipGetDevice(&before)) && before != device && went_well(hipSetDevice(device));
   }
-  ~OnDevice() { if (changed) (void)hipSetDevice(before); }
+  ~OnDevice() { if (changed) (void)went_well(hipSetDevice(before)); }
 };
 void host_block_release(HostBlock &b) {
   if (!b.pinned) {
@@ -350,10 +356,10 @@ void host_block_release(HostBlock &b) {
   }
   RelaxedCapture relaxed;
   if (b.copied) {
-    (void)hipEventSynchronize((hipEvent_t)b.copied);
-    (void)hipEventDestroy((hipEvent_t)b.copied);
+    (void)went_well(hipEventSynchronize((hipEvent_t)b.copied));
+    (void)went_well(hipEventDestroy((hipEvent_t)b.copied));
   }
-  (void)hipHostFree(b.p);
+  (void)went_well(hipHostFree(b.p));
   b = HostBlock();
 }
 void host_pool_context(int change, int device = 0) {
@@ -392,10 +398,9 @@ HostBlock host_block_take(size_t bytes) {
     for (size_t i = 0; i < hp.idle.size() && pick < 0; ++i) {
       const HostBlock &x = hp.idle[i];
       if (x.cap < bytes || x.cap > 2 * cap) continue;
-      if (!x.copied || hipEventQuery((hipEvent_t)x.copied) == hipSuccess) pick = (int)i;
+      if (!x.copied || went_well(hipEventQuery((hipEvent_t)x.copied))) pick = (int)i;
       else if (busy < 0) busy = (int)i;
     }
-    if (busy >= 0) (void)hipGetLastError();              // (hipErrorNotReady is no error here)
     if (pick < 0 && hp.idle.size() >= kMaxIdleBlocks) pick = busy;
     if (pick >= 0) {
       b = hp.idle[pick];
@@ -410,7 +415,7 @@ HostBlock host_block_take(size_t bytes) {
   lk.unlock();
   if (b.p) {
     RelaxedCapture relaxed;
-    if (b.copied) (void)hipEventSynchronize((hipEvent_t)b.copied);
+    if (b.copied) (void)went_well(hipEventSynchronize((hipEvent_t)b.copied));
     return b;
   }
   b.cap = cap;
@@ -463,6 +468,7 @@ struct DevicePool {
   std::vector<DeviceBlock> idle;     // oldest first
   size_t idle_bytes = 0;
   hipStream_t stream = nullptr;      // the context's
+  int device = 0;                    // the stream's
   bool closed = false;
   // on_stream: the block will be used on the context's own stream, where its last use is over by then; else
   // a block whose last use is over already is preferred, and a new one to waiting
@@ -473,10 +479,9 @@ struct DevicePool {
       int pick = -1, busy = -1;
       for (size_t i = 0; i < idle.size() && pick < 0; ++i) {
         if (idle[i].cap < bytes || idle[i].cap > 2 * cap) continue;
-        if (on_stream || hipEventQuery(idle[i].used) == hipSuccess) pick = (int)i;
+        if (on_stream || went_well(hipEventQuery(idle[i].used))) pick = (int)i;
         else if (busy < 0) busy = (int)i;
       }
-      if (busy >= 0) (void)hipGetLastError();            // (hipErrorNotReady is no error here)
       if (pick < 0 && idle.size() >= kMaxIdleBlocks) pick = busy;
       if (pick >= 0) {
         *out = idle[pick];
@@ -493,11 +498,12 @@ struct DevicePool {
     if (!b.p) return;
     {
       std::lock_guard<std::mutex> lk(mu);
+      OnDevice on(device);               // (the event and the stream have to be of one device)
       hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
       if (!closed && idle.size() < kMaxIdleBlocks && idle_bytes + b.cap <= kMaxIdleDevice &&
-          hipStreamIsCapturing(stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone &&
-          (b.used || hipEventCreateWithFlags(&b.used, hipEventDisableTiming) == hipSuccess) &&
-          hipEventRecord(b.used, stream) == hipSuccess) {
+          went_well(hipStreamIsCapturing(stream, &cs)) && cs == hipStreamCaptureStatusNone &&
+          (b.used || went_well(hipEventCreateWithFlags(&b.used, hipEventDisableTiming))) &&
+          went_well(hipEventRecord(b.used, stream))) {
         idle.push_back(b);
         idle_bytes += b.cap;
         b = DeviceBlock();
@@ -508,8 +514,8 @@ struct DevicePool {
   }
   static void release(DeviceBlock &b) {
     RelaxedCapture relaxed;
-    if (b.p) (void)hipFree(b.p);     // (waits for the device)
-    if (b.used) (void)hipEventDestroy(b.used);
+    if (b.p) (void)went_well(hipFree(b.p));     // (waits for the device)
+    if (b.used) (void)went_well(hipEventDestroy(b.used));
     b = DeviceBlock();
   }
   void close() {
@@ -2366,6 +2372,7 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   c->blocks = std::make_shared<DevicePool>();
   c->blocks->stream = (hipStream_t)hip_stream;
   if (hipGetDevice(&c->device) != hipSuccess) (void)hipGetLastError();
+  c->blocks->device = c->device;
   host_pool_context(1, c->device);
   c->m = *model;
   c->L = L;

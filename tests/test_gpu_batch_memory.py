@@ -110,3 +110,32 @@ def test_forked_process_packs_views_and_frees():
     first.free()
     second.free()
     enc.close()
+
+
+def test_free_during_another_capture_leaves_no_error():
+    """Freeing a batch whose context is on the default stream while a blocking stream is captured: asking for the
+    default stream's state fails then, which is no error of the next call."""
+    import ctypes as C
+    torch, model, weights, states = _setup([(2, 3), (2, 4)])
+    hip = xrl.load_library()                        # (its dependencies are looked up with it)
+    stream, graph = C.c_void_p(), C.c_void_p()
+    assert hip.hipStreamCreate(C.byref(stream)) == 0
+    a, b = xrl.Encoder(model, weights), xrl.Encoder(model, weights, stream=torch.cuda.ExternalStream(stream.value))
+    mine, other = a.pack(states[0]), b.pack(states[1])
+    a.encode(mine)
+    want = b.encode(other)
+    out = torch.zeros_like(want)
+    torch.cuda.synchronize()
+    relaxed = 2
+    assert hip.hipStreamBeginCapture(stream, relaxed) == 0
+    try:
+        mine.free()
+        b.encode(other, out=out)
+    finally:
+        assert hip.hipStreamEndCapture(stream, C.byref(graph)) == 0
+        assert hip.hipGraphDestroy(graph) == 0
+    assert torch.equal(b.encode(other), want)
+    other.free()
+    a.close()
+    b.close()
+    assert hip.hipStreamDestroy(stream) == 0
