@@ -240,7 +240,9 @@ int xrl_batch_upload(xrl_ctx *ctx, xrl_batch *b);
  * rewrites of a few graphs (message-passing rounds of the MLP kind, at most 15; no receiver of more
  * than 32 in-edges) is reduced to its distinct nodes by the context that uploaded it when it is
  * first saved for the backward pass, or encoded a second time: that one call waits for the stream
- * twice, later calls compute every round once per distinct node. States and embeddings are
+ * twice, later calls compute every round once per distinct node. (A context on which calls have been
+ * captured reduces no further batches: a graph keeps the addresses of the context's buffers, which
+ * grow with the batches it is given, and only then.) States and embeddings are
  * the same bits; gradients are summed in another, equally fixed order.
  * Errors: NULL, SHAPE, OOM, HIP (also: an earlier one-launch encode on this context did not
  * complete, see XRL_CLUSTER_SPIN_LIMIT). */

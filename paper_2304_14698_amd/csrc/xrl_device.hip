@@ -202,6 +202,7 @@ struct xrl_ctx {
   std::vector<void *> hx;       // last encode of a reduced batch: h of the level below, per class
   std::shared_ptr<DevicePool> blocks;
   hipStream_t copy_stream = nullptr;   // uploads of kCopyStreamBytes and more
+  bool captured = false;        // calls on it have been captured: graphs hold addresses in the workspaces
   uint64_t enc_batch = 0;
   bool enc_saved = false;
   float *pool = nullptr, *carry = nullptr, *ro_act[2] = {nullptr, nullptr};
@@ -815,7 +816,12 @@ struct Bump {
   }
 };
 
-int check_batch(const xrl_ctx *c, const xrl_batch *b, const char *who) {
+bool is_capturing(const xrl_ctx *c) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  return went_well(hipStreamIsCapturing(c->stream, &cap)) && cap != hipStreamCaptureStatusNone;
+}
+
+int check_batch(xrl_ctx *c, const xrl_batch *b, const char *who) {
   if (!c || !b) return fail(XRL_ERR_NULL, "%s: ctx or batch is NULL", who);
   if (!b->uploaded) return fail(XRL_ERR_STATE, "%s: batch was not uploaded (xrl_batch_upload)", who);
   const xrl_model_desc &x = c->m, &y = b->model;
@@ -826,9 +832,10 @@ int check_batch(const xrl_ctx *c, const xrl_batch *b, const char *who) {
     const_cast<xrl_batch *>(b)->shared = true;
     if (b->mem.copied) HIP_TRY(hipEventSynchronize((hipEvent_t)b->mem.copied));
   }
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (!b->shared && hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
+  if (!(c->captured && b->shared) && is_capturing(c)) {
+    c->captured = true;
     const_cast<xrl_batch *>(b)->shared = true;   // (replays may run on any stream)
+  }
   return XRL_OK;
 }
 
@@ -1589,9 +1596,8 @@ int make_groupings(xrl_ctx *c, const xrl_batch *b, Distinct *q, bool fold) {
   group_write_kernel<<<per_item, dim3(256), 0, c->stream>>>(a, x);
   HIP_TRY(hipGetLastError());
   // (while a stream is being captured nothing runs: eager calls make them for themselves)
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   q->grouped_fold = fold;
-  q->grouped = hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+  q->grouped = !is_capturing(c);
   return XRL_OK;
 }
 
@@ -2635,11 +2641,11 @@ int xrl_encode(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save_for_backwa
   }
   if (b->owner == c->id && b->encodes >= 0) {
     // Reduced to its distinct nodes when it is first saved for a backward pass, or encoded again: a batch
-    // encoded once and forward only would not earn back what finding them takes.
+    // encoded once and forward only would not earn back what finding them takes. Not in a capture, nor
+    // once the context has been through one: a reduced batch's buffers may be larger than those it was
+    // encoded whole in, and to grow them would free what the graphs write to.
     xrl_batch *mb = const_cast<xrl_batch *>(b);
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if ((save_for_backward || ++mb->encodes > 1) && distinct_pays(c, b) &&
-        hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) {
+    if ((save_for_backward || ++mb->encodes > 1) && !c->captured && distinct_pays(c, b)) {
       mb->encodes = -1;
       if ((rc = find_distinct(c, mb))) return rc;
     }

@@ -109,3 +109,45 @@ def test_reduced_batch_against_the_oracle(monkeypatch):
     state = synth.concat_states([synth.make_state(rng, synth.resnet_dag(rng, 2), n, by_block=True) for n in (12, 3)])
     w = synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1)
     run_backward_case(xrl, model, state, w, seed=4)
+
+
+def test_a_captured_context_keeps_its_buffers(monkeypatch):
+    """A graph of a batch encoded whole holds addresses in the context's buffers: neither that batch nor a later one is
+    reduced after the capture, as its buffers might have to grow, and replays among eager calls stay right."""
+    import torch
+    monkeypatch.setenv("XRL_DISTINCT_MIN_US", "0")
+    monkeypatch.setenv("XRL_RESIDENT_MAX_GRAPHS", "0")
+    rng = np.random.Generator(np.random.PCG64(6))
+    model, _ = synth.make_config(1)
+    model.update(hidden=128, precision="bf16", rounds=3)
+    states = [synth.concat_states([synth.make_state(rng, synth.resnet_dag(rng, 3), n, by_block=True)]) for n in (20, 5)]
+    w = [synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1) for _ in range(2)]
+    side = torch.cuda.Stream()
+    enc = xrl.Encoder(model, w[0], stream=side)
+    batch, other = (enc.pack(s) for s in states)
+    first = enc.encode(batch)
+    out = torch.empty_like(first)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side, capture_error_mode="relaxed"):
+        enc.encode(batch, out=out)
+    for weights in (w[0], w[1]):
+        enc.set_weights(weights)
+        for _ in range(3):
+            eager = enc.encode(batch)
+            enc.encode(other)
+            torch.cuda.synchronize()
+            out.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, eager)
+    assert enc.batch_level(batch, 0)[0] == batch.N and enc.batch_level(other, 0)[0] == other.N
+    fresh = xrl.Encoder(model, w[1])                # (the same batch is reduced where nothing was captured)
+    again = fresh.pack(states[0])
+    fresh.encode(again)
+    assert torch.equal(fresh.encode(again), eager) and fresh.batch_level(again, 0)[0] < again.N
+    for x in (batch, other, again):
+        x.free()
+    fresh.close()
+    enc.close()
