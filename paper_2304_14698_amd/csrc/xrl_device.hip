@@ -493,7 +493,23 @@ struct DevicePool {
     }
     *out = DeviceBlock();
     out->cap = cap;
-    return hipMalloc(&out->p, cap);
+    return allocate(&out->p, cap);
+  }
+  // hipMalloc; where the device has no room, once more without the idle blocks
+  hipError_t allocate(void **p, size_t bytes) {
+    const hipError_t e = hipMalloc(p, bytes);
+    if (went_well(e)) return e;
+    std::vector<DeviceBlock> drop;
+    {
+      std::lock_guard<std::mutex> lk(mu);
+      drop.swap(idle);
+      idle_bytes = 0;
+    }
+    if (drop.empty()) return e;
+    for (DeviceBlock &x : drop) release(x);
+    const hipError_t again = hipMalloc(p, bytes);
+    (void)went_well(again);
+    return again;
   }
   void give(DeviceBlock &b) {
     if (!b.p) return;
@@ -775,9 +791,9 @@ int ensure_ws(xrl_ctx *c, size_t bytes) {
   c->ws_bytes = 0;
   c->enc_batch = 0;
   c->enc_saved = false;
-  hipError_t e = hipMalloc((void **)&c->ws, bytes);
+  hipError_t e = c->blocks->allocate((void **)&c->ws, bytes);
   if (e != hipSuccess) {
-    (void)hipGetLastError();
+    c->ws = nullptr;
     return fail(XRL_ERR_OOM, "workspace of %zu bytes: %s", bytes, hipGetErrorString(e));
   }
   c->ws_bytes = bytes;
@@ -790,9 +806,9 @@ int ensure_buf(xrl_ctx *c, char **buf, size_t *have, size_t bytes, const char *w
   if (*buf) HIP_TRY(hipFree(*buf));
   *buf = nullptr;
   *have = 0;
-  hipError_t e = hipMalloc((void **)buf, bytes);
+  hipError_t e = c->blocks->allocate((void **)buf, bytes);
   if (e != hipSuccess) {
-    (void)hipGetLastError();
+    *buf = nullptr;
     return fail(XRL_ERR_OOM, "%s of %zu bytes: %s", what, bytes, hipGetErrorString(e));
   }
   *have = bytes;
@@ -1644,7 +1660,6 @@ int find_distinct(xrl_ctx *c, xrl_batch *b) {
   q->levels = L;
   auto take = [&](int i, size_t bytes) -> char * {
     if (c->blocks->take(bytes, true, &q->block[i]) == hipSuccess) return (char *)q->block[i].p;
-    (void)hipGetLastError();
     q->block[i] = DeviceBlock();
     return nullptr;
   };
@@ -2548,10 +2563,7 @@ int xrl_batch_upload(xrl_ctx *c, xrl_batch *b) {
   }
   DeviceBlock got;
   hipError_t e = c->blocks->take(off, up == c->stream, &got);
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(XRL_ERR_OOM, "device copy of the batch (%zu bytes): %s", off, hipGetErrorString(e));
-  }
+  if (e != hipSuccess) return fail(XRL_ERR_OOM, "device copy of the batch (%zu bytes): %s", off, hipGetErrorString(e));
   blk = (char *)got.p;
   d.block = blk;
   d.bytes = got.cap;

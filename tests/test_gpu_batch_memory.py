@@ -139,3 +139,58 @@ def test_free_during_another_capture_leaves_no_error():
     a.close()
     b.close()
     assert hip.hipStreamDestroy(stream) == 0
+
+
+@pytest.mark.parametrize("what", ["upload", "workspace"])
+def test_idle_blocks_make_room(what):
+    """With the device nearly full, memory that the pool keeps idle is given back before a call is refused."""
+    import ctypes as C
+    torch, _, _, _ = _setup([])
+    model, _ = synth.make_config(1)
+    model.update(hidden=256, precision="fp32", rounds=4, n_node_dense=900, n_op_types=32)
+    rng = np.random.Generator(np.random.PCG64(2))
+    weights = synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1)
+
+    def state(n):                                   # n graphs of one node, 3.6 KB each
+        return dict(n_states=1, state_graph_ptr=np.array([0, n], np.int32), graph_node_ptr=np.arange(n + 1, dtype=np.int32),
+                    graph_edge_ptr=np.zeros(n + 1, np.int32), node_op=(np.arange(n) % 32).astype(np.int32),
+                    node_dense=np.full((n, 900), 0.25, np.float32), edge_src=np.zeros(0, np.int32), edge_dst=np.zeros(0, np.int32),
+                    edge_feat=np.zeros((0, model["d_edge"]), np.float32), graph_global=np.zeros((n, 1), np.float32),
+                    slot_mask=np.ones(n, np.uint8))
+    small, n, n_big = state(1000), 66000, 160000    # device blocks of 256 and 640 MiB; workspace of 0.9 GB
+    hip = xrl.load_library()
+    hip.hipMalloc.argtypes = [C.POINTER(C.c_void_p), C.c_size_t]
+    enc = xrl.Encoder(model, weights)
+    first = enc.pack(small)
+    want = enc.encode(first, save_for_backward=True).cpu()
+    emb = torch.empty((n, 256), device="cuda")
+    idle = [enc.pack(state(n)) for _ in range(3)]
+    if what == "workspace":
+        first = enc.pack(state(n))
+    for b in idle:
+        b.free()
+    torch.cuda.synchronize()
+    filler = []
+    try:
+        for _ in range(40):                         # (the free memory reported first is too little)
+            left = torch.cuda.mem_get_info()[0] - (512 << 20)
+            if left < 16 << 20:
+                break
+            p = C.c_void_p()
+            assert hip.hipMalloc(C.byref(p), min(left, 16 << 30)) == 0
+            filler.append(p)
+        assert torch.cuda.mem_get_info()[0] < 530 << 20
+        if what == "upload":
+            big = enc.pack(state(n_big))
+            big.free()
+            assert torch.equal(enc.encode(first, save_for_backward=True).cpu(), want)
+        else:
+            enc.encode(first, save_for_backward=True, out=emb)
+            torch.cuda.synchronize()
+    finally:
+        for p in filler:
+            hip.hipFree(p)
+    if what == "workspace":
+        assert torch.equal(emb[:1000].cpu(), want)
+    first.free()
+    enc.close()
