@@ -6,10 +6,13 @@
 // is computed once per class, on the graph of one representative per class (its smallest node) and
 // the representatives' in-edges.
 //
-// Classes are found by hashing a node's key into an open-addressing table (32-bit tag, smallest node
+// Classes are found by hashing a node's key into an open-addressing table (36-bit tag, smallest node
 // that has it) and then comparing the key itself with that node's, word by word: a node whose tag
 // is another key's too becomes a class of its own, so equality never rests on the hash.
-// Class numbers ascend with their representatives, whatever order the hardware ran in.
+// The search for a tag begins at a slot that the tag alone decides, so nodes of one tag share one slot
+// whatever order the hardware ran in, and with it the classes. (A slot chosen by other bits of the hash
+// would let two keys of one tag meet or miss each other by the order of insertion.) Class numbers
+// ascend with their representatives.
 //
 // What it saves, a kept minibatch's update step: 4.3 M nodes, H = 256: 88.0 -> 14.4 ms (20 % of the edges are
 // left over five rounds); 354 k nodes, H = 128: 4.3 -> 1.85 ms (40 %); 73 k nodes re-evaluated in fp32:
@@ -25,6 +28,7 @@
 
 constexpr int kMaxLevels = 16;            // levels 0 .. rounds
 constexpr unsigned long long kEmptySlot = ~0ull;
+constexpr int kNodeBits = 28;             // of a table slot; the others are the tag (a batch has fewer than 2^28 - 1 nodes)
 constexpr int kScanItems = 1024;          // nodes per block of the class kernels (four per thread)
 
 struct ClassArgs {
@@ -33,7 +37,7 @@ struct ClassArgs {
   const uint32_t *edge_feat, *node_dense;  // bit patterns
   int De, Dd;
   const int32_t *prev;                     // class of each node one level below; nullptr: level 0
-  unsigned long long *table;               // [mask + 1] tag << 32 | smallest node, kEmptySlot
+  unsigned long long *table;               // [mask + 1] tag << kNodeBits | smallest node, kEmptySlot
   uint32_t mask;
   const int32_t *state_graph_ptr, *graph_node_ptr;
   int32_t *slot;                           // [N] table slot, then (representatives) the class number
@@ -68,9 +72,8 @@ __device__ __forceinline__ void class_insert(const ClassArgs &a, int64_t n) {
     for (size_t w = (size_t)e0 * a.De; w < (size_t)e1 * a.De; ++w) h = mix64(h, a.edge_feat[w]);
   }
   h = mix64(h, h >> 32);
-  const unsigned long long tag = (h >> 32) % 0xffffffffull;           // (not that of an empty slot)
-  const unsigned long long mine = tag << 32 | (uint32_t)n;
-  uint32_t s = (uint32_t)h & a.mask;
+  const unsigned long long tag = h >> kNodeBits, mine = tag << kNodeBits | (uint32_t)n;
+  uint32_t s = (uint32_t)tag & a.mask;
   for (uint32_t i = 0; i <= a.mask; ++i, s = (s + 1) & a.mask) {      // (the table has more slots than there are nodes)
     // (a slot's tag is written once and its node only falls: most nodes find themselves above it)
     unsigned long long w = __hip_atomic_load(a.table + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -78,7 +81,7 @@ __device__ __forceinline__ void class_insert(const ClassArgs &a, int64_t n) {
       w = atomicCAS(a.table + s, kEmptySlot, mine);
       if (w == kEmptySlot) w = mine;
     }
-    if (w >> 32 != tag) continue;
+    if (w >> kNodeBits != tag) continue;
     if (w > mine) atomicMin(a.table + s, mine);
     a.slot[n] = (int32_t)s;
     break;
@@ -136,7 +139,7 @@ __global__ __launch_bounds__(256) void class_verify_kernel(const ClassArgs a) {
   for (int i = 0; i < kScanItems / 256; ++i) {
     const int64_t n = (int64_t)blockIdx.x * kScanItems + i * 256 + threadIdx.x;
     if (n >= a.N) break;
-    int32_t r = (int32_t)(uint32_t)a.table[a.slot[n]];
+    int32_t r = (int32_t)(a.table[a.slot[n]] & ((1u << kNodeBits) - 1));
     if (r != (int32_t)n && !same_key(a, n, r)) r = (int32_t)n;
     a.rep[n] = r;
     if (r == (int32_t)n) { ++v.x; v.y += a.in_ptr[n + 1] - a.in_ptr[n]; }

@@ -1627,7 +1627,7 @@ int make_groupings(xrl_ctx *c, const xrl_batch *b, Distinct *q, bool fold) {
 bool distinct_pays(const xrl_ctx *c, const xrl_batch *b) {
   const int H = c->m.hidden, R = c->m.rounds, De = c->m.d_edge;
   if (c->distinct_min_us < 0 || c->m.round_kind != XRL_ROUND_MLP || R < 1 || R + 1 > kMaxLevels || b->G <= b->S || b->N < 1 || b->E < 1 || b->n_split_tiles > 0 ||
-      b->N + b->E > (int64_t)1 << 28)                       // (table slots and sort keys are 32-bit)
+      b->N + b->E > (int64_t)1 << kNodeBits)                // (table slots hold node numbers of so many bits)
     return false;
   const double flops = 2.0 * R * H * ((double)b->N * 3 * H + (double)b->E * (3 * H + De));
   const double us = flops / (c->elem == 2 ? 7e8 : 7e7);                                 // (flops per us measured)

@@ -151,3 +151,53 @@ def test_a_captured_context_keeps_its_buffers(monkeypatch):
         x.free()
     fresh.close()
     enc.close()
+
+
+def _tags(dense):
+    """Tags of level-0 keys of nodes without in-edges, operator 0, one attribute: the hash of the class table restated."""
+    def mix(h, v):
+        h = (h ^ v) * np.uint64(0x9E3779B97F4A7C15)
+        return h ^ (h >> np.uint64(29))
+    h = mix(np.zeros(len(dense), np.uint64), np.uint64(0))
+    h = mix(h, dense.view(np.uint32).astype(np.uint64))
+    return mix(h, h >> np.uint64(32)) >> np.uint64(28)
+
+
+def test_keys_of_one_tag(monkeypatch):
+    """Two keys of one tag share a table slot: the one of the smallest node is a class, every node of the other a class of
+    its own, in every run; values are those of the whole batch."""
+    import torch
+    dense = np.arange(1 << 21, dtype=np.float32)
+    tags = _tags(dense)
+    order = np.argsort(tags, kind="stable")
+    twins = np.flatnonzero(tags[order][1:] == tags[order][:-1])
+    assert len(twins) > 0
+    a, b = dense[order[twins[0]]], dense[order[twins[0] + 1]]
+    model, _ = synth.make_config(1)
+    model.update(hidden=64, precision="fp32", rounds=1, n_node_dense=1)
+    rng = np.random.Generator(np.random.PCG64(5))
+    w = synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1)
+    G = 700                                         # graphs p -> q, p of the first key and of the second by turns
+    value = np.where(np.arange(G) % 2 == 0, a, b)
+    state = dict(n_states=1, state_graph_ptr=np.array([0, G], np.int32), graph_node_ptr=np.arange(0, 2 * G + 1, 2, dtype=np.int32),
+                 graph_edge_ptr=np.arange(G + 1, dtype=np.int32), node_op=np.zeros(2 * G, np.int32),
+                 node_dense=np.stack([value, np.zeros(G)], 1).astype(np.float32).reshape(-1, 1), edge_src=np.zeros(G, np.int32),
+                 edge_dst=np.ones(G, np.int32), edge_feat=np.zeros((G, model["d_edge"]), np.float32),
+                 graph_global=np.zeros((G, model["d_global"]), np.float32), slot_mask=np.ones(G, np.uint8))
+    got = []
+    for min_us in ("-1", "0", "0", "0"):
+        monkeypatch.setenv("XRL_DISTINCT_MIN_US", min_us)
+        monkeypatch.setenv("XRL_RESIDENT_MAX_GRAPHS", "0")
+        enc = xrl.Encoder(model, w)
+        batch = enc.pack(state)
+        emb = enc.encode(batch, save_for_backward=True).cpu()
+        dw = torch.zeros(enc.n_weights, device="cuda")
+        enc.encode_backward(batch, torch.ones(G, 64, device="cuda"), dw)
+        got.append((emb, dw.cpu(), [enc.batch_level(batch, r)[0] for r in (0, 1)]))
+        batch.free()
+        enc.close()
+    assert got[0][2] == [2 * G, 2 * G]
+    assert float((got[1][1] - got[0][1]).norm() / got[0][1].norm()) < 1e-5
+    for emb, dw, nodes in got[1:]:
+        assert nodes == [2 + G // 2, 2 + 2 * (G // 2)]      # first key, q, every node of the second key; and its q
+        assert torch.equal(emb, got[0][0]) and torch.equal(dw, got[1][1])
