@@ -1705,12 +1705,17 @@ int find_distinct(xrl_ctx *c, xrl_batch *b) {
     return XRL_OK;
   };
   if ((rc = read_counts(2 * L))) { drop(); return rc; }
-  int64_t sumE = 0, sumN = 0;
+  int64_t sumE = 0, sumN = 0, items = N;
   for (int l = 0; l < L; ++l) {
     q->lv[l].N = c->h_counts[2 * l];
     q->lv[l].E = c->h_counts[2 * l + 1];
-    if (l > 0) { sumE += q->lv[l].E; sumN += q->lv[l].N; }
+    if (l > 0) {
+      sumE += q->lv[l].E; sumN += q->lv[l].N;
+      items += std::max(level_rows(q->lv[l], false), level_rows(q->lv[l], true));
+    }
   }
+  // (the sort that makes the groupings counts the items of all levels in 32 bits)
+  if (items > INT32_MAX - kSortItems) { drop(); return XRL_OK; }
   // (a level costs a copy of its states more, so a quarter of the edges has to go)
   if (4 * (sumE + sumN) > 3 * R * (E + N) && c->distinct_min_us != 0) { drop(); return XRL_OK; }
   // ---- the levels' graphs
@@ -1738,7 +1743,7 @@ int find_distinct(xrl_ctx *c, xrl_batch *b) {
     tl.chunk0[l] = chunks;
     o[l].src = plan(e * 4); o[l].dst = plan(e * 4); o[l].self = plan(n * 4);
     o[l].tile = plan((e / 16 + 2 * nc + 4) * 4);
-    o[l].dptr = plan((q->lv[l - 1].N + 1) * 4); o[l].down = plan((e + n + std::max(e, n)) * 4); o[l].dseg = plan((e + n + std::max(e, n)) * 4);
+    o[l].dptr = plan((q->lv[l - 1].N + 1) * 4); o[l].down = plan((e + n + std::max(e, n)) * 4); o[l].dseg = plan((e + n + std::max(e, n)) * 4);   // (level_rows)
   }
   const size_t o_mptr = plan((q->lv[R].N + 1) * 4), o_mgraph = plan(N * 4), o_mseg = plan(N * 4);
   const size_t o_cuts = plan((size_t)chunks * kTileChunkMax * 4), o_count = plan((size_t)(chunks + 1) * 4);
