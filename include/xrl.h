@@ -204,17 +204,20 @@ int xrl_batch_free(xrl_batch *b);   /* frees host and device copies; NULL is acc
  * with an identity second layer, which changes no result; weights and gradients keep the one-layer
  * layout of xrl_weight_tensor.
  * Environment, read here: XRL_PERSISTENT_MIN_ROWS = row count from which the persistent MLP
- * kernels replace the others (default 8192 when saving for the backward pass and at hidden = 256, else 32768; 0 = always; results agree within rounding);
+ * kernels replace the others (default 8192 when saving for the backward pass and at hidden = 256, else
+ * 32768; 0 = always; results agree within rounding). Up to
+ * 8192 it does not apply to a batch reduced to its distinct nodes (see xrl_encode) that is saved for the
+ * backward pass: its rounds of any size run on them;
  * XRL_WGRAD_WIDE_MIN_ROWS = row count from which the weight-gradient kernel uses 256-column
  * tiles (default 2^18 at hidden = 256, else 2^20; same sums in a different, equally fixed order);
  * XRL_RESIDENT_MAX_GRAPHS (default 256; 0 = never) and XRL_RESIDENT_MAX_TILES (default 4) =
  * largest batch, in graphs and in 32-row tiles of nodes or edges per graph, that xrl_encode runs
  * as one launch with a block per graph (message-passing rounds of the MLP kind, rows of at most
  * 256 bytes, no receiver of more than 32 in-edges; results identical to the other path's) when it
- * saves for the backward pass -- and otherwise too if one of these four variables is set: forward
+ * saves for the backward pass -- and otherwise too if XRL_RESIDENT_MAX_GRAPHS is set: forward
  * only, a launch per layer is the faster way;
- * XRL_CLUSTER_MAX_GRAPHS (default 48; 0 = never) = largest batch of graphs of more tiles than
- * that which xrl_encode runs as one launch with several blocks per graph, used when a block per
+ * XRL_CLUSTER_MAX_GRAPHS (default 48; 0 = never; forward only: if set) = largest batch of graphs of more
+ * tiles than that which xrl_encode runs as one launch with several blocks per graph, used when a block per
  * four tiles of the largest graph fits the GPU at once (the few dozen candidates of one rewriting
  * step, Section 4.2; same results). Its blocks wait for each other; XRL_CLUSTER_SPIN_LIMIT =
  * polls after which such a wait gives up (default 2^21, about two seconds): the launch then

@@ -164,8 +164,8 @@ struct xrl_ctx {
   Layout Lu;                      // the caller's layout (single_layer)
   float *d_dw_int = nullptr;      // [L.total] internal gradient vector (single_layer)
   int32_t *d_wmap = nullptr;      // [Lu.total] index in the internal vector of each of the caller's weights
-  bool one_launch_forward = false; // forward-only encodes of small batches take the one-launch forms too
   int64_t cluster_max_graphs = 0; // largest batch (graphs) for the one-launch encoder with several blocks per graph
+  int64_t resident_max_forward = 0, cluster_max_forward = 0;   // the same two limits of encodes that do not save
   unsigned cluster_spin_limit = kClusterSpinLimit;   // polls after which one of its waits gives up (XRL_CLUSTER_SPIN_LIMIT)
   int device = 0;               // the device that was current at xrl_create
   char *static_ws = nullptr;    // this device's copy of `scratch` (its device address)
@@ -2082,19 +2082,21 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   for (int i = 0; i < nagg; ++i) acc(a_rows(i) * H * sizeof(T));        // (GAT: the agg slot holds z)
   for (int i = 0; q && i < nagg; ++i) acc(a_rows(i) * H * sizeof(T));
   const xrl_batch_device &d = b->dev;
-  const bool resident_ok = !gat && !q && (save || c->one_launch_forward) && H * sizeof(T) <= 256 && d.graph_tile_ptr && R <= kResidentMaxRounds;
+  const bool resident_ok = !gat && !q && H * sizeof(T) <= 256 && d.graph_tile_ptr && R <= kResidentMaxRounds;
+  const int64_t resident_max = save ? c->resident_max_graphs : c->resident_max_forward;
+  const int64_t cluster_max = save ? c->cluster_max_graphs : c->cluster_max_forward;
   const int64_t graph_tiles = std::max<int64_t>((b->max_graph_nodes + 31) / 32, b->max_graph_tiles);
   // blocks per graph of the one-launch encoder: one while a graph's phase is a single pass of a
   // block's four waves; otherwise as many as give every tile of a phase a wave of its own, if
   // that many are resident at once (at most one block per CU; graphs padded to a multiple of 8)
   int cluster_k = 0;
-  if (resident_ok && c->resident_max_graphs > 0 && G <= c->cluster_max_graphs && G > 0 &&
+  if (resident_ok && c->resident_max_graphs > 0 && G <= cluster_max && G > 0 &&
       graph_tiles > c->resident_max_tiles) {
     const int64_t slots = c->n_cu / (8 * ((G + 7) / 8));
     cluster_k = (int)((graph_tiles + 3) / 4);
     if (cluster_k > slots) cluster_k = 0;   // a phase would take a second pass: the launch-per-phase path is as fast
   }
-  const bool resident_batch = resident_ok && ((G <= c->resident_max_graphs && graph_tiles <= c->resident_max_tiles) ||
+  const bool resident_batch = resident_ok && ((G <= resident_max && graph_tiles <= c->resident_max_tiles) ||
                                               cluster_k > 0);
   // Large bf16 batches run on kernels that can keep z1 and the ReLU masks of every fused MLP for
   // the backward pass (a row of H elements and 2 H / 32 words per node or edge and MLP): kept when
@@ -2418,22 +2420,24 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   // (measured: at H = 256 the 256-column tiles win from about 300 k rows on, at H = 128 from 1 M)
   c->wide_min_rows = model->hidden >= 256 ? (1 << 18) : (1 << 20);
   if (const char *e = getenv("XRL_WGRAD_WIDE_MIN_ROWS")) c->wide_min_rows = atoll(e);
-  // Batches the one-launch encoders take when saving for the backward pass (0 graphs = never). A forward-only
-  // encode takes them only in a context made with one of the variables below: since a tile of the
+  // Largest batches of the one-launch encoders (0 graphs = never). A forward-only encode takes them up to a
+  // limit that the variable of that form states, and by default never: since a tile of the
   // launch-per-layer path is split over H / 32 waves that path is the faster one at every size they
   // cover (us per encode, one launch / a launch per layer: nine 50-node graphs, fp32, H = 64, two
   // rounds 50 / 38; bf16, H = 128, five rounds: the same graphs 79 / 57, 200 of them 81 / 76, 15 graphs of 338
-  // nodes 97 / 61, of 565 nodes 106 / 76).
-  for (const char *name : {"XRL_RESIDENT_MAX_GRAPHS", "XRL_RESIDENT_MAX_TILES", "XRL_CLUSTER_MAX_GRAPHS", "XRL_CLUSTER_SPIN_LIMIT"})
-    c->one_launch_forward |= getenv(name) != nullptr;
+  // nodes 97 / 61, of 565 nodes 106 / 76). Saving for the backward pass, where from 8192 rows on the other path
+  // is the persistent kernels': the nine graphs 51 / 39, 79 / 63, the 200 (10 k nodes) 88 / 167, 338 nodes 101 / 68,
+  // 565 nodes (8.5 k) 117 / 160; with the backward pass, which starts from more there, 295 / 284, 488 / 466,
+  // 659 / 669, 619 / 576, 657 / 630.
   // (one block of four waves per graph while every phase of a graph is a single pass of its waves)
   c->resident_max_graphs = 256;
   c->resident_max_tiles = 4;
-  if (const char *e = getenv("XRL_RESIDENT_MAX_GRAPHS")) c->resident_max_graphs = atoll(e);
+  if (const char *e = getenv("XRL_RESIDENT_MAX_GRAPHS")) c->resident_max_graphs = c->resident_max_forward = atoll(e);
   if (const char *e = getenv("XRL_RESIDENT_MAX_TILES")) c->resident_max_tiles = atoll(e);
   // ... and with several blocks per graph, for the few dozen larger graphs of one rewriting step
   c->cluster_max_graphs = 48;
-  if (const char *e = getenv("XRL_CLUSTER_MAX_GRAPHS")) c->cluster_max_graphs = std::min<int64_t>(atoll(e), kClusterMaxGraphs);
+  if (const char *e = getenv("XRL_CLUSTER_MAX_GRAPHS"))
+    c->cluster_max_graphs = c->cluster_max_forward = std::min<int64_t>(atoll(e), kClusterMaxGraphs);
   if (const char *e = getenv("XRL_CLUSTER_SPIN_LIMIT")) c->cluster_spin_limit = (unsigned)std::max<long long>(0, std::min<long long>(atoll(e), kClusterSpinLimit));
   {
     int v = 0;

@@ -765,27 +765,38 @@ def test_one_launch_encoder_wait_that_gives_up(xrl, monkeypatch):
     """The waits between the blocks of a graph are bounded. With the bound forced to zero polls
     from the host, a block whose partners have not arrived yet goes on at once: the launch still
     finishes (every access stays inside the batch's arrays), the next xrl_encode reports the
-    invalid result once, and the context then works again."""
+    invalid result once, and the context then works again (shown on the launch-per-layer form: the
+    limit of this context lets none of the other form's waits succeed)."""
     import torch
     model, state = synth.make_config(3, n_states=1, n_cand=13)
     w = weights_for(model)
+
+    def launches(enc):
+        torch.cuda.synchronize()
+        return enc.read_timing("resident")[1]
     enc = xrl.Encoder(model, w)
+    enc.set_timing(True)
     batch = enc.pack(state)
-    good = enc.encode(batch).clone()
-    torch.cuda.synchronize()
+    good = enc.encode(batch, save_for_backward=True).clone()
+    assert launches(enc) == 1
+    assert torch.equal(enc.encode(batch), good) and launches(enc) == 0      # (forward only: a launch per layer)
     enc.close()
     monkeypatch.setenv("XRL_CLUSTER_SPIN_LIMIT", "0")
     enc = xrl.Encoder(model, w)
+    enc.set_timing(True)
     batch = enc.pack(state)
-    enc.encode(batch)
-    torch.cuda.synchronize()
+    assert torch.equal(enc.encode(batch), good) and launches(enc) == 0      # (the limit alone selects no kernel)
+    enc.encode(batch, save_for_backward=True)
+    assert launches(enc) == 1
     with pytest.raises(xrl.XrlError, match="did not complete"):
-        enc.encode(batch)
+        enc.encode(batch, save_for_backward=True)
+    assert torch.equal(enc.encode(batch), good) and launches(enc) == 0
     monkeypatch.delenv("XRL_CLUSTER_SPIN_LIMIT")
     enc2 = xrl.Encoder(model, w)            # (the limit is read when a context is made)
+    enc2.set_timing(True)
     batch2 = enc2.pack(state)
-    again = enc2.encode(batch2)
-    torch.cuda.synchronize()
+    again = enc2.encode(batch2, save_for_backward=True)
+    assert launches(enc2) == 1
     assert torch.equal(again, good)
     batch.free(); batch2.free()
     enc.close(); enc2.close()
