@@ -205,7 +205,7 @@ int xrl_batch_free(xrl_batch *b);   /* frees host and device copies; NULL is acc
  * layout of xrl_weight_tensor.
  * Environment, read here: XRL_PERSISTENT_MIN_ROWS = row count from which the persistent MLP
  * kernels replace the others (default 8192 when saving for the backward pass and at hidden = 256, else
- * 32768; 0 = always; results agree within rounding). Up to
+ * 32768; 0 = always; states and embeddings are the same bits, gradients agree within rounding). Up to
  * 8192 it does not apply to a batch reduced to its distinct nodes (see xrl_encode) that is saved for the
  * backward pass: its rounds of any size run on them;
  * XRL_WGRAD_WIDE_MIN_ROWS = row count from which the weight-gradient kernel uses 256-column

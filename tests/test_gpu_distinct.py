@@ -100,6 +100,46 @@ def test_reduction_changes_nothing(kind, hidden, precision, layers, readout, mon
     assert np.linalg.norm(da - db) <= (1e-5 if precision == "fp32" else 2e-2) * np.linalg.norm(da)
 
 
+@pytest.mark.parametrize("hidden,precision,d_edge,n_cand", [(64, "bf16", 8, 100), (128, "bf16", 8, 100), (256, "bf16", 8, 30),
+                                                            (128, "bf16", 20, 100), (64, "fp32", 8, 30)])
+def test_reduction_at_default_thresholds(hidden, precision, d_edge, n_cand, monkeypatch):
+    """A kept batch as a program runs it: the first forward-only encode takes the whole batch, on the persistent kernels
+    where it is large enough for them, the second one its levels, on a mixture of split and persistent ones, and a
+    saving encode the levels on persistent ones throughout. All give the whole batch's bits. (d_edge = 20: edge
+    attributes wider than the persistent edge kernels take, and the backward pass that recomputes.)"""
+    import torch
+    rng = np.random.Generator(np.random.PCG64(5))
+    model, _ = synth.make_config(1)
+    model.update(hidden=hidden, precision=precision, rounds=5, d_edge=d_edge)
+    state = synth.concat_states([synth.make_state(rng, synth.resnet_dag(rng, 16), n_cand, by_block=True)])
+    state["edge_feat"] = np.ascontiguousarray(np.tile(state["edge_feat"], (1, 3))[:, :d_edge])
+    w = synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1)
+    N = len(state["node_op"])
+    assert N > (8192 if hidden == 256 else 32768) or precision == "fp32"
+    got = []
+    for min_us in ("-1", "0"):
+        monkeypatch.setenv("XRL_DISTINCT_MIN_US", min_us)
+        enc = xrl.Encoder(model, w)
+        batch = enc.pack(state)
+        embs = [enc.encode(batch)]
+        assert enc.batch_level(batch, 0)[0] == N
+        embs.append(enc.encode(batch))
+        nodes = [enc.batch_level(batch, r)[0] for r in range(6)]
+        assert (max(nodes) < N and min(nodes) < 8192) if min_us == "0" else nodes == [N] * 6
+        embs.append(enc.encode(batch, save_for_backward=True))
+        acts = [enc.get_activation(batch, "h", r) for r in range(6)] + [enc.get_activation(batch, "agg", r) for r in range(1, 6)]
+        dw = torch.zeros(enc.n_weights, device="cuda")
+        enc.encode_backward(batch, torch.randn(batch.G, hidden, generator=torch.Generator().manual_seed(1)).cuda(), dw)
+        got.append((embs, acts, dw.double()))
+        batch.free()
+        enc.close()
+    (e0, a0, d0), (e1, a1, d1) = got
+    assert all(torch.equal(x, e0[0]) for x in e0 + e1)
+    assert all(torch.equal(x, y) for x, y in zip(a0, a1))
+    # (as in test_reduction_changes_nothing)
+    assert float((d1 - d0).norm() / d0.norm()) <= (1e-5 if precision == "fp32" else 2e-2)
+
+
 def test_reduced_batch_against_the_oracle(monkeypatch):
     from test_gpu_backward import run_backward_case
     monkeypatch.setenv("XRL_DISTINCT_MIN_US", "0")

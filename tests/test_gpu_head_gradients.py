@@ -1,10 +1,12 @@
 """Heads backward at the row counts where its launches change shape: rows per block of the row-MLP
 backward (1, 2, 4, 8), chunks of 64 rows and their remainders in the weight gradients, layers of
-one chunk beside layers of many. Against the float64 oracle; fp32 sums of at most 2049 terms whose
-factors carry a few dozen fp32 operations: 1e-5 of the tensor's norm."""
+one chunk beside layers of many. Against the float64 oracle, every tensor by itself: 1e-5 of its norm
+and, for sums that cancel (the last bias: the gradients of a softmax's logits sum to zero), the heads'
+kappa of grad_checks times the norm of the sums of absolute terms."""
 import numpy as np
 import pytest
 
+import grad_checks as GC
 import synth
 from oracle import xrl_oracle as O
 from test_gpu_forward import heads_only_state, oracle_model, weights_for
@@ -30,6 +32,15 @@ def test_head_gradients_at_row_counts(hidden, n_states, n_cand):
     t = lambda x: torch.from_numpy(x).cuda()
     dw = torch.zeros(enc.n_weights, dtype=torch.float32, device="cuda")
     demb = enc.policy_value_backward(batch, t(emb), t(dlogp), t(dvalue), t(dentropy), dw)
-    ref_demb, ref_dw = O.policy_value_backward(om, w, emb.astype(np.float64), state, dlogp, dvalue, dentropy)
-    for got, ref in ((demb.cpu().numpy(), ref_demb), (dw.cpu().numpy(), ref_dw)):
-        assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref)
+    bound = O.zero_grads(om)
+    ref_demb, ref_dw = O.policy_value_backward(om, w, emb.astype(np.float64), state, dlogp, dvalue, dentropy, bound=bound)
+    assert np.linalg.norm(demb.cpu().numpy() - ref_demb) <= 1e-5 * np.linalg.norm(ref_demb)
+    got, bound = dw.cpu().numpy().astype(np.float64), O.flatten(om, bound)
+    L = float(np.abs(O.policy_value(om, w, emb.astype(np.float64), state)["logit"]).max())
+    for name, sl, _ in GC.tensors(om):
+        err = np.linalg.norm(got[sl] - ref_dw[sl])
+        if not name.startswith(("policy", "value")):
+            assert err == 0, name
+            continue
+        tol = 1e-5 * np.linalg.norm(ref_dw[sl]) + (2e-6 + 1e-5 * max(1.0, L)) * np.linalg.norm(bound[sl])
+        assert err <= tol, (name, err, tol)
