@@ -1650,6 +1650,7 @@ bool distinct_pays(const xrl_ctx *c, const xrl_batch *b) {
 // Finds the levels' classes, reads back how many there are, and, if that is few enough, makes the levels'
 // graphs. Two waits for the stream (the counts of classes, then of tiles).
 int find_distinct(xrl_ctx *c, xrl_batch *b) {
+  RelaxedCapture relaxed;               // (an encode that neither allocated nor waited before must not end another stream's capture)
   const int R = c->m.rounds, L = R + 1, De = c->m.d_edge, Dd = c->m.n_node_dense;
   const int64_t N = b->N, E = b->E;
   const xrl_batch_device &d = b->dev;

@@ -241,3 +241,29 @@ def test_keys_of_one_tag(monkeypatch):
     for emb, dw, nodes in got[1:]:
         assert nodes == [2 + G // 2, 2 + 2 * (G // 2)]      # first key, q, every node of the second key; and its q
         assert torch.equal(emb, got[0][0]) and torch.equal(dw, got[1][1])
+
+
+def test_reducing_during_another_streams_capture(monkeypatch):
+    """The encode that reduces a batch allocates and waits; a capture that is under way on another stream goes on."""
+    import torch
+    monkeypatch.setenv("XRL_DISTINCT_MIN_US", "0")
+    rng = np.random.Generator(np.random.PCG64(6))
+    model, _ = synth.make_config(1)
+    state = synth.concat_states([synth.make_state(rng, synth.resnet_dag(rng, 3), 20, by_block=True)])
+    enc = xrl.Encoder(model, synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1), stream=torch.cuda.Stream())
+    batch = enc.pack(state)
+    want = enc.encode(batch)
+    out = torch.empty_like(want)
+    x = torch.zeros(8, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):       # (the mode that forbids unsafe calls)
+        x += 1
+        enc.encode(batch, out=out)
+        x += 1
+    assert enc.batch_level(batch, 0)[0] < batch.N
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(out, want) and float(x.sum()) == 16
+    batch.free()
+    enc.close()
