@@ -846,6 +846,7 @@ int check_batch(xrl_ctx *c, const xrl_batch *b, const char *who) {
     return fail(XRL_ERR_SHAPE, "%s: batch was packed for different feature widths", who);
   if (b->owner != c->id) {               // uploaded by another context, perhaps on another stream
     const_cast<xrl_batch *>(b)->shared = true;
+    RelaxedCapture relaxed;              // (this stream or another may be under capture: the wait is no part of it)
     if (b->mem.copied) HIP_TRY(hipEventSynchronize((hipEvent_t)b->mem.copied));
   }
   if (!(c->captured && b->shared) && is_capturing(c)) {

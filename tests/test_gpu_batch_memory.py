@@ -194,3 +194,28 @@ def test_idle_blocks_make_room(what):
         assert torch.equal(emb[:1000].cpu(), want)
     first.free()
     enc.close()
+
+
+def test_another_contexts_batch_in_a_capture():
+    """A batch that one context uploaded, encoded by another one under capture: the wait for its transfer is not
+    captured and does not end the capture."""
+    torch, model, weights, states = _setup([(4, 10)])
+    side = torch.cuda.Stream()
+    a, b = xrl.Encoder(model, weights, stream=torch.cuda.Stream()), xrl.Encoder(model, weights, stream=side)
+    batch = a.pack(states[0])
+    want = a.encode(batch)
+    out = torch.empty_like(b.encode(batch))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        b.encode(batch, out=out)
+    for _ in range(3):
+        out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        eager = a.encode(batch)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want) and torch.equal(eager, want)
+    batch.free()
+    a.close()
+    b.close()
