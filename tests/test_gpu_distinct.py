@@ -267,3 +267,53 @@ def test_reducing_during_another_streams_capture(monkeypatch):
     assert torch.equal(out, want) and float(x.sum()) == 16
     batch.free()
     enc.close()
+
+
+@pytest.mark.parametrize("grouped", [True, False])
+def test_reduced_step_in_a_graph(grouped, monkeypatch):
+    """A saving encode and its backward pass of a reduced batch in a graph; grouped = False: the batch's first backward pass is
+    the captured one, which then makes its groupings in every replay. Replays among eager steps under new weights."""
+    import torch
+    monkeypatch.setenv("XRL_DISTINCT_MIN_US", "0")
+    monkeypatch.setenv("XRL_RESIDENT_MAX_GRAPHS", "0")
+    rng = np.random.Generator(np.random.PCG64(6))
+    model, _ = synth.make_config(1)
+    model.update(hidden=128, precision="bf16", rounds=3)
+    state = synth.concat_states([synth.make_state(rng, synth.resnet_dag(rng, 4), n, by_block=True) for n in (30, 9)])
+    w = [synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1) for _ in range(2)]
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        enc = xrl.Encoder(model, w[0], stream=side)
+        up = torch.randn(41, 128, generator=torch.Generator().manual_seed(2)).cuda()
+        twin, batch = enc.pack(state), enc.pack(state)
+        emb, dw = torch.empty(41, 128, device="cuda"), torch.zeros(enc.n_weights, device="cuda")
+
+        def step(b):
+            enc.encode(b, save_for_backward=True, out=emb)
+            dw.zero_()
+            enc.encode_backward(b, up, dw)
+        step(twin)                                  # (the workspaces have their sizes)
+        if grouped:
+            step(batch)
+        else:
+            enc.encode(batch, save_for_backward=True)
+        assert enc.batch_level(batch, 0)[0] < batch.N
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side, capture_error_mode="relaxed"):
+            step(batch)
+        for weights in w:
+            enc.set_weights(weights)
+            for _ in range(3):
+                step(twin)
+                want = emb.clone(), dw.clone()
+                emb.zero_()
+                graph.replay()
+                torch.cuda.synchronize()
+                assert torch.equal(emb, want[0]) and torch.equal(dw, want[1])
+                step(batch)
+                torch.cuda.synchronize()
+                assert torch.equal(emb, want[0]) and torch.equal(dw, want[1])
+        batch.free()
+        twin.free()
+        enc.close()
