@@ -29,15 +29,25 @@ PEAK_HBM_GBS = 8000.0
 # hash covers the files the kernel is built from (comments and blank space apart); otherwise null.
 TRAFFIC = {
     # configuration 2 (profiles/forward_config2_bf16_hbm_traffic.md): persistent forward kernels, weights in LDS
-    (2, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2p.hip.h"), sha256_16="c1095d7066032095",
-                              bytes_per_launch=(11154.7 * 2.000 + 11599.5 * 1.000) * 1024),
-    (2, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2p.hip.h"), sha256_16="c1095d7066032095",
-                              bytes_per_launch=(15508.5 * 2.000 + 18218.2 * 1.000) * 1024),
-    # configuration 4 (profiles/forward_config4_bf16_kernel_stats_and_traffic.md): register-stationary forward kernels
-    (4, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h"), sha256_16="b61a512bcdbfb016",
-                              bytes_per_launch=(89442.7 * 2.000 + 70572.0 * 1.000) * 1024),
-    (4, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h"), sha256_16="b61a512bcdbfb016",
-                              bytes_per_launch=(118742.4 * 2.000 + 162434.5 * 1.000) * 1024),
+    (2, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2p.hip.h"), sha256_16="fd3c0eea759fbd7e",
+                              bytes_per_launch=(11146.9 * 2.000 + 11599.5 * 1.000) * 1024),
+    (2, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2p.hip.h"), sha256_16="fd3c0eea759fbd7e",
+                              bytes_per_launch=(15498.3 * 2.000 + 18218.2 * 1.000) * 1024),
+    # configuration 4 (profiles/forward_config4_bf16_kernel_stats_and_traffic.md): register-stationary forward kernels on the
+    # levels of the reduced batch, mean over the rounds (so the sources that decide the levels belong to it)
+    (4, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="908801e909df0b11",
+                              bytes_per_launch=(30503.2 * 2.000 + 40853.2 * 1.000) * 1024),
+    (4, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="908801e909df0b11",
+                              bytes_per_launch=(42850.6 * 2.000 + 41315.2 * 1.000) * 1024),
+    # configuration 5 (profiles/step_config5_bf16_hbm_traffic.md): the same, saving, and the backward kernels
+    (5, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="908801e909df0b11",
+                              bytes_per_launch=(232484.6 * 2.000 + 1057668.6 * 1.000) * 1024),
+    (5, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="908801e909df0b11",
+                              bytes_per_launch=(311879.8 * 2.000 + 660799.0 * 1.000) * 1024),
+    (5, "bf16", "bwd_edge"): dict(sources=("mma.hip.h", "mlp2_bwd.hip.h", "mlp2_bwdz.hip.h", "distinct.hip.h"), sha256_16="44d2f5df597e5169",
+                                  bytes_per_launch=(233177.3 * 2.000 + 2312662.1 * 1.000) * 1024),
+    (5, "bf16", "bwd_node"): dict(sources=("mma.hip.h", "mlp2_bwd.hip.h", "mlp2_bwdz.hip.h", "distinct.hip.h"), sha256_16="44d2f5df597e5169",
+                                  bytes_per_launch=(181945.7 * 2.000 + 929924.2 * 1.000) * 1024),
 }
 
 
@@ -271,9 +281,11 @@ def main():
         "pool": dict(kernel="per-graph readout sum (fused with the readout MLP)", flops=0.0,
                      bytes=levels[R][0] * H * b + (4 * N if reduced else 0) + 4 * (G + 1) + G * H * 4),
         "grad_gather": dict(kernel="per-node sum of the per-edge gradients (receiver and sender side)", flops=0.0,
-                            # (reduced: then summed per distinct node of the round below, in fp32 first)
-                            bytes=(EH + n_recv * H * b + mask_n if kept else 2 * EH) + 2 * NH + 4 * (2 * n_node + n_edge)
-                            + (NH + n_below * H * (8 + b) if reduced else 0)),
+                            # (reduced: the three kinds of rows summed per distinct node of the round below, in fp32
+                            # first, which is written, read and stored as the operand type)
+                            bytes=(EH + NH + (n_recv * H * b if kept else EH) + 8 * (n_edge + 2 * n_node) + mask_n * zk
+                                   + n_below * H * (8 + b)) if reduced else
+                            (EH + n_recv * H * b + mask_n if kept else 2 * EH) + 2 * NH + 4 * (2 * n_node + n_edge)),
     }
     if kept:
         work.update({

@@ -192,7 +192,7 @@ __global__ __launch_bounds__(256) void class_of_kernel(const ClassArgs a) {
 
 // The graph of a level's representatives: receiver-order arrays like the batch's own.
 struct LevelFillArgs {
-  int64_t n_cls, n_edges;
+  int64_t n_cls;
   const int32_t *reps, *ptr, *cls, *prev;   // classes of this level and of the one below (nullptr: level 0)
   const int32_t *in_ptr, *in_src, *node_op;
   const float *edge_feat, *node_dense;

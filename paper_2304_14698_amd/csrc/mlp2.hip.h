@@ -1,5 +1,5 @@
 // Fused two-layer ReLU MLP over a tile of rows, both layers on the matrix cores, the hidden
-// activation never leaving registers. One kernel template serves the three learned transforms of
+// activation never leaving the block. One kernel template serves the three learned transforms of
 // the encoder (Section 3.4):
 //   EMBED  rows = nodes,  x = [sum of incoming edge attrs | one-hot op | dense attrs]   -> h0
 //          (the sum over the node's in-edges is formed in the prologue)
@@ -7,9 +7,9 @@
 //          -> ReLU MLP -> summed per receiver (the message-passing sum)                 -> agg
 //   NODE   rows = nodes,  x = [h | agg]                                                 -> h'
 //
-// Each wave owns 32 rows. Both layers are computed transposed (features x rows: the weights are
-// the A operand, the gathered input rows the B operand, loaded straight from global memory into
-// registers), so layer 1's accumulator layout (lane = row, registers = features) is, after ReLU
+// A tile is 32 rows: one wave's (mlp2_wave_tile, the one-launch encoders) or, split by output features, that
+// of a block of H / 32 waves (mlp2_split_kernel). Both layers are computed transposed (features x rows: the weights are
+// the A operand, the gathered input rows the B operand), so layer 1's accumulator layout (lane = row, registers = features) is, after ReLU
 // and conversion, the B-operand layout of layer 2; layer 2's accumulators have lane = row as
 // well, so a row leaves as register quads and the per-receiver sum runs across adjacent lanes.
 // Weights are pre-arranged in the per-lane fragment order (arrange_weights_kernel in the
@@ -22,7 +22,7 @@ enum { KIND_EMBED = 0, KIND_EDGE = 1, KIND_NODE = 2 };
 
 struct Mlp2Args {
   int64_t n_rows;
-  int64_t n_blocks;        // number of 128-row tiles
+  int64_t n_blocks;        // number of tiles
   const void *W1s, *W2s;   // fragment-ordered weights, operand type
   const float *b1, *b2;    // [H]
   int nslab1;              // slabs of layer 1's (zero-padded) input width
@@ -430,7 +430,8 @@ __device__ __forceinline__ void mlp2_wave_tile(const Mlp2Args &a, const int64_t 
   }
 }
 
-// Split form, one launch per layer where the persistent kernels do not apply (fp32, small batches): a block of H / 32 waves takes one
+// Split form, one launch per layer where the persistent kernels do not apply (fp32; small batches in bf16, save
+// the levels of a reduced batch that is saved for the backward pass): a block of H / 32 waves takes one
 // tile, wave w the 32 output features of block w in both layers. The tile's input rows are gathered
 // once, as operand fragments, each wave its share, and shared through LDS, as is relu(z1); a wave
 // streams only its own slices of the weights, eight fragments ahead. A tile's chain of dependent

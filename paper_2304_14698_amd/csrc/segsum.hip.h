@@ -1,7 +1,8 @@
 // Deterministic segment sum over consecutive rows: out[s, :] = sum of rows [ptr[s], ptr[s+1]).
 // Used for the receiver-side sum of incoming edge attributes (node-update layer, Section 3.4),
-// the per-graph sum of node states (global-update layer); the backward pass gathers per node
-// instead (node_grad_gather_kernel at the end of this file).
+// the per-graph sum of node states (global-update layer), and the gradients of a reduced batch per class
+// (distinct.hip.h); the backward pass of a batch that is not reduced gathers per node instead
+// (node_grad_gather_kernel at the end of this file).
 //
 // Rows are cut into fixed sub-tiles of RT rows; D / VEC lanes own one sub-tile, each lane a
 // 16-byte column slice. A lane walks its sub-tile in row order, so every sum has a fixed order

@@ -1756,7 +1756,7 @@ int find_distinct(xrl_ctx *c, xrl_batch *b) {
     LevelFillArgs f;
     memset(&f, 0, sizeof(f));
     auto at = [&](size_t x) { return (int32_t *)(blk + x); };
-    f.n_cls = g.N; f.n_edges = g.E; f.reps = reps[l]; f.ptr = ptr[l]; f.cls = q->cls[l]; f.prev = l > 0 ? q->cls[l - 1] : nullptr;
+    f.n_cls = g.N; f.reps = reps[l]; f.ptr = ptr[l]; f.cls = q->cls[l]; f.prev = l > 0 ? q->cls[l - 1] : nullptr;
     f.in_ptr = d.in_ptr; f.in_src = d.in_src; f.node_op = d.node_op; f.edge_feat = d.edge_feat; f.node_dense = d.node_dense;
     f.De = De; f.Dd = Dd; f.receivers = c->d_counts + 2 * kMaxLevels + l;
     f.o_ptr = at(o[l].ptr); f.o_agg_src = at(o[l].agg); f.o_feat = (float *)(blk + o[l].feat);
