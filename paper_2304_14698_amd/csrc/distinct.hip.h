@@ -89,7 +89,8 @@ __device__ __forceinline__ void class_insert(const ClassArgs &a, int64_t n) {
 }
 // The nodes of every state's first graph, a block each, before all nodes: they are the smallest of most
 // classes, so the others find their class in place and leave the table alone (all at once, thousands
-// of nodes would go for the same slots: 98 against 17 us per level at 703 k nodes of 2080 graphs).
+// of nodes would go for the same slots: 98 us per level at 703 k nodes of 2080 graphs, against 9 for these and
+// then 30 for all).
 __global__ __launch_bounds__(256) void class_insert_first_kernel(const ClassArgs a) {
   const int g = a.state_graph_ptr[blockIdx.x], n1 = a.graph_node_ptr[g + 1];
   for (int n = a.graph_node_ptr[g] + threadIdx.x; n < n1; n += 256) class_insert(a, n);
