@@ -237,7 +237,7 @@ def main():
     kern = {}
     names = ("embed", "edge", "edge_fixup", "node", "gat_linear", "gat_aggregate", "pool", "readout", "heads", "resident")
     if backward:
-        names += ("bwd_edge", "bwd_node", "bwd_embed", "wgrad_edge", "wgrad_node", "wgrad_embed", "grad_gather", "gat_bwd")
+        names += ("bwd_edge", "bwd_node", "bwd_embed", "wgrad", "grad_gather", "gat_bwd")
     for k in names:
         tot, n = enc.read_timing(k)
         kern[k] = dict(avg_us=(tot / n * 1e3 if n else 0.0), launches_per_step=n / args.steps)
@@ -287,6 +287,9 @@ def main():
                                    + n_below * H * (8 + b)) if reduced else
                             (EH + n_recv * H * b + mask_n if kept else 2 * EH) + 2 * NH + 4 * (2 * n_node + n_edge)),
     }
+    # the weight gradients of a step share a launch or a few (one MLP's alone is not timed)
+    n_wgrad = max(kern["wgrad"]["launches_per_step"], 1) if backward else 1
+    wgrad_flops = 2.0 * H * (R * (n_edge * (3 * H + De + 2) + n_node * (3 * H + 2)) + n_node0 * (De + Tn + Dd + H + 2))
     if kept:
         work.update({
             "bwd_edge": dict(kernel="backward through the edge MLP from the kept forward (one launch per round)",
@@ -300,12 +303,10 @@ def main():
                              bytes=3 * NH + n_recv * H * b + mask_n * (1 + 1 / max(R, 1)) + 4 * n_node),
             "bwd_embed": dict(kernel="backward through the embed MLP from the kept forward", flops=2.0 * n_node0 * H * H,
                               bytes=2 * NH0 + mask_n0),
-            "wgrad_edge": dict(kernel="weight gradients of one edge MLP, both layers",
-                               flops=2.0 * n_edge * H * (3 * H + De + 2), bytes=NH + 4 * EH + n_edge * De * 4 + 8 * n_edge),
-            "wgrad_node": dict(kernel="weight gradients of one node MLP, both layers",
-                               flops=2.0 * n_node * H * (3 * H + 2), bytes=4 * NH + n_recv * H * b + 4 * n_node),
-            "wgrad_embed": dict(kernel="weight gradients of the embed MLP, both layers",
-                                flops=2.0 * n_node0 * H * (De + Tn + Dd + H + 2), bytes=3 * NH0 + n_edge0 * De * 4 + n_node0 * (8 + 4 * Dd)),
+            "wgrad": dict(kernel="weight gradients of all MLPs, both layers", flops=wgrad_flops / n_wgrad,
+                          # first layer: its input rows (node states once, not once per edge) and dz1; second: relu(z1), dz2
+                          bytes=(R * (NH + 4 * EH + n_edge * (De * 4 + 8) + 4 * NH + n_recv * H * b + 4 * n_node)
+                                 + 3 * NH0 + n_edge0 * De * 4 + n_node0 * (8 + 4 * Dd)) / n_wgrad),
         })
     else:
         # small batches and fp32: the backward kernels recompute the first layer (and, for the edge
@@ -315,10 +316,7 @@ def main():
                              bytes=None),
             "bwd_node": dict(kernel="backward through the node MLP (one launch per round)", flops=2.0 * n_node * H * 5 * H, bytes=None),
             "bwd_embed": dict(kernel="backward through the embed MLP", flops=2.0 * n_node0 * H * (De + Dd + 2 * H), bytes=None),
-            "wgrad_edge": dict(kernel="weight gradients of one edge MLP, both layers", flops=2.0 * n_edge * H * (3 * H + De + 2), bytes=None),
-            "wgrad_node": dict(kernel="weight gradients of one node MLP, both layers", flops=2.0 * n_node * H * (3 * H + 2), bytes=None),
-            "wgrad_embed": dict(kernel="weight gradients of the embed MLP, both layers",
-                                flops=2.0 * n_node0 * H * (De + Tn + Dd + H + 2), bytes=None),
+            "wgrad": dict(kernel="weight gradients of all MLPs, both layers", flops=wgrad_flops / n_wgrad, bytes=None),
         })
     ridge = peak * 1e12 / (PEAK_HBM_GBS * 1e9)           # flop per byte at which the two peaks meet
     report = {}

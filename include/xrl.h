@@ -208,8 +208,9 @@ int xrl_batch_free(xrl_batch *b);   /* frees host and device copies; NULL is acc
  * 32768; 0 = always; states and embeddings are the same bits, gradients agree within rounding). Up to
  * 8192 it does not apply to a batch reduced to its distinct nodes (see xrl_encode) that is saved for the
  * backward pass: its rounds of any size run on them;
- * XRL_WGRAD_WIDE_MIN_ROWS = row count from which the weight-gradient kernel uses 256-column
- * tiles (default 2^18 at hidden = 256, else 2^20; same sums in a different, equally fixed order);
+ * XRL_WGRAD_WIDE_MIN_ROWS = rows of the products of one weight-gradient launch, added up, from which it uses
+ * 256-column tiles at hidden = 256 in bf16 (default 2^18; same sums in a different, equally fixed order);
+ * XRL_GRAD_ROOM = bytes of gradients kept for one such launch (default 2^31; always at least one MLP's);
  * XRL_RESIDENT_MAX_GRAPHS (default 256; 0 = never) and XRL_RESIDENT_MAX_TILES (default 4) =
  * largest batch, in graphs and in 32-row tiles of nodes or edges per graph, that xrl_encode runs
  * as one launch with a block per graph (message-passing rounds of the MLP kind, rows of at most
@@ -372,10 +373,11 @@ int xrl_mlp_backward(xrl_ctx *ctx, const xrl_batch *b, int32_t kind, int32_t rou
  * "edge_fixup", "node", "pool", "readout", "heads"} (the steps of Section 3.4 / 3.3.2 in
  * execution order; "gat_linear", "gat_aggregate" with XRL_ROUND_GAT; "resident" = the whole
  * encoder of a small batch in one launch). Backward (Section 3.3.4):
- * {"bwd_edge", "bwd_node", "bwd_embed"} = gradients through the fused MLPs, {"wgrad_edge",
- * "wgrad_node", "wgrad_embed"} = both layers' weight gradients of one such MLP with their
- * reductions ("wgrad": the same for a single product through xrl_weight_gradient), "grad_gather" =
- * per-node sum of the per-edge gradients; "gat_bwd" = one attention round's backward.
+ * {"bwd_edge", "bwd_node", "bwd_embed"} = gradients through the fused MLPs, "wgrad" = the weight
+ * gradients of as many MLPs as one launch takes, with their reductions (a single product through
+ * xrl_weight_gradient; {"wgrad_edge", "wgrad_node", "wgrad_embed"}: accepted, no launch is only
+ * theirs), "grad_gather" = per-node sum of the per-edge gradients; "gat_bwd" = one attention
+ * round's backward.
  * Errors: NULL, INDEX, HIP. */
 int xrl_set_timing(xrl_ctx *ctx, int enabled);
 int xrl_read_timing(xrl_ctx *ctx, const char *kernel, double *total_ms, int64_t *launches);

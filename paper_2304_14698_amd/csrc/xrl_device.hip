@@ -123,6 +123,9 @@ static const char *const kTimedNames[TK_COUNT] = {"embed", "edge", "edge_fixup",
 constexpr int64_t kMaxFusedSlots = 4096;   // largest G the single-launch heads kernel takes
 constexpr int kCounts = 3 * kMaxLevels;
 constexpr int64_t kPersistentMinRows = 8192;   // rows from which the persistent kernels replace the split one
+constexpr size_t kZeroRow = 1024 + 256;        // 1 KB of zeros and behind it one element that is 1 (see WgradLaunch)
+constexpr size_t kGradRoom = (size_t)2 << 30;   // gradients kept for a launch of weight gradients (see encode_backward_impl)
+constexpr int kAvecChunks = 1024;              // most chunks of rows of an attention vector's gradient
 constexpr int64_t kClusterMaxGraphs = 256; // largest G of the one-launch encoder with several blocks per graph
 
 // Scratch of xrl_policy_value_static, the entry point that allocates nothing: per-state counters,
@@ -146,7 +149,8 @@ struct xrl_ctx {
   int max_lds = 65536;          // LDS bytes one block may use
   int64_t p_min_rows = 8192;    // smallest row count for the persistent kernels (XRL_PERSISTENT_MIN_ROWS) when saving
   int64_t p_min_rows_forward = 8192;   // for the backward pass, and when not
-  int64_t wide_min_rows = 1 << 20;   // ... for the 256-column weight-gradient tiles (XRL_WGRAD_WIDE_MIN_ROWS)
+  int64_t wide_min_rows = 1 << 18;   // rows of a launch's products from which 256-column weight-gradient tiles are used (XRL_WGRAD_WIDE_MIN_ROWS)
+  size_t grad_room = kGradRoom;      // XRL_GRAD_ROOM
   int64_t resident_max_graphs = 0;   // largest batch (graphs) for the one-launch encoder (XRL_RESIDENT_MAX_GRAPHS)
   int64_t resident_max_tiles = 0;    // ... and the most 32-row tiles (nodes, or edges) of one graph (XRL_RESIDENT_MAX_TILES)
   float *d_w = nullptr;         // flat fp32 weights
@@ -1222,151 +1226,107 @@ int launch_mlp2_bwdz(xrl_ctx *c, int kind, Mlp2BwdzArgs &a, bool fold, bool give
   return fail(XRL_ERR_UNSUPPORTED, "hidden = %d", c->m.hidden);
 }
 
-// rows per chunk / number of chunks of the weight-gradient kernels
-inline void wgrad_chunks(int64_t n_rows, int *rows_per_chunk, int *n_chunks) {
-  int64_t nc = (n_rows + 127) / 128;        // (small batches: enough chunks to occupy the machine)
-  if (nc > 512) nc = 512;
-  if (nc < 1) nc = 1;
-  int64_t rpc = (n_rows + nc - 1) / nc;
-  rpc = (rpc + 63) / 64 * 64;
-  *rows_per_chunk = (int)rpc;
-  *n_chunks = (int)((n_rows + rpc - 1) / rpc);
-  if (*n_chunks < 1) *n_chunks = 1;
-}
-inline size_t wgrad_partial_floats(int64_t n_rows, int Ka, int H, int n_cu) {
-  int rpc, nc;
-  wgrad_chunks(n_rows, &rpc, &nc);
-  // transpose-read kernel: at most n_cu wide tiles of 256 columns plus 2 n_cu tiles of 128, or
-  // 2 n_cu tiles of 128 columns alone (see launch_wgrad_h)
-  const size_t wide = (size_t)n_cu * 256 * H + (size_t)2 * n_cu * 128 * H;
-  return std::max((size_t)nc * ((Ka + 1 + 63) / 64 * 64) * H, wide);
+// Weight-gradient products waiting for one launch (see wgrad.hip.h), and the memory their partials go to.
+struct WgradQueue {
+  WgradLaunch a;
+  int n = 0;
+  float *partial = nullptr;
+  size_t partial_floats = 0;
+};
+constexpr int wgrad_rows(size_t elem, int ta) { return elem == 2 ? ta / 4 : 16; }   // rows per stage: 32 and 64 in bf16
+// Memory for the partials of a launch's jobs: those on 256-column and those on 128-column tiles.
+inline size_t wgrad_partial_floats(const xrl_ctx *c) {
+  const int H = c->m.hidden, De = c->m.d_edge;
+  return wgrad_partial_bound(H, 128, 2 * c->n_cu, De) + (c->elem == 2 && H == 256 ? wgrad_partial_bound(H, 256, c->n_cu, De) : 0);
 }
 
-template <int H, int KIND, int TA>
-int launch_wgrad2(xrl_ctx *c, const WgradArgs &a, const Wgrad2Plan &p, int ka_base, int KaP, int bias_row) {
-  constexpr int RS = TA == 256 ? 64 : 32;      // the wide tiles run one block per CU: 64 rows in flight per stage
-  constexpr size_t lds = wgrad2_lds_bytes<H, TA, RS>();
-  auto kern = wgrad2_kernel<H, KIND, TA, RS>;
+template <typename T, int H, int TA>
+int launch_wgrads(xrl_ctx *c, WgradLaunch &a, int n, float *partial, size_t floats, size_t *used) {
+  constexpr int RS = wgrad_rows(sizeof(T), TA);
+  using S = WgradShape<T, H, TA, RS>;
+  const WgradPlan p = plan_wgrads(a, n, H, TA, RS, c->n_cu * 256 / TA);
+  if (p.partial_floats > floats) return fail(XRL_ERR_STATE, "weight gradients: %zu floats of partial sums, %zu planned", p.partial_floats, floats);
+  for (int i = 0; i < n; ++i)
+    if (a.job[i].kt) {
+      a.job[i].partial = partial;
+      partial += (size_t)a.job[i].ny * a.job[i].KaP * H;
+    }
+  *used = p.partial_floats;
+  a.zero_row = c->zero_row;
+  auto kern = wgrad_kernel<T, H, TA, RS>;
   static bool attr_set = false;          // one attribute per kernel instantiation
   if (!attr_set) {
-    HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS));
     attr_set = true;
   }
-  WgradArgs b = a;
-  b.rows_per_chunk = p.rows_per_slot;
-  b.n_chunks = p.ny;
-  kern<<<dim3((unsigned)(p.ny * p.kt)), dim3(2 * TA), lds, c->stream>>>(b, p.kt, p.ny, ka_base, KaP, bias_row);
+  if (p.blocks > 0) kern<<<dim3((unsigned)p.blocks), dim3(S::NT), S::LDS, c->stream>>>(a);
+  if (p.entries > 0) wgrad_reduce_kernel<<<dim3((unsigned)p.entries), dim3(256), 0, c->stream>>>(a, H);
   HIP_TRY(hipGetLastError());
   return XRL_OK;
 }
 
-template <int H, int TA>
-int launch_wgrad2_kind(xrl_ctx *c, int kind, const WgradArgs &a, const Wgrad2Plan &p, int ka_base, int KaP,
-                       int bias_row = -1) {
-  if (kind == WG_PLAIN) return launch_wgrad2<H, WG_PLAIN, TA>(c, a, p, ka_base, KaP, bias_row);
-  if (kind == WG_EDGE) return launch_wgrad2<H, WG_EDGE, TA>(c, a, p, ka_base, KaP, bias_row);
-  return launch_wgrad2<H, WG_NODE, TA>(c, a, p, ka_base, KaP, bias_row);
-}
-
-template <typename T, int H>
-int launch_wgrad_h(xrl_ctx *c, int kind, WgradArgs &a, float *dW, float *db) {
-  if (a.n_rows <= 0) return XRL_OK;
-  const int64_t n = (int64_t)(a.Ka + 1) * H;
-  auto reduce = [&](const float *partial, int n_chunks, int KaP, int Ka, float *dw, float *dbias) {
-    const int64_t cnt = (int64_t)(Ka + (dbias ? 1 : 0)) * H;
-    if (cnt > 0)
-      wgrad_reduce_kernel<<<dim3((unsigned)((cnt + 31) / 32)), dim3(256), 0, c->stream>>>(partial, n_chunks, KaP, Ka, H,
-                                                                                         dw, dbias);
-  };
-  if constexpr (sizeof(T) == 2) {
-    if (kind != WG_EMBED) {                                // transpose-read kernel
-      int rc;
-      const int k_main = kind == WG_PLAIN ? a.Ka : 2 * H;  // the H-wide column parts
-      bool wide = false;
-      if constexpr (H >= 128) wide = k_main % 256 == 0 && a.n_rows >= c->wide_min_rows;
-      // PLAIN and NODE have one column past the H-wide parts, the all-ones bias column: its sums
-      // come from the vector ALU of the first tile's blocks (EDGE also has the edge attributes
-      // there and keeps them on the matrix cores)
-      const bool only_bias = kind != WG_EDGE && a.Ka == k_main && k_main % 128 == 0;
-      if (wide) {
-        if constexpr (H >= 128) {
-          const Wgrad2Plan pa = wgrad2_plan(a.n_rows, k_main / 256, c->n_cu, 1);
-          const int KaP = k_main + (only_bias && db ? 1 : 0);
-          if ((rc = launch_wgrad2_kind<H, 256>(c, kind, a, pa, 0, KaP, only_bias && db ? k_main : -1))) return rc;
-          reduce(a.partial, pa.ny, KaP, k_main, dW, only_bias ? db : nullptr);
-          if (!only_bias) {
-            // one launch of narrow tiles for the columns past the H-wide parts
-            WgradArgs t = a;
-            t.partial = a.partial + (size_t)pa.ny * KaP * H;
-            const Wgrad2Plan pb = wgrad2_plan(a.n_rows, 1, c->n_cu, 2);
-            if ((rc = launch_wgrad2_kind<H, 128>(c, kind, t, pb, k_main, 128))) return rc;
-            reduce(t.partial, pb.ny, 128, a.Ka - k_main, dW + (size_t)k_main * H, db);
-          }
-        }
-      } else if (only_bias) {
-        const Wgrad2Plan p = wgrad2_plan(a.n_rows, k_main / 128, c->n_cu, 2);
-        const int KaP = k_main + (db ? 1 : 0);
-        if ((rc = launch_wgrad2_kind<H, 128>(c, kind, a, p, 0, KaP, db ? k_main : -1))) return rc;
-        reduce(a.partial, p.ny, KaP, a.Ka, dW, db);
-      } else {
-        const Wgrad2Plan p = wgrad2_plan(a.n_rows, (a.Ka + 1 + 127) / 128, c->n_cu, 2);
-        if ((rc = launch_wgrad2_kind<H, 128>(c, kind, a, p, 0, p.kt * 128))) return rc;
-        reduce(a.partial, p.ny, p.kt * 128, a.Ka, dW, db);
-      }
-      HIP_TRY(hipGetLastError());
-      return XRL_OK;
-    }
-  }
-  wgrad_chunks(a.n_rows, &a.rows_per_chunk, &a.n_chunks);
-  const int kt = (a.Ka + 1 + 63) / 64;
-  dim3 grid((unsigned)kt, (unsigned)a.n_chunks);
-  if (kind == WG_PLAIN) wgrad_kernel<T, H, WG_PLAIN><<<grid, dim3(256), 0, c->stream>>>(a);
-  else if (kind == WG_EDGE) wgrad_kernel<T, H, WG_EDGE><<<grid, dim3(256), 0, c->stream>>>(a);
-  else if (kind == WG_NODE) wgrad_kernel<T, H, WG_NODE><<<grid, dim3(256), 0, c->stream>>>(a);
-  else wgrad_kernel<T, H, WG_EMBED><<<grid, dim3(256), 0, c->stream>>>(a);
-  wgrad_reduce_kernel<<<dim3((unsigned)((n + 31) / 32)), dim3(256), 0, c->stream>>>(
-      a.partial, a.n_chunks, kt * 64, a.Ka, H, dW, db);
-  HIP_TRY(hipGetLastError());
-  return XRL_OK;
-}
-
+// Launches what waits. At H = 256, 256-column tiles where the H-wide parts fill them and enough rows wait that the
+// chip's blocks, one per CU, are long against their start: products of 68 k rows in all 87 / 98 us (128-column /
+// 256-column tiles), 250 k 147 / 147, 437 k 202 / 198, 671 k 268 / 258, 1.2 M 405 / 379, 3 M 1188 / 960. At H = 128 the
+// second layers' products do not fill them and the others gain too little: 1.4 M rows, all on
+// 128-column tiles 187 us, two launches 110 + 85.
 template <typename T>
-int launch_wgrad(xrl_ctx *c, int kind, WgradArgs &a, float *dW, float *db) {
+int flush_wgrads(xrl_ctx *c, WgradQueue &q) {
+  if (q.n == 0) return XRL_OK;
+  Timed t(c, TK_WGRAD);
+  const int n = q.n;
+  q.n = 0;
+  float *partial = q.partial;
+  size_t left = q.partial_floats, used = 0;
+  auto run = [&](auto h) -> int {
+    constexpr int H = decltype(h)::value;
+    int n_narrow = n;
+    if constexpr (sizeof(T) == 2 && H == 256) {
+      int64_t rows = 0;
+      for (int i = 0; i < n; ++i) rows += q.a.job[i].n_rows;
+      if (rows >= c->wide_min_rows) {
+        WgradLaunch wide;
+        int n_wide = 0;
+        n_narrow = 0;
+        for (int i = 0; i < n; ++i) {
+          const WgradJob j = q.a.job[i];
+          const bool fits = j.kind == WG_EDGE || j.kind == WG_NODE || (j.kind == WG_PLAIN && j.Ka % 256 == 0 && j.ny == 0);
+          if (fits) wide.job[n_wide++] = j;
+          else q.a.job[n_narrow++] = j;
+        }
+        const int rc = n_wide ? launch_wgrads<T, H, 256>(c, wide, n_wide, partial, left, &used) : XRL_OK;
+        if (rc) return rc;
+        partial += used;
+        left -= used;
+      }
+    }
+    return n_narrow ? launch_wgrads<T, H, 128>(c, q.a, n_narrow, partial, left, &used) : XRL_OK;
+  };
   switch (c->m.hidden) {
-    case 64: return launch_wgrad_h<T, 64>(c, kind, a, dW, db);
-    case 128: return launch_wgrad_h<T, 128>(c, kind, a, dW, db);
-    case 256: return launch_wgrad_h<T, 256>(c, kind, a, dW, db);
+    case 64: return run(std::integral_constant<int, 64>());
+    case 128: return run(std::integral_constant<int, 128>());
+    case 256: return run(std::integral_constant<int, 256>());
   }
   return fail(XRL_ERR_UNSUPPORTED, "hidden = %d", c->m.hidden);
 }
 
-// dW[Kx, H] += X[:, :Kx]^T dZ and db += 1^T dZ for X = a.A [rows, a.Ka] (a.Ka = Kx rounded up to 8, the
-// columns past Kx zero): the plain product, whose tile also holds the all-ones column at a.Ka
+// Puts a product in the queue (launching what waits when the queue is full). EDGE: the attributes become a product of
+// their own when they are too wide for the extra columns.
 template <typename T>
-int launch_wgrad_embed_rows(xrl_ctx *c, WgradArgs &a, int Kx, float *dW, float *db) {
-  if constexpr (sizeof(T) == 2) {
-    if (a.n_rows <= 0) return XRL_OK;
-    auto run = [&](auto h) -> int {
-      constexpr int H = decltype(h)::value;
-      const Wgrad2Plan p = wgrad2_plan(a.n_rows, (a.Ka + 1 + 127) / 128, c->n_cu, 2);
-      const int KaP = p.kt * 128;
-      int rc = launch_wgrad2<H, WG_PLAIN, 128>(c, a, p, 0, KaP, -1);
-      if (rc) return rc;
-      const int64_t cnt_w = (int64_t)Kx * H;
-      if (cnt_w > 0)
-        wgrad_reduce_kernel<<<dim3((unsigned)((cnt_w + 31) / 32)), dim3(256), 0, c->stream>>>(a.partial, p.ny, KaP, Kx, H, dW, nullptr);
-      wgrad_reduce_kernel<<<dim3((unsigned)((H + 31) / 32)), dim3(256), 0, c->stream>>>(a.partial + (size_t)a.Ka * H, p.ny, KaP, 0, H,
-                                                                                     nullptr, db);
-      HIP_TRY(hipGetLastError());
-      return XRL_OK;
-    };
-    switch (c->m.hidden) {
-      case 64: return run(std::integral_constant<int, 64>());
-      case 128: return run(std::integral_constant<int, 128>());
-      case 256: return run(std::integral_constant<int, 256>());
-    }
+int queue_wgrad(xrl_ctx *c, WgradQueue &q, const WgradJob &job) {
+  if (job.n_rows <= 0) return XRL_OK;
+  if (q.n + 2 > kWgradMaxJobs)
+    if (int rc = flush_wgrads<T>(c, q)) return rc;
+  q.a.job[q.n++] = job;
+  if (job.kind == WG_EDGE && job.De >= kWgradExtra) {
+    q.a.job[q.n - 1].db = nullptr;
+    WgradJob attr = job;
+    attr.kind = WG_ATTR;
+    attr.Ka = job.De;
+    attr.dW = job.dW + (size_t)2 * c->m.hidden * c->m.hidden;
+    q.a.job[q.n++] = attr;
   }
-  return fail(XRL_ERR_UNSUPPORTED, "launch_wgrad_embed_rows: bf16 contexts only");
+  return XRL_OK;
 }
 
 RowMlpBwdArgs rowmlp_bwd_args(xrl_ctx *c, const MlpRef &r, bool relu_last, float *const *act, const float *dout,
@@ -1512,12 +1472,13 @@ __global__ void broadcast_dpool_kernel(const float *dx, int ldx, const int32_t *
   store4<T>(dh + (size_t)n * H + f, v);
 }
 
-// The node-update layer's input rows written out for its weight gradient (bf16 path):
+// The node-update layer's input rows written out for its weight gradient:
 // X[n, :] = [sum over node n's in-edges (receiver order: the node-update kernel's order) of their
 // attribute rows | one-hot operator type | dense attributes | zeros up to Kp columns]; one thread per
 // node and eight columns.
+template <typename T>
 __global__ void embed_input_rows_kernel(const float *edge_feat, const int32_t *in_ptr, const int32_t *node_op,
-                                        const float *node_dense, int64_t N, int De, int Tn, int Dd, int Kp, bf16_t *X) {
+                                        const float *node_dense, int64_t N, int De, int Tn, int Dd, int Kp, T *X) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int q = Kp / 8;
   if (i >= N * q) return;
@@ -1549,7 +1510,8 @@ __global__ void embed_input_rows_kernel(const float *edge_feat, const int32_t *i
     if (k >= De && k < De + Tn) v[j] = k - De == op ? 1.f : 0.f;
     else if (k >= De + Tn && k < De + Tn + Dd) v[j] = node_dense[(size_t)n * Dd + (k - De - Tn)];
   }
-  *(bf16x8 *)(X + (size_t)n * Kp + k0) = pack_bf16x8(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]);
+  store4<T>(X + (size_t)n * Kp + k0, v);
+  store4<T>(X + (size_t)n * Kp + k0 + 4, v + 4);
 }
 
 // ---- batches reduced to distinct nodes (distinct.hip.h)
@@ -1805,7 +1767,19 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   // (edge tiles end at receiver boundaries unless a receiver has more than 32 in-edges)
   const bool fold = kept && b->n_split_tiles == 0;
   const bool embed_kept = c->embed_kept, recompute = gat ? !embed_kept : !kept;
-  for (int i = 0; i < (recompute ? 3 : 2); ++i) acc((size_t)M * H * sizeof(T));   // (z1,) dz1, dz2
+  // What the weight gradients of an MLP read -- dz1, dz2 and, where the forward kept none, z1 [rows, H] -- stays
+  // until their launch, which takes as many MLPs as there is room for: all of them up to kGradRoom, else
+  // the largest at least. (2 GiB: 12.5 ms step of 4.3 M nodes, H = 256, three launches; one launch of all would gain 2 x 30 us.)
+  auto unit_bytes = [&](int64_t rows, int n) { return n * align_up((size_t)rows * H * sizeof(T)); };
+  const int per_mlp = recompute ? 3 : 2;
+  size_t room_all = unit_bytes(N0, per_mlp), room_one = room_all;
+  for (int r = 1; r <= R; ++r)
+    for (int64_t rows : {lev(r).N, gat ? 0 : lev(r).E}) {
+      const size_t bytes = unit_bytes(rows, gat ? 1 : per_mlp);
+      room_all += bytes;
+      room_one = std::max(room_one, bytes);
+    }
+  if (gat) acc((size_t)maxN * H * sizeof(T));                      // dpre
   // per-edge d h_sender; d h_receiver: per edge, or summed per receiver (a reduced batch: d h_sender, the
   // classes' own dh and d h_receiver one behind the other, see GroupArgs)
   int64_t max_rows = 0;
@@ -1813,17 +1787,16 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   acc((size_t)(q ? max_rows : maxE) * H * sizeof(T));
   if (!q) acc((size_t)M * H * sizeof(T));
   for (int i = 0; i < 3; ++i) acc((size_t)maxN * H * sizeof(T));   // dh (two buffers), dagg
-  // bf16: the node-update layer's input rows are written out for its weight gradient, Kp columns
+  // the node-update layer's input rows are written out for its weight gradient, Kp columns
   const int Kx = De + m.n_op_types + m.n_node_dense, Kp = (Kx + 7) / 8 * 8;
-  const bool embed_rows = sizeof(T) == 2 && N > 0;
-  if (embed_rows) acc((size_t)N0 * Kp * 2);
-  const size_t part = std::max(std::max(wgrad_partial_floats(M, 2 * H + De, H, c->n_cu), wgrad_partial_floats(M, H, H, c->n_cu)),
-                               small_wgrad_partial_floats(c->L.readout, G));
+  acc((size_t)N0 * Kp * sizeof(T));
+  const size_t part = std::max(wgrad_partial_floats(c), small_wgrad_partial_floats(c->L.readout, G));
   acc(part * 4);
   acc((size_t)G * H * 4); acc((size_t)G * H * 4); acc((size_t)G * (H + Dg) * 4);
   if (gat) {                                                       // softmax weights and score gradients
     for (int i = 0; i < 2; ++i) acc((size_t)maxE * 4);
     for (int i = 0; i < 4; ++i) acc((size_t)maxN * 4);
+    for (int r = 0; r < R; ++r) acc((size_t)kAvecChunks * 2 * H * 4);   // chunk sums of the attention vectors' gradients
   }
   // a reduced batch: fp32 sums per class, their carries, the pool's gradient per graph; and, the first
   // time, the sort that makes the groupings these sums go by (in the same place)
@@ -1836,29 +1809,52 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
     sort_bytes = q->grouped && q->grouped_fold == fold ? 0 : grouping_bytes(b, q, fold);
     need = std::max(need, sort_bytes);
   }
-  int rc = ensure_bws(c, need);
+  size_t room = std::min(room_all, std::max(room_one, c->grad_room));
+  const size_t o_room = align_up(need);
+  int rc = ensure_bws(c, o_room + room);
+  if (rc == XRL_ERR_OOM && room > room_one) rc = ensure_bws(c, o_room + (room = room_one));
   if (rc) return rc;
   if (q && !(q->grouped && q->grouped_fold == fold) && (rc = make_groupings(c, b, q, fold))) return rc;
   Bump bump{c->bws};
-  T *z1 = recompute ? bump.take<T>((size_t)M * H) : nullptr;
-  T *dz1 = bump.take<T>((size_t)M * H), *dz2 = bump.take<T>((size_t)M * H);
+  T *dpre = gat ? bump.take<T>((size_t)maxN * H) : nullptr;
   T *dsrc = bump.take<T>((size_t)(q ? max_rows : maxE) * H), *ddst = q ? nullptr : bump.take<T>((size_t)M * H);
   T *dhA = bump.take<T>((size_t)maxN * H), *dhB = bump.take<T>((size_t)maxN * H);
   T *dagg = bump.take<T>((size_t)maxN * H);
-  bf16_t *xrows = embed_rows ? bump.take<bf16_t>((size_t)N0 * Kp) : nullptr;
+  T *xrows = bump.take<T>((size_t)N0 * Kp);
   float *partial = bump.take<float>(part);
   float *rdz[3] = {bump.take<float>((size_t)G * H), bump.take<float>((size_t)G * H), nullptr};
   float *rdx = bump.take<float>((size_t)G * (H + Dg));
-  float *g_ale = nullptr, *g_due = nullptr, *g_als = nullptr, *g_dus = nullptr, *g_dss = nullptr, *g_dsd = nullptr;
+  float *g_avec = nullptr, *g_ale = nullptr, *g_due = nullptr, *g_als = nullptr, *g_dus = nullptr, *g_dss = nullptr, *g_dsd = nullptr;
   if (gat) {
     g_ale = bump.take<float>((size_t)maxE); g_due = bump.take<float>((size_t)maxE);
     g_als = bump.take<float>((size_t)maxN); g_dus = bump.take<float>((size_t)maxN);
     g_dss = bump.take<float>((size_t)maxN); g_dsd = bump.take<float>((size_t)maxN);
+    g_avec = bump.take<float>((size_t)R * kAvecChunks * 2 * H);
   }
   bump.off = o_reduced;
   float *csum = q ? bump.take<float>((size_t)maxN * H) : nullptr;
   float *ccarry = q ? bump.take<float>((size_t)((std::max(N, max_rows) + 15) / 16) * 2 * H) : nullptr;
   float *dpool_rows = q ? bump.take<float>((size_t)G * H) : nullptr;
+  WgradQueue wq;
+  wq.partial = partial; wq.partial_floats = part;
+  char *const room_base = c->bws + o_room;
+  size_t room_used = 0;
+  // memory for an MLP's gradients; what waits is launched first when there is none left (every one given out
+  // so far is complete then: the next is asked for behind the kernels that fill the last)
+  struct MlpGrads { T *z1 = nullptr, *dz1 = nullptr, *dz2 = nullptr; };
+  auto next_grads = [&](int64_t rows, MlpGrads *m, int n) -> int {
+    const size_t one = unit_bytes(rows, 1);
+    if (room_used + n * one > room) {
+      if (int rc2 = flush_wgrads<T>(c, wq)) return rc2;
+      room_used = 0;
+    }
+    T *p = (T *)(room_base + room_used);
+    room_used += n * one;
+    m->dz1 = p;
+    m->dz2 = n > 1 ? (T *)((char *)p + one) : nullptr;
+    m->z1 = n > 2 ? (T *)((char *)p + 2 * one) : nullptr;
+    return XRL_OK;
+  };
   constexpr int PV = 16 / sizeof(T);
   // the gradients of the rows `vals`, summed per segment (fp32) and stored: masked, as the dz2 of the layer
   // that produced the segments' states, or as their dh
@@ -1872,6 +1868,8 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
     return XRL_OK;
   };
 
+  MlpGrads node_grads, edge_grads;         // of the MLP at hand; node_grads: then of the node-side layer below
+  if (!gat && (rc = next_grads(R > 0 ? lev(R).N : N0, &node_grads, per_mlp))) return rc;
   // ---- global-update layer backward
   float *ract[3] = {c->ro_act[0], c->ro_act[1], nullptr};
   if ((rc = launch_rowmlp_bwd(c, rowmlp_bwd_args(c, c->L.readout, true, ract, d_demb, G, rdz, rdx)))) return rc;
@@ -1888,7 +1886,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
         rdx, H + Dg, nullptr, d.graph_node_ptr, m.readout == XRL_READOUT_MEAN, G, H, dpool_rows);
     const uint16_t *mask = kept ? c->ym_node[R - 1] : nullptr;
     dz2_given = mask != nullptr;
-    if ((rc = contract(float(), dpool_rows, q->mem_graph, q->mem_ptr, q->mem_seg, N, lev(R).N, mask, mask ? dz2 : dhA))) return rc;
+    if ((rc = contract(float(), dpool_rows, q->mem_graph, q->mem_ptr, q->mem_seg, N, lev(R).N, mask, mask ? node_grads.dz2 : dhA))) return rc;
   } else if (N > 0) {
     if (dpool_table)
       broadcast_dpool_kernel<T><<<dim3((unsigned)((G * (H / 4) + 255) / 256)), dim3(256), 0, c->stream>>>(
@@ -1902,37 +1900,32 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   Mlp2BwdArgs a;
   memset(&a, 0, sizeof(a));
   a.De = De; a.Tn = m.n_op_types; a.Dd = m.n_node_dense;
-  a.z1 = z1; a.dz1 = dz1; a.dz2 = dz2;
-  WgradArgs wa;
-  memset(&wa, 0, sizeof(wa));
   // (after a forward of one launch per layer the received sums of nodes without in-edges were never written)
-  a.zero_row = wa.zero_row = c->zero_row;
-  wa.De = De; wa.Tn = m.n_op_types; wa.Dd = m.n_node_dense;
-  wa.partial = partial;
+  a.zero_row = c->zero_row;
   auto set_w = [&](const EncMlp &e) {
     a.W1s = e.W1s; a.W2s = e.W2s; a.W2bt = e.W2bt; a.W1bt = e.W1bt; a.b1 = e.b1; a.b2 = e.b2; a.nslab1 = e.nslab1;
   };
-  auto wgrads = [&](int kind, int64_t rows, int Ka, const MlpRef &r, const void *z1_kept) -> int {
-    wa.n_rows = rows; wa.Ka = Ka; wa.dZ = dz1; wa.A = nullptr;
-    // both layers' weight gradients of this MLP and their reductions
-    Timed t(c, kind == WG_EDGE ? TK_WGRAD_EDGE : (kind == WG_NODE ? TK_WGRAD_NODE : TK_WGRAD_EMBED));
-    int rc2 = launch_wgrad<T>(c, kind, wa, dweights + r.w[0], dweights + r.b[0]);
-    if (rc2) return rc2;
-    wa.Ka = H; wa.dZ = dz2; wa.A = kept ? z1_kept : z1;
-    return launch_wgrad<T>(c, WG_PLAIN, wa, dweights + r.w[1], dweights + r.b[1]);
+  // both layers' weight gradients of an MLP whose gradients have been computed; x: the first layer's input
+  auto wgrads = [&](WgradJob x, const MlpRef &r, const MlpGrads &mg, const void *z1) -> int {
+    x.dZ = mg.dz1; x.dW = dweights + r.w[0]; x.db = dweights + r.b[0];
+    if (int rc2 = queue_wgrad<T>(c, wq, x)) return rc2;
+    WgradJob y = {};
+    y.kind = WG_PLAIN; y.A = z1; y.Ka = H; y.n_rows = x.n_rows;
+    y.dZ = mg.dz2; y.dW = dweights + r.w[1]; y.db = dweights + r.b[1];
+    return queue_wgrad<T>(c, wq, y);
   };
   // gradients through one fused MLP: from what the forward kept, else with its first layer recomputed
   Mlp2BwdzArgs za;
   memset(&za, 0, sizeof(za));
-  za.dz1 = dz1; za.dz2 = dz2;
   auto set_graph = [&](const LevelGraph &g) {
-    a.in_ptr = wa.in_ptr = g.in_ptr; a.in_src = wa.in_src = g.in_src; a.in_dst = wa.in_dst = za.in_dst = g.in_dst;
-    a.edge_feat = wa.edge_feat = g.edge_feat; a.node_op = wa.node_op = g.node_op; a.node_dense = wa.node_dense = g.node_dense;
-    wa.agg_src = za.agg_src = g.agg_src;
+    a.in_ptr = g.in_ptr; a.in_src = g.in_src; a.in_dst = za.in_dst = g.in_dst;
+    a.edge_feat = g.edge_feat; a.node_op = g.node_op; a.node_dense = g.node_dense;
+    za.agg_src = g.agg_src;
     a.agg_src = c->agg_skip ? g.agg_src : nullptr;
     za.tile_ptr = g.tile_ptr; za.n_tiles = g.n_tiles;
   };
-  auto mlp_bwd = [&](int kind, const EncMlp &e, const uint16_t *z1mask, const uint16_t *ymask) -> int {
+  auto mlp_bwd = [&](int kind, const EncMlp &e, const MlpGrads &mg, const uint16_t *z1mask, const uint16_t *ymask) -> int {
+    a.z1 = mg.z1; a.dz1 = za.dz1 = mg.dz1; a.dz2 = za.dz2 = mg.dz2;
     if constexpr (sizeof(T) == 2) {
       if (kept || (embed_kept && kind == KIND_EMBED)) {
         za.n_rows = a.n_rows; za.W2bt = e.W2bt; za.W1bt = e.W1bt; za.dy = a.dy;
@@ -1940,7 +1933,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
         za.dy_index = (dy_by_graph && kind != KIND_EDGE) ? d.node_graph : nullptr;
         dy_by_graph = false;
         const bool given = dz2_given && kind != KIND_EDGE;   // (the gather of the round above left dz2 in place)
-        if (given) za.dy = dz2;
+        if (given) za.dy = mg.dz2;
         if (kind != KIND_EDGE) dz2_given = false;
         return launch_mlp2_bwdz(c, kind, za, fold, given);
       }
@@ -1958,29 +1951,31 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
     ga.a_src = c->d_w + c->L.gat[r].a_src; ga.a_dst = c->d_w + c->L.gat[r].a_dst;
     ga.in_ptr = d.in_ptr; ga.in_src = d.in_src; ga.in_dst = d.in_dst; ga.out_ptr = d.out_ptr; ga.out_pos = d.out_pos;
     ga.alpha_e = g_ale; ga.du_e = g_due; ga.alpha_s = g_als; ga.du_s = g_dus; ga.d_ss = g_dss; ga.d_sd = g_dsd;
-    ga.dpre = dz2; ga.dz = dz1;
+    MlpGrads mg;
+    if ((rc = next_grads(N, &mg, 1))) return rc;
+    ga.dpre = dpre; ga.dz = mg.dz1;
     const int64_t threads = N * (H / PV);
     const dim3 grid_n((unsigned)((threads + 255) / 256));
     gat_bwd_scores_kernel<T, PV><<<grid_n, dim3(256), 0, c->stream>>>(ga, H);
     gat_bwd_dz_kernel<T, PV><<<grid_n, dim3(256), 0, c->stream>>>(ga, H);
-    // d a_src, d a_dst: chunk partials (at most 512 chunks: they share the weight-gradient buffer)
-    int64_t nc = (N + 1023) / 1024;
-    if (nc > 512) nc = 512;
-    const int rpc = (int)((N + nc - 1) / nc);
-    nc = (N + rpc - 1) / rpc;
-    gat_avec_grad_kernel<T, PV><<<dim3((unsigned)nc), dim3(256), (size_t)(256 / (H / PV)) * 2 * H * sizeof(float), c->stream>>>(
-        (const T *)c->agg[r + 1], g_dss, g_dsd, N, rpc, H, partial);
-    wgrad_reduce_kernel<<<dim3((unsigned)((H + 31) / 32)), dim3(256), 0, c->stream>>>(
-        partial, (int)nc, 2, 1, H, dweights + c->L.gat[r].a_src, nullptr);
-    wgrad_reduce_kernel<<<dim3((unsigned)((H + 31) / 32)), dim3(256), 0, c->stream>>>(
-        partial + H, (int)nc, 2, 1, H, dweights + c->L.gat[r].a_dst, nullptr);
-    // dW = h^T dz (no bias row), dh = dz W^T
-    wa.n_rows = N; wa.Ka = H; wa.dZ = dz1; wa.A = c->h[r];
-    if ((rc = launch_wgrad<T>(c, WG_PLAIN, wa, dweights + c->L.gat[r].W, nullptr))) return rc;
+    // d a_src, d a_dst (neighbours in the weight vector): sums of chunks of rows, added up with the weight gradients
+    const int64_t chunks = std::min<int64_t>(kAvecChunks, (N + 63) / 64);
+    const int rpc = (int)((N + chunks - 1) / chunks);
+    WgradJob av = {};
+    av.ny = (int)((N + rpc - 1) / rpc); av.KaP = 2; av.k_rows = 2; av.bias_row = -1; av.n_rows = N;
+    av.partial = g_avec + (size_t)r * kAvecChunks * 2 * H;
+    av.dW = dweights + c->L.gat[r].a_src;
+    gat_avec_grad_kernel<T, PV><<<dim3((unsigned)av.ny), dim3(256), (size_t)(256 / (H / PV)) * 2 * H * sizeof(float), c->stream>>>(
+        (const T *)c->agg[r + 1], g_dss, g_dsd, N, rpc, H, av.partial);
+    if ((rc = queue_wgrad<T>(c, wq, av))) return rc;
+    // dW = h^T dz (no bias), dh = dz W^T
+    WgradJob x = {};
+    x.kind = WG_PLAIN; x.A = c->h[r]; x.Ka = H; x.n_rows = N; x.dZ = mg.dz1; x.dW = dweights + c->L.gat[r].W;
+    if ((rc = queue_wgrad<T>(c, wq, x))) return rc;
     GatArgs gl;
     memset(&gl, 0, sizeof(gl));
     gl.n_rows = N; gl.n_blocks = (N + 127) / 128;
-    gl.h = dz1; gl.Ws = c->gatWt[r]; gl.a_src = ga.a_src; gl.a_dst = ga.a_dst; gl.z = dhB;
+    gl.h = mg.dz1; gl.Ws = c->gatWt[r]; gl.a_src = ga.a_src; gl.a_dst = ga.a_dst; gl.z = dhB;
     const unsigned grid_l = (unsigned)((gl.n_blocks + 7) / 8 * 8);
     switch (H) {
       case 64: gat_linear_kernel<T, 64><<<dim3(grid_l), dim3(256), 0, c->stream>>>(gl); break;
@@ -2000,24 +1995,28 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
     set_w(c->node[r]);
     a.n_rows = N; a.h = h_in; a.agg = c->agg[r + 1]; a.y = c->h[r + 1]; a.dy = dhA;
     a.dx_a = dhB; a.dx_b = dagg;
-    { Timed t(c, TK_BWD_NODE); rc = mlp_bwd(KIND_NODE, c->node[r], kept ? c->zm_node[r] : nullptr, kept ? c->ym_node[r] : nullptr); }
+    { Timed t(c, TK_BWD_NODE); rc = mlp_bwd(KIND_NODE, c->node[r], node_grads, kept ? c->zm_node[r] : nullptr, kept ? c->ym_node[r] : nullptr); }
     if (rc) return rc;
-    wa.h = h_in; wa.agg = c->agg[r + 1];
-    if ((rc = wgrads(WG_NODE, N, 2 * H, c->L.node[r], kept ? c->z1_node[r] : nullptr))) return rc;
+    WgradJob x = {};
+    x.kind = WG_NODE; x.A = h_in; x.agg = c->agg[r + 1]; x.dst = g.agg_src; x.Ka = 2 * H; x.n_rows = N;
+    if ((rc = wgrads(x, c->L.node[r], node_grads, kept ? c->z1_node[r] : node_grads.z1))) return rc;
     // edge MLP of round r+1: upstream = dagg gathered by receiver
     set_w(c->edge[r]);
     a.n_rows = E; a.h = h_in; a.agg = nullptr; a.y = nullptr; a.dy = dagg;
     a.dx_a = dsrc; a.dx_b = ddst;
-    { Timed t(c, TK_BWD_EDGE); rc = mlp_bwd(KIND_EDGE, c->edge[r], kept ? c->zm_edge[r] : nullptr, kept ? c->ym_edge[r] : nullptr); }
+    if ((rc = next_grads(E, &edge_grads, per_mlp))) return rc;
+    { Timed t(c, TK_BWD_EDGE); rc = mlp_bwd(KIND_EDGE, c->edge[r], edge_grads, kept ? c->zm_edge[r] : nullptr, kept ? c->ym_edge[r] : nullptr); }
     if (rc) return rc;
-    if ((rc = wgrads(WG_EDGE, E, 2 * H + De, c->L.edge[r], kept ? c->z1_edge[r] : nullptr))) return rc;
+    x.kind = WG_EDGE; x.agg = nullptr; x.src = g.in_src; x.dst = g.in_dst; x.edge_feat = g.edge_feat; x.De = De; x.n_rows = E;
+    if ((rc = wgrads(x, c->L.edge[r], edge_grads, kept ? c->z1_edge[r] : edge_grads.z1))) return rc;
+    if ((rc = next_grads(lev(r).N, &node_grads, per_mlp))) return rc;
     // dh[r] = d(node MLP)/dh + sum over in-edges of d h_receiver + sum over out-edges of d h_sender
     const uint16_t *below = kept ? (r > 0 ? c->ym_node[r - 1] : c->ym_embed) : nullptr;
     Timed timed(c, TK_GRAD_GATHER);
     if (q) {
       // ... of all the classes that split one of the level below, masked as below
       dz2_given = below != nullptr;
-      if ((rc = contract(T(), dsrc, g.down, g.down_ptr, g.down_seg, level_rows(g, fold), lev(r).N, below, below ? dz2 : dhA))) return rc;
+      if ((rc = contract(T(), dsrc, g.down, g.down_ptr, g.down_seg, level_rows(g, fold), lev(r).N, below, below ? node_grads.dz2 : dhA))) return rc;
       continue;
     }
     if (E > 0) {
@@ -2028,7 +2027,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
       T *masked_out = nullptr;
       const uint16_t *mask = nullptr;
       if constexpr (sizeof(T) == 2) {
-        if (kept) { masked_out = dz2; mask = below; }
+        if (kept) { masked_out = node_grads.dz2; mask = below; }
       }
       node_grad_gather_kernel<T, PV><<<dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, c->stream>>>(
           ddst, dsrc, g.in_ptr, g.out_ptr, g.out_pos, N, H, dhB, fold ? 1 : 0, masked_out, mask);
@@ -2041,22 +2040,17 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   set_graph(g0);
   set_w(c->embed);
   a.n_rows = N0; a.h = nullptr; a.agg = nullptr; a.y = c->h[0]; a.dy = dhA; a.dx_a = nullptr; a.dx_b = nullptr;
-  { Timed t(c, TK_BWD_EMBED); rc = mlp_bwd(KIND_EMBED, c->embed, embed_kept ? c->zm_embed : nullptr, embed_kept ? c->ym_embed : nullptr); }
+  if (gat && (rc = next_grads(N0, &node_grads, per_mlp))) return rc;
+  { Timed t(c, TK_BWD_EMBED); rc = mlp_bwd(KIND_EMBED, c->embed, node_grads, embed_kept ? c->zm_embed : nullptr, embed_kept ? c->ym_embed : nullptr); }
   if (rc) return rc;
-  if constexpr (sizeof(T) == 2) {
-    // first layer: dW1 = X^T dz1 on the transpose-read kernel, X written out once; its Kx real rows
-    // and the bias row (row Kp of the slices' partial tiles) are reduced separately
-    Timed t(c, TK_WGRAD_EMBED);
-    const int64_t threads = N0 * (Kp / 8);
-    embed_input_rows_kernel<<<dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, c->stream>>>(
+  // first layer: dW1 = X^T dz1, X written out once, its Kx real columns padded to Kp
+  if (N0 > 0)
+    embed_input_rows_kernel<T><<<dim3((unsigned)((N0 * (Kp / 8) + 255) / 256)), dim3(256), 0, c->stream>>>(
         g0.edge_feat, g0.in_ptr, g0.node_op, g0.node_dense, N0, De, m.n_op_types, m.n_node_dense, Kp, xrows);
-    wa.n_rows = N0; wa.Ka = Kp; wa.dZ = dz1; wa.A = xrows;
-    if ((rc = launch_wgrad_embed_rows<T>(c, wa, Kx, dweights + c->L.embed.w[0], dweights + c->L.embed.b[0]))) return rc;
-    wa.Ka = H; wa.dZ = dz2; wa.A = embed_kept ? c->z1_embed : z1;
-    if ((rc = launch_wgrad<T>(c, WG_PLAIN, wa, dweights + c->L.embed.w[1], dweights + c->L.embed.b[1]))) return rc;
-  } else {
-    if ((rc = wgrads(WG_EMBED, N0, Kx, c->L.embed, nullptr))) return rc;
-  }
+  WgradJob x = {};
+  x.kind = WG_PLAIN; x.A = xrows; x.Ka = Kp; x.k_rows = Kx; x.n_rows = N0;
+  if ((rc = wgrads(x, c->L.embed, node_grads, embed_kept ? c->z1_embed : node_grads.z1))) return rc;
+  if ((rc = flush_wgrads<T>(c, wq))) return rc;
   HIP_TRY(hipGetLastError());
   return XRL_OK;
 }
@@ -2419,9 +2413,8 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   // (H = 64: 17.5 k 73 / 59, 73 k 105 / 113); H = 256: 17.5 k 194 / 215
   c->p_min_rows_forward = model->hidden <= 128 ? 4 * kPersistentMinRows : kPersistentMinRows;
   if (const char *e = getenv("XRL_PERSISTENT_MIN_ROWS")) c->p_min_rows = c->p_min_rows_forward = atoll(e);
-  // (measured: at H = 256 the 256-column tiles win from about 300 k rows on, at H = 128 from 1 M)
-  c->wide_min_rows = model->hidden >= 256 ? (1 << 18) : (1 << 20);
   if (const char *e = getenv("XRL_WGRAD_WIDE_MIN_ROWS")) c->wide_min_rows = atoll(e);
+  if (const char *e = getenv("XRL_GRAD_ROOM")) c->grad_room = (size_t)std::max<long long>(0, atoll(e));
   // Largest batches of the one-launch encoders (0 graphs = never). A forward-only encode takes them up to a
   // limit that the variable of that form states, and by default never: since a tile of the
   // launch-per-layer path is split over H / 32 waves that path is the faster one at every size they
@@ -2449,20 +2442,26 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   // the weights, followed by 1 KB of zeros (16-byte aligned) that kernels read in place of absent rows
   const size_t w_bytes = align_up(sizeof(float) * L.total);
   // zero row, heads' counters, the one-launch encoder's counters
-  const size_t tail_bytes = 1024 + sizeof(int32_t) * kMaxFusedSlots + sizeof(unsigned) * kClusterMaxGraphs + sizeof(int32_t) * kCounts;
+  const size_t tail_bytes = kZeroRow + sizeof(int32_t) * kMaxFusedSlots + sizeof(unsigned) * kClusterMaxGraphs + sizeof(int32_t) * kCounts;
   e = hipMalloc((void **)&c->d_w, w_bytes + tail_bytes);
   if (e != hipSuccess) {
     xrl_destroy(c);
     return fail(XRL_ERR_OOM, "device weights: %s", hipGetErrorString(e));
   }
   c->zero_row = (char *)c->d_w + w_bytes;
-  c->d_counter = (int32_t *)((char *)c->zero_row + 1024);
+  c->d_counter = (int32_t *)((char *)c->zero_row + kZeroRow);
   c->d_arrived = (unsigned *)(c->d_counter + kMaxFusedSlots);
   c->d_counts = (int32_t *)(c->d_arrived + kClusterMaxGraphs);
   e = hipMemset(c->zero_row, 0, tail_bytes);
   if (e != hipSuccess) {
     xrl_destroy(c);
     return fail(XRL_ERR_HIP, "hipMemset: %s", hipGetErrorString(e));
+  }
+  const uint32_t one = c->elem == 2 ? 0x3f80u : 0x3f800000u;       // 1 in the operand type, zeros behind it
+  e = hipMemcpy((char *)c->zero_row + 1024, &one, sizeof(one), hipMemcpyHostToDevice);
+  if (e != hipSuccess) {
+    xrl_destroy(c);
+    return fail(XRL_ERR_HIP, "hipMemcpy: %s", hipGetErrorString(e));
   }
   e = hipHostMalloc((void **)&c->h_counts, sizeof(int32_t) * kCounts, hipHostMallocDefault);
   if (e == hipSuccess) e = hipHostMalloc((void **)&c->h_fault, sizeof(unsigned), hipHostMallocMapped);
@@ -2996,22 +2995,22 @@ int xrl_weight_gradient(xrl_ctx *c, const xrl_batch *b, int32_t kind, const void
   if (n_rows == 0) return XRL_OK;
   if (!d_x || !d_dZ || !d_dW || !d_db || (kind == XRL_WG_NODE && !d_x2))
     return fail(XRL_ERR_NULL, "xrl_weight_gradient: NULL device pointer");
-  const int Ka = kind == XRL_WG_PLAIN ? H : (kind == XRL_WG_EDGE ? 2 * H + De : 2 * H);
-  const size_t part = wgrad_partial_floats(n_rows, Ka, H, c->n_cu);
+  const size_t part = wgrad_partial_floats(c);
   if ((rc = ensure_bws(c, align_up(part * 4)))) return rc;
-  WgradArgs wa;
-  memset(&wa, 0, sizeof(wa));
   const xrl_batch_device &d = b->dev;
-  wa.in_ptr = d.in_ptr; wa.in_src = d.in_src; wa.in_dst = d.in_dst; wa.edge_feat = d.edge_feat;
-  wa.agg_src = d.agg_src; wa.zero_row = c->zero_row;
-  wa.node_op = d.node_op; wa.node_dense = d.node_dense; wa.De = De; wa.Tn = c->m.n_op_types; wa.Dd = c->m.n_node_dense;
-  wa.partial = (float *)c->bws;
-  wa.n_rows = n_rows; wa.Ka = Ka; wa.dZ = d_dZ;
-  if (kind == XRL_WG_PLAIN) wa.A = d_x;
-  else { wa.h = d_x; wa.agg = d_x2; }
-  const int wk = kind == XRL_WG_PLAIN ? WG_PLAIN : (kind == XRL_WG_EDGE ? WG_EDGE : WG_NODE);
-  Timed t(c, TK_WGRAD);
-  return c->elem == 2 ? launch_wgrad<bf16_t>(c, wk, wa, d_dW, d_db) : launch_wgrad<float>(c, wk, wa, d_dW, d_db);
+  WgradQueue q;
+  q.partial = (float *)c->bws; q.partial_floats = part;
+  WgradJob j = {};
+  j.kind = kind == XRL_WG_PLAIN ? WG_PLAIN : (kind == XRL_WG_EDGE ? WG_EDGE : WG_NODE);
+  j.A = d_x; j.agg = d_x2; j.Ka = kind == XRL_WG_PLAIN ? H : 2 * H; j.n_rows = n_rows;
+  j.src = d.in_src; j.dst = kind == XRL_WG_EDGE ? d.in_dst : d.agg_src; j.edge_feat = d.edge_feat; j.De = De;
+  j.dZ = d_dZ; j.dW = d_dW; j.db = d_db;
+  auto run = [&](auto tag) -> int {
+    using T = decltype(tag);
+    const int rc2 = queue_wgrad<T>(c, q, j);
+    return rc2 ? rc2 : flush_wgrads<T>(c, q);
+  };
+  return c->elem == 2 ? run(bf16_t()) : run(float());
 }
 
 int xrl_mlp_backward(xrl_ctx *c, const xrl_batch *b, int32_t kind, int32_t round, const void *d_h,
