@@ -24,7 +24,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
-#include "mma.hip.h"
+#include "segsum.hip.h"
 
 constexpr int kMaxLevels = 16;            // levels 0 .. rounds
 constexpr unsigned long long kEmptySlot = ~0ull;
@@ -425,29 +425,139 @@ __global__ __launch_bounds__(256) void expand_states_kernel(const f32x4 *in, con
   out[i] = in[(size_t)from[c] * pieces + (i - c * pieces)];
 }
 
-// The sum of a level's gradients per class of the level below (fp32), stored in the operand type; with
-// ymask (bf16) multiplied by the ReLU mask of the layer that produced those states, as
-// node_grad_gather_kernel does. One thread per eight columns.
-template <typename T>
-__global__ __launch_bounds__(256) void store_summed_kernel(const float *sum, int64_t n_rows, int D, const uint16_t *ymask, T *out) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n_rows * (D / 8)) return;
-  const int64_t n = i / (D / 8);
-  const int c = (int)(i - n * (D / 8)) * 8;
-  const f32x4 *p = (const f32x4 *)(sum + (size_t)n * D + c);
-  const f32x4 lo4 = p[0], hi4 = p[1];
-  float v[8];
+// Sums of rows per class in fp32 and, rounded once, their store in the operand type; with ymask (bf16) multiplied
+// by the ReLU mask of the layer that produced the classes' states (see node_grad_gather_kernel). The
+// rows are listed class by class (perm, -1 = a row of zeros; seg the class of each place; every class has
+// one), and H / VEC lanes take sixteen places: all indices, then all rows and the mask words of the classes
+// that end here, are requested at once, so a group waits twice whatever classes it holds. A class
+// that lies inside is stored at once; the pieces of others go to carry[places / 16][begun before, goes on].
+// Bound by the gather of the rows. H = 256, 3.4 M rows of 512 bytes into 400 k classes: 423 us (4.6 TB/s) and 99 for
+// the classes in several pieces; a walk that read a segment's end when it reached it, an fp32 array of
+// the sums and a pass that masked it took 815 + 90 + 108. The pool's gradient, 4.3 M rows of a 4.7 MB table:
+// 379 + 123 us, 609 + 124 + 216 before.
+constexpr int kSumRows = 16;
+struct ClassSumArgs {
+  const void *vals, *zero_row;
+  const int32_t *perm, *seg, *ptr;   // [n_rows] (readable up to the next multiple of sixteen), [classes + 1]
+  int64_t n_rows;
+  int D;
+  const uint16_t *ymask;
+  void *out;                         // [classes, D]
+  float *carry;                      // [n_rows / 16, rounded up][2][D]
+};
+// the mask bits of columns c .. c + 3 of row n (c a multiple of 4), lowest first
+__device__ __forceinline__ unsigned mask_word(const uint16_t *ymask, int64_t n, int D, int c) {
+  return ymask[((size_t)(n / 32) * (D / 32) + c / 32) * 64 + (size_t)(n % 32) + 8 * (c & 4)];
+}
+template <typename TOut>
+__device__ __forceinline__ void store_masked4(TOut *p, float *v, bool masked, unsigned word, int c) {
+  const unsigned bits = masked ? word >> (4 * (c % 32 / 8)) : 0xfu;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) { v[j] = lo4[j]; v[4 + j] = hi4[j]; }
-  if (ymask) {
-    const size_t w = ((size_t)(n / 32) * (D / 32) + c / 32) * 64 + (size_t)(n % 32);
-    const unsigned lo = ymask[w] >> (4 * (c % 32 / 8)), hi = ymask[w + 32] >> (4 * (c % 32 / 8));
+  for (int j = 0; j < 4; ++j) v[j] = (bits >> j) & 1u ? v[j] : 0.f;
+  store4<TOut>(p, v);
+}
+template <typename TIn, typename TOut, int VEC>
+__global__ __launch_bounds__(256) void class_sum_kernel(const ClassSumArgs a) {
+  constexpr int NR = kSumRows, NQ = VEC / 4;
+  typedef int i32x4 __attribute__((ext_vector_type(4)));
+  const int lpr = a.D / VEC;
+  const int64_t gt = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t st = gt / lpr, r0 = st * NR;
+  if (r0 >= a.n_rows) return;
+  const int c = (int)(gt - st * lpr) * VEC;
+  const int nv = a.n_rows - r0 < NR ? (int)(a.n_rows - r0) : NR;
+  i32x4 row4[NR / 4], seg4[NR / 4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      v[j] = (lo >> j) & 1u ? v[j] : 0.f;
-      v[4 + j] = (hi >> j) & 1u ? v[4 + j] : 0.f;
+  for (int i = 0; i < NR / 4; ++i) {
+    row4[i] = ((const i32x4 *)(a.perm + r0))[i];
+    seg4[i] = ((const i32x4 *)(a.seg + r0))[i];
+  }
+  const int before = r0 > 0 ? a.seg[r0 - 1] : -1, after = r0 + NR < a.n_rows ? a.seg[r0 + NR] : -1;
+  float v[NR][VEC];
+  int seg[NR];
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    const int r = i < nv ? row4[i / 4][i % 4] : -1;        // (places past the last: zeros of the last one's class)
+    seg[i] = i < nv ? seg4[i / 4][i % 4] : seg[i - 1 > 0 ? i - 1 : 0];
+    RowVec<TIn, VEC>::load((r < 0 ? (const TIn *)a.zero_row : (const TIn *)a.vals + (size_t)r * a.D) + c, v[i]);
+  }
+  unsigned word[NR][NQ];
+  const bool masked = a.ymask != nullptr;
+#pragma unroll
+  for (int i = 0; i < NR; ++i)
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) word[i][q] = 0;
+  if (masked) {
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+      if (i == NR - 1 || seg[i + 1 < NR ? i + 1 : i] != seg[i]) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) word[i][q] = mask_word(a.ymask, seg[i], a.D, c + 4 * q);
+      }
+  }
+  float acc[VEC];
+#pragma unroll
+  for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
+  bool begun = seg[0] == before;
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) acc[j] += v[i][j];
+    if (i == NR - 1 || seg[i + 1 < NR ? i + 1 : i] != seg[i]) {
+      if (begun || (i == NR - 1 && after == seg[i])) {
+        float *p = a.carry + ((size_t)st * 2 + (begun ? 0 : 1)) * a.D + c;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) store4<float>(p + 4 * q, acc + 4 * q);
+      } else {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) store_masked4<TOut>((TOut *)a.out + (size_t)seg[i] * a.D + c + 4 * q, acc + 4 * q, masked, word[i][q], c + 4 * q);
+      }
+      begun = false;
+#pragma unroll
+      for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
     }
   }
-  store4<T>(out + (size_t)n * D + c, v);
-  store4<T>(out + (size_t)n * D + c + 4, v + 4);
+}
+// The classes in several pieces. A wave looks at kCarryGroups groups of sixteen places, one per lane, and for those
+// whose last class begins there and goes on adds up its pieces, one class after the other (of 64 groups: 70 us
+// however small the level): D / 4 lanes a piece, the wave's
+// 256 / D lane groups every 256 / D-th of them, eight in flight each, added in group order.
+constexpr int kCarryGroups = 4;
+template <typename TOut>
+__global__ __launch_bounds__(256) void class_sum_carried_kernel(const ClassSumArgs a) {
+  constexpr int NR = kSumRows;
+  const int lane = threadIdx.x & 63;
+  const int64_t st0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kCarryGroups, mine = st0 + lane;
+  int seg = -1;
+  bool starts = false;
+  if (lane < kCarryGroups && (mine + 1) * NR < a.n_rows) {
+    seg = a.seg[mine * NR + NR - 1];
+    starts = a.seg[(mine + 1) * NR] == seg && a.ptr[seg] >= mine * NR;
+  }
+  const int lpr = a.D / 4, parts = 64 / lpr, c = (lane % lpr) * 4, part = lane / lpr;
+  for (unsigned long long todo = __ballot(starts); todo; todo &= todo - 1) {
+    const int l = __builtin_ctzll(todo);
+    const int s = __shfl(seg, l);
+    const int64_t st = st0 + l, end = a.ptr[s + 1], n = (end + NR - 1) / NR - st;   // its pieces: this group's last, then first ones
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    for (int64_t t = part; t < n; t += 8 * parts) {
+      f32x4 v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int64_t ti = t + i * parts < n ? t + i * parts : t;
+        v[i] = *(const f32x4 *)(a.carry + ((size_t)(st + ti) * 2 + (ti == 0 ? 1 : 0)) * a.D + c);
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (t + i * parts < n) sum += v[i];
+    }
+    float y[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      y[j] = sum[j];
+      for (int p = 1; p < parts; ++p) y[j] += __shfl(sum[j], (lane + p * lpr) & 63);
+    }
+    if (part == 0)
+      store_masked4<TOut>((TOut *)a.out + (size_t)s * a.D + c, y, a.ymask != nullptr, a.ymask ? mask_word(a.ymask, s, a.D, c) : 0u, c);
+  }
 }

@@ -1,8 +1,7 @@
 // Deterministic segment sum over consecutive rows: out[s, :] = sum of rows [ptr[s], ptr[s+1]).
 // Used for the receiver-side sum of incoming edge attributes (node-update layer, Section 3.4),
-// the per-graph sum of node states (global-update layer), and the gradients of a reduced batch per class
-// (distinct.hip.h); the backward pass of a batch that is not reduced gathers per node instead
-// (node_grad_gather_kernel at the end of this file).
+// and the per-graph sum of node states (global-update layer); the backward pass gathers per node instead
+// (node_grad_gather_kernel at the end of this file), or sums per class (distinct.hip.h).
 //
 // Rows are cut into fixed sub-tiles of RT rows; D / VEC lanes own one sub-tile, each lane a
 // 16-byte column slice. A lane walks its sub-tile in row order, so every sum has a fixed order
@@ -60,7 +59,6 @@ struct SegsumArgs {
   const void *zero_row; // D zeros of type TIn (with perm)
   const int32_t *ptr;   // [n_seg + 1]
   const int32_t *row_seg;  // nullable: segment of vals row i (saves the search for a sub-tile's first segment)
-  const int32_t *pos_seg;  // nullable: segment of row r of the reduction
   int64_t n_rows, n_seg;
   int D, RT;
   void *out;            // [n_seg, D], type TOut
@@ -86,7 +84,7 @@ __global__ __launch_bounds__(256) void segsum_kernel(const SegsumArgs a) {
       RowVec<TIn, VEC>::load((r < 0 ? (const TIn *)a.zero_row : vals + (size_t)r * a.D) + c, v[i]);
     }
   }
-  int seg = a.pos_seg ? a.pos_seg[r0] : a.row_seg ? a.row_seg[a.perm ? (int64_t)a.perm[r0] : r0] : seg_of_row(a.ptr, a.n_seg, r0);
+  int seg = a.row_seg ? a.row_seg[a.perm ? (int64_t)a.perm[r0] : r0] : seg_of_row(a.ptr, a.n_seg, r0);
   if (Put::kZeroEmpty && st == 0)                               // empty segments before row 0
     for (int s = 0; s < seg; ++s)
 #pragma unroll

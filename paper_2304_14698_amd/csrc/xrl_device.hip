@@ -864,7 +864,7 @@ int check_batch(xrl_ctx *c, const xrl_batch *b, const char *who) {
 template <typename TIn, typename TOut, int VEC, int RT>
 int launch_segsum_rt(xrl_ctx *c, const void *vals, const int32_t *perm, const int32_t *ptr,
                      const int32_t *row_seg, int64_t n_rows, int64_t n_seg, int D, void *out,
-                     float *carry, const int32_t *pos_seg = nullptr) {
+                     float *carry) {
   if (n_seg == 0) return XRL_OK;
   if (n_rows == 0) {
     static_assert(sizeof(TOut) == 4, "zero fill below writes fp32 words");
@@ -877,7 +877,6 @@ int launch_segsum_rt(xrl_ctx *c, const void *vals, const int32_t *perm, const in
   a.vals = vals; a.perm = perm; a.ptr = ptr; a.n_rows = n_rows; a.n_seg = n_seg;
   a.zero_row = c->zero_row;
   a.row_seg = perm ? nullptr : row_seg;
-  a.pos_seg = pos_seg;
   a.D = D; a.RT = RT; a.out = out; a.carry = carry;
   const int64_t nsub = (n_rows + RT - 1) / RT;
   const int64_t threads = nsub * (D / VEC);
@@ -1707,9 +1706,9 @@ int find_distinct(xrl_ctx *c, xrl_batch *b) {
     tl.chunk0[l] = chunks;
     o[l].src = plan(e * 4); o[l].dst = plan(e * 4); o[l].self = plan(n * 4);
     o[l].tile = plan((e / 16 + 2 * nc + 4) * 4);
-    o[l].dptr = plan((q->lv[l - 1].N + 1) * 4); o[l].down = plan((e + n + std::max(e, n)) * 4); o[l].dseg = plan((e + n + std::max(e, n)) * 4);   // (level_rows)
+    o[l].dptr = plan((q->lv[l - 1].N + 1) * 4); o[l].down = plan((e + n + std::max(e, n) + kSumRows) * 4); o[l].dseg = plan((e + n + std::max(e, n) + kSumRows) * 4);   // (level_rows)
   }
-  const size_t o_mptr = plan((q->lv[R].N + 1) * 4), o_mgraph = plan(N * 4), o_mseg = plan(N * 4);
+  const size_t o_mptr = plan((q->lv[R].N + 1) * 4), o_mgraph = plan((N + kSumRows) * 4), o_mseg = plan((N + kSumRows) * 4);
   const size_t o_cuts = plan((size_t)chunks * kTileChunkMax * 4), o_count = plan((size_t)(chunks + 1) * 4);
   char *blk = take(1, off);
   if (!blk) { drop(); return XRL_OK; }
@@ -1798,13 +1797,12 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
     for (int i = 0; i < 4; ++i) acc((size_t)maxN * 4);
     for (int r = 0; r < R; ++r) acc((size_t)kAvecChunks * 2 * H * 4);   // chunk sums of the attention vectors' gradients
   }
-  // a reduced batch: fp32 sums per class, their carries, the pool's gradient per graph; and, the first
+  // a reduced batch: the pieces of sums per class, the pool's gradient per graph; and, the first
   // time, the sort that makes the groupings these sums go by (in the same place)
   size_t sort_bytes = 0;
   const size_t o_reduced = need;
   if (q) {
-    acc((size_t)maxN * H * 4);
-    acc((size_t)((std::max(N, max_rows) + 15) / 16) * 2 * H * 4);
+    acc((size_t)((std::max(N, max_rows) + kSumRows - 1) / kSumRows) * 2 * H * 4);
     acc((size_t)G * H * 4);
     sort_bytes = q->grouped && q->grouped_fold == fold ? 0 : grouping_bytes(b, q, fold);
     need = std::max(need, sort_bytes);
@@ -1832,8 +1830,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
     g_avec = bump.take<float>((size_t)R * kAvecChunks * 2 * H);
   }
   bump.off = o_reduced;
-  float *csum = q ? bump.take<float>((size_t)maxN * H) : nullptr;
-  float *ccarry = q ? bump.take<float>((size_t)((std::max(N, max_rows) + 15) / 16) * 2 * H) : nullptr;
+  float *ccarry = q ? bump.take<float>((size_t)((std::max(N, max_rows) + kSumRows - 1) / kSumRows) * 2 * H) : nullptr;
   float *dpool_rows = q ? bump.take<float>((size_t)G * H) : nullptr;
   WgradQueue wq;
   wq.partial = partial; wq.partial_floats = part;
@@ -1856,14 +1853,18 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
     return XRL_OK;
   };
   constexpr int PV = 16 / sizeof(T);
-  // the gradients of the rows `vals`, summed per segment (fp32) and stored: masked, as the dz2 of the layer
-  // that produced the segments' states, or as their dh
+  // the gradients of the rows `vals`, summed per class (fp32) and stored: masked, as the dz2 of the layer
+  // that produced the classes' states, or as their dh
   auto contract = [&](auto tag, const void *vals, const int32_t *perm, const int32_t *ptr, const int32_t *seg, int64_t rows,
-                      int64_t n_seg, const uint16_t *ymask, T *out) -> int {
+                      const uint16_t *ymask, T *out) -> int {
     using TIn = decltype(tag);
-    const int rc2 = launch_segsum_rt<TIn, float, 16 / sizeof(TIn), 16>(c, vals, perm, ptr, seg, rows, n_seg, H, csum, ccarry, seg);
-    if (rc2) return rc2;
-    store_summed_kernel<T><<<dim3((unsigned)((n_seg * (H / 8) + 255) / 256)), dim3(256), 0, c->stream>>>(csum, n_seg, H, ymask, out);
+    constexpr int VEC = 16 / sizeof(TIn);
+    ClassSumArgs s;
+    s.vals = vals; s.zero_row = c->zero_row; s.perm = perm; s.seg = seg; s.ptr = ptr; s.n_rows = rows; s.D = H;
+    s.ymask = ymask; s.out = out; s.carry = ccarry;
+    const int64_t groups = (rows + kSumRows - 1) / kSumRows;
+    class_sum_kernel<TIn, T, VEC><<<dim3((unsigned)((groups * (H / VEC) + 255) / 256)), dim3(256), 0, c->stream>>>(s);
+    class_sum_carried_kernel<T><<<dim3((unsigned)((groups + 4 * kCarryGroups - 1) / (4 * kCarryGroups))), dim3(256), 0, c->stream>>>(s);
     HIP_TRY(hipGetLastError());
     return XRL_OK;
   };
@@ -1886,7 +1887,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
         rdx, H + Dg, nullptr, d.graph_node_ptr, m.readout == XRL_READOUT_MEAN, G, H, dpool_rows);
     const uint16_t *mask = kept ? c->ym_node[R - 1] : nullptr;
     dz2_given = mask != nullptr;
-    if ((rc = contract(float(), dpool_rows, q->mem_graph, q->mem_ptr, q->mem_seg, N, lev(R).N, mask, mask ? node_grads.dz2 : dhA))) return rc;
+    if ((rc = contract(float(), dpool_rows, q->mem_graph, q->mem_ptr, q->mem_seg, N, mask, mask ? node_grads.dz2 : dhA))) return rc;
   } else if (N > 0) {
     if (dpool_table)
       broadcast_dpool_kernel<T><<<dim3((unsigned)((G * (H / 4) + 255) / 256)), dim3(256), 0, c->stream>>>(
@@ -2016,7 +2017,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
     if (q) {
       // ... of all the classes that split one of the level below, masked as below
       dz2_given = below != nullptr;
-      if ((rc = contract(T(), dsrc, g.down, g.down_ptr, g.down_seg, level_rows(g, fold), lev(r).N, below, below ? node_grads.dz2 : dhA))) return rc;
+      if ((rc = contract(T(), dsrc, g.down, g.down_ptr, g.down_seg, level_rows(g, fold), below, below ? node_grads.dz2 : dhA))) return rc;
       continue;
     }
     if (E > 0) {
