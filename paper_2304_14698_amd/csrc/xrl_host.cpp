@@ -258,10 +258,6 @@ bool plan_block(xrl_batch *b, int64_t Nc = 0, int64_t Ec = 0, int64_t n_an = 0, 
   b->o_graph_node_ptr = p.take((G + 1) * 4);
   b->o_in_ptr = p.take((N + 1) * 4);
   b->o_in_src = p.take(E * 4);
-  b->o_in_dst = p.take(E * 4);
-  b->o_out_ptr = p.take((N + 1) * 4);
-  b->o_out_pos = p.take(E * 4);
-  b->o_node_graph = p.take(N * 4);
   b->o_graph_global = p.take(G * Dg * 4);
   b->o_mask = p.take(G);
   if (ed) {
@@ -458,14 +454,13 @@ int xrl_pack_state(const xrl_model_desc *model, const xrl_state_desc *st, xrl_ba
     b->model = *model;
     b->S = S; b->G = G; b->N = N; b->E = E;
     if (!plan_block(b)) throw std::bad_alloc();
-    int32_t *gnp = b->at<int32_t>(b->o_graph_node_ptr), *in_ptr = b->at<int32_t>(b->o_in_ptr), *out_ptr = b->at<int32_t>(b->o_out_ptr);
-    int32_t *node_op = b->at<int32_t>(b->o_node_op), *node_graph = b->at<int32_t>(b->o_node_graph);
-    int32_t *in_src = b->at<int32_t>(b->o_in_src), *in_dst = b->at<int32_t>(b->o_in_dst), *in_eid = b->at<int32_t>(b->o_in_eid);
-    int32_t *out_pos = b->at<int32_t>(b->o_out_pos);
+    int32_t *gnp = b->at<int32_t>(b->o_graph_node_ptr), *in_ptr = b->at<int32_t>(b->o_in_ptr);
+    int32_t *node_op = b->at<int32_t>(b->o_node_op);
+    int32_t *in_src = b->at<int32_t>(b->o_in_src), *in_eid = b->at<int32_t>(b->o_in_eid);
     float *node_dense = b->at<float>(b->o_node_dense), *edge_feat = b->at<float>(b->o_edge_feat);
     memcpy(b->at<int32_t>(b->o_state_graph_ptr), st->state_graph_ptr, sizeof(int32_t) * (S + 1));
     memcpy(gnp, st->graph_node_ptr, sizeof(int32_t) * (G + 1));
-    in_ptr[0] = out_ptr[0] = 0;
+    in_ptr[0] = 0;
     const int T = pack_thread_count(N + E);
     const std::vector<int64_t> cut = graph_ranges(st, G, T);
     std::vector<PackIssue> issue((size_t)4 * T);
@@ -497,34 +492,27 @@ int xrl_pack_state(const xrl_model_desc *model, const xrl_state_desc *st, xrl_ba
         memcpy(node_op + n0, st->node_op + n0, sizeof(int32_t) * (n1 - n0));
         if (Dd > 0) memcpy(node_dense + n0 * Dd, st->node_dense + n0 * Dd, sizeof(float) * (n1 - n0) * Dd);
         memset(in_ptr + n0 + 1, 0, sizeof(int32_t) * (n1 - n0));
-        memset(out_ptr + n0 + 1, 0, sizeof(int32_t) * (n1 - n0));
       }
-      // Receiver order: stable counting sort of each graph's edges by receiver; then the sender-side
-      // index (receiver-order positions grouped by sender, ascending position). A graph's edges
-      // keep the index range they came with, so the graph ranges are independent.
+      // Receiver order: stable counting sort of each graph's edges by receiver. A graph's edges keep the index
+      // range they came with, so the graph ranges are independent.
       std::vector<int32_t> cur;
       for (int64_t g = g0; g < g1; ++g) {
         const int32_t base = st->graph_node_ptr[g], n = st->graph_node_ptr[g + 1] - base;
         const int64_t a = st->graph_edge_ptr[g], z = st->graph_edge_ptr[g + 1];
-        for (int32_t i = 0; i < n; ++i) node_graph[base + i] = (int32_t)g;
-        int32_t *inp = in_ptr + base + 1, *outp = out_ptr + base + 1;   // counts, then ends
-        for (int64_t e = a; e < z; ++e) {
-          inp[st->edge_dst[e]]++;
-          outp[st->edge_src[e]]++;
-        }
-        if (cur.size() < (size_t)2 * n) cur.resize((size_t)2 * n);
-        int32_t ri = (int32_t)a, ro = (int32_t)a;
+        int32_t *inp = in_ptr + base + 1;                 // counts, then ends
+        for (int64_t e = a; e < z; ++e) inp[st->edge_dst[e]]++;
+        if (cur.size() < (size_t)n) cur.resize((size_t)n);
+        int32_t ri = (int32_t)a;
         for (int32_t i = 0; i < n; ++i) {
-          cur[i] = ri; cur[n + i] = ro;                   // first position of node i's in- / out-edges
-          ri += inp[i]; ro += outp[i];
-          inp[i] = ri; outp[i] = ro;
+          cur[i] = ri;                                    // first position of node i's in-edges
+          ri += inp[i];
+          inp[i] = ri;
         }
         auto place = [&](auto width) {
           constexpr size_t kRow = sizeof(float) * decltype(width)::value;      // 0: any width
           for (int64_t e = a; e < z; ++e) {
             const int32_t p = cur[st->edge_dst[e]]++;
             in_src[p] = base + st->edge_src[e];
-            in_dst[p] = base + st->edge_dst[e];
             in_eid[p] = (int32_t)e;
             memcpy(edge_feat + (size_t)p * De, st->edge_feat + (size_t)e * De, kRow ? kRow : sizeof(float) * De);
           }
@@ -532,7 +520,6 @@ int xrl_pack_state(const xrl_model_desc *model, const xrl_state_desc *st, xrl_ba
         if (De == 8) place(std::integral_constant<int, 8>());
         else if (De == 4) place(std::integral_constant<int, 4>());
         else place(std::integral_constant<int, 0>());
-        for (int64_t p = a; p < z; ++p) out_pos[cur[n + (in_src[p] - base)]++] = (int32_t)p;
       }
       range_tiles(in_ptr, gnp, g0, g1, (int32_t)e0, G <= kGraphTileMaxGraphs, rt[t]);
     });
@@ -709,11 +696,9 @@ int xrl_pack_state_edits(const xrl_model_desc *model, const xrl_edit_state_desc 
     for (int64_t s = 0; s < S; ++s) b->max_slots = std::max(b->max_slots, sgp[s + 1] - sgp[s]);
     // (node_op, node_dense and edge_feat of the batch are not written here: the device fills its
     // copies from node_from / edge_from, and xrl_batch_host_view writes edge_feat on demand)
-    int32_t *in_ptr = b->at<int32_t>(b->o_in_ptr), *out_ptr = b->at<int32_t>(b->o_out_ptr);
-    int32_t *node_graph = b->at<int32_t>(b->o_node_graph), *out_pos = b->at<int32_t>(b->o_out_pos);
-    int32_t *in_src = b->at<int32_t>(b->o_in_src), *in_dst = b->at<int32_t>(b->o_in_dst), *in_eid = b->at<int32_t>(b->o_in_eid);
+    int32_t *in_ptr = b->at<int32_t>(b->o_in_ptr), *in_src = b->at<int32_t>(b->o_in_src), *in_eid = b->at<int32_t>(b->o_in_eid);
     int32_t *node_from = b->at<int32_t>(b->o_node_from), *edge_from = b->at<int32_t>(b->o_edge_from);
-    in_ptr[0] = out_ptr[0] = 0;
+    in_ptr[0] = 0;
     auto put = [&](size_t off, const void *src, int64_t bytes) {
       if (bytes > 0) memcpy(b->mem.p + off, src, (size_t)bytes);
     };
@@ -734,14 +719,14 @@ int xrl_pack_state_edits(const xrl_model_desc *model, const xrl_edit_state_desc 
     }
     std::vector<RangeTiles> rt(T);
     const bool merged = run_ranges(cut, [&](int t, int64_t g0, int64_t g1) {
-      std::vector<int32_t> newid, erank, cur, add_order;
+      std::vector<int32_t> newid, erank, add_order;
       std::vector<uint8_t> dead;
       for (int64_t g = g0; g < g1; ++g) {
         const int64_t s = g_state[g], c = g_cand[g];
         const int32_t nb = st->cur_node_ptr[s], n = st->cur_node_ptr[s + 1] - nb;
         const int64_t e0 = st->cur_edge_ptr[s], e1 = st->cur_edge_ptr[s + 1];
         const int32_t *ip = bin_ptr.data() + nb + s;
-        const int32_t base = gnp[g], ng = gnp[g + 1] - base, eb = gep[g];
+        const int32_t base = gnp[g], eb = gep[g];
         const int32_t an0 = c < 0 ? 0 : st->add_node_ptr[c], n_new = c < 0 ? 0 : st->add_node_ptr[c + 1] - an0;
         const int32_t ae0 = c < 0 ? 0 : st->add_edge_ptr[c], n_ae_c = c < 0 ? 0 : st->add_edge_ptr[c + 1] - ae0;
         // surviving nodes -> new ids; surviving edges -> rank in the candidate's edge list
@@ -772,18 +757,12 @@ int xrl_pack_state_edits(const xrl_model_desc *model, const xrl_edit_state_desc 
         // nodes
         for (int32_t i = 0; i < n; ++i) {
           if (dead[i]) continue;
-          const int32_t v = base + newid[i];
-          node_graph[v] = (int32_t)g;
-          node_from[v] = nb + i;
+          node_from[base + newid[i]] = nb + i;
         }
-        for (int32_t k = 0; k < n_new; ++k) {
-          const int32_t v = base + nk + k;
-          node_graph[v] = (int32_t)g;
-          node_from[v] = -1 - (an0 + k);
-        }
+        for (int32_t k = 0; k < n_new; ++k) node_from[base + nk + k] = -1 - (an0 + k);
         // receiver order: per receiver its surviving in-edges (edge ids ascending), then its new ones
         int32_t p = eb, ka = 0;
-        int32_t *inp = in_ptr + base + 1, *outp = out_ptr + base + 1;
+        int32_t *inp = in_ptr + base + 1;
         int32_t vcur = 0;
         for (int32_t i = 0; i < n + n_new; ++i) {
           if (i < n && dead[i]) continue;
@@ -794,7 +773,6 @@ int xrl_pack_state_edits(const xrl_model_desc *model, const xrl_edit_state_desc 
               if (erank[el] < 0) continue;
               const int64_t e = e0 + el;
               in_src[p] = base + newid[st->edge_src[e]];
-              in_dst[p] = base + v;
               in_eid[p] = eb + erank[el];
               edge_from[p] = (int32_t)e;
               ++p;
@@ -803,20 +781,12 @@ int xrl_pack_state_edits(const xrl_model_desc *model, const xrl_edit_state_desc 
           for (; ka < n_ae_c && newid[st->add_edge_dst[ae0 + add_order[ka]]] == v; ++ka) {
             const int32_t k = ae0 + add_order[ka];
             in_src[p] = base + newid[st->add_edge_src[k]];
-            in_dst[p] = base + v;
             in_eid[p] = eb + ek + add_order[ka];
             edge_from[p] = -1 - k;
             ++p;
           }
           inp[v] = p;                                // end of v's in-edges
         }
-        // sender-side index: receiver-order positions grouped by sender, ascending position
-        for (int32_t v = 0; v < ng; ++v) outp[v] = 0;
-        for (int32_t q = eb; q < p; ++q) outp[in_src[q] - base]++;
-        cur.assign(ng, 0);
-        int32_t ro = eb;
-        for (int32_t v = 0; v < ng; ++v) { cur[v] = ro; ro += outp[v]; outp[v] = ro; }
-        for (int32_t q = eb; q < p; ++q) out_pos[cur[in_src[q] - base]++] = q;
       }
       range_tiles(in_ptr, gnp.data(), g0, g1, gep[g0], G <= kGraphTileMaxGraphs, rt[t]);
     });
@@ -862,37 +832,69 @@ int xrl_batch_dims(const xrl_batch *b, int64_t *S, int64_t *G, int64_t *N, int64
   return XRL_OK;
 }
 
+// What packing left out, from what it wrote. Null: out of memory.
+static PackedArrays *packed_arrays(const xrl_batch *b) {
+  const int64_t N = b->N, E = b->E;
+  const int De = b->model.d_edge;
+  const int32_t *in_ptr = b->at<int32_t>(b->o_in_ptr), *in_src = b->at<int32_t>(b->o_in_src), *gnp = b->at<int32_t>(b->o_graph_node_ptr);
+  std::unique_ptr<PackedArrays> a;
+  try {
+    a.reset(new PackedArrays());
+    a->in_dst.resize(E); a->out_ptr.resize(N + 1); a->out_pos.resize(E); a->node_graph.resize(N);
+    if (b->from_edits) a->edge_feat.resize((size_t)E * De);
+  } catch (const std::bad_alloc &) {
+    return nullptr;
+  }
+  for (int64_t g = 0; g < b->G; ++g)
+    for (int32_t n = gnp[g]; n < gnp[g + 1]; ++n) a->node_graph[n] = (int32_t)g;
+  for (int64_t n = 0; n < N; ++n)
+    for (int32_t p = in_ptr[n]; p < in_ptr[n + 1]; ++p) a->in_dst[p] = (int32_t)n;
+  // sender index: receiver-order positions grouped by sender, ascending (out_ptr[s]: next place while they are dealt
+  // out, i.e. the end of s's, the beginning of s + 1's)
+  std::fill(a->out_ptr.begin(), a->out_ptr.end(), 0);
+  for (int64_t p = 0; p < E; ++p) a->out_ptr[in_src[p]]++;
+  int32_t sum = 0;
+  for (int64_t n = 0; n <= N; ++n) {
+    const int32_t k = a->out_ptr[n];
+    a->out_ptr[n] = sum;
+    sum += k;
+  }
+  for (int64_t p = 0; p < E; ++p) a->out_pos[a->out_ptr[in_src[p]]++] = (int32_t)p;
+  for (int64_t n = N; n > 0; --n) a->out_ptr[n] = a->out_ptr[n - 1];
+  a->out_ptr[0] = 0;
+  if (b->from_edits) {
+    const int32_t *edge_from = b->at<int32_t>(b->o_edge_from);
+    for (int64_t p = 0; p < E; ++p) {
+      const int32_t f = edge_from[p];
+      const float *src = f >= 0 ? b->at<float>(b->o_base_feat) + (size_t)f * De : b->at<float>(b->o_new_feat) + (size_t)(-1 - f) * De;
+      memcpy(a->edge_feat.data() + (size_t)p * De, src, sizeof(float) * De);
+    }
+  }
+  return a.release();
+}
+
 int xrl_batch_host_view(const xrl_batch *cb, xrl_packed_view *v) {
   if (!cb || !v) return fail(XRL_ERR_NULL, "xrl_batch_host_view: NULL argument");
   xrl_batch *b = const_cast<xrl_batch *>(cb);
-  const int De = b->model.d_edge;
-  const float *edge_feat = b->from_edits ? b->view_edge_feat.data() : b->at<float>(b->o_edge_feat);
-  if (b->from_edits && b->view_edge_feat.size() != (size_t)b->E * De) {
-    // packed from edits: the per-edge attribute rows are written out on first request
-    try {
-      b->view_edge_feat.resize((size_t)b->E * De);
-    } catch (const std::bad_alloc &) {
-      return fail(XRL_ERR_OOM, "xrl_batch_host_view: out of host memory");
-    }
-    const int32_t *edge_from = b->at<int32_t>(b->o_edge_from);
-    for (int64_t p = 0; p < b->E; ++p) {
-      const int32_t f = edge_from[p];
-      const float *src = f >= 0 ? b->at<float>(b->o_base_feat) + (size_t)f * De : b->at<float>(b->o_new_feat) + (size_t)(-1 - f) * De;
-      memcpy(&b->view_edge_feat[(size_t)p * De], src, sizeof(float) * De);
-    }
-    edge_feat = b->view_edge_feat.data();
+  PackedArrays *a = b->view.load();
+  if (!a) {
+    // (made without a lock: of several threads that ask first, one publishes its copy, and the others drop theirs)
+    PackedArrays *mine = packed_arrays(b);
+    if (!mine) return fail(XRL_ERR_OOM, "xrl_batch_host_view: out of host memory");
+    if (b->view.compare_exchange_strong(a, mine)) a = mine;
+    else delete mine;
   }
   v->S = b->S; v->G = b->G; v->N = b->N; v->E = b->E;
   v->state_graph_ptr = b->at<int32_t>(b->o_state_graph_ptr);
   v->graph_node_ptr = b->at<int32_t>(b->o_graph_node_ptr);
   v->in_ptr = b->at<int32_t>(b->o_in_ptr);
   v->in_src = b->at<int32_t>(b->o_in_src);
-  v->in_dst = b->at<int32_t>(b->o_in_dst);
+  v->in_dst = a->in_dst.data();
   v->in_eid = b->at<int32_t>(b->o_in_eid);
-  v->out_ptr = b->at<int32_t>(b->o_out_ptr);
-  v->out_pos = b->at<int32_t>(b->o_out_pos);
-  v->node_graph = b->at<int32_t>(b->o_node_graph);
-  v->edge_feat = edge_feat;
+  v->out_ptr = a->out_ptr.data();
+  v->out_pos = a->out_pos.data();
+  v->node_graph = a->node_graph.data();
+  v->edge_feat = b->from_edits ? a->edge_feat.data() : b->at<float>(b->o_edge_feat);
   v->n_tiles = b->n_tiles;
   v->tile_ptr = b->at<int32_t>(b->o_tile);
   v->n_graph_tiles = b->n_graph_tiles;

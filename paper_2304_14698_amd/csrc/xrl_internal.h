@@ -86,18 +86,24 @@ void host_block_give(HostBlock &b);
 struct Distinct;            // the batch's graphs reduced to distinct nodes (device translation unit)
 struct DevicePool;          // idle device blocks of one context (device translation unit)
 
+// Host copies, for views, of arrays that packing does not write.
+struct PackedArrays {
+  RawVec<int32_t> in_dst, out_ptr, out_pos, node_graph;
+  RawVec<float> edge_feat;                     // of a batch packed from edits
+};
+
 // The packed arrays lie in one host block, those the device needs first and in the device's layout:
 // array i of the device block is at the same offset in both. Behind them, in the host block, in_eid;
-// in the device block, the arrays that the device writes itself.
+// in the device block, the arrays that the device writes itself: receivers, the nodes' graphs and
+// (for a backward pass) the sender index follow from the others, and are neither packed nor sent.
 struct xrl_batch {
   xrl_model_desc model;
   int64_t S = 0, G = 0, N = 0, E = 0;
   int32_t max_slots = 0;  // largest number of slots in one state
   HostBlock mem;
   size_t send_bytes = 0;  // transferred to the device
-  size_t o_state_graph_ptr = 0, o_graph_node_ptr = 0, o_in_ptr = 0, o_out_ptr = 0, o_node_op = 0, o_in_src = 0,
-         o_in_dst = 0, o_out_pos = 0, o_node_graph = 0, o_node_dense = 0, o_edge_feat = 0, o_graph_global = 0,
-         o_mask = 0, o_tile = 0, o_gtile = 0, o_graph_tile = 0, o_in_eid = 0;
+  size_t o_state_graph_ptr = 0, o_graph_node_ptr = 0, o_in_ptr = 0, o_node_op = 0, o_in_src = 0, o_node_dense = 0,
+         o_edge_feat = 0, o_graph_global = 0, o_mask = 0, o_tile = 0, o_gtile = 0, o_graph_tile = 0, o_in_eid = 0;
   template <typename T> T *at(size_t off) const { return (T *)(mem.p + off); }
   int64_t n_tiles = 0;            // edge tiles of the message kernels (see the packer): [n_tiles + 1] at o_tile
   int64_t n_split_tiles = 0;      // tiles that end inside a receiver's in-edge range
@@ -116,9 +122,10 @@ struct xrl_batch {
   bool from_edits = false;
   size_t o_node_from = 0, o_edge_from = 0, o_base_op = 0, o_new_op = 0, o_base_dense = 0, o_new_dense = 0,
          o_base_feat = 0, o_new_feat = 0;
-  RawVec<float> view_edge_feat;
+  std::atomic<PackedArrays *> view{nullptr};   // made by the first xrl_batch_host_view
   xrl_batch_device dev;
   bool uploaded = false;
+  bool out_index = false;                  // the device's sender index has been made on the owner's stream
   // the context that uploaded it: its other users wait for its transfer, and a device block that only it
   // has used goes back to its pool (reuse on the same stream is ordered), any other is freed
   uint64_t owner = 0;
@@ -129,7 +136,10 @@ struct xrl_batch {
   uint64_t id = 0;  // unique per packed batch; ties saved activations to their batch
   xrl_batch() = default;
   xrl_batch(const xrl_batch &) = delete;
-  ~xrl_batch() { host_block_give(mem); }
+  ~xrl_batch() {
+    host_block_give(mem);
+    delete view.load();
+  }
 };
 
 constexpr int64_t kGraphTileMaxGraphs = 4096;
