@@ -1073,6 +1073,37 @@ int launch_mlp2(xrl_ctx *c, int kind, Mlp2Args &a) {
   return fail(XRL_ERR_UNSUPPORTED, "hidden = %d", c->m.hidden);
 }
 
+// z = h W of the attention rounds (and the backward's dh = dz W^T): W in LDS where it fits.
+template <typename T, int H>
+int launch_gat_linear_h(xrl_ctx *c, GatArgs &a) {
+  using S = GatLds<T, H>;
+  if constexpr (S::FITS) {
+    auto kern = gat_linear_lds_kernel<T, H>;
+    static bool attr_set = false;
+    if (!attr_set) {
+      HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, S::BYTES));
+      attr_set = true;
+    }
+    const int64_t n_wt = (a.n_rows + 31) / 32, want = ((n_wt + S::NW - 1) / S::NW + 7) / 8 * 8;
+    const int64_t cap = (int64_t)c->n_cu / 8 * 8 * S::PER_CU;
+    kern<<<dim3((unsigned)std::min(want, cap)), dim3(64 * S::NW), S::BYTES, c->stream>>>(a);
+  } else {
+    a.n_blocks = (a.n_rows + 127) / 128;
+    gat_linear_kernel<T, H><<<dim3((unsigned)((a.n_blocks + 7) / 8 * 8)), dim3(256), 0, c->stream>>>(a);
+  }
+  HIP_TRY(hipGetLastError());
+  return XRL_OK;
+}
+template <typename T>
+int launch_gat_linear(xrl_ctx *c, GatArgs &a) {
+  switch (c->m.hidden) {
+    case 64: return launch_gat_linear_h<T, 64>(c, a);
+    case 128: return launch_gat_linear_h<T, 128>(c, a);
+    case 256: return launch_gat_linear_h<T, 256>(c, a);
+  }
+  return fail(XRL_ERR_UNSUPPORTED, "hidden = %d", c->m.hidden);
+}
+
 RowMlpArgs rowmlp_args(xrl_ctx *c, const MlpRef &r, bool relu_last, const float *in1, int w1, const float *in2,
                        int w2, int64_t n_rows, float *out, float *const *act, int *dmax_out = nullptr) {
   RowMlpArgs a;
@@ -2037,7 +2068,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
     ga.n_rows = N; ga.z = c->agg[r + 1]; ga.hout = c->h[r + 1]; ga.dout = dhA;
     ga.s_src = c->gat_ss[r]; ga.s_dst = c->gat_sd[r];
     ga.a_src = c->d_w + c->L.gat[r].a_src; ga.a_dst = c->d_w + c->L.gat[r].a_dst;
-    ga.in_ptr = d.in_ptr; ga.in_src = d.in_src; ga.in_dst = d.in_dst; ga.out_ptr = d.out_ptr; ga.out_pos = d.out_pos;
+    ga.in_ptr = d.in_ptr; ga.in_src = d.in_src; ga.in_dst = d.in_dst; ga.out_ptr = d.out_ptr; ga.out_pos = d.out_pos; ga.zero_row = c->zero_row;
     ga.alpha_e = g_ale; ga.du_e = g_due; ga.alpha_s = g_als; ga.du_s = g_dus; ga.d_ss = g_dss; ga.d_sd = g_dsd;
     MlpGrads mg;
     if ((rc = next_grads(N, &mg, 1))) return rc;
@@ -2062,15 +2093,9 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
     if ((rc = queue_wgrad<T>(c, wq, x))) return rc;
     GatArgs gl;
     memset(&gl, 0, sizeof(gl));
-    gl.n_rows = N; gl.n_blocks = (N + 127) / 128;
+    gl.n_rows = N;
     gl.h = mg.dz1; gl.Ws = c->gatWt[r]; gl.a_src = ga.a_src; gl.a_dst = ga.a_dst; gl.z = dhB;
-    const unsigned grid_l = (unsigned)((gl.n_blocks + 7) / 8 * 8);
-    switch (H) {
-      case 64: gat_linear_kernel<T, 64><<<dim3(grid_l), dim3(256), 0, c->stream>>>(gl); break;
-      case 128: gat_linear_kernel<T, 128><<<dim3(grid_l), dim3(256), 0, c->stream>>>(gl); break;
-      default: gat_linear_kernel<T, 256><<<dim3(grid_l), dim3(256), 0, c->stream>>>(gl); break;
-    }
-    HIP_TRY(hipGetLastError());
+    if ((rc = launch_gat_linear<T>(c, gl))) return rc;
     std::swap(dhA, dhB);
   }
   for (int r = R - 1; r >= 0 && !gat; --r) {
@@ -2372,18 +2397,12 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
     if (gat) {                         // graph-attention reading of the round
       if (N > 0) {
         GatArgs ga;
-        ga.n_rows = N; ga.n_blocks = (N + 127) / 128;
+        ga.n_rows = N;
         ga.h = hcur; ga.Ws = c->gatW[r];
         ga.a_src = c->d_w + c->L.gat[r].a_src; ga.a_dst = c->d_w + c->L.gat[r].a_dst;
         ga.z = aggb; ga.s_src = c->gat_ss[save ? r : 0]; ga.s_dst = c->gat_sd[save ? r : 0];
-        ga.in_ptr = d.in_ptr; ga.in_src = d.in_src; ga.out = hnext;
-        { Timed t(c, TK_GAT_LINEAR);
-          const unsigned grid = (unsigned)((ga.n_blocks + 7) / 8 * 8);
-          switch (H) {
-            case 64: gat_linear_kernel<T, 64><<<dim3(grid), dim3(256), 0, c->stream>>>(ga); break;
-            case 128: gat_linear_kernel<T, 128><<<dim3(grid), dim3(256), 0, c->stream>>>(ga); break;
-            default: gat_linear_kernel<T, 256><<<dim3(grid), dim3(256), 0, c->stream>>>(ga); break;
-          } }
+        ga.in_ptr = d.in_ptr; ga.in_src = d.in_src; ga.out = hnext; ga.zero_row = c->zero_row;
+        { Timed t(c, TK_GAT_LINEAR); if ((rc = launch_gat_linear<T>(c, ga))) return rc; }
         { Timed t(c, TK_GAT_AGGREGATE);
           const int64_t threads = N * (H / PV);
           gat_aggregate_kernel<T, PV><<<dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, c->stream>>>(ga, H); }
