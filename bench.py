@@ -235,7 +235,7 @@ def main():
     for _ in range(args.steps):
         step()
     kern = {}
-    names = ("embed", "edge", "edge_fixup", "node", "gat_linear", "gat_aggregate", "pool", "readout", "heads", "resident")
+    names = ("embed", "edge", "edge_fixup", "node", "gat_linear", "gat_aggregate", "pool", "readout", "heads", "resident", "round")
     if backward:
         names += ("bwd_edge", "bwd_node", "bwd_embed", "wgrad", "grad_gather", "gat_bwd")
     for k in names:

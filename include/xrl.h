@@ -208,6 +208,8 @@ int xrl_batch_free(xrl_batch *b);   /* frees host and device copies; NULL is acc
  * 32768; 0 = always; states and embeddings are the same bits, gradients agree within rounding). Up to
  * 8192 it does not apply to a batch reduced to its distinct nodes (see xrl_encode) that is saved for the
  * backward pass: its rounds of any size run on them;
+ * XRL_ROUND_BLOCKS = blocks per compute unit, of 28 nodes each, up to which a forward-only encode in bf16 at hidden
+ * <= 128 runs a message-passing round as one launch (default 4 at hidden = 64, else 2; 0 = never; same bits);
  * XRL_WGRAD_WIDE_MIN_ROWS = rows of the products of one weight-gradient launch, added up, from which it uses
  * 256-column tiles at hidden = 256 in bf16 (default 2^18; same sums in a different, equally fixed order);
  * XRL_GRAD_ROOM = bytes of gradients kept for one such launch (default 2^31; always at least one MLP's);
@@ -371,8 +373,8 @@ int xrl_mlp_backward(xrl_ctx *ctx, const xrl_batch *b, int32_t kind, int32_t rou
  * xrl_read_timing synchronises the stream, returns the summed duration and launch count
  * recorded since the last read for `kernel` and forgets them. Forward: {"embed", "edge",
  * "edge_fixup", "node", "pool", "readout", "heads"} (the steps of Section 3.4 / 3.3.2 in
- * execution order; "gat_linear", "gat_aggregate" with XRL_ROUND_GAT; "resident" = the whole
- * encoder of a small batch in one launch). Backward (Section 3.3.4):
+ * execution order; "gat_linear", "gat_aggregate" with XRL_ROUND_GAT; "round" = a whole round of a small
+ * batch in one launch, "resident" = its whole encoder). Backward (Section 3.3.4):
  * {"bwd_edge", "bwd_node", "bwd_embed"} = gradients through the fused MLPs, "wgrad" = the weight
  * gradients of as many MLPs as one launch takes, with their reductions (a single product through
  * xrl_weight_gradient; {"wgrad_edge", "wgrad_node", "wgrad_embed"}: accepted, no launch is only

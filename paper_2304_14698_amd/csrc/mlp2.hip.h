@@ -567,3 +567,152 @@ __global__ __launch_bounds__(2 * H) void mlp2_split_kernel(const Mlp2Args a) {
     if (e.to_c0 || e.to_c1) store_tile_rows<float, H>(a.carry, wt * 2 + (e.to_c1 ? 1 : 0), true, w, g, one[0]);
   }
 }
+
+// A whole message-passing round in one launch, bf16, forward only, for batches of a few tiles per compute unit: a
+// node's received sum needs its own in-edges alone, so a block of H / 32 waves that owns some consecutive
+// nodes runs the edge MLP on their in-edges, 32 at a time (cut between receivers: no receiver may have
+// more), keeps the sums in LDS, as the second half of the node MLP's input fragments, and goes on with
+// the node MLP. Same operations in the same order per output as the two split kernels: the same bits.
+// Bound by its chain of dependent steps (ranges, indices, rows, four products, stores); a wave requests all its
+// weights of an MLP (100 registers) under the steps before. fp32, whose products are four times
+// as long, gains nothing. As many nodes a block as give every compute unit one, 16 to 28: their in-edges, about one
+// per node, then mostly fit one pass. us per encode of five rounds, two launches a round /
+// one, H = 128: 454 nodes 56.5 / 46.4, 5.1 k 60.8 / 49.9, 7.1 k 61.9 / 58.3, 13.8 k 78.0 / 70.6, 20.6 k 96.0 / 96.9; H = 64: 454
+// 48.0 / 35.5, 5.1 k 47.6 / 37.9, 13.8 k 54.5 / 48.2, 27.4 k 65.6 / 56.6.
+constexpr int kRoundNodesMin = 16, kRoundNodesMax = 28;
+struct RoundArgs {
+  Mlp2Args edge, node;     // node.out: [N, H]; node.agg and edge.out are not used
+  int nodes;               // of a block, at most 32
+};
+template <typename T, int H>
+struct RoundTile {
+  using S = SplitTile<T, H>;
+  static constexpr int STAGE = S::MB * BlockStage<T>::BYTES;
+  static constexpr int BYTES = 2 * S::XBYTES + STAGE;          // edge fragments (then relu(z1)), node fragments, staging
+  static constexpr bool FITS = sizeof(T) == 2 && H <= 128;
+};
+// Layers 1 and 2 of a tile whose input fragments lie in `xs`: acc = this wave's 32 output features, bias
+// included, before the last ReLU. relu(z1) goes where `zs` points (which may be xs).
+template <typename T, int H, int TAIL>
+__device__ __forceinline__ void split_layers(const Mlp2Args &a, const typename Operand<T>::vec *xs, typename Operand<T>::vec *zs,
+                                             const typename Operand<T>::vec (&w1)[2 * SplitTile<T, H>::HS + 1],
+                                             const typename Operand<T>::vec (&w2)[SplitTile<T, H>::MB * SplitTile<T, H>::QB],
+                                             const TailRaw<Operand<T>::V> *xt, int64_t row,
+                                             int w, int lane, f32x16 &acc) {
+  using S = SplitTile<T, H>;
+  using Opd = Operand<T>;
+  using vec = typename Opd::vec;
+  constexpr int V = Opd::V, HS = S::HS, MB = S::MB, QB = S::QB, NC2 = MB * QB;
+  const int g = lane >> 5;
+#pragma unroll
+  for (int s = 0; s < 2 * HS; ++s) Opd::mma(w1[s], xs[s * 64 + lane], acc);
+  if constexpr (TAIL) {
+    const vec *W1 = (const vec *)a.W1s + (size_t)w * 64 + lane;
+    const float *xe = a.edge_feat + (size_t)row * a.De;
+    for (int s = 2 * HS; s < a.nslab1; ++s) {                   // edge attributes
+      const vec xv = tail_to_operand<T>(s == 2 * HS ? *xt : load_tail<V>(xe, a.De, s - 2 * HS, g));
+      const vec wv = s == 2 * HS ? w1[2 * HS] : W1[(size_t)s * MB * 64];
+      Opd::mma(wv, xv, acc);
+    }
+  }
+  __syncthreads();                                              // (every wave has read its input fragments)
+#pragma unroll
+  for (int q = 0; q < QB; ++q) zs[(w * QB + q) * 64 + lane] = relu_operand<T>(acc, q);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = a.b2[32 * w + acc_row(r, g)];
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < NC2; ++c) Opd::mma(w2[c], zs[c * 64 + lane], acc);
+}
+template <typename T, int H>
+__global__ __launch_bounds__(2 * H) void mlp2_round_kernel(const RoundArgs a) {
+  using S = SplitTile<T, H>;
+  using Opd = Operand<T>;
+  using vec = typename Opd::vec;
+  constexpr int V = Opd::V, SL = 2 * V, HS = S::HS, MB = S::MB, QB = S::QB, NC2 = MB * QB;
+  extern __shared__ __align__(16) char smem[];
+  vec *xe = (vec *)smem, *xn = (vec *)(smem + S::XBYTES);       // [2 HS][64] each
+  const Mlp2Args &e = a.edge, &n = a.node;
+  const int64_t n_tiles = n.n_blocks, per_xcd = (n_tiles + 7) / 8;
+  const int64_t wt = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;      // (see mlp2_split_kernel)
+  if ((int64_t)(blockIdx.x / 8) >= per_xcd || wt >= n_tiles) return;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  char *stage = smem + 2 * S::XBYTES + w * BlockStage<T>::BYTES;
+  // all the edge MLP's weights of this wave first, under the chain of indices
+  vec w1[2 * HS + 1], w2[NC2];
+  auto weights = [&](const Mlp2Args &m, int n1) {
+    const vec *p1 = (const vec *)m.W1s + (size_t)w * 64 + lane, *p2 = (const vec *)m.W2s + (size_t)w * 64 + lane;
+#pragma unroll
+    for (int s = 0; s < 2 * HS + 1; ++s) w1[s] = p1[(size_t)(s < n1 ? s : 0) * MB * 64];
+#pragma unroll
+    for (int c = 0; c < NC2; ++c) w2[c] = p2[(size_t)c * MB * 64];
+  };
+  const int64_t n0 = wt * a.nodes;
+  const int nn = n.n_rows - n0 < a.nodes ? (int)(n.n_rows - n0) : a.nodes;
+  const int lo = n.in_ptr[n0], hi = n.in_ptr[n0 + (l32 < nn ? l32 + 1 : nn)];   // hi: end of node l32's in-edges
+  weights(e, 2 * HS + 1);
+  __builtin_amdgcn_sched_barrier(0);
+  // ---- the node MLP's own half, and zeros for the sums of nodes without in-edges
+  constexpr int MINE = 2 * HS / MB, OWN = HS / MB;              // consecutive slabs this wave fetches of an edge's two rows, of a node's
+  static_assert(MINE * MB == 2 * HS && OWN * MB == HS && HS % MINE == 0, "");
+  const T *h = (const T *)n.h;
+  {
+    const T *own = h + (size_t)(n0 + (l32 < nn ? l32 : nn - 1)) * H + g * V;
+    vec x[OWN];
+#pragma unroll
+    for (int i = 0; i < OWN; ++i) x[i] = *(const vec *)(own + (w * OWN + i) * SL);
+#pragma unroll
+    for (int i = 0; i < OWN; ++i) {
+      xn[(w * OWN + i) * 64 + lane] = x[i];
+      xn[(HS + w * OWN + i) * 64 + lane] = Opd::zero();
+    }
+  }
+  const int end = __shfl(hi, nn - 1);
+  for (int c0 = lo; c0 < end;) {
+    // the receivers whose in-edges end within the next 32 (at least one: none has more)
+    const int upto = __popcll(__ballot(hi <= c0 + 32 && lane < nn));
+    const int c1 = __shfl(hi, upto - 1), nv = c1 - c0;
+    const int64_t row = c0 + (l32 < nv ? l32 : nv - 1);
+    const int src = e.in_src[row], dst = e.in_dst[row];
+    const int s0 = w * MINE;
+    const T *px = h + (size_t)(s0 < HS ? src : dst) * H + g * V + (s0 < HS ? s0 : s0 - HS) * SL;
+    vec x[MINE];
+#pragma unroll
+    for (int i = 0; i < MINE; ++i) x[i] = *(const vec *)(px + i * SL);
+    const TailRaw<V> xt = load_tail<V>(e.edge_feat + (size_t)row * e.De, e.De, 0, g);
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = e.b1[32 * w + acc_row(r, g)];
+    __syncthreads();                                            // (the pass before has read relu(z1))
+#pragma unroll
+    for (int i = 0; i < MINE; ++i) xe[(s0 + i) * 64 + lane] = x[i];
+    __syncthreads();
+    split_layers<T, H, 1>(e, xe, xe, w1, w2, &xt, row, w, lane, acc);
+    if (c1 >= end) weights(n, 2 * HS);                          // (the node MLP's, under the sums)
+    EdgeTileMeta m;
+    m.dst = dst; m.prev_d = m.next_d = -1;                      // (a pass holds whole receivers)
+    f32x16 one[1] = {acc};
+    const EdgeRoute to = edge_run_sums<1>(one, m, nv, lane);
+    if (to.dsel >= 0) {
+      // as operand fragments: feature f of this wave's 32 is element f % V of slab f / 2V, lane group (f % 2V) / V
+      char *p = (char *)(xn + (HS + w * QB) * 64 + (to.dsel - (int)n0));
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        float v[4] = {one[0][4 * q], one[0][4 * q + 1], one[0][4 * q + 2], one[0][4 * q + 3]};
+        const int slab = sizeof(T) == 2 ? q / 2 : q, half = sizeof(T) == 2 ? q % 2 : g, at = sizeof(T) == 2 ? 8 * g : 0;
+        store4<T>((T *)(p + (slab * 64 + half * 32) * 16 + at), v);
+      }
+    }
+    c0 = c1;
+  }
+  if (lo >= end) weights(n, 2 * HS);
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = n.b1[32 * w + acc_row(r, g)];
+  __syncthreads();
+  split_layers<T, H, 0>(n, xn, xe, w1, w2, nullptr, 0, w, lane, acc);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = relu_f32(acc[r]);
+  store_block_via_lds<T, H>((T *)n.out, n0, nn, w, lane, acc, stage);
+}

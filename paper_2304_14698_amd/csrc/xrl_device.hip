@@ -114,11 +114,11 @@ __global__ __launch_bounds__(256) void arrange_weights_kernel(const SwzJob *jobs
 // kernels whose launches can be timed with HIP events (xrl_set_timing / xrl_read_timing)
 enum { TK_EMBED = 0, TK_EDGE, TK_EDGE_FIXUP, TK_NODE, TK_POOL, TK_READOUT, TK_HEADS, TK_GAT_LINEAR,
        TK_GAT_AGGREGATE, TK_BWD_EDGE, TK_BWD_NODE, TK_BWD_EMBED, TK_WGRAD, TK_GRAD_GATHER, TK_GAT_BWD, TK_RESIDENT,
-       TK_WGRAD_EDGE, TK_WGRAD_NODE, TK_WGRAD_EMBED, TK_COUNT };
+       TK_WGRAD_EDGE, TK_WGRAD_NODE, TK_WGRAD_EMBED, TK_ROUND, TK_COUNT };
 static const char *const kTimedNames[TK_COUNT] = {"embed", "edge", "edge_fixup", "node", "pool", "readout",
                                                   "heads", "gat_linear", "gat_aggregate", "bwd_edge", "bwd_node",
                                                   "bwd_embed", "wgrad", "grad_gather", "gat_bwd", "resident",
-                                                  "wgrad_edge", "wgrad_node", "wgrad_embed"};
+                                                  "wgrad_edge", "wgrad_node", "wgrad_embed", "round"};
 
 constexpr int64_t kMaxFusedSlots = 4096;   // largest G the single-launch heads kernel takes
 constexpr int kCounts = 3 * kMaxLevels;
@@ -151,6 +151,7 @@ struct xrl_ctx {
   int64_t p_min_rows_forward = 8192;   // for the backward pass, and when not
   int64_t wide_min_rows = 1 << 18;   // rows of a launch's products from which 256-column weight-gradient tiles are used (XRL_WGRAD_WIDE_MIN_ROWS)
   size_t grad_room = kGradRoom;      // XRL_GRAD_ROOM
+  int64_t round_blocks = 0;          // blocks per compute unit up to which a round is one launch, see mlp2_round_kernel (XRL_ROUND_BLOCKS)
   int64_t resident_max_graphs = 0;   // largest batch (graphs) for the one-launch encoder (XRL_RESIDENT_MAX_GRAPHS)
   int64_t resident_max_tiles = 0;    // ... and the most 32-row tiles (nodes, or edges) of one graph (XRL_RESIDENT_MAX_TILES)
   float *d_w = nullptr;         // flat fp32 weights
@@ -916,6 +917,43 @@ int launch_mlp2_split(xrl_ctx *c, const Mlp2Args &a) {
   kern<<<dim3((unsigned)((a.n_blocks + 7) / 8 * 8)), dim3(2 * H), S::BYTES, c->stream>>>(a);
   HIP_TRY(hipGetLastError());
   return XRL_OK;
+}
+
+// Whole rounds (see mlp2_round_kernel): forward only, where the two kernels of a round would be split ones, up to
+// round_blocks blocks per compute unit.
+template <typename T, int H>
+int launch_round_h(xrl_ctx *c, const RoundArgs &a) {
+  if constexpr (RoundTile<T, H>::FITS) {
+    auto kern = mlp2_round_kernel<T, H>;
+    static bool attr_set = false;
+    if (!attr_set) {
+      HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, RoundTile<T, H>::BYTES));
+      attr_set = true;
+    }
+    kern<<<dim3((unsigned)((a.node.n_blocks + 7) / 8 * 8)), dim3(2 * H), RoundTile<T, H>::BYTES, c->stream>>>(a);
+    HIP_TRY(hipGetLastError());
+    return XRL_OK;
+  }
+  return fail(XRL_ERR_UNSUPPORTED, "launch_round_h: hidden = %d", H);
+}
+template <typename T>
+bool round_applies(const xrl_ctx *c, const LevelGraph &g) {
+  const int H = c->m.hidden;
+  const bool fits = H == 64 ? RoundTile<T, 64>::FITS : H == 128 ? RoundTile<T, 128>::FITS : RoundTile<T, 256>::FITS;
+  if (std::max(g.N, g.E) >= c->min_rows_now) return false;      // (the persistent kernels')
+  return fits && g.N > 0 && g.N <= kRoundNodesMax * c->round_blocks * c->n_cu;
+}
+template <typename T>
+int launch_round(xrl_ctx *c, RoundArgs &a) {
+  const int64_t even = (a.node.n_rows + c->n_cu - 1) / c->n_cu;
+  a.nodes = (int)std::max<int64_t>(kRoundNodesMin, std::min<int64_t>(kRoundNodesMax, even));
+  a.node.n_blocks = (a.node.n_rows + a.nodes - 1) / a.nodes;
+  switch (c->m.hidden) {
+    case 64: return launch_round_h<T, 64>(c, a);
+    case 128: return launch_round_h<T, 128>(c, a);
+    case 256: return launch_round_h<T, 256>(c, a);
+  }
+  return fail(XRL_ERR_UNSUPPORTED, "hidden = %d", c->m.hidden);
 }
 
 template <typename T, int H>
@@ -2415,6 +2453,20 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
     }
     set_graph(g);
     a.agg_src = g.agg_src;
+    if (!save && b->n_split_tiles == 0 && round_applies<T>(c, g)) {
+      RoundArgs ra;
+      set_w(c->edge[r]);
+      a.n_rows = E; a.h = hcur;
+      ra.edge = a;
+      set_w(c->node[r]);
+      a.n_rows = N; a.out = hnext;
+      ra.node = a;
+      { Timed t(c, TK_ROUND); rc = launch_round<T>(c, ra); }
+      if (rc) return rc;
+      c->h[r + 1] = hnext;
+      hcur = hnext;
+      continue;
+    }
     set_w(c->edge[r]);
     a.n_rows = E; a.h = hcur; a.out = aggb;
     a.z1 = c->z1_edge[r]; a.z1mask = c->zm_edge[r]; a.ymask = c->ym_edge[r];
@@ -2521,6 +2573,8 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   c->p_min_rows_forward = model->hidden <= 128 ? 4 * kPersistentMinRows : kPersistentMinRows;
   if (const char *e = getenv("XRL_PERSISTENT_MIN_ROWS")) c->p_min_rows = c->p_min_rows_forward = atoll(e);
   if (const char *e = getenv("XRL_WGRAD_WIDE_MIN_ROWS")) c->wide_min_rows = atoll(e);
+  c->round_blocks = model->hidden == 64 ? 4 : 2;
+  if (const char *e = getenv("XRL_ROUND_BLOCKS")) c->round_blocks = atoll(e);
   if (const char *e = getenv("XRL_GRAD_ROOM")) c->grad_room = (size_t)std::max<long long>(0, atoll(e));
   // Largest batches of the one-launch encoders (0 graphs = never). A forward-only encode takes them up to a
   // limit that the variable of that form states, and by default never: since a tile of the
