@@ -23,7 +23,7 @@ enum { KIND_EMBED = 0, KIND_EDGE = 1, KIND_NODE = 2 };
 struct Mlp2Args {
   int64_t n_rows;
   int64_t n_blocks;        // number of tiles
-  const void *W1s, *W2s;   // fragment-ordered weights, operand type
+  const void *W1s, *W2s;   // fragment-ordered weights, operand type (mlp2_split3_kernel: their parts)
   const float *b1, *b2;    // [H]
   int nslab1;              // slabs of layer 1's (zero-padded) input width
   const void *h;           // [N, H] operand type            (EDGE, NODE)
@@ -564,6 +564,138 @@ __global__ __launch_bounds__(2 * H) void mlp2_split_kernel(const Mlp2Args a) {
     f32x16 one[1] = {acc};
     const EdgeRoute e = edge_run_sums<1>(one, m, nv, lane);
     store_block_rows_via_lds<T, H>(out, e.dsel, w, lane, one[0], stage);
+    if (e.to_c0 || e.to_c1) store_tile_rows<float, H>(a.carry, wt * 2 + (e.to_c1 ? 1 : 0), true, w, g, one[0]);
+  }
+}
+
+// The same split form for the fp32 edge and node MLPs of H = 128, whose launches were bound by the matrix cores (12.5 k
+// cycles of fp32 matrix instructions per wave and edge tile): operands in three bf16 parts (Split3), 4.8 k cycles of
+// bf16 ones. Weights come in parts (arrange_weights_kernel: the three parts of a fragment one behind the other),
+// input rows and relu(z1) are cut on their way into LDS. Bound by the weights' way from L2 (307 KB a tile) from a few
+// tiles per compute unit on. us, fp32 instructions / parts: edge 168 tiles 15.8 / 13.8, 904 38.0 / 28.6, 1768 62.5 / 44.6; node
+// 944 tiles 39.0 / 26.1. Relative error of the embeddings against float64, nine states, geometric mean 1.44e-7 / 1.32e-7;
+// of the gradients, five states, 2.82e-7 / 2.52e-7. (H = 256: embeddings 1.95e-7 / 1.83e-7, but the heads' gradients of a state,
+// differences of its slots, came out 1.3 times as far off: left on fp32 instructions. H = 64: latency, not products.)
+template <int H>
+struct Split3Tile {
+  static constexpr int HS = H / 16, MB = H / 32, NC2 = 2 * MB;
+  static constexpr int XBYTES = 2 * HS * 3 * 1024, ZBYTES = NC2 * 3 * 1024, SBYTES = MB * BlockStage<float>::BYTES;
+  static constexpr int BYTES = XBYTES > ZBYTES + SBYTES ? XBYTES : ZBYTES + SBYTES;
+};
+template <int H, int KIND>
+__global__ __launch_bounds__(2 * H) void mlp2_split3_kernel(const Mlp2Args a) {
+  using S = Split3Tile<H>;
+  using vec = bf16x8;
+  constexpr int HS = S::HS, MB = S::MB, NC2 = S::NC2, RING = 4;   // slabs of weights in flight, three fragments each
+  static_assert(KIND == KIND_EDGE || KIND == KIND_NODE, "");
+  extern __shared__ __align__(16) char smem[];
+  const int64_t n_tiles = a.n_blocks, per_xcd = (n_tiles + 7) / 8;
+  const int64_t wt = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;      // (see mlp2_split_kernel)
+  if ((int64_t)(blockIdx.x / 8) >= per_xcd || wt >= n_tiles) return;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int64_t row0 = wt * 32;
+  int nv;
+  if constexpr (KIND == KIND_EDGE) {
+    row0 = a.tile_ptr[wt];
+    nv = a.tile_ptr[wt + 1] - (int)row0;
+  } else {
+    nv = a.n_rows - row0 < 32 ? (int)(a.n_rows - row0) : 32;
+  }
+  const int64_t row = row0 + (l32 < nv ? l32 : nv - 1);         // clamp loads; stores are guarded
+  auto weights = [&](const void *W, int s) {                    // slab s of this wave's 32 features
+    const vec *p = (const vec *)W + ((size_t)s * MB + w) * 192 + lane;
+    return Split3{{p[0], p[64], p[128]}};
+  };
+  auto shared = [&](int s) {                                    // operand s of the tile, shared through LDS
+    const vec *p = (const vec *)smem + s * 192 + lane;
+    return Split3{{p[0], p[64], p[128]}};
+  };
+  auto share = [&](int s, const Split3 &x) {
+    vec *p = (vec *)smem + s * 192 + lane;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) p[k * 64] = x.p[k];
+  };
+  f32x16 acc, corr;
+  // ---------------- layer 1
+  const float *pa, *pb;
+  if constexpr (KIND == KIND_EDGE) {
+    pa = (const float *)a.h + (size_t)a.in_src[row] * H + g * 8;
+    pb = (const float *)a.h + (size_t)a.in_dst[row] * H + g * 8;
+  } else {
+    pa = (const float *)a.h + (size_t)row * H + g * 8;
+    const int64_t ar = a.agg_src ? (int64_t)a.agg_src[row] : row;
+    pb = ar < 0 ? (const float *)a.zero_row + g * 8 : (const float *)a.agg + (size_t)ar * H + g * 8;
+  }
+  Split3 wq[RING];
+#pragma unroll
+  for (int s = 0; s < RING; ++s) wq[s] = weights(a.W1s, s);
+  constexpr int MINE = 2 * HS / MB;                             // consecutive slabs of the row this wave fetches and cuts
+  static_assert(MINE * MB == 2 * HS && HS % MINE == 0 && 2 * HS >= RING, "");
+  const int s0 = w * MINE;
+  const float *px = s0 < HS ? pa + s0 * 16 : pb + (s0 - HS) * 16;
+  f32x4 x[MINE][2];
+#pragma unroll
+  for (int i = 0; i < MINE; ++i)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) x[i][k] = *(const f32x4 *)(px + i * 16 + 4 * k);
+  [[maybe_unused]] TailRaw<8> xt;
+  if constexpr (KIND == KIND_EDGE) xt = load_tail<8>(a.edge_feat + (size_t)row * a.De, a.De, 0, g);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) { acc[r] = a.b1[32 * w + acc_row(r, g)]; corr[r] = 0.f; }
+  auto cut = [](const f32x4 &lo, const f32x4 &hi) {
+    const float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return split3(v);
+  };
+#pragma unroll
+  for (int i = 0; i < MINE; ++i) share(s0 + i, cut(x[i][0], x[i][1]));
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < 2 * HS; ++s) {
+    mma_split3(wq[s % RING], shared(s), acc, corr);
+    if (s + RING < 2 * HS || (KIND == KIND_EDGE && s + RING == 2 * HS)) wq[s % RING] = weights(a.W1s, s + RING);
+  }
+  if constexpr (KIND == KIND_EDGE) {
+    const float *xe = a.edge_feat + (size_t)row * a.De;
+    for (int s = 2 * HS; s < a.nslab1; ++s) {                   // edge attributes
+      const TailRaw<8> r = s == 2 * HS ? xt : load_tail<8>(xe, a.De, s - 2 * HS, g);
+      const Split3 wv = s == 2 * HS ? wq[(2 * HS) % RING] : weights(a.W1s, s);
+      mma_split3(wv, cut(r.q[0], r.q[1]), acc, corr);
+    }
+  }
+  // ---------------- layer 2
+#pragma unroll
+  for (int c = 0; c < RING; ++c) wq[c] = weights(a.W2s, c);
+  __syncthreads();                                              // (every wave has read its input fragments)
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    float z[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) z[j] = relu_f32(acc[8 * q + j] + corr[8 * q + j]);
+    share(2 * w + q, split3(z));
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) { acc[r] = a.b2[32 * w + acc_row(r, g)]; corr[r] = 0.f; }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < NC2; ++c) {
+    mma_split3(wq[c % RING], shared(c), acc, corr);
+    if (c + RING < NC2) wq[c % RING] = weights(a.W2s, c + RING);
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] += corr[r];
+  // ---------------- epilogue on this wave's 32 features
+  float *out = (float *)a.out;
+  char *stage = smem + S::ZBYTES + w * BlockStage<float>::BYTES;
+  if constexpr (KIND != KIND_EDGE) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = relu_f32(acc[r]);
+    store_block_via_lds<float, H>(out, row0, nv, w, lane, acc, stage);
+  } else {
+    const EdgeTileMeta m = load_edge_meta(a.in_dst, a.n_rows, row0, nv, l32);
+    f32x16 one[1] = {acc};
+    const EdgeRoute e = edge_run_sums<1>(one, m, nv, lane);
+    store_block_rows_via_lds<float, H>(out, e.dsel, w, lane, one[0], stage);
     if (e.to_c0 || e.to_c1) store_tile_rows<float, H>(a.carry, wt * 2 + (e.to_c1 ? 1 : 0), true, w, g, one[0]);
   }
 }

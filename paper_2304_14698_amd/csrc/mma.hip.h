@@ -315,3 +315,39 @@ __device__ __forceinline__ void store_block_rows_via_lds(TO *base, int dsel, int
   }
   wave_lds_fence();
 }
+
+// Eight floats as three bf16 parts each: v = p[0] + p[1] + p[2] exactly (every part is what is left, rounded to
+// nearest: the second is at most 2^-9 and the third 2^-18 of v). A product of two such numbers is the six products of parts of
+// weight 2^-18 and above, each exact in fp32, to within 2^-26 of itself and without a bias (with parts cut off towards
+// zero, which all have v's sign, what is left out added up to 2^-23, and the error of an encode to 1.7 times). Values are finite: an infinity, which only an
+// overflow can bring in here, becomes a NaN.
+struct Split3 {
+  bf16x8 p[3];
+};
+__device__ __forceinline__ Split3 split3(const float (&v)[8]) {
+  Split3 s;
+  u32x4 w[3];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float lo = v[2 * j], hi = v[2 * j + 1];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const unsigned u = cvt_pk_bf16(lo, hi);
+      w[k][j] = u;
+      lo -= __uint_as_float(u << 16);
+      hi -= __uint_as_float(u & 0xffff0000u);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) s.p[k] = __builtin_bit_cast(bf16x8, w[k]);
+  return s;
+}
+// acc + corr += a b: the leading products apart from the others, whose own rounding is then below acc's
+__device__ __forceinline__ void mma_split3(const Split3 &a, const Split3 &b, f32x16 &acc, f32x16 &corr) {
+  corr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.p[0], b.p[2], corr, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.p[0], b.p[0], acc, 0, 0, 0);
+  corr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.p[2], b.p[0], corr, 0, 0, 0);
+  corr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.p[1], b.p[1], corr, 0, 0, 0);
+  corr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.p[0], b.p[1], corr, 0, 0, 0);
+  corr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.p[1], b.p[0], corr, 0, 0, 0);
+}

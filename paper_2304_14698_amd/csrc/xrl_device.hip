@@ -42,6 +42,7 @@ inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
 struct EncMlp {           // device pointers of one encoder MLP
   const void *W1s = nullptr, *W2s = nullptr;
+  const void *W1p = nullptr, *W2p = nullptr;     // forward in parts (xrl_ctx::parts): edge and node MLPs
   const void *W2bt = nullptr, *W1bt = nullptr;   // backward: contraction over the weight's columns
   const float *b1 = nullptr, *b2 = nullptr;
   int nslab1 = 0;
@@ -61,9 +62,11 @@ struct EncMlp {           // device pointers of one encoder MLP
 //   [chunk][column block][lane][j], element j of chunk c in lane group g is contraction index
 //   2V*c + 8*(j/4) + 4*g + j%4 (the accumulator layout), lane l addresses column 32*cb + l%32; used
 //   for the forward's layer 2 and for the backward's W2^T and W1^T products.
+// SWZ_FRAGMENT3, SWZ_CHAIN3: those orders for V = 8, each fragment as the three bf16 parts of its fp32 elements, the
+//   lanes' first parts, then their second, then their third.
 // SWZ_COPY: n floats as they are.
 // W[k][f] = weights[src + k' * sk + f * sf], k' = k, or k + k_gap from k_gap_at on.
-enum { SWZ_FRAGMENT = 0, SWZ_CHAIN, SWZ_COPY };
+enum { SWZ_FRAGMENT = 0, SWZ_CHAIN, SWZ_FRAGMENT3, SWZ_CHAIN3, SWZ_COPY };
 struct SwzJob {
   int64_t dst;       // byte offset of the copy
   int64_t src, n;    // flat offset; SWZ_COPY: floats
@@ -94,14 +97,18 @@ __global__ __launch_bounds__(256) void arrange_weights_kernel(const SwzJob *jobs
     const int64_t t = i >> 6;
     const int cb = (int)(t % j.cb), s = (int)(t / j.cb);
     const float *p = w + j.src + (int64_t)(32 * cb + (l & 31)) * j.sf;
+    const bool frag = j.kind == SWZ_FRAGMENT || j.kind == SWZ_FRAGMENT3;
     float v[8];
     for (int e = 0; e < j.V; ++e) {
-      int k = j.kind == SWZ_FRAGMENT ? s * 2 * j.V + g * j.V + e : 2 * j.V * s + 8 * (e >> 2) + 4 * g + (e & 3);
+      int k = frag ? s * 2 * j.V + g * j.V + e : 2 * j.V * s + 8 * (e >> 2) + 4 * g + (e & 3);
       const bool in = k < j.K;
-      if (j.kind == SWZ_FRAGMENT && k >= j.k_gap_at) k += j.k_gap;
+      if (frag && k >= j.k_gap_at) k += j.k_gap;
       v[e] = in ? p[(int64_t)k * j.sk] : 0.f;
     }
-    if (j.bf16) {
+    if (j.kind == SWZ_FRAGMENT3 || j.kind == SWZ_CHAIN3) {
+      const Split3 parts = split3(v);
+      for (int k = 0; k < 3; ++k) *(bf16x8 *)(dst + j.dst + ((t * 3 + k) * 64 + l) * 16) = parts.p[k];
+    } else if (j.bf16) {
       *(bf16x8 *)(dst + j.dst + i * 16) = pack_bf16x8(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7]);
     } else {
       float *o = (float *)(dst + j.dst) + i * j.V;
@@ -220,6 +227,7 @@ struct xrl_ctx {
   std::vector<void *> z1_edge, z1_node;
   std::vector<uint16_t *> ym_edge, ym_node, zm_edge, zm_node;   // mask bits of y and of z1, per round
   uint16_t *ym_embed = nullptr, *zm_embed = nullptr;
+  bool parts() const { return elem == 4 && m.hidden == 128; }   // the forward's edge and node MLPs run on mlp2_split3_kernel
   // optional per-kernel timing
   bool timing = false;
   struct Span { int kind; hipEvent_t a, b; };
@@ -608,7 +616,7 @@ int plan_weights(xrl_ctx *c) {
   std::vector<SwzJob> jobs;
   auto put = [&](SwzJob j) {
     j.dst = (int64_t)(off = align_up(off));
-    off += (size_t)j.groups * j.V * (j.bf16 ? 2 : 4);
+    off += (size_t)j.groups * (j.kind == SWZ_FRAGMENT3 || j.kind == SWZ_CHAIN3 ? 48 : j.V * (j.bf16 ? 2 : 4));
     jobs.push_back(j);
     return (size_t)j.dst;
   };
@@ -626,7 +634,7 @@ int plan_weights(xrl_ctx *c) {
     j.groups = (int64_t)(Kc / (2 * V)) * j.cb * 64;
     return put(j);
   };
-  struct Ref { size_t w1, w2, w2bt, w1bt = 0, w1x = 0; int ns, nsx = 0; };
+  struct Ref { size_t w1, w2, w2bt, w1bt = 0, w1x = 0, w1p = 0, w2p = 0; int ns, nsx = 0; };
   std::vector<Ref> refs;
   const bool b16 = c->elem == 2;
   auto add = [&](const MlpRef &r, bool embed) {
@@ -641,6 +649,17 @@ int plan_weights(xrl_ctx *c) {
     ref.w2 = chain(r.w[1], H, H, H, 1);
     ref.w2bt = chain(r.w[1], H, H, 1, H);               // W2^T
     if (!embed) ref.w1bt = chain(r.w[0], H, 2 * H, 1, H);   // (W1^T)[:, :2H]: edge and node MLPs
+    if (!embed && c->parts()) {                         // forward of fp32 edge and node MLPs: in parts
+      auto parts = [&](int64_t w, int K, int kind) {
+        SwzJob j = {};
+        j.kind = kind; j.V = 8; j.K = K; j.cb = H / 32; j.src = w; j.sk = H; j.sf = 1;
+        j.k_gap_at = 1 << 30;
+        j.groups = (int64_t)((K + 15) / 16) * j.cb * 64;
+        return put(j);
+      };
+      ref.w1p = parts(r.w[0], r.d_in[0], SWZ_FRAGMENT3);
+      ref.w2p = parts(r.w[1], H, SWZ_CHAIN3);
+    }
     refs.push_back(ref);
   };
   add(c->L.embed, true);
@@ -691,6 +710,8 @@ int plan_weights(xrl_ctx *c) {
   auto bind = [&](EncMlp &e, const Ref &ref, const MlpRef &r) {
     e.W1s = c->d_swz + ref.w1;
     e.W2s = c->d_swz + ref.w2;
+    e.W1p = c->d_swz + ref.w1p;
+    e.W2p = c->d_swz + ref.w2p;
     e.W2bt = c->d_swz + ref.w2bt;
     e.W1bt = c->d_swz + ref.w1bt;
     e.b1 = c->d_w + r.b[0];
@@ -956,12 +977,32 @@ int launch_round(xrl_ctx *c, RoundArgs &a) {
   return fail(XRL_ERR_UNSUPPORTED, "hidden = %d", c->m.hidden);
 }
 
+template <int H, int KIND>
+int launch_mlp2_split3(xrl_ctx *c, const Mlp2Args &a) {
+  using S = Split3Tile<H>;
+  auto kern = mlp2_split3_kernel<H, KIND>;
+  static bool attr_set = false;          // one attribute per kernel instantiation
+  if (!attr_set) {
+    HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, S::BYTES));
+    attr_set = true;
+  }
+  kern<<<dim3((unsigned)((a.n_blocks + 7) / 8 * 8)), dim3(2 * H), S::BYTES, c->stream>>>(a);
+  HIP_TRY(hipGetLastError());
+  return XRL_OK;
+}
+
 template <typename T, int H>
 int launch_mlp2_h(xrl_ctx *c, int kind, const Mlp2Args &a) {
   if (a.n_rows <= 0) return XRL_OK;
+  if constexpr (sizeof(T) == 4 && H == 128) {              // (xrl_ctx::parts)
+    if (kind == KIND_EDGE) return launch_mlp2_split3<H, KIND_EDGE>(c, a);
+    if (kind == KIND_NODE) return launch_mlp2_split3<H, KIND_NODE>(c, a);
+    return launch_mlp2_split<float, T, H, KIND_EMBED>(c, a);
+  } else {
   if (kind == KIND_EMBED) return launch_mlp2_split<float, T, H, KIND_EMBED>(c, a);
   if (kind == KIND_EDGE) return launch_mlp2_split<T, T, H, KIND_EDGE>(c, a);
   return launch_mlp2_split<T, T, H, KIND_NODE>(c, a);
+  }
 }
 
 // Persistent LDS-resident-weights variant (bf16, H <= 128, edge and node kinds).
@@ -2354,7 +2395,9 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   set_graph(lev(0));
   a.carry = c->carry; a.zero_row = c->zero_row;
   auto set_w = [&](const EncMlp &e) {
-    a.W1s = e.W1s; a.W2s = e.W2s; a.b1 = e.b1; a.b2 = e.b2; a.nslab1 = e.nslab1;
+    const bool parts = c->parts() && &e != &c->embed;
+    a.W1s = parts ? e.W1p : e.W1s; a.W2s = parts ? e.W2p : e.W2s; a.b1 = e.b1; a.b2 = e.b2;
+    a.nslab1 = parts ? (e.nslab1 + 1) / 2 : e.nslab1;       // (in parts: slabs of sixteen columns)
     a.W1x = e.W1x; a.nslabx = e.nslabx; a.table = e.table;
   };
   set_w(c->embed);
