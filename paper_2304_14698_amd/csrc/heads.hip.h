@@ -5,10 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+#include <type_traits>
 #include "segsum.hip.h"
-
-// Rows per block of the row-MLP kernels: 8 reuses every weight read eight times (large batches);
-// 1 gives one block per row so that small batches still spread over the chip.
 
 // Up to three affine layers over rows of [in1 | in2]; ReLU after every layer except, when
 // relu_last == 0, the last. Optionally stores every layer's output (post-activation) for the
@@ -24,29 +22,49 @@ struct RowMlpArgs {
   float *act[3];           // nullable each
 };
 
-// One row through the layers of `a`, all 256 threads of the block cooperating. These kernels are
-// bound by memory latency, not bandwidth, so a layer's weights are requested in as few dependent
-// rounds as possible: with d_out a multiple of 4 (and the matrix 16-byte aligned) a thread owns
-// four adjacent outputs and one of 256 / (d_out / 4) slices of the contraction, loads its weights
-// 16 bytes at a time, sixteen loads in flight, and the slices' partial sums are added in slice
-// order; other layers (a single output, say) split the contraction the same way with scalar loads.
-// cur holds the input row (d_in[0] floats) on entry; cur/nxt: >= widest layer; part: 1024 floats,
-// 16-byte aligned. `row` indexes the stores to a.act[l] and a.out. COHERENT_OUT stores a.out with
-// device scope, for a consumer in another block of the same launch.
+// ROWS rows (row .. row + ROWS - 1, those below a.n_rows stored) through the layers of `a`, all 256 threads of the block
+// cooperating. These kernels are bound by memory latency and, from about two blocks per compute unit on, by
+// every block reading all the weights from L2; so a layer's weights are requested in as few dependent
+// rounds as possible, and several rows share them where there are rows enough: with d_out a multiple of 4 (and the
+// matrix 16-byte aligned) a thread owns four adjacent outputs and one of 256 / (d_out / 4) slices of the
+// contraction, loads its weights 16 bytes at a time, sixteen loads in flight (a remainder as sixteen, eight or
+// four, whose missing rows re-read the last one and count as zeros), and the slices' partial sums are added in slice
+// order; other layers (a single output, say) split the contraction the same way with scalar loads. A row's
+// sums do not depend on ROWS.
+// cur holds the input rows (d_in[0] floats each, ld apart) on entry; cur/nxt: >= ROWS * ld floats, ld >= widest layer;
+// part: ROWS * 1024 floats, 16-byte aligned. COHERENT_OUT stores a.out with device scope, for a consumer in
+// another block of the same launch.
+template <typename F>
+__device__ __forceinline__ void in_batches(int k0, int k1, F f) {
+  for (int k = k0; k < k1;) {
+    if (k1 - k > 8) { f(k, std::integral_constant<int, 16>()); k += 16; }
+    else if (k1 - k > 4) { f(k, std::integral_constant<int, 8>()); k += 8; }
+    else { f(k, std::integral_constant<int, 4>()); k += 4; }
+  }
+}
 template <bool COHERENT_OUT = false>
 __device__ __forceinline__ void store_row_out(float *p, float y) {
   if constexpr (COHERENT_OUT) __hip_atomic_store(p, y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   else *p = y;
 }
 
-template <bool COHERENT_OUT = false>
+template <bool COHERENT_OUT = false, int ROWS = 1>
 __device__ __forceinline__ void block_row_mlp(const RowMlpArgs &a, float *cur, float *nxt, float *part,
-                                              int64_t row) {
+                                              int64_t row, int ld = 0) {
   const int t = threadIdx.x;
   for (int l = 0; l < a.n_layers; ++l) {
     const int din = a.d_in[l], dout = a.d_out[l];
     const bool relu = a.relu_last || (l + 1 < a.n_layers);
     const float *W = a.W[l];
+    auto finish = [&](int r, int f, float v) {
+      v += a.b[l][f];
+      const float y = relu ? fmaxf(v, 0.f) : v;
+      nxt[r * ld + f] = y;
+      if (ROWS == 1 || row + r < a.n_rows) {
+        if (a.act[l]) a.act[l][(row + r) * dout + f] = y;
+        if (l + 1 == a.n_layers) store_row_out<COHERENT_OUT>(a.out + (row + r) * dout + f, y);
+      }
+    };
     if ((dout & 3) == 0 && dout <= 1024 && ((uintptr_t)W & 15) == 0) {
       const int fq = dout >> 2;                           // 16-byte columns
       int KQ = 256 / fq;                                  // slices of the contraction
@@ -56,36 +74,35 @@ __device__ __forceinline__ void block_row_mlp(const RowMlpArgs &a, float *cur, f
       if (kq < KQ) {
         const int k0 = kq * kc, k1 = (k0 + kc) < din ? (k0 + kc) : din;
         const float4 *Wp = (const float4 *)W + fl;
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        int k = k0;
-        for (; k + 16 <= k1; k += 16) {
-          float4 w[16];
+        float4 acc[ROWS];
 #pragma unroll
-          for (int i = 0; i < 16; ++i) w[i] = Wp[(size_t)(k + i) * fq];
+        for (int r = 0; r < ROWS; ++r) acc[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+        in_batches(k0, k1, [&](int k, auto batch) {
+          constexpr int U = decltype(batch)::value;
+          float4 w[U];
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const float x = cur[k + i];
-            acc.x = fmaf(x, w[i].x, acc.x); acc.y = fmaf(x, w[i].y, acc.y);
-            acc.z = fmaf(x, w[i].z, acc.z); acc.w = fmaf(x, w[i].w, acc.w);
+          for (int i = 0; i < U; ++i) {
+            w[i] = Wp[(size_t)(k + i < k1 ? k + i : k1 - 1) * fq];
+            if (k + i >= k1) w[i] = make_float4(0.f, 0.f, 0.f, 0.f);
           }
-        }
-        for (; k < k1; ++k) {
-          const float4 w = Wp[(size_t)k * fq];
-          const float x = cur[k];
-          acc.x = fmaf(x, w.x, acc.x); acc.y = fmaf(x, w.y, acc.y);
-          acc.z = fmaf(x, w.z, acc.z); acc.w = fmaf(x, w.w, acc.w);
-        }
-        ((float4 *)part)[kq * fq + fl] = acc;
+#pragma unroll
+          for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+            for (int i = 0; i < U; ++i) {
+              const float x = k + i < k1 ? cur[r * ld + k + i] : 0.f;
+              acc[r].x = fmaf(x, w[i].x, acc[r].x); acc[r].y = fmaf(x, w[i].y, acc[r].y);
+              acc[r].z = fmaf(x, w[i].z, acc[r].z); acc[r].w = fmaf(x, w[i].w, acc[r].w);
+            }
+        });
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) ((float4 *)part)[r * 256 + kq * fq + fl] = acc[r];
       }
       __syncthreads();
-      for (int f = t; f < dout; f += 256) {
-        float v = part[f];
-        for (int q = 1; q < KQ; ++q) v += part[q * dout + f];
-        v += a.b[l][f];
-        const float y = relu ? fmaxf(v, 0.f) : v;
-        nxt[f] = y;
-        if (a.act[l]) a.act[l][row * dout + f] = y;
-        if (l + 1 == a.n_layers) store_row_out<COHERENT_OUT>(a.out + row * dout + f, y);
+      for (int i = t; i < ROWS * dout; i += 256) {
+        const int r = i / dout, f = i - r * dout;
+        float v = part[r * 1024 + f];
+        for (int q = 1; q < KQ; ++q) v += part[r * 1024 + q * dout + f];
+        finish(r, f, v);
       }
       __syncthreads();
     } else {
@@ -97,34 +114,39 @@ __device__ __forceinline__ void block_row_mlp(const RowMlpArgs &a, float *cur, f
       const int k0 = kq * kc, k1 = (k0 + kc) < din ? (k0 + kc) : din;
       for (int f0 = 0; f0 < dout; f0 += fw) {
         const int f = f0 + fl;
-        float acc = 0.f;
-        if (f < dout) {
-          int k = k0;
-          for (; k + 16 <= k1; k += 16) {
-            float w[16];
+        float acc[ROWS];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) w[i] = W[(size_t)(k + i) * dout + f];
+        for (int r = 0; r < ROWS; ++r) acc[r] = 0.f;
+        if (f < dout)
+          in_batches(k0, k1, [&](int k, auto batch) {
+            constexpr int U = decltype(batch)::value;
+            float w[U];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc = fmaf(cur[k + i], w[i], acc);
-          }
-          for (; k < k1; ++k) acc = fmaf(cur[k], W[(size_t)k * dout + f], acc);
-        }
+            for (int i = 0; i < U; ++i) {
+              w[i] = W[(size_t)(k + i < k1 ? k + i : k1 - 1) * dout + f];
+              if (k + i >= k1) w[i] = 0.f;
+            }
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+              for (int i = 0; i < U; ++i) acc[r] = fmaf(k + i < k1 ? cur[r * ld + k + i] : 0.f, w[i], acc[r]);
+          });
         if (KQ > 1) {
-          part[t] = acc;
+#pragma unroll
+          for (int r = 0; r < ROWS; ++r) part[r * 1024 + t] = acc[r];
           __syncthreads();
-          if (kq == 0) {
-            acc = part[fl];
-            for (int q = 1; q < KQ; ++q) acc += part[q * fw + fl];
+          for (int i = t; i < ROWS * fw; i += 256) {
+            const int r = i / fw, fi = i - r * fw;
+            if (f0 + fi >= dout) continue;
+            float v = part[r * 1024 + fi];
+            for (int q = 1; q < KQ; ++q) v += part[r * 1024 + q * fw + fi];
+            finish(r, f0 + fi, v);
           }
+          __syncthreads();
+        } else if (f < dout) {
+#pragma unroll
+          for (int r = 0; r < ROWS; ++r) finish(r, f, acc[r]);
         }
-        if (kq == 0 && f < dout) {
-          acc += a.b[l][f];
-          const float y = relu ? fmaxf(acc, 0.f) : acc;
-          nxt[f] = y;
-          if (a.act[l]) a.act[l][row * dout + f] = y;
-          if (l + 1 == a.n_layers) store_row_out<COHERENT_OUT>(a.out + row * dout + f, y);
-        }
-        if (KQ > 1) __syncthreads();
       }
       __syncthreads();
     }
@@ -132,13 +154,14 @@ __device__ __forceinline__ void block_row_mlp(const RowMlpArgs &a, float *cur, f
   }
 }
 
+// One, two or four rows per block by block_row_mlp; eight with a thread per output, which is enough from 4096 rows on.
 template <int ROWMLP_ROWS>
 __global__ __launch_bounds__(256) void rowmlp_kernel(const RowMlpArgs a) {
-  // two buffers of ROWMLP_ROWS * dmax floats; with one row per block, 1024 floats of partial sums first
+  // two buffers of ROWMLP_ROWS * dmax floats; up to four rows per block, 1024 floats of partial sums a row first
   extern __shared__ __align__(16) float sm[];
   int dmax = a.d_in[0];
   for (int l = 0; l < a.n_layers; ++l) dmax = a.d_out[l] > dmax ? a.d_out[l] : dmax;
-  float *cur = sm + (ROWMLP_ROWS == 1 ? 1024 : 0), *nxt = cur + ROWMLP_ROWS * dmax;
+  float *cur = sm + (ROWMLP_ROWS <= 4 ? ROWMLP_ROWS * 1024 : 0), *nxt = cur + ROWMLP_ROWS * dmax;
   const int64_t row0 = (int64_t)blockIdx.x * ROWMLP_ROWS;
   for (int i = threadIdx.x; i < ROWMLP_ROWS * a.d_in[0]; i += blockDim.x) {
     const int r = i / a.d_in[0], k = i - r * a.d_in[0];
@@ -148,8 +171,8 @@ __global__ __launch_bounds__(256) void rowmlp_kernel(const RowMlpArgs a) {
     cur[r * dmax + k] = v;
   }
   __syncthreads();
-  if constexpr (ROWMLP_ROWS == 1) {
-    block_row_mlp(a, cur, nxt, sm, row0);
+  if constexpr (ROWMLP_ROWS <= 4) {
+    block_row_mlp<false, ROWMLP_ROWS>(a, cur, nxt, sm, row0, dmax);
     return;
   }
   for (int l = 0; l < a.n_layers; ++l) {
@@ -248,8 +271,9 @@ __device__ __forceinline__ void graph_readout_block(const T *h, const int n0, co
   block_row_mlp(mlp, cur, nxt, part, g);
 }
 
+// (five blocks per compute unit: many graphs, update of 1040, take 20.9 us so and 25.8 with four)
 template <typename T, int VEC, int UF, bool MAPPED>
-__global__ __launch_bounds__(256) void graph_readout_kernel(const T *h, const int32_t *graph_node_ptr, int H,
+__global__ __launch_bounds__(256, 5) void graph_readout_kernel(const T *h, const int32_t *graph_node_ptr, int H,
                                                             int mean, float *pool, const RowMlpArgs mlp,
                                                             const int32_t *row_of) {
   extern __shared__ __align__(16) float sm[];   // [256 * VEC] partial sums, then the MLP's buffers
@@ -267,62 +291,56 @@ __global__ void mean_scale_kernel(float *pool, const int32_t *graph_node_ptr, in
   pool[i] = pool[i] / (float)(n > 1 ? n : 1);
 }
 
-// Block-wide reductions over 256 threads in a fixed tree order (deterministic).
+// Block-wide reductions over 256 threads in a fixed order: inside a wave by exchange, then the four waves' in order.
+// red: 8 words of LDS (the result is read by all before it is written again).
 __device__ __forceinline__ float block_sum(float v, float *red) {
-  const int t = threadIdx.x;
-  red[t] = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (t < s) red[t] += red[t + s];
-    __syncthreads();
-  }
-  const float r = red[0];
+  const float r = ((red[0] + red[1]) + red[2]) + red[3];
   __syncthreads();
   return r;
 }
-
-// One block per state: masked log-softmax over the state's slots, entropy, first-max action,
-// the mean embedding of the valid slots and, on it, the value head (value.n_layers == 0 skips it).
-__global__ __launch_bounds__(256) void state_policy_kernel(
-    const float *logit, const uint8_t *mask, const int32_t *state_graph_ptr, const float *emb,
-    int H, float *logp, float *entropy, int32_t *action, float *zmean, const RowMlpArgs value) {
-  __shared__ float red[256];
-  __shared__ int redi[256];
-  __shared__ __align__(16) float zbuf[1024];                      // partial sums of the mean embedding
-  __shared__ __align__(16) float vcur[512], vnxt[512];            // value head: layer input / output
-  const int s = blockIdx.x, t = threadIdx.x;
-  const int j0 = state_graph_ptr[s], j1 = state_graph_ptr[s + 1];
-  // max valid logit and the lowest slot index attaining it
-  float best = -INFINITY;
-  int besti = 0x7fffffff;
-  for (int j = j0 + t; j < j1; j += 256)
-    if (mask[j]) {
-      const float l = logit[j];
-      if (l > best || (l == best && j < besti)) { best = l; besti = j; }
-    }
-  red[t] = best; redi[t] = besti;
-  __syncthreads();
-  for (int k = 128; k > 0; k >>= 1) {
-    if (t < k) {
-      const float o = red[t + k];
-      const int oi = redi[t + k];
-      if (o > red[t] || (o == red[t] && oi < redi[t])) { red[t] = o; redi[t] = oi; }
-    }
-    __syncthreads();
+struct BestSlot {
+  float value;
+  int index;             // lowest index that has it
+};
+__device__ __forceinline__ BestSlot better(const BestSlot &a, const BestSlot &b) {
+  return b.value > a.value || (b.value == a.value && b.index < a.index) ? b : a;
+}
+__device__ __forceinline__ BestSlot block_best(BestSlot b, float *red) {
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const BestSlot other{__shfl_xor(b.value, o), __shfl_xor(b.index, o)};
+    b = better(b, other);
   }
-  const float M = red[0];
-  const int arg = redi[0];
+  const int w = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) { red[w] = b.value; red[4 + w] = __int_as_float(b.index); }
   __syncthreads();
+  for (int k = 0; k < 4; ++k) b = better(b, BestSlot{red[k], __float_as_int(red[4 + k])});
+  __syncthreads();
+  return b;
+}
+// A state's masked log-softmax, entropy and first-max action from its slots' logits (ld: reads one).
+template <typename Load>
+__device__ __forceinline__ float state_softmax(Load ld, const uint8_t *mask, int j0, int j1, float *logp, float *entropy, int32_t *action,
+                                               float *red) {
+  const int t = threadIdx.x;
+  BestSlot best{-INFINITY, 0x7fffffff};
+  for (int j = j0 + t; j < j1; j += 256)
+    if (mask[j]) best = better(best, BestSlot{ld(j), j});
+  best = block_best(best, red);
   float se = 0.f;
   int cnt = 0;
   for (int j = j0 + t; j < j1; j += 256)
-    if (mask[j]) { se += expf(logit[j] - M); ++cnt; }
-  const float lse = M + logf(block_sum(se, red));
+    if (mask[j]) { se += expf(ld(j) - best.value); ++cnt; }
+  const float lse = best.value + logf(block_sum(se, red));
   const float nvalid = block_sum((float)cnt, red);
   float ent = 0.f;
   for (int j = j0 + t; j < j1; j += 256) {
     if (mask[j]) {
-      const float lp = logit[j] - lse;
+      const float lp = ld(j) - lse;
       logp[j] = lp;
       ent -= expf(lp) * lp;
     } else {
@@ -330,7 +348,21 @@ __global__ __launch_bounds__(256) void state_policy_kernel(
     }
   }
   ent = block_sum(ent, red);
-  if (t == 0) { entropy[s] = ent; action[s] = arg - j0; }
+  if (t == 0) { *entropy = ent; *action = best.index - j0; }
+  return nvalid;
+}
+
+// One block per state: masked log-softmax over the state's slots, entropy, first-max action,
+// the mean embedding of the valid slots and, on it, the value head (value.n_layers == 0 skips it).
+__global__ __launch_bounds__(256) void state_policy_kernel(
+    const float *logit, const uint8_t *mask, const int32_t *state_graph_ptr, const float *emb,
+    int H, float *logp, float *entropy, int32_t *action, float *zmean, const RowMlpArgs value) {
+  __shared__ float red[8];
+  __shared__ __align__(16) float zbuf[1024];                      // partial sums of the mean embedding
+  __shared__ __align__(16) float vcur[512], vnxt[512];            // value head: layer input / output
+  const int s = blockIdx.x, t = threadIdx.x;
+  const int j0 = state_graph_ptr[s], j1 = state_graph_ptr[s + 1];
+  const float nvalid = state_softmax([&](int j) { return logit[j]; }, mask, j0, j1, logp, entropy + s, action + s, red);
   // mean embedding of the valid slots: H / 4 threads cover a row with 16-byte loads, the 1024 / H
   // thread groups take every (1024/H)-th slot, eight loads in flight each; the groups' partial
   // sums are combined in group order
@@ -367,25 +399,28 @@ __global__ __launch_bounds__(256) void state_policy_kernel(
   if (value.n_layers > 0) block_row_mlp(value, vcur, vnxt, zbuf, s);
 }
 
-// Both heads in one launch for batches of at most a few thousand slots. Blocks [0, G): the policy
-// MLP of one slot, and the block that finishes a state's last slot (a per-state counter, which it
-// also resets) does that state's masked log-softmax, entropy and first-max action. Blocks
-// [G, G + S): the mean embedding of a state's valid slots and the value head on it, independent of
-// the policy blocks. Results are the same as rowmlp_kernel<1> followed by state_policy_kernel.
+// Both heads in one launch for batches of at most a few thousand slots. The first blocks: the policy
+// MLP of ROWS slots, of one or of several states; the block that finishes a state's last slot (a per-state
+// counter, which it also resets) does that state's masked log-softmax, entropy and first-max action. The last
+// S blocks: the mean embedding of a state's valid slots and the value head on it, independent of
+// the policy blocks. Results are the same as rowmlp_kernel<1> followed by state_policy_kernel, for any ROWS.
 // Logits cross blocks through device-scope stores and loads (each completed before the block's
-// counter increment is issued), so no cache write-back or invalidation is needed.
+// counter increment is issued), so no cache write-back or invalidation is needed. us before ROWS: 1040 slots of H = 128
+// 31.6, now 22.6; 2096 slots 48 and 25.
+template <int ROWS>
 __global__ __launch_bounds__(256) void policy_value_kernel(
     const RowMlpArgs policy, const uint8_t *mask, const int32_t *state_graph_ptr, int G, int S, int H,
     int32_t *counter, float *logp, float *entropy, int32_t *action, float *zmean, const RowMlpArgs value) {
-  __shared__ __align__(16) float part[1024];
-  __shared__ __align__(16) float bufa[512], bufb[512];
-  __shared__ float red[256];
+  constexpr int LD = 512;
+  __shared__ __align__(16) float part[ROWS * 1024];
+  __shared__ __align__(16) float bufa[ROWS * LD], bufb[ROWS * LD];
+  __shared__ float red[8];
   __shared__ int redi[256];
-  __shared__ int sh_state, sh_last;
-  const int t = threadIdx.x;
-  if ((int)blockIdx.x >= G) {
+  __shared__ int sh_state[ROWS], sh_done[ROWS], sh_n_done;
+  const int t = threadIdx.x, policy_blocks = (G + ROWS - 1) / ROWS;
+  if ((int)blockIdx.x >= policy_blocks) {
     // ---- value head of state s
-    const int s = blockIdx.x - G;
+    const int s = blockIdx.x - policy_blocks;
     const int j0 = state_graph_ptr[s], j1 = state_graph_ptr[s + 1];
     const float *emb = policy.in1;
     const int tpr = H / 4, ng = 256 / tpr, c4 = (t % tpr) * 4, q = t / tpr;   // H is 64, 128 or 256
@@ -424,65 +459,47 @@ __global__ __launch_bounds__(256) void policy_value_kernel(
     if (value.n_layers > 0) block_row_mlp(value, bufa, bufb, part, s);
     return;
   }
-  // ---- policy MLP of slot j; meanwhile find the slot's state
-  const int j = blockIdx.x;
-  if (t == 0) sh_state = -1;
-  for (int k = t; k < H; k += 256) bufa[k] = policy.in1[(size_t)j * H + k];
-  __syncthreads();
-  for (int s = t; s < S; s += 256)
-    if (state_graph_ptr[s] <= j && j < state_graph_ptr[s + 1]) sh_state = s;
-  block_row_mlp<true>(policy, bufa, bufb, part, j);
-  __builtin_amdgcn_s_waitcnt(0x0F70);                              // vmcnt(0): this wave's logit store has completed
-  __syncthreads();
-  const int s = sh_state;
-  if (s < 0) return;                                               // (a slot outside every state: not packed by this library)
-  const int j0 = state_graph_ptr[s], j1 = state_graph_ptr[s + 1];
-  if (t == 0) {
-    const int done = atomicAdd(&counter[s], 1);
-    sh_last = done == j1 - j0 - 1;
-    if (sh_last) counter[s] = 0;                                   // ready for the next launch
+  // ---- policy MLP of the block's slots; meanwhile find their states
+  const int slot0 = blockIdx.x * ROWS;
+  if (t < ROWS) sh_state[t] = -1;
+  for (int i = t; i < ROWS * H; i += 256) {
+    const int r = i / H, k = i - r * H;
+    bufa[r * LD + k] = slot0 + r < G ? policy.in1[(size_t)(slot0 + r) * H + k] : 0.f;
   }
   __syncthreads();
-  if (!sh_last) return;
+  for (int s = t; s < S; s += 256) {
+    const int a = state_graph_ptr[s], z = state_graph_ptr[s + 1];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+      if (a <= slot0 + r && slot0 + r < z) sh_state[r] = s;
+  }
+  block_row_mlp<true, ROWS>(policy, bufa, bufb, part, slot0, LD);
+  __builtin_amdgcn_s_waitcnt(0x0F70);                              // vmcnt(0): this wave's logit stores have completed
+  __syncthreads();
+  if (t == 0) {
+    int n = 0;
+    for (int r = 0; r < ROWS;) {                                   // the block's slots, state by state (-1: past the last slot)
+      const int s = sh_state[r];
+      int k = 1;
+      while (r + k < ROWS && sh_state[r + k] == s) ++k;
+      if (s >= 0) {
+        const int slots = state_graph_ptr[s + 1] - state_graph_ptr[s];
+        if (atomicAdd(&counter[s], k) + k == slots) {
+          counter[s] = 0;                                          // ready for the next launch
+          sh_done[n++] = s;
+        }
+      }
+      r += k;
+    }
+    sh_n_done = n;
+  }
+  __syncthreads();
   const float *logit = policy.out;
   auto ld = [&](int i) { return __hip_atomic_load(logit + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-  // max valid logit and the lowest slot index attaining it
-  float best = -INFINITY;
-  int besti = 0x7fffffff;
-  for (int i = j0 + t; i < j1; i += 256)
-    if (mask[i]) {
-      const float l = ld(i);
-      if (l > best || (l == best && i < besti)) { best = l; besti = i; }
-    }
-  red[t] = best; redi[t] = besti;
-  __syncthreads();
-  for (int k = 128; k > 0; k >>= 1) {
-    if (t < k) {
-      const float o = red[t + k];
-      const int oi = redi[t + k];
-      if (o > red[t] || (o == red[t] && oi < redi[t])) { red[t] = o; redi[t] = oi; }
-    }
-    __syncthreads();
+  for (int i = 0; i < sh_n_done; ++i) {
+    const int s = sh_done[i];
+    (void)state_softmax(ld, mask, state_graph_ptr[s], state_graph_ptr[s + 1], logp, entropy + s, action + s, red);
   }
-  const float M = red[0];
-  const int arg = redi[0];
-  __syncthreads();
-  float se = 0.f;
-  for (int i = j0 + t; i < j1; i += 256)
-    if (mask[i]) se += expf(ld(i) - M);
-  const float lse = M + logf(block_sum(se, red));
-  float ent = 0.f;
-  for (int i = j0 + t; i < j1; i += 256) {
-    if (mask[i]) {
-      const float lp = ld(i) - lse;
-      logp[i] = lp;
-      ent -= expf(lp) * lp;
-    } else {
-      logp[i] = -INFINITY;
-    }
-  }
-  ent = block_sum(ent, red);
-  if (t == 0) { entropy[s] = ent; action[s] = arg - j0; }
 }
 
 // dJ/dlogit per slot from (dlogp, dentropy) and the forward's logp/entropy; one block per state.
@@ -490,7 +507,7 @@ __global__ __launch_bounds__(256) void policy_value_kernel(
 __global__ __launch_bounds__(256) void state_policy_bwd_kernel(
     const float *logp, const float *entropy, const uint8_t *mask, const int32_t *state_graph_ptr,
     const float *dlogp, const float *dentropy, float *dlogit, float *inv_nvalid) {
-  __shared__ float red[256];
+  __shared__ float red[8];
   const int s = blockIdx.x, t = threadIdx.x;
   const int j0 = state_graph_ptr[s], j1 = state_graph_ptr[s + 1];
   float cs = 0.f;
@@ -557,11 +574,24 @@ __device__ __forceinline__ void rowmlp_bwd_block(const RowMlpBwdArgs &a, int blo
 #pragma unroll
       for (int r = 0; r < ROWMLP_ROWS; ++r) acc[r] = 0.f;
       const float *wrow = a.W[l] + (size_t)k * dout;
-#pragma unroll 8
-      for (int f = 0; f < dout; ++f) {
-        const float w = wrow[f];
+      // aligned rows by 16-byte pieces, four in flight: us, 1040 rows of H = 128 19.1, now 15.9; 262 rows 15.9 and 13.6
+      if ((dout & 15) == 0 && ((uintptr_t)a.W[l] & 15) == 0) {
+        for (int f = 0; f < dout; f += 16) {
+          f32x4 w[4];
 #pragma unroll
-        for (int r = 0; r < ROWMLP_ROWS; ++r) acc[r] = fmaf(cur[r * dmax + f], w, acc[r]);
+          for (int i = 0; i < 4; ++i) w[i] = *(const f32x4 *)(wrow + f + 4 * i);
+#pragma unroll
+          for (int r = 0; r < ROWMLP_ROWS; ++r)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[r] = fmaf(cur[r * dmax + f + i], w[i / 4][i % 4], acc[r]);
+        }
+      } else {
+#pragma unroll 8
+        for (int f = 0; f < dout; ++f) {
+          const float w = wrow[f];
+#pragma unroll
+          for (int r = 0; r < ROWMLP_ROWS; ++r) acc[r] = fmaf(cur[r * dmax + f], w, acc[r]);
+        }
       }
 #pragma unroll
       for (int r = 0; r < ROWMLP_ROWS; ++r) {
@@ -718,7 +748,7 @@ __global__ __launch_bounds__(256) void ppo_objective_kernel(
     const float *logp, const float *value, const float *entropy, const int32_t *state_graph_ptr,
     const uint8_t *mask, const int32_t *action, const float *old_logp, const float *advantage, const float *v_target,
     int S, float eps, float c1, float c2, float *J, float *dlogp, float *dvalue, float *dentropy) {
-  __shared__ float red[256];
+  __shared__ float red[8];
   const int t = threadIdx.x;
   const float inv = 1.f / (float)(S > 0 ? S : 1);
   float clip = 0.f, vf = 0.f, ent = 0.f, bad = 0.f;

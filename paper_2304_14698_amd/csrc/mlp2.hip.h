@@ -574,7 +574,7 @@ __global__ __launch_bounds__(2 * H) void mlp2_split_kernel(const Mlp2Args a) {
 // input rows and relu(z1) are cut on their way into LDS. Bound by the weights' way from L2 (307 KB a tile) from a few
 // tiles per compute unit on. us, fp32 instructions / parts: edge 168 tiles 15.8 / 13.8, 904 38.0 / 28.6, 1768 62.5 / 44.6; node
 // 944 tiles 39.0 / 26.1. Relative error of the embeddings against float64, nine states, geometric mean 1.44e-7 / 1.32e-7;
-// of the gradients, five states, 2.82e-7 / 2.52e-7. (H = 256: embeddings 1.95e-7 / 1.83e-7, but the heads' gradients of a state,
+// of the gradients, five states, 2.82e-7 / 2.54e-7. (H = 256: embeddings 1.95e-7 / 1.83e-7, but the heads' gradients of a state,
 // differences of its slots, came out 1.3 times as far off: left on fp32 instructions. H = 64: latency, not products.)
 template <int H>
 struct Split3Tile {

@@ -1204,17 +1204,30 @@ RowMlpArgs rowmlp_args(xrl_ctx *c, const MlpRef &r, bool relu_last, const float 
   return a;
 }
 
+// Rows per block of block_row_mlp's kernels, which share a layer's weights: where the blocks would fill less than half of the
+// chip a row's latency counts; from four rows per compute unit on the weights' way from L2 does. us of policy_value_kernel at
+// 1 / 2 / 4 rows per block: H = 128, 13 slots 13.9 / 15.6 / 19.0, 129 17.1 / 16.4 / 19.2, 262 18.7 / 18.0 / 20.4, 2096
+// 50.2 / 36.5 / 26.3; H = 256, 257 slots 43.3 / 37.4 / 36.7.
+template <typename Go>
+void by_rows(const xrl_ctx *c, int64_t n, Go go) {
+  if (n < c->n_cu / 2) go(std::integral_constant<int, 1>());
+  else if (n < 4 * c->n_cu) go(std::integral_constant<int, 2>());
+  else go(std::integral_constant<int, 4>());
+}
+
 int launch_rowmlp(xrl_ctx *c, const MlpRef &r, bool relu_last, const float *in1, int w1,
                   const float *in2, int w2, int64_t n_rows, float *out, float *const *act) {
   if (n_rows <= 0) return XRL_OK;
   int dmax = 0;
   const RowMlpArgs a = rowmlp_args(c, r, relu_last, in1, w1, in2, w2, n_rows, out, act, &dmax);
-  if (n_rows <= 4096) {
-    rowmlp_kernel<1><<<dim3((unsigned)n_rows), dim3(256), (size_t)(1024 + 2 * dmax) * sizeof(float), c->stream>>>(a);
-  } else {
-    const unsigned blocks = (unsigned)((n_rows + 7) / 8);
-    rowmlp_kernel<8><<<dim3(blocks), dim3(256), (size_t)2 * 8 * dmax * sizeof(float), c->stream>>>(a);
-  }
+  if (n_rows <= 4096)
+    by_rows(c, n_rows, [&](auto rows) {
+      constexpr int ROWS = decltype(rows)::value;
+      rowmlp_kernel<ROWS><<<dim3((unsigned)((n_rows + ROWS - 1) / ROWS)), dim3(256), (size_t)ROWS * (1024 + 2 * dmax) * sizeof(float),
+                            c->stream>>>(a);                     // (dmax <= 512: at most 32 KB of LDS)
+    });
+  else
+    rowmlp_kernel<8><<<dim3((unsigned)((n_rows + 7) / 8)), dim3(256), (size_t)2 * 8 * dmax * sizeof(float), c->stream>>>(a);
   HIP_TRY(hipGetLastError());
   return XRL_OK;
 }
@@ -1229,8 +1242,11 @@ int launch_heads(xrl_ctx *c, const xrl_batch *b, const float *d_emb, float *logi
   const RowMlpArgs va = rowmlp_args(c, c->L.value, false, zmean, H, nullptr, 0, b->S, value, vact);
   if (b->G <= kMaxFusedSlots) {
     const RowMlpArgs pa = rowmlp_args(c, c->L.policy, false, d_emb, H, nullptr, 0, b->G, logit, pact);
-    policy_value_kernel<<<dim3((unsigned)(b->G + b->S)), dim3(256), 0, c->stream>>>(
-        pa, d.mask, d.state_graph_ptr, (int)b->G, (int)b->S, H, c->d_counter, logp, entropy, action, zmean, va);
+    by_rows(c, b->G, [&](auto rows) {
+      constexpr int ROWS = decltype(rows)::value;
+      policy_value_kernel<ROWS><<<dim3((unsigned)((b->G + ROWS - 1) / ROWS + b->S)), dim3(256), 0, c->stream>>>(
+          pa, d.mask, d.state_graph_ptr, (int)b->G, (int)b->S, H, c->d_counter, logp, entropy, action, zmean, va);
+    });
     const hipError_t le = hipGetLastError();
     if (le != hipSuccess) {
       // (a launch that the runtime rejected has not run; one that failed later may have left
@@ -1445,7 +1461,8 @@ RowMlpBwdArgs rowmlp_bwd_args(xrl_ctx *c, const MlpRef &r, bool relu_last, float
   a.n_layers = r.n_layers;
   a.relu_last = relu_last ? 1 : 0;
   for (int l = 0; l < r.n_layers; ++l) {
-    a.W[l] = c->d_w + r.w[l];
+    const auto it = c->row_w.find(r.w[l]);                  // (16-byte aligned)
+    a.W[l] = it != c->row_w.end() ? it->second : c->d_w + r.w[l];
     a.d_in[l] = r.d_in[l];
     a.d_out[l] = r.d_out[l];
     a.act[l] = act[l];
@@ -2955,8 +2972,11 @@ int xrl_policy_value_static(xrl_ctx *c, const xrl_batch *b, const float *d_emb, 
   fill_zero_kernel<<<dim3((unsigned)((b->S + 255) / 256)), dim3(256), 0, c->stream>>>((float *)counter, b->S);
   const RowMlpArgs va = rowmlp_args(c, c->L.value, false, zmean, H, nullptr, 0, b->S, d_value, nullptr);
   const RowMlpArgs pa = rowmlp_args(c, c->L.policy, false, d_emb, H, nullptr, 0, b->G, logit, nullptr);
-  policy_value_kernel<<<dim3((unsigned)(b->G + b->S)), dim3(256), 0, c->stream>>>(
-      pa, b->dev.mask, b->dev.state_graph_ptr, (int)b->G, (int)b->S, H, counter, d_logp, d_entropy, d_action, zmean, va);
+  by_rows(c, b->G, [&](auto rows) {
+    constexpr int ROWS = decltype(rows)::value;
+    policy_value_kernel<ROWS><<<dim3((unsigned)((b->G + ROWS - 1) / ROWS + b->S)), dim3(256), 0, c->stream>>>(
+        pa, b->dev.mask, b->dev.state_graph_ptr, (int)b->G, (int)b->S, H, counter, d_logp, d_entropy, d_action, zmean, va);
+  });
   HIP_TRY(hipGetLastError());
   return XRL_OK;
 }
