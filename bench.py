@@ -281,10 +281,10 @@ def main():
         "pool": dict(kernel="per-graph readout sum (fused with the readout MLP)", flops=0.0,
                      bytes=levels[R][0] * H * b + (4 * N if reduced else 0) + 4 * (G + 1) + G * H * 4),
         "grad_gather": dict(kernel="per-node sum of the per-edge gradients (receiver and sender side)", flops=0.0,
-                            # (reduced: the three kinds of rows summed per distinct node of the round below, in fp32
-                            # first, which is written, read and stored as the operand type)
+                            # (reduced: the three kinds of rows summed per distinct node of the round below, stored
+                            # as the operand type)
                             bytes=(EH + NH + (n_recv * H * b if kept else EH) + 8 * (n_edge + 2 * n_node) + mask_n * zk
-                                   + n_below * H * (8 + b)) if reduced else
+                                   + n_below * H * b) if reduced else
                             (EH + n_recv * H * b + mask_n if kept else 2 * EH) + 2 * NH + 4 * (2 * n_node + n_edge)),
     }
     # the weight gradients of a step share a launch or a few (one MLP's alone is not timed)
