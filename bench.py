@@ -40,14 +40,17 @@ TRAFFIC = {
     (4, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="908801e909df0b11",
                               bytes_per_launch=(42850.6 * 2.000 + 41315.2 * 1.000) * 1024),
     # configuration 5 (profiles/step_config5_bf16_hbm_traffic.md): the same, saving, and the backward kernels
-    (5, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="908801e909df0b11",
-                              bytes_per_launch=(232484.6 * 2.000 + 1057668.6 * 1.000) * 1024),
-    (5, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="908801e909df0b11",
-                              bytes_per_launch=(311879.8 * 2.000 + 660799.0 * 1.000) * 1024),
-    (5, "bf16", "bwd_edge"): dict(sources=("mma.hip.h", "mlp2_bwd.hip.h", "mlp2_bwdz.hip.h", "distinct.hip.h"), sha256_16="44d2f5df597e5169",
-                                  bytes_per_launch=(233177.3 * 2.000 + 2312662.1 * 1.000) * 1024),
-    (5, "bf16", "bwd_node"): dict(sources=("mma.hip.h", "mlp2_bwd.hip.h", "mlp2_bwdz.hip.h", "distinct.hip.h"), sha256_16="44d2f5df597e5169",
-                                  bytes_per_launch=(181945.7 * 2.000 + 929924.2 * 1.000) * 1024),
+    (5, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="3bb452e62f39d7b5",
+                              bytes_per_launch=(232500.8 * 2.000 + 1057668.6 * 1.000) * 1024),
+    (5, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="3bb452e62f39d7b5",
+                              bytes_per_launch=(311876.4 * 2.000 + 660799.0 * 1.000) * 1024),
+    (5, "bf16", "bwd_edge"): dict(sources=("mma.hip.h", "mlp2_bwd.hip.h", "mlp2_bwdz.hip.h", "distinct.hip.h"), sha256_16="c51c0a56d1d9859b",
+                                  bytes_per_launch=(232938.1 * 2.000 + 2312605.5 * 1.000) * 1024),
+    (5, "bf16", "bwd_node"): dict(sources=("mma.hip.h", "mlp2_bwd.hip.h", "mlp2_bwdz.hip.h", "distinct.hip.h"), sha256_16="c51c0a56d1d9859b",
+                                  bytes_per_launch=(181935.1 * 2.000 + 929704.4 * 1.000) * 1024),
+    # (the products of a launch and the sums of its slices)
+    (5, "bf16", "wgrad"): dict(sources=("mma.hip.h", "wgrad.hip.h", "distinct.hip.h"), sha256_16="f30a7945cbba1e01",
+                               bytes_per_launch=((4072263.4 + 26884.2) * 2.000 + (67306.7 + 2010.5) * 1.000) * 1024),
 }
 
 
