@@ -29,15 +29,15 @@ PEAK_HBM_GBS = 8000.0
 # hash covers the files the kernel is built from (comments and blank space apart); otherwise null.
 TRAFFIC = {
     # configuration 2 (profiles/forward_config2_bf16_hbm_traffic.md): persistent forward kernels, weights in LDS
-    (2, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2p.hip.h"), sha256_16="fd3c0eea759fbd7e",
-                              bytes_per_launch=(11146.9 * 2.000 + 11599.5 * 1.000) * 1024),
-    (2, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2p.hip.h"), sha256_16="fd3c0eea759fbd7e",
-                              bytes_per_launch=(15498.3 * 2.000 + 18218.2 * 1.000) * 1024),
+    (2, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2p.hip.h"), sha256_16="c82375f820edf5ab",
+                              bytes_per_launch=(11153.6 * 2.000 + 11599.5 * 1.000) * 1024),
+    (2, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2p.hip.h"), sha256_16="c82375f820edf5ab",
+                              bytes_per_launch=(15506.5 * 2.000 + 18218.2 * 1.000) * 1024),
     # configuration 4 (profiles/forward_config4_bf16_kernel_stats_and_traffic.md): register-stationary forward kernels on the
     # levels of the reduced batch, mean over the rounds (so the sources that decide the levels belong to it)
-    (4, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="908801e909df0b11",
-                              bytes_per_launch=(30503.2 * 2.000 + 40853.2 * 1.000) * 1024),
-    (4, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="908801e909df0b11",
+    (4, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="3bb452e62f39d7b5",
+                              bytes_per_launch=(30502.9 * 2.000 + 40853.2 * 1.000) * 1024),
+    (4, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="3bb452e62f39d7b5",
                               bytes_per_launch=(42850.6 * 2.000 + 41315.2 * 1.000) * 1024),
     # configuration 5 (profiles/step_config5_bf16_hbm_traffic.md): the same, saving, and the backward kernels
     (5, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="3bb452e62f39d7b5",
