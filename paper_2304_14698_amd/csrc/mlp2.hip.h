@@ -24,6 +24,7 @@ struct Mlp2Args {
   int64_t n_rows;
   int64_t n_blocks;        // number of tiles
   const void *W1s, *W2s;   // fragment-ordered weights, operand type (mlp2_split3_kernel: their parts)
+  const float *W1, *W2;    // the same as they are given, [in, H] (mlp2_split3_kernel alone)
   const float *b1, *b2;    // [H]
   int nslab1;              // slabs of layer 1's (zero-padded) input width
   const void *h;           // [N, H] operand type            (EDGE, NODE)
@@ -671,7 +672,10 @@ __global__ __launch_bounds__(2 * H) void mlp2_split3_kernel(const Mlp2Args a) {
   for (int q = 0; q < 2; ++q) {
     float z[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) z[j] = relu_f32(acc[8 * q + j] + corr[8 * q + j]);
+    for (int j = 0; j < 8; ++j) {
+      const float v = acc[8 * q + j] + corr[8 * q + j];
+      z[j] = fabsf(v) < INFINITY ? relu_f32(v) : NAN;           // (not finite: the row's every output becomes a NaN)
+    }
     share(2 * w + q, split3(z));
   }
 #pragma unroll
@@ -684,6 +688,35 @@ __global__ __launch_bounds__(2 * H) void mlp2_split3_kernel(const Mlp2Args a) {
   }
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] += corr[r];
+  // ---------------- rows with a value that has no parts, or that overflowed: once more, in fp32
+  float sum0 = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) sum0 = fmaf(acc[r], 0.f, sum0);  // (0, or a NaN)
+  const unsigned long long odd = __ballot(sum0 != 0.f && l32 < nv);
+  for (unsigned rows = (unsigned)(odd | odd >> 32); rows; rows &= rows - 1) {
+    const int r = __builtin_ctz(rows);                          // (lane r of the first half: its pointers are the row's)
+    const float *xa = (const float *)__shfl((unsigned long long)pa, r), *xb = (const float *)__shfl((unsigned long long)pb, r);
+    const int K = KIND == KIND_EDGE ? 2 * H + a.De : 2 * H;
+    const float *xe = a.edge_feat + (KIND == KIND_EDGE ? (size_t)__shfl(row, r) * a.De : 0);
+    constexpr int NF = H / 64;                                  // relu(z1) of features lane, lane + 64, ..
+    float z[NF];
+#pragma unroll
+    for (int i = 0; i < NF; ++i) z[i] = a.b1[lane + 64 * i];
+    for (int k = 0; k < K; ++k) {
+      const float x = k < H ? xa[k] : k < 2 * H ? xb[k - H] : xe[k - 2 * H];
+#pragma unroll
+      for (int i = 0; i < NF; ++i) z[i] = fmaf(x, a.W1[(size_t)k * H + lane + 64 * i], z[i]);
+    }
+    float y = a.b2[32 * w + l32];                               // feature 32 w + l32, twice
+    for (int k = 0; k < 64; ++k)
+#pragma unroll
+      for (int i = 0; i < NF; ++i) y = fmaf(__shfl(relu_f32(z[i]), k), a.W2[(size_t)(k + 64 * i) * H + 32 * w + l32], y);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float v = __shfl(y, acc_row(i, g));
+      acc[i] = l32 == r ? v : acc[i];
+    }
+  }
   // ---------------- epilogue on this wave's 32 features
   float *out = (float *)a.out;
   char *stage = smem + S::ZBYTES + w * BlockStage<float>::BYTES;

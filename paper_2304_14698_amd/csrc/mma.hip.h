@@ -316,11 +316,13 @@ __device__ __forceinline__ void store_block_rows_via_lds(TO *base, int dsel, int
   wave_lds_fence();
 }
 
-// Eight floats as three bf16 parts each: v = p[0] + p[1] + p[2] exactly (every part is what is left, rounded to
-// nearest: the second is at most 2^-9 and the third 2^-18 of v). A product of two such numbers is the six products of parts of
+// Eight floats as three bf16 parts each: v = p[0] + p[1] + p[2] exactly for 2^-108 <= |v| < 2^128 (1 - 2^-9) (every part is
+// what is left, rounded to nearest: the second is at most 2^-9 and the third 2^-18 of v). A product of two such numbers is the six products of parts of
 // weight 2^-18 and above, each exact in fp32, to within 2^-26 of itself and without a bias (with parts cut off towards
-// zero, which all have v's sign, what is left out added up to 2^-23, and the error of an encode to 1.7 times). Values are finite: an infinity, which only an
-// overflow can bring in here, becomes a NaN.
+// zero, which all have v's sign, what is left out added up to 2^-23, and the error of an encode to 1.7 times).
+// Smaller values are off by at most 2^-126, the least normal bf16. From 2^128 (1 - 2^-9) on the first part rounds to an infinity, the
+// rest becomes a NaN, and every product with v, with 0 too, an infinity or a NaN: what is summed from
+// parts has to be looked at, and computed otherwise where it is not finite (see mlp2_split3_kernel).
 struct Split3 {
   bf16x8 p[3];
 };

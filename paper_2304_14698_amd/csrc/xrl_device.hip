@@ -43,6 +43,7 @@ inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 struct EncMlp {           // device pointers of one encoder MLP
   const void *W1s = nullptr, *W2s = nullptr;
   const void *W1p = nullptr, *W2p = nullptr;     // forward in parts (xrl_ctx::parts): edge and node MLPs
+  const float *W1 = nullptr, *W2 = nullptr;      // as they are given
   const void *W2bt = nullptr, *W1bt = nullptr;   // backward: contraction over the weight's columns
   const float *b1 = nullptr, *b2 = nullptr;
   int nslab1 = 0;
@@ -712,6 +713,8 @@ int plan_weights(xrl_ctx *c) {
     e.W2s = c->d_swz + ref.w2;
     e.W1p = c->d_swz + ref.w1p;
     e.W2p = c->d_swz + ref.w2p;
+    e.W1 = c->d_w + r.w[0];
+    e.W2 = c->d_w + r.w[1];
     e.W2bt = c->d_swz + ref.w2bt;
     e.W1bt = c->d_swz + ref.w1bt;
     e.b1 = c->d_w + r.b[0];
@@ -2413,7 +2416,7 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   a.carry = c->carry; a.zero_row = c->zero_row;
   auto set_w = [&](const EncMlp &e) {
     const bool parts = c->parts() && &e != &c->embed;
-    a.W1s = parts ? e.W1p : e.W1s; a.W2s = parts ? e.W2p : e.W2s; a.b1 = e.b1; a.b2 = e.b2;
+    a.W1s = parts ? e.W1p : e.W1s; a.W2s = parts ? e.W2p : e.W2s; a.W1 = e.W1; a.W2 = e.W2; a.b1 = e.b1; a.b2 = e.b2;
     a.nslab1 = parts ? (e.nslab1 + 1) / 2 : e.nslab1;       // (in parts: slabs of sixteen columns)
     a.W1x = e.W1x; a.nslabx = e.nslabx; a.table = e.table;
   };
