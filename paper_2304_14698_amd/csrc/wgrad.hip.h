@@ -78,6 +78,14 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 // TA = X columns per block, 128 (four waves, two blocks per CU) or 256 (eight waves, one block per CU: dZ is
 // read once per 256 instead of once per 128 columns). RS = rows per stage: what a block has in
 // flight from memory while it multiplies the previous stage; one block per CU needs 64 in bf16.
+// A slice may have tens of thousands of rows, and the error of a sum taken step after step grows with the root of the
+// steps (of 2 rows in fp32, of 16 in bf16). So every FOLD rows the sums are added to second ones: in registers where there are
+// as many again, in fp32 at H = 256 in the partial tile. Relative error of 2^20 rows' products of random sign
+// against float64, one chain / folded: fp32 5.9e-7 / 2.3e-7 (H = 256 8.5e-7 / 2.4e-7), bf16, 2^22 rows, 5.0e-7 / 2.2e-7; of the
+// encoder's fp32 gradients, 5 k to 110 k nodes, 1.0 to 3 times less. It costs nothing that can be measured at H <= 128 and
+// 12 % of the launch in fp32 at H = 256 (93 k nodes 4.5 / 5.0 ms). bf16 at H = 256 keeps one chain (5.0e-7 at 2^21 rows, ten thousand
+// times below its operands' rounding): 160 of 256 registers hold sums, and the tile's way to memory and back every 2048
+// rows cost a quarter of the launch.
 // A stage goes from memory into LDS directly (lds_direct_load16), as the rows lie there: 16-byte piece s of LDS
 // row r holds piece s ^ swizzle(r), which moves the rows r .. r + 3 that a transpose read touches to
 // different banks where their lengths, multiples of 256 bytes, would put them on the same.
@@ -91,7 +99,9 @@ struct WgradShape {
   static constexpr int XB = RS * XP * 16, ZB = RS * ZP * 16, EB = RS * EP * 16;   // bytes of a stage
   static constexpr int XV = RS * XP / NT, ZV = RS * ZP / NT;         // pieces per thread and stage
   static constexpr size_t LDS = 2 * (size_t)(XB + ZB + EB);
-  static_assert(ZV >= 1 && XV >= 1 && RS % ST == 0 && RS * EP == NT / 2 && (NT / XP) % 4 == 0 && (NT / ZP) % 4 == 0, "");
+  static constexpr bool SECOND = H <= 128;                           // second sums in registers ...
+  static constexpr int FOLD = SECOND ? (sizeof(T) == 4 ? 128 : 1024) : sizeof(T) == 4 ? 192 : 0;   // ... or in the partial tile (0: none)
+  static_assert(ZV >= 1 && XV >= 1 && RS % ST == 0 && RS * EP == NT / 2 && (NT / XP) % 4 == 0 && (NT / ZP) % 4 == 0 && FOLD % RS == 0, "");
 };
 // swizzle(r) in 64-byte blocks, for rows of P pieces
 template <typename T, int P>
@@ -130,14 +140,55 @@ __device__ __forceinline__ typename Operand<T>::vec lds_column_operand(const cha
 // column from the piece behind it: a select on the address, so that no load is under a condition. The row
 // indices of gathered X columns are fetched two stages ahead. EXTRA: also 32 columns beside the tile, an
 // EDGE product's [attributes | 1 | 0 ..], else the all-ones column alone.
-template <typename T, int H, int TA, int RS, int KIND, bool EXTRA>
+template <typename T, int H, int TA, int RS>
+struct WgradSums {
+  using S = WgradShape<T, H, TA, RS>;
+  f32x16 main[2][S::NB], extra[S::NE];   // of 32-column blocks of X (the extra columns) and of dZ
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int i = 0; i < S::NB; ++i) main[m][i][r] = 0.f;
+#pragma unroll
+      for (int i = 0; i < S::NE; ++i) extra[i][r] = 0.f;
+    }
+  }
+  __device__ __forceinline__ void add(const WgradSums &o, bool with_extra) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int i = 0; i < S::NB; ++i) main[m][i] += o.main[m][i];
+    if (with_extra)
+#pragma unroll
+      for (int i = 0; i < S::NE; ++i) extra[i] += o.extra[i];
+  }
+};
+// A 32-column block's sums to the partial tile (rows H apart; out: this lane's column), or added to what is there
+template <int H>
+__device__ __forceinline__ void wgrad_put(float *out, int g, bool add, f32x16 &s) {
+  unsigned at = (unsigned)(4 * g * H);
+  asm volatile("" : "+v"(at));           // (formed here: kept over the stage loop, the addresses of all blocks spill)
+  if (add) {
+    float t[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) t[r] = out[at + (unsigned)(acc_row(r, 0) * H)];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] += t[r];
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) out[at + (unsigned)(acc_row(r, 0) * H)] = s[r];
+}
+template <typename T, int H, int TA, int RS, int KIND, bool EXTRA, typename Fold>
 __device__ __forceinline__ void wgrad_run(const WgradJob &j, const char *zero_row, int ka0, int64_t r_begin, int64_t r_end, char *smem,
-                                          f32x16 (&acc)[2][WgradShape<T, H, TA, RS>::NB],
-                                          f32x16 (&acce)[WgradShape<T, H, TA, RS>::NE]) {
+                                          WgradSums<T, H, TA, RS> &sums, Fold fold) {
   using S = WgradShape<T, H, TA, RS>;
   using Opd = Operand<T>;
   using vec = typename Opd::vec;
   constexpr int V = S::V, ST = S::ST, XV = S::XV, ZV = S::ZV, NB = S::NB, NE = S::NE, NT = S::NT, XP = S::XP, ZP = S::ZP, EP = S::EP;
+  auto &acc = sums.main;
+  auto &acce = sums.extra;
   constexpr bool GATHER = KIND == WG_EDGE || KIND == WG_NODE, ATTRS = EXTRA && KIND == WG_EDGE;
   char *const Xs = smem, *const Zs = smem + 2 * S::XB, *const Es = Zs + 2 * S::ZB;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -279,6 +330,9 @@ __device__ __forceinline__ void wgrad_run(const WgradJob &j, const char *zero_ro
     if (sn < n_stage) commit(sn);
     arrived();
     __syncthreads();
+    if constexpr (S::FOLD > 0) {
+      if (sn % (S::FOLD / RS) == 0 && sn < n_stage) fold();
+    }
 #pragma unroll
     for (int c = 0; c < XV; ++c) ix1[c] = ix2[c];
   }
@@ -299,21 +353,40 @@ __global__ __launch_bounds__(2 * TA, 2) void wgrad_kernel(const WgradLaunch a) {
   const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wa = wave % S::WA, wb = wave / S::WA;
+  const bool extra = j.extra && kq == 0;
 
-  f32x16 acc[2][NB], acce[NE];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
+  WgradSums<T, H, TA, RS> sums;
+  sums.clear();
+  float *const out0 = j.partial + (size_t)y * j.KaP * H;
+  bool put_before = false;
+  auto put = [&]() __attribute__((always_inline)) {
+    float *out = out0 + (size_t)(ka0 + 64 * wa) * H + 32 * wb * NB + l32;
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
-      for (int i = 0; i < NB; ++i) acc[m][i][r] = 0.f;
+      for (int i = 0; i < NB; ++i) wgrad_put<H>(out + (size_t)32 * m * H + 32 * i, g, put_before, sums.main[m][i]);
+    if (extra && wa * NE < NB) {
+      float *oe = out0 + (size_t)j.kt * TA * H + 32 * (wb * NB + wa * NE) + l32;
 #pragma unroll
-    for (int i = 0; i < NE; ++i) acce[i][r] = 0.f;
-  }
-  const bool extra = j.extra && kq == 0;
-  const char *zeros = (const char *)a.zero_row;
+      for (int i = 0; i < NE; ++i) wgrad_put<H>(oe + 32 * i, g, put_before, sums.extra[i]);
+    }
+    put_before = true;
+  };
+  // with: the extra columns too
   auto run = [&](auto kind, auto with) {
-    wgrad_run<T, H, TA, RS, decltype(kind)::value, decltype(with)::value>(j, zeros, ka0, r_begin, r_end, smem, acc, acce);
+    constexpr int KIND = decltype(kind)::value;
+    constexpr bool WITH = decltype(with)::value;
+    const char *zeros = (const char *)a.zero_row;
+    if constexpr (S::SECOND) {
+      WgradSums<T, H, TA, RS> second;
+      second.clear();
+      auto fold = [&]() __attribute__((always_inline)) { second.add(sums, WITH); sums.clear(); };
+      wgrad_run<T, H, TA, RS, KIND, WITH>(j, zeros, ka0, r_begin, r_end, smem, sums, fold);
+      sums.add(second, WITH);
+    } else {
+      auto fold = [&]() __attribute__((always_inline)) { put(); sums.clear(); };
+      wgrad_run<T, H, TA, RS, KIND, WITH>(j, zeros, ka0, r_begin, r_end, smem, sums, fold);
+    }
   };
   using std::integral_constant;
   typedef integral_constant<bool, true> yes;
@@ -330,21 +403,7 @@ __global__ __launch_bounds__(2 * TA, 2) void wgrad_kernel(const WgradLaunch a) {
   } else {
     run(integral_constant<int, WG_ATTR>(), no());
   }
-  float *const out0 = j.partial + (size_t)y * j.KaP * H;
-  float *out = out0 + (size_t)(ka0 + 64 * wa) * H + 32 * wb * NB + l32;
-#pragma unroll
-  for (int m = 0; m < 2; ++m)
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) out[(size_t)(32 * m + acc_row(r, g)) * H + 32 * i] = acc[m][i][r];
-  if (extra && wa * NE < NB) {
-    float *oe = out0 + (size_t)j.kt * TA * H + 32 * (wb * NB + wa * NE) + l32;
-#pragma unroll
-    for (int i = 0; i < NE; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) oe[(size_t)acc_row(r, g) * H + 32 * i] = acce[i][r];
-  }
+  put();
 }
 
 // dW[k, f] += sum over slices of partial[slice, k, f] for k < k_rows; db[f] += row bias_row. A block handles

@@ -36,3 +36,39 @@ def test_backward_of_more_products_than_one_launch_takes(xrl, room, monkeypatch)
     model, state = synth.make_config(1)
     model.update(rounds=7)                         # 30 products; a launch takes 24
     run_backward_case(xrl, model, state, weights_for(model))
+
+
+@pytest.mark.parametrize("hidden,precision,rows", [(64, "fp32", 1 << 20), (128, "fp32", (1 << 20) + 37), (256, "fp32", 1 << 20),
+                                                   (64, "bf16", 1 << 22), (128, "bf16", (1 << 22) - 5), (256, "bf16", 1 << 21)])
+def test_weight_gradient_error_of_long_sums(xrl, hidden, precision, rows):  # noqa: F811
+    """Slices of thousands of rows. Terms of random sign: a sum of k of them grows with the root of k, and L additions
+    one after the other, each rounded to 2^-24 / sqrt(3) of the sum so far (root mean square, at most), leave
+    2^-24 sqrt(L / 6) of the whole. Added one after the other: the steps (2 rows in fp32, 16 in bf16) between two
+    foldings into the second sums, the foldings of a slice, an eighth of the slices, eight; a third of room on top."""
+    import torch
+    model, state = synth.make_config(1)
+    model.update(hidden=hidden, precision=precision)
+    enc = xrl.Encoder(model, weights_for(model))
+    batch = enc.pack(state)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    dt = torch.float32 if precision == "fp32" else torch.bfloat16
+    x = torch.relu(torch.randn(rows, hidden, generator=gen, device="cuda")).to(dt)
+    dz = torch.randn(rows, hidden, generator=gen, device="cuda").to(dt)
+    dW, db = torch.zeros(hidden, hidden, device="cuda"), torch.zeros(hidden, device="cuda")
+    enc.weight_gradient(batch, "plain", x=x, dz=dz, dW=dW, db=db)
+    torch.cuda.synchronize()
+    ref, step = torch.zeros(hidden, hidden, dtype=torch.float64, device="cuda"), 1 << 17
+    for i in range(0, rows, step):
+        ref += x[i:i + step].double().t().contiguous() @ dz[i:i + step].double()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    wide = precision == "bf16" and hidden == 256
+    slices = cus if wide else 2 * cus * 128 // max(hidden, 128)
+    per_slice = rows / slices
+    fold = {64: (128, 1024), 128: (128, 1024), 256: (192, per_slice)}[hidden][precision == "bf16"]
+    L = fold / (2 if precision == "fp32" else 16) + per_slice / fold + slices / 8 + 8
+    for got, want in ((dW, ref), (db, dz.double().sum(0))):
+        err = float((got.double() - want).norm() / want.norm())
+        print(f"{err:.2e} of {4 / 3 * 2 ** -24 * (L / 6) ** 0.5:.2e}")
+        assert err <= 4 / 3 * 2 ** -24 * (L / 6) ** 0.5
+    batch.free()
+    enc.close()
