@@ -212,7 +212,8 @@ int xrl_batch_free(xrl_batch *b);   /* frees host and device copies; NULL is acc
  * <= 128 runs a message-passing round as one launch (default 4 at hidden = 64, else 2; 0 = never; same bits);
  * XRL_WGRAD_WIDE_MIN_ROWS = rows of the products of one weight-gradient launch, added up, from which it uses
  * 256-column tiles at hidden = 256 in bf16 (default 2^18; same sums in a different, equally fixed order);
- * XRL_GRAD_ROOM = bytes of gradients kept for one such launch (default 2^31; always at least one MLP's);
+ * XRL_GRAD_ROOM = bytes of gradients kept for one such launch (default 2^31; always at least one MLP's; what is there
+ * where more has been refused, or captured calls hold addresses in a smaller workspace);
  * XRL_RESIDENT_MAX_GRAPHS (default 256; 0 = never) and XRL_RESIDENT_MAX_TILES (default 4) =
  * largest batch, in graphs and in 32-row tiles of nodes or edges per graph, that xrl_encode runs
  * as one launch with a block per graph (message-passing rounds of the MLP kind, rows of at most

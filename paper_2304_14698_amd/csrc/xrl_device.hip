@@ -24,6 +24,7 @@
 #include "wgrad.hip.h"
 #include "segsum.hip.h"
 #include "distinct.hip.h"
+#include "room.h"
 #include "xrl_internal.h"
 
 using namespace xrl;
@@ -205,6 +206,7 @@ struct xrl_ctx {
   size_t hws_bytes = 0;
   char *bws = nullptr;          // backward scratch
   size_t bws_bytes = 0;
+  bool room_refused = false;    // (see fit_room)
   // buffers of the last encode (inside ws)
   uint64_t id = 0;              // unique per context
   int32_t *d_counts = nullptr;  // class and tile counts of the levels of a batch, and their copy in pinned memory
@@ -2019,10 +2021,10 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
     sort_bytes = q->grouped && q->grouped_fold == fold ? 0 : grouping_bytes(b, q, fold);
     need = std::max(need, sort_bytes);
   }
-  size_t room = std::min(room_all, std::max(room_one, c->grad_room));
   const size_t o_room = align_up(need);
-  int rc = ensure_bws(c, o_room + room);
-  if (rc == XRL_ERR_OOM && room > room_one) rc = ensure_bws(c, o_room + (room = room_one));
+  size_t room = 0;
+  int rc = fit_room(c->bws_bytes, o_room, room_one, std::min(room_all, std::max(room_one, c->grad_room)), c->captured, XRL_ERR_OOM,
+                    &c->room_refused, &room, [&](size_t bytes) { return ensure_bws(c, bytes); });
   if (rc) return rc;
   if (q && !(q->grouped && q->grouped_fold == fold) && (rc = make_groupings(c, b, q, fold))) return rc;
   Bump bump{c->bws};

@@ -6,6 +6,7 @@ backward pass against the oracle, fp32)."""
 import numpy as np
 import pytest
 
+import paper_2304_14698_amd as xrl_package
 import synth
 from test_gpu_backward import run_backward_case
 from test_gpu_forward import weights_for
@@ -72,3 +73,47 @@ def test_weight_gradient_error_of_long_sums(xrl, hidden, precision, rows):  # no
         assert err <= 4 / 3 * 2 ** -24 * (L / 6) ** 0.5
     batch.free()
     enc.close()
+
+
+def test_backward_of_a_larger_batch_leaves_a_graphs_workspace():
+    """A captured backward pass keeps its addresses: a larger batch whose gradients' room would not fit beside what it
+    cannot do without takes the room that is there. Its gradients are those of a context without graphs but for the
+    order of the weight gradients' sums, whose slices follow the room."""
+    import torch
+    rng = np.random.Generator(np.random.PCG64(8))
+    model, _ = synth.make_config(1)
+    model.update(hidden=64, precision="fp32", rounds=5)
+    w = weights_for(model)
+    base = synth.resnet_dag(rng, 8)
+    states = [synth.concat_states([synth.make_state(rng, base, n, by_block=True)]) for n in (60, 72)]
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        alone = xrl_package.Encoder(model, w, stream=side)
+        enc = xrl_package.Encoder(model, w, stream=side)
+
+        def step(e, b):
+            emb = e.encode(b, save_for_backward=True)
+            dw = torch.zeros(e.n_weights, device="cuda")
+            e.encode_backward(b, torch.ones_like(emb), dw)
+            return dw
+        large = [e.pack(states[1]) for e in (alone, enc)]
+        enc.encode(large[1], save_for_backward=True)          # (the forward's workspace has its size)
+        small = enc.pack(states[0])
+        want = step(enc, small)
+        dw, up = torch.zeros_like(want), torch.ones(small.G, 64, device="cuda")
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side, capture_error_mode="relaxed"):
+            dw.zero_()
+            enc.encode_backward(small, up, dw)
+        reference = step(alone, large[0])
+        for _ in range(3):
+            got = step(enc, large[1])
+            torch.cuda.synchronize()
+            assert float((got - reference).norm()) <= 1e-6 * float(reference.norm())
+            step(enc, small)                                  # (what the graph's backward pass is of)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(dw, want)
+        for x in large + [small, alone, enc]:
+            x.free() if hasattr(x, "free") else x.close()
