@@ -209,7 +209,8 @@ int xrl_batch_free(xrl_batch *b);   /* frees host and device copies; NULL is acc
  * 8192 it does not apply to a batch reduced to its distinct nodes (see xrl_encode) that is saved for the
  * backward pass: its rounds of any size run on them;
  * XRL_ROUND_BLOCKS = blocks per compute unit, of 28 nodes each, up to which a forward-only encode in bf16 at hidden
- * <= 128 runs a message-passing round as one launch (default 4 at hidden = 64, else 2; 0 = never; same bits);
+ * <= 128 runs a message-passing round as one launch (default 4 at hidden = 64, else 2, and only where no block's nodes
+ * have more than 72 in-edges; 0 = never; same bits);
  * XRL_WGRAD_WIDE_MIN_ROWS = rows of the products of one weight-gradient launch, added up, from which it uses
  * 256-column tiles at hidden = 256 in bf16 (default 2^18; same sums in a different, equally fixed order);
  * XRL_GRAD_ROOM = bytes of gradients kept for one such launch (default 2^31; always at least one MLP's; what is there

@@ -744,7 +744,10 @@ __global__ __launch_bounds__(2 * H) void mlp2_split3_kernel(const Mlp2Args a) {
 // per node, then mostly fit one pass. us per encode of five rounds, two launches a round /
 // one, H = 128: 454 nodes 56.5 / 46.4, 5.1 k 60.8 / 49.9, 7.1 k 61.9 / 58.3, 13.8 k 78.0 / 70.6, 20.6 k 96.0 / 96.9; H = 64: 454
 // 48.0 / 35.5, 5.1 k 47.6 / 37.9, 13.8 k 54.5 / 48.2, 27.4 k 65.6 / 56.6.
-constexpr int kRoundNodesMin = 16, kRoundNodesMax = 28;
+// Two passes over a block's in-edges are the most that gain: same, 1 k nodes of 1 / 2 / 4 / 8 / 30 in-edges, H = 128:
+// 63.5 / 49.2, 63.5 / 50.4, 66.1 / 60.5, 69.0 / 88.0, 93.7 / 275.8, H = 64: 53.0 / 39.4, 56.0 / 41.2, 56.3 / 48.8, 58.2 / 66.8, 68.8 / 199.9; three,
+// of 28 nodes of 3 in-edges, 88.6 / 85.0 and 63.8 / 59.9, of 6 or more, 28 nodes of 4 in-edges, 90.9 / 98.0 and 62.9 / 67.7.
+constexpr int kRoundNodesMin = 16, kRoundNodesMax = 28, kRoundEdges = 72;   // (a receiver that does not fit is left to the next pass)
 struct RoundArgs {
   Mlp2Args edge, node;     // node.out: [N, H]; node.agg and edge.out are not used
   int nodes;               // of a block, at most 32

@@ -161,6 +161,7 @@ struct xrl_ctx {
   int64_t wide_min_rows = 1 << 18;   // rows of a launch's products from which 256-column weight-gradient tiles are used (XRL_WGRAD_WIDE_MIN_ROWS)
   size_t grad_room = kGradRoom;      // XRL_GRAD_ROOM
   int64_t round_blocks = 0;          // blocks per compute unit up to which a round is one launch, see mlp2_round_kernel (XRL_ROUND_BLOCKS)
+  bool round_any = false;            // ... whatever their in-edges (if it is set)
   int64_t resident_max_graphs = 0;   // largest batch (graphs) for the one-launch encoder (XRL_RESIDENT_MAX_GRAPHS)
   int64_t resident_max_tiles = 0;    // ... and the most 32-row tiles (nodes, or edges) of one graph (XRL_RESIDENT_MAX_TILES)
   float *d_w = nullptr;         // flat fp32 weights
@@ -946,7 +947,8 @@ int launch_mlp2_split(xrl_ctx *c, const Mlp2Args &a) {
 }
 
 // Whole rounds (see mlp2_round_kernel): forward only, where the two kernels of a round would be split ones, up to
-// round_blocks blocks per compute unit.
+// round_blocks blocks per compute unit whose fullest has kRoundEdges in-edges, which are 32 at a time one pass after the other
+// where a launch of their own takes them side by side.
 template <typename T, int H>
 int launch_round_h(xrl_ctx *c, const RoundArgs &a) {
   if constexpr (RoundTile<T, H>::FITS) {
@@ -962,17 +964,27 @@ int launch_round_h(xrl_ctx *c, const RoundArgs &a) {
   }
   return fail(XRL_ERR_UNSUPPORTED, "launch_round_h: hidden = %d", H);
 }
+int64_t round_nodes(const xrl_ctx *c, int64_t N) {        // of a block
+  return std::max<int64_t>(kRoundNodesMin, std::min<int64_t>(kRoundNodesMax, (N + c->n_cu - 1) / c->n_cu));
+}
+// in_ptr: the graph's, on the host; nullptr for a level of a reduced batch, where only the mean is known, and half as much
+// again left for the fullest block.
 template <typename T>
-bool round_applies(const xrl_ctx *c, const LevelGraph &g) {
+bool round_applies(const xrl_ctx *c, const LevelGraph &g, const int32_t *in_ptr) {
   const int H = c->m.hidden;
   const bool fits = H == 64 ? RoundTile<T, 64>::FITS : H == 128 ? RoundTile<T, 128>::FITS : RoundTile<T, 256>::FITS;
   if (std::max(g.N, g.E) >= c->min_rows_now) return false;      // (the persistent kernels')
-  return fits && g.N > 0 && g.N <= kRoundNodesMax * c->round_blocks * c->n_cu;
+  if (!fits || g.N <= 0 || g.N > kRoundNodesMax * c->round_blocks * c->n_cu) return false;
+  if (c->round_any) return true;
+  const int64_t nodes = round_nodes(c, g.N);
+  if (!in_ptr) return g.E * nodes * 3 <= kRoundEdges * 2 * g.N;
+  for (int64_t n = 0; n < g.N; n += nodes)                      // (at most round_blocks n_cu blocks, or N / 16)
+    if (in_ptr[std::min(n + nodes, g.N)] - in_ptr[n] > kRoundEdges) return false;
+  return true;
 }
 template <typename T>
 int launch_round(xrl_ctx *c, RoundArgs &a) {
-  const int64_t even = (a.node.n_rows + c->n_cu - 1) / c->n_cu;
-  a.nodes = (int)std::max<int64_t>(kRoundNodesMin, std::min<int64_t>(kRoundNodesMax, even));
+  a.nodes = (int)round_nodes(c, a.node.n_rows);
   a.node.n_blocks = (a.node.n_rows + a.nodes - 1) / a.nodes;
   switch (c->m.hidden) {
     case 64: return launch_round_h<T, 64>(c, a);
@@ -2484,6 +2496,7 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   c->h[0] = hb[0];
   T *hcur = hb[0];
   // ---- message-passing rounds
+  bool one_launch = false;             // a whole round in one launch
   for (int r = 0; r < R; ++r) {
     T *aggb = save ? ab[r] : ab[0];
     T *hnext = save ? hb[r + 1] : hb[(r + 1) & 1];
@@ -2518,7 +2531,9 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
     }
     set_graph(g);
     a.agg_src = g.agg_src;
-    if (!save && b->n_split_tiles == 0 && round_applies<T>(c, g)) {
+    if (!q && r == 0 && !save) one_launch = b->n_split_tiles == 0 && round_applies<T>(c, g, b->at<int32_t>(b->o_in_ptr));
+    if (q && !save) one_launch = round_applies<T>(c, g, nullptr);
+    if (one_launch) {
       RoundArgs ra;
       set_w(c->edge[r]);
       a.n_rows = E; a.h = hcur;
@@ -2639,7 +2654,7 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   if (const char *e = getenv("XRL_PERSISTENT_MIN_ROWS")) c->p_min_rows = c->p_min_rows_forward = atoll(e);
   if (const char *e = getenv("XRL_WGRAD_WIDE_MIN_ROWS")) c->wide_min_rows = atoll(e);
   c->round_blocks = model->hidden == 64 ? 4 : 2;
-  if (const char *e = getenv("XRL_ROUND_BLOCKS")) c->round_blocks = atoll(e);
+  if (const char *e = getenv("XRL_ROUND_BLOCKS")) { c->round_blocks = atoll(e); c->round_any = true; }
   if (const char *e = getenv("XRL_GRAD_ROOM")) c->grad_room = (size_t)std::max<long long>(0, atoll(e));
   // Largest batches of the one-launch encoders (0 graphs = never). A forward-only encode takes them up to a
   // limit that the variable of that form states, and by default never: since a tile of the

@@ -45,3 +45,24 @@ def test_round_in_one_launch_equals_two(hidden, d_edge, rounds, sizes, monkeypat
             batch.free()
             enc.close()
         assert np.array_equal(got[0], got[1]), degrees
+
+
+@pytest.mark.parametrize("hidden", [64, 128])
+@pytest.mark.parametrize("degrees,one", [((1,), True), ((0, 2, 4, 2), True), ((4, 4, 5, 4), True), ((8, 0), True), ((6,), False), ((10, 0), False), ((30,), False), ("cluster", False)])
+def test_dense_receivers_keep_two_launches(hidden, degrees, one, monkeypatch):
+    """A block's in-edges go 32 at a time, one pass after the other: where its nodes have more than 72, in one block of
+    the batch too, the edges have a launch of their own."""
+    import torch  # noqa: F401
+    monkeypatch.delenv("XRL_ROUND_BLOCKS", raising=False)
+    rng = np.random.Generator(np.random.PCG64(43))
+    model, _ = synth.make_config(1)
+    model.update(hidden=hidden, precision="bf16", rounds=2)
+    enc = xrl.Encoder(model, synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1))
+    degrees = [1] * 500 + [16] * 8 + [1] * 600 if degrees == "cluster" else degrees
+    graphs = [_graph(rng, 1000, degrees, model["d_edge"])]
+    batch = enc.pack(synth.concat_states([(graphs, np.ones(1, np.uint8))]))
+    enc.set_timing(True)
+    enc.encode(batch)
+    assert (enc.read_timing("round")[1] > 0) == one
+    batch.free()
+    enc.close()
