@@ -1695,26 +1695,37 @@ GroupArgs groupings(const xrl_batch *b, Distinct *q, bool fold) {
   add(b->N, q->lv[R].N, q->cls[R], b->dev.node_graph, q->mem_ptr, q->mem_seg, q->mem_graph);
   return a;
 }
-size_t grouping_bytes(const xrl_batch *b, Distinct *q, bool fold) {
-  const GroupArgs a = groupings(b, q, fold);
-  const int64_t n = a.item0[a.n], nb = (n + kSortItems - 1) / kSortItems;
+// A stable sort of n (key, value) items, keys below n_keys: the memory it takes, and the sort, whose items `fill` puts into
+// that memory. Returns where they lie then.
+size_t sort_bytes_of(int64_t n) {
+  const int64_t nb = (n + kSortItems - 1) / kSortItems;
   return 2 * align_up((size_t)n * 8) + align_up((size_t)nb * 256 * 4) + 1024;
 }
-int make_groupings(xrl_ctx *c, const xrl_batch *b, Distinct *q, bool fold) {
-  const GroupArgs a = groupings(b, q, fold);
-  const int64_t n = a.item0[a.n];
+template <typename Fill>
+uint2 *sort_items(xrl_ctx *c, char *mem, int64_t n, uint32_t n_keys, Fill fill) {
   const int nb = (int)((n + kSortItems - 1) / kSortItems);
-  Bump bump{c->bws};
+  Bump bump{mem};
   uint2 *x = bump.take<uint2>((size_t)n), *y = bump.take<uint2>((size_t)n);
   int32_t *hist = bump.take<int32_t>((size_t)nb * 256), *total = bump.take<int32_t>(256);
-  const dim3 per_item((unsigned)((n + 255) / 256));
-  group_items_kernel<<<per_item, dim3(256), 0, c->stream>>>(a, x);
-  for (int shift = 0; shift < 32 && (a.key0[a.n] - 1) >> shift; shift += 8) {
+  fill(x);
+  for (int shift = 0; shift < 32 && (n_keys - 1) >> shift; shift += 8) {
     sort_count_kernel<<<dim3((unsigned)nb), dim3(256), 0, c->stream>>>(x, n, shift, hist, nb);
     sort_scan_kernel<<<dim3(256), dim3(256), 0, c->stream>>>(hist, nb, total);
     sort_scatter_kernel<<<dim3((unsigned)nb), dim3(256), 0, c->stream>>>(x, n, shift, hist, nb, total, y);
     std::swap(x, y);
   }
+  return x;
+}
+size_t grouping_bytes(const xrl_batch *b, Distinct *q, bool fold) {
+  const GroupArgs a = groupings(b, q, fold);
+  return sort_bytes_of(a.item0[a.n]);
+}
+int make_groupings(xrl_ctx *c, const xrl_batch *b, Distinct *q, bool fold) {
+  const GroupArgs a = groupings(b, q, fold);
+  const dim3 per_item((unsigned)((a.item0[a.n] + 255) / 256));
+  const uint2 *x = sort_items(c, c->bws, a.item0[a.n], a.key0[a.n], [&](uint2 *items) {
+    group_items_kernel<<<per_item, dim3(256), 0, c->stream>>>(a, items);
+  });
   group_write_kernel<<<per_item, dim3(256), 0, c->stream>>>(a, x);
   HIP_TRY(hipGetLastError());
   // (while a stream is being captured nothing runs: eager calls make them for themselves)
@@ -1891,11 +1902,11 @@ int find_distinct(xrl_ctx *c, xrl_batch *b) {
 
 // The sender index of a batch: out_ptr, and the receiver-order positions of the edges grouped by sender, ascending.
 // A block per graph: a counting sort of the graph's edges in which each of four waves takes a quarter of them,
-// counted per wave and node (in LDS, or for graphs of more than kOutLdsNodes nodes in `count`, [4][N]).
+// counted per wave and node in LDS. Where a graph has more nodes than that holds, the batch's edges are sorted by sender as
+// one list: with one block and its counters in memory a graph of 200 k nodes and 400 k edges took 5.6 ms, so 0.09.
 constexpr int kOutLdsNodes = 8192;
-template <bool LDS>
 __global__ __launch_bounds__(256) void out_index_kernel(const int32_t *graph_node_ptr, const int32_t *in_ptr, const int32_t *in_src,
-                                                        int32_t *count, int32_t *out_ptr, int32_t *out_pos) {
+                                                        int32_t *out_ptr, int32_t *out_pos) {
   extern __shared__ __align__(16) int32_t out_cnt[];
   __shared__ int2 ws[4];
   const int g = blockIdx.x, t = threadIdx.x, lane = t & 63, w = t >> 6;
@@ -1905,7 +1916,7 @@ __global__ __launch_bounds__(256) void out_index_kernel(const int32_t *graph_nod
     return;
   }
   const int a = in_ptr[base], z = in_ptr[base + n];
-  volatile int32_t *cnt = LDS ? out_cnt : count + (size_t)4 * base;    // [4][n]
+  volatile int32_t *cnt = out_cnt;                                     // [4][n]
   for (int i = t; i < 4 * n; i += 256) cnt[i] = 0;
   __syncthreads();
   const int quarter = ((z - a + 3) / 4 + 63) / 64 * 64, e0 = a + w * quarter, e1 = e0 + quarter < z ? e0 + quarter : z;
@@ -1950,23 +1961,62 @@ __global__ __launch_bounds__(256) void out_index_kernel(const int32_t *graph_nod
     if (in) out_pos[place] = e + lane;
   }
 }
-size_t out_index_bytes(const xrl_batch *b) { return b->max_graph_nodes > kOutLdsNodes ? (size_t)4 * b->N * 4 : 0; }
-// Makes the batch's sender index on the context's stream unless it is there (for the owner, whose stream orders its calls;
-// other contexts make it each time, and a graph in every replay: the same values). scratch: out_index_bytes.
-int make_out_index(xrl_ctx *c, const xrl_batch *b, int32_t *scratch) {
-  if (b->G == 0 || (b->out_index && b->owner == c->id)) return XRL_OK;
-  const xrl_batch_device &d = b->dev;
-  const bool lds = b->max_graph_nodes <= kOutLdsNodes;
-  const size_t bytes = lds ? (size_t)16 * std::max(b->max_graph_nodes, 1) : 0;
-  static bool attr_set = false;
-  if (!attr_set) {
-    HIP_TRY(hipFuncSetAttribute((const void *)out_index_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, 16 * kOutLdsNodes));
-    attr_set = true;
+__global__ __launch_bounds__(256) void out_items_kernel(const int32_t *in_src, int64_t E, uint2 *items) {
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (e < E) items[e] = make_uint2((uint32_t)in_src[e], (uint32_t)e);
+}
+// From the sorted items: the position of each, and each sender's first, by search (a sender may have none).
+__global__ __launch_bounds__(256) void out_write_kernel(const uint2 *items, int64_t E, int64_t N, int32_t *out_ptr, int32_t *out_pos) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < E) out_pos[i] = (int32_t)items[i].y;
+  if (i > N) return;
+  int64_t lo = 0, hi = E;
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) >> 1;
+    if (items[mid].x < (uint32_t)i) lo = mid + 1;
+    else hi = mid;
   }
-  if (lds) out_index_kernel<true><<<dim3((unsigned)b->G), dim3(256), bytes, c->stream>>>(d.graph_node_ptr, d.in_ptr, d.in_src, nullptr, d.out_ptr, d.out_pos);
-  else out_index_kernel<false><<<dim3((unsigned)b->G), dim3(256), 0, c->stream>>>(d.graph_node_ptr, d.in_ptr, d.in_src, scratch, d.out_ptr, d.out_pos);
+  out_ptr[i] = (int32_t)lo;
+}
+size_t out_index_bytes(const xrl_batch *b) { return b->max_graph_nodes > kOutLdsNodes ? sort_bytes_of(b->E) : 0; }
+// Makes the batch's sender index on the context's stream unless it is there. Whichever context first needs it makes it; the others
+// wait for that (the block's event marks the end of it). A graph makes it in every replay unless it was there
+// before: the same values. scratch: out_index_bytes.
+int make_out_index(xrl_ctx *c, const xrl_batch *cb, char *scratch) {
+  xrl_batch *b = const_cast<xrl_batch *>(cb);
+  if (b->G == 0) return XRL_OK;
+  std::lock_guard<std::mutex> lk(b->out_mu);
+  xrl_batch_device &d = b->dev;
+  if (b->out_maker) {
+    if (b->out_maker == c->id) return XRL_OK;
+    RelaxedCapture relaxed;              // (this stream or another may be under capture: the wait is no part of it)
+    HIP_TRY(hipEventSynchronize((hipEvent_t)d.used));
+    return XRL_OK;
+  }
+  if (b->max_graph_nodes <= kOutLdsNodes) {
+    static bool attr_set = false;
+    if (!attr_set) {
+      HIP_TRY(hipFuncSetAttribute((const void *)out_index_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 16 * kOutLdsNodes));
+      attr_set = true;
+    }
+    out_index_kernel<<<dim3((unsigned)b->G), dim3(256), (size_t)16 * std::max(b->max_graph_nodes, 1), c->stream>>>(
+        d.graph_node_ptr, d.in_ptr, d.in_src, d.out_ptr, d.out_pos);
+  } else {
+    const dim3 per_edge((unsigned)((b->E + 255) / 256)), per_item((unsigned)((std::max(b->E, b->N + 1) + 255) / 256));
+    const uint2 *x = nullptr;
+    if (b->E > 0)
+      x = sort_items(c, scratch, b->E, (uint32_t)b->N, [&](uint2 *items) {
+        out_items_kernel<<<per_edge, dim3(256), 0, c->stream>>>(d.in_src, b->E, items);
+      });
+    out_write_kernel<<<per_item, dim3(256), 0, c->stream>>>(x, b->E, b->N, d.out_ptr, d.out_pos);
+  }
   HIP_TRY(hipGetLastError());
-  if (b->owner == c->id && !is_capturing(c)) const_cast<xrl_batch *>(b)->out_index = true;
+  if (is_capturing(c)) return XRL_OK;
+  hipEvent_t made = (hipEvent_t)d.used;
+  if ((made || went_well(hipEventCreateWithFlags(&made, hipEventDisableTiming)))) {
+    d.used = made;
+    if (went_well(hipEventRecord(made, c->stream))) b->out_maker = c->id;
+  }
   return XRL_OK;
 }
 
@@ -2057,7 +2107,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   }
   if (!q) {
     const size_t n = out_index_bytes(b);
-    int32_t *scratch = bump.take<int32_t>(n / 4);
+    char *scratch = bump.take<char>(n);
     if ((rc = make_out_index(c, b, scratch))) return rc;
   }
   bump.off = o_reduced;
@@ -2904,7 +2954,7 @@ int xrl_batch_upload(xrl_ctx *c, xrl_batch *b) {
   d.graph_tile_ptr = b->has_graph_tiles ? (int32_t *)(blk + b->o_graph_tile) : nullptr;
   d.agg_src = (int32_t *)(blk + o_as);
   b->encodes = 0;
-  b->out_index = false;
+  b->out_maker = 0;
   b->uploaded = true;
   return XRL_OK;
 }

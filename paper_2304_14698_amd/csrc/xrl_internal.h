@@ -5,6 +5,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -59,7 +60,7 @@ template <typename T> using RawVec = std::vector<T, RawAlloc<T>>;
 struct xrl_batch_device {
   void *block = nullptr;
   size_t bytes = 0;
-  void *used = nullptr;   // event behind the block's last use before this batch
+  void *used = nullptr;   // event behind the block's last use before this batch, then behind the making of the sender index
   int32_t *state_graph_ptr = nullptr, *graph_node_ptr = nullptr, *node_op = nullptr;
   int32_t *in_ptr = nullptr, *in_src = nullptr, *in_dst = nullptr;
   int32_t *out_ptr = nullptr, *out_pos = nullptr, *node_graph = nullptr, *tile_ptr = nullptr;
@@ -125,7 +126,8 @@ struct xrl_batch {
   std::atomic<PackedArrays *> view{nullptr};   // made by the first xrl_batch_host_view
   xrl_batch_device dev;
   bool uploaded = false;
-  bool out_index = false;                  // the device's sender index has been made on the owner's stream
+  std::mutex out_mu;                       // of the sender index on the device:
+  uint64_t out_maker = 0;                  // the context that made it, 0: none yet (dev.used then marks the end of that)
   // the context that uploaded it: its other users wait for its transfer, and a device block that only it
   // has used goes back to its pool (reuse on the same stream is ordered), any other is freed
   uint64_t owner = 0;

@@ -8,6 +8,7 @@ import pytest
 
 import synth
 from test_gpu_backward import run_stable_case, xrl  # noqa: F401
+from test_gpu_forward import weights_for
 
 pytestmark = pytest.mark.gpu
 
@@ -29,3 +30,68 @@ def test_sender_index(xrl, nodes, hub, monkeypatch):  # noqa: F811
     graphs[0] = _with_hub(rng, graphs[0], hub)
     state = synth.concat_states([(graphs, np.ones(len(graphs), np.uint8))])
     run_stable_case(xrl, model, state, "fixed", max_nodes=max(g.n_nodes for g in graphs))
+
+
+def _chain(rng, n, d):
+    """A state of one graph of n nodes, node i with d in-edges from the fifty before it; the last half sends to nobody."""
+    model, state = synth.make_config(1)
+    model.update(hidden=64, precision="bf16", rounds=1)
+    dst = np.repeat(np.arange(n), d).astype(np.int32)
+    src = (np.maximum(0, dst - 1 - rng.integers(0, 50, len(dst))) // 2).astype(np.int32)
+    graph = dict(n_states=1, state_graph_ptr=np.array([0, 1], np.int32), graph_node_ptr=np.array([0, n], np.int32),
+                 graph_edge_ptr=np.array([0, len(dst)], np.int32), node_op=rng.integers(0, 30, n).astype(np.int32),
+                 node_dense=rng.standard_normal((n, model["n_node_dense"])).astype(np.float32), edge_src=src, edge_dst=dst,
+                 edge_feat=rng.standard_normal((len(dst), model["d_edge"])).astype(np.float32),
+                 graph_global=np.zeros((1, model["d_global"]), np.float32), slot_mask=np.ones(1, np.uint8))
+    return model, graph
+
+
+@pytest.mark.parametrize("round_kind", ["mlp", "gat"])
+def test_sender_index_of_a_large_graph_is_made_once(xrl, round_kind, monkeypatch):  # noqa: F811
+    """A graph of 200 k nodes: the backward pass that makes the index may take 1.5 times one that finds it and half a
+    millisecond, and one of another context, on another stream, the same. Same gradients, bit for bit."""
+    import torch
+    monkeypatch.setenv("XRL_DISTINCT_MIN_US", "-1")
+    rng = np.random.Generator(np.random.PCG64(22))
+    model, state = _chain(rng, 200000, 2)
+    model.update(round_kind=round_kind)
+    w = weights_for(model)
+    side = torch.cuda.Stream()
+    enc, other = xrl.Encoder(model, w), xrl.Encoder(model, w, stream=side)
+
+    def backward(e, b):
+        with torch.cuda.stream(e.stream):
+            emb = e.encode(b, save_for_backward=True)
+            dw = torch.zeros(e.n_weights, device="cuda")
+            up = torch.ones_like(emb)
+            t = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            t[0].record()
+            e.encode_backward(b, up, dw)
+            t[1].record()
+            torch.cuda.synchronize()
+            return dw, t[0].elapsed_time(t[1])
+    for _ in range(3):                                        # (the workspaces have their sizes)
+        batch = enc.pack(state)
+        want, first = backward(enc, batch)
+        dw, kept = backward(enc, batch)
+        assert torch.equal(dw, want)
+        for e in (other, enc, other):
+            dw, also = backward(e, batch)
+            assert torch.equal(dw, want)
+        batch.free()
+    print(f"{first:.3f} ms, then {kept:.3f}, another context's {also:.3f}")
+    assert first <= 1.5 * kept + 0.5 and also <= 1.5 * kept + 0.5
+    enc.close()
+    other.close()
+
+
+@pytest.mark.parametrize("edges", [0, 1, 40])
+def test_sender_index_of_a_large_graph_with_few_edges(xrl, edges, monkeypatch):  # noqa: F811
+    monkeypatch.setenv("XRL_DISTINCT_MIN_US", "-1")
+    rng = np.random.Generator(np.random.PCG64(23))
+    model, _ = synth.make_config(1)
+    model.update(hidden=64, precision="fp32", rounds=1)
+    g = synth.layered_dag(rng, 8300)
+    pick = rng.choice(len(g.src), edges, replace=False)
+    g = dataclasses.replace(g, src=g.src[pick], dst=g.dst[pick], efeat=g.efeat[pick])
+    run_stable_case(xrl, model, synth.concat_states([([g], np.ones(1, np.uint8))]), "fixed", max_nodes=g.n_nodes)
