@@ -1,6 +1,7 @@
 """Attention rounds at the edges of their kernels: receivers of no, one, two (requested together) and more in-edges,
 node counts around a 32-row tile, a lone node; every width. Forward and backward against the oracle, at the
-criteria of test_gpu_backward.py (its figures for tiny graphs in bf16)."""
+criteria of test_gpu_backward.py for attention rounds. In bf16 there are as many such graphs that a ReLU mask which
+the forward's rounding turns over is a small share of a gradient."""
 import dataclasses
 
 import numpy as np
@@ -29,6 +30,7 @@ def test_attention_edge_cases(xrl, hidden, precision):  # noqa: F811
     rng = np.random.Generator(np.random.PCG64(31))
     model, _ = synth.make_config(1)
     model.update(hidden=hidden, precision=precision, round_kind="gat", rounds=2)
-    graphs = [_graph(rng, n, d) for n, d in ((27, (0, 1, 2, 3, 5)), (33, (1,)), (64, (2,)), (1, (0,)), (40, (0, 0, 40)))]
+    kinds = ((27, (0, 1, 2, 3, 5)), (33, (1,)), (64, (2,)), (1, (0,)), (40, (0, 0, 40)))
+    graphs = [_graph(rng, n, d) for _ in range(1 if precision == "fp32" else 40) for n, d in kinds]
     state = synth.concat_states([(graphs, np.ones(len(graphs), np.uint8))])
-    run_backward_case(xrl, model, state, weights_for(model), bf16_rel=0.8, bf16_cos=0.75)
+    run_backward_case(xrl, model, state, weights_for(model), bf16_rel=0.3, bf16_cos=0.95)

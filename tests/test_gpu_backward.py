@@ -230,8 +230,8 @@ def test_backward_single_learned_matrix_per_layer(xrl, round_kind, cfg, hidden, 
 
 @pytest.mark.parametrize("hidden", [128, 256])
 def test_backward_wide_weight_gradient_tiles(xrl, hidden, monkeypatch):
-    """The 256-column tiles of the weight-gradient kernel (used from 2^20 rows on) forced onto a
-    small batch, where row slices are short and ragged."""
+    """The 256-column tiles of the weight-gradient kernel (at H = 256, used from 2^18 rows on) forced onto a
+    small batch, where row slices are short and ragged; H = 128, which has none, is not to take notice."""
     monkeypatch.setenv("XRL_WGRAD_WIDE_MIN_ROWS", "0")
     model, state = synth.make_config(4, n_cand=3)
     model.update(hidden=hidden, precision="bf16", rounds=2)

@@ -96,7 +96,8 @@ def test_weight_gradient_product(xrl, hidden, precision):
 
 @pytest.mark.parametrize("hidden", [128, 256])
 def test_weight_gradient_product_wide_tiles(xrl, hidden, monkeypatch):
-    """The 256-column tiles (used from 2^20 rows on), forced onto the same small batch."""
+    """The 256-column tiles of H = 256 (used from 2^18 rows on), forced onto the same small batch; H = 128, which has none,
+    is not to take notice."""
     monkeypatch.setenv("XRL_WGRAD_WIDE_MIN_ROWS", "0")
     model, state = synth.make_config(4, n_cand=3)
     model.update(hidden=hidden, precision="bf16")

@@ -117,3 +117,46 @@ def test_backward_of_a_larger_batch_leaves_a_graphs_workspace():
             assert torch.equal(dw, want)
         for x in large + [small, alone, enc]:
             x.free() if hasattr(x, "free") else x.close()
+
+
+@pytest.mark.parametrize("form", ["kept", "reduced", "attention", "attention fp32"])
+def test_little_room_launches_mlp_by_mlp(form, monkeypatch):
+    """Room for the largest MLP's gradients alone: the others wait for the launch of those before, in the same place. Against all of
+    them in one launch: what is multiplied is the same, in bits, so a tensor may differ by the order of its sums alone,
+    2^-24 times the root of its additions (a few hundred: 1e-6) of the sum of its terms' sizes, here a few times the
+    tensor. By form: dz2 written into the room by the gather of a whole batch, by the class sums of a reduced one; dz1
+    read by dh = dz W^T after its product has been queued, and reductions alone in the queue, 26 jobs of them."""
+    monkeypatch.setenv("XRL_PERSISTENT_MIN_ROWS", "0")
+    monkeypatch.setenv("XRL_RESIDENT_MAX_GRAPHS", "0")
+    monkeypatch.setenv("XRL_DISTINCT_MIN_US", "0" if form == "reduced" else "-1")
+    import torch
+    rng = np.random.Generator(np.random.PCG64(13))
+    model, _ = synth.make_config(1)
+    gat = form.startswith("attention")
+    model.update(hidden=128, precision="fp32" if form.endswith("fp32") else "bf16", rounds=12 if gat else 5, round_kind="gat" if gat else "mlp")
+    state = synth.concat_states([synth.make_state(rng, synth.resnet_dag(rng, 4), n, by_block=True) for n in (30, 9)])
+    w, got = weights_for(model), []
+    up = torch.randn(41, 128, generator=torch.Generator().manual_seed(2)).cuda()
+    for room in ("0", None):
+        monkeypatch.delenv("XRL_GRAD_ROOM", raising=False)
+        if room is not None:
+            monkeypatch.setenv("XRL_GRAD_ROOM", room)
+        enc = xrl_package.Encoder(model, w)
+        batch = enc.pack(state)
+        enc.encode(batch, save_for_backward=True)
+        assert (enc.batch_level(batch, 0)[0] < batch.N) == (form == "reduced")
+        dw = torch.zeros(enc.n_weights, device="cuda")
+        enc.encode_backward(batch, up, dw)                    # (workspaces)
+        dw.zero_()
+        enc.set_timing(True)
+        enc.encode_backward(batch, up, dw)
+        launches = enc.read_timing("wgrad")[1]
+        assert launches >= 5 if room == "0" else launches <= 2
+        got.append(dw.double().cpu().numpy())
+        batch.free()
+        enc.close()
+    o = 0
+    for name, shape in xrl_package.weight_layout(model):
+        a, b = (x[o:o + int(np.prod(shape))] for x in got)
+        o += int(np.prod(shape))
+        assert np.linalg.norm(a - b) <= 1e-5 * np.linalg.norm(b), name
