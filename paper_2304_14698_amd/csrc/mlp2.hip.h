@@ -668,14 +668,18 @@ __global__ __launch_bounds__(2 * H) void mlp2_split3_kernel(const Mlp2Args a) {
 #pragma unroll
   for (int c = 0; c < RING; ++c) wq[c] = weights(a.W2s, c);
   __syncthreads();                                              // (every wave has read its input fragments)
+  float odd = 0.f;                                              // a NaN if one of them is not finite, which then makes the row's every output one
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    acc[r] += corr[r];
+    odd = fmaf(acc[r], 0.f, odd);
+  }
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     float z[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float v = acc[8 * q + j] + corr[8 * q + j];
-      z[j] = fabsf(v) < INFINITY ? relu_f32(v) : NAN;           // (not finite: the row's every output becomes a NaN)
-    }
+    for (int j = 0; j < 8; ++j) z[j] = relu_f32(acc[8 * q + j]);
+    if (q == 0) z[0] += odd;
     share(2 * w + q, split3(z));
   }
 #pragma unroll
@@ -689,15 +693,17 @@ __global__ __launch_bounds__(2 * H) void mlp2_split3_kernel(const Mlp2Args a) {
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] += corr[r];
   // ---------------- rows with a value that has no parts, or that overflowed: once more, in fp32
-  float sum0 = 0.f;
+  odd = 0.f;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) sum0 = fmaf(acc[r], 0.f, sum0);  // (0, or a NaN)
-  const unsigned long long odd = __ballot(sum0 != 0.f && l32 < nv);
-  for (unsigned rows = (unsigned)(odd | odd >> 32); rows; rows &= rows - 1) {
-    const int r = __builtin_ctz(rows);                          // (lane r of the first half: its pointers are the row's)
-    const float *xa = (const float *)__shfl((unsigned long long)pa, r), *xb = (const float *)__shfl((unsigned long long)pb, r);
+  for (int r = 0; r < 16; ++r) odd = fmaf(acc[r], 0.f, odd);
+  const unsigned long long lanes = __ballot(odd != 0.f && l32 < nv);
+  for (unsigned rows = (unsigned)(lanes | lanes >> 32); rows; rows &= rows - 1) {
+    const int r = __builtin_ctz(rows);
+    const int64_t ro = row0 + r;
+    const int64_t first = KIND == KIND_EDGE ? a.in_src[ro] : ro, second = KIND == KIND_EDGE ? a.in_dst[ro] : a.agg_src ? a.agg_src[ro] : ro;
+    const float *xa = (const float *)a.h + (size_t)first * H, *xe = a.edge_feat + (KIND == KIND_EDGE ? (size_t)ro * a.De : 0);
+    const float *xb = second < 0 ? (const float *)a.zero_row : (const float *)(KIND == KIND_EDGE ? a.h : a.agg) + (size_t)second * H;
     const int K = KIND == KIND_EDGE ? 2 * H + a.De : 2 * H;
-    const float *xe = a.edge_feat + (KIND == KIND_EDGE ? (size_t)__shfl(row, r) * a.De : 0);
     constexpr int NF = H / 64;                                  // relu(z1) of features lane, lane + 64, ..
     float z[NF];
 #pragma unroll
