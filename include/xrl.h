@@ -177,8 +177,9 @@ int xrl_weight_tensor(const xrl_model_desc *model, int32_t index, char *name, si
  * process forked off one with a context packs, views and frees batches, its parent's included, in
  * ordinary memory without a call to the GPU's runtime.
  * Batches current + candidate graphs into one meta-graph with its slot mask (Section 3.3.2):
- * validates, converts endpoints to global node ids, sorts edges by receiver (stable) and builds
- * the sender-side index. Errors: NULL, SHAPE, INDEX, VALUE (non-finite attribute), MASK. */
+ * validates, converts endpoints to global node ids and sorts edges by receiver (stable). (The sender-side
+ * index follows from that: the device makes its own, xrl_batch_host_view writes the host's on first
+ * request.) Errors: NULL, SHAPE, INDEX, VALUE (non-finite attribute), MASK. */
 int xrl_pack_state(const xrl_model_desc *model, const xrl_state_desc *state, xrl_batch **out);
 /* xrl_pack_state_edits: the same packed batch as xrl_pack_state on the candidate graphs the edits
  * stand for (every array of xrl_batch_host_view identical; in_eid counts edges in the order stated

@@ -575,8 +575,11 @@ __global__ __launch_bounds__(2 * H) void mlp2_split_kernel(const Mlp2Args a) {
 // input rows and relu(z1) are cut on their way into LDS. Bound by the weights' way from L2 (307 KB a tile) from a few
 // tiles per compute unit on. us, fp32 instructions / parts: edge 168 tiles 15.8 / 13.8, 904 38.0 / 28.6, 1768 62.5 / 44.6; node
 // 944 tiles 39.0 / 26.1. Relative error of the embeddings against float64, nine states, geometric mean 1.44e-7 / 1.32e-7;
-// of the gradients, five states, 2.82e-7 / 2.54e-7. (H = 256: embeddings 1.95e-7 / 1.83e-7, but the heads' gradients of a state,
-// differences of its slots, came out 1.3 times as far off: left on fp32 instructions. H = 64: latency, not products.)
+// of the gradients, five states, 2.82e-7 / 2.54e-7; of the heads' gradients of a state, differences of its slots, 104 states,
+// 1.01 +- 0.05 times the fp32 instructions'. Rows with a value that has no parts, or that overflow, are computed once more by
+// fp32 multiply-adds (0.3 us a launch to look for them). (H = 256: embeddings 1.95e-7 / 1.83e-7, but the heads' gradients of five
+// states came out 1.3 times as far off: left on fp32 instructions. H = 64 is left on them too: in a copy of the library parts
+// took 76 us per encode of 0.5 k nodes for 80, 141 for 177 of 34 k, 776 for 1106 of 338 k; its error has not been measured.)
 template <int H>
 struct Split3Tile {
   static constexpr int HS = H / 16, MB = H / 32, NC2 = 2 * MB;

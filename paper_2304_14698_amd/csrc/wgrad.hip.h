@@ -83,9 +83,9 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 // as many again, in fp32 at H = 256 in the partial tile. Relative error of 2^20 rows' products of random sign
 // against float64, one chain / folded: fp32 5.9e-7 / 2.3e-7 (H = 256 8.5e-7 / 2.4e-7), bf16, 2^22 rows, 5.0e-7 / 2.2e-7; of the
 // encoder's fp32 gradients, 5 k to 110 k nodes, 1.0 to 3 times less. It costs nothing that can be measured at H <= 128 and
-// 12 % of the launch in fp32 at H = 256 (93 k nodes 4.5 / 5.0 ms). bf16 at H = 256 keeps one chain (5.0e-7 at 2^21 rows, ten thousand
-// times below its operands' rounding): 160 of 256 registers hold sums, and the tile's way to memory and back every 2048
-// rows cost a quarter of the launch.
+// 12 % of the launch in fp32 at H = 256 (93 k nodes 4.5 / 5.0 ms). bf16 at H = 256 keeps one chain (5.0e-7 at 2^21 rows; the
+// gradients of 110 k nodes are 3.1e-2 from float64 for the operands' rounding, to three digits whatever the chain): 160 of 256
+// registers hold sums, and the tile's way to memory and back every 2048 rows cost a quarter of the launch.
 // A stage goes from memory into LDS directly (lds_direct_load16), as the rows lie there: 16-byte piece s of LDS
 // row r holds piece s ^ swizzle(r), which moves the rows r .. r + 3 that a transpose read touches to
 // different banks where their lengths, multiples of 256 bytes, would put them on the same.

@@ -120,7 +120,8 @@ __global__ __launch_bounds__(256) void arrange_weights_kernel(const SwzJob *jobs
 }
 }  // namespace
 
-// kernels whose launches can be timed with HIP events (xrl_set_timing / xrl_read_timing)
+// kernels whose launches can be timed with HIP events (xrl_set_timing / xrl_read_timing; WGRAD_EDGE, _NODE and _EMBED, whose products
+// share launches, are names that may still be read: no launch is only theirs)
 enum { TK_EMBED = 0, TK_EDGE, TK_EDGE_FIXUP, TK_NODE, TK_POOL, TK_READOUT, TK_HEADS, TK_GAT_LINEAR,
        TK_GAT_AGGREGATE, TK_BWD_EDGE, TK_BWD_NODE, TK_BWD_EMBED, TK_WGRAD, TK_GRAD_GATHER, TK_GAT_BWD, TK_RESIDENT,
        TK_WGRAD_EDGE, TK_WGRAD_NODE, TK_WGRAD_EMBED, TK_ROUND, TK_COUNT };
@@ -2834,7 +2835,8 @@ __global__ void expand_rows_kernel(const int32_t *from, int64_t n, int width, co
 // What follows from a batch's in-edge ranges and its graphs' node ranges, one thread per node: agg_src (n for a
 // node with in-edges, -1 for one without), the receiver of every edge and the graph of every node. Packing and
 // sending them and the sender index instead took a fifth of a batch's bytes (half of one packed from edits):
-// us per step, 129 graphs of 565 nodes 347 / 325 without, from edits 438 / 376, 2080 graphs of 338 nodes 1609 / 1468.
+// us per step, four alternating runs each (the host's part varies): 129 graphs of 565 nodes 365 to 388 / 322 to 384 without, from
+// edits 417 to 448 / 365 to 379, 2080 graphs of 338 nodes 1929 to 2191 / 1536 to 1713.
 __global__ __launch_bounds__(256) void derive_index_kernel(const int32_t *in_ptr, const int32_t *graph_node_ptr, int64_t N, int G,
                                                            int32_t *agg_src, int32_t *in_dst, int32_t *node_graph) {
   const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
