@@ -2013,8 +2013,9 @@ int make_out_index(xrl_ctx *c, const xrl_batch *cb, char *scratch) {
   }
   HIP_TRY(hipGetLastError());
   if (is_capturing(c)) return XRL_OK;
+  RelaxedCapture relaxed;
   hipEvent_t made = (hipEvent_t)d.used;
-  if ((made || went_well(hipEventCreateWithFlags(&made, hipEventDisableTiming)))) {
+  if (made || went_well(hipEventCreateWithFlags(&made, hipEventDisableTiming))) {
     d.used = made;
     if (went_well(hipEventRecord(made, c->stream))) b->out_maker = c->id;
   }

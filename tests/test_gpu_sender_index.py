@@ -95,3 +95,48 @@ def test_sender_index_of_a_large_graph_with_few_edges(xrl, edges, monkeypatch): 
     pick = rng.choice(len(g.src), edges, replace=False)
     g = dataclasses.replace(g, src=g.src[pick], dst=g.dst[pick], efeat=g.efeat[pick])
     run_stable_case(xrl, model, synth.concat_states([([g], np.ones(1, np.uint8))]), "fixed", max_nodes=g.n_nodes)
+
+
+@pytest.mark.parametrize("nodes,made", [(300, True), (300, False), (8300, True), (8300, False)])
+def test_sender_index_under_capture(xrl, nodes, made, monkeypatch):  # noqa: F811
+    """A captured backward pass of a context that did not upload the batch: the index is there already, or every replay makes
+    it. Replays among eager passes of both contexts."""
+    import torch
+    monkeypatch.setenv("XRL_DISTINCT_MIN_US", "-1")
+    rng = np.random.Generator(np.random.PCG64(24))
+    model, state = _chain(rng, nodes, 2)
+    model.update(round_kind="gat")
+    w = weights_for(model)
+    side = torch.cuda.Stream()
+    enc, other = xrl.Encoder(model, w), xrl.Encoder(model, w, stream=side)
+    twin, batch = enc.pack(state), enc.pack(state)
+    up, dw = torch.ones(1, 64, device="cuda"), torch.zeros(enc.n_weights, device="cuda")
+
+    def step(e, b):
+        with torch.cuda.stream(e.stream):
+            e.encode(b, save_for_backward=True)
+            out = torch.zeros_like(dw)
+            e.encode_backward(b, up, out)
+            torch.cuda.synchronize()
+            return out
+    want = step(enc, twin)
+    assert torch.equal(step(other, twin), want)               # (the workspaces have their sizes)
+    if made:
+        step(enc, batch)
+    with torch.cuda.stream(side):
+        other.encode(batch, save_for_backward=True)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side, capture_error_mode="relaxed"):
+            dw.zero_()
+            other.encode_backward(batch, up, dw)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(dw, want)
+        dw.zero_()
+        assert torch.equal(step(enc, batch), want) and torch.equal(step(other, batch), want)
+    batch.free()
+    twin.free()
+    enc.close()
+    other.close()
