@@ -441,6 +441,8 @@ __device__ __forceinline__ void mlp2_wave_tile(const Mlp2Args &a, const int64_t 
 // themselves). Same operations in the same order per output: the same bits. Edge kernel, us, a wave
 // per tile / split: fp32 H = 128: 158 tiles 39.7 / 14.1, 2278 105 / 88, 13.7 k 479 / 458; H = 256: 158 tiles
 // 171 / 35, 2278 514 / 275; H = 64: 200 tiles 16.4 / 12.6, 2278 35.2 / 35.0; bf16 H = 256: 158 tiles 40.8 / 11.6.
+// The requests keep their distance only behind scheduling barriers (see the loops): without, fp32 H = 256 edge 971 tiles 111.1 us, with
+// 108.6, node 119.5 / 107.7, 1916 tiles 213 / 209 and 202 / 184; H = 64 1915 tiles 25.7 / 23.4 and 23.2 / 21.4; bf16 H = 256 179 tiles 11.8 / 10.7.
 template <typename T, int H>
 struct SplitTile {
   static constexpr int V = Operand<T>::V, HS = H / (2 * V), MB = H / 32, QB = 32 / (2 * V);
@@ -472,14 +474,16 @@ __global__ __launch_bounds__(2 * H) void mlp2_split_kernel(const Mlp2Args a) {
     nv = a.n_rows - row0 < 32 ? (int)(a.n_rows - row0) : 32;
   }
   const int64_t row = row0 + (l32 < nv ? l32 : nv - 1);         // clamp loads; stores are guarded
-  f32x16 acc;
+  f32x16 acc, b2;                                               // (all loads in front of the barriers: one behind is waited for by itself)
+  [[maybe_unused]] EdgeTileMeta meta;
   // ---------------- layer 1
   if constexpr (KIND != KIND_EMBED) {
     const vec *W1 = (const vec *)a.W1s + (size_t)w * 64 + lane;
     const T *pa, *pb;
     if constexpr (KIND == KIND_EDGE) {
+      meta = load_edge_meta(a.in_dst, a.n_rows, row0, nv, l32);
       pa = (const T *)a.h + (size_t)a.in_src[row] * H + g * V;
-      pb = (const T *)a.h + (size_t)a.in_dst[row] * H + g * V;
+      pb = (const T *)a.h + (size_t)meta.dst * H + g * V;
     } else {
       pa = (const T *)a.h + (size_t)row * H + g * V;
       const int64_t ar = a.agg_src ? (int64_t)a.agg_src[row] : row;
@@ -498,15 +502,20 @@ __global__ __launch_bounds__(2 * H) void mlp2_split_kernel(const Mlp2Args a) {
     [[maybe_unused]] TailRaw<V> xt;
     if constexpr (KIND == KIND_EDGE) xt = load_tail<V>(a.edge_feat + (size_t)row * a.De, a.De, 0, g);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = a.b1[32 * w + acc_row(r, g)];
+    for (int r = 0; r < 16; ++r) { acc[r] = a.b1[32 * w + acc_row(r, g)]; b2[r] = a.b2[32 * w + acc_row(r, g)]; }
     vec *xs = (vec *)smem;                                      // [2 HS][64]
 #pragma unroll
     for (int i = 0; i < MINE; ++i) xs[(s0 + i) * 64 + lane] = x[i];
     __syncthreads();
+    vec x0 = xs[lane];
 #pragma unroll
     for (int s = 0; s < 2 * HS; ++s) {
-      Opd::mma(wq[s % RING], xs[s * 64 + lane], acc);
+      const vec x1 = xs[(s + 1 < 2 * HS ? s + 1 : 0) * 64 + lane];
+      Opd::mma(wq[s % RING], x0, acc);
       if (s + RING < 2 * HS || (KIND == KIND_EDGE && s + RING == 2 * HS)) wq[s % RING] = W1[(size_t)(s + RING) * MB * 64];
+      x0 = x1;
+      // the compiler otherwise moves every request down to its use, to save registers, and each is waited for by itself
+      __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (KIND == KIND_EDGE) {
       const float *xe = a.edge_feat + (size_t)row * a.De;
@@ -524,9 +533,9 @@ __global__ __launch_bounds__(2 * H) void mlp2_split_kernel(const Mlp2Args a) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const f32x4 t = *(const f32x4 *)(trow + 8 * q);
-      const f32x4 b = *(const f32x4 *)(a.b1 + 32 * w + 8 * q + 4 * g);
+      const f32x4 b = *(const f32x4 *)(a.b1 + 32 * w + 8 * q + 4 * g), c = *(const f32x4 *)(a.b2 + 32 * w + 8 * q + 4 * g);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[4 * q + j] = t[j] + b[j];
+      for (int j = 0; j < 4; ++j) { acc[4 * q + j] = t[j] + b[j]; b2[4 * q + j] = c[j]; }
     }
     for (int s = 0; s < a.nslabx; ++s) {
       const f32x4 xv = embed_columns(er, a.edge_feat, a.De, a.Dd, s * 8 + g * 4);
@@ -543,13 +552,16 @@ __global__ __launch_bounds__(2 * H) void mlp2_split_kernel(const Mlp2Args a) {
   if constexpr (KIND != KIND_EMBED) __syncthreads();            // (every wave has read its input fragments)
 #pragma unroll
   for (int q = 0; q < QB; ++q) zs[(w * QB + q) * 64 + lane] = relu_operand<T>(acc, q);
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = a.b2[32 * w + acc_row(r, g)];
+  acc = b2;
   __syncthreads();
+  vec z0 = zs[lane];
 #pragma unroll
   for (int c = 0; c < NC2; ++c) {
-    Opd::mma(wq[c % RING2], zs[c * 64 + lane], acc);
+    const vec z1 = zs[(c + 1 < NC2 ? c + 1 : 0) * 64 + lane];
+    Opd::mma(wq[c % RING2], z0, acc);
     if (c + RING2 < NC2) wq[c % RING2] = W2[(size_t)(c + RING2) * MB * 64];
+    z0 = z1;
+    __builtin_amdgcn_sched_barrier(0);
   }
   // ---------------- epilogue on this wave's 32 features
   T *out = (T *)a.out;
@@ -561,9 +573,8 @@ __global__ __launch_bounds__(2 * H) void mlp2_split_kernel(const Mlp2Args a) {
     if constexpr (KIND == KIND_EMBED)
       if (w == 0) zero_source_rows<T, H>(a, row0, nv, a.in_ptr[row + 1] == a.in_ptr[row], lane);
   } else {
-    const EdgeTileMeta m = load_edge_meta(a.in_dst, a.n_rows, row0, nv, l32);
     f32x16 one[1] = {acc};
-    const EdgeRoute e = edge_run_sums<1>(one, m, nv, lane);
+    const EdgeRoute e = edge_run_sums<1>(one, meta, nv, lane);
     store_block_rows_via_lds<T, H>(out, e.dsel, w, lane, one[0], stage);
     if (e.to_c0 || e.to_c1) store_tile_rows<float, H>(a.carry, wt * 2 + (e.to_c1 ? 1 : 0), true, w, g, one[0]);
   }
@@ -572,9 +583,11 @@ __global__ __launch_bounds__(2 * H) void mlp2_split_kernel(const Mlp2Args a) {
 // The same split form for the fp32 edge and node MLPs of H = 128, whose launches were bound by the matrix cores (12.5 k
 // cycles of fp32 matrix instructions per wave and edge tile): operands in three bf16 parts (Split3), 4.8 k cycles of
 // bf16 ones. Weights come in parts (arrange_weights_kernel: the three parts of a fragment one behind the other),
-// input rows and relu(z1) are cut on their way into LDS. Bound by the weights' way from L2 (307 KB a tile) from a few
-// tiles per compute unit on. us, fp32 instructions / parts: edge 168 tiles 15.8 / 13.8, 904 38.0 / 28.6, 1768 62.5 / 44.6; node
-// 944 tiles 39.0 / 26.1. Relative error of the embeddings against float64, nine states, geometric mean 1.44e-7 / 1.32e-7;
+// input rows and relu(z1) are cut on their way into LDS. Three blocks share a compute unit, each a chain of indices, rows, products
+// and stores; from a few tiles per compute unit on the matrix cores are busy about half of the time (two tiles a block, for half the weights'
+// way from L2, gained 5 % at 5000 tiles and lost a third at 300). us, fp32 instructions / parts / parts with the
+// weights requested four slabs ahead throughout: edge 179 tiles 15.8 / 14.1 / 11.5, 969 38.0 / 27.7 / 25.0, 1918 62.5 / 47.6 / 43.4; node
+// 179 tiles - / 12.8 / 10.1, 969 39.0 / 25.1 / 22.8. Relative error of the embeddings against float64, nine states, geometric mean 1.44e-7 / 1.32e-7;
 // of the gradients, five states, 2.82e-7 / 2.54e-7; of the heads' gradients of a state, differences of its slots, 104 states,
 // 1.01 +- 0.05 times the fp32 instructions'. Rows with a value that has no parts, or that overflow, are computed once more by
 // fp32 multiply-adds (0.3 us a launch to look for them). (H = 256: embeddings 1.95e-7 / 1.83e-7, but the heads' gradients of five
@@ -620,12 +633,14 @@ __global__ __launch_bounds__(2 * H) void mlp2_split3_kernel(const Mlp2Args a) {
 #pragma unroll
     for (int k = 0; k < 3; ++k) p[k * 64] = x.p[k];
   };
-  f32x16 acc, corr;
+  f32x16 acc, corr, b2;
   // ---------------- layer 1
   const float *pa, *pb;
+  [[maybe_unused]] EdgeTileMeta meta;
   if constexpr (KIND == KIND_EDGE) {
+    meta = load_edge_meta(a.in_dst, a.n_rows, row0, nv, l32);
     pa = (const float *)a.h + (size_t)a.in_src[row] * H + g * 8;
-    pb = (const float *)a.h + (size_t)a.in_dst[row] * H + g * 8;
+    pb = (const float *)a.h + (size_t)meta.dst * H + g * 8;
   } else {
     pa = (const float *)a.h + (size_t)row * H + g * 8;
     const int64_t ar = a.agg_src ? (int64_t)a.agg_src[row] : row;
@@ -646,7 +661,11 @@ __global__ __launch_bounds__(2 * H) void mlp2_split3_kernel(const Mlp2Args a) {
   [[maybe_unused]] TailRaw<8> xt;
   if constexpr (KIND == KIND_EDGE) xt = load_tail<8>(a.edge_feat + (size_t)row * a.De, a.De, 0, g);
 #pragma unroll
-  for (int r = 0; r < 16; ++r) { acc[r] = a.b1[32 * w + acc_row(r, g)]; corr[r] = 0.f; }
+  for (int r = 0; r < 16; ++r) {
+    acc[r] = a.b1[32 * w + acc_row(r, g)];
+    b2[r] = a.b2[32 * w + acc_row(r, g)];
+    corr[r] = 0.f;
+  }
   auto cut = [](const f32x4 &lo, const f32x4 &hi) {
     const float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return split3(v);
@@ -654,10 +673,14 @@ __global__ __launch_bounds__(2 * H) void mlp2_split3_kernel(const Mlp2Args a) {
 #pragma unroll
   for (int i = 0; i < MINE; ++i) share(s0 + i, cut(x[i][0], x[i][1]));
   __syncthreads();
+  Split3 x0 = shared(0);
 #pragma unroll
   for (int s = 0; s < 2 * HS; ++s) {
-    mma_split3(wq[s % RING], shared(s), acc, corr);
+    const Split3 x1 = shared(s + 1 < 2 * HS ? s + 1 : 0);
+    mma_split3(wq[s % RING], x0, acc, corr);
     if (s + RING < 2 * HS || (KIND == KIND_EDGE && s + RING == 2 * HS)) wq[s % RING] = weights(a.W1s, s + RING);
+    x0 = x1;
+    __builtin_amdgcn_sched_barrier(0);                          // (see mlp2_split_kernel)
   }
   if constexpr (KIND == KIND_EDGE) {
     const float *xe = a.edge_feat + (size_t)row * a.De;
@@ -686,12 +709,16 @@ __global__ __launch_bounds__(2 * H) void mlp2_split3_kernel(const Mlp2Args a) {
     share(2 * w + q, split3(z));
   }
 #pragma unroll
-  for (int r = 0; r < 16; ++r) { acc[r] = a.b2[32 * w + acc_row(r, g)]; corr[r] = 0.f; }
+  for (int r = 0; r < 16; ++r) { acc[r] = b2[r]; corr[r] = 0.f; }
   __syncthreads();
+  x0 = shared(0);
 #pragma unroll
   for (int c = 0; c < NC2; ++c) {
-    mma_split3(wq[c % RING], shared(c), acc, corr);
+    const Split3 x1 = shared(c + 1 < NC2 ? c + 1 : 0);
+    mma_split3(wq[c % RING], x0, acc, corr);
     if (c + RING < NC2) wq[c % RING] = weights(a.W2s, c + RING);
+    x0 = x1;
+    __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] += corr[r];
@@ -734,9 +761,8 @@ __global__ __launch_bounds__(2 * H) void mlp2_split3_kernel(const Mlp2Args a) {
     for (int r = 0; r < 16; ++r) acc[r] = relu_f32(acc[r]);
     store_block_via_lds<float, H>(out, row0, nv, w, lane, acc, stage);
   } else {
-    const EdgeTileMeta m = load_edge_meta(a.in_dst, a.n_rows, row0, nv, l32);
     f32x16 one[1] = {acc};
-    const EdgeRoute e = edge_run_sums<1>(one, m, nv, lane);
+    const EdgeRoute e = edge_run_sums<1>(one, meta, nv, lane);
     store_block_rows_via_lds<float, H>(out, e.dsel, w, lane, one[0], stage);
     if (e.to_c0 || e.to_c1) store_tile_rows<float, H>(a.carry, wt * 2 + (e.to_c1 ? 1 : 0), true, w, g, one[0]);
   }
