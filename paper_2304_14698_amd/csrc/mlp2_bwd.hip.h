@@ -8,14 +8,14 @@
 //     y^T   = W2^T z1^T           (EDGE only: its per-edge output is not stored by the forward)
 //     dz1^T = W2 dz2^T            (W2 pre-arranged with the contraction over its columns)
 //     dx^T  = W1 dz1^T            (W1 pre-arranged with the contraction over its columns)
-// Weights: a block of 4 waves (128 rows) walks through the four weight matrices in units of
-// H / 16 fragments (1 KB each; the fragments one 32-feature output block needs), four units to a
-// group; in the bf16 instantiations a group is fetched from L2 once per block -- each wave a
-// quarter of it, requested a whole group (about 2000 MFMA cycles at H = 256) before it is needed
-// -- into a double-buffered LDS area and read from there by all four waves, one block barrier per
-// group (fetching every fragment per wave made the kernel L2-bound: 780 KB of weights per 32
-// rows at H = 256; groups of one unit left the fetch latency exposed). The fp32 instantiations
-// read their fragments straight from L2.
+// A block of H / 32 waves takes one tile of 32 rows, wave w the 32 output features of block w of z1, y and
+// dz1, and blocks w and H / 32 + w of dx; a product's input is shared through LDS as operand fragments, and a wave streams
+// its own slices of the weights, eight fragments ahead (mlp2_split_kernel does the forward the same way). What bounds it: few tiles,
+// the chain of dependent products, which is H / 32 times shorter than with a wave per tile; many, in fp32, the matrix cores (87 % busy at
+// H = 256), in bf16 the weights' way from L2. us per launch, a wave per tile (four of them sharing the weights through LDS in bf16) / this,
+// edge: fp32 H = 64: 1.8 k edges 29.0 / 13.1, 20 k 31.0 / 22.6, 158 k 108.7 / 99.4; H = 128: 91.5 / 20.6, 131 / 49.9, 370 / 302; H = 256:
+// 371 / 56.7, 534 / 166, 2128 / 1093; bf16: H = 64: 1.8 k 11.0 / 7.1, 39 k 16.0 / 13.4; H = 128: 18.8 / 9.3, 29.5 / 25.3; H = 256: 44.1 / 15.1, 95.9 / 62.8
+// (157 k, which only attributes of more than eight columns bring here in bf16, 245 / 251).
 // The kernel writes z1, dz1, dz2 as [rows, H] for the weight-gradient kernel, and dx:
 //   EDGE: per-edge gradients w.r.t. h_sender and h_receiver ([E, H] each; summed per node later),
 //   NODE: d/dh and d/dagg [N, H],   EMBED: nothing (its inputs are data).
@@ -32,6 +32,9 @@ struct Mlp2BwdArgs {
   const void *W2bt, *W1bt;   // contraction over the weight's columns (SWZ_CHAIN order)
   const float *b1, *b2;
   int nslab1;
+  const void *W1x;           // EMBED: see Mlp2Args
+  int nslabx;
+  const float *table;
   const void *h, *agg;       // forward inputs, operand type
   const int32_t *agg_src;    // NODE: [N] row of agg per node, -1 = none (zeros are read); or nullptr
   const void *zero_row;      // 1 KB of zeros
@@ -60,336 +63,173 @@ __device__ __forceinline__ bf16x8 acc_slab<bf16_t>(const f32x16 &acc, int q) {
                      acc[8 * q + 5], acc[8 * q + 6], acc[8 * q + 7]);
 }
 
-// Weight fragments for all four waves, UG units of UF fragments per group. SHARED: through LDS
-// (see the file header); otherwise each wave reads its own from global memory. `idx(u, j)` is
-// the index inside W (already offset by the lane) of fragment j of the group's u-th unit, or
-// negative if there is no such fragment.
-template <typename vecT, int UF, int UG, bool SHARED>
-struct WeightGroups {
-  static constexpr int GF = UF * UG, PW = GF / 4;         // fragments per group / fetched per wave
-  static_assert(GF % 4 == 0, "a group is fetched by four waves");
-  f32x4 (*buf)[GF][64];                                   // [2][GF][64] in LDS (SHARED)
-  int p = 0, wave, lane;
-  f32x4 r[PW];
-  template <typename Idx>
-  __device__ __forceinline__ void fetch(const vecT *W, Idx idx) {
-    if constexpr (SHARED) {
-#pragma unroll
-      for (int i = 0; i < PW; ++i) {
-        const int jg = wave * PW + i;
-        const int fi = idx(jg / UF, jg % UF);
-        if (fi >= 0) r[i] = __builtin_bit_cast(f32x4, W[(size_t)fi * 64]);
-      }
-    }
-  }
-  __device__ __forceinline__ void commit(int q) {
-    if constexpr (SHARED) {
-#pragma unroll
-      for (int i = 0; i < PW; ++i) buf[q][wave * PW + i][lane] = r[i];
-    }
-  }
-  // first group of a phase: fetch, store, barrier
-  template <typename Idx>
-  __device__ __forceinline__ void begin(const vecT *W, Idx idx) {
-    if constexpr (SHARED) {
-      fetch(W, idx);
-      commit(p);
-      __syncthreads();
-    }
-  }
-  // after the MFMAs of the current group: publish the next one (already fetched), swap
-  __device__ __forceinline__ void next(bool have_next) {
-    if constexpr (SHARED) {
-      if (have_next) commit(p ^ 1);
-      __syncthreads();
-      p ^= 1;
-    }
-  }
-  // fragment j of unit u of the current group
-  template <typename Idx>
-  __device__ __forceinline__ vecT get(const vecT *W, Idx idx, int u, int j) const {
-    if constexpr (SHARED) return __builtin_bit_cast(vecT, buf[p][u * UF + j][lane]);
-    else return W[(size_t)idx(u, j) * 64];
-  }
+// (Operations in the order of the forward kernel. EMBED: z1 as the forward forms it, from the op type's row of W1 and the fp32 columns.)
+template <typename T, int H>
+struct BwdTile {
+  using S = SplitTile<T, H>;
+  static constexpr int EBYTES = S::HS * 1024;                   // an exchange area: [HS][64] fragments; two of them hold the input
+  static constexpr int BYTES = 2 * EBYTES + S::MB * BlockStage<T>::BYTES;
 };
-
-// One unit's fragments as registers (SHARED: all LDS reads in flight together, the MFMAs behind
-// them wait for one fragment each) or, for the direct path, read where they are used.
-template <typename vecT, int UF, int UG, bool SHARED>
-struct UnitFrags {
-  vecT w[SHARED ? UF : 1];
-  template <typename Idx>
-  __device__ __forceinline__ void load(const WeightGroups<vecT, UF, UG, SHARED> &wg, const vecT *W, Idx idx, int u) {
-    if constexpr (SHARED) {
-#pragma unroll
-      for (int j = 0; j < UF; ++j) w[j] = wg.get(W, idx, u, j);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-  template <typename Idx>
-  __device__ __forceinline__ vecT operator()(const WeightGroups<vecT, UF, UG, SHARED> &wg, const vecT *W, Idx idx,
-                                             int u, int j) const {
-    if constexpr (SHARED) return w[j];
-    else return wg.get(W, idx, u, j);
-  }
-};
-
 template <typename T1, typename T, int H, int KIND>
-__global__ __launch_bounds__(256) void mlp2_bwd_kernel(const Mlp2BwdArgs a) {
+__global__ __launch_bounds__(2 * H) void mlp2_bwd_kernel(const Mlp2BwdArgs a) {
+  using S = SplitTile<T, H>;
+  using B = BwdTile<T, H>;
   using Opd = Operand<T>;
   using vec = typename Opd::vec;
-  constexpr int V = Opd::V, SL = 2 * V, MB = H / 32, HS = H / SL, QB = 32 / SL;
-  using Opd1 = Operand<T1>;
-  using vec1 = typename Opd1::vec;
-  constexpr int V1 = Opd1::V, SL1 = 2 * V1;
-  constexpr bool SHARED = sizeof(T) == 2;
-  constexpr int UF = MB * QB;                               // fragments per unit (H / 16 in bf16)
-  constexpr int SPU = UF / MB;                              // layer-1 slabs per unit
-  constexpr int UG = H >= 256 ? 4 : 2;                      // units per group (H <= 128: two blocks share a CU's LDS)
-  using WG = WeightGroups<vec, UF, UG, SHARED>;
-  using UFr = UnitFrags<vec, UF, UG, SHARED>;
-
-  const int64_t per_xcd = (a.n_blocks + 7) / 8;
-  const int64_t tile = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (tile >= a.n_blocks) return;                           // (the whole block)
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, g = lane >> 5;
-  const int64_t row0 = (tile * 4 + wave) * 32;
-  int64_t row = row0 + l32;
-  const bool valid = row < a.n_rows;
-  if (!valid) row = a.n_rows - 1;
-  // every [rows, H] result leaves through a per-wave staging buffer, one 32-feature block at a time
+  constexpr int V = Opd::V, SL = 2 * V, HS = S::HS, MB = S::MB, QB = S::QB;
+  constexpr int RING = HS < 8 ? HS : 8;                         // weight fragments in flight
+  static_assert(MB * QB == HS, "");
   extern __shared__ __align__(16) char smem[];
-  char *stage = smem + wave * BlockStage<float>::BYTES;
-  const int64_t left = a.n_rows - row0;
-  const int n_valid = left < 32 ? (left > 0 ? (int)left : 0) : 32;
-  WG wg;
-  wg.buf = reinterpret_cast<f32x4 (*)[WG::GF][64]>(smem + 4 * BlockStage<float>::BYTES);
-  wg.wave = wave; wg.lane = lane;
+  vec *ea = (vec *)smem, *eb = (vec *)(smem + B::EBYTES);
+  const int64_t n_tiles = a.n_blocks, per_xcd = (n_tiles + 7) / 8;
+  const int64_t wt = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;      // (see mlp2_split_kernel)
+  if ((int64_t)(blockIdx.x / 8) >= per_xcd || wt >= n_tiles) return;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, g = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  char *stage = smem + 2 * B::EBYTES + w * BlockStage<T>::BYTES;
+  const int64_t row0 = wt * 32;
+  const int nv = a.n_rows - row0 < 32 ? (int)(a.n_rows - row0) : 32;
+  const int64_t row = row0 + (l32 < nv ? l32 : nv - 1);         // clamp loads; stores are guarded
 
-  // ---------------- z1^T = relu(W1^T x^T + b1), exactly as in the forward kernel
-  f32x16 acc1[MB];
+  vec wq[RING];
+  // first fragments of a product: block cb of the cbs blocks of W
+  auto begin = [&](const void *W, int cb, int cbs) {
+    const vec *p = (const vec *)W + (size_t)cb * 64 + lane;
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
+    for (int c = 0; c < RING; ++c) wq[c] = p[(size_t)c * cbs * 64];
+  };
+  // acc += block cb of W times the N fragments of x (LDS); one more fragment of W is left in wq[N % RING] if EXTRA
+  auto product = [&](auto n, auto extra, const void *W, int cb, int cbs, const vec *x, f32x16 &acc) {
+    constexpr int N = decltype(n)::value, LAST = N + (decltype(extra)::value ? 1 : 0);
+    const vec *p = (const vec *)W + (size_t)cb * 64 + lane;
+    vec x0 = x[lane];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc1[mb][r] = a.b1[32 * mb + acc_row(r, g)];
-  int64_t src = 0, dst = 0;
-  {
-    // layer 1's fragments are contiguous: unit u = fragments [u * UF, u * UF + UF) = SPU slabs
-    const vec *W1 = (const vec *)a.W1s + lane;              // (vec and vec1 are both 16 bytes)
-    const int n_frag = a.nslab1 * MB, n_units = (a.nslab1 + SPU - 1) / SPU;
-    [[maybe_unused]] const T *pa = nullptr, *pb = nullptr;
-    [[maybe_unused]] EmbedRow er;
+    for (int c = 0; c < N; ++c) {
+      const vec x1 = x[(c + 1 < N ? c + 1 : 0) * 64 + lane];
+      Opd::mma(wq[c % RING], x0, acc);
+      if (c + RING < LAST) wq[c % RING] = p[(size_t)(c + RING) * cbs * 64];
+      x0 = x1;
+      __builtin_amdgcn_sched_barrier(0);                        // (see mlp2_split_kernel)
+    }
+  };
+  constexpr std::integral_constant<int, HS> one_part{};
+  constexpr std::false_type no{};
+  auto share = [&](vec *to, const f32x16 &d) {
+#pragma unroll
+    for (int q = 0; q < QB; ++q) to[(w * QB + q) * 64 + lane] = acc_slab<T>(d, q);
+  };
+
+  // ---------------- z1^T = relu(W1^T x^T + b1), exactly as in the forward kernel, and what dz2 is formed of
+  f32x16 z1, dy, y;
+  auto quads = [&](const T *p, f32x16 &v) {                     // this wave's 32 features of a row
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      float t[4];
+      load4<T>(p + 32 * w + 8 * q + 4 * g, t);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[4 * q + j] = t[j];
+    }
+  };
+  if constexpr (KIND != KIND_EMBED) {
+    const T *pa, *pb;
+    int64_t dyr = row;
     if constexpr (KIND == KIND_EDGE) {
-      src = a.in_src[row];
-      dst = a.in_dst[row];
-      pa = (const T *)a.h + (size_t)src * H + g * V;
-      pb = (const T *)a.h + (size_t)dst * H + g * V;
-    } else if constexpr (KIND == KIND_NODE) {
+      dyr = a.in_dst[row];
+      pa = (const T *)a.h + (size_t)a.in_src[row] * H + g * V;
+      pb = (const T *)a.h + (size_t)dyr * H + g * V;
+    } else {
       pa = (const T *)a.h + (size_t)row * H + g * V;
       const int64_t ar = a.agg_src ? (int64_t)a.agg_src[row] : row;
       pb = ar < 0 ? (const T *)a.zero_row + g * V : (const T *)a.agg + (size_t)ar * H + g * V;
-    } else {
-      er = load_embed_row(a.node_op, a.in_ptr, a.node_dense, a.Dd, row);
     }
-    // fragment j of unit u of the group that starts at unit u0
-    auto idx_from = [&](int u0) {
-      return [=](int u, int j) { const int f = (u0 + u) * UF + j; return f < n_frag ? f : -1; };
-    };
-    wg.begin(W1, idx_from(0));
-    int u0 = 0;
-    if constexpr (KIND != KIND_EMBED) {
-      // the 2 HS slabs of the two H-wide input parts: gathered rows, requested XQ slabs ahead
-      constexpr int NSH = 2 * HS, XQ = 8 < NSH ? 8 : NSH, NSU = NSH / SPU;
-      static_assert(NSU % UG == 0, "the H-wide parts fill whole groups");
-      auto load_slab = [&](int s) -> vec {
-        if (s < HS) return *(const vec *)(pa + s * SL);
-        return *(const vec *)(pb + (s - HS) * SL);   // (the forward zeroed the received sums of nodes without in-edges)
-      };
-      vec xq[XQ];
+    begin(a.W1s, w, MB);
+    constexpr int MINE = 2 * HS / MB;                           // consecutive slabs of the row this wave fetches
+    static_assert(MINE * MB == 2 * HS && HS % MINE == 0, "");
+    const int s0 = w * MINE;
+    const T *px = s0 < HS ? pa + s0 * SL : pb + (s0 - HS) * SL;
+    vec x[MINE];
 #pragma unroll
-      for (int s = 0; s < XQ; ++s) xq[s] = load_slab(s);
+    for (int i = 0; i < MINE; ++i) x[i] = *(const vec *)(px + i * SL);
+    [[maybe_unused]] TailRaw<V> xt;
+    if constexpr (KIND == KIND_EDGE) xt = load_tail<V>(a.edge_feat + (size_t)row * a.De, a.De, 0, g);
 #pragma unroll
-      for (int g0 = 0; g0 < NSU; g0 += UG) {
-        const auto idx = idx_from(g0);
-        if (g0 + UG < n_units) wg.fetch(W1, idx_from(g0 + UG));
+    for (int r = 0; r < 16; ++r) {
+      z1[r] = a.b1[32 * w + acc_row(r, g)];
+      if constexpr (KIND == KIND_EDGE) y[r] = a.b2[32 * w + acc_row(r, g)];
+    }
+    quads((const T *)a.dy + (size_t)dyr * H, dy);
+    if constexpr (KIND != KIND_EDGE) quads((const T *)a.y + (size_t)row * H, y);
 #pragma unroll
-        for (int u = 0; u < UG; ++u) {
-          UFr w;
-          w.load(wg, W1, idx, u);
-#pragma unroll
-          for (int j2 = 0; j2 < SPU; ++j2) {
-            const int sl = (g0 + u) * SPU + j2;
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) Opd::mma(w(wg, W1, idx, u, j2 * MB + mb), xq[sl % XQ], acc1[mb]);
-            if (sl + XQ < NSH) xq[sl % XQ] = load_slab(sl + XQ);
-          }
-        }
-        wg.next(g0 + UG < n_units);
+    for (int i = 0; i < MINE; ++i) ea[(s0 + i) * 64 + lane] = x[i];
+    __syncthreads();
+    product(std::integral_constant<int, 2 * HS>(), std::bool_constant<KIND == KIND_EDGE>(), a.W1s, w, MB, ea, z1);
+    if constexpr (KIND == KIND_EDGE) {
+      const vec *W1 = (const vec *)a.W1s + (size_t)w * 64 + lane;
+      for (int s = 2 * HS; s < a.nslab1; ++s) {                 // edge attributes
+        const vec xv = tail_to_operand<T>(s == 2 * HS ? xt : load_tail<V>(a.edge_feat + (size_t)row * a.De, a.De, s - 2 * HS, g));
+        const vec wv = s == 2 * HS ? wq[(2 * HS) % RING] : W1[(size_t)s * MB * 64];
+        Opd::mma(wv, xv, z1);
       }
-      u0 = NSU;
     }
-    // the remaining slabs (EDGE: edge attributes; EMBED: all of them)
-    for (; u0 < n_units; u0 += UG) {
-      const auto idx = idx_from(u0);
-      if (u0 + UG < n_units) wg.fetch(W1, idx_from(u0 + UG));
+  } else {
+    const EmbedRow er = load_embed_row(a.node_op, a.in_ptr, a.node_dense, a.Dd, row);
+    const float *trow = a.table + (size_t)er.op * H + 32 * w + 4 * g;
+    quads((const T *)a.dy + (size_t)row * H, dy);
+    quads((const T *)a.y + (size_t)row * H, y);
 #pragma unroll
-      for (int u = 0; u < UG; ++u)
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 t = *(const f32x4 *)(trow + 8 * q);
+      const f32x4 b = *(const f32x4 *)(a.b1 + 32 * w + 8 * q + 4 * g);
 #pragma unroll
-        for (int j2 = 0; j2 < SPU; ++j2) {
-          const int sl = (u0 + u) * SPU + j2;
-          if (sl < a.nslab1) {
-            if constexpr (KIND == KIND_EMBED) {
-              vec1 x;
-#pragma unroll
-              for (int j = 0; j < V1; ++j) {
-                const int k = sl * SL1 + g * V1 + j;        // column of [edge-attr sum | one-hot | dense]
-                float v = 0.f;
-                if (k >= a.De && k < a.De + a.Tn) v = (k - a.De == er.op) ? 1.f : 0.f;
-                else if (k >= a.De + a.Tn && k < a.De + a.Tn + a.Dd) v = er.dense[k - a.De - a.Tn];
-                x[j] = Opd1::from_float(v);
-              }
-              if (sl * SL1 + g * V1 < a.De) {               // (De and V1 are multiples of 4)
-                const f32x4 e4 = embed_columns(er, a.edge_feat, a.De, 0, sl * SL1 + g * V1);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) x[j] = Opd1::from_float(e4[j]);
-              }
-#pragma unroll
-              for (int mb = 0; mb < MB; ++mb)
-                Opd1::mma(__builtin_bit_cast(vec1, wg.get(W1, idx, u, j2 * MB + mb)), x, acc1[mb]);
-            } else {
-              const vec x = tail_to_operand<T>(load_tail<V>(a.edge_feat + (size_t)row * a.De, a.De, sl - 2 * HS, g));
-#pragma unroll
-              for (int mb = 0; mb < MB; ++mb) Opd::mma(wg.get(W1, idx, u, j2 * MB + mb), x, acc1[mb]);
-            }
-          }
-        }
-      wg.next(u0 + UG < n_units);
+      for (int j = 0; j < 4; ++j) z1[4 * q + j] = t[j] + b[j];
+    }
+    const f32x4 *W1 = (const f32x4 *)a.W1x + (size_t)w * 64 + lane;
+    for (int s = 0; s < a.nslabx; ++s) {
+      const f32x4 xv = embed_columns(er, a.edge_feat, a.De, a.Dd, s * 8 + g * 4);
+      Operand<float>::mma(W1[(size_t)s * MB * 64], xv, z1);
     }
   }
+  begin(KIND == KIND_EDGE ? a.W2s : a.W2bt, w, MB);
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc1[mb][r] = relu_f32(acc1[mb][r]);
-    store_block_via_lds<T, H>((T *)a.z1, row0, n_valid, mb, lane, acc1[mb], stage);
-  }
+  for (int r = 0; r < 16; ++r) z1[r] = relu_f32(z1[r]);
+  __syncthreads();                                              // (every wave has read the input)
 
-  // ---------------- dz2^T = dy^T * [y^T > 0], stored and kept as operand slabs
-  vec dz2s[MB][QB];
-  {
-    using DY = T;
-    const DY *dyrow = (const DY *)a.dy + (size_t)(KIND == KIND_EDGE ? dst : row) * H;
-    [[maybe_unused]] const vec *W2 = (const vec *)a.W2s + lane;
-    [[maybe_unused]] const T *yrow = KIND == KIND_EDGE ? nullptr : (const T *)a.y + (size_t)row * H + 4 * g;
-    // dy (and, where the forward stored it, y) of block nb + 1 is requested while block nb is
-    // worked on: the fences of the staged stores keep the compiler from doing that itself
-    auto load_dy = [&](int nb, f32x16 &d, f32x16 &yv) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float v[4];
-        load4<DY>(dyrow + 32 * nb + 8 * q + 4 * g, v);
-        d[4 * q] = v[0]; d[4 * q + 1] = v[1]; d[4 * q + 2] = v[2]; d[4 * q + 3] = v[3];
-        if constexpr (KIND != KIND_EDGE) {
-          load4<T>(yrow + 32 * nb + 8 * q, v);
-          yv[4 * q] = v[0]; yv[4 * q + 1] = v[1]; yv[4 * q + 2] = v[2]; yv[4 * q + 3] = v[3];
-        }
-      }
-    };
-    f32x16 dyc, yc, dyn, yn;
-    load_dy(0, dyc, yc);
-    // EDGE: y^T block nb needs W2's fragments ((mb, q), nb) for all (mb, q): unit nb
-    auto idx_from = [&](int u0) { return [=](int u, int j) { return j * MB + u0 + u; }; };
-    if constexpr (KIND == KIND_EDGE) wg.begin(W2, idx_from(0));
-#pragma unroll
-    for (int nb = 0; nb < MB; ++nb) {
-      if (nb + 1 < MB) load_dy(nb + 1, dyn, yn);
-      if constexpr (KIND == KIND_EDGE) {
-        const int g0 = nb / UG * UG, u = nb % UG;
-        const auto idx = idx_from(g0);
-        if (u == 0 && g0 + UG < MB) wg.fetch(W2, idx_from(g0 + UG));
-        UFr w;
-        w.load(wg, W2, idx, u);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) yc[r] = a.b2[32 * nb + acc_row(r, g)];
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-          for (int q = 0; q < QB; ++q) Opd::mma(w(wg, W2, idx, u, mb * QB + q), acc_slab<T>(acc1[mb], q), yc);
-        if (u == UG - 1) wg.next(g0 + UG < MB);
-      }
-      f32x16 d;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) d[r] = yc[r] > 0.f ? dyc[r] : 0.f;
-      store_block_via_lds<T, H>((T *)a.dz2, row0, n_valid, nb, lane, d, stage);
-#pragma unroll
-      for (int q = 0; q < QB; ++q) dz2s[nb][q] = acc_slab<T>(d, q);
-      if (nb + 1 < MB) { dyc = dyn; yc = yn; }
-    }
+  // ---------------- dz2^T = dy^T * [y^T > 0]
+  if constexpr (KIND == KIND_EDGE) {
+    share(ea, z1);
+    store_block_via_lds<T, H>((T *)a.z1, row0, nv, w, lane, z1, stage);
+    __syncthreads();
+    product(one_part, no, a.W2s, w, MB, ea, y);
+    begin(a.W2bt, w, MB);
   }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) dy[r] = y[r] > 0.f ? dy[r] : 0.f;
+  share(eb, dy);
+  if constexpr (KIND != KIND_EDGE) store_block_via_lds<T, H>((T *)a.z1, row0, nv, w, lane, z1, stage);
+  store_block_via_lds<T, H>((T *)a.dz2, row0, nv, w, lane, dy, stage);
+  __syncthreads();
 
-  // ---------------- dz1^T = (W2 dz2^T) * [z1^T > 0]: unit mb = the W2^T fragments of block mb
-  vec dz1s[MB][QB];
-  {
-    const vec *W2b = (const vec *)a.W2bt + lane;
-    auto idx_from = [&](int u0) { return [=](int u, int j) { return j * MB + u0 + u; }; };
-    wg.begin(W2b, idx_from(0));
+  // ---------------- dz1^T = (W2 dz2^T) * [z1^T > 0]
+  f32x16 d;
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      const int g0 = mb / UG * UG, u = mb % UG;
-      const auto idx = idx_from(g0);
-      if (u == 0 && g0 + UG < MB) wg.fetch(W2b, idx_from(g0 + UG));
-      UFr w;
-      w.load(wg, W2b, idx, u);
-      f32x16 d;
+  for (int r = 0; r < 16; ++r) d[r] = 0.f;
+  product(one_part, no, a.W2bt, w, MB, eb, d);
+  if constexpr (KIND != KIND_EMBED) begin(a.W1bt, w, 2 * MB);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) d[r] = 0.f;
-#pragma unroll
-      for (int nb = 0; nb < MB; ++nb)
-#pragma unroll
-        for (int q = 0; q < QB; ++q) Opd::mma(w(wg, W2b, idx, u, nb * QB + q), dz2s[nb][q], d);
-      if (u == UG - 1) wg.next(g0 + UG < MB);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) d[r] = acc1[mb][r] > 0.f ? d[r] : 0.f;
-      store_block_via_lds<T, H>((T *)a.dz1, row0, n_valid, mb, lane, d, stage);
-#pragma unroll
-      for (int q = 0; q < QB; ++q) dz1s[mb][q] = acc_slab<T>(d, q);
-    }
-  }
+  for (int r = 0; r < 16; ++r) d[r] = z1[r] > 0.f ? d[r] : 0.f;
+  if constexpr (KIND != KIND_EMBED) share(ea, d);
+  store_block_via_lds<T, H>((T *)a.dz1, row0, nv, w, lane, d, stage);
 
-  // ---------------- dx^T = W1 dz1^T over the first 2H input columns (h parts only): unit kb =
-  // the W1^T fragments of the 32-column block kb of [part a | part b]
+  // ---------------- dx^T = W1 dz1^T over the first 2H input columns (h parts only)
   if constexpr (KIND != KIND_EMBED) {
-    const vec *W1b = (const vec *)a.W1bt + lane;
-    constexpr int KB = 2 * MB;
-    auto idx_from = [&](int u0) { return [=](int u, int j) { return j * KB + u0 + u; }; };
-    wg.begin(W1b, idx_from(0));
+    __syncthreads();
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
-      const int g0 = kb / UG * UG, u = kb % UG;
-      const auto idx = idx_from(g0);
-      if (u == 0 && g0 + UG < KB) wg.fetch(W1b, idx_from(g0 + UG));
-      UFr w;
-      w.load(wg, W1b, idx, u);
-      f32x16 d;
+    for (int part = 0; part < 2; ++part) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) d[r] = 0.f;
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int q = 0; q < QB; ++q) Opd::mma(w(wg, W1b, idx, u, mb * QB + q), dz1s[mb][q], d);
-      if (u == UG - 1) wg.next(g0 + UG < KB);
-      if constexpr (KIND == KIND_EDGE) {
-        T *o = (T *)(kb < MB ? a.dx_a : a.dx_b);
-        store_block_via_lds<T, H>(o, row0, n_valid, kb % MB, lane, d, stage);
-      } else {
-        store_block_via_lds<T, H>((T *)(kb < MB ? a.dx_a : a.dx_b), row0, n_valid, kb % MB, lane, d, stage);
-      }
+      product(one_part, no, a.W1bt, part * MB + w, 2 * MB, ea, d);
+      if (part == 0) begin(a.W1bt, MB + w, 2 * MB);
+      store_block_via_lds<T, H>((T *)(part == 0 ? a.dx_a : a.dx_b), row0, nv, w, lane, d, stage);
     }
   }
-}
-
-// dynamic LDS of mlp2_bwd_kernel: four staging buffers, then (bf16) two groups of fragments
-template <typename T, int H>
-constexpr size_t mlp2_bwd_lds_bytes() {
-  constexpr int MB = H / 32, QB = 32 / (2 * Operand<T>::V), UG = H >= 256 ? 4 : 2;
-  return 4 * (size_t)BlockStage<float>::BYTES + (sizeof(T) == 2 ? 2 * (size_t)(MB * QB * UG) * 1024 : 0);
 }

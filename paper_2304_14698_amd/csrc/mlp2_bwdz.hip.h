@@ -8,9 +8,9 @@
 // dz2 and dz1 are stored for the weight-gradient kernel, which reads relu(z1) from the forward's
 // copy. Everything is kept transposed
 // (features x rows: lane = row, registers = features), each result already laid out as the next
-// contraction's B operand, as in mlp2_bwd_kernel; the three live tiles of that kernel (z1, dz2,
-// dz1) shrink to two, which lets eight waves share a compute unit at H = 256. The weights go
-// through the same double-buffered LDS groups, fetched once per block of NW waves. A wave's tile
+// contraction's B operand; of the three tiles a recomputing pass holds (z1, dz2, dz1) two are live,
+// which lets eight waves share a compute unit at H = 256. The weights go
+// through double-buffered LDS groups, fetched once per block of NW waves. A wave's tile
 // is the forward kernel's wave tile, because the mask bits are per tile and lane of that kernel: 32
 // consecutive nodes, or for EDGE an edge tile of the packer (at most 32 edges). Those tiles are cut at receiver
 // boundaries, so with FOLD (batches in which no receiver has more than 32 in-edges) the gradients

@@ -1300,15 +1300,14 @@ __global__ void export_rows_kernel(const T *src, int64_t n_rows, int D, const in
 
 template <typename T1, typename T, int H, int KIND>
 int launch_mlp2_bwd_k(xrl_ctx *c, const Mlp2BwdArgs &a) {
-  constexpr size_t lds = mlp2_bwd_lds_bytes<T, H>();
+  constexpr int lds = BwdTile<T, H>::BYTES;
   auto kern = mlp2_bwd_kernel<T1, T, H, KIND>;
   static bool attr_set = false;          // one attribute per kernel instantiation
   if (!attr_set) {
-    HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     attr_set = true;
   }
-  const unsigned grid = (unsigned)(((a.n_blocks + 7) / 8) * 8);
-  kern<<<dim3(grid), dim3(256), lds, c->stream>>>(a);
+  kern<<<dim3((unsigned)((a.n_blocks + 7) / 8 * 8)), dim3(2 * H), lds, c->stream>>>(a);
   HIP_TRY(hipGetLastError());
   return XRL_OK;
 }
@@ -1323,7 +1322,7 @@ int launch_mlp2_bwd_h(xrl_ctx *c, int kind, const Mlp2BwdArgs &a) {
 
 template <typename T>
 int launch_mlp2_bwd(xrl_ctx *c, int kind, Mlp2BwdArgs &a) {
-  a.n_blocks = (a.n_rows + 127) / 128;
+  a.n_blocks = (a.n_rows + 31) / 32;
   switch (c->m.hidden) {
     case 64: return launch_mlp2_bwd_h<T, 64>(c, kind, a);
     case 128: return launch_mlp2_bwd_h<T, 128>(c, kind, a);
@@ -2188,6 +2187,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   a.zero_row = c->zero_row;
   auto set_w = [&](const EncMlp &e) {
     a.W1s = e.W1s; a.W2s = e.W2s; a.W2bt = e.W2bt; a.W1bt = e.W1bt; a.b1 = e.b1; a.b2 = e.b2; a.nslab1 = e.nslab1;
+    a.W1x = e.W1x; a.nslabx = e.nslabx; a.table = e.table;
   };
   // both layers' weight gradients of an MLP whose gradients have been computed; x: the first layer's input
   auto wgrads = [&](WgradJob x, const MlpRef &r, const MlpGrads &mg, const void *z1) -> int {
