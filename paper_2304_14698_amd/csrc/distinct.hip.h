@@ -428,9 +428,12 @@ __global__ __launch_bounds__(256) void expand_states_kernel(const f32x4 *in, con
 // Sums of rows per class in fp32 and, rounded once, their store in the operand type; with ymask (bf16) multiplied
 // by the ReLU mask of the layer that produced the classes' states (see node_grad_gather_kernel). The
 // rows are listed class by class (perm, -1 = a row of zeros; seg the class of each place; every class has
-// one), and H / VEC lanes take sixteen places: all indices, then all rows and the mask words of the classes
-// that end here, are requested at once, so a group waits twice whatever classes it holds. A class
-// that lies inside is stored at once; the pieces of others go to carry[places / 16][begun before, goes on].
+// one), and H / VEC lanes take STEPS times sixteen places: a step's indices, then all its rows and the mask words of the classes
+// that end there, are requested at once, so a step waits twice whatever classes it holds. A class
+// that lies inside the group is stored at once; the pieces of others go to carry[group][begun before, goes on], 8 H bytes a
+// group and back again. One step leaves most lanes to hide the gathers with, four the fewest pieces. us of this kernel and the next at 1 / 2 / 4 steps, H = 256:
+// 4.36 M rows of the pool's table 493 / 456 / 409, 3.5 M rows 535 / 492 / 458, 582 k rows 125 / 111 / 110, 162 k rows 36 / 32 / 35; H = 128: 368 k rows
+// 42.8 / 38.8 / 45.1, 251 k 30.8 / 27.2 / 31.0, 143 k 22.5 / 22.8 / 28.7.
 // Bound by the gather of the rows. H = 256, 3.4 M rows of 512 bytes into 400 k classes: 423 us (4.6 TB/s) and 99 for
 // the classes in several pieces; a walk that read a segment's end when it reached it, an fp32 array of
 // the sums and a pass that masked it took 815 + 90 + 108. The pool's gradient, 4.3 M rows of a 4.7 MB table:
@@ -443,7 +446,8 @@ struct ClassSumArgs {
   int D;
   const uint16_t *ymask;
   void *out;                         // [classes, D]
-  float *carry;                      // [n_rows / 16, rounded up][2][D]
+  float *carry;                      // [n_rows / group, rounded up][2][D]
+  int group;                         // places a group of lanes takes
 };
 // the mask bits of columns c .. c + 3 of row n (c a multiple of 4), lowest first
 __device__ __forceinline__ unsigned mask_word(const uint16_t *ymask, int64_t n, int D, int c) {
@@ -456,76 +460,86 @@ __device__ __forceinline__ void store_masked4(TOut *p, float *v, bool masked, un
   for (int j = 0; j < 4; ++j) v[j] = (bits >> j) & 1u ? v[j] : 0.f;
   store4<TOut>(p, v);
 }
-template <typename TIn, typename TOut, int VEC>
+template <typename TIn, typename TOut, int VEC, int STEPS>
 __global__ __launch_bounds__(256) void class_sum_kernel(const ClassSumArgs a) {
   constexpr int NR = kSumRows, NQ = VEC / 4;
   typedef int i32x4 __attribute__((ext_vector_type(4)));
   const int lpr = a.D / VEC;
   const int64_t gt = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t st = gt / lpr, r0 = st * NR;
+  constexpr int GROUP = STEPS * NR;
+  const int64_t st = gt / lpr, r_end = (st + 1) * GROUP < a.n_rows ? (st + 1) * GROUP : a.n_rows;
+  int64_t r0 = st * GROUP;
   if (r0 >= a.n_rows) return;
   const int c = (int)(gt - st * lpr) * VEC;
-  const int nv = a.n_rows - r0 < NR ? (int)(a.n_rows - r0) : NR;
-  i32x4 row4[NR / 4], seg4[NR / 4];
-#pragma unroll
-  for (int i = 0; i < NR / 4; ++i) {
-    row4[i] = ((const i32x4 *)(a.perm + r0))[i];
-    seg4[i] = ((const i32x4 *)(a.seg + r0))[i];
-  }
-  const int before = r0 > 0 ? a.seg[r0 - 1] : -1, after = r0 + NR < a.n_rows ? a.seg[r0 + NR] : -1;
-  float v[NR][VEC];
-  int seg[NR];
-#pragma unroll
-  for (int i = 0; i < NR; ++i) {
-    const int r = i < nv ? row4[i / 4][i % 4] : -1;        // (places past the last: zeros of the last one's class)
-    seg[i] = i < nv ? seg4[i / 4][i % 4] : seg[i - 1 > 0 ? i - 1 : 0];
-    RowVec<TIn, VEC>::load((r < 0 ? (const TIn *)a.zero_row : (const TIn *)a.vals + (size_t)r * a.D) + c, v[i]);
-  }
-  unsigned word[NR][NQ];
   const bool masked = a.ymask != nullptr;
-#pragma unroll
-  for (int i = 0; i < NR; ++i)
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) word[i][q] = 0;
-  if (masked) {
-#pragma unroll
-    for (int i = 0; i < NR; ++i)
-      if (i == NR - 1 || seg[i + 1 < NR ? i + 1 : i] != seg[i]) {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) word[i][q] = mask_word(a.ymask, seg[i], a.D, c + 4 * q);
-      }
-  }
+  const int before = r0 > 0 ? a.seg[r0 - 1] : -1;
+  bool begun = false;
   float acc[VEC];
 #pragma unroll
   for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
-  bool begun = seg[0] == before;
+  for (;;) {
+    const int nv = r_end - r0 < NR ? (int)(r_end - r0) : NR;
+    const bool last = STEPS == 1 || r0 + NR >= r_end;
+    i32x4 row4[NR / 4], seg4[NR / 4];
 #pragma unroll
-  for (int i = 0; i < NR; ++i) {
-#pragma unroll
-    for (int j = 0; j < VEC; ++j) acc[j] += v[i][j];
-    if (i == NR - 1 || seg[i + 1 < NR ? i + 1 : i] != seg[i]) {
-      if (begun || (i == NR - 1 && after == seg[i])) {
-        float *p = a.carry + ((size_t)st * 2 + (begun ? 0 : 1)) * a.D + c;
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) store4<float>(p + 4 * q, acc + 4 * q);
-      } else {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) store_masked4<TOut>((TOut *)a.out + (size_t)seg[i] * a.D + c + 4 * q, acc + 4 * q, masked, word[i][q], c + 4 * q);
-      }
-      begun = false;
-#pragma unroll
-      for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
+    for (int i = 0; i < NR / 4; ++i) {
+      row4[i] = ((const i32x4 *)(a.perm + r0))[i];
+      seg4[i] = ((const i32x4 *)(a.seg + r0))[i];
     }
+    const int after = r0 + NR < a.n_rows ? a.seg[r0 + NR] : -1;
+    float v[NR][VEC];
+    int seg[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const int r = i < nv ? row4[i / 4][i % 4] : -1;      // (places past the last: zeros of the last one's class)
+      seg[i] = i < nv ? seg4[i / 4][i % 4] : seg[i - 1 > 0 ? i - 1 : 0];
+      RowVec<TIn, VEC>::load((r < 0 ? (const TIn *)a.zero_row : (const TIn *)a.vals + (size_t)r * a.D) + c, v[i]);
+    }
+    unsigned word[NR][NQ];
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) word[i][q] = 0;
+    if (masked) {
+#pragma unroll
+      for (int i = 0; i < NR; ++i)
+        if (i == NR - 1 || seg[i + 1 < NR ? i + 1 : i] != seg[i]) {
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) word[i][q] = mask_word(a.ymask, seg[i], a.D, c + 4 * q);
+        }
+    }
+    if (r0 == st * GROUP) begun = seg[0] == before;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+#pragma unroll
+      for (int j = 0; j < VEC; ++j) acc[j] += v[i][j];
+      const bool ends = (i == NR - 1 ? after : seg[i + 1 < NR ? i + 1 : i]) != seg[i];
+      if (ends || (i == NR - 1 && last)) {
+        if (begun || !ends) {
+          float *p = a.carry + ((size_t)st * 2 + (begun ? 0 : 1)) * a.D + c;
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) store4<float>(p + 4 * q, acc + 4 * q);
+        } else {
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) store_masked4<TOut>((TOut *)a.out + (size_t)seg[i] * a.D + c + 4 * q, acc + 4 * q, masked, word[i][q], c + 4 * q);
+        }
+        begun = false;
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
+      }
+    }
+    if (last) break;
+    r0 += NR;
   }
 }
-// The classes in several pieces. A wave looks at kCarryGroups groups of sixteen places, one per lane, and for those
+// The classes in several pieces. A wave looks at kCarryGroups groups of places, one per lane, and for those
 // whose last class begins there and goes on adds up its pieces, one class after the other (of 64 groups: 70 us
 // however small the level): D / 4 lanes a piece, the wave's
 // 256 / D lane groups every 256 / D-th of them, eight in flight each, added in group order.
 constexpr int kCarryGroups = 4;
 template <typename TOut>
 __global__ __launch_bounds__(256) void class_sum_carried_kernel(const ClassSumArgs a) {
-  constexpr int NR = kSumRows;
+  const int NR = a.group;
   const int lane = threadIdx.x & 63;
   const int64_t st0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kCarryGroups, mine = st0 + lane;
   int seg = -1;

@@ -160,6 +160,7 @@ struct xrl_ctx {
   int64_t p_min_rows = 8192;    // smallest row count for the persistent kernels (XRL_PERSISTENT_MIN_ROWS) when saving
   int64_t p_min_rows_forward = 8192;   // for the backward pass, and when not
   int64_t wide_min_rows = 1 << 18;   // rows of a launch's products from which 256-column weight-gradient tiles are used (XRL_WGRAD_WIDE_MIN_ROWS)
+  int sum_steps = 0;                 // steps of a group of class_sum_kernel, 0: by the rows (XRL_SUM_STEPS)
   size_t grad_room = kGradRoom;      // XRL_GRAD_ROOM
   int64_t round_blocks = 0;          // blocks per compute unit up to which a round is one launch, see mlp2_round_kernel (XRL_ROUND_BLOCKS)
   bool round_any = false;            // ... whatever their in-edges (if it is set)
@@ -2144,9 +2145,19 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
     ClassSumArgs s;
     s.vals = vals; s.zero_row = c->zero_row; s.perm = perm; s.seg = seg; s.ptr = ptr; s.n_rows = rows; s.D = H;
     s.ymask = ymask; s.out = out; s.carry = ccarry;
-    const int64_t groups = (rows + kSumRows - 1) / kSumRows;
-    class_sum_kernel<TIn, T, VEC><<<dim3((unsigned)((groups * (H / VEC) + 255) / 256)), dim3(256), 0, c->stream>>>(s);
-    class_sum_carried_kernel<T><<<dim3((unsigned)((groups + 4 * kCarryGroups - 1) / (4 * kCarryGroups))), dim3(256), 0, c->stream>>>(s);
+    const int64_t blocks = ((rows + kSumRows - 1) / kSumRows * (H / VEC) + 255) / 256;   // of one step a group
+    auto go = [&](auto steps) {
+      constexpr int STEPS = decltype(steps)::value;
+      s.group = STEPS * kSumRows;
+      const int64_t groups = (rows + s.group - 1) / s.group;
+      class_sum_kernel<TIn, T, VEC, STEPS><<<dim3((unsigned)((groups * (H / VEC) + 255) / 256)), dim3(256), 0, c->stream>>>(s);
+      class_sum_carried_kernel<T><<<dim3((unsigned)((groups + 4 * kCarryGroups - 1) / (4 * kCarryGroups))), dim3(256), 0, c->stream>>>(s);
+    };
+    // (the classes in several pieces, and their way to memory and back, against lanes to hide the gathers with: see class_sum_kernel)
+    const int steps = c->sum_steps > 0 ? c->sum_steps : blocks >= 16 * c->n_cu ? 4 : blocks >= 3 * c->n_cu ? 2 : 1;
+    if (steps >= 4) go(std::integral_constant<int, 4>());
+    else if (steps >= 2) go(std::integral_constant<int, 2>());
+    else go(std::integral_constant<int, 1>());
     HIP_TRY(hipGetLastError());
     return XRL_OK;
   };
@@ -2707,6 +2718,7 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   if (const char *e = getenv("XRL_WGRAD_WIDE_MIN_ROWS")) c->wide_min_rows = atoll(e);
   c->round_blocks = model->hidden == 64 ? 4 : 2;
   if (const char *e = getenv("XRL_ROUND_BLOCKS")) { c->round_blocks = atoll(e); c->round_any = true; }
+  if (const char *e = getenv("XRL_SUM_STEPS")) c->sum_steps = atoi(e);
   if (const char *e = getenv("XRL_GRAD_ROOM")) c->grad_room = (size_t)std::max<long long>(0, atoll(e));
   // Largest batches of the one-launch encoders (0 graphs = never). A forward-only encode takes them up to a
   // limit that the variable of that form states, and by default never: since a tile of the
