@@ -2,7 +2,8 @@
 // graph, so most of their nodes have, for the first rounds, exactly the history of a node of another
 // graph: the same operator, attributes and incoming edge attributes (level 0), and at level l + 1 the
 // same level-l class and, edge by edge in the batch's receiver order, senders of the same level-l
-// classes. Nodes of one class at level l have the same state after l rounds, bit for bit, so a round
+// classes; the first two in-edges of a node count in either order, since every sum over a node's
+// in-edges adds these two to each other before anything else. Nodes of one class at level l have the same state after l rounds, bit for bit, so a round
 // is computed once per class, on the graph of one representative per class (its smallest node) and
 // the representatives' in-edges.
 //
@@ -14,9 +15,9 @@
 // would let two keys of one tag meet or miss each other by the order of insertion.) Class numbers
 // ascend with their representatives.
 //
-// What it saves, a kept minibatch's update step: 4.3 M nodes, H = 256: 88.0 -> 14.4 ms (20 % of the edges are
-// left over five rounds); 354 k nodes, H = 128: 4.3 -> 1.85 ms (40 %); 73 k nodes re-evaluated in fp32:
-// 1.19 -> 0.66 ms. The attention rounds keep to the whole batch: their backward gathers per sender, and a
+// What it saves, a kept minibatch's update step, whole / reduced / with the first two in-edges in either order: 4.3 M nodes,
+// H = 256: 88.0 / 11.0 / 3.42 ms (13, then 2.5 % of the edges left over five rounds); 354 k nodes, H = 128: 4.3 / 1.11 / 0.82 ms (24, 10 %);
+// 73 k nodes re-evaluated in fp32: 1.19 / 0.35 / 0.23 ms (36, 6 %). The attention rounds keep to the whole batch: their backward gathers per sender, and a
 // sender shared by thousands of graphs made that pass 8 times slower than what the rest gained.
 //
 // Bound by gathers of 4-byte class numbers and by table probes: one pass of each over the nodes and
@@ -36,6 +37,7 @@ struct ClassArgs {
   const int32_t *in_ptr, *in_src, *node_op;
   const uint32_t *edge_feat, *node_dense;  // bit patterns
   int De, Dd;
+  const uint8_t *swapped;                  // [N] 1: the first two in-edges change places (see first_two_kernel)
   const int32_t *prev;                     // class of each node one level below; nullptr: level 0
   unsigned long long *table;               // [mask + 1] tag << kNodeBits | smallest node, kEmptySlot
   uint32_t mask;
@@ -60,16 +62,49 @@ __global__ __launch_bounds__(256) void class_clear_kernel(unsigned long long *ta
   if (i < n) table[i] = kEmptySlot;
 }
 
+// The graphs of a state list their edges in different orders, so the first two in-edges of a node and of its
+// copies in other graphs often come swapped, and what is downstream of them would be distinct (the sums are the
+// same bits: x + y = y + x). Where a node's two come is therefore decided by the attributes' bit patterns, then the senders'
+// operators, attributes and in-degrees: pairs alike in all of these stay as given, which may cost a class,
+// never a wrong one. (The third and further in-edges keep their places: another order would be other sums.)
+// Edges left, rounds 1-5: 4.3 M nodes of 16 transformer states 1.7, 2.9, 6, 18, 37 % -> 1.3, 1.9, 2.4, 3.0, 3.8; one such
+// state 7, 17, 36, 53, 70 % -> 3, 5, 6, 7, 8; 16 residual networks' states 7, 11, 20, 34, 49 % -> 5, 7, 10, 13, 17.
+__global__ __launch_bounds__(256) void first_two_kernel(const ClassArgs a, uint8_t *swapped) {
+  const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (n >= a.N) return;
+  const int e0 = a.in_ptr[n];
+  int order = 0;                           // 1: the second comes first, -1: as given
+  if (a.in_ptr[n + 1] - e0 >= 2) {
+    auto differ = [&](uint32_t x, uint32_t y) {
+      if (order == 0 && x != y) order = y < x ? 1 : -1;
+    };
+    const size_t f = (size_t)e0 * a.De;
+    for (int w = 0; w < a.De && order == 0; ++w) differ(a.edge_feat[f + w], a.edge_feat[f + a.De + w]);
+    if (order == 0) {
+      const int32_t s = a.in_src[e0], t = a.in_src[e0 + 1];
+      differ((uint32_t)a.node_op[s], (uint32_t)a.node_op[t]);
+      for (int k = 0; k < a.Dd && order == 0; ++k) differ(a.node_dense[(size_t)s * a.Dd + k], a.node_dense[(size_t)t * a.Dd + k]);
+      differ((uint32_t)(a.in_ptr[s + 1] - a.in_ptr[s]), (uint32_t)(a.in_ptr[t + 1] - a.in_ptr[t]));
+    }
+  }
+  swapped[n] = order > 0;
+}
+// the k-th in-edge of a node whose first is e0
+__device__ __forceinline__ int in_edge(int e0, int k, int swapped) { return e0 + (k < 2 ? k ^ swapped : k); }
+
 __device__ __forceinline__ void class_insert(const ClassArgs &a, int64_t n) {
-  const int e0 = a.in_ptr[n], e1 = a.in_ptr[n + 1];
+  const int e0 = a.in_ptr[n], d = a.in_ptr[n + 1] - e0, sw = a.swapped[n];
   uint64_t h;
   if (a.prev) {
     h = mix64(0x51ED270B27B4F3CFull, (uint32_t)a.prev[n]);
-    for (int e = e0; e < e1; ++e) h = mix64(h, (uint32_t)a.prev[a.in_src[e]]);
+    for (int k = 0; k < d; ++k) h = mix64(h, (uint32_t)a.prev[a.in_src[in_edge(e0, k, sw)]]);
   } else {
-    h = mix64((uint32_t)a.node_op[n], (uint32_t)(e1 - e0));
+    h = mix64((uint32_t)a.node_op[n], (uint32_t)d);
     for (int k = 0; k < a.Dd; ++k) h = mix64(h, a.node_dense[(size_t)n * a.Dd + k]);
-    for (size_t w = (size_t)e0 * a.De; w < (size_t)e1 * a.De; ++w) h = mix64(h, a.edge_feat[w]);
+    for (int k = 0; k < d; ++k) {
+      const uint32_t *f = a.edge_feat + (size_t)in_edge(e0, k, sw) * a.De;
+      for (int w = 0; w < a.De; ++w) h = mix64(h, f[w]);
+    }
   }
   h = mix64(h, h >> 32);
   const unsigned long long tag = h >> kNodeBits, mine = tag << kNodeBits | (uint32_t)n;
@@ -103,14 +138,18 @@ __global__ __launch_bounds__(256) void class_insert_kernel(const ClassArgs a) {
 __device__ __forceinline__ bool same_key(const ClassArgs &a, int64_t n, int64_t r) {
   const int e0 = a.in_ptr[n], d = a.in_ptr[n + 1] - e0, f0 = a.in_ptr[r];
   if (a.in_ptr[r + 1] - f0 != d) return false;
+  const int sn = a.swapped[n], sr = a.swapped[r];
   if (a.prev) {
     bool same = a.prev[n] == a.prev[r];
-    for (int k = 0; k < d; ++k) same &= a.prev[a.in_src[e0 + k]] == a.prev[a.in_src[f0 + k]];
+    for (int k = 0; k < d; ++k) same &= a.prev[a.in_src[in_edge(e0, k, sn)]] == a.prev[a.in_src[in_edge(f0, k, sr)]];
     return same;
   }
   bool same = a.node_op[n] == a.node_op[r];
   for (int k = 0; k < a.Dd; ++k) same &= a.node_dense[(size_t)n * a.Dd + k] == a.node_dense[(size_t)r * a.Dd + k];
-  for (int64_t w = 0; w < (int64_t)d * a.De; ++w) same &= a.edge_feat[(size_t)e0 * a.De + w] == a.edge_feat[(size_t)f0 * a.De + w];
+  for (int k = 0; k < d; ++k) {
+    const uint32_t *x = a.edge_feat + (size_t)in_edge(e0, k, sn) * a.De, *y = a.edge_feat + (size_t)in_edge(f0, k, sr) * a.De;
+    for (int w = 0; w < a.De; ++w) same &= x[w] == y[w];
+  }
   return same;
 }
 

@@ -1789,7 +1789,7 @@ int find_distinct(xrl_ctx *c, xrl_batch *b) {
   char *cls_block = take(0, n_bytes * L);
   if (!cls_block) return XRL_OK;                            // (no memory for it: the batch is used as it is)
   const size_t scratch = align_up((size_t)slots * 8) + 2 * n_bytes + align_up((size_t)nb * 8) +
-                         (n_bytes + align_up((size_t)(N + 1) * 4)) * L;
+                         (n_bytes + align_up((size_t)(N + 1) * 4)) * L + align_up((size_t)N);
   int rc = ensure_bws(c, scratch);
   if (rc) { drop(); return rc == XRL_ERR_OOM ? XRL_OK : rc; }
   Bump bump{c->bws};
@@ -1800,8 +1800,11 @@ int find_distinct(xrl_ctx *c, xrl_batch *b) {
   a.table = bump.take<unsigned long long>(slots); a.mask = slots - 1;
   a.state_graph_ptr = d.state_graph_ptr; a.graph_node_ptr = d.graph_node_ptr;
   a.slot = bump.take<int32_t>((size_t)N); a.rep = bump.take<int32_t>((size_t)N); a.block_sum = bump.take<int2>((size_t)nb);
+  uint8_t *swapped = bump.take<uint8_t>((size_t)N);
+  a.swapped = swapped;
   std::vector<int32_t *> reps(L), ptr(L);
   const dim3 per_node((unsigned)((N + 255) / 256)), per_block((unsigned)nb), b256(256);
+  first_two_kernel<<<per_node, b256, 0, c->stream>>>(a, swapped);
   for (int l = 0; l < L; ++l) {
     a.prev = l > 0 ? q->cls[l - 1] : nullptr;
     a.cls = q->cls[l] = (int32_t *)(cls_block + n_bytes * l);
