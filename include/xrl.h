@@ -249,7 +249,8 @@ int xrl_batch_upload(xrl_ctx *ctx, xrl_batch *b);
  * rewrites of a few graphs (message-passing rounds of the MLP kind, at most 15; no receiver of more
  * than 32 in-edges) is reduced to its distinct nodes by the context that uploaded it when it is
  * first saved for the backward pass, or encoded a second time: that one call waits for the stream
- * twice, later calls compute every round once per distinct node. (A context on which calls have been
+ * twice, later calls compute every round once per distinct node. In bf16 at hidden = 256 the first forward-only
+ * encode of a large batch of rewrites is reduced too, on the device and for that call alone, without a wait. (A context on which calls have been
  * captured reduces no further batches: a graph keeps the addresses of the context's buffers, which
  * grow with the batches it is given, and only then.) States and embeddings are
  * the same bits; gradients are summed in another, equally fixed order.
@@ -258,7 +259,7 @@ int xrl_batch_upload(xrl_ctx *ctx, xrl_batch *b);
 int xrl_encode(xrl_ctx *ctx, const xrl_batch *b, float *d_emb, int save_for_backward);
 
 /* What xrl_encode computes of the batch in round `level` (0: the node-update layer): nodes, edges, nodes
- * with in-edges and edge tiles -- the batch's own, or its distinct ones once it has been reduced.
+ * with in-edges and edge tiles -- the batch's own, or its distinct ones once it has been reduced for good.
  * Errors: NULL, STATE, INDEX. */
 int xrl_batch_level(xrl_ctx *ctx, const xrl_batch *b, int32_t level, int64_t counts[4]);
 

@@ -56,7 +56,25 @@ struct Mlp2Args {
   float *carry;            // [n_tiles, 2, H]                (EDGE)
   const int32_t *tile_ptr; // [n_tiles + 1] first edge of each edge tile (EDGE)
   int64_t n_tiles;         //                                (EDGE)
+  // kernels instantiated for a level whose size the host does not know: its counts on the device, and the row
+  // of h of each edge's receiver (EDGE; in_src: of its sender) or of each node (NODE)
+  const unsigned long long *level_counts;
+  const int32_t *h_row;
 };
+// Counts of a level in one word (what the blocks that make it take at once from one counter)
+constexpr int kCountBits = 21;
+__device__ __forceinline__ int32_t level_classes(unsigned long long v) { return (int32_t)(v & ((1u << kCountBits) - 1)); }
+__device__ __forceinline__ int32_t level_edges(unsigned long long v) { return (int32_t)(v >> kCountBits & ((1u << kCountBits) - 1)); }
+__device__ __forceinline__ int32_t level_tiles(unsigned long long v) { return (int32_t)(v >> 2 * kCountBits); }
+template <bool LEVEL, bool EDGES>
+__device__ __forceinline__ Mlp2Args of_level(Mlp2Args a) {
+  if constexpr (LEVEL) {
+    const unsigned long long v = *a.level_counts;
+    a.n_rows = __builtin_amdgcn_readfirstlane(EDGES ? level_edges(v) : level_classes(v));
+    a.n_tiles = __builtin_amdgcn_readfirstlane(level_tiles(v));
+  }
+  return a;
+}
 
 // Raw (fp32) piece of one row's trailing attributes that lane group g feeds to slab `ts` of the
 // tail: columns [ts*2V + g*V, +V) of a row of `width` floats (width a multiple of 4), zeros

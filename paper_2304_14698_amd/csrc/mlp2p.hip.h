@@ -348,8 +348,10 @@ __global__ __launch_bounds__(64 * NW) void mlp2p_kernel(const Mlp2Args a) {
 // At H = 256 the second layer's weights alone take 128 KB: the table then stays in global memory
 // (32 KB, read through the caches), the block has four waves, and the rows leave through a
 // staging buffer of one 32-feature block per wave.
-template <typename T, int H, int NW, bool SAVE>
-__global__ __launch_bounds__(64 * NW) void embedp_kernel(const Mlp2Args a) {
+// LEVEL: as in mlp2r_kernel.
+template <typename T, int H, int NW, bool SAVE, bool LEVEL>
+__global__ __launch_bounds__(64 * NW) void embedp_kernel(const Mlp2Args args) {
+  const Mlp2Args a = of_level<LEVEL, false>(args);
   using Opd = Operand<T>;
   using vec = typename Opd::vec;
   constexpr int V = Opd::V, SL = 2 * V, MB = H / 32, QB = 32 / SL, NC2 = MB * QB, NT = 64 * NW;

@@ -99,24 +99,25 @@ __device__ __forceinline__ RTileRows rtile_rows(const Mlp2Args &a, int64_t wt) {
 struct RFetch {
   int src[4];
 };
-template <int H, int KIND>
+template <int H, int KIND, bool LEVEL>
 __device__ __forceinline__ RFetch rtile_index(const Mlp2Args &a, const RTileRows &t, int w, int lane) {
   using R = RTile<H, KIND>;
   RFetch f;
-  const int32_t *ip = w < R::MB / 2 ? a.in_src : a.in_dst;     // EDGE: first half senders, second half receivers
+  // EDGE: first half senders, second half receivers; NODE: agg_src, of a level the nodes' rows in the first half
+  const int32_t *ip = KIND == KIND_EDGE ? (w < R::MB / 2 ? a.in_src : LEVEL ? a.h_row : a.in_dst)
+                                        : (LEVEL && w < R::MB / 2 ? a.h_row : a.agg_src);
   int lq = lane / R::LPR;                                       // (opaque: recomputed per call, not four registers
   asm volatile("" : "+v"(lq));                                  //  of per-instruction row numbers kept across the loop)
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int r = R::RPI * ((4 * w + j) % (H / 16)) + lq;
     const int64_t row = t.r0 + (r < t.nv ? r : t.nv - 1);
-    if constexpr (KIND == KIND_EDGE) f.src[j] = ip[row];
-    else f.src[j] = a.agg_src[row];   // (requested by every wave, whichever part it fetches: a load under a
+    f.src[j] = ip[row];               // (requested by every wave, whichever part it fetches: a load under a
                                       //  condition would be waited for on the spot, behind the row prefetch)
   }
   return f;
 }
-template <int H, int KIND>
+template <int H, int KIND, bool LEVEL>
 __device__ __forceinline__ void rtile_fetch(const Mlp2Args &a, const RTileRows &t, const RFetch &f, int w, int lane,
                                             char *xbuf) {
   using R = RTile<H, KIND>;
@@ -128,7 +129,7 @@ __device__ __forceinline__ void rtile_fetch(const Mlp2Args &a, const RTileRows &
     const int q = 4 * w + j, r = R::RPI * (q % (H / 16)) + lv / R::LPR;
     const int piece = (lv % R::LPR) ^ (r & R::SWM);
     int64_t srow = f.src[j];
-    if constexpr (KIND == KIND_NODE) {
+    if constexpr (KIND == KIND_NODE && !LEVEL) {
       if (w < R::MB / 2) srow = t.r0 + (r < t.nv ? r : t.nv - 1);   // the node's own state
     }
     const bf16_t *rowp = srow < 0 ? (const bf16_t *)a.zero_row : base + (size_t)srow * H;
@@ -152,8 +153,10 @@ __device__ __forceinline__ void rtile_fetch(const Mlp2Args &a, const RTileRows &
 // stores them -- from the 4 KB of the buffer that only its own prefetch loads write, so no wave
 // waits for another. Row r sits at 4096 (r / 4) + 64 ((r / 4) % 4) + 528 (r % 4): 16-byte aligned,
 // and the 8-byte writes of 32 rows fall on 16 different bank groups.
-template <int H, int KIND, bool SAVE>
-__global__ __launch_bounds__((RTile<H, KIND>::NT), (RTile<H, KIND>::WAVES_PER_SIMD)) void mlp2r_kernel(const Mlp2Args a) {
+// LEVEL: a level of a batch that is reduced without the host (see once_fill_kernel).
+template <int H, int KIND, bool SAVE, bool LEVEL>
+__global__ __launch_bounds__((RTile<H, KIND>::NT), (RTile<H, KIND>::WAVES_PER_SIMD)) void mlp2r_kernel(const Mlp2Args args) {
+  const Mlp2Args a = of_level<LEVEL, KIND == KIND_EDGE>(args);
   using T = bf16_t;
   using R = RTile<H, KIND>;
   constexpr int MB = R::MB, HS = H / 16, NT = R::NT;
@@ -179,16 +182,16 @@ __global__ __launch_bounds__((RTile<H, KIND>::NT), (RTile<H, KIND>::WAVES_PER_SI
   // first two tiles' rows, third tile's indices
   RTileRows cur = rtile_rows<KIND>(a, wt);
   RTileRows nxt = cur;
-  rtile_fetch<H, KIND>(a, cur, rtile_index<H, KIND>(a, cur, w, lane), w, lane, smem);
+  rtile_fetch<H, KIND, LEVEL>(a, cur, rtile_index<H, KIND, LEVEL>(a, cur, w, lane), w, lane, smem);
   if (wt + nbx < t_end) {
     nxt = rtile_rows<KIND>(a, wt + nbx);
-    rtile_fetch<H, KIND>(a, nxt, rtile_index<H, KIND>(a, nxt, w, lane), w, lane, smem + R::XBUF);
+    rtile_fetch<H, KIND, LEVEL>(a, nxt, rtile_index<H, KIND, LEVEL>(a, nxt, w, lane), w, lane, smem + R::XBUF);
   }
   RTileRows nn = nxt;
   RFetch fn;
   if (wt + 2 * nbx < t_end) {
     nn = rtile_rows<KIND>(a, wt + 2 * nbx);
-    fn = rtile_index<H, KIND>(a, nn, w, lane);
+    fn = rtile_index<H, KIND, LEVEL>(a, nn, w, lane);
   }
   // this wave's weight slices, loaded once, and the biases in accumulator order (parked in LDS:
   // the weight slices leave few registers)
@@ -379,12 +382,12 @@ __global__ __launch_bounds__((RTile<H, KIND>::NT), (RTile<H, KIND>::WAVES_PER_SI
       __builtin_amdgcn_sched_barrier(0);
     }
     // the buffer this tile used is free now: rows of the tile after next, indices one further
-    if (wt + 2 * nbx < t_end) rtile_fetch<H, KIND>(a, nn, fn, w, lane, smem + buf * R::XBUF);
+    if (wt + 2 * nbx < t_end) rtile_fetch<H, KIND, LEVEL>(a, nn, fn, w, lane, smem + buf * R::XBUF);
     cur = nxt;
     nxt = nn;
     if (wt + 3 * nbx < t_end) {
       nn = rtile_rows<KIND>(a, wt + 3 * nbx);
-      fn = rtile_index<H, KIND>(a, nn, w, lane);
+      fn = rtile_index<H, KIND, LEVEL>(a, nn, w, lane);
     }
     buf ^= 1;
   }

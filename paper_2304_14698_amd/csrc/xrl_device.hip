@@ -1071,11 +1071,11 @@ inline size_t embedp_lds_bytes(int H, int nslabx, int Tn) {
   return w + (size_t)Tn * H * 4 + (size_t)kPersistWaves * RowStage<bf16_t, 128>::BYTES;
 }
 
-template <int H, bool SAVE>
+template <int H, bool SAVE, bool LEVEL = false>
 int launch_embedp_s(xrl_ctx *c, Mlp2Args &a) {
   constexpr int NW = embedp_waves(H);
   const size_t lds = embedp_lds_bytes(H, a.nslabx, a.Tn);
-  auto kern = embedp_kernel<bf16_t, H, NW, SAVE>;
+  auto kern = embedp_kernel<bf16_t, H, NW, SAVE, LEVEL>;
   static size_t attr_lds = 0;
   if (lds > attr_lds) {
     HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
@@ -1112,10 +1112,10 @@ inline bool mlp2p_applies(const xrl_ctx *c, int kind, const Mlp2Args &a) {
 }
 
 // Register-stationary variant (bf16, edge and node kinds).
-template <int H, int KIND, bool SAVE>
+template <int H, int KIND, bool SAVE, bool LEVEL = false>
 int launch_mlp2r_ks(xrl_ctx *c, Mlp2Args &a) {
   using R = RTile<H, KIND>;
-  auto kern = mlp2r_kernel<H, KIND, SAVE>;
+  auto kern = mlp2r_kernel<H, KIND, SAVE, LEVEL>;
   static bool attr_set = false;
   if (!attr_set) {
     HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, R::BYTES));
@@ -1735,21 +1735,13 @@ int make_groupings(xrl_ctx *c, const xrl_batch *b, Distinct *q, bool fold) {
   return XRL_OK;
 }
 
-// Whether a batch's levels are worth finding: its encode is estimated from the products' flops, and its
-// graphs have to look like rewrites of their state's first (half of the first 64 operators of a sample of
-// graphs the same, place by place). Finding the levels and the groupings takes 0.4 to 0.6 ms (70 k to
-// 700 k nodes), two waits included. Measured, us per step without / with, by the estimate (update
-// with a fresh minibatch, so that every step pays for it; 5 rounds, H = 128): 30 us 1008 / 1410, 108 us
-// 1912 / 1721, 216 us 3115 / 3874, 430 us 5380 / 3779; fp32 200 us 2265 / 2587. A batch kept over
-// the steps pays once: 430 us 622 / 337 forward only.
-bool distinct_pays(const xrl_ctx *c, const xrl_batch *b) {
-  const int H = c->m.hidden, R = c->m.rounds, De = c->m.d_edge;
-  if (c->distinct_min_us < 0 || c->m.round_kind != XRL_ROUND_MLP || R < 1 || R + 1 > kMaxLevels || b->G <= b->S || b->N < 1 || b->E < 1 || b->n_split_tiles > 0 ||
-      b->N + b->E > (int64_t)1 << kNodeBits)                // (table slots hold node numbers of so many bits)
-    return false;
-  const double flops = 2.0 * R * H * ((double)b->N * 3 * H + (double)b->E * (3 * H + De));
-  const double us = flops / (c->elem == 2 ? 7e8 : 7e7);                                 // (flops per us measured)
-  if (us < (double)c->distinct_min_us) return false;
+double encode_estimate_us(const xrl_ctx *c, const xrl_batch *b) {
+  const double H = c->m.hidden, De = c->m.d_edge;
+  return 2.0 * c->m.rounds * H * ((double)b->N * 3 * H + (double)b->E * (3 * H + De)) / (c->elem == 2 ? 7e8 : 7e7);   // (flops per us measured)
+}
+// Whether a batch's graphs look like rewrites of their state's first: half of the first 64 operators of a sample of
+// graphs the same, place by place.
+bool looks_like_rewrites(const xrl_ctx *c, const xrl_batch *b) {
   if (b->from_edits || c->distinct_min_us == 0) return true;
   const int32_t *sgp = b->at<int32_t>(b->o_state_graph_ptr), *gnp = b->at<int32_t>(b->o_graph_node_ptr), *op = b->at<int32_t>(b->o_node_op);
   const int64_t step = std::max<int64_t>(1, b->G / 64);
@@ -1763,6 +1755,110 @@ bool distinct_pays(const xrl_ctx *c, const xrl_batch *b) {
     seen += 64;
   }
   return 2 * same >= seen;
+}
+
+// Whether a batch's levels are worth finding: its encode is estimated from the products' flops, and its
+// graphs have to look like rewrites of their state's first (half of the first 64 operators of a sample of
+// graphs the same, place by place). Finding the levels and the groupings takes 0.4 to 0.6 ms (70 k to
+// 700 k nodes), two waits included. Measured, us per step without / with, by the estimate (update
+// with a fresh minibatch, so that every step pays for it; 5 rounds, H = 128): 30 us 1008 / 1410, 108 us
+// 1912 / 1721, 216 us 3115 / 3874, 430 us 5380 / 3779; fp32 200 us 2265 / 2587. A batch kept over
+// the steps pays once: 430 us 622 / 337 forward only.
+bool distinct_pays(const xrl_ctx *c, const xrl_batch *b) {
+  const int R = c->m.rounds;
+  if (c->distinct_min_us < 0 || c->m.round_kind != XRL_ROUND_MLP || R < 1 || R + 1 > kMaxLevels || b->G <= b->S || b->N < 1 || b->E < 1 || b->n_split_tiles > 0 ||
+      b->N + b->E > (int64_t)1 << kNodeBits)                // (table slots hold node numbers of so many bits)
+    return false;
+  return encode_estimate_us(c, b) >= (double)c->distinct_min_us && looks_like_rewrites(c, b);
+}
+
+// The same for one forward-only encode (see OnceArgs): no wait and nothing kept, so it pays for the classes alone.
+// us of an encode as it is / by levels, H = 256, by the estimate: one inception-shaped state 110 us 210 / 337, 217 289 / 368,
+// 417 444 / 454, 828 736 / 563; a transformer-shaped one 216 288 / 289, 429 439 / 309, 715 632 / 332; states of residual networks
+// 505 508 / 353, 2008 1800 / 587. At H <= 128 a round costs a third of that and finding its level as much; in fp32 the
+// kernels of a round take their sizes from the host.
+constexpr int kOnceMinUs = 430;
+bool once_pays(const xrl_ctx *c, const xrl_batch *b) {
+  const xrl_model_desc &m = c->m;
+  if (c->elem != 2 || m.hidden != 256 || c->distinct_min_us < 0 || c->captured || m.round_kind != XRL_ROUND_MLP || m.rounds < 1 ||
+      m.rounds + 1 > kMaxLevels || b->G <= b->S || b->n_split_tiles > 0 || b->E < 1 || std::max(b->N, b->E) > kOnceMax)
+    return false;
+  Mlp2Args t;
+  memset(&t, 0, sizeof(t));
+  t.De = m.d_edge; t.Tn = m.n_op_types; t.Dd = m.n_node_dense; t.n_rows = std::min(b->N, b->E);
+  t.nslabx = c->embed.nslabx;
+  if (!mlp2p_applies(c, KIND_EMBED, t)) return false;
+  for (int r = 0; r < m.rounds; ++r) {
+    t.nslab1 = c->edge[r].nslab1;
+    if (!mlp2r_applies(c, KIND_EDGE, t)) return false;
+  }
+  return (c->distinct_min_us == 0 || encode_estimate_us(c, b) >= kOnceMinUs) && looks_like_rewrites(c, b);
+}
+struct OnceLevels {
+  OnceArgs o;
+  int32_t *cls[2];
+  unsigned long long *counts;              // [levels]
+  unsigned blocks_per_graph;
+  const int32_t *classes(int l) const { return cls[l & 1]; }
+};
+int once_begin(xrl_ctx *c, const xrl_batch *b, OnceLevels &q) {
+  const int64_t N = b->N, E = b->E;
+  const int De = c->m.d_edge, Dd = c->m.n_node_dense;
+  const xrl_batch_device &d = b->dev;
+  uint32_t slots = 1024;
+  while (slots < (uint64_t)N + N / 2) slots *= 2;
+  const int64_t max_tiles = 2 * E / 33 + 2 * ((N + kOnceNodes - 1) / kOnceNodes) + 2;
+  auto plan = [&](char *base) -> size_t {
+    Bump m{base};
+    ClassArgs &a = q.o.k;
+    a.table = m.take<unsigned long long>(slots);
+    q.counts = m.take<unsigned long long>(kMaxLevels);
+    q.o.num = m.take<int32_t>(slots);
+    a.swapped = m.take<uint8_t>((size_t)N);
+    a.slot = m.take<int32_t>((size_t)N);
+    for (int i = 0; i < 2; ++i) q.cls[i] = m.take<int32_t>((size_t)N);
+    q.o.o_ptr = m.take<int32_t>((size_t)N + 1);
+    q.o.o_agg_src = m.take<int32_t>((size_t)N);
+    q.o.o_self = m.take<int32_t>((size_t)N);
+    q.o.o_op = m.take<int32_t>((size_t)N);
+    q.o.o_src = m.take<int32_t>((size_t)E);
+    q.o.o_dst = m.take<int32_t>((size_t)E);
+    q.o.o_hrow = m.take<int32_t>((size_t)E);
+    q.o.o_tile = m.take<int32_t>((size_t)max_tiles);
+    q.o.o_feat = m.take<float>((size_t)E * De);
+    q.o.o_dense = m.take<float>((size_t)N * Dd);
+    return m.off;
+  };
+  memset(&q, 0, sizeof(q));
+  RelaxedCapture relaxed;               // (as in find_distinct)
+  if (int rc = ensure_bws(c, plan(nullptr))) return rc;
+  plan(c->bws);
+  ClassArgs &a = q.o.k;
+  a.N = N; a.in_ptr = d.in_ptr; a.in_src = d.in_src; a.node_op = d.node_op;
+  a.edge_feat = (const uint32_t *)d.edge_feat; a.node_dense = (const uint32_t *)d.node_dense; a.De = De; a.Dd = Dd;
+  a.mask = slots - 1; a.state_graph_ptr = d.state_graph_ptr; a.graph_node_ptr = d.graph_node_ptr;
+  q.blocks_per_graph = (unsigned)std::max<int64_t>(1, (b->max_graph_nodes + 255) / 256);
+  once_clear_kernel<<<dim3((slots + 255) / 256), dim3(256), 0, c->stream>>>(a.table, slots, q.counts);
+  first_two_kernel<<<dim3((unsigned)((N + 255) / 256)), dim3(256), 0, c->stream>>>(a, (uint8_t *)a.swapped);
+  HIP_TRY(hipGetLastError());
+  return XRL_OK;
+}
+// the classes and the graph of level l; `a`: as the kernels of the round take it
+int once_level(xrl_ctx *c, const xrl_batch *b, OnceLevels &q, int l, Mlp2Args &a) {
+  const dim3 per_node((unsigned)((b->N + 255) / 256)), b256(256);
+  q.o.k.prev = l > 0 ? q.cls[(l - 1) & 1] : nullptr;
+  q.o.k.cls = q.cls[l & 1];
+  q.o.counts = q.counts + l;
+  once_insert_first_kernel<<<dim3((unsigned)b->S * q.blocks_per_graph), b256, 0, c->stream>>>(q.o.k, (int)q.blocks_per_graph);
+  once_insert_kernel<<<per_node, b256, 0, c->stream>>>(q.o.k);
+  once_fill_kernel<<<dim3((unsigned)((b->N + kOnceNodes - 1) / kOnceNodes)), b256, 0, c->stream>>>(q.o);
+  once_class_kernel<<<per_node, b256, 0, c->stream>>>(q.o.k, q.o.num);
+  HIP_TRY(hipGetLastError());
+  a.level_counts = q.o.counts;
+  a.in_ptr = q.o.o_ptr; a.in_src = q.o.o_src; a.in_dst = q.o.o_dst; a.agg_src = q.o.o_agg_src; a.edge_feat = q.o.o_feat;
+  a.node_op = q.o.o_op; a.node_dense = q.o.o_dense; a.tile_ptr = q.o.o_tile;
+  a.n_tiles = b->n_tiles;                  // (of the whole batch: the grid)
+  return XRL_OK;
 }
 
 // Finds the levels' classes, reads back how many there are, and, if that is few enough, makes the levels'
@@ -2483,6 +2579,37 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   c->enc_batch = b->id;
   c->enc_saved = save != 0;
 
+  // ---- global-update layer: per-graph sum (or mean) of the last states (with cls: of each node's class), then the readout MLP
+  auto readout = [&](const T *hlast, const int32_t *cls) -> int {
+    int rc = XRL_OK;
+    if (N <= 4096 * G) {
+      // many graphs of moderate size: one block per graph sums its nodes and runs the readout MLP
+      Timed t(c, TK_POOL);
+      int dmax = 0;
+      const RowMlpArgs ra = rowmlp_args(c, c->L.readout, true, c->pool, H, d.graph_global, m.d_global, G, d_emb,
+                                        c->ro_act, &dmax);
+      const size_t lds = (size_t)(256 * PV + 2 * dmax) * sizeof(float);
+      const int mean = m.readout == XRL_READOUT_MEAN ? 1 : 0;
+      if (cls)
+        graph_readout_kernel<T, PV, 8, true><<<dim3((unsigned)G), dim3(256), lds, c->stream>>>(
+            hlast, d.graph_node_ptr, H, mean, c->pool, ra, cls);
+      else
+        graph_readout_kernel<T, PV, 8, false><<<dim3((unsigned)G), dim3(256), lds, c->stream>>>(
+            hlast, d.graph_node_ptr, H, mean, c->pool, ra, nullptr);
+      HIP_TRY(hipGetLastError());
+      return XRL_OK;
+    }
+    { Timed t(c, TK_POOL);
+      rc = launch_segsum<T, float, PV>(c, hlast, cls, d.graph_node_ptr, d.node_graph, N, G, H, c->pool, c->carry); }
+    if (rc) return rc;
+    if (m.readout == XRL_READOUT_MEAN && G > 0)
+      mean_scale_kernel<<<dim3((unsigned)((G * H + 255) / 256)), dim3(256), 0, c->stream>>>(c->pool, d.graph_node_ptr, G, H, 0);
+    { Timed t(c, TK_READOUT);
+      rc = launch_rowmlp(c, c->L.readout, true, c->pool, H, d.graph_global, m.d_global, G, d_emb, c->ro_act); }
+    if (rc) return rc;
+    HIP_TRY(hipGetLastError());
+    return XRL_OK;
+  };
   // ---- node-update layer: the embed MLP (it sums each node's incoming edge attrs itself)
   Mlp2Args a;
   memset(&a, 0, sizeof(a));
@@ -2556,6 +2683,35 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   // zeros for nodes without in-edges through agg_src, so nobody has to write those rows
   a.n_agg = 0; a.agg_src = lev(0).agg_src;
   c->agg_skip = !gat;
+  OnceLevels once;
+  if constexpr (sizeof(T) == 2) {
+    bool by_levels = !save && !q && once_pays(c, b);
+    if (by_levels) {
+      rc = once_begin(c, b, once);
+      if (rc && rc != XRL_ERR_OOM) return rc;
+      by_levels = rc == XRL_OK;        // (no memory for it: the batch is encoded as it is)
+    }
+    if (by_levels) {
+      if ((rc = once_level(c, b, once, 0, a))) return rc;
+      { Timed t(c, TK_EMBED); rc = launch_embedp_s<256, false, true>(c, a); }
+      if (rc) return rc;
+      T *hcur = hb[0];
+      for (int r = 0; r < R; ++r) {
+        T *hnext = hb[(r + 1) & 1];
+        if ((rc = once_level(c, b, once, r + 1, a))) return rc;
+        set_w(c->edge[r]);
+        a.n_rows = E; a.h = hcur; a.out = ab[0]; a.h_row = once.o.o_hrow;
+        { Timed t(c, TK_EDGE); rc = launch_mlp2r_ks<256, KIND_EDGE, false, true>(c, a); }
+        if (rc) return rc;
+        set_w(c->node[r]);
+        a.n_rows = N; a.agg = ab[0]; a.out = hnext; a.h_row = once.o.o_self;
+        { Timed t(c, TK_NODE); rc = launch_mlp2r_ks<256, KIND_NODE, false, true>(c, a); }
+        if (rc) return rc;
+        hcur = hnext;
+      }
+      return readout(hcur, once.classes(R));
+    }
+  }
   a.z1 = c->z1_embed; a.z1mask = c->zm_embed; a.ymask = c->ym_embed;
   { Timed t(c, TK_EMBED); rc = launch_mlp2<T>(c, KIND_EMBED, a); }
   if (rc) return rc;
@@ -2633,34 +2789,7 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
     c->agg[r + 1] = aggb;
     hcur = hnext;
   }
-  // ---- global-update layer: per-graph sum (or mean), then the readout MLP
-  if (N <= 4096 * G) {
-    // many graphs of moderate size: one block per graph sums its nodes and runs the readout MLP
-    Timed t(c, TK_POOL);
-    int dmax = 0;
-    const RowMlpArgs ra = rowmlp_args(c, c->L.readout, true, c->pool, H, d.graph_global, m.d_global, G, d_emb,
-                                      c->ro_act, &dmax);
-    const size_t lds = (size_t)(256 * PV + 2 * dmax) * sizeof(float);
-    const int mean = m.readout == XRL_READOUT_MEAN ? 1 : 0;
-    if (q)
-      graph_readout_kernel<T, PV, 8, true><<<dim3((unsigned)G), dim3(256), lds, c->stream>>>(
-          hcur, d.graph_node_ptr, H, mean, c->pool, ra, q->cls[R]);
-    else
-      graph_readout_kernel<T, PV, 8, false><<<dim3((unsigned)G), dim3(256), lds, c->stream>>>(
-          hcur, d.graph_node_ptr, H, mean, c->pool, ra, nullptr);
-    HIP_TRY(hipGetLastError());
-    return XRL_OK;
-  }
-  { Timed t(c, TK_POOL);
-    rc = launch_segsum<T, float, PV>(c, hcur, q ? q->cls[R] : nullptr, d.graph_node_ptr, d.node_graph, N, G, H, c->pool, c->carry); }
-  if (rc) return rc;
-  if (m.readout == XRL_READOUT_MEAN && G > 0)
-    mean_scale_kernel<<<dim3((unsigned)((G * H + 255) / 256)), dim3(256), 0, c->stream>>>(c->pool, d.graph_node_ptr, G, H, 0);
-  { Timed t(c, TK_READOUT);
-    rc = launch_rowmlp(c, c->L.readout, true, c->pool, H, d.graph_global, m.d_global, G, d_emb, c->ro_act); }
-  if (rc) return rc;
-  HIP_TRY(hipGetLastError());
-  return XRL_OK;
+  return readout(hcur, q ? q->cls[R] : nullptr);
 }
 
 }  // namespace

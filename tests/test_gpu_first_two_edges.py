@@ -4,6 +4,7 @@ import dataclasses
 
 import numpy as np
 import pytest
+import torch  # noqa: F401  (its HIP runtime is loaded ahead of the library)
 
 import paper_2304_14698_amd as xrl
 import synth
