@@ -78,14 +78,25 @@ struct SwzJob {
 
 namespace {
 // One row of blocks (y) per copy, a lane fragment (16 bytes in bf16 and fp32 operands) per thread and
-// step; the last row copies the flat vector itself. Bound by the reads of the staged vector (each
-// matrix is read by two to four copies, from L2), which is far below the transfer that precedes it.
+// step; the last rows copy the flat vector itself, four 16-byte pieces per thread. Bound by the latency of two round trips. (One
+// row of blocks for the flat vector, 4 bytes a step, took 36 steps and most of the launch, and loads under conditions came one by one: H = 128, fp32 25 us, so 10; H = 256 47, so 17.)
+constexpr int kFlatPieces = 4;
 __global__ __launch_bounds__(256) void arrange_weights_kernel(const SwzJob *jobs, int n_jobs, const float *w, int64_t n_w,
                                                               char *dst, float *d_w) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if ((int)blockIdx.y == n_jobs) {
-    for (; i < n_w; i += stride) d_w[i] = w[i];
+  if ((int)blockIdx.y >= n_jobs) {
+    const int64_t n4 = n_w / 4, all = stride * (gridDim.y - n_jobs);
+    i += stride * ((int)blockIdx.y - n_jobs);
+    if (i < n_w - 4 * n4) d_w[4 * n4 + i] = w[4 * n4 + i];
+    for (; i < n4; i += all * kFlatPieces) {
+      f32x4 v[kFlatPieces];
+#pragma unroll
+      for (int k = 0; k < kFlatPieces; ++k) v[k] = ((const f32x4 *)w)[i + k * all < n4 ? i + k * all : i];
+#pragma unroll
+      for (int k = 0; k < kFlatPieces; ++k)
+        if (i + k * all < n4) ((f32x4 *)d_w)[i + k * all] = v[k];
+    }
     return;
   }
   const SwzJob j = jobs[blockIdx.y];
@@ -101,12 +112,23 @@ __global__ __launch_bounds__(256) void arrange_weights_kernel(const SwzJob *jobs
     const float *p = w + j.src + (int64_t)(32 * cb + (l & 31)) * j.sf;
     const bool frag = j.kind == SWZ_FRAGMENT || j.kind == SWZ_FRAGMENT3;
     float v[8];
-    for (int e = 0; e < j.V; ++e) {
-      int k = frag ? s * 2 * j.V + g * j.V + e : 2 * j.V * s + 8 * (e >> 2) + 4 * g + (e & 3);
-      const bool in = k < j.K;
-      if (frag && k >= j.k_gap_at) k += j.k_gap;
-      v[e] = in ? p[(int64_t)k * j.sk] : 0.f;
-    }
+    auto gather = [&](auto width) {      // (every load under no condition: all in flight at once)
+      constexpr int V = decltype(width)::value;
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        const int k0 = frag ? s * 2 * V + g * V + e : 2 * V * s + 8 * (e >> 2) + 4 * g + (e & 3);
+        int k = k0 < j.K ? k0 : j.K - 1;
+        if (frag && k >= j.k_gap_at) k += j.k_gap;
+        v[e] = p[(int64_t)k * j.sk];
+      }
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        const int k0 = frag ? s * 2 * V + g * V + e : 2 * V * s + 8 * (e >> 2) + 4 * g + (e & 3);
+        if (k0 >= j.K) v[e] = 0.f;
+      }
+    };
+    if (j.V == 8) gather(std::integral_constant<int, 8>());
+    else gather(std::integral_constant<int, 4>());
     if (j.kind == SWZ_FRAGMENT3 || j.kind == SWZ_CHAIN3) {
       const Split3 parts = split3(v);
       for (int k = 0; k < 3; ++k) *(bf16x8 *)(dst + j.dst + ((t * 3 + k) * 64 + l) * 16) = parts.p[k];
@@ -811,7 +833,8 @@ int upload_weights(xrl_ctx *c, const float *w_user) {
   (void)hipEventRecord(c->wstage_free, c->stream);
   if (rc) return rc;
   const unsigned gx = (unsigned)std::min<int64_t>((c->swz_max_groups + 255) / 256, 256);
-  arrange_weights_kernel<<<dim3(gx, (unsigned)c->n_swz_jobs + 1), dim3(256), 0, c->stream>>>(
+  const unsigned flat = (unsigned)((c->L.total / 4 + (int64_t)gx * 256 * kFlatPieces - 1) / ((int64_t)gx * 256 * kFlatPieces));
+  arrange_weights_kernel<<<dim3(gx, (unsigned)c->n_swz_jobs + std::max(flat, 1u)), dim3(256), 0, c->stream>>>(
       c->swz_jobs, c->n_swz_jobs, c->d_wstage, c->L.total, c->d_swz, c->d_w);
   HIP_TRY(hipGetLastError());
   return XRL_OK;
