@@ -248,7 +248,7 @@ int xrl_batch_upload(xrl_ctx *ctx, xrl_batch *b);
  * the same senders' histories, edge by edge -- have the same state, bit for bit. A large batch of
  * rewrites of a few graphs (message-passing rounds of the MLP kind, at most 15; no receiver of more
  * than 32 in-edges) is reduced to its distinct nodes by the context that uploaded it when it is
- * first saved for the backward pass, or encoded a second time: that one call waits for the stream
+ * first saved for the backward pass, or encoded a second time (a smaller one: several times): that one call waits for the stream
  * twice, later calls compute every round once per distinct node. In bf16 at hidden = 256 the first forward-only
  * encode of a large batch of rewrites is reduced too, on the device and for that call alone, without a wait. (A context on which calls have been
  * captured reduces no further batches: a graph keeps the addresses of the context's buffers, which

@@ -1787,12 +1787,27 @@ bool looks_like_rewrites(const xrl_ctx *c, const xrl_batch *b) {
 // with a fresh minibatch, so that every step pays for it; 5 rounds, H = 128): 30 us 1008 / 1410, 108 us
 // 1912 / 1721, 216 us 3115 / 3874, 430 us 5380 / 3779; fp32 200 us 2265 / 2587. A batch kept over
 // the steps pays once: 430 us 622 / 337 forward only.
-bool distinct_pays(const xrl_ctx *c, const xrl_batch *b) {
+// A smaller batch, from a tenth of that estimate on (fp32: a quarter), pays over several encodes: it is reduced once as much has
+// been spent for want of it (three times the estimate for a step that is differentiated, 0.8 for another) as it takes, so
+// no number of encodes costs more than twice what the better choice would. Kept batches, us per step whole / reduced:
+// update bf16 H = 128, 38 us 672 / 590, 124 us 1105 / 608, H = 256, 150 us 1339 / 1014, H = 64, 31 us 674 / 439, fp32, 95 us
+// 715 / 466; forward only 238 / 194, 324 / 199, 518 / 410, 179 / 128, 207 / 163; below: H = 256, 26 us 735 / 975, fp32, 65 us 588 / 585.
+constexpr double kReduceUs = 450;
+bool distinct_pays(const xrl_ctx *c, xrl_batch *b, bool save) {
   const int R = c->m.rounds;
-  if (c->distinct_min_us < 0 || c->m.round_kind != XRL_ROUND_MLP || R < 1 || R + 1 > kMaxLevels || b->G <= b->S || b->N < 1 || b->E < 1 || b->n_split_tiles > 0 ||
+  if (c->distinct_min_us < 0 || c->captured || c->m.round_kind != XRL_ROUND_MLP || R < 1 || R + 1 > kMaxLevels || b->G <= b->S || b->N < 1 || b->E < 1 || b->n_split_tiles > 0 ||
       b->N + b->E > (int64_t)1 << kNodeBits)                // (table slots hold node numbers of so many bits)
     return false;
-  return encode_estimate_us(c, b) >= (double)c->distinct_min_us && looks_like_rewrites(c, b);
+  const double us = encode_estimate_us(c, b), min_us = (double)c->distinct_min_us;
+  if (us >= min_us) return (save || b->encodes > 0) && looks_like_rewrites(c, b);
+  if (us < min_us / (c->elem == 2 ? 10 : 4)) return false;
+  if (b->forgone_us < kReduceUs) {
+    b->forgone_us += us * (save ? 3.0 : 0.8);
+    return false;
+  }
+  if (looks_like_rewrites(c, b)) return true;
+  b->encodes = -1;                          // (not asked again)
+  return false;
 }
 
 // The same for one forward-only encode (see OnceArgs): no wait and nothing kept, so it pays for the classes alone.
@@ -3124,6 +3139,7 @@ int xrl_batch_upload(xrl_ctx *c, xrl_batch *b) {
   d.graph_tile_ptr = b->has_graph_tiles ? (int32_t *)(blk + b->o_graph_tile) : nullptr;
   d.agg_src = (int32_t *)(blk + o_as);
   b->encodes = 0;
+  b->forgone_us = 0;
   b->out_maker = 0;
   b->uploaded = true;
   return XRL_OK;
@@ -3144,14 +3160,16 @@ int xrl_encode(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save_for_backwa
                              "blocks of its one-launch form ran out); its embeddings are invalid");
   }
   if (b->owner == c->id && b->encodes >= 0) {
-    // Reduced to its distinct nodes when it is first saved for a backward pass, or encoded again: a batch
-    // encoded once and forward only would not earn back what finding them takes. Not in a capture, nor
+    // Reduced to its distinct nodes when it is first saved for a backward pass, or encoded again (a smaller one: several
+    // times): a batch encoded once and forward only would not earn back what finding them takes. Not in a capture, nor
     // once the context has been through one: a reduced batch's buffers may be larger than those it was
     // encoded whole in, and to grow them would free what the graphs write to.
     xrl_batch *mb = const_cast<xrl_batch *>(b);
-    if ((save_for_backward || ++mb->encodes > 1) && !c->captured && distinct_pays(c, b)) {
+    if (distinct_pays(c, mb, save_for_backward != 0)) {
       mb->encodes = -1;
       if ((rc = find_distinct(c, mb))) return rc;
+    } else if (!save_for_backward && mb->encodes >= 0) {
+      ++mb->encodes;
     }
   }
   return c->elem == 2 ? encode_impl<bf16_t>(c, b, d_emb, save_for_backward)

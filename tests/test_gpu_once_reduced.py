@@ -37,3 +37,24 @@ def test_levels_made_on_the_device(readout, rounds, monkeypatch):
     whole = _embeddings(model, w, pack, "-1", monkeypatch)
     levels = _embeddings(model, w, pack, "0", monkeypatch)
     assert all(np.array_equal(a, b) for a, b in zip(whole, levels))
+
+
+@pytest.mark.parametrize("save", [False, True])
+def test_a_kept_batch_is_reduced_after_some_encodes(save):
+    """Below the threshold of the first: the more an encode takes, the sooner; same bits before and after."""
+    rng = np.random.Generator(np.random.PCG64(12))
+    model, _ = synth.make_config(1)
+    model.update(hidden=128, precision="bf16", rounds=5)
+    state = synth.concat_states([synth.make_state(rng, synth.resnet_dag(rng, 16), 90, by_block=True)])
+    enc = xrl.Encoder(model, synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1))
+    batch = enc.pack(state)
+    us = 10 * 128 * (batch.N * 384 + batch.E * 392) / 7e8
+    assert 30 < us < 300
+    first, whole = enc.encode(batch, save_for_backward=save).cpu().numpy(), 1
+    while enc.batch_level(batch, 0)[0] == batch.N and whole < 20:
+        assert np.array_equal(enc.encode(batch, save_for_backward=save).cpu().numpy(), first)
+        whole += 1
+    assert whole == np.ceil(450 / (us * (3.0 if save else 0.8))) + 1
+    assert np.array_equal(enc.encode(batch).cpu().numpy(), first)
+    batch.free()
+    enc.close()
