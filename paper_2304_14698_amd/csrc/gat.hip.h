@@ -199,16 +199,11 @@ struct GatAhead {
   }
 };
 
-// One receiver per group of H * sizeof(T) / 16 lanes, each lane a 16-byte column slice: softmax
+// One receiver per group of H * sizeof(T) / 16 lanes, each a 16-byte column slice: softmax
 // over the receiver's in-edges (contiguous in receiver order) plus the self edge, weighted sum
 // of the gathered z rows, ReLU. Edges are taken in order, so the result is run-to-run identical.
 template <typename T, int VEC>
-__global__ __launch_bounds__(256) void gat_aggregate_kernel(const GatArgs a, int H) {
-  const int lpr = H / VEC;
-  const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t n = gt / lpr;
-  if (n >= a.n_rows) return;
-  const int c = (int)(gt - n * lpr) * VEC;
+__device__ __forceinline__ void gat_aggregate_row(const GatArgs &a, int H, int64_t n, int c, float *r) {
   const T *z = (const T *)a.z;
   const int e0 = a.in_ptr[n], e1 = a.in_ptr[n + 1];
   GatAhead<T, VEC> ahead;
@@ -243,13 +238,138 @@ __global__ __launch_bounds__(256) void gat_aggregate_kernel(const GatArgs a, int
     for (int j = 0; j < VEC; ++j) acc[j] = fmaf(w, v[j], acc[j]);
   }
   const float inv = 1.f / den;
+#pragma unroll
+  for (int j = 0; j < VEC; ++j) r[j] = fmaxf(acc[j] * inv, 0.f);
+}
+template <typename T, int VEC>
+__global__ __launch_bounds__(256) void gat_aggregate_kernel(const GatArgs a, int H) {
+  const int lpr = H / VEC;
+  const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t n = gt / lpr;
+  if (n >= a.n_rows) return;
+  const int c = (int)(gt - n * lpr) * VEC;
+  float r[VEC];
+  gat_aggregate_row<T, VEC>(a, H, n, c, r);
   T *o = (T *)a.out + (size_t)n * H + c;
 #pragma unroll
-  for (int q = 0; q < VEC / 4; ++q) {
-    float r[4];
+  for (int q = 0; q < VEC / 4; ++q) store4<T>(o + 4 * q, r + 4 * q);
+}
+
+// A round's aggregation and the product of the next round in one launch: a persistent block of 32 receivers' lane groups
+// aggregates a tile of 32 rows into LDS as operand fragments, and one of its waves, each in turn, forms z = h W of the tile from
+// there and from W, which the block keeps in LDS, while the others aggregate the next tile (two tile buffers, one
+// barrier a tile). h leaves for memory only where it is kept for the backward pass. The arithmetic is that of the two
+// kernels above. Bound by the aggregation's three dependent gathers. Encodes of
+// five rounds, two kernels a round / this one, us: bf16 H = 128, 1 k nodes 64.3 / 55.8, 18 k 90 / 80, 37 k 135 / 110, 55 k 145 / 128, 145 k 220 / 243;
+// H = 64, 1 k 60 / 47, 37 k 86 / 69, 73 k 125 / 96; fp32 H = 64, 1 k 71 / 56, 37 k 136 / 116, 55 k 149 / 143, 73 k 172 / 176. Two blocks a
+// compute unit: for three the registers spill (22 us a round of 35 k nodes for 18; two kernels 24).
+template <typename T, int H>
+struct GatRound {
+  static constexpr int MB = H / 32, HS = H / (2 * Operand<T>::V), LPR = H * (int)sizeof(T) / 16;
+  static constexpr int NW = 32 * LPR / 64, NT = 64 * NW;                       // lanes for 32 receivers
+  static constexpr int SROW = H * (int)sizeof(T) + 16, XBYTES = 32 * SROW;     // a tile as operand fragments, then its rows of z
+  static constexpr int WBYTES = HS * MB * 1024, ABYTES = 2 * MB * 2 * 16 * 4;
+  static constexpr int BYTES = WBYTES + ABYTES + 2 * XBYTES;
+  static constexpr bool FITS = WBYTES <= 32 * 1024;
+  static constexpr int PER_CU = 2;
+};
+struct GatNext {                 // of the next round
+  const void *Ws;
+  const float *a_src, *a_dst;
+  void *z;
+  float *s_src, *s_dst;
+};
+template <typename T, int H>
+__global__ __launch_bounds__((GatRound<T, H>::NT), (GatRound<T, H>::PER_CU * GatRound<T, H>::NW / 4)) void gat_round_kernel(const GatArgs a, const GatNext next) {
+  using Opd = Operand<T>;
+  using vec = typename Opd::vec;
+  using S = GatRound<T, H>;
+  constexpr int VEC = 16 / (int)sizeof(T), MB = S::MB, HS = S::HS, NT = S::NT;
+  extern __shared__ __align__(16) char smem[];
+  vec *Wl = (vec *)smem;                                             // [HS][MB][64]
+  float(*al)[MB][2][16] = (float(*)[MB][2][16])(smem + S::WBYTES);   // a_src, a_dst in accumulator order
+  char *xbuf = smem + S::WBYTES + S::ABYTES;
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nbx = gridDim.x / 8, xcd = blockIdx.x % 8, lid = blockIdx.x / 8;
+  const int64_t n_wt = (a.n_rows + 31) / 32, per_xcd = (n_wt + 7) / 8, t_begin = xcd * per_xcd;
+  const int64_t t_end = t_begin + per_xcd < n_wt ? t_begin + per_xcd : n_wt;
+  int64_t wt = t_begin + lid;
+  if (wt >= t_end) return;                                           // (the whole block)
+  {
+    constexpr int NF = HS * MB * 64, C = (NF + NT - 1) / NT;
+    const vec *W = (const vec *)next.Ws;
+    vec t[C];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) r[j] = fmaxf(acc[4 * q + j] * inv, 0.f);
-    store4<T>(o + 4 * q, r);
+    for (int c = 0; c < C; ++c) t[c] = W[tid + c * NT < NF ? tid + c * NT : 0];
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+      if (tid + c * NT < NF) Wl[tid + c * NT] = t[c];
+    if (tid < MB * 32) {
+      const int f = 32 * (tid / 32) + acc_row(tid % 16, (tid / 16) % 2);
+      al[0][tid / 32][(tid / 16) % 2][tid % 16] = next.a_src[f];
+      al[1][tid / 32][(tid / 16) % 2][tid % 16] = next.a_dst[f];
+    }
+  }
+  const int row = tid / S::LPR, piece = tid % S::LPR, c = piece * VEC;
+  int turn = 0, buf = 0;
+  for (; wt < t_end; wt += nbx) {
+    asm volatile("" ::: "memory");                           // (W's fragments are read from LDS in every tile)
+    char *x = xbuf + buf * S::XBYTES;
+    const int64_t row0 = wt * 32;
+    const int64_t n = row0 + row < a.n_rows ? row0 + row : a.n_rows - 1;
+    float r[VEC];
+    gat_aggregate_row<T, VEC>(a, H, n, c, r);
+    T *f = (T *)(x + ((size_t)(piece / 2) * 64 + (piece & 1) * 32 + row) * 16);   // piece 2 s + g of a row: slab s, lane group g
+#pragma unroll
+    for (int q = 0; q < VEC / 4; ++q) store4<T>(f + 4 * q, r + 4 * q);
+    if (a.out && row0 + row < a.n_rows) {
+      T *o = (T *)a.out + (size_t)n * H + c;
+#pragma unroll
+      for (int q = 0; q < VEC / 4; ++q) store4<T>(o + 4 * q, r + 4 * q);
+    }
+    __syncthreads();
+    if (wave == turn) {
+      vec h[HS];
+#pragma unroll
+      for (int s = 0; s < HS; ++s) h[s] = *(const vec *)(x + ((size_t)s * 64 + lane) * 16);
+      wave_lds_fence();
+      float ps = 0.f, pd = 0.f;
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        f32x16 acc;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+#pragma unroll
+        for (int s = 0; s < HS; ++s) Opd::mma(Wl[(s * MB + mb) * 64 + lane], h[s], acc);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          ps = fmaf(acc[i], al[0][mb][g][i], ps);
+          pd = fmaf(acc[i], al[1][mb][g][i], pd);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float v[4] = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+          store4<T>((T *)(x + l32 * S::SROW) + 32 * mb + 8 * q + 4 * g, v);
+        }
+      }
+      ps += __shfl_xor(ps, 32);                              // the row's other half of the features
+      pd += __shfl_xor(pd, 32);
+      if (g == 0 && row0 + l32 < a.n_rows) {
+        next.s_src[row0 + l32] = ps;
+        next.s_dst[row0 + l32] = pd;
+      }
+      wave_lds_fence();
+      constexpr int RPI = 64 / S::LPR;
+#pragma unroll
+      for (int i = 0; i < 32 / RPI; ++i) {
+        const int rr = i * RPI + lane / S::LPR, p = lane % S::LPR;
+        const f32x4 v = *(const f32x4 *)(x + rr * S::SROW + p * 16);
+        if (row0 + rr < a.n_rows) *(f32x4 *)((char *)((T *)next.z + (size_t)(row0 + rr) * H) + p * 16) = v;
+      }
+    }
+    turn = turn + 1 == S::NW ? 0 : turn + 1;
+    buf ^= 1;
   }
 }
 

@@ -1225,6 +1225,36 @@ int launch_gat_linear(xrl_ctx *c, GatArgs &a) {
   return fail(XRL_ERR_UNSUPPORTED, "hidden = %d", c->m.hidden);
 }
 
+// An attention round's aggregation with the product of the next round, where W fits LDS twice per compute unit and there
+// are few tiles per block: with more the barriers cost what the launches and the way of h through memory did
+// (the figures at gat_round_kernel).
+constexpr int64_t kGatRoundRows = 65536;
+template <typename T>
+bool gat_round_applies(const xrl_ctx *c, int64_t n) {
+  const int H = c->m.hidden;
+  return n <= kGatRoundRows && ((H == 64 && GatRound<T, 64>::FITS) || (H == 128 && GatRound<T, 128>::FITS));
+}
+template <typename T, int H>
+int launch_gat_round_h(xrl_ctx *c, const GatArgs &a, const GatNext &next) {
+  using S = GatRound<T, H>;
+  if constexpr (S::FITS) {
+    auto kern = gat_round_kernel<T, H>;
+    static bool attr_set = false;
+    if (!attr_set) {
+      HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, S::BYTES));
+      attr_set = true;
+    }
+    const int64_t want = ((a.n_rows + 31) / 32 + 7) / 8 * 8, cap = (int64_t)c->n_cu / 8 * 8 * S::PER_CU;
+    kern<<<dim3((unsigned)std::min(want, cap)), dim3(S::NT), S::BYTES, c->stream>>>(a, next);
+    HIP_TRY(hipGetLastError());
+  }
+  return XRL_OK;
+}
+template <typename T>
+int launch_gat_round(xrl_ctx *c, const GatArgs &a, const GatNext &next) {
+  return c->m.hidden == 64 ? launch_gat_round_h<T, 64>(c, a, next) : launch_gat_round_h<T, 128>(c, a, next);
+}
+
 RowMlpArgs rowmlp_args(xrl_ctx *c, const MlpRef &r, bool relu_last, const float *in1, int w1, const float *in2,
                        int w2, int64_t n_rows, float *out, float *const *act, int *dmax_out = nullptr) {
   RowMlpArgs a;
@@ -2563,8 +2593,8 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
       if (l > 0) { acc((size_t)lev(l).E * H * sizeof(T)); acc(ym_words(l) * 2); acc(ym_words(l) * 2); }
     }
   }
-  const int n_gs = gat ? (save ? R : 1) : 0;                            // saved per round for the backward
-  for (int i = 0; i < 2 * n_gs; ++i) acc(a_rows(i / 2) * 4);
+  const int n_gs = gat ? (save ? R : std::min(R, 2)) : 0;               // saved per round for the backward; or in turn
+  for (int i = 0; i < 2 * n_gs; ++i) acc((size_t)N * 4);
   // (a reduced batch has few huge graphs at most: the carries of the readout's segment sum are not needed)
   const size_t carry_floats = std::max(std::max(segsum_carry_floats(E, De), q && N <= 4096 * G ? 0 : segsum_carry_floats(N, H)),
                                        (size_t)max_tiles * 2 * H);
@@ -2586,8 +2616,8 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   c->gat_ss.assign(R, nullptr);
   c->gat_sd.assign(R, nullptr);
   for (int i = 0; i < n_gs; ++i) {
-    c->gat_ss[i] = bump.take<float>(a_rows(i));
-    c->gat_sd[i] = bump.take<float>(a_rows(i));
+    c->gat_ss[i] = bump.take<float>((size_t)N);
+    c->gat_sd[i] = bump.take<float>((size_t)N);
   }
   c->carry = bump.take<float>(carry_floats);
   c->pool = bump.take<float>((size_t)G * H);
@@ -2772,14 +2802,25 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
     }
     if (gat) {                         // graph-attention reading of the round
       if (N > 0) {
+        const bool fused = gat_round_applies<T>(c, N);
+        // (not saved, z of one round is read while that of the next is written: in turn in ab[0] and, once the first
+        // product has read h from there, hb[0])
+        if (!save && fused) { aggb = r % 2 ? hb[0] : ab[0]; hnext = hb[1]; }
         GatArgs ga;
         ga.n_rows = N;
         ga.h = hcur; ga.Ws = c->gatW[r];
         ga.a_src = c->d_w + c->L.gat[r].a_src; ga.a_dst = c->d_w + c->L.gat[r].a_dst;
-        ga.z = aggb; ga.s_src = c->gat_ss[save ? r : 0]; ga.s_dst = c->gat_sd[save ? r : 0];
+        ga.z = aggb; ga.s_src = c->gat_ss[save ? r : r % n_gs]; ga.s_dst = c->gat_sd[save ? r : r % n_gs];
         ga.in_ptr = d.in_ptr; ga.in_src = d.in_src; ga.out = hnext; ga.zero_row = c->zero_row;
-        { Timed t(c, TK_GAT_LINEAR); if ((rc = launch_gat_linear<T>(c, ga))) return rc; }
-        { Timed t(c, TK_GAT_AGGREGATE);
+        if (r == 0 || !fused) { Timed t(c, TK_GAT_LINEAR); if ((rc = launch_gat_linear<T>(c, ga))) return rc; }
+        if (fused && r + 1 < R) {
+          if (!save) ga.out = nullptr;
+          const GatNext next = {c->gatW[r + 1], c->d_w + c->L.gat[r + 1].a_src, c->d_w + c->L.gat[r + 1].a_dst,
+                                save ? ab[r + 1] : r % 2 ? ab[0] : hb[0], c->gat_ss[save ? r + 1 : (r + 1) % n_gs],
+                                c->gat_sd[save ? r + 1 : (r + 1) % n_gs]};
+          Timed t(c, TK_ROUND);
+          if ((rc = launch_gat_round<T>(c, ga, next))) return rc;
+        } else { Timed t(c, TK_GAT_AGGREGATE);
           const int64_t threads = N * (H / PV);
           gat_aggregate_kernel<T, PV><<<dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, c->stream>>>(ga, H); }
         HIP_TRY(hipGetLastError());
