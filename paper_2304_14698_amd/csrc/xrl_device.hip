@@ -157,6 +157,7 @@ constexpr int kCounts = 3 * kMaxLevels;
 constexpr int64_t kPersistentMinRows = 8192;   // rows from which the persistent kernels replace the split one
 constexpr size_t kZeroRow = 1024 + 256;        // 1 KB of zeros and behind it one element that is 1 (see WgradLaunch)
 constexpr size_t kGradRoom = (size_t)2 << 30;   // gradients kept for a launch of weight gradients (see encode_backward_impl)
+constexpr size_t kSliceBytes = (size_t)4 << 20;   // table rows are gathered from by column slices: an XCD's L2
 constexpr int kAvecChunks = 1024;              // most chunks of rows of an attention vector's gradient
 constexpr int64_t kClusterMaxGraphs = 256; // largest G of the one-launch encoder with several blocks per graph
 
@@ -2306,18 +2307,19 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   // the gradients of the rows `vals`, summed per class (fp32) and stored: masked, as the dz2 of the layer
   // that produced the classes' states, or as their dh
   auto contract = [&](auto tag, const void *vals, const int32_t *perm, const int32_t *ptr, const int32_t *seg, int64_t rows,
-                      const uint16_t *ymask, T *out) -> int {
+                      const uint16_t *ymask, T *out, size_t table_bytes) -> int {
     using TIn = decltype(tag);
     constexpr int VEC = 16 / sizeof(TIn);
     ClassSumArgs s;
     s.vals = vals; s.zero_row = c->zero_row; s.perm = perm; s.seg = seg; s.ptr = ptr; s.n_rows = rows; s.D = H;
     s.ymask = ymask; s.out = out; s.carry = ccarry;
     const int64_t blocks = ((rows + kSumRows - 1) / kSumRows * (H / VEC) + 255) / 256;   // of one step a group
+    s.slices = table_bytes >= kSliceBytes && H / VEC >= 64 ? 8 : 1;
     auto go = [&](auto steps) {
       constexpr int STEPS = decltype(steps)::value;
       s.group = STEPS * kSumRows;
       const int64_t groups = (rows + s.group - 1) / s.group;
-      class_sum_kernel<TIn, T, VEC, STEPS><<<dim3((unsigned)((groups * (H / VEC) + 255) / 256)), dim3(256), 0, c->stream>>>(s);
+      class_sum_kernel<TIn, T, VEC, STEPS><<<dim3((unsigned)((groups * (H / VEC / s.slices) + 255) / 256 * s.slices)), dim3(256), 0, c->stream>>>(s);
       class_sum_carried_kernel<T><<<dim3((unsigned)((groups + 4 * kCarryGroups - 1) / (4 * kCarryGroups))), dim3(256), 0, c->stream>>>(s);
     };
     // (the classes in several pieces, and their way to memory and back, against lanes to hide the gathers with: see class_sum_kernel)
@@ -2347,7 +2349,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
         rdx, H + Dg, nullptr, d.graph_node_ptr, m.readout == XRL_READOUT_MEAN, G, H, dpool_rows);
     const uint16_t *mask = kept ? c->ym_node[R - 1] : nullptr;
     dz2_given = mask != nullptr;
-    if ((rc = contract(float(), dpool_rows, q->mem_graph, q->mem_ptr, q->mem_seg, N, mask, mask ? node_grads.dz2 : dhA))) return rc;
+    if ((rc = contract(float(), dpool_rows, q->mem_graph, q->mem_ptr, q->mem_seg, N, mask, mask ? node_grads.dz2 : dhA, (size_t)G * H * 4))) return rc;
   } else if (N > 0) {
     if (dpool_table)
       broadcast_dpool_kernel<T><<<dim3((unsigned)((G * (H / 4) + 255) / 256)), dim3(256), 0, c->stream>>>(
@@ -2472,7 +2474,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
     if (q) {
       // ... of all the classes that split one of the level below, masked as below
       dz2_given = below != nullptr;
-      if ((rc = contract(T(), dsrc, g.down, g.down_ptr, g.down_seg, level_rows(g, fold), below, below ? node_grads.dz2 : dhA))) return rc;
+      if ((rc = contract(T(), dsrc, g.down, g.down_ptr, g.down_seg, level_rows(g, fold), below, below ? node_grads.dz2 : dhA, 0))) return rc;
       continue;
     }
     if (E > 0) {
