@@ -35,22 +35,22 @@ TRAFFIC = {
                               bytes_per_launch=(15506.5 * 2.000 + 18218.2 * 1.000) * 1024),
     # configuration 4 (profiles/forward_config4_bf16_kernel_stats_and_traffic.md): register-stationary forward kernels on the
     # levels of the reduced batch, mean over the rounds (so the sources that decide the levels belong to it)
-    (4, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="3bb452e62f39d7b5",
-                              bytes_per_launch=(30502.9 * 2.000 + 40853.2 * 1.000) * 1024),
-    (4, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="3bb452e62f39d7b5",
-                              bytes_per_launch=(42850.6 * 2.000 + 41315.2 * 1.000) * 1024),
+    (4, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="ddae8ab14a588c4f",
+                              bytes_per_launch=(20801.6 * 2.000 + 25991.7 * 1.000) * 1024),
+    (4, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="ddae8ab14a588c4f",
+                              bytes_per_launch=(27930.8 * 2.000 + 26453.7 * 1.000) * 1024),
     # configuration 5 (profiles/step_config5_bf16_hbm_traffic.md): the same, saving, and the backward kernels
-    (5, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="3bb452e62f39d7b5",
-                              bytes_per_launch=(232500.8 * 2.000 + 1057668.6 * 1.000) * 1024),
-    (5, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="3bb452e62f39d7b5",
-                              bytes_per_launch=(311876.4 * 2.000 + 660799.0 * 1.000) * 1024),
-    (5, "bf16", "bwd_edge"): dict(sources=("mma.hip.h", "mlp2_bwd.hip.h", "mlp2_bwdz.hip.h", "distinct.hip.h"), sha256_16="c51c0a56d1d9859b",
-                                  bytes_per_launch=(232938.1 * 2.000 + 2312605.5 * 1.000) * 1024),
-    (5, "bf16", "bwd_node"): dict(sources=("mma.hip.h", "mlp2_bwd.hip.h", "mlp2_bwdz.hip.h", "distinct.hip.h"), sha256_16="c51c0a56d1d9859b",
-                                  bytes_per_launch=(181935.1 * 2.000 + 929704.4 * 1.000) * 1024),
+    (5, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="ddae8ab14a588c4f",
+                              bytes_per_launch=(58002.1 * 2.000 + 248146.9 * 1.000) * 1024),
+    (5, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="ddae8ab14a588c4f",
+                              bytes_per_launch=(81358.3 * 2.000 + 172861.0 * 1.000) * 1024),
+    (5, "bf16", "bwd_edge"): dict(sources=("mma.hip.h", "mlp2_bwd.hip.h", "mlp2_bwdz.hip.h", "distinct.hip.h"), sha256_16="84af4a3f66b6b945",
+                                  bytes_per_launch=(57287.1 * 2.000 + 533482.5 * 1.000) * 1024),
+    (5, "bf16", "bwd_node"): dict(sources=("mma.hip.h", "mlp2_bwd.hip.h", "mlp2_bwdz.hip.h", "distinct.hip.h"), sha256_16="84af4a3f66b6b945",
+                                  bytes_per_launch=(47993.2 * 2.000 + 240269.3 * 1.000) * 1024),
     # (the products of a launch and the sums of its slices)
-    (5, "bf16", "wgrad"): dict(sources=("mma.hip.h", "wgrad.hip.h", "distinct.hip.h"), sha256_16="f30a7945cbba1e01",
-                               bytes_per_launch=((4072263.4 + 26884.2) * 2.000 + (67306.7 + 2010.5) * 1.000) * 1024),
+    (5, "bf16", "wgrad"): dict(sources=("mma.hip.h", "wgrad.hip.h", "distinct.hip.h"), sha256_16="df3223d22aca227c",
+                               bytes_per_launch=((1454902.7 + 25409.8) * 2.000 + (67488.0 + 2680.7) * 1.000) * 1024),
 }
 
 
