@@ -378,7 +378,8 @@ int xrl_mlp_backward(xrl_ctx *ctx, const xrl_batch *b, int32_t kind, int32_t rou
  * recorded since the last read for `kernel` and forgets them. Forward: {"embed", "edge",
  * "edge_fixup", "node", "pool", "readout", "heads"} (the steps of Section 3.4 / 3.3.2 in
  * execution order; "gat_linear", "gat_aggregate" with XRL_ROUND_GAT; "round" = a whole round of a small
- * batch in one launch, "resident" = its whole encoder). Backward (Section 3.3.4):
+ * batch in one launch, "resident" = its whole encoder; "levels" = the making of the levels of a batch that is
+ * reduced for one encode, R + 2 of them). Backward (Section 3.3.4):
  * {"bwd_edge", "bwd_node", "bwd_embed"} = gradients through the fused MLPs, "wgrad" = the weight
  * gradients of as many MLPs as one launch takes, with their reductions (a single product through
  * xrl_weight_gradient; {"wgrad_edge", "wgrad_node", "wgrad_embed"}: accepted, no launch is only

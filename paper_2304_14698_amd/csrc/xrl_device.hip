@@ -146,11 +146,11 @@ __global__ __launch_bounds__(256) void arrange_weights_kernel(const SwzJob *jobs
 // share launches, are names that may still be read: no launch is only theirs)
 enum { TK_EMBED = 0, TK_EDGE, TK_EDGE_FIXUP, TK_NODE, TK_POOL, TK_READOUT, TK_HEADS, TK_GAT_LINEAR,
        TK_GAT_AGGREGATE, TK_BWD_EDGE, TK_BWD_NODE, TK_BWD_EMBED, TK_WGRAD, TK_GRAD_GATHER, TK_GAT_BWD, TK_RESIDENT,
-       TK_WGRAD_EDGE, TK_WGRAD_NODE, TK_WGRAD_EMBED, TK_ROUND, TK_COUNT };
+       TK_WGRAD_EDGE, TK_WGRAD_NODE, TK_WGRAD_EMBED, TK_ROUND, TK_LEVELS, TK_COUNT };
 static const char *const kTimedNames[TK_COUNT] = {"embed", "edge", "edge_fixup", "node", "pool", "readout",
                                                   "heads", "gat_linear", "gat_aggregate", "bwd_edge", "bwd_node",
                                                   "bwd_embed", "wgrad", "grad_gather", "gat_bwd", "resident",
-                                                  "wgrad_edge", "wgrad_node", "wgrad_embed", "round"};
+                                                  "wgrad_edge", "wgrad_node", "wgrad_embed", "round", "levels"};
 
 constexpr int64_t kMaxFusedSlots = 4096;   // largest G the single-launch heads kernel takes
 constexpr int kCounts = 3 * kMaxLevels;
@@ -2757,18 +2757,21 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   if constexpr (sizeof(T) == 2) {
     bool by_levels = !save && !q && once_pays(c, b);
     if (by_levels) {
+      Timed t(c, TK_LEVELS);
       rc = once_begin(c, b, once);
       if (rc && rc != XRL_ERR_OOM) return rc;
       by_levels = rc == XRL_OK;        // (no memory for it: the batch is encoded as it is)
     }
     if (by_levels) {
-      if ((rc = once_level(c, b, once, 0, a))) return rc;
+      { Timed t(c, TK_LEVELS); rc = once_level(c, b, once, 0, a); }
+      if (rc) return rc;
       { Timed t(c, TK_EMBED); rc = launch_embedp_s<256, false, true>(c, a); }
       if (rc) return rc;
       T *hcur = hb[0];
       for (int r = 0; r < R; ++r) {
         T *hnext = hb[(r + 1) & 1];
-        if ((rc = once_level(c, b, once, r + 1, a))) return rc;
+        { Timed t(c, TK_LEVELS); rc = once_level(c, b, once, r + 1, a); }
+        if (rc) return rc;
         set_w(c->edge[r]);
         a.n_rows = E; a.h = hcur; a.out = ab[0]; a.h_row = once.o.o_hrow;
         { Timed t(c, TK_EDGE); rc = launch_mlp2r_ks<256, KIND_EDGE, false, true>(c, a); }

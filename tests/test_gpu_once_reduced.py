@@ -15,11 +15,14 @@ def _embeddings(model, w, pack, min_us, monkeypatch):
     monkeypatch.setenv("XRL_DISTINCT_MIN_US", min_us)
     monkeypatch.setenv("XRL_PERSISTENT_MIN_ROWS", "0")
     enc = xrl.Encoder(model, w)
+    enc.set_timing(True)
     got = []
     for _ in range(3):                       # (batches in turn: the levels' memory is used again)
         for state, edits in pack:
             batch = enc.pack_edits(state) if edits else enc.pack(state)
             got.append(enc.encode(batch).cpu().numpy())
+            # (the memory made ready, then the level of the node-update layer and one a round)
+            assert enc.read_timing("levels")[1] == (0 if min_us == "-1" else model["rounds"] + 2)
             batch.free()
     enc.close()
     return got
