@@ -1841,7 +1841,41 @@ bool distinct_pays(const xrl_ctx *c, xrl_batch *b, bool save) {
   return false;
 }
 
-// The same for one forward-only encode (see OnceArgs): no wait and nothing kept, so it pays for the classes alone.
+// Whether nodes that stand at the same place of a graph and of its state's first are alike in all that level 0 goes by: five
+// of eight, of the first and last sixteen places of eight graphs as far as the operators are the same (a rewrite moves what is behind
+// it; sixteen graphs and 32 places took 18 us of host time, these 3). Rewrites 0.76 to 0.97 (what is missing are nodes of three and more
+// in-edges, listed in another order); noise on every edge's attributes 0.41 to 0.60, a dense attribute changed at every third node 0.29 to
+// 0.48, at every tenth 0.63 to 0.79. Encodes of 91 k nodes, H = 256, us, whole / by levels, in this order: 519 / 324, 527 / 681, 531 / 688, 537 / 537.
+bool attributes_alike(const xrl_ctx *c, const xrl_batch *b) {
+  if (b->from_edits || c->distinct_min_us == 0) return true;
+  const int32_t *sgp = b->at<int32_t>(b->o_state_graph_ptr), *gnp = b->at<int32_t>(b->o_graph_node_ptr), *op = b->at<int32_t>(b->o_node_op);
+  const int32_t *in_ptr = b->at<int32_t>(b->o_in_ptr);
+  const float *dense = b->at<float>(b->o_node_dense), *feat = b->at<float>(b->o_edge_feat);
+  const size_t De = c->m.d_edge, Dd = c->m.n_node_dense;
+  auto same_edges = [&](int64_t x, int64_t y, int64_t n) { return memcmp(feat + x * De, feat + y * De, n * De * sizeof(float)) == 0; };
+  auto alike = [&](int64_t u, int64_t v) {
+    const int64_t e = in_ptr[u], f = in_ptr[v], d = in_ptr[u + 1] - e;
+    if (in_ptr[v + 1] - f != d || memcmp(dense + u * Dd, dense + v * Dd, Dd * sizeof(float)) != 0) return false;
+    return same_edges(e, f, d) || (d >= 2 && same_edges(e, f + 1, 1) && same_edges(e + 1, f, 1) && same_edges(e + 2, f + 2, d - 2));
+  };
+  constexpr int kGraphs = 8, kPlaces = 16;
+  int64_t same = 0, seen = 0, s = 0;
+  for (int k = 0; k < kGraphs; ++k) {
+    int64_t g = k * b->G / kGraphs;
+    while (sgp[s + 1] <= g) ++s;
+    const int64_t f = sgp[s];
+    if (g == f && ++g == sgp[s + 1]) continue;
+    const int n = std::min(kPlaces, std::min(gnp[g + 1] - gnp[g], gnp[f + 1] - gnp[f]));
+    auto walk = [&](int64_t u, int64_t v, int step) {
+      for (int i = 0; i < n && op[u] == op[v]; ++i, u += step, v += step) { ++seen; same += alike(u, v); }
+    };
+    if (n > 0) { walk(gnp[g], gnp[f], 1); walk(gnp[g + 1] - 1, gnp[f + 1] - 1, -1); }
+  }
+  return seen > 0 && 8 * same >= 5 * seen;
+}
+
+// The same for one forward-only encode (see OnceArgs): no wait and nothing kept, so it pays for the classes alone. There is no way
+// out once it has begun, so a batch known to have too many distinct nodes is left whole, and the sample goes by the attributes too.
 // us of an encode as it is / by levels, H = 256, by the estimate: one inception-shaped state 110 us 210 / 337, 217 289 / 368,
 // 417 444 / 454, 828 736 / 563; a transformer-shaped one 216 288 / 289, 429 439 / 309, 715 632 / 332; states of residual networks
 // 505 508 / 353, 2008 1800 / 587. At H <= 128 a round costs a third of that and finding its level as much; in fp32 the
@@ -1850,7 +1884,7 @@ constexpr int kOnceMinUs = 430;
 bool once_pays(const xrl_ctx *c, const xrl_batch *b) {
   const xrl_model_desc &m = c->m;
   if (c->elem != 2 || m.hidden != 256 || c->distinct_min_us < 0 || c->captured || m.round_kind != XRL_ROUND_MLP || m.rounds < 1 ||
-      m.rounds + 1 > kMaxLevels || b->G <= b->S || b->n_split_tiles > 0 || b->E < 1 || std::max(b->N, b->E) > kOnceMax)
+      m.rounds + 1 > kMaxLevels || b->G <= b->S || b->n_split_tiles > 0 || b->E < 1 || std::max(b->N, b->E) > kOnceMax || b->few_alike)
     return false;
   Mlp2Args t;
   memset(&t, 0, sizeof(t));
@@ -1861,7 +1895,7 @@ bool once_pays(const xrl_ctx *c, const xrl_batch *b) {
     t.nslab1 = c->edge[r].nslab1;
     if (!mlp2r_applies(c, KIND_EDGE, t)) return false;
   }
-  return (c->distinct_min_us == 0 || encode_estimate_us(c, b) >= kOnceMinUs) && looks_like_rewrites(c, b);
+  return (c->distinct_min_us == 0 || encode_estimate_us(c, b) >= kOnceMinUs) && looks_like_rewrites(c, b) && attributes_alike(c, b);
 }
 struct OnceLevels {
   OnceArgs o;
@@ -2004,7 +2038,11 @@ int find_distinct(xrl_ctx *c, xrl_batch *b) {
   // (the sort that makes the groupings counts the items of all levels in 32 bits)
   if (items > INT32_MAX - kSortItems) { drop(); return XRL_OK; }
   // (a level costs a copy of its states more, so a quarter of the edges has to go)
-  if (4 * (sumE + sumN) > 3 * R * (E + N) && c->distinct_min_us != 0) { drop(); return XRL_OK; }
+  if (4 * (sumE + sumN) > 3 * R * (E + N) && c->distinct_min_us != 0) {
+    b->few_alike = true;
+    drop();
+    return XRL_OK;
+  }
   // ---- the levels' graphs
   size_t off = 0;
   auto plan = [&](size_t bytes) { const size_t o = off; off += align_up(bytes + 16); return o; };
@@ -3186,6 +3224,7 @@ int xrl_batch_upload(xrl_ctx *c, xrl_batch *b) {
   d.agg_src = (int32_t *)(blk + o_as);
   b->encodes = 0;
   b->forgone_us = 0;
+  b->few_alike = false;
   b->out_maker = 0;
   b->uploaded = true;
   return XRL_OK;

@@ -135,6 +135,7 @@ struct xrl_batch {
   std::shared_ptr<Distinct> distinct;      // used by the owner only
   int encodes = 0;                         // the owner's calls of xrl_encode, until the batch is looked at for it
   double forgone_us = 0;                   // what they would have taken less, by an estimate, had it been reduced before
+  std::atomic<bool> few_alike{false};      // its distinct nodes have been counted: too many of them
   std::atomic<bool> shared{false};
   uint64_t id = 0;  // unique per packed batch; ties saved activations to their batch
   xrl_batch() = default;

@@ -61,3 +61,70 @@ def test_a_kept_batch_is_reduced_after_some_encodes(save):
     assert np.array_equal(enc.encode(batch).cpu().numpy(), first)
     batch.free()
     enc.close()
+
+
+def _large_state(rng, model, kind):
+    """A state of transformer-shaped graphs, large enough for the default threshold: rewrites of the first; the same with noise on
+    every edge's attributes; with a dense attribute of every third node changed."""
+    state = synth.concat_states([synth.make_state(rng, synth.transformer_dag(rng, 12), 150, by_block=True)])
+    if kind == "edges":
+        state["edge_feat"] = (state["edge_feat"] + rng.standard_normal(state["edge_feat"].shape) / 64).astype(np.float32)
+    elif kind == "nodes":
+        dense = state["node_dense"].copy()
+        some = rng.random(len(dense)) < 1 / 3
+        dense[some, 0] += rng.standard_normal(int(some.sum())).astype(np.float32)
+        state["node_dense"] = dense
+    us = 2 * model["rounds"] * 256 * (len(state["node_op"]) * 768 + len(state["edge_src"]) * 776) / 7e8
+    assert us > 430
+    return state
+
+
+@pytest.mark.parametrize("kind", ["rewrites", "edges", "nodes"])
+def test_a_batch_of_distinct_nodes_is_left_whole(kind):
+    """Default threshold: graphs alike in their operators alone have nothing to gain from levels, neither when they are encoded
+    once, nor in any encode after their distinct nodes have been counted (by the second encode), by any context."""
+    rng = np.random.Generator(np.random.PCG64(13))
+    model, _ = synth.make_config(1)
+    model.update(hidden=256, precision="bf16", rounds=5)
+    state = _large_state(rng, model, kind)
+    w = synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1)
+    enc, other = xrl.Encoder(model, w), xrl.Encoder(model, w)
+    batch = enc.pack(state)
+    levels = []
+    for e in (enc, enc, enc, other):
+        e.set_timing(True)
+        emb = e.encode(batch).cpu().numpy()
+        levels.append(e.read_timing("levels")[1])
+        if len(levels) == 1:
+            first = emb
+        assert np.array_equal(emb, first)
+    # (rewrites: by levels once, then reduced for good; the other context goes by levels)
+    assert levels == ([7, 0, 0, 7] if kind == "rewrites" else [0, 0, 0, 0])
+    assert (enc.batch_level(batch, 5)[0] < batch.N) == (kind == "rewrites")
+    batch.free()
+    enc.close()
+    other.close()
+
+
+def test_counted_and_left_whole():
+    """A batch that passes for rewrites by its sample (first and last nodes alike) and is not: the first encode goes by levels, the
+    second counts its distinct nodes, later ones take it whole."""
+    rng = np.random.Generator(np.random.PCG64(14))
+    model, _ = synth.make_config(1)
+    model.update(hidden=256, precision="bf16", rounds=5)
+    state = _large_state(rng, model, "rewrites")
+    dense, gnp = state["node_dense"].copy(), state["graph_node_ptr"]
+    for a, b in zip(gnp[:-1], gnp[1:]):
+        dense[a + 32:b - 32, 0] += rng.standard_normal(b - a - 64).astype(np.float32)
+    state["node_dense"] = dense
+    enc = xrl.Encoder(model, synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1))
+    batch = enc.pack(state)
+    levels, embs = [], []
+    for _ in range(4):
+        enc.set_timing(True)
+        embs.append(enc.encode(batch).cpu().numpy())
+        levels.append(enc.read_timing("levels")[1])
+    assert levels == [7, 0, 0, 0] and enc.batch_level(batch, 5)[0] == batch.N
+    assert all(np.array_equal(e, embs[0]) for e in embs)
+    batch.free()
+    enc.close()
