@@ -250,7 +250,8 @@ int xrl_batch_upload(xrl_ctx *ctx, xrl_batch *b);
  * than 32 in-edges) is reduced to its distinct nodes by the context that uploaded it when it is
  * first saved for the backward pass, or encoded a second time (a smaller one: several times): that one call waits for the stream
  * twice, later calls compute every round once per distinct node. In bf16 at hidden = 256 the first forward-only
- * encode of a large batch of rewrites is reduced too, on the device and for that call alone, without a wait. (A context on which calls have been
+ * encode of a large batch of rewrites is reduced too, on the device and for that call alone; like any encode it waits only
+ * when the context's workspace has to grow. (A context on which calls have been
  * captured reduces no further batches: a graph keeps the addresses of the context's buffers, which
  * grow with the batches it is given, and only then.) States and embeddings are
  * the same bits; gradients are summed in another, equally fixed order.

@@ -233,6 +233,7 @@ struct xrl_ctx {
   char *bws = nullptr;          // backward scratch
   size_t bws_bytes = 0;
   bool room_refused = false;    // (see fit_room)
+  size_t levels_refused = SIZE_MAX;   // least size of ws with levels in it that there was no memory for
   // buffers of the last encode (inside ws)
   uint64_t id = 0;              // unique per context
   int32_t *d_counts = nullptr;  // class and tile counts of the levels of a batch, and their copy in pinned memory
@@ -1904,44 +1905,44 @@ struct OnceLevels {
   unsigned blocks_per_graph;
   const int32_t *classes(int l) const { return cls[l & 1]; }
 };
-int once_begin(xrl_ctx *c, const xrl_batch *b, OnceLevels &q) {
+// Lays the levels' memory out at base and returns its size.
+size_t once_plan(const xrl_ctx *c, const xrl_batch *b, char *base, OnceLevels &q) {
   const int64_t N = b->N, E = b->E;
   const int De = c->m.d_edge, Dd = c->m.n_node_dense;
-  const xrl_batch_device &d = b->dev;
+  memset(&q, 0, sizeof(q));
   uint32_t slots = 1024;
   while (slots < (uint64_t)N + N / 2) slots *= 2;
   const int64_t max_tiles = 2 * E / 33 + 2 * ((N + kOnceNodes - 1) / kOnceNodes) + 2;
-  auto plan = [&](char *base) -> size_t {
-    Bump m{base};
-    ClassArgs &a = q.o.k;
-    a.table = m.take<unsigned long long>(slots);
-    q.counts = m.take<unsigned long long>(kMaxLevels);
-    q.o.num = m.take<int32_t>(slots);
-    a.swapped = m.take<uint8_t>((size_t)N);
-    a.slot = m.take<int32_t>((size_t)N);
-    for (int i = 0; i < 2; ++i) q.cls[i] = m.take<int32_t>((size_t)N);
-    q.o.o_ptr = m.take<int32_t>((size_t)N + 1);
-    q.o.o_agg_src = m.take<int32_t>((size_t)N);
-    q.o.o_self = m.take<int32_t>((size_t)N);
-    q.o.o_op = m.take<int32_t>((size_t)N);
-    q.o.o_src = m.take<int32_t>((size_t)E);
-    q.o.o_dst = m.take<int32_t>((size_t)E);
-    q.o.o_hrow = m.take<int32_t>((size_t)E);
-    q.o.o_tile = m.take<int32_t>((size_t)max_tiles);
-    q.o.o_feat = m.take<float>((size_t)E * De);
-    q.o.o_dense = m.take<float>((size_t)N * Dd);
-    return m.off;
-  };
-  memset(&q, 0, sizeof(q));
-  RelaxedCapture relaxed;               // (as in find_distinct)
-  if (int rc = ensure_bws(c, plan(nullptr))) return rc;
-  plan(c->bws);
+  Bump m{base};
+  ClassArgs &a = q.o.k;
+  a.mask = slots - 1;
+  a.table = m.take<unsigned long long>(slots);
+  q.counts = m.take<unsigned long long>(kMaxLevels);
+  q.o.num = m.take<int32_t>(slots);
+  a.swapped = m.take<uint8_t>((size_t)N);
+  a.slot = m.take<int32_t>((size_t)N);
+  for (int i = 0; i < 2; ++i) q.cls[i] = m.take<int32_t>((size_t)N);
+  q.o.o_ptr = m.take<int32_t>((size_t)N + 1);
+  q.o.o_agg_src = m.take<int32_t>((size_t)N);
+  q.o.o_self = m.take<int32_t>((size_t)N);
+  q.o.o_op = m.take<int32_t>((size_t)N);
+  q.o.o_src = m.take<int32_t>((size_t)E);
+  q.o.o_dst = m.take<int32_t>((size_t)E);
+  q.o.o_hrow = m.take<int32_t>((size_t)E);
+  q.o.o_tile = m.take<int32_t>((size_t)max_tiles);
+  q.o.o_feat = m.take<float>((size_t)E * De);
+  q.o.o_dense = m.take<float>((size_t)N * Dd);
+  return m.off;
+}
+int once_begin(xrl_ctx *c, const xrl_batch *b, OnceLevels &q) {
+  const int64_t N = b->N;
+  const xrl_batch_device &d = b->dev;
   ClassArgs &a = q.o.k;
   a.N = N; a.in_ptr = d.in_ptr; a.in_src = d.in_src; a.node_op = d.node_op;
-  a.edge_feat = (const uint32_t *)d.edge_feat; a.node_dense = (const uint32_t *)d.node_dense; a.De = De; a.Dd = Dd;
-  a.mask = slots - 1; a.state_graph_ptr = d.state_graph_ptr; a.graph_node_ptr = d.graph_node_ptr;
+  a.edge_feat = (const uint32_t *)d.edge_feat; a.node_dense = (const uint32_t *)d.node_dense; a.De = c->m.d_edge; a.Dd = c->m.n_node_dense;
+  a.state_graph_ptr = d.state_graph_ptr; a.graph_node_ptr = d.graph_node_ptr;
   q.blocks_per_graph = (unsigned)std::max<int64_t>(1, (b->max_graph_nodes + 255) / 256);
-  once_clear_kernel<<<dim3((slots + 255) / 256), dim3(256), 0, c->stream>>>(a.table, slots, q.counts);
+  once_clear_kernel<<<dim3(a.mask / 256 + 1), dim3(256), 0, c->stream>>>(a.table, a.mask + 1, q.counts);
   first_two_kernel<<<dim3((unsigned)((N + 255) / 256)), dim3(256), 0, c->stream>>>(a, (uint8_t *)a.swapped);
   HIP_TRY(hipGetLastError());
   return XRL_OK;
@@ -2642,8 +2643,23 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   acc((size_t)G * H * 4);
   acc((size_t)G * H * 4);
   acc((size_t)G * H * 4);
-  int rc = ensure_ws(c, need);
-  if (rc) return rc;
+  // (the levels of a batch reduced for this encode lie behind the rest, so that there is one allocation and wait at most: a context's
+  // first call, 287 k nodes at H = 256, held its caller 846 us with a second one, 557 so. RelaxedCapture: an encode that neither
+  // allocated nor waited before must not end another stream's capture)
+  OnceLevels once;
+  bool by_levels = false;
+  int rc = XRL_OK;
+  const size_t o_levels = need;
+  if constexpr (sizeof(T) == 2) by_levels = !save && !q && once_pays(c, b);
+  if (by_levels) {
+    RelaxedCapture relaxed;
+    const size_t bytes = o_levels + once_plan(c, b, nullptr, once);
+    rc = bytes < c->levels_refused ? ensure_ws(c, bytes) : XRL_ERR_OOM;
+    if (rc && rc != XRL_ERR_OOM) return rc;
+    by_levels = rc == XRL_OK;          // (no memory for them: the batch is encoded as it is, and as much is not asked for again)
+    if (!by_levels) c->levels_refused = std::min(c->levels_refused, bytes);
+  }
+  if (!by_levels && (rc = ensure_ws(c, need))) return rc;
   Bump bump{c->ws};
   c->h.assign(R + 1, nullptr);
   c->agg.assign(R + 1, nullptr);
@@ -2791,16 +2807,11 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   // zeros for nodes without in-edges through agg_src, so nobody has to write those rows
   a.n_agg = 0; a.agg_src = lev(0).agg_src;
   c->agg_skip = !gat;
-  OnceLevels once;
   if constexpr (sizeof(T) == 2) {
-    bool by_levels = !save && !q && once_pays(c, b);
     if (by_levels) {
-      Timed t(c, TK_LEVELS);
-      rc = once_begin(c, b, once);
-      if (rc && rc != XRL_ERR_OOM) return rc;
-      by_levels = rc == XRL_OK;        // (no memory for it: the batch is encoded as it is)
-    }
-    if (by_levels) {
+      once_plan(c, b, c->ws + o_levels, once);
+      { Timed t(c, TK_LEVELS); rc = once_begin(c, b, once); }
+      if (rc) return rc;
       { Timed t(c, TK_LEVELS); rc = once_level(c, b, once, 0, a); }
       if (rc) return rc;
       { Timed t(c, TK_EMBED); rc = launch_embedp_s<256, false, true>(c, a); }

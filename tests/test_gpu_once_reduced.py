@@ -128,3 +128,34 @@ def test_counted_and_left_whole():
     assert all(np.array_equal(e, embs[0]) for e in embs)
     batch.free()
     enc.close()
+
+
+def test_levels_need_no_workspace_of_their_own():
+    """An encode by levels on a context whose encode workspace is large enough queues its work and returns: its levels lie there
+    too, so nothing is allocated, which would wait for the stream."""
+    import time
+    rng = np.random.Generator(np.random.PCG64(15))
+    model, _ = synth.make_config(1)
+    model.update(hidden=256, precision="bf16", rounds=5)
+    state = _large_state(rng, model, "rewrites")
+    lone = synth.concat_states([([synth.layered_dag(rng, 120000)], np.ones(1, np.uint8))])   # (no rewrites of it: not reduced)
+    enc = xrl.Encoder(model, synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1))
+    enc.encode(enc.pack(lone), save_for_backward=True)       # (saves more than the encode below takes)
+    out = torch.empty((len(state["slot_mask"]), 256), device="cuda")
+    held = []
+    for _ in range(3):
+        batch = enc.pack(state)
+        torch.cuda.synchronize()
+        enc.set_timing(True)
+        torch.cuda._sleep(200_000_000)                          # about a tenth of a second
+        t0 = time.perf_counter()
+        enc.encode(batch, out=out)
+        held.append(time.perf_counter() - t0)
+        done = torch.cuda.Event()
+        done.record()
+        assert not done.query(), "the queue was not held long enough to tell"
+        torch.cuda.synchronize()
+        assert enc.read_timing("levels")[1] == 7
+        batch.free()
+    assert max(held) < 0.02, held
+    enc.close()
