@@ -1820,11 +1820,16 @@ bool looks_like_rewrites(const xrl_ctx *c, const xrl_batch *b) {
 // 1912 / 1721, 216 us 3115 / 3874, 430 us 5380 / 3779; fp32 200 us 2265 / 2587. A batch kept over
 // the steps pays once: 430 us 622 / 337 forward only.
 // A smaller batch, from a tenth of that estimate on (fp32: a quarter), pays over several encodes: it is reduced once as much has
-// been spent for want of it (three times the estimate for a step that is differentiated, 0.8 for another) as it takes, so
-// no number of encodes costs more than twice what the better choice would. Kept batches, us per step whole / reduced:
-// update bf16 H = 128, 38 us 672 / 590, 124 us 1105 / 608, H = 256, 150 us 1339 / 1014, H = 64, 31 us 674 / 439, fp32, 95 us
-// 715 / 466; forward only 238 / 194, 324 / 199, 518 / 410, 179 / 128, 207 / 163; below: H = 256, 26 us 735 / 975, fp32, 65 us 588 / 585.
+// been spent for want of it (three times the estimate for a step that is differentiated, 0.8 for another) as it takes. But
+// not one of less than kReduceNodes, up to two thirds of that estimate: its launches are a tile or less per compute unit, and
+// few tiles take as long as that. Kept batches, us per step whole / reduced, residual networks' and transformers' states:
+// update bf16 H = 128, 31 us 637 / 579, 46 us 718 / 584, 67 us 817 / 598; H = 64, 31 us 667 / 452, 67 us 1110 / 465; H = 256, 8.8 k nodes 51 us
+// 1054 / 991, 82 us 1156 / 1006, 154 us 1373 / 1015 (but 7.1 k nodes 809 / 994); fp32 H = 64, 77 us 652 / 440; H = 128, 8.8 k nodes 128 us
+// 831 / 599 (7.1 k 646 / 597); H = 256, 196 us 1531 / 1441 (119 us 1441 / 1439); forward only in the same order 213 / 189, 245 / 189, 259 / 192; 170 / 127,
+// 232 / 137; 448 / 419, 464 / 429, 528 / 432 (418 / 431); 186 / 151; 256 / 225 (215 / 225); 623 / 630 (619 / 632). An inception-shaped state, 64 to 75 % of
+// whose edges are left, least: bf16 H = 128, 26 us 608 / 613, 210 / 201; H = 256, 60 us 1087 / 1062, 452 / 439.
 constexpr double kReduceUs = 450;
+constexpr int64_t kReduceNodes = 8192;
 bool distinct_pays(const xrl_ctx *c, xrl_batch *b, bool save) {
   const int R = c->m.rounds;
   if (c->distinct_min_us < 0 || c->captured || c->m.round_kind != XRL_ROUND_MLP || R < 1 || R + 1 > kMaxLevels || b->G <= b->S || b->N < 1 || b->E < 1 || b->n_split_tiles > 0 ||
@@ -1832,7 +1837,7 @@ bool distinct_pays(const xrl_ctx *c, xrl_batch *b, bool save) {
     return false;
   const double us = encode_estimate_us(c, b), min_us = (double)c->distinct_min_us;
   if (us >= min_us) return (save || b->encodes > 0) && looks_like_rewrites(c, b);
-  if (us < min_us / (c->elem == 2 ? 10 : 4)) return false;
+  if (us < min_us / (c->elem == 2 ? 10 : 4) || (b->N < kReduceNodes && us < min_us * 2 / 3)) return false;
   if (b->forgone_us < kReduceUs) {
     b->forgone_us += us * (save ? 3.0 : 0.8);
     return false;

@@ -159,3 +159,25 @@ def test_levels_need_no_workspace_of_their_own():
         batch.free()
     assert max(held) < 0.02, held
     enc.close()
+
+
+@pytest.mark.parametrize("hidden,precision,n_cand,reduced", [
+    (256, "bf16", 20, False), (256, "bf16", 30, True), (128, "fp32", 20, False), (128, "fp32", 26, True),
+    (256, "fp32", 5, False), (256, "fp32", 12, True)])
+def test_a_small_kept_batch_is_left_whole(hidden, precision, n_cand, reduced):
+    """A kept batch that fills no pass of the chip gains nothing from being reduced, however often it is encoded: below 8192 nodes, up to
+    two thirds of the estimate from which a batch is reduced at once."""
+    rng = np.random.Generator(np.random.PCG64(16))
+    model, _ = synth.make_config(1)
+    model.update(hidden=hidden, precision=precision, rounds=5)
+    state = synth.concat_states([synth.make_state(rng, synth.resnet_dag(rng, 16), n_cand, by_block=True)])
+    enc = xrl.Encoder(model, synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1))
+    batch = enc.pack(state)
+    us = 10 * hidden * (batch.N * 3 * hidden + batch.E * (3 * hidden + 8)) / (7e8 if precision == "bf16" else 7e7)
+    assert (30 if precision == "bf16" else 75) < us < 300       # (a smaller kept batch, by its estimate)
+    assert reduced == (batch.N >= 8192 or us >= 200)
+    for _ in range(40):
+        enc.encode(batch, save_for_backward=True)
+    assert (enc.batch_level(batch, 0)[0] < batch.N) == reduced
+    batch.free()
+    enc.close()
