@@ -230,8 +230,9 @@ int xrl_batch_free(xrl_batch *b);   /* frees host and device copies; NULL is acc
  * finishes with invalid embeddings, and the next xrl_encode on the context returns XRL_ERR_HIP
  * (once), after which the context works again;
  * XRL_DISTINCT_MIN_US = smallest batch, as the estimated time of its encode in microseconds, that
- * is reduced to its distinct nodes (default 300; 0 = every batch that can be; -1 = none; see
- * xrl_encode). */
+ * is reduced to its distinct nodes when it is first saved or encoded again (default 300; 0 = every batch that can be;
+ * -1 = none); a batch that is kept is reduced after several encodes from a tenth of that on (fp32: a quarter; of less
+ * than 8192 nodes: two thirds), one that is encoded once from 430 on, or from that if it is more; see xrl_encode. */
 int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip_stream,
                xrl_ctx **out);
 int xrl_set_weights(xrl_ctx *ctx, const float *weights_host);

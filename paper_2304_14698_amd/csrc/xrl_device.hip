@@ -1901,7 +1901,7 @@ bool once_pays(const xrl_ctx *c, const xrl_batch *b) {
     t.nslab1 = c->edge[r].nslab1;
     if (!mlp2r_applies(c, KIND_EDGE, t)) return false;
   }
-  return (c->distinct_min_us == 0 || encode_estimate_us(c, b) >= kOnceMinUs) && looks_like_rewrites(c, b) && attributes_alike(c, b);
+  return (c->distinct_min_us == 0 || encode_estimate_us(c, b) >= (double)std::max<int64_t>(kOnceMinUs, c->distinct_min_us)) && looks_like_rewrites(c, b) && attributes_alike(c, b);
 }
 struct OnceLevels {
   OnceArgs o;

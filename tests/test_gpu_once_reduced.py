@@ -181,3 +181,22 @@ def test_a_small_kept_batch_is_left_whole(hidden, precision, n_cand, reduced):
     assert (enc.batch_level(batch, 0)[0] < batch.N) == reduced
     batch.free()
     enc.close()
+
+
+@pytest.mark.parametrize("min_us,levels", [("300", 7), ("500", 7), ("2000", 0)])
+def test_the_threshold_holds_for_one_encode_too(min_us, levels, monkeypatch):
+    """A batch below the smallest one that is to be reduced is left whole when it is encoded once, as when it is kept."""
+    rng = np.random.Generator(np.random.PCG64(17))
+    model, _ = synth.make_config(1)
+    model.update(hidden=256, precision="bf16", rounds=5)
+    state = _large_state(rng, model, "rewrites")
+    monkeypatch.setenv("XRL_DISTINCT_MIN_US", min_us)
+    enc = xrl.Encoder(model, synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1))
+    batch = enc.pack(state)
+    us = 10 * 256 * (batch.N * 768 + batch.E * 776) / 7e8
+    assert 500 < us < 2000
+    enc.set_timing(True)
+    enc.encode(batch)
+    assert enc.read_timing("levels")[1] == levels
+    batch.free()
+    enc.close()
