@@ -39,41 +39,6 @@ struct Mlp2BwdzArgs {
                                // receivers without in-edges are not written)
 };
 
-// Weight fragments for NW waves, UG units of UF fragments per group, through LDS: every wave
-// fetches GF / NW of a group's fragments a whole group ahead of their use.
-template <int UF, int UG, int NW>
-struct WeightGroupsN {
-  static constexpr int GF = UF * UG, PW = GF / NW;
-  static_assert(GF % NW == 0, "a group is fetched by all waves of the block");
-  f32x4 (*buf)[GF][64];
-  int p = 0, wave, lane;
-  f32x4 r[PW];
-  template <typename Idx>
-  __device__ __forceinline__ void fetch(const bf16x8 *W, Idx idx) {
-#pragma unroll
-    for (int i = 0; i < PW; ++i) {
-      const int jg = wave * PW + i;
-      r[i] = __builtin_bit_cast(f32x4, W[(size_t)idx(jg / UF, jg % UF) * 64]);
-    }
-  }
-  __device__ __forceinline__ void commit(int q) {
-#pragma unroll
-    for (int i = 0; i < PW; ++i) buf[q][wave * PW + i][lane] = r[i];
-  }
-  template <typename Idx>
-  __device__ __forceinline__ void begin(const bf16x8 *W, Idx idx) {
-    fetch(W, idx);
-    commit(p);
-    __syncthreads();
-  }
-  __device__ __forceinline__ void next(bool have_next) {
-    if (have_next) commit(p ^ 1);
-    __syncthreads();
-    p ^= 1;
-  }
-  __device__ __forceinline__ bf16x8 get(int u, int j) const { return __builtin_bit_cast(bf16x8, buf[p][u * UF + j][lane]); }
-};
-
 template <int H>
 struct BwdzShape {
   static constexpr int NW = H >= 256 ? 8 : 4;                 // waves per block

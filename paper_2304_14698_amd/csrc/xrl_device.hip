@@ -1368,10 +1368,42 @@ int launch_mlp2_bwd_k(xrl_ctx *c, const Mlp2BwdArgs &a) {
   return XRL_OK;
 }
 
+// Edge and node MLPs in bf16 from many rows on: a wave per tile, four of them sharing the weights' way from L2. It takes as long
+// for a part of a pass of the chip (H = 64: 131 k rows, 128: 66 k, 256: 33 k) as for a whole one, so it is taken by the share of its passes
+// that is filled. us, split / wide, by that share: H = 64, edge 0.39 14.6 / 15.1, 0.57 19.1 / 18.6, 0.62 32.3 / 29.0, 0.81 98.2 / 83.2, node 0.54 18.7 / 21.3,
+// 0.62 20.5 / 21.6, 0.67 37.9 / 37.4, 0.72 23.6 / 22.4; H = 128, edge 0.63 26.3 / 26.8, 0.65 44.1 / 41.8, 0.72 81.3 / 68.1, 0.98 34.4 / 28.8, node 0.62 41.2 /
+// 42.9, 0.69 94.4 / 84.7; H = 256, edge 0.76 124.8 / 131.8 and 174.8 / 185.8, 0.79 81.2 / 88.2, 0.87 238 / 234, 0.995 271 / 242, node 0.75 75.3 / 78.8, 0.83
+// 214 / 210, 0.93 101 / 88.9.
+template <int H, int KIND>
+int launch_mlp2_bwd_wide(xrl_ctx *c, const Mlp2BwdArgs &args, bool *launched) {
+  auto kern = mlp2_bwd_wide_kernel<H, KIND>;
+  static std::atomic<int> per_cu{0};     // blocks resident on a compute unit
+  int fit = per_cu;
+  if (!fit) {
+    HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, BwdWide<H>::BYTES));
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, (const void *)kern, 256, BwdWide<H>::BYTES));
+    per_cu = fit = std::max(fit, 1);
+  }
+  constexpr int64_t kFilled = H == 64 ? (KIND == KIND_EDGE ? 50 : 66) : H == 128 ? 65 : 82;    // percent
+  Mlp2BwdArgs a = args;
+  a.n_blocks = (a.n_rows + 127) / 128;
+  const int64_t pass = (int64_t)fit * c->n_cu, passes = (a.n_blocks + pass - 1) / pass;
+  *launched = 100 * a.n_blocks >= kFilled * passes * pass;
+  if (!*launched) return XRL_OK;
+  kern<<<dim3((unsigned)((a.n_blocks + 7) / 8 * 8)), dim3(256), BwdWide<H>::BYTES, c->stream>>>(a);
+  HIP_TRY(hipGetLastError());
+  return XRL_OK;
+}
+
 template <typename T, int H>
 int launch_mlp2_bwd_h(xrl_ctx *c, int kind, const Mlp2BwdArgs &a) {
   if (a.n_rows <= 0) return XRL_OK;
   if (kind == KIND_EMBED) return launch_mlp2_bwd_k<float, T, H, KIND_EMBED>(c, a);
+  if constexpr (sizeof(T) == 2) {
+    bool launched = false;
+    const int rc = kind == KIND_EDGE ? launch_mlp2_bwd_wide<H, KIND_EDGE>(c, a, &launched) : launch_mlp2_bwd_wide<H, KIND_NODE>(c, a, &launched);
+    if (rc || launched) return rc;
+  }
   if (kind == KIND_EDGE) return launch_mlp2_bwd_k<T, T, H, KIND_EDGE>(c, a);
   return launch_mlp2_bwd_k<T, T, H, KIND_NODE>(c, a);
 }
