@@ -44,7 +44,7 @@ struct Mlp2BwdArgs {
   const float *edge_feat;
   const int32_t *node_op;
   const float *node_dense;
-  int De, Tn, Dd;
+  int De, Dd;
   void *z1, *dz1, *dz2;      // [rows, H] operand type
   void *dx_a, *dx_b;         // EDGE: d h_sender, d h_receiver [E, H] operand type;
                              // NODE: d h, d agg [N, H] operand type
@@ -70,7 +70,7 @@ struct BwdTile {
   static constexpr int EBYTES = S::HS * 1024;                   // an exchange area: [HS][64] fragments; two of them hold the input
   static constexpr int BYTES = 2 * EBYTES + S::MB * BlockStage<T>::BYTES;
 };
-template <typename T1, typename T, int H, int KIND>
+template <typename T, int H, int KIND>
 __global__ __launch_bounds__(2 * H) void mlp2_bwd_kernel(const Mlp2BwdArgs a) {
   using S = SplitTile<T, H>;
   using B = BwdTile<T, H>;

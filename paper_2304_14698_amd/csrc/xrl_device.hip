@@ -48,7 +48,7 @@ struct EncMlp {           // device pointers of one encoder MLP
   const void *W2bt = nullptr, *W1bt = nullptr;   // backward: contraction over the weight's columns
   const float *b1 = nullptr, *b2 = nullptr;
   int nslab1 = 0;
-  // embed MLP, forward: W1's rows for [edge-attr sum | dense attrs] in fragment order (fp32), and
+  // embed MLP, in place of W1s: W1's rows for [edge-attr sum | dense attrs] in fragment order (fp32), and
   // its rows for the one-hot op type as a plain [Tn, H] table
   const void *W1x = nullptr;
   const float *table = nullptr;
@@ -664,18 +664,18 @@ int plan_weights(xrl_ctx *c) {
     j.groups = (int64_t)(Kc / (2 * V)) * j.cb * 64;
     return put(j);
   };
-  struct Ref { size_t w1, w2, w2bt, w1bt = 0, w1x = 0, w1p = 0, w2p = 0; int ns, nsx = 0; };
+  struct Ref { size_t w1 = 0, w2, w2bt, w1bt = 0, w1x = 0, w1p = 0, w2p = 0; int ns = 0, nsx = 0; };
   std::vector<Ref> refs;
   const bool b16 = c->elem == 2;
   auto add = [&](const MlpRef &r, bool embed) {
     Ref ref;
-    const int V1 = embed ? 4 : V;                       // the embed MLP's first layer keeps fp32 operands in both modes
-    ref.ns = (r.d_in[0] + 2 * V1 - 1) / (2 * V1);
-    if (embed) {                                        // (see EncMlp::W1x: the one-hot rows are left out)
+    if (embed) {                                        // (see EncMlp::W1x: fp32 operands in both modes, the one-hot rows left out)
       ref.w1x = frag(r.w[0], De + Dd, H, 4, false, H, 1, De, Tn);
       ref.nsx = (De + Dd + 7) / 8;
+    } else {
+      ref.w1 = frag(r.w[0], r.d_in[0], H, V, b16, H, 1);
+      ref.ns = (r.d_in[0] + 2 * V - 1) / (2 * V);
     }
-    ref.w1 = frag(r.w[0], r.d_in[0], H, V1, b16 && !embed, H, 1);
     ref.w2 = chain(r.w[1], H, H, H, 1);
     ref.w2bt = chain(r.w[1], H, H, 1, H);               // W2^T
     if (!embed) ref.w1bt = chain(r.w[0], H, 2 * H, 1, H);   // (W1^T)[:, :2H]: edge and node MLPs
@@ -1354,10 +1354,10 @@ __global__ void export_rows_kernel(const T *src, int64_t n_rows, int D, const in
 }
 
 
-template <typename T1, typename T, int H, int KIND>
+template <typename T, int H, int KIND>
 int launch_mlp2_bwd_k(xrl_ctx *c, const Mlp2BwdArgs &a) {
   constexpr int lds = BwdTile<T, H>::BYTES;
-  auto kern = mlp2_bwd_kernel<T1, T, H, KIND>;
+  auto kern = mlp2_bwd_kernel<T, H, KIND>;
   static bool attr_set = false;          // one attribute per kernel instantiation
   if (!attr_set) {
     HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
@@ -1398,14 +1398,14 @@ int launch_mlp2_bwd_wide(xrl_ctx *c, const Mlp2BwdArgs &args, bool *launched) {
 template <typename T, int H>
 int launch_mlp2_bwd_h(xrl_ctx *c, int kind, const Mlp2BwdArgs &a) {
   if (a.n_rows <= 0) return XRL_OK;
-  if (kind == KIND_EMBED) return launch_mlp2_bwd_k<float, T, H, KIND_EMBED>(c, a);
+  if (kind == KIND_EMBED) return launch_mlp2_bwd_k<T, H, KIND_EMBED>(c, a);
   if constexpr (sizeof(T) == 2) {
     bool launched = false;
     const int rc = kind == KIND_EDGE ? launch_mlp2_bwd_wide<H, KIND_EDGE>(c, a, &launched) : launch_mlp2_bwd_wide<H, KIND_NODE>(c, a, &launched);
     if (rc || launched) return rc;
   }
-  if (kind == KIND_EDGE) return launch_mlp2_bwd_k<T, T, H, KIND_EDGE>(c, a);
-  return launch_mlp2_bwd_k<T, T, H, KIND_NODE>(c, a);
+  if (kind == KIND_EDGE) return launch_mlp2_bwd_k<T, H, KIND_EDGE>(c, a);
+  return launch_mlp2_bwd_k<T, H, KIND_NODE>(c, a);
 }
 
 template <typename T>
@@ -2438,7 +2438,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
 
   Mlp2BwdArgs a;
   memset(&a, 0, sizeof(a));
-  a.De = De; a.Tn = m.n_op_types; a.Dd = m.n_node_dense;
+  a.De = De; a.Dd = m.n_node_dense;
   // (after a forward of one launch per layer the received sums of nodes without in-edges were never written)
   a.zero_row = c->zero_row;
   auto set_w = [&](const EncMlp &e) {
@@ -3664,7 +3664,7 @@ int xrl_mlp_backward(xrl_ctx *c, const xrl_batch *b, int32_t kind, int32_t round
   const xrl_batch_device &d = b->dev;
   Mlp2BwdArgs a;
   memset(&a, 0, sizeof(a));
-  a.De = c->m.d_edge; a.Tn = c->m.n_op_types; a.Dd = c->m.n_node_dense;
+  a.De = c->m.d_edge; a.Dd = c->m.n_node_dense;
   a.in_ptr = d.in_ptr; a.in_src = d.in_src; a.in_dst = d.in_dst;
   a.edge_feat = d.edge_feat; a.node_op = d.node_op; a.node_dense = d.node_dense;
   const EncMlp &e = kind == XRL_WG_EDGE ? c->edge[round] : c->node[round];
