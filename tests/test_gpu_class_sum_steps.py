@@ -44,3 +44,43 @@ def test_pool_gradient_by_column_slices(monkeypatch):
         enc.close()
     assert torch.equal(got[0][0], got[1][0])
     assert float((got[1][1] - got[0][1]).norm() / got[0][1].norm()) <= 2e-2
+
+
+def test_column_slices_column_by_column(monkeypatch):
+    """The same sums one column at a time: copies of one graph, whose upstream gradients are positive multiples of one row, so that
+    no two terms of a column of the last node MLP's second bias gradient (the sum of the pool's gradient over the rows whose output is
+    positive) have different signs. Rows rounded to bf16 one by one, or their sums: at most 2^-9 of each, so 2^-8 between the two."""
+    import numpy as np
+    import torch
+
+    import paper_2304_14698_amd as xrl
+    import synth
+    rng = np.random.Generator(np.random.PCG64(22))
+    model, _ = synth.make_config(1)
+    model.update(hidden=256, precision="bf16", rounds=2)
+    graph = synth.layered_dag(rng, 18)
+    state = synth.concat_states([([graph] * 4133, np.ones(4133, np.uint8))])
+    layout = xrl.weight_layout(model)
+    w = synth.init_weights(rng, layout, bias_range=0.1)
+    g = torch.Generator().manual_seed(2)
+    up = ((torch.rand(4133, 1, generator=g) + 0.5) * torch.randn(1, 256, generator=g)).cuda()
+    got = []
+    for min_us in ("-1", "0"):
+        monkeypatch.setenv("XRL_DISTINCT_MIN_US", min_us)
+        enc = xrl.Encoder(model, w)
+        batch = enc.pack(state)
+        enc.encode(batch, save_for_backward=True)
+        assert (enc.batch_level(batch, 2)[0] < 32) == (min_us == "0")
+        dw = torch.zeros(enc.n_weights, device="cuda")
+        enc.encode_backward(batch, up, dw)
+        got.append(dw.double().cpu().numpy())
+        batch.free()
+        enc.close()
+    at = 0
+    for name, shape in layout:
+        if name == "node1.b1":
+            break
+        at += int(np.prod(shape))
+    whole, reduced = (x[at:at + 256] for x in got)
+    assert np.count_nonzero(whole) > 128
+    assert np.all(np.abs(whole - reduced) <= (2.0 ** -8 + 1e-5) * np.abs(whole))

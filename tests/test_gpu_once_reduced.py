@@ -42,24 +42,33 @@ def test_levels_made_on_the_device(readout, rounds, monkeypatch):
     assert all(np.array_equal(a, b) for a, b in zip(whole, levels))
 
 
-@pytest.mark.parametrize("save", [False, True])
-def test_a_kept_batch_is_reduced_after_some_encodes(save):
-    """Below the threshold of the first: the more an encode takes, the sooner; same bits before and after."""
+@pytest.mark.parametrize("hidden,precision", [(64, "bf16"), (128, "bf16"), (64, "fp32")])
+def test_a_kept_batch_is_reduced_after_some_encodes(hidden, precision):
+    """Below the threshold of the first: the more an encode takes, the sooner, and sooner if it is saved for the backward pass, but not
+    by the first; same bits before and after, and reduced for good."""
     rng = np.random.Generator(np.random.PCG64(12))
     model, _ = synth.make_config(1)
-    model.update(hidden=128, precision="bf16", rounds=5)
-    state = synth.concat_states([synth.make_state(rng, synth.resnet_dag(rng, 16), 90, by_block=True)])
+    model.update(hidden=hidden, precision=precision, rounds=5)
     enc = xrl.Encoder(model, synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1))
-    batch = enc.pack(state)
-    us = 10 * 128 * (batch.N * 384 + batch.E * 392) / 7e8
-    assert 30 < us < 300
-    first, whole = enc.encode(batch, save_for_backward=save).cpu().numpy(), 1
-    while enc.batch_level(batch, 0)[0] == batch.N and whole < 20:
-        assert np.array_equal(enc.encode(batch, save_for_backward=save).cpu().numpy(), first)
-        whole += 1
-    assert whole == np.ceil(450 / (us * (3.0 if save else 0.8))) + 1
-    assert np.array_equal(enc.encode(batch).cpu().numpy(), first)
-    batch.free()
+    per_us = 10 * hidden * (6 * hidden + 8) / (7e8 if precision == "bf16" else 7e7)
+    taken = {}
+    for us in ((40, 80, 160) if precision == "bf16" else (90, 130, 220)):
+        for save in (False, True):
+            state = synth.concat_states([synth.make_state(rng, synth.resnet_dag(rng, 16), round(us / per_us / 345), by_block=True)])
+            batch = enc.pack(state)
+            first, whole = enc.encode(batch, save_for_backward=save).cpu().numpy(), 1
+            while enc.batch_level(batch, 0)[0] == batch.N and whole < 60:
+                assert np.array_equal(enc.encode(batch, save_for_backward=save).cpu().numpy(), first)
+                whole += 1
+            taken[us, save] = whole
+            for again in (False, True):
+                assert np.array_equal(enc.encode(batch, save_for_backward=again).cpu().numpy(), first)
+            assert enc.batch_level(batch, 0)[0] < batch.N
+            batch.free()
+    for save in (False, True):
+        n = [v for (us, s), v in sorted(taken.items()) if s == save]
+        assert 1 < n[2] <= n[1] <= n[0] < 60 and n[2] < n[0], taken
+    assert all(taken[us, True] < taken[us, False] for us, _ in taken), taken
     enc.close()
 
 
@@ -200,3 +209,85 @@ def test_the_threshold_holds_for_one_encode_too(min_us, levels, monkeypatch):
     assert enc.read_timing("levels")[1] == levels
     batch.free()
     enc.close()
+
+
+@pytest.mark.parametrize("d_edge,n_dense,n_states,cand", [(8, 4, 1, 150), (4, 0, 3, 47), (8, 1, 40, 4)])
+def test_levels_of_many_distinct_nodes(d_edge, n_dense, n_states, cand, monkeypatch):
+    """Levels that keep far more nodes and edges than a pass of the chip's persistent blocks takes (256 of one edge or node tile at a
+    time with the next two requested ahead, 1024 waves of one node tile each), and partly filled last tiles."""
+    rng = np.random.Generator(np.random.PCG64(18))
+    model, _ = synth.make_config(1)
+    model.update(hidden=256, precision="bf16", rounds=2, d_edge=d_edge, n_node_dense=n_dense)
+    state = synth.concat_states([synth.make_state(rng, synth.transformer_dag(rng, 12), cand, by_block=True) for _ in range(n_states)])
+    N, E = len(state["node_op"]), len(state["edge_src"])
+    state["node_dense"] = np.ascontiguousarray(state["node_dense"][:, :n_dense])
+    feat = np.ascontiguousarray(state["edge_feat"][:, :d_edge])
+    other = rng.random(E) < 0.7                                  # (attributes that make most nodes distinct)
+    feat[other, -1] += rng.standard_normal(int(other.sum())).astype(np.float32)
+    state["edge_feat"] = feat
+    w = synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1)
+    whole, levels = ([e for e in _embeddings(model, w, [(state, False)], us, monkeypatch)] for us in ("-1", "0"))
+    assert all(np.array_equal(a, whole[0]) for a in whole + levels)
+    monkeypatch.setenv("XRL_DISTINCT_MIN_US", "0")
+    enc = xrl.Encoder(model, w)
+    batch = enc.pack(state)
+    for _ in range(2):                                           # (the second one counts the levels)
+        enc.encode(batch)
+    nodes, edges, _, tiles = zip(*[enc.batch_level(batch, r) for r in range(3)])
+    assert min(nodes) > 1024 * 32 + 32 and min(tiles[1:]) > 3 * 256 and max(nodes) < N, (nodes, tiles)
+    assert any(n % 32 for n in nodes)
+    batch.free()
+    enc.close()
+
+
+def test_levels_on_another_context_and_after_a_capture():
+    """A context that did not upload the batch goes by its levels too; one whose calls have been captured does not, for that batch and
+    later ones. The same bits all along."""
+    rng = np.random.Generator(np.random.PCG64(19))
+    model, _ = synth.make_config(1)
+    model.update(hidden=256, precision="bf16", rounds=5)
+    state = _large_state(rng, model, "rewrites")
+    w = synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1)
+    side = torch.cuda.Stream()
+    owner, other, captured = xrl.Encoder(model, w), xrl.Encoder(model, w), xrl.Encoder(model, w, stream=side)
+    batch = owner.pack(state)
+
+    def encode(enc, b):
+        enc.set_timing(True)
+        emb = enc.encode(b)
+        torch.cuda.synchronize()
+        n = enc.read_timing("levels")[1]
+        enc.set_timing(False)
+        return emb, n
+
+    first, n = encode(owner, batch)
+    assert n == 7
+    for _ in range(2):
+        emb, n = encode(other, batch)
+        assert n == 7 and torch.equal(emb, first)
+    small = captured.pack(synth.concat_states([([synth.layered_dag(rng, 60)], np.ones(1, np.uint8))]))
+    out = captured.encode(small)
+    torch.cuda.synchronize()
+    emb, n = encode(captured, batch)
+    assert n == 7 and torch.equal(emb, first)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side, capture_error_mode="relaxed"):
+        captured.encode(small, out=out)
+    for _ in range(2):
+        emb, n = encode(captured, batch)
+        assert n == 0 and torch.equal(emb, first)
+        eager = captured.encode(small)
+        torch.cuda.synchronize()
+        out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager)
+    later = captured.pack(state)
+    emb, n = encode(captured, later)
+    assert n == 0 and torch.equal(emb, first)
+    del graph
+    for b in (batch, small, later):
+        b.free()
+    for e in (owner, other, captured):
+        e.close()
