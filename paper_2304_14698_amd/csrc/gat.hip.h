@@ -2,9 +2,10 @@
 // cites graph attention for its learned per-edge weighting): per round
 //   z = h W;  per edge j -> i: s = LeakyReLU_0.2(a_src . z_j + a_dst . z_i), likewise for a self
 //   edge; alpha = softmax of s over i's in-edges plus the self edge;  h'_i = ReLU(sum alpha z_j).
-// Two kernels: the dense part on the matrix cores (z and the two per-node scalars a_src . z,
-// a_dst . z, taken from the fp32 accumulators), then a gather-bound pass over each receiver's
-// contiguous in-edge range. The backward pass (further down) is gather-based as well: one
+// The dense part on the matrix cores (z and the two per-node scalars a_src . z, a_dst . z, taken from
+// the fp32 accumulators), then a gather-bound pass over each receiver's contiguous in-edge
+// range: a kernel each, or (gat_round_kernel, smaller batches) the pass of one round and the dense part
+// of the next in one launch. The backward pass (further down) is gather-based as well: one
 // pass per receiver for the softmax and score gradients, one per sender for dz, then two dense
 // products (dh = dz W^T, dW = h^T dz) on the matrix cores.
 #pragma once

@@ -73,8 +73,9 @@ template <int KIND>
 __device__ __forceinline__ RTileRows rtile_rows(const Mlp2Args &a, int64_t wt) {
   RTileRows t;
   if constexpr (KIND == KIND_EDGE) {
-    // wt is uniform: read the tile table through the scalar unit (the constant address space; the
-    // table is never written on the device). As an ordinary load it would be a vector load whose
+    // wt is uniform: read the tile table through the scalar unit (the constant address space: nothing
+    // writes the table while the kernel runs. once_fill_kernel rewrites it in front of every round, and a
+    // launch begins with its scalar cache empty). As an ordinary load it would be a vector load whose
     // result is needed in scalar registers at once, and the wait for it also waits for every row
     // prefetch issued just before.
     typedef const __attribute__((address_space(4))) int32_t *cptr;
