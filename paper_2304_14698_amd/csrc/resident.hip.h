@@ -1,13 +1,13 @@
 // One-launch encoder for small batches (the agent's own inference loop encodes one state of a few
-// dozen candidate graphs per step, Section 4.2): one block per graph runs the node-update layer,
-// every message-passing round and the global-update layer (Section 3.4) on its graph, with block
+// dozen candidate graphs per step, Section 4.2): one block per graph runs the node-update layer
+// and every message-passing round (Section 3.4) on its graph, with block
 // barriers where the other path has kernel boundaries. A graph's node states and received
 // sums live in the same global buffers as with a launch per layer (a few hundred KB per graph: they
 // stay in the CU's L1 and the XCD's L2), so both paths save the same activations for the
 // backward pass; what the launch removes is a dozen launch latencies and pipeline drains.
 //
-// Tiles, arithmetic and the order of every sum are those of mlp2_wave_tile and
-// graph_readout_block, so the embeddings equal those of a launch per layer bit for bit. Edge tiles
+// Tiles, arithmetic and the order of every sum are those of mlp2_wave_tile, and the readout's launch follows
+// (it shares its weights over graphs better than a block per graph could), so the embeddings equal those of a launch per layer bit for bit. Edge tiles
 // come from the packer's per-graph table (no tile spans two graphs, no receiver spans two
 // tiles), which is why no carry fix-up is needed here.
 #pragma once
@@ -31,9 +31,6 @@ struct ResidentArgs {
   int w1_bytes_max;                      // LDS reserved for a phase's first-layer weights
   int64_t E;
   const int32_t *graph_node_ptr, *graph_tile_ptr, *gtile_ptr;
-  int mean;
-  float *pool;
-  RowMlpArgs readout;
   // several blocks per graph (encode_cluster_kernel)
   int K;                                 // blocks per graph
   int G;                                 // graphs
@@ -63,8 +60,7 @@ __device__ __forceinline__ void fill_lds(char *dst, const void *src, int bytes) 
   }
 }
 
-// LDS: [four waves' row staging | W1 of the running phase | its W2 | the embed layer's table];
-// the readout reuses it from the start. With a handful of tiles per graph a weight fragment
+// LDS: [four waves' row staging | W1 of the running phase | its W2 | the embed layer's table]. With a handful of tiles per graph a weight fragment
 // requested from L2 one slab ahead of its MFMAs (as the split kernel does, where other waves
 // hide the wait) would cost a memory round trip per slab, so every phase first copies its two
 // matrices into LDS in one batch of loads.
@@ -115,7 +111,6 @@ __global__ __launch_bounds__(256) void encode_resident_kernel(const ResidentArgs
     }
     __syncthreads();
   }
-  graph_readout_block<T, VEC>((const T *)ra.h[ra.rounds], n0, n1, gi, H, ra.mean, ra.pool, ra.readout, (float *)smem);
 }
 
 // ---- several blocks per graph ------------------------------------------------------------------
@@ -212,7 +207,7 @@ __global__ __launch_bounds__(256) void encode_cluster_kernel(const ResidentArgs 
       mlp2_wave_tile<T, T, H, KIND_NODE>(a, n0 + 32 * j, left < 32 ? left : 32, 0, stage, lane);
     }
     if (r + 1 == ra.rounds && kb != 0) {
-      // the graph's first block does the readout: the others only report that their rows are out
+      // the graph's first block puts the counter back: the others only report that they are done with it
       __syncthreads();
       if (threadIdx.x == 0) cluster_arrive(ctr);
       return;
@@ -222,5 +217,4 @@ __global__ __launch_bounds__(256) void encode_cluster_kernel(const ResidentArgs 
   }
   // (every block of the graph has arrived for the last time: the counter can go back to zero)
   if (threadIdx.x == 0) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  graph_readout_block<T, VEC>((const T *)ra.h[ra.rounds], n0, n1, gi, H, ra.mean, ra.pool, ra.readout, (float *)smem);
 }

@@ -1,0 +1,811 @@
+// Row-MLPs on the fp32 matrix cores: sixteen rows of per-graph or per-state data per block through the readout MLP of the
+// global-update layer (Section 3.4) or the policy and value heads (Section 3.3.2), and back.
+//
+// What bounds them: every block reads all the weights from L2 (320 KB for a head at H = 256), and a row is too few products
+// to hide that behind; so sixteen rows share a fragment (v_mfma_f32_16x16x4_f32, full fp32 operands and sums), the weights lie in
+// fragment order (a fragment of 16 outputs by 16 contraction indices is one coalesced 1 KB load), and the eight waves of a
+// block own different outputs, so that a layer costs one barrier. A wave requests the fragments of its next step -- across
+// the barrier between two layers -- before the products of this one: at H = 256 a step's 32 instructions take longer than
+// the L2's answer. Both halves of a layer's widths are padded to sixteen with zeros in the fragments; any width fits.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <stdint.h>
+#include <type_traits>
+#include "mma.hip.h"
+#include "segsum.hip.h"
+
+constexpr int kRowTile = 16, kRowThreads = 512, kRowWaves = kRowThreads / 64, kRowFrags = 8;
+
+// One affine map of a row-MLP: y = x M, M in fragment order ([output tile][contraction group][lane] of four floats:
+// lane l has output 16 * tile + l % 16, contraction indices 16 * group + 4 * (l / 16) .. + 3).
+struct RowMap {
+  const f32x4 *w;
+  int n_in, n_out;
+};
+// The widths of an MLP from its input on, where the kernel is made for them (0: known at run time only). These launches are chains of a
+// few round trips, and every width that has to be asked for first lengthens them.
+template <int... W>
+struct RowWidths {
+  static constexpr int N = sizeof...(W) - 1;                       // maps
+  static constexpr int w[N + 1] = {W...};
+  static constexpr bool known = ((W > 0) && ...);                  // (else with registers of two waves per SIMD: it would spill)
+  static constexpr int waves = known || N == 2 ? 4 : 2;
+  template <int M> static __device__ __forceinline__ int in(const RowMap *map) { if constexpr (w[M] > 0) return w[M]; else return map[M].n_in; }
+  template <int M> static __device__ __forceinline__ int out(const RowMap *map) { if constexpr (w[M + 1] > 0) return w[M + 1]; else return map[M].n_out; }
+};
+template <int M> using MapIndex = std::integral_constant<int, M>;
+
+// Kernel arguments lie in host memory, and the compiler asks for them where they are first used: one round trip of 1 us after another.
+// This asks for all their cache lines at once.
+template <typename Args>
+__device__ __forceinline__ void touch_args(const Args &a) {
+  const unsigned *p = (const unsigned *)&a;
+  constexpr int N = (int)((sizeof(Args) + 63) / 64);
+  unsigned v[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] = p[i * 16];
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" ::"s"(v[i]));
+}
+// floats of LDS between two rows of x: sixteen rows' 16-byte reads touch all banks
+__host__ __device__ inline int row_pitch(int width) { return ((width + 15) >> 4) * 16 + 4; }
+
+// x (LDS, sixteen rows `pitch` apart, padding columns zero) through the maps in turn; x2: room for as many. All 512 threads call it;
+// stage() writes x, behind the first requests for weights (no barrier after it). Per output a lane holds four rows, 4 * (lane / 16) + i: their
+// sums of map M's column f start from pre(M, f) and pass through post(M, f, sums), which leaves in them what goes to the next
+// map's x (zeros in padding columns). Returns the x that holds the last results, after a barrier.
+template <typename W>
+struct RowMaps {
+  static constexpr int HALF = kRowFrags / 2;
+  const RowMap *map;
+  int lane, wave, c16, q4, pitch;
+  f32x4 next[kRowFrags];                             // of the wave's next step
+
+  // A step is kRowFrags fragments of one output tile (a unit) or, where there are more tiles than waves, of two; where there are
+  // at most half as many tiles as waves, of one half of a tile's contraction (a unit too: the halves are added in LDS).
+  template <int M> __device__ __forceinline__ int groups() const { return (W::template in<M>(map) + 15) >> 4; }
+  template <int M> __device__ __forceinline__ int tiles() const { return (W::template out<M>(map) + 15) >> 4; }
+  template <int M> __device__ __forceinline__ bool two() const { return tiles<M>() > kRowWaves; }
+  template <int M> __device__ __forceinline__ int half() const {   // groups of the first half, or 0
+    return tiles<M>() <= kRowWaves / 2 && groups<M>() > HALF ? (groups<M>() + 1) >> 1 : 0;
+  }
+  template <int M> __device__ __forceinline__ int units() const { return two<M>() ? (tiles<M>() + 1) >> 1 : half<M>() ? 2 * tiles<M>() : tiles<M>(); }
+  template <int M> __device__ __forceinline__ int steps() const {
+    const int g = half<M>() ? half<M>() : groups<M>();
+    return two<M>() ? (g + HALF - 1) / HALF : (g + kRowFrags - 1) / kRowFrags;
+  }
+  template <int M> __device__ __forceinline__ void request(int u, int s) {   // (past the end the last fragment again: its products are left out)
+    const int G = groups<M>(), last = tiles<M>() - 1, t0 = two<M>() ? 2 * u : half<M>() ? u >> 1 : u, t1 = t0 < last ? t0 + 1 : last;
+    const f32x4 *w0 = map[M].w + (unsigned)(t0 * G) * 64u, *w1 = map[M].w + (unsigned)(t1 * G) * 64u;
+    const int g0 = s * (two<M>() ? HALF : kRowFrags) + (u & 1 ? half<M>() : 0);
+#pragma unroll
+    for (int i = 0; i < kRowFrags; ++i) {
+      int g = g0 + (two<M>() ? i >> 1 : i);
+      g = g < G ? g : G - 1;
+      const f32x4 *p = (two<M>() && (i & 1) ? w1 : w0) + (unsigned)g * 64u;   // (the same for all lanes)
+      next[i] = p[lane];
+    }
+  }
+  template <int M> __device__ __forceinline__ void request_first() {
+    if constexpr (M < W::N)
+      if (wave < units<M>()) request<M>(wave, 0);
+  }
+  template <int M, typename Pre, typename Post>
+  __device__ __forceinline__ void run(float *x, float *x2, Pre &pre, Post &post) {
+    const int T = tiles<M>(), n_units = units<M>(), n_steps = steps<M>(), n_out = W::template out<M>(map);
+    const float *xr = x + c16 * pitch + 4 * q4;
+    if (wave >= n_units) {
+      request_first<M + 1>();
+      if (half<M>()) __syncthreads();
+    }
+    for (int u = wave; u < n_units; u += kRowWaves) {
+      const int t0 = two<M>() ? 2 * u : half<M>() ? u >> 1 : u, f0 = 16 * t0 + c16;
+      const bool upper = half<M>() && (u & 1);
+      const int gend = half<M>() && !upper ? half<M>() : groups<M>();
+      // four sums per output, of every fourth contraction index: an instruction need not wait for the one before, and
+      // rounding errors are those of chains a quarter as long
+      f32x4 sum[2][4];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const float from = (two<M>() || k == 0) && !upper ? pre(MapIndex<M>(), f0 + 16 * k < n_out ? f0 + 16 * k : n_out - 1) : 0.f;
+        sum[k][0] = f32x4{from, from, from, from};
+#pragma unroll
+        for (int j = 1; j < 4; ++j) sum[k][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      for (int s = 0; s < n_steps; ++s) {
+        f32x4 w[kRowFrags], a[HALF];
+#pragma unroll
+        for (int i = 0; i < kRowFrags; ++i) w[i] = next[i];
+        if (s + 1 < n_steps) request<M>(u, s + 1);
+        else if (u + kRowWaves < n_units) request<M>(u + kRowWaves, 0);
+        else request_first<M + 1>();
+        int g0 = s * (two<M>() ? HALF : kRowFrags) + (upper ? half<M>() : 0);
+        auto rows = [&]() {
+#pragma unroll
+          for (int i = 0; i < HALF; ++i) a[i] = *(const f32x4 *)(xr + 16 * (g0 + i < gend ? g0 + i : gend - 1));
+        };
+        rows();
+        if (two<M>()) {
+#pragma unroll
+          for (int i = 0; i < HALF; ++i) {
+            if (g0 + i >= gend) break;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              sum[0][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j], w[2 * i][j], sum[0][j], 0, 0, 0);
+              sum[1][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j], w[2 * i + 1][j], sum[1][j], 0, 0, 0);
+            }
+          }
+        } else {
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            if (g0 >= gend) break;
+            if (h == 1) rows();
+#pragma unroll
+            for (int i = 0; i < HALF; ++i) {
+              if (g0 + i >= gend) break;
+#pragma unroll
+              for (int j = 0; j < 4; ++j) sum[0][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j], w[h * HALF + i][j], sum[0][j], 0, 0, 0);
+            }
+            g0 += HALF;
+          }
+        }
+      }
+      f32x4 acc[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) acc[k] = (sum[k][0] + sum[k][2]) + (sum[k][1] + sum[k][3]);
+      if (half<M>()) {                               // (a wave has one unit at most: all pass this barrier once, see above)
+        if (upper) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) x2[(4 * q4 + i) * pitch + f0] = acc[0][i];
+        }
+        __syncthreads();
+        if (upper) break;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[0][i] += x2[(4 * q4 + i) * pitch + f0];
+      }
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        if (k == 1 && (!two<M>() || t0 + 1 >= T)) break;
+        const int f = f0 + 16 * k;
+        if (f < n_out) post(MapIndex<M>(), f, acc[k]);
+        else acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x2[(4 * q4 + i) * pitch + f] = acc[k][i];
+      }
+    }
+    __syncthreads();
+    if constexpr (M + 1 < W::N) run<M + 1>(x2, x, pre, post);
+  }
+};
+template <typename W, typename Stage, typename Pre, typename Post>
+__device__ __forceinline__ float *row_maps(const RowMap *map, float *x, float *x2, int pitch, Stage stage, Pre pre, Post post) {
+  RowMaps<W> m;
+  m.map = map;
+  m.lane = threadIdx.x & 63;
+  m.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);       // (what steers the loops is the same for a wave's lanes)
+  m.c16 = m.lane & 15;
+  m.q4 = m.lane >> 4;
+  m.pitch = pitch;
+  m.template request_first<0>();
+  stage();
+  __syncthreads();
+  m.template run<0>(x, x2, pre, post);
+  return W::N % 2 ? x2 : x;
+}
+
+// ---- forward
+struct RowFwdArgs {
+  int relu_last;
+  RowMap map[3];
+  const float *b[3];
+  const float *in1, *in2;  // in2 nullable
+  int w1, w2;              // widths of in1 (a multiple of 4, rows 16-byte aligned) / in2; w1 + w2 == map[0].n_in
+  int64_t n_rows;
+  float *out;              // [n_rows, map[last].n_out]
+  float *act[3];           // nullable each: every layer's output (after its ReLU)
+  int pitch;               // of the widest layer
+};
+__host__ __device__ inline size_t row_lds_floats(int pitch) { return (size_t)(2 * kRowTile + 3) * pitch; }   // x, x2, the biases
+
+// the layers' biases, `pitch` floats apart behind x and x2 (a sum that starts from one does not wait for memory); all widths are at
+// most kRowThreads, and all loads in flight at once
+template <typename W>
+struct RowBiases {
+  float v[W::N];
+  template <int M = 0> __device__ __forceinline__ void request(const RowFwdArgs &a) {
+    if constexpr (M < W::N) {
+      const int n = W::template out<M>(a.map), t = threadIdx.x;
+      v[M] = a.b[M][t < n ? t : n - 1];
+      request<M + 1>(a);
+    }
+  }
+  template <int M = 0> __device__ __forceinline__ void store(const RowFwdArgs &a, float *x, int pitch) const {
+    if constexpr (M < W::N) {
+      if ((int)threadIdx.x < W::template out<M>(a.map)) x[(2 * kRowTile + M) * pitch + threadIdx.x] = v[M];
+      store<M + 1>(a, x, pitch);
+    }
+  }
+};
+// rows row0 .. row0 + 15 of [in1 | in2], zeros past the last row and column: two rows a wave, the first 256 columns of in1 and 64 of
+// in2 in one round trip
+struct RowInputs {
+  f32x4 v[2];
+  float g[2];
+  __device__ __forceinline__ void request(const RowFwdArgs &a, int w1, int64_t row0) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      int64_t row = row0 + 2 * (threadIdx.x >> 6) + i;
+      row = row < a.n_rows ? row : a.n_rows - 1;
+      v[i] = *(const f32x4 *)(a.in1 + row * w1 + (4 * lane < w1 ? 4 * lane : 0));
+      g[i] = a.w2 ? a.in2[row * a.w2 + (lane < a.w2 ? lane : 0)] : 0.f;
+    }
+  }
+  __device__ __forceinline__ void store(const RowFwdArgs &a, int w1, int width, int64_t row0, float *x, int pitch) const {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int r = 2 * (threadIdx.x >> 6) + i;
+      const bool on = row0 + r < a.n_rows;
+      float *xr = x + r * pitch;
+      if (4 * lane < w1) *(f32x4 *)(xr + 4 * lane) = on ? v[i] : f32x4{0.f, 0.f, 0.f, 0.f};
+      if (w1 + lane < width) xr[w1 + lane] = on && lane < a.w2 ? g[i] : 0.f;
+      for (int k = lane + 64; k < width - w1; k += 64) xr[w1 + k] = on && k < a.w2 ? a.in2[(row0 + r) * a.w2 + k] : 0.f;
+    }
+  }
+};
+// The layers of `a` on sixteen rows, row0 .. of which those below row_end are stored; stage() writes them and the biases to x. COHERENT_OUT
+// stores a.out with device scope, for a consumer in another block of the same launch.
+template <typename W, bool COHERENT_OUT, typename Stage>
+__device__ __forceinline__ float *row_forward(const RowFwdArgs &a, int64_t row0, int64_t row_end, float *x, int pitch, Stage stage) {
+  const int q4 = (threadIdx.x & 63) >> 4;
+  const unsigned n_rows = row_end - row0 < kRowTile ? (unsigned)(row_end - row0) : kRowTile;
+  const float *bias = x + 2 * kRowTile * pitch;
+  const bool relu_last = a.relu_last;
+  return row_maps<W>(a.map, x, x + kRowTile * pitch, pitch, stage,
+    [&](auto m, int f) { return bias[decltype(m)::value * pitch + f]; },
+    [&](auto m, int f, f32x4 &y) {
+      constexpr int M = decltype(m)::value;
+      constexpr bool last = M + 1 == W::N;
+      const unsigned n_out = W::template out<M>(a.map);
+      float *keep = a.act[M], *out = a.out + row0 * n_out;
+      if (keep) keep += row0 * n_out;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (!last || relu_last) y[i] = fmaxf(y[i], 0.f);
+        const unsigned r = 4 * q4 + i, at = r * n_out + f;
+        if (keep && r < n_rows) keep[at] = y[i];
+        if (last && r < n_rows) {
+          if constexpr (COHERENT_OUT) __hip_atomic_store(out + at, y[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          else out[at] = y[i];
+        }
+      }
+    });
+}
+template <typename W>
+__global__ __launch_bounds__(kRowThreads, W::waves) void row_forward_kernel(const RowFwdArgs a) {
+  extern __shared__ __align__(16) float sm[];
+  touch_args(a);
+  const int64_t row0 = (int64_t)blockIdx.x * kRowTile;
+  const int pitch = a.pitch;
+  (void)row_forward<W, false>(a, row0, a.n_rows, sm, pitch, [&]() {
+    RowInputs in;
+    RowBiases<W> b;
+    in.request(a, a.w1, row0);
+    b.request(a);
+    in.store(a, a.w1, (W::template in<0>(a.map) + 15) & ~15, row0, sm, pitch);
+    b.store(a, sm, pitch);
+  });
+}
+
+// ---- readout: the sum (or mean) of a graph's node states by a block, stored as pool[g, :] and left in row (LDS; nullable).
+// H / VEC lanes cover a node's row with 16-byte loads. The nodes are dealt over 512 / (H / VEC) groups, of which a thread of a block of
+// THREADS threads holds V = 512 / THREADS (eight loads in flight in all), and the groups' sums are added in an order that does not
+// depend on THREADS: a graph's sum is the same bits in a batch of any size.
+// MAPPED: row_of[n] is the row of h that holds node n's state (else row n); it is read a step ahead. part: THREADS * VEC floats of LDS.
+template <typename T, int VEC, int H, bool MAPPED, int THREADS>
+__device__ __forceinline__ void graph_pool(const T *h, const int32_t *graph_node_ptr, const int32_t *row_of, int g, int mean, float *pool,
+                                           float *part, float *row) {
+  constexpr int tpr = H / VEC, Q = 256 / tpr, B = THREADS / tpr, NG = 2 * Q, V = 512 / THREADS, UF = 8 / V;
+  const int t = threadIdx.x, c0 = (t % tpr) * VEC, q = t / tpr, n0 = graph_node_ptr[g], n1 = graph_node_ptr[g + 1];
+  float acc[V][VEC];
+#pragma unroll
+  for (int v = 0; v < V; ++v)
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) acc[v][j] = 0.f;
+  int at[V][UF];                                         // (past the end the graph's last row again, left out of the sum)
+  auto places = [&](int n) {
+#pragma unroll
+    for (int v = 0; v < V; ++v)
+#pragma unroll
+      for (int i = 0; i < UF; ++i) {
+        const int k = n + v * B + i * NG;
+        at[v][i] = k < n1 ? k : n1 - 1;
+        if (MAPPED) at[v][i] = row_of[at[v][i]];
+      }
+  };
+  if (n0 < n1) {
+    places(n0 + q);
+    for (int n = n0 + q; n - q < n1; n += UF * NG) {
+      float x[V][UF][VEC];
+#pragma unroll
+      for (int v = 0; v < V; ++v)
+#pragma unroll
+        for (int i = 0; i < UF; ++i) RowVec<T, VEC>::load(h + (size_t)at[v][i] * H + c0, x[v][i]);
+      places(n + UF * NG);
+#pragma unroll
+      for (int v = 0; v < V; ++v)
+#pragma unroll
+        for (int i = 0; i < UF; ++i)
+#pragma unroll
+          for (int j = 0; j < VEC; ++j) acc[v][j] += n + v * B + i * NG < n1 ? x[v][i][j] : 0.f;
+    }
+  }
+  // the sum over q < Q of group q + group q + Q
+  if constexpr (V == 2) {
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) acc[0][j] += acc[1][j];
+  }
+#pragma unroll
+  for (int j = 0; j < VEC; j += 4) *(f32x4 *)(part + t * VEC + j) = f32x4{acc[0][j], acc[0][j + 1], acc[0][j + 2], acc[0][j + 3]};
+  __syncthreads();
+  if (t < H) {
+    float a = 0.f;
+#pragma unroll
+    for (int k = 0; k < Q; ++k) {
+      const float x = V == 2 ? part[k * H + t] : part[k * H + t] + part[(k + Q) * H + t];
+      a = k ? a + x : x;
+    }
+    if (mean) a *= 1.f / (float)(n1 - n0 > 1 ? n1 - n0 : 1);
+    pool[(size_t)g * H + t] = a;
+    if (row) row[t] = a;
+  }
+}
+// Many graphs: a block sums one, the readout MLP follows in a launch of its own (row_forward_kernel), whose blocks
+// share the weights among sixteen graphs.
+template <typename T, int VEC, int H, bool MAPPED, int THREADS>
+__global__ __launch_bounds__(THREADS) void graph_pool_kernel(const T *h, const int32_t *graph_node_ptr, const int32_t *row_of, int mean, float *pool) {
+  __shared__ __align__(16) float part[THREADS * VEC];
+  graph_pool<T, VEC, H, MAPPED, THREADS>(h, graph_node_ptr, row_of, blockIdx.x, mean, pool, part, nullptr);
+}
+// Few graphs: both in one launch, a block per graph, the MLP's first weights requested ahead of the sum.
+template <typename W, typename T, int VEC, bool MAPPED>
+__global__ __launch_bounds__(kRowThreads, 4) void graph_readout_kernel(const T *h, const int32_t *graph_node_ptr, const int32_t *row_of, int mean,
+                                                                       float *pool, const RowFwdArgs a) {
+  constexpr int H = W::w[1];
+  extern __shared__ __align__(16) float sm[];
+  __shared__ __align__(16) float part[kRowThreads * VEC];
+  touch_args(a);
+  const int g = blockIdx.x, t = threadIdx.x, pitch = a.pitch;
+  (void)row_forward<W, false>(a, g, g + 1, sm, pitch, [&]() {
+    RowBiases<W> b;
+    b.request(a);
+    for (int i = t; i < kRowTile * pitch; i += kRowThreads)        // row 0: the pool (below), the global attributes
+      if (i >= H) sm[i] = i < H + a.w2 ? a.in2[(size_t)g * a.w2 + (i - H)] : 0.f;
+    b.store(a, sm, pitch);
+    graph_pool<T, VEC, H, MAPPED, kRowThreads>(h, graph_node_ptr, row_of, g, mean, pool, part, sm);
+  });
+}
+
+// ---- reductions over a wave or the block, in a fixed order
+struct BestSlot {
+  float value;
+  int index;             // lowest index that has it
+};
+__device__ __forceinline__ BestSlot better(const BestSlot &a, const BestSlot &b) {
+  return b.value > a.value || (b.value == a.value && b.index < a.index) ? b : a;
+}
+__device__ __forceinline__ float wave_sum(float v) {
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o);
+  return v;
+}
+__device__ __forceinline__ BestSlot wave_best(BestSlot b) {
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) b = better(b, BestSlot{__shfl_xor(b.value, o), __shfl_xor(b.index, o)});
+  return b;
+}
+// the block's two sums; red: 2 * kRowWaves floats, which all have read when it returns
+__device__ __forceinline__ float2 row_block_sum(float a, float b, float *red) {
+  a = wave_sum(a);
+  b = wave_sum(b);
+  const int w = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) { red[2 * w] = a; red[2 * w + 1] = b; }
+  __syncthreads();
+  float2 s = make_float2(red[0], red[1]);
+#pragma unroll
+  for (int k = 1; k < kRowWaves; ++k) { s.x += red[2 * k]; s.y += red[2 * k + 1]; }
+  __syncthreads();
+  return s;
+}
+__device__ __forceinline__ BestSlot row_block_best(BestSlot b, float *red) {
+  b = wave_best(b);
+  const int w = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 0) { red[2 * w] = b.value; red[2 * w + 1] = __int_as_float(b.index); }
+  __syncthreads();
+  for (int k = 0; k < kRowWaves; ++k) b = better(b, BestSlot{red[2 * k], __float_as_int(red[2 * k + 1])});
+  __syncthreads();
+  return b;
+}
+
+// A state's masked log-softmax over its slots j0 .. j1 - 1: what its logits (ld: reads one) say of it, by a wave where
+// the state has at most 64 slots (WIDE == 1) and by the block otherwise -- a state's results do not depend on what is beside it.
+// A thread's first slot is read once and stays in registers.
+template <int WIDE>
+struct StateSoftmax {
+  static constexpr int STEP = WIDE ? kRowThreads : 64;
+  int j0, j1, first;       // this thread's slots: first, first + STEP, ..
+  bool on;                 // of the first one
+  float x;
+  float lse, entropy, n_valid;
+  int best;                // first slot that has the largest logit
+  static __device__ __forceinline__ float2 sum(float a, float b, float *red) {
+    if constexpr (WIDE) return row_block_sum(a, b, red);
+    else return make_float2(wave_sum(a), wave_sum(b));
+  }
+  // go(j, its logit) for this thread's slots that are not masked
+  template <typename Load, typename Go>
+  __device__ __forceinline__ void each(Load ld, const uint8_t *mask, Go go) const {
+    if (on) go(first, x);
+    if constexpr (WIDE)
+      for (int j = first + STEP; j < j1; j += STEP)
+        if (mask[j]) go(j, ld(j));
+  }
+  template <typename Load>
+  __device__ __forceinline__ StateSoftmax(Load ld, const uint8_t *mask, int begin, int end, float *red) {
+    j0 = begin; j1 = end;
+    first = j0 + (int)(threadIdx.x & (STEP - 1));
+    x = first < j1 ? ld(first) : 0.f;                    // (beside the mask's load, not behind it)
+    on = first < j1 && mask[first];
+    BestSlot b{-INFINITY, 0x7fffffff};
+    each(ld, mask, [&](int j, float v) { b = better(b, BestSlot{v, j}); });
+    if constexpr (WIDE) b = row_block_best(b, red);
+    else b = wave_best(b);
+    best = b.index;
+    float se = 0.f, cnt = 0.f;
+    each(ld, mask, [&](int, float v) { se += expf(v - b.value); cnt += 1.f; });
+    const float2 s = sum(se, cnt, red);
+    lse = b.value + logf(s.x);
+    n_valid = s.y;
+    float ent = 0.f;
+    each(ld, mask, [&](int, float v) { const float lp = v - lse; ent -= expf(lp) * lp; });
+    entropy = sum(ent, 0.f, red).x;
+  }
+  // what the heads give
+  template <typename Load>
+  __device__ __forceinline__ void write(Load ld, const uint8_t *mask, float *logp, float *entropy_out, int32_t *action) const {
+    if (first < j1) logp[first] = on ? x - lse : -INFINITY;
+    if constexpr (WIDE)
+      for (int j = first + STEP; j < j1; j += STEP) logp[j] = mask[j] ? ld(j) - lse : -INFINITY;
+    if (first == j0) { *entropy_out = entropy; *action = best - j0; }
+  }
+};
+
+// Both heads, forward, in one launch. The first blocks: the policy MLP of sixteen slots, of one or of several states;
+// the block that finishes a state's last slot (a per-state counter, which it also resets; none where a block has all of
+// them) does that state's masked log-softmax, entropy and first-max action. The last blocks: the mean
+// embedding of the valid slots of value_rows states and the value head on it, independent of the policy blocks.
+// Logits cross blocks through device-scope stores and loads (each completed before the block's
+// counter increment is issued), so no cache write-back or invalidation is needed. logp null: the logits alone.
+struct HeadsArgs {
+  RowFwdArgs policy, value;          // of the same widths; value.in1 is not read
+  const uint8_t *mask;
+  const int32_t *state_graph_ptr;
+  int G, S, value_rows;
+  int32_t *counter;
+  float *logp, *entropy;
+  int32_t *action;
+  float *zmean;
+};
+template <typename W>
+__global__ __launch_bounds__(kRowThreads, W::waves) void heads_kernel(const HeadsArgs a) {
+  extern __shared__ __align__(16) float sm[];
+  __shared__ float red[2 * kRowWaves];
+  __shared__ int sh_state[kRowTile], sh_done[kRowTile], sh_n_done;
+  __shared__ __align__(16) f32x4 part[kRowThreads];
+  __shared__ int n_valid[kRowThreads];
+  touch_args(a);
+  constexpr int H = W::w[0];
+  const int t = threadIdx.x, policy_blocks = (a.G + kRowTile - 1) / kRowTile, pitch = a.policy.pitch;
+  const bool is_value = (int)blockIdx.x >= policy_blocks;
+  const RowFwdArgs &mlp = is_value ? a.value : a.policy;            // (one copy of the layers' code for both)
+  const int slot0 = blockIdx.x * kRowTile;
+  const int s0 = ((int)blockIdx.x - policy_blocks) * a.value_rows, s1 = s0 + a.value_rows < a.S ? s0 + a.value_rows : a.S;
+  const float *y = row_forward<W, true>(mlp, is_value ? s0 : slot0, is_value ? s1 : a.G, sm, pitch, [&]() {
+    RowBiases<W> biases;
+    if (!is_value) {
+      // the block's slots; meanwhile find their states
+      RowInputs in;
+      in.request(mlp, H, slot0);
+      biases.request(mlp);
+      if (a.logp && t < kRowTile) sh_state[t] = -1;
+      __syncthreads();
+      in.store(mlp, H, H, slot0, sm, pitch);
+      biases.store(mlp, sm, pitch);
+      if (!a.logp) return;
+      for (int s = t; s < a.S; s += kRowThreads) {
+        const int p0 = a.state_graph_ptr[s], p1 = a.state_graph_ptr[s + 1];
+        for (int r = p0 > slot0 ? p0 - slot0 : 0; r < kRowTile && slot0 + r < p1; ++r) sh_state[r] = s;
+      }
+      return;
+    }
+    // the mean embedding of the valid slots: H / 4 threads cover a row with 16-byte loads, the 2048 / H thread groups
+    // take every (2048 / H)-th slot, eight or (H = 256) sixteen loads in flight each; the groups' sums are added in order
+    constexpr int U = H > 128 ? 16 : 8;
+    const float *emb = a.policy.in1;
+    const int tpr = H / 4, ng = kRowThreads / tpr, c4 = (t % tpr) * 4, q = t / tpr; 
+    for (int i = t; i < kRowTile * pitch; i += kRowThreads) sm[i] = 0.f;
+    biases.request(mlp);
+    biases.store(mlp, sm, pitch);
+    for (int s = s0; s < s1; ++s) {
+      const int j0 = a.state_graph_ptr[s], j1 = a.state_graph_ptr[s + 1];
+      f32x4 p = f32x4{0.f, 0.f, 0.f, 0.f};
+      int cnt = 0;
+      for (int j = j0 + q; j < j1; j += U * ng) {
+        f32x4 v[U];
+        bool on[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+          const int ji = j + i * ng < j1 ? j + i * ng : j;
+          v[i] = *(const f32x4 *)(emb + (size_t)ji * H + c4);
+          on[i] = j + i * ng < j1 && a.mask[ji];
+        }
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+          if (on[i]) { p += v[i]; ++cnt; }
+      }
+      part[t] = p;
+      n_valid[t] = cnt;
+      __syncthreads();
+      if (t < tpr) {
+        f32x4 acc = part[t];
+        int n = n_valid[0];
+        for (int k = 1; k < ng; ++k) { acc += part[k * tpr + t]; n += n_valid[k * tpr]; }
+        const float nv = (float)n;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] /= nv;
+        *(f32x4 *)(a.zmean + (size_t)s * H + c4) = acc;
+        *(f32x4 *)(sm + (s - s0) * pitch + c4) = acc;
+      }
+      __syncthreads();
+    }
+  });
+  if (is_value) return;
+  if (!a.logp) return;
+  __builtin_amdgcn_s_waitcnt(0x0F70);                              // vmcnt(0): this wave's logit stores have completed
+  __syncthreads();
+  if (t < kRowTile) {
+    // one thread per slot; that of a state's first slot here speaks for the state (the sixteen lanes are one wave's)
+    const int s = sh_state[t];
+    bool done = false;
+    if (s >= 0 && (t == 0 || sh_state[t - 1] != s)) {
+      int k = 1;
+      while (t + k < kRowTile && sh_state[t + k] == s) ++k;
+      const int slots = a.state_graph_ptr[s + 1] - a.state_graph_ptr[s];
+      done = k == slots;
+      if (!done && atomicAdd(&a.counter[s], k) + k == slots) {
+        a.counter[s] = 0;                                          // ready for the next launch
+        done = true;
+      }
+    }
+    const unsigned long long who = __ballot(done);
+    if (done) sh_done[__popcll(who & ((1ull << t) - 1))] = s;
+    if (t == 0) sh_n_done = __popcll(who);
+  }
+  __syncthreads();
+  const float *logit = a.policy.out;
+  auto with_logits = [&](int j0, int j1, auto go) {                // its own logits are still in LDS
+    if (j0 >= slot0 && j1 <= slot0 + kRowTile) go([&](int j) { return y[(j - slot0) * pitch]; });
+    else go([&](int j) { return __hip_atomic_load(logit + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); });
+  };
+  const int n_done = sh_n_done;
+  for (int i = 0; i < n_done; ++i) {
+    const int s = sh_done[i], j0 = a.state_graph_ptr[s], j1 = a.state_graph_ptr[s + 1];
+    if (j1 - j0 > 64) {
+      with_logits(j0, j1, [&](auto ld) { StateSoftmax<1>(ld, a.mask, j0, j1, red).write(ld, a.mask, a.logp, a.entropy + s, a.action + s); });
+    } else if (i % kRowWaves == t >> 6) {
+      with_logits(j0, j1, [&](auto ld) { StateSoftmax<0>(ld, a.mask, j0, j1, red).write(ld, a.mask, a.logp, a.entropy + s, a.action + s); });
+    }
+  }
+}
+
+// The same per state where a batch has more states than counters: one block per state, logits from memory.
+__global__ __launch_bounds__(kRowThreads) void state_policy_kernel(const float *logit, const uint8_t *mask, const int32_t *state_graph_ptr,
+                                                                   float *logp, float *entropy, int32_t *action) {
+  __shared__ float red[2 * kRowWaves];
+  const int s = blockIdx.x, j0 = state_graph_ptr[s], j1 = state_graph_ptr[s + 1];
+  auto ld = [&](int j) { return logit[j]; };
+  if (j1 - j0 > 64) StateSoftmax<1>(ld, mask, j0, j1, red).write(ld, mask, logp, entropy + s, action + s);
+  else if (threadIdx.x < 64 && j1 > j0) StateSoftmax<0>(ld, mask, j0, j1, red).write(ld, mask, logp, entropy + s, action + s);
+}
+
+// ---- backward: given dout [n_rows, width of the last layer] and every layer's saved output, the gradients dz[l] before
+// the layers' ReLUs (stored, for the weight gradients) and dx [n_rows, d_in].
+struct RowBwdArgs {
+  int relu_last;
+  RowMap map[3];           // map[0] is the last layer's: contraction over its outputs
+  const float *act[3];     // saved outputs of each layer
+  const float *dout;
+  int64_t n_rows;
+  float *dz[3];            // [n_rows, width of layer l]
+  float *dx;               // [n_rows, d_in]
+  int pitch;
+  // the policy head's dx also takes its state's share of the gradient of the mean embedding, and nothing where a slot
+  // is masked: dx[j] = mask[j] ? dx[j] + dmean[s] * inv_valid[s] : 0 (mask null: neither)
+  const uint8_t *mask;
+  const int32_t *state_graph_ptr;
+  const float *dmean, *inv_valid;
+  int S;
+};
+// LDS of a backward block: x, x2 and, of every layer below the last, the outputs whose ReLU the gradient passes (below the first: the
+// states' gradients of the mean embedding)
+inline size_t row_bwd_lds_floats(const RowBwdArgs &a) {
+  size_t n = 2 * a.pitch;
+  for (const RowMap &m : a.map)
+    if (m.w) n += row_pitch(m.n_out);
+  return kRowTile * n;
+}
+
+// Two rows a wave of a [*, w] array, row_of(r) for the block's row r < n (the last again past them): the first 256 columns
+// requested together, before any is waited for (16 bytes a lane where the width is a multiple of four, else four loads)
+struct RowPiece {
+  f32x4 v[2];
+  template <typename RowOf>
+  __device__ __forceinline__ void request(const float *src, int w, int n, RowOf row_of) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int r = 2 * (threadIdx.x >> 6) + i;
+      const float *q = src + (int64_t)row_of(r < n ? r : n - 1) * w;
+      if ((w & 3) == 0) {
+        v[i] = *(const f32x4 *)(q + (4 * lane < w ? 4 * lane : 0));
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[i][k] = q[4 * lane + k < w ? 4 * lane + k : w - 1];
+      }
+    }
+  }
+  // put(r, f, value) for the sixteen rows' w columns
+  template <typename RowOf, typename Put>
+  __device__ __forceinline__ void store(const float *src, int w, int n, RowOf row_of, Put put) const {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int r = 2 * (threadIdx.x >> 6) + i;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (4 * lane + k < w) put(r, 4 * lane + k, v[i][k]);
+      for (int f = 256 + lane; f < w; f += 64) put(r, f, src[(int64_t)row_of(r < n ? r : n - 1) * w + f]);
+    }
+  }
+};
+// The sixteen rows from row0, of which those below row_end exist (at least one); state, share (LDS, with MASKED only): the slots'
+// states and factors of the mean embedding's gradient, -1 where masked. first() writes them, and dout where that is this block's to write.
+template <typename W, bool MASKED, typename First>
+__device__ __forceinline__ void row_backward(const RowBwdArgs &a, int64_t row0, int64_t row_end, float *x, int pitch, const int *state,
+                                             const float *share, First first) {
+  constexpr int L = W::N;
+  static_assert(L == 2 || L == 3, "row-MLPs of two or three layers");
+  const int lane = threadIdx.x & 63, q4 = lane >> 4;
+  const int n = (int)(row_end - row0 < kRowTile ? row_end - row0 : kRowTile);
+  // what post takes, of each map
+  const int pitch0 = row_pitch(W::template out<0>(a.map)), pitch1 = row_pitch(W::template out<1>(a.map)), pitchl = row_pitch(W::template out<L - 1>(a.map));
+  float *const below0 = x + 2 * kRowTile * pitch, *const below1 = below0 + kRowTile * pitch0, *const below2 = below1 + kRowTile * pitch1;
+  float *const belowl = L > 2 ? below2 : below1;
+  (void)row_maps<W>(a.map, x, x + kRowTile * pitch, pitch,
+    [&]() {
+      auto own = [&](int r) { return row0 + r; };
+      auto of_state = [&](int r) { return state[r]; };
+      const int w = W::template in<0>(a.map), w0 = W::template out<0>(a.map), w1 = W::template out<1>(a.map), wl = W::template out<L - 1>(a.map);
+      RowPiece p0, p1, pr, pm, pd;
+      p0.request(a.act[L - 2], w0, n, own);
+      if (L > 2) p1.request(a.act[0], w1, n, own);
+      if (a.relu_last) pr.request(a.act[L - 1], w, n, own);
+      first();
+      if constexpr (MASKED) {
+        __syncthreads();
+        pm.request(a.dmean, wl, n, of_state);
+      }
+      pd.request(a.dout, w, n, own);
+      p0.store(a.act[L - 2], w0, n, own, [&](int r, int f, float v) { below0[r * pitch0 + f] = v; });
+      if (L > 2) p1.store(a.act[0], w1, n, own, [&](int r, int f, float v) { below1[r * pitch1 + f] = v; });
+      if (MASKED) pm.store(a.dmean, wl, n, of_state, [&](int r, int f, float v) { belowl[r * pitchl + f] = v; });
+      if (a.relu_last) pr.store(a.act[L - 1], w, n, own, [&](int r, int f, float v) { x[r * pitch + f] = v; });
+      float *dz = a.dz[L - 1] + row0 * w;
+      pd.store(a.dout, w, n, own, [&](int r, int f, float v) {
+        if (r >= n || (a.relu_last && !(x[r * pitch + f] > 0.f))) v = 0.f;
+        x[r * pitch + f] = v;
+        if (r < n) dz[r * w + f] = v;
+      });
+      const int wide = (w + 15) & ~15;
+      for (int f = w + lane; f < wide; f += 64) {
+        x[2 * (threadIdx.x >> 6) * pitch + f] = 0.f;
+        x[(2 * (threadIdx.x >> 6) + 1) * pitch + f] = 0.f;
+      }
+    },
+    [&](auto, int) { return 0.f; },
+    [&](auto m, int f, f32x4 &y) {
+      constexpr int M = decltype(m)::value;
+      const unsigned w = W::template out<M>(a.map);
+      float *to;
+      if constexpr (M + 1 < L) to = a.dz[L - 2 - M] + row0 * w;
+      else to = a.dx + row0 * w;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = 4 * q4 + i;
+        if (M + 1 < L) {
+          if (!((M ? below1[r * pitch1 + f] : below0[r * pitch0 + f]) > 0.f)) y[i] = 0.f;
+        } else if (MASKED) {
+          const float k = r < n ? share[r] : -1.f;
+          y[i] = k >= 0.f ? y[i] + belowl[r * pitchl + f] * k : 0.f;
+        }
+        if (r < n) to[r * w + f] = y[i];
+        else y[i] = 0.f;
+      }
+    });
+}
+template <typename W, bool MASKED>
+__global__ __launch_bounds__(kRowThreads, W::waves) void row_backward_kernel(const RowBwdArgs a) {
+  extern __shared__ __align__(16) float sm[];
+  __shared__ int state[kRowTile];
+  __shared__ float share[kRowTile];
+  const int64_t row0 = (int64_t)blockIdx.x * kRowTile;
+  touch_args(a);
+  row_backward<W, MASKED>(a, row0, a.n_rows, sm, a.pitch, state, share, [&]() {
+    if constexpr (MASKED) {
+      for (int s = threadIdx.x; s < a.S; s += kRowThreads) {
+        const int64_t p0 = a.state_graph_ptr[s] - row0, p1 = a.state_graph_ptr[s + 1] - row0;
+        for (int64_t r = p0 > 0 ? p0 : 0; r < kRowTile && r < p1; ++r) {
+          state[r] = s;
+          share[r] = a.mask[row0 + r] ? a.inv_valid[s] : -1.f;
+        }
+      }
+    }
+  });
+}
+
+// Backward of what a state's slots have in common, value_rows states per block: from the logits and the outputs' gradients
+//   dlogit_k = c_k - p_k * sum_valid c  -  dent * p_k * (logp_k + entropy),  c = dlogp      (0 when masked)
+// and the value head's backward pass (whose dx is the gradient of the mean embedding).
+struct HeadsStateBwdArgs {
+  RowBwdArgs value;
+  const float *logit;
+  const uint8_t *mask;
+  const int32_t *state_graph_ptr;
+  const float *dlogp, *dentropy;
+  float *dlogit, *inv_valid;
+  int S, value_rows;
+};
+template <typename W>
+__global__ __launch_bounds__(kRowThreads, W::waves) void heads_state_bwd_kernel(const HeadsStateBwdArgs a) {
+  extern __shared__ __align__(16) float sm[];
+  __shared__ float red[2 * kRowWaves];
+  const int t = threadIdx.x, s0 = blockIdx.x * a.value_rows, s1 = s0 + a.value_rows < a.S ? s0 + a.value_rows : a.S;
+  touch_args(a);
+  row_backward<W, false>(a.value, s0, s1, sm, a.value.pitch, nullptr, nullptr, [&]() {
+    auto ld = [&](int j) { return a.logit[j]; };
+    for (int s = s0; s < s1; ++s) {
+      const int j0 = a.state_graph_ptr[s], j1 = a.state_graph_ptr[s + 1];
+      auto slots = [&](auto wide) {
+        using Softmax = StateSoftmax<decltype(wide)::value>;
+        const int at = j0 + (int)(t & (Softmax::STEP - 1));
+        const float first = at < j1 ? a.dlogp[at] : 0.f, de = a.dentropy[s];
+        const Softmax m(ld, a.mask, j0, j1, red);
+        auto c = [&](int j) { return j == m.first ? first : a.dlogp[j]; };
+        float cs = 0.f;
+        m.each(ld, a.mask, [&](int j, float) { cs += c(j); });
+        cs = Softmax::sum(cs, 0.f, red).x;
+        for (int j = m.first; j < j1; j += Softmax::STEP)
+          if (j == m.first ? !m.on : !a.mask[j]) a.dlogit[j] = 0.f;
+        m.each(ld, a.mask, [&](int j, float x) {
+          const float lp = x - m.lse, p = expf(lp);
+          a.dlogit[j] = c(j) - p * cs - de * p * (lp + m.entropy);
+        });
+        if (m.first == j0) a.inv_valid[s] = 1.f / m.n_valid;
+      };
+      if (j1 - j0 > 64) slots(MapIndex<1>());
+      else if ((s - s0) % kRowWaves == t >> 6) slots(MapIndex<0>());    // (the same choice for all threads of a wave)
+    }
+  });
+}

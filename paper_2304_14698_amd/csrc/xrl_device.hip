@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "heads.hip.h"
+#include "rowmm.hip.h"
 #include "mlp2.hip.h"
 #include "mlp2_bwd.hip.h"
 #include "mlp2_bwdz.hip.h"
@@ -66,12 +67,13 @@ struct EncMlp {           // device pointers of one encoder MLP
 //   for the forward's layer 2 and for the backward's W2^T and W1^T products.
 // SWZ_FRAGMENT3, SWZ_CHAIN3: those orders for V = 8, each fragment as the three bf16 parts of its fp32 elements, the
 //   lanes' first parts, then their second, then their third.
-// SWZ_COPY: n floats as they are.
+// SWZ_ROWS: [output tile][contraction group][lane][j]: lane l, element j of the row-MLPs' fragments (RowMap) holds
+//   W[16 * group + 4 * (l / 16) + j][16 * tile + l % 16] (cb: contraction groups, n: outputs), zero beyond K and n.
 // W[k][f] = weights[src + k' * sk + f * sf], k' = k, or k + k_gap from k_gap_at on.
-enum { SWZ_FRAGMENT = 0, SWZ_CHAIN, SWZ_FRAGMENT3, SWZ_CHAIN3, SWZ_COPY };
+enum { SWZ_FRAGMENT = 0, SWZ_CHAIN, SWZ_FRAGMENT3, SWZ_CHAIN3, SWZ_ROWS };
 struct SwzJob {
   int64_t dst;       // byte offset of the copy
-  int64_t src, n;    // flat offset; SWZ_COPY: floats
+  int64_t src, n;    // flat offset; SWZ_ROWS: outputs
   int64_t groups;    // lane fragments of V elements
   int32_t kind, V, bf16, K, cb, sk, sf, k_gap_at, k_gap, pad;
 };
@@ -101,14 +103,19 @@ __global__ __launch_bounds__(256) void arrange_weights_kernel(const SwzJob *jobs
   }
   const SwzJob j = jobs[blockIdx.y];
   for (; i < j.groups; i += stride) {
-    if (j.kind == SWZ_COPY) {
-      float *o = (float *)(dst + j.dst);
-      for (int64_t k = 4 * i; k < 4 * i + 4 && k < j.n; ++k) o[k] = w[j.src + k];
-      continue;
-    }
     const int l = (int)(i & 63), g = l >> 5;
     const int64_t t = i >> 6;
     const int cb = (int)(t % j.cb), s = (int)(t / j.cb);
+    if (j.kind == SWZ_ROWS) {
+      const int f = 16 * s + (l & 15), k0 = 16 * cb + 4 * (l >> 4), fc = f < (int)j.n ? f : (int)j.n - 1;
+      f32x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = w[j.src + (int64_t)(k0 + e < j.K ? k0 + e : j.K - 1) * j.sk + (int64_t)fc * j.sf];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) if (k0 + e >= j.K || f >= (int)j.n) o[e] = 0.f;
+      ((f32x4 *)(dst + j.dst))[i] = o;
+      continue;
+    }
     const float *p = w + j.src + (int64_t)(32 * cb + (l & 31)) * j.sf;
     const bool frag = j.kind == SWZ_FRAGMENT || j.kind == SWZ_FRAGMENT3;
     float v[8];
@@ -152,7 +159,7 @@ static const char *const kTimedNames[TK_COUNT] = {"embed", "edge", "edge_fixup",
                                                   "bwd_embed", "wgrad", "grad_gather", "gat_bwd", "resident",
                                                   "wgrad_edge", "wgrad_node", "wgrad_embed", "round", "levels"};
 
-constexpr int64_t kMaxFusedSlots = 4096;   // largest G the single-launch heads kernel takes
+constexpr int64_t kMaxFusedStates = 4096;  // most states that the heads' launch counts slots of
 constexpr int kCounts = 3 * kMaxLevels;
 constexpr int64_t kPersistentMinRows = 8192;   // rows from which the persistent kernels replace the split one
 constexpr size_t kZeroRow = 1024 + 256;        // 1 KB of zeros and behind it one element that is 1 (see WgradLaunch)
@@ -165,7 +172,7 @@ constexpr int64_t kClusterMaxGraphs = 256; // largest G of the one-launch encode
 // the logits when the caller does not ask for them, and the per-state mean embeddings. One copy
 // per GPU, held until the process ends; host code never passes the array's name to a kernel, only
 // the address hipGetSymbolAddress reports for the current device (static_scratch below).
-constexpr int64_t kStaticMaxSlots = kMaxFusedSlots;          // G
+constexpr int64_t kStaticMaxSlots = kMaxFusedStates;         // G
 constexpr int64_t kStaticMaxStateFloats = 65536;             // S * hidden
 constexpr size_t kStaticCounterOff = 0;
 constexpr size_t kStaticLogitOff = kStaticCounterOff + sizeof(int32_t) * kStaticMaxSlots;
@@ -190,7 +197,7 @@ struct xrl_ctx {
   int64_t resident_max_graphs = 0;   // largest batch (graphs) for the one-launch encoder (XRL_RESIDENT_MAX_GRAPHS)
   int64_t resident_max_tiles = 0;    // ... and the most 32-row tiles (nodes, or edges) of one graph (XRL_RESIDENT_MAX_TILES)
   float *d_w = nullptr;         // flat fp32 weights
-  int32_t *d_counter = nullptr; // kMaxFusedSlots per-state counters of policy_value_kernel, zero between launches
+  int32_t *d_counter = nullptr; // kMaxFusedStates per-state counters of heads_kernel, zero between launches
   unsigned *d_arrived = nullptr; // kClusterMaxGraphs per-graph counters of encode_cluster_kernel, zero between launches
   unsigned *h_fault = nullptr;   // pinned host word a kernel sets when one of its bounded waits gives up ...
   unsigned *d_fault = nullptr;   // ... and the address kernels write it through
@@ -224,7 +231,7 @@ struct xrl_ctx {
   std::vector<const void *> gatW;   // XRL_ROUND_GAT: fragment-ordered W of each round
   std::vector<const void *> gatWt;  //   and of W^T (backward: dh = dz W^T)
   std::vector<float *> gat_ss, gat_sd;   // saved per-node scores of each round (inside ws)
-  std::unordered_map<int64_t, const float *> row_w;   // readout / head matrices, 16-byte aligned copies
+  std::unordered_map<int64_t, RowMap> row_fwd, row_bwd;   // readout and head matrices in fragment order, and transposed
   // workspaces (grow-only): encoder activations, and a separate small one for the heads
   char *ws = nullptr;
   size_t ws_bytes = 0;
@@ -704,17 +711,20 @@ int plan_weights(xrl_ctx *c) {
       add(c->L.node[r], false);
     }
   }
-  // the row-MLPs read their matrices with 16-byte loads: aligned copies, keyed by flat offset
-  std::vector<std::pair<int64_t, size_t>> row_off;
-  auto copy = [&](int64_t src, int64_t n) {
+  // the row-MLPs' matrices, keyed by flat offset: fragments of y = x W and of its transpose
+  struct RowRef { int64_t w; int n_in, n_out; size_t fwd, bwd; };
+  std::vector<RowRef> row_maps;
+  auto rows = [&](int64_t w, int K, int64_t n, int sk, int sf) {
     SwzJob j = {};
-    j.kind = SWZ_COPY; j.V = 4; j.src = src; j.n = n;
-    j.groups = (n + 3) / 4;
+    j.kind = SWZ_ROWS; j.V = 4; j.K = K; j.n = n; j.cb = (K + 15) / 16; j.src = w; j.sk = sk; j.sf = sf;
+    j.groups = (n + 15) / 16 * j.cb * 64;
     return put(j);
   };
   for (const MlpRef *r : {&c->L.readout, &c->L.policy, &c->L.value})
-    for (int l = 0; l < r->n_layers; ++l)
-      row_off.push_back({r->w[l], copy(r->w[l], (int64_t)r->d_in[l] * r->d_out[l])});
+    for (int l = 0; l < r->n_layers; ++l) {
+      const int in = r->d_in[l], out = r->d_out[l];
+      row_maps.push_back({r->w[l], in, out, rows(r->w[l], in, out, out, 1), rows(r->w[l], out, in, 1, out)});
+    }
   const size_t o_jobs = align_up(off);
   c->swz_bytes = o_jobs + jobs.size() * sizeof(SwzJob);
   HIP_TRY(hipMalloc((void **)&c->d_swz, c->swz_bytes));
@@ -753,7 +763,10 @@ int plan_weights(xrl_ctx *c) {
     e.nslabx = ref.nsx;
     e.table = c->d_w + r.w[0] + (size_t)m.d_edge * H;    // meaningful for the embed MLP only
   };
-  for (const auto &ro : row_off) c->row_w[ro.first] = (const float *)(c->d_swz + ro.second);
+  for (const RowRef &r : row_maps) {
+    c->row_fwd[r.w] = RowMap{(const f32x4 *)(c->d_swz + r.fwd), r.n_in, r.n_out};
+    c->row_bwd[r.w] = RowMap{(const f32x4 *)(c->d_swz + r.bwd), r.n_out, r.n_in};
+  }
   size_t i = 0;
   bind(c->embed, refs[i++], c->L.embed);
   if (gat) {
@@ -1257,84 +1270,96 @@ int launch_gat_round(xrl_ctx *c, const GatArgs &a, const GatNext &next) {
   return c->m.hidden == 64 ? launch_gat_round_h<T, 64>(c, a, next) : launch_gat_round_h<T, 128>(c, a, next);
 }
 
-RowMlpArgs rowmlp_args(xrl_ctx *c, const MlpRef &r, bool relu_last, const float *in1, int w1, const float *in2,
-                       int w2, int64_t n_rows, float *out, float *const *act, int *dmax_out = nullptr) {
-  RowMlpArgs a;
-  memset(&a, 0, sizeof(a));
-  a.n_layers = r.n_layers;
-  a.relu_last = relu_last ? 1 : 0;
-  int dmax = r.d_in[0];
-  for (int l = 0; l < r.n_layers; ++l) {
-    const auto it = c->row_w.find(r.w[l]);
-    a.W[l] = it != c->row_w.end() ? it->second : c->d_w + r.w[l];
-    a.b[l] = c->d_w + r.b[l];
-    a.d_in[l] = r.d_in[l];
-    a.d_out[l] = r.d_out[l];
-    a.act[l] = act ? act[l] : nullptr;
-    if (r.d_out[l] > dmax) dmax = r.d_out[l];
-  }
-  a.in1 = in1; a.in2 = in2; a.w1 = w1; a.w2 = w2; a.n_rows = n_rows; a.out = out;
-  if (dmax_out) *dmax_out = dmax;
-  return a;
+// (Beyond 64 KB, with what a kernel holds besides, a launch has to be allowed its LDS: heads 512 wide, hundreds of global attributes.)
+template <typename Kernel>
+int allow_row_lds(Kernel kern, size_t lds) {
+  if (lds > 40 * 1024) HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  return XRL_OK;
 }
-
-// Rows per block of block_row_mlp's kernels, which share a layer's weights: where the blocks would fill less than half of the
-// chip a row's latency counts; from four rows per compute unit on the weights' way from L2 does. us of policy_value_kernel at
-// 1 / 2 / 4 rows per block: H = 128, 13 slots 13.9 / 15.6 / 19.0, 129 17.1 / 16.4 / 19.2, 262 18.7 / 18.0 / 20.4, 2096
-// 50.2 / 36.5 / 26.3; H = 256, 257 slots 43.3 / 37.4 / 36.7.
-template <typename Go>
-void by_rows(const xrl_ctx *c, int64_t n, Go go) {
-  if (n < c->n_cu / 2) go(std::integral_constant<int, 1>());
-  else if (n < 4 * c->n_cu) go(std::integral_constant<int, 2>());
-  else go(std::integral_constant<int, 4>());
-}
-
-int launch_rowmlp(xrl_ctx *c, const MlpRef &r, bool relu_last, const float *in1, int w1,
-                  const float *in2, int w2, int64_t n_rows, float *out, float *const *act) {
-  if (n_rows <= 0) return XRL_OK;
-  int dmax = 0;
-  const RowMlpArgs a = rowmlp_args(c, r, relu_last, in1, w1, in2, w2, n_rows, out, act, &dmax);
-  if (n_rows <= 4096)
-    by_rows(c, n_rows, [&](auto rows) {
-      constexpr int ROWS = decltype(rows)::value;
-      rowmlp_kernel<ROWS><<<dim3((unsigned)((n_rows + ROWS - 1) / ROWS)), dim3(256), (size_t)ROWS * (1024 + 2 * dmax) * sizeof(float),
-                            c->stream>>>(a);                     // (dmax <= 512: at most 32 KB of LDS)
-    });
-  else
-    rowmlp_kernel<8><<<dim3((unsigned)((n_rows + 7) / 8)), dim3(256), (size_t)2 * 8 * dmax * sizeof(float), c->stream>>>(a);
+template <typename Kernel, typename Args>
+int launch_rows(Kernel kern, const Args &a, int64_t blocks, size_t lds_floats, hipStream_t stream) {
+  const size_t lds = lds_floats * sizeof(float);
+  if (int rc = allow_row_lds(kern, lds)) return rc;
+  kern<<<dim3((unsigned)blocks), dim3(kRowThreads), lds, stream>>>(a);
   HIP_TRY(hipGetLastError());
   return XRL_OK;
 }
+inline int64_t row_blocks(int64_t n) { return (n + kRowTile - 1) / kRowTile; }
 
-// Policy MLP, per-state softmax statistics and value head (Section 3.3.2): one launch for batches
-// of up to kMaxFusedSlots slots, otherwise the row-MLP kernel followed by the per-state kernel.
-// pact / vact (nullable) receive every layer's output for the backward pass.
+// go(forward widths, backward widths) of the heads and of the readout MLP: the paper's head widths are known to the kernels, any
+// others asked for; the readout's backward pass stops at the pool (the global attributes are inputs)
+template <typename Go>
+int with_head_widths(const xrl_ctx *c, Go go) {
+  const bool paper = c->m.head_hidden[0] == 256 && c->m.head_hidden[1] == 64;
+  auto of = [&](auto h) -> int {
+    constexpr int H = decltype(h)::value;
+    return paper ? go(RowWidths<H, 256, 64, 1>(), RowWidths<1, 64, 256, H>()) : go(RowWidths<H, 0, 0, 1>(), RowWidths<1, 0, 0, H>());
+  };
+  return c->m.hidden == 64 ? of(std::integral_constant<int, 64>()) : c->m.hidden == 128 ? of(std::integral_constant<int, 128>()) :
+                                                                                         of(std::integral_constant<int, 256>());
+}
+template <typename Go>
+int with_readout_widths(const xrl_ctx *c, Go go) {
+  return c->m.hidden == 64 ? go(RowWidths<0, 64, 64>(), RowWidths<64, 64, 64>()) :
+         c->m.hidden == 128 ? go(RowWidths<0, 128, 128>(), RowWidths<128, 128, 128>()) : go(RowWidths<0, 256, 256>(), RowWidths<256, 256, 256>());
+}
+
+RowFwdArgs row_fwd_args(const xrl_ctx *c, const MlpRef &r, bool relu_last, const float *in1, int w1, const float *in2, int w2,
+                        int64_t n_rows, float *out, float *const *act) {
+  RowFwdArgs a;
+  memset(&a, 0, sizeof(a));
+  a.relu_last = relu_last ? 1 : 0;
+  int widest = r.d_in[0];
+  for (int l = 0; l < r.n_layers; ++l) {
+    a.map[l] = c->row_fwd.at(r.w[l]);
+    a.b[l] = c->d_w + r.b[l];
+    a.act[l] = act ? act[l] : nullptr;
+    widest = std::max(widest, r.d_out[l]);
+  }
+  a.in1 = in1; a.in2 = in2; a.w1 = w1; a.w2 = w2; a.n_rows = n_rows; a.out = out;
+  a.pitch = row_pitch(widest);
+  return a;
+}
+int launch_readout(xrl_ctx *c, const RowFwdArgs &a) {
+  if (a.n_rows <= 0) return XRL_OK;
+  return with_readout_widths(c, [&](auto fwd, auto) {
+    return launch_rows(row_forward_kernel<decltype(fwd)>, a, row_blocks(a.n_rows), row_lds_floats(a.pitch), c->stream);
+  });
+}
+
+// States per block of what the heads do a state at a time: one while each gets a block of its own on the chip, then as many as
+// share the value head's fragments
+inline int value_rows(const xrl_ctx *c, int64_t S) {
+  return (int)std::min<int64_t>(kRowTile, (S + c->n_cu - 1) / c->n_cu);
+}
+// Policy MLP, per-state softmax statistics and value head (Section 3.3.2) in one launch; a batch of more states than there
+// are counters runs the softmax in a second one. pact / vact (nullable) receive every layer's output for the backward
+// pass, which has no use for what the softmax gives: logp null leaves it out.
 int launch_heads(xrl_ctx *c, const xrl_batch *b, const float *d_emb, float *logit, float *logp, float *entropy,
-                 int32_t *action, float *zmean, float *value, float *const *pact, float *const *vact) {
+                 int32_t *action, float *zmean, float *value, float *const *pact, float *const *vact, int32_t *counter) {
   const int H = c->m.hidden;
   const xrl_batch_device &d = b->dev;
-  const RowMlpArgs va = rowmlp_args(c, c->L.value, false, zmean, H, nullptr, 0, b->S, value, vact);
-  if (b->G <= kMaxFusedSlots) {
-    const RowMlpArgs pa = rowmlp_args(c, c->L.policy, false, d_emb, H, nullptr, 0, b->G, logit, pact);
-    by_rows(c, b->G, [&](auto rows) {
-      constexpr int ROWS = decltype(rows)::value;
-      policy_value_kernel<ROWS><<<dim3((unsigned)((b->G + ROWS - 1) / ROWS + b->S)), dim3(256), 0, c->stream>>>(
-          pa, d.mask, d.state_graph_ptr, (int)b->G, (int)b->S, H, c->d_counter, logp, entropy, action, zmean, va);
-    });
-    const hipError_t le = hipGetLastError();
-    if (le != hipSuccess) {
-      // (a launch that the runtime rejected has not run; one that failed later may have left
-      // counters of unfinished states above zero: they go back to zero before the next use)
-      (void)hipMemsetAsync(c->d_counter, 0, sizeof(int32_t) * kMaxFusedSlots, c->stream);
-      return fail(XRL_ERR_HIP, "policy_value_kernel: %s", hipGetErrorString(le));
-    }
-    return XRL_OK;
+  HeadsArgs a;
+  a.policy = row_fwd_args(c, c->L.policy, false, d_emb, H, nullptr, 0, b->G, logit, pact);
+  a.value = row_fwd_args(c, c->L.value, false, nullptr, H, nullptr, 0, b->S, value, vact);
+  const bool counted = b->S <= kMaxFusedStates;
+  a.mask = d.mask; a.state_graph_ptr = d.state_graph_ptr; a.G = (int)b->G; a.S = (int)b->S;
+  a.value_rows = value_rows(c, b->S);
+  a.counter = counter; a.logp = counted ? logp : nullptr; a.entropy = entropy; a.action = action; a.zmean = zmean;
+  const int64_t blocks = row_blocks(b->G) + (b->S + a.value_rows - 1) / a.value_rows;
+  const int rc = with_head_widths(c, [&](auto fwd, auto) {
+    return launch_rows(heads_kernel<decltype(fwd)>, a, blocks, row_lds_floats(a.policy.pitch), c->stream);
+  });
+  if (rc) {
+    // (a launch that the runtime rejected has not run; one that failed later may have left
+    // counters of unfinished states above zero: they go back to zero before the next use)
+    if (counter == c->d_counter) (void)hipMemsetAsync(counter, 0, sizeof(int32_t) * kMaxFusedStates, c->stream);
+    return rc;
   }
-  int rc = launch_rowmlp(c, c->L.policy, false, d_emb, H, nullptr, 0, b->G, logit, pact);
-  if (rc) return rc;
-  state_policy_kernel<<<dim3((unsigned)b->S), dim3(256), 0, c->stream>>>(
-      logit, d.mask, d.state_graph_ptr, d_emb, H, logp, entropy, action, zmean, va);
-  HIP_TRY(hipGetLastError());
+  if (logp && !counted) {
+    state_policy_kernel<<<dim3((unsigned)b->S), dim3(kRowThreads), 0, c->stream>>>(logit, d.mask, d.state_graph_ptr, logp, entropy, action);
+    HIP_TRY(hipGetLastError());
+  }
   return XRL_OK;
 }
 
@@ -1559,43 +1584,27 @@ int queue_wgrad(xrl_ctx *c, WgradQueue &q, const WgradJob &job) {
   return XRL_OK;
 }
 
-RowMlpBwdArgs rowmlp_bwd_args(xrl_ctx *c, const MlpRef &r, bool relu_last, float *const *act, const float *dout,
-                              int64_t n_rows, float *const *dz, float *dx) {
-  RowMlpBwdArgs a;
+RowBwdArgs row_bwd_args(const xrl_ctx *c, const MlpRef &r, bool relu_last, float *const *act, const float *dout,
+                        int64_t n_rows, float *const *dz, float *dx) {
+  RowBwdArgs a;
   memset(&a, 0, sizeof(a));
-  a.n_layers = r.n_layers;
   a.relu_last = relu_last ? 1 : 0;
+  int widest = r.d_in[0];
   for (int l = 0; l < r.n_layers; ++l) {
-    const auto it = c->row_w.find(r.w[l]);                  // (16-byte aligned)
-    a.W[l] = it != c->row_w.end() ? it->second : c->d_w + r.w[l];
-    a.d_in[l] = r.d_in[l];
-    a.d_out[l] = r.d_out[l];
+    a.map[r.n_layers - 1 - l] = c->row_bwd.at(r.w[l]);
     a.act[l] = act[l];
     a.dz[l] = dz[l];
+    widest = std::max(widest, r.d_out[l]);
   }
   a.dout = dout; a.n_rows = n_rows; a.dx = dx;
+  a.pitch = row_pitch(widest);
   return a;
 }
-// a's rows and, if given, b's in one launch (see rowmlp_bwd_kernel for the rows per block)
-int launch_rowmlp_bwd(xrl_ctx *c, const RowMlpBwdArgs &a, const RowMlpBwdArgs *b = nullptr) {
-  RowMlpBwdArgs other;
-  memset(&other, 0, sizeof(other));
-  if (b) other = *b;
-  if (a.n_rows + other.n_rows <= 0) return XRL_OK;
-  int dmax = 1;
-  for (const RowMlpBwdArgs *m : {&a, (const RowMlpBwdArgs *)&other})
-    for (int l = 0; l < m->n_layers; ++l) dmax = std::max(dmax, std::max(m->d_in[l], m->d_out[l]));
-  auto go = [&](auto rows) -> int {
-    constexpr int ROWS = decltype(rows)::value;
-    const int64_t blocks = (a.n_rows + ROWS - 1) / ROWS + (other.n_rows + ROWS - 1) / ROWS;
-    rowmlp_bwd_kernel<ROWS><<<dim3((unsigned)blocks), dim3(256), (size_t)2 * ROWS * dmax * sizeof(float), c->stream>>>(a, other);
-    HIP_TRY(hipGetLastError());
-    return XRL_OK;
-  };
-  if (a.n_rows < 2 * c->n_cu) return go(std::integral_constant<int, 1>());
-  if (a.n_rows < 4 * c->n_cu) return go(std::integral_constant<int, 2>());
-  if (a.n_rows < 8 * c->n_cu) return go(std::integral_constant<int, 4>());
-  return go(std::integral_constant<int, 8>());
+int launch_readout_backward(xrl_ctx *c, const RowBwdArgs &a) {
+  if (a.n_rows <= 0) return XRL_OK;
+  return with_readout_widths(c, [&](auto, auto bwd) {
+    return launch_rows(row_backward_kernel<decltype(bwd), false>, a, row_blocks(a.n_rows), row_bwd_lds_floats(a), c->stream);
+  });
 }
 
 // dW, db of every layer of one or two small row-MLPs in one launch (and one reduction): x of layer 0 is
@@ -1660,24 +1669,6 @@ int launch_small_wgrads(xrl_ctx *c, const SmallWgradMlp *mlps, int n_mlps, float
   if (entries > 0) small_wgrad_reduce_kernel<<<dim3((unsigned)entries), dim3(256), 0, c->stream>>>(a);
   HIP_TRY(hipGetLastError());
   return XRL_OK;
-}
-
-// demb[j, :] = mask[j] ? demb[j, :] + dz[s, :] * inv_n[s] : 0 for the slots j of state s; one block
-// per slot (a batch may be a single state of hundreds of slots), which finds its state by bisection
-__global__ void demb_combine_kernel(float *demb, const float *dzs, const float *inv_n, const uint8_t *mask,
-                                    const int32_t *state_graph_ptr, int S, int H) {
-  const int j = blockIdx.x;
-  int lo = 0, hi = S;                       // state_graph_ptr[lo] <= j < state_graph_ptr[hi]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (state_graph_ptr[mid] <= j) lo = mid; else hi = mid;
-  }
-  const float w = inv_n[lo];
-  const bool on = mask[j] != 0;
-  for (int f = threadIdx.x; f < H; f += blockDim.x) {
-    const size_t o = (size_t)j * H + f;
-    demb[o] = on ? demb[o] + dzs[(size_t)lo * H + f] * w : 0.f;
-  }
 }
 
 // dh[n, :] = dx[graph(n), :H] (divided by the graph's node count for the mean readout), stored in
@@ -2312,7 +2303,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   acc((size_t)N0 * Kp * sizeof(T));
   const size_t part = std::max(wgrad_partial_floats(c), small_wgrad_partial_floats(c->L.readout, G));
   acc(part * 4);
-  acc((size_t)G * H * 4); acc((size_t)G * H * 4); acc((size_t)G * (H + Dg) * 4);
+  for (int i = 0; i < 3; ++i) acc((size_t)G * H * 4);
   if (gat) {                                                       // softmax weights and score gradients
     for (int i = 0; i < 2; ++i) acc((size_t)maxE * 4);
     for (int i = 0; i < 4; ++i) acc((size_t)maxN * 4);
@@ -2343,7 +2334,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   T *xrows = bump.take<T>((size_t)N0 * Kp);
   float *partial = bump.take<float>(part);
   float *rdz[3] = {bump.take<float>((size_t)G * H), bump.take<float>((size_t)G * H), nullptr};
-  float *rdx = bump.take<float>((size_t)G * (H + Dg));
+  float *rdx = bump.take<float>((size_t)G * H);
   float *g_avec = nullptr, *g_ale = nullptr, *g_due = nullptr, *g_als = nullptr, *g_dus = nullptr, *g_dss = nullptr, *g_dsd = nullptr;
   if (gat) {
     g_ale = bump.take<float>((size_t)maxE); g_due = bump.take<float>((size_t)maxE);
@@ -2411,7 +2402,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   if (!gat && (rc = next_grads(R > 0 ? lev(R).N : N0, &node_grads, per_mlp))) return rc;
   // ---- global-update layer backward
   float *ract[3] = {c->ro_act[0], c->ro_act[1], nullptr};
-  if ((rc = launch_rowmlp_bwd(c, rowmlp_bwd_args(c, c->L.readout, true, ract, d_demb, G, rdz, rdx)))) return rc;
+  if ((rc = launch_readout_backward(c, row_bwd_args(c, c->L.readout, true, ract, d_demb, G, rdz, rdx)))) return rc;
   const SmallWgradMlp readout = {&c->L.readout, c->pool, d.graph_global, H, Dg, ract, rdz, G};
   if ((rc = launch_small_wgrads(c, &readout, 1, dweights, partial, part))) return rc;
   // The gradient w.r.t. the last node states is the pool's, the same row for every node of a graph.
@@ -2422,17 +2413,17 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   if (q) {
     // (a reduced batch: summed over each class's nodes of all graphs)
     broadcast_dpool_kernel<float><<<dim3((unsigned)((G * (H / 4) + 255) / 256)), dim3(256), 0, c->stream>>>(
-        rdx, H + Dg, nullptr, d.graph_node_ptr, m.readout == XRL_READOUT_MEAN, G, H, dpool_rows);
+        rdx, H, nullptr, d.graph_node_ptr, m.readout == XRL_READOUT_MEAN, G, H, dpool_rows);
     const uint16_t *mask = kept ? c->ym_node[R - 1] : nullptr;
     dz2_given = mask != nullptr;
     if ((rc = contract(float(), dpool_rows, q->mem_graph, q->mem_ptr, q->mem_seg, N, mask, mask ? node_grads.dz2 : dhA, (size_t)G * H * 4))) return rc;
   } else if (N > 0) {
     if (dpool_table)
       broadcast_dpool_kernel<T><<<dim3((unsigned)((G * (H / 4) + 255) / 256)), dim3(256), 0, c->stream>>>(
-          rdx, H + Dg, nullptr, d.graph_node_ptr, m.readout == XRL_READOUT_MEAN, G, H, dhA);
+          rdx, H, nullptr, d.graph_node_ptr, m.readout == XRL_READOUT_MEAN, G, H, dhA);
     else
       broadcast_dpool_kernel<T><<<dim3((unsigned)((N * (H / 4) + 255) / 256)), dim3(256), 0, c->stream>>>(
-          rdx, H + Dg, d.node_graph, d.graph_node_ptr, m.readout == XRL_READOUT_MEAN, N, H, dhA);
+          rdx, H, d.node_graph, d.graph_node_ptr, m.readout == XRL_READOUT_MEAN, N, H, dhA);
   }
   bool dy_by_graph = dpool_table;          // until the first backward kernel has consumed the table
 
@@ -2744,21 +2735,40 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   auto readout = [&](const T *hlast, const int32_t *cls) -> int {
     int rc = XRL_OK;
     if (N <= 4096 * G) {
-      // many graphs of moderate size: one block per graph sums its nodes and runs the readout MLP
-      Timed t(c, TK_POOL);
-      int dmax = 0;
-      const RowMlpArgs ra = rowmlp_args(c, c->L.readout, true, c->pool, H, d.graph_global, m.d_global, G, d_emb,
-                                        c->ro_act, &dmax);
-      const size_t lds = (size_t)(256 * PV + 2 * dmax) * sizeof(float);
+      // Many graphs of moderate size: a block per graph. Where each has a compute unit to itself the readout MLP follows in the same
+      // launch; a block more, and every unit's way to the weights and its matrix cores are shared by MLPs of one row in sixteen: us in
+      // one launch / two, 9 graphs of 50 nodes, H = 64 5.7 / 6.8, 15 of 338, H = 128 8.1 / 9.8, 129 of 565 10.3 / 12.4, 257 of 1253,
+      // H = 256 38 / 33, 1040 of 338, H = 128 31 / 18, 2080 58 / 39, 4624 of 940, H = 256 334 / 145. (Sums by 512 threads a graph until two
+      // blocks meet on a unit, 257 graphs 22 / 18, then 256: 1040 graphs 13.8 / 11.4.)
+      const RowFwdArgs ra = row_fwd_args(c, c->L.readout, true, c->pool, H, d.graph_global, m.d_global, G, d_emb, c->ro_act);
       const int mean = m.readout == XRL_READOUT_MEAN ? 1 : 0;
-      if (cls)
-        graph_readout_kernel<T, PV, 8, true><<<dim3((unsigned)G), dim3(256), lds, c->stream>>>(
-            hlast, d.graph_node_ptr, H, mean, c->pool, ra, cls);
-      else
-        graph_readout_kernel<T, PV, 8, false><<<dim3((unsigned)G), dim3(256), lds, c->stream>>>(
-            hlast, d.graph_node_ptr, H, mean, c->pool, ra, nullptr);
-      HIP_TRY(hipGetLastError());
-      return XRL_OK;
+      if (G > c->n_cu) {
+        { Timed t(c, TK_POOL);
+          rc = with_readout_widths(c, [&](auto fwd, auto) -> int {
+            constexpr int HH = decltype(fwd)::w[1];
+            auto go = [&](auto threads) -> int {
+              constexpr int THREADS = decltype(threads)::value;
+              auto kern = cls ? graph_pool_kernel<T, PV, HH, true, THREADS> : graph_pool_kernel<T, PV, HH, false, THREADS>;
+              kern<<<dim3((unsigned)G), dim3(THREADS), 0, c->stream>>>(hlast, d.graph_node_ptr, cls, mean, c->pool);
+              HIP_TRY(hipGetLastError());
+              return XRL_OK;
+            };
+            return G < 2 * c->n_cu ? go(std::integral_constant<int, 512>()) : go(std::integral_constant<int, 256>());
+          }); }
+        if (rc) return rc;
+        Timed t(c, TK_READOUT);
+        return launch_readout(c, ra);
+      }
+      if (G == 0) return XRL_OK;
+      Timed t(c, TK_POOL);
+      return with_readout_widths(c, [&](auto fwd, auto) -> int {
+        auto kern = cls ? graph_readout_kernel<decltype(fwd), T, PV, true> : graph_readout_kernel<decltype(fwd), T, PV, false>;
+        const size_t lds = row_lds_floats(ra.pitch) * sizeof(float);
+        if (int rc2 = allow_row_lds(kern, lds)) return rc2;
+        kern<<<dim3((unsigned)G), dim3(kRowThreads), lds, c->stream>>>(hlast, d.graph_node_ptr, cls, mean, c->pool, ra);
+        HIP_TRY(hipGetLastError());
+        return XRL_OK;
+      });
     }
     { Timed t(c, TK_POOL);
       rc = launch_segsum<T, float, PV>(c, hlast, cls, d.graph_node_ptr, d.node_graph, N, G, H, c->pool, c->carry); }
@@ -2766,7 +2776,7 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
     if (m.readout == XRL_READOUT_MEAN && G > 0)
       mean_scale_kernel<<<dim3((unsigned)((G * H + 255) / 256)), dim3(256), 0, c->stream>>>(c->pool, d.graph_node_ptr, G, H, 0);
     { Timed t(c, TK_READOUT);
-      rc = launch_rowmlp(c, c->L.readout, true, c->pool, H, d.graph_global, m.d_global, G, d_emb, c->ro_act); }
+      rc = launch_readout(c, row_fwd_args(c, c->L.readout, true, c->pool, H, d.graph_global, m.d_global, G, d_emb, c->ro_act)); }
     if (rc) return rc;
     HIP_TRY(hipGetLastError());
     return XRL_OK;
@@ -2810,26 +2820,21 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
       c->h[r + 1] = ra.h[r + 1];
       c->agg[r + 1] = ra.agg[r];
     }
-    ra.mean = m.readout == XRL_READOUT_MEAN ? 1 : 0;
-    ra.pool = c->pool;
-    int dmax = 0;
-    ra.readout = rowmlp_args(c, c->L.readout, true, c->pool, H, d.graph_global, m.d_global, G, d_emb, c->ro_act, &dmax);
     const int MB = H / 32;
     int w1 = c->embed.nslabx;
     for (int r = 0; r < R; ++r) w1 = std::max(w1, std::max(c->edge[r].nslab1, c->node[r].nslab1));
     ra.w1_bytes_max = w1 * MB * 1024;
     const size_t w2_bytes = (size_t)MB * (32 / (2 * PV)) * MB * 1024;
-    const size_t lds = std::max((size_t)4 * RowStage<T, 128>::BYTES + ra.w1_bytes_max + w2_bytes + (size_t)m.n_op_types * H * 4,
-                                (size_t)(256 * PV + 2 * dmax) * sizeof(float));
+    const size_t lds = (size_t)4 * RowStage<T, 128>::BYTES + ra.w1_bytes_max + w2_bytes + (size_t)m.n_op_types * H * 4;
     ra.K = cluster_k; ra.G = (int)G; ra.arrived = c->d_arrived; ra.fault = c->d_fault; ra.spin_limit = c->cluster_spin_limit;
     if (lds <= (size_t)c->max_lds) {
-      Timed t(c, TK_RESIDENT);
       const unsigned grid = cluster_k > 0 ? (unsigned)(8 * ((G + 7) / 8) * cluster_k) : (unsigned)G;
       auto launch = [&](auto kern) -> int {
         if (lds > 65536) HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        kern<<<dim3(grid), dim3(256), lds, c->stream>>>(ra);
+        { Timed t(c, TK_RESIDENT);
+          kern<<<dim3(grid), dim3(256), lds, c->stream>>>(ra); }
         HIP_TRY(hipGetLastError());
-        return XRL_OK;
+        return readout((const T *)ra.h[R], nullptr);
       };
       if (cluster_k > 0) {   // (grid <= number of CUs and a block fits a CU: every block is resident)
         if (H == 64) return launch(encode_cluster_kernel<T, 64>);
@@ -3049,7 +3054,7 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   // the weights, followed by 1 KB of zeros (16-byte aligned) that kernels read in place of absent rows
   const size_t w_bytes = align_up(sizeof(float) * L.total);
   // zero row, heads' counters, the one-launch encoder's counters
-  const size_t tail_bytes = kZeroRow + sizeof(int32_t) * kMaxFusedSlots + sizeof(unsigned) * kClusterMaxGraphs + sizeof(int32_t) * kCounts;
+  const size_t tail_bytes = kZeroRow + sizeof(int32_t) * kMaxFusedStates + sizeof(unsigned) * kClusterMaxGraphs + sizeof(int32_t) * kCounts;
   e = hipMalloc((void **)&c->d_w, w_bytes + tail_bytes);
   if (e != hipSuccess) {
     xrl_destroy(c);
@@ -3057,7 +3062,7 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   }
   c->zero_row = (char *)c->d_w + w_bytes;
   c->d_counter = (int32_t *)((char *)c->zero_row + kZeroRow);
-  c->d_arrived = (unsigned *)(c->d_counter + kMaxFusedSlots);
+  c->d_arrived = (unsigned *)(c->d_counter + kMaxFusedStates);
   c->d_counts = (int32_t *)(c->d_arrived + kClusterMaxGraphs);
   e = hipMemset(c->zero_row, 0, tail_bytes);
   if (e != hipSuccess) {
@@ -3339,7 +3344,7 @@ int xrl_policy_value(xrl_ctx *c, const xrl_batch *b, const float *d_emb, float *
   float *logit = d_logit ? d_logit : (float *)c->hws;
   float *zmean = (float *)(c->hws + align_up((size_t)b->G * 4));
   Timed t(c, TK_HEADS);
-  return launch_heads(c, b, d_emb, logit, d_logp, d_entropy, d_action, zmean, d_value, nullptr, nullptr);
+  return launch_heads(c, b, d_emb, logit, d_logp, d_entropy, d_action, zmean, d_value, nullptr, nullptr, c->d_counter);
 }
 
 int xrl_policy_value_static(xrl_ctx *c, const xrl_batch *b, const float *d_emb, float *d_logp,
@@ -3361,15 +3366,7 @@ int xrl_policy_value_static(xrl_ctx *c, const xrl_batch *b, const float *d_emb, 
   float *zmean = (float *)(c->static_ws + kStaticZmeanOff);
   // the array keeps the last call's contents: the counters must start at zero
   fill_zero_kernel<<<dim3((unsigned)((b->S + 255) / 256)), dim3(256), 0, c->stream>>>((float *)counter, b->S);
-  const RowMlpArgs va = rowmlp_args(c, c->L.value, false, zmean, H, nullptr, 0, b->S, d_value, nullptr);
-  const RowMlpArgs pa = rowmlp_args(c, c->L.policy, false, d_emb, H, nullptr, 0, b->G, logit, nullptr);
-  by_rows(c, b->G, [&](auto rows) {
-    constexpr int ROWS = decltype(rows)::value;
-    policy_value_kernel<ROWS><<<dim3((unsigned)((b->G + ROWS - 1) / ROWS + b->S)), dim3(256), 0, c->stream>>>(
-        pa, b->dev.mask, b->dev.state_graph_ptr, (int)b->G, (int)b->S, H, counter, d_logp, d_entropy, d_action, zmean, va);
-  });
-  HIP_TRY(hipGetLastError());
-  return XRL_OK;
+  return launch_heads(c, b, d_emb, logit, d_logp, d_entropy, d_action, zmean, d_value, nullptr, nullptr, counter);
 }
 
 int xrl_ppo_objective(xrl_ctx *c, const xrl_batch *b, const float *d_logp, const float *d_value,
@@ -3448,7 +3445,7 @@ int policy_value_backward_run(xrl_ctx *c, const xrl_batch *b, const float *d_emb
   const int64_t G = b->G, S = b->S;
   size_t need = 0;
   auto acc = [&](size_t n) { need += align_up(n * 4); };
-  acc(G); acc(G); acc(S); acc(S * H); acc(S); acc(S);                 // logit logp ent zmean action value
+  acc(G); acc(S * H); acc(S);                                         // logit zmean value
   acc(G * h0); acc(G * h1); acc(G);                                   // policy activations
   acc(S * h0); acc(S * h1); acc(S);                                   // value activations
   acc(G); acc(S);                                                     // dlogit, 1/|valid|
@@ -3458,9 +3455,7 @@ int policy_value_backward_run(xrl_ctx *c, const xrl_batch *b, const float *d_emb
   acc(spart_floats);                                                  // chunk partials of the heads' weight gradients
   if ((rc = ensure_hws(c, need))) return rc;
   Bump bump{c->hws};
-  float *logit = bump.take<float>(G), *logp = bump.take<float>(G), *ent = bump.take<float>(S);
-  float *zmean = bump.take<float>(S * H);
-  int32_t *action = bump.take<int32_t>(S);
+  float *logit = bump.take<float>(G), *zmean = bump.take<float>(S * H);
   float *value = bump.take<float>(S);
   float *pact[3] = {bump.take<float>(G * h0), bump.take<float>(G * h1), bump.take<float>(G)};
   float *vact[3] = {bump.take<float>(S * h0), bump.take<float>(S * h1), bump.take<float>(S)};
@@ -3471,14 +3466,20 @@ int policy_value_backward_run(xrl_ctx *c, const xrl_batch *b, const float *d_emb
   float *spart = spart_floats ? bump.take<float>(spart_floats) : nullptr;
   const xrl_batch_device &d = b->dev;
   // forward of the heads, keeping every layer's output
-  if ((rc = launch_heads(c, b, d_emb, logit, logp, ent, action, zmean, value, pact, vact))) return rc;
-  // backward
-  state_policy_bwd_kernel<<<dim3((unsigned)S), dim3(256), 0, c->stream>>>(logp, ent, d.mask, d.state_graph_ptr,
-                                                                        d_dlogp, d_dentropy, dlogit, inv_n);
-  const RowMlpBwdArgs value_rows = rowmlp_bwd_args(c, c->L.value, false, vact, d_dvalue, S, vdz, dzs);
-  if ((rc = launch_rowmlp_bwd(c, rowmlp_bwd_args(c, c->L.policy, false, pact, dlogit, G, pdz, d_demb), &value_rows))) return rc;
-  demb_combine_kernel<<<dim3((unsigned)G), dim3(H < 256 ? H : 256), 0, c->stream>>>(d_demb, dzs, inv_n, d.mask,
-                                                                                 d.state_graph_ptr, (int)S, H);
+  if ((rc = launch_heads(c, b, d_emb, logit, nullptr, nullptr, nullptr, zmean, value, pact, vact, c->d_counter))) return rc;
+  // backward: what belongs to a state (the softmax, the value head), then the slots' policy MLP
+  HeadsStateBwdArgs sb;
+  sb.value = row_bwd_args(c, c->L.value, false, vact, d_dvalue, S, vdz, dzs);
+  sb.logit = logit; sb.mask = d.mask; sb.state_graph_ptr = d.state_graph_ptr; sb.dlogp = d_dlogp; sb.dentropy = d_dentropy;
+  sb.dlogit = dlogit; sb.inv_valid = inv_n; sb.S = (int)S; sb.value_rows = value_rows(c, S);
+  RowBwdArgs pb = row_bwd_args(c, c->L.policy, false, pact, dlogit, G, pdz, d_demb);
+  pb.mask = d.mask; pb.state_graph_ptr = d.state_graph_ptr; pb.dmean = dzs; pb.inv_valid = inv_n; pb.S = (int)S;
+  rc = with_head_widths(c, [&](auto, auto bwd) {
+    if (int rc2 = launch_rows(heads_state_bwd_kernel<decltype(bwd)>, sb, (S + sb.value_rows - 1) / sb.value_rows,
+                              row_bwd_lds_floats(sb.value), c->stream)) return rc2;
+    return launch_rows(row_backward_kernel<decltype(bwd), true>, pb, row_blocks(G), row_bwd_lds_floats(pb), c->stream);
+  });
+  if (rc) return rc;
   const SmallWgradMlp heads[2] = {{&c->L.policy, d_emb, nullptr, H, 0, pact, pdz, G}, {&c->L.value, zmean, nullptr, H, 0, vact, vdz, S}};
   if ((rc = launch_small_wgrads(c, heads, 2, d_dweights, spart, spart_floats))) return rc;
   HIP_TRY(hipGetLastError());

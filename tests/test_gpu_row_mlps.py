@@ -1,0 +1,92 @@
+"""The row-MLPs (readout, heads) where their launches and loops change: widths that are no multiples of sixteen, one tile, more
+tiles than waves, as wide as they go; states that share a block of the value head, more states than there are slot counters; graphs
+up to one a compute unit (readout in one launch) and beyond (sum and MLP apart, two block sizes), wide and no global attributes.
+Against the float64 oracle with the heads' criterion of test_gpu_head_gradients.py and the forward's fp32 tolerance; a graph's
+embedding and a state's outputs are the same bits whatever the batch around them."""
+import numpy as np
+import pytest
+
+import grad_checks as GC
+import synth
+from oracle import xrl_oracle as O
+from test_gpu_forward import check_emb, heads_only_state, oracle_model, weights_for
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hidden,heads,n_states,n_cand", [
+    (64, (16, 16), 2, 20), (128, (17, 3), 3, 42), (64, (129, 64), 2, 70), (256, (512, 512), 2, 30), (128, (1, 1), 1, 16),
+    (64, (256, 64), 300, 1), (64, (40, 12), 4100, 0)])
+def test_heads_of_any_width(hidden, heads, n_states, n_cand):
+    import torch
+    import paper_2304_14698_amd as xrl
+    model, _ = synth.make_config(1)
+    model.update(hidden=hidden, precision="fp32", head_hidden=heads)
+    rng = np.random.Generator(np.random.PCG64(n_states + heads[0]))
+    if n_cand == 0:                                             # n_states states of one slot
+        state = heads_only_state(rng, model, 1, n_states - 1, fixed=True)
+        state.update(n_states=n_states, state_graph_ptr=np.arange(n_states + 1, dtype=np.int32), slot_mask=np.ones(n_states, np.uint8))
+    else:
+        state = heads_only_state(rng, model, n_states, n_cand, fixed=True)
+    G, w, om = len(state["slot_mask"]), weights_for(model), oracle_model(model)
+    emb = rng.standard_normal((G, hidden)).astype(np.float32)
+    dlogp = (rng.standard_normal(G) * state["slot_mask"]).astype(np.float32)
+    dvalue, dentropy = (rng.standard_normal(n_states).astype(np.float32) for _ in range(2))
+    enc = xrl.Encoder(model, w)
+    batch = enc.pack(state)
+    t = lambda x: torch.from_numpy(x).cuda()
+    got = {k: v.cpu().numpy() for k, v in enc.policy_value(batch, t(emb)).items()}
+    ref = O.policy_value(om, w, emb.astype(np.float64), state)
+    valid = state["slot_mask"].astype(bool)
+    L = max(1.0, float(np.abs(ref["logit"]).max()))
+    for k in ("logp", "entropy", "value"):
+        a, r = (np.asarray(x[k], np.float64) for x in (got, ref))
+        a, r = (a[valid], r[valid]) if k == "logp" else (a, r)
+        assert np.abs(a - r).max() <= 2e-5 * max(1.0, np.abs(r).max()), k
+    dw = torch.zeros(enc.n_weights, dtype=torch.float32, device="cuda")
+    demb = enc.policy_value_backward(batch, t(emb), t(dlogp), t(dvalue), t(dentropy), dw).cpu().numpy()
+    bound = O.zero_grads(om)
+    ref_demb, ref_dw = O.policy_value_backward(om, w, emb.astype(np.float64), state, dlogp, dvalue, dentropy, bound=bound)
+    assert np.linalg.norm(demb - ref_demb) <= 1e-5 * np.linalg.norm(ref_demb)
+    assert not demb[~valid].any()
+    bound, dw = O.flatten(om, bound), dw.cpu().numpy().astype(np.float64)
+    for name, sl, _ in GC.tensors(om):
+        if name.startswith(("policy", "value")):
+            tol = 1e-5 * np.linalg.norm(ref_dw[sl]) + (2e-6 + 1e-5 * L) * np.linalg.norm(bound[sl])
+            assert np.linalg.norm(dw[sl] - ref_dw[sl]) <= tol, name
+
+
+def first_graphs(state, n):
+    """The state's first n graphs, as one state."""
+    N, E = state["graph_node_ptr"][n], state["graph_edge_ptr"][n]
+    out = {k: state[k][:N] for k in ("node_op", "node_dense")}
+    out.update({k: state[k][:E] for k in ("edge_src", "edge_dst", "edge_feat")})
+    out.update({k: state[k][:n + 1] for k in ("graph_node_ptr", "graph_edge_ptr")})
+    if state.get("graph_global") is not None:
+        out["graph_global"] = state["graph_global"][:n]
+    return dict(out, n_states=1, state_graph_ptr=np.array([0, n], np.int32), slot_mask=state["slot_mask"][:n])
+
+
+@pytest.mark.parametrize("readout", ["sum", "mean"])
+@pytest.mark.parametrize("hidden,d_global,precision", [(64, 0, "fp32"), (128, 100, "fp32"), (256, 1, "fp32"), (128, 3, "bf16")])
+def test_readout_at_graph_counts(hidden, d_global, precision, readout):
+    import torch
+    import paper_2304_14698_amd as xrl
+    model, state = synth.make_config(1, n_cand=530)
+    model.update(hidden=hidden, precision=precision, rounds=1, d_global=d_global, readout=readout)
+    rng = np.random.Generator(np.random.PCG64(hidden))
+    state["graph_global"] = rng.standard_normal((531, d_global)).astype(np.float32) if d_global else None
+    w, om = weights_for(model), oracle_model(model)
+    enc = xrl.Encoder(model, w)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    alone = None
+    for n in (7, n_cu, n_cu + 1, 2 * n_cu - 1, 2 * n_cu):
+        n = min(n, 531)
+        st = first_graphs(state, n)
+        batch = enc.pack(st)
+        got = enc.encode(batch).cpu().numpy()
+        if alone is None:
+            alone = got
+            check_emb(got, O.encode(om, w, st), model, "emb")
+        assert np.array_equal(got[:7], alone), n
+        batch.free()
