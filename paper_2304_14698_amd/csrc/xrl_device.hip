@@ -190,6 +190,7 @@ struct xrl_ctx {
   int64_t p_min_rows = 8192;    // smallest row count for the persistent kernels (XRL_PERSISTENT_MIN_ROWS) when saving
   int64_t p_min_rows_forward = 8192;   // for the backward pass, and when not
   int64_t wide_min_rows = 1 << 18;   // rows of a launch's products from which 256-column weight-gradient tiles are used (XRL_WGRAD_WIDE_MIN_ROWS)
+  int64_t pool_window_nodes = 4096;  // nodes per compute unit from which the pool's gradient goes by windows of graphs (XRL_POOL_WINDOW_NODES)
   int sum_steps = 0;                 // steps of a group of class_sum_kernel, 0: by the rows (XRL_SUM_STEPS)
   size_t grad_room = kGradRoom;      // XRL_GRAD_ROOM
   int64_t round_blocks = 0;          // blocks per compute unit up to which a round is one launch, see mlp2_round_kernel (XRL_ROUND_BLOCKS)
@@ -2316,7 +2317,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   const size_t o_reduced = need;
   if (q) {
     acc((size_t)((std::max(N, max_rows) + kSumRows - 1) / kSumRows) * 2 * H * 4);
-    acc((size_t)G * H * 4);
+    acc((size_t)kWindows * G * H * 4);
     sort_bytes = q->grouped && q->grouped_fold == fold ? 0 : grouping_bytes(b, q, fold);
     need = std::max(need, sort_bytes);
   }
@@ -2349,7 +2350,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   }
   bump.off = o_reduced;
   float *ccarry = q ? bump.take<float>((size_t)((std::max(N, max_rows) + kSumRows - 1) / kSumRows) * 2 * H) : nullptr;
-  float *dpool_rows = q ? bump.take<float>((size_t)G * H) : nullptr;
+  float *dpool_rows = q ? bump.take<float>((size_t)kWindows * G * H) : nullptr;
   WgradQueue wq;
   wq.partial = partial; wq.partial_floats = part;
   char *const room_base = c->bws + o_room;
@@ -2412,11 +2413,27 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   bool dz2_given = false;                  // dz2 of the next node-side layer down is in place already
   if (q) {
     // (a reduced batch: summed over each class's nodes of all graphs)
-    broadcast_dpool_kernel<float><<<dim3((unsigned)((G * (H / 4) + 255) / 256)), dim3(256), 0, c->stream>>>(
-        rdx, H, nullptr, d.graph_node_ptr, m.readout == XRL_READOUT_MEAN, G, H, dpool_rows);
     const uint16_t *mask = kept ? c->ym_node[R - 1] : nullptr;
     dz2_given = mask != nullptr;
-    if ((rc = contract(float(), dpool_rows, q->mem_graph, q->mem_ptr, q->mem_seg, N, mask, mask ? node_grads.dz2 : dhA, (size_t)G * H * 4))) return rc;
+    T *const out = mask ? node_grads.dz2 : dhA;
+    if (N >= c->pool_window_nodes * c->n_cu) {                      // (see pool_class_sum_kernel)
+      pool_windows_kernel<<<dim3((unsigned)(((G + kWindowStrip - 1) / kWindowStrip * (H / 4) + 255) / 256)), dim3(256), 0, c->stream>>>(
+          rdx, d.graph_node_ptr, m.readout == XRL_READOUT_MEAN, G, H, dpool_rows);
+      ClassSumArgs s;
+      s.vals = dpool_rows; s.zero_row = c->zero_row; s.perm = q->mem_graph; s.seg = q->mem_seg; s.ptr = q->mem_ptr; s.n_rows = N; s.D = H;
+      s.ymask = mask; s.out = out; s.carry = ccarry; s.slices = 1; s.group = 64;
+      const int64_t groups = (N + s.group - 1) / s.group;
+      const dim3 grid((unsigned)((groups + 3) / 4));
+      if (H == 64) pool_class_sum_kernel<T, 64><<<grid, dim3(256), 0, c->stream>>>(s, G);
+      else if (H == 128) pool_class_sum_kernel<T, 128><<<grid, dim3(256), 0, c->stream>>>(s, G);
+      else pool_class_sum_kernel<T, 256><<<grid, dim3(256), 0, c->stream>>>(s, G);
+      class_sum_carried_kernel<T><<<dim3((unsigned)((groups + 4 * kCarryGroups - 1) / (4 * kCarryGroups))), dim3(256), 0, c->stream>>>(s);
+      HIP_TRY(hipGetLastError());
+    } else {
+      broadcast_dpool_kernel<float><<<dim3((unsigned)((G * (H / 4) + 255) / 256)), dim3(256), 0, c->stream>>>(
+          rdx, H, nullptr, d.graph_node_ptr, m.readout == XRL_READOUT_MEAN, G, H, dpool_rows);
+      if ((rc = contract(float(), dpool_rows, q->mem_graph, q->mem_ptr, q->mem_seg, N, mask, out, (size_t)G * H * 4))) return rc;
+    }
   } else if (N > 0) {
     if (dpool_table)
       broadcast_dpool_kernel<T><<<dim3((unsigned)((G * (H / 4) + 255) / 256)), dim3(256), 0, c->stream>>>(
@@ -3026,6 +3043,7 @@ int xrl_create(const xrl_model_desc *model, const float *weights_host, void *hip
   c->round_blocks = model->hidden == 64 ? 4 : 2;
   if (const char *e = getenv("XRL_ROUND_BLOCKS")) { c->round_blocks = atoll(e); c->round_any = true; }
   if (const char *e = getenv("XRL_SUM_STEPS")) c->sum_steps = atoi(e);
+  if (const char *e = getenv("XRL_POOL_WINDOW_NODES")) c->pool_window_nodes = atoll(e);
   if (const char *e = getenv("XRL_GRAD_ROOM")) c->grad_room = (size_t)std::max<long long>(0, atoll(e));
   // Largest batches of the one-launch encoders (0 graphs = never). A forward-only encode takes them up to a
   // limit that the variable of that form states, and by default never: since a tile of the

@@ -1,0 +1,50 @@
+"""The pool's gradient by windows of graphs (1, 4 and 16 consecutive ones): classes that lie in every graph, in runs with gaps, twice
+in a graph, in one graph; runs that begin and end inside, at the end of and across a wave's 64 places. The same sums as row by
+row in another order, in fp32: n terms of either order err by at most n * 2^-24 of the sum of their absolute values, and by about
+the root of that; the largest class here has 700 terms: 2^-24 * 700 = 4.2e-5 of a sum that does not cancel, asserted at a quarter of it on the
+whole gradient. In bf16 the sums are rounded to 2^-9 once per class either way."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("readout", ["sum", "mean"])
+@pytest.mark.parametrize("hidden,precision", [(64, "fp32"), (128, "fp32"), (256, "fp32"), (64, "bf16"), (128, "bf16"), (256, "bf16")])
+def test_pool_gradient_by_windows(hidden, precision, readout, monkeypatch):
+    import torch
+
+    import paper_2304_14698_amd as xrl
+    rng = np.random.Generator(np.random.PCG64(hidden))
+    model, _ = synth.make_config(1)
+    model.update(hidden=hidden, precision=precision, rounds=2, readout=readout)
+    base = [synth.layered_dag(rng, n) for n in (11, 7, 5)]
+    b, n = base[0], base[0].n_nodes
+    two = lambda x: np.concatenate([x, x])
+    twice = dataclasses.replace(b, op=two(b.op), dense=two(b.dense), layer=two(b.layer), block=two(b.block), efeat=two(b.efeat),
+                                src=np.concatenate([b.src, b.src + n]), dst=np.concatenate([b.dst, b.dst + n]))
+    graphs = [base[0]] * 333 + [base[int(i)] for i in rng.integers(0, 3, 200)] + [base[i % 17 == 0] for i in range(163)]
+    graphs[40] = graphs[41] = graphs[350] = twice                # classes with two places in a graph
+    graphs += [synth.layered_dag(rng, 6) for _ in range(9)]      # classes of one graph
+    state = synth.concat_states([(graphs, np.ones(len(graphs), np.uint8))])
+    w = synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1)
+    up = torch.randn(len(graphs), hidden, generator=torch.Generator().manual_seed(1)).cuda()
+    monkeypatch.setenv("XRL_DISTINCT_MIN_US", "0")
+    got = []
+    for nodes in ("0", "1000000000"):
+        monkeypatch.setenv("XRL_POOL_WINDOW_NODES", nodes)
+        enc = xrl.Encoder(model, w)
+        batch = enc.pack(state)
+        enc.encode(batch, save_for_backward=True)
+        assert enc.batch_level(batch, 2)[0] < len(state["node_op"]) // 4
+        dw = torch.zeros(enc.n_weights, device="cuda")
+        enc.encode_backward(batch, up, dw)
+        got.append(dw.double())
+        batch.free()
+        enc.close()
+    assert float(got[1].norm()) > 0
+    assert float((got[0] - got[1]).norm() / got[1].norm()) <= (1e-5 if precision == "fp32" else 2e-2)
