@@ -162,10 +162,12 @@ __device__ __forceinline__ void class_insert(const ClassArgs &a, int64_t n) {
 // of nodes would go for the same slots: 98 us per level at 703 k nodes of 2080 graphs, against 9 for these and
 // then 30 for all).
 __global__ __launch_bounds__(256) void class_insert_first_kernel(const ClassArgs a) {
+  touch_args(a);
   const int g = a.state_graph_ptr[blockIdx.x], n1 = a.graph_node_ptr[g + 1];
   for (int n = a.graph_node_ptr[g] + threadIdx.x; n < n1; n += 256) class_insert(a, n);
 }
 __global__ __launch_bounds__(256) void class_insert_kernel(const ClassArgs a) {
+  touch_args(a);
   const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (n < a.N) class_insert(a, n);
 }
@@ -225,6 +227,7 @@ __device__ __forceinline__ int2 block_scan_pair(int2 v, int2 *wave_sum, int2 &su
 }
 
 __global__ __launch_bounds__(256) void class_verify_kernel(const ClassArgs a) {
+  touch_args(a);
   __shared__ int2 ws[4];
   int2 v = make_int2(0, 0), sum;
   for (int i = 0; i < kScanItems / 256; ++i) {
@@ -293,6 +296,7 @@ struct LevelFillArgs {
   int32_t *receivers;                       // classes with in-edges, counted
 };
 __global__ __launch_bounds__(256) void level_fill_kernel(const LevelFillArgs a) {
+  touch_args(a);
   const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (c >= a.n_cls) return;
   const int32_t r = a.reps[c], e0 = a.in_ptr[r], d = a.in_ptr[r + 1] - e0, p0 = a.ptr[c];
@@ -361,11 +365,13 @@ __device__ __forceinline__ void once_insert(const ClassArgs &a, int64_t n) {
 }
 // the nodes of every state's first graph ahead of the others (see class_insert_first_kernel)
 __global__ __launch_bounds__(256) void once_insert_first_kernel(const ClassArgs a, int blocks_per_graph) {
+  touch_args(a);
   const int g = a.state_graph_ptr[blockIdx.x / blocks_per_graph];
   const int n = a.graph_node_ptr[g] + (int)(blockIdx.x % blocks_per_graph) * 256 + (int)threadIdx.x;
   if (n < a.graph_node_ptr[g + 1]) once_insert(a, n);
 }
 __global__ __launch_bounds__(256) void once_insert_kernel(const ClassArgs a) {
+  touch_args(a);
   const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (n < a.N) once_insert(a, n);
 }
@@ -700,6 +706,7 @@ __device__ __forceinline__ void store_masked4(TOut *p, float *v, bool masked, un
 }
 template <typename TIn, typename TOut, int VEC, int STEPS>
 __global__ __launch_bounds__(256) void class_sum_kernel(const ClassSumArgs a) {
+  touch_args(a);
   constexpr int NR = kSumRows, NQ = VEC / 4;
   typedef int i32x4 __attribute__((ext_vector_type(4)));
   const int lpr = a.D / VEC / a.slices;                    // lanes of a group
@@ -923,6 +930,7 @@ __global__ __launch_bounds__(256) void pool_class_sum_kernel(const ClassSumArgs 
 constexpr int kCarryGroups = 4;
 template <typename TOut>
 __global__ __launch_bounds__(256) void class_sum_carried_kernel(const ClassSumArgs a) {
+  touch_args(a);
   const int NR = a.group;
   const int lane = threadIdx.x & 63;
   const int64_t st0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kCarryGroups, mine = st0 + lane;

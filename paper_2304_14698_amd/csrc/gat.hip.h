@@ -94,6 +94,7 @@ struct GatLds {
 };
 template <typename T, int H>
 __global__ __launch_bounds__((64 * GatLds<T, H>::NW)) void gat_linear_lds_kernel(const GatArgs a) {
+  touch_args(a);
   using Opd = Operand<T>;
   using vec = typename Opd::vec;
   using S = GatLds<T, H>;
@@ -244,6 +245,7 @@ __device__ __forceinline__ void gat_aggregate_row(const GatArgs &a, int H, int64
 }
 template <typename T, int VEC>
 __global__ __launch_bounds__(256) void gat_aggregate_kernel(const GatArgs a, int H) {
+  touch_args(a);
   const int lpr = H / VEC;
   const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t n = gt / lpr;
@@ -282,6 +284,7 @@ struct GatNext {                 // of the next round
 };
 template <typename T, int H>
 __global__ __launch_bounds__((GatRound<T, H>::NT), (GatRound<T, H>::PER_CU * GatRound<T, H>::NW / 4)) void gat_round_kernel(const GatArgs a, const GatNext next) {
+  touch_args(a);
   using Opd = Operand<T>;
   using vec = typename Opd::vec;
   using S = GatRound<T, H>;
@@ -405,6 +408,7 @@ __device__ __forceinline__ float group_sum(float v, int width) {
 // of its in-edges and self edge, and the gradients of their scores. Edges in order.
 template <typename T, int VEC>
 __global__ __launch_bounds__(256) void gat_bwd_scores_kernel(const GatBwdArgs a, int H) {
+  touch_args(a);
   const int lpr = H / VEC;
   const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int64_t n = gt / lpr;
@@ -480,6 +484,7 @@ __global__ __launch_bounds__(256) void gat_bwd_scores_kernel(const GatBwdArgs a,
 // positions out_pos[k], ascending) and the two score gradients; also d_ss[j].
 template <typename T, int VEC>
 __global__ __launch_bounds__(256) void gat_bwd_dz_kernel(const GatBwdArgs a, int H) {
+  touch_args(a);
   const int lpr = H / VEC;
   const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t n = gt / lpr;

@@ -53,6 +53,7 @@ struct SmallWgradArgs {
   SmallWgradJob job[kWgradJobs];
 };
 __global__ __launch_bounds__(256) void small_wgrad_kernel(const SmallWgradArgs a) {
+  touch_args(a);
   __shared__ __align__(16) float xs[kWgradStage][kWgradTile], zs[kWgradStage][kWgradTile];
   int ji = 0;
   while (ji + 1 < a.n_jobs && (int)blockIdx.x >= a.job[ji + 1].block0) ++ji;
@@ -120,6 +121,7 @@ __global__ __launch_bounds__(256) void small_wgrad_kernel(const SmallWgradArgs a
 }
 // dW / db += the chunks' sums, every entry in chunk order (eight loads in flight); layers of one chunk have no blocks
 __global__ __launch_bounds__(256) void small_wgrad_reduce_kernel(const SmallWgradArgs a) {
+  touch_args(a);
   int ji = 0;
   while (ji + 1 < a.n_jobs && (int)blockIdx.x >= a.job[ji + 1].entry0) ++ji;
   const SmallWgradJob &j = a.job[ji];

@@ -470,6 +470,7 @@ struct SplitTile {
 };
 template <typename T1, typename T, int H, int KIND>
 __global__ __launch_bounds__(2 * H) void mlp2_split_kernel(const Mlp2Args a) {
+  touch_args(a);
   using S = SplitTile<T, H>;
   using Opd = Operand<T>;
   using vec = typename Opd::vec;
@@ -619,6 +620,7 @@ struct Split3Tile {
 };
 template <int H, int KIND>
 __global__ __launch_bounds__(2 * H) void mlp2_split3_kernel(const Mlp2Args a) {
+  touch_args(a);
   using S = Split3Tile<H>;
   using vec = bf16x8;
   constexpr int HS = S::HS, MB = S::MB, NC2 = S::NC2, RING = 4;   // slabs of weights in flight, three fragments each
@@ -847,6 +849,7 @@ __device__ __forceinline__ void split_layers(const Mlp2Args &a, const typename O
 }
 template <typename T, int H>
 __global__ __launch_bounds__(2 * H) void mlp2_round_kernel(const RoundArgs a) {
+  touch_args(a);
   using S = SplitTile<T, H>;
   using Opd = Operand<T>;
   using vec = typename Opd::vec;

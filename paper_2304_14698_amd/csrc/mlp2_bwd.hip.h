@@ -72,6 +72,7 @@ struct BwdTile {
 };
 template <typename T, int H, int KIND>
 __global__ __launch_bounds__(2 * H) void mlp2_bwd_kernel(const Mlp2BwdArgs a) {
+  touch_args(a);
   using S = SplitTile<T, H>;
   using B = BwdTile<T, H>;
   using Opd = Operand<T>;
@@ -283,6 +284,7 @@ struct BwdWide {
 };
 template <int H, int KIND>
 __global__ __launch_bounds__(256) void mlp2_bwd_wide_kernel(const Mlp2BwdArgs a) {
+  touch_args(a);
   static_assert(KIND != KIND_EMBED, "the embed MLP's backward has two products: the split form is the faster one at any size");
   using T = bf16_t;
   using S = BwdWide<H>;

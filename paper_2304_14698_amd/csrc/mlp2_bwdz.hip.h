@@ -55,6 +55,7 @@ struct BwdzShape {
 // and left the result where the weight gradient reads dz2, so it is neither masked nor stored here.
 template <int H, int KIND, bool FOLD, bool GIVEN = false>
 __global__ __launch_bounds__((64 * BwdzShape<H>::NW)) void mlp2_bwdz_kernel(const Mlp2BwdzArgs a) {
+  touch_args(a);
   static_assert(!FOLD || KIND == KIND_EDGE, "only the edge MLP's receiver-side gradients are summed");
   static_assert(!GIVEN || KIND != KIND_EDGE, "the edge MLP's upstream gradient is gathered per receiver");
   using T = bf16_t;

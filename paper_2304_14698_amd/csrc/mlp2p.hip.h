@@ -205,6 +205,7 @@ __device__ __forceinline__ void save_output_mask(const Mlp2Args &a, const f32x16
 
 template <typename T, int H, int KIND, int NW, bool SAVE>
 __global__ __launch_bounds__(64 * NW) void mlp2p_kernel(const Mlp2Args a) {
+  touch_args(a);
   using Opd = Operand<T>;
   using vec = typename Opd::vec;
   constexpr int V = Opd::V, SL = 2 * V, MB = H / 32, HS = H / SL, QB = 32 / SL;
@@ -351,6 +352,7 @@ __global__ __launch_bounds__(64 * NW) void mlp2p_kernel(const Mlp2Args a) {
 // LEVEL: as in mlp2r_kernel.
 template <typename T, int H, int NW, bool SAVE, bool LEVEL>
 __global__ __launch_bounds__(64 * NW) void embedp_kernel(const Mlp2Args args) {
+  touch_args(args);
   const Mlp2Args a = of_level<LEVEL, false>(args);
   using Opd = Operand<T>;
   using vec = typename Opd::vec;

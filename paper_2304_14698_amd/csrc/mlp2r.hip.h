@@ -157,6 +157,7 @@ __device__ __forceinline__ void rtile_fetch(const Mlp2Args &a, const RTileRows &
 // LEVEL: a level of a batch that is reduced without the host (see once_fill_kernel).
 template <int H, int KIND, bool SAVE, bool LEVEL>
 __global__ __launch_bounds__((RTile<H, KIND>::NT), (RTile<H, KIND>::WAVES_PER_SIMD)) void mlp2r_kernel(const Mlp2Args args) {
+  touch_args(args);
   const Mlp2Args a = of_level<LEVEL, KIND == KIND_EDGE>(args);
   using T = bf16_t;
   using R = RTile<H, KIND>;

@@ -36,18 +36,6 @@ struct RowWidths {
 };
 template <int M> using MapIndex = std::integral_constant<int, M>;
 
-// Kernel arguments lie in host memory, and the compiler asks for them where they are first used: one round trip of 1 us after another.
-// This asks for all their cache lines at once.
-template <typename Args>
-__device__ __forceinline__ void touch_args(const Args &a) {
-  const unsigned *p = (const unsigned *)&a;
-  constexpr int N = (int)((sizeof(Args) + 63) / 64);
-  unsigned v[N];
-#pragma unroll
-  for (int i = 0; i < N; ++i) v[i] = p[i * 16];
-#pragma unroll
-  for (int i = 0; i < N; ++i) asm volatile("" ::"s"(v[i]));
-}
 // floats of LDS between two rows of x: sixteen rows' 16-byte reads touch all banks
 __host__ __device__ inline int row_pitch(int width) { return ((width + 15) >> 4) * 16 + 4; }
 

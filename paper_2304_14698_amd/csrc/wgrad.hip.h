@@ -346,6 +346,7 @@ __global__ __launch_bounds__(2 * TA, 2) void wgrad_kernel(const WgradLaunch a) {
   const WgradPlace place = wgrad_place(a, blockIdx.x);
   if (place.job == kWgradMaxJobs) return;
   const WgradJob &j = a.job[place.job];
+  touch_args(j);
   const int kq = place.kq, y = place.y;
   const int ka0 = kq * TA;
   const int64_t r_begin = (int64_t)y * j.rows_per_slice;
