@@ -31,15 +31,15 @@ __device__ __forceinline__ float block_sum(float v, float *red) {
 
 // Weight gradients of a few affine layers over G or S rows each, one launch for all of them:
 //   dW[k, f] += sum_rows x[row, k] dz[row, f],  db[f] += sum_rows dz[row, f]
-// x = [x1 | x2] (x2 nullable); k = d_in is the bias row (x = 1). A block owns a 64 x 64 tile of one layer's
-// [d_in + 1, d_out] and one chunk of its rows; rows go through LDS sixteen at a time (the next sixteen
-// requested before the products of these), and a thread holds 4 x 4 sums: two 16-byte LDS reads for
-// sixteen products, where one thread per entry waited for two loads per product (H = 128, 1040 rows,
-// 16 states: 250 us for the eight layers of heads and readout, a launch and a reduction each; here 32 us
-// in four launches; 4624 rows, H = 256: 760 -> 81 us). With one chunk the sums
-// are added to dW / db directly; with several, chunk c writes partial[c][k][f], which
-// small_wgrad_reduce_kernel adds up in a fixed order.
-constexpr int kWgradJobs = 6, kWgradTile = 64, kWgradStage = 16;
+// x = [x1 | x2] (x2 nullable). A block owns a 64 x 64 tile of one layer's matrix and one chunk of its rows, a quarter of which
+// each wave multiplies on v_mfma_f32_16x16x4_f32 (fp32 operands and sums): four rows of 64 columns of x and of dz are one 16-byte load a
+// lane each, whose element j is the operand of columns 4 i + j, so sixteen instructions follow two loads and nothing goes through
+// LDS before the waves' sums are added, in order. Bound by the round trips of a launch: 32 rows a wave are in flight together. The
+// blocks of a layer's first 64 rows of dW add up dz for db. With one chunk the sums are added to dW / db
+// directly; with several, chunk c writes partial[c][k][f] (row d_in: db), which small_wgrad_reduce_kernel adds up in a fixed order.
+// us with their reductions, before (vector code, rows through LDS) / now: 104 rows of H = 64 14 / 9, 1040 of H = 128 15 / 13, 4624 of
+// H = 256 36 / 30.
+constexpr int kWgradJobs = 6, kWgradTile = 64, kWgradFly = 8;
 struct SmallWgradJob {
   const float *x1, *x2, *dz;
   int w1, w2, d_in, d_out;       // w1 + w2 == d_in
@@ -53,10 +53,12 @@ struct SmallWgradArgs {
   SmallWgradJob job[kWgradJobs];
 };
 __global__ __launch_bounds__(256) void small_wgrad_kernel(const SmallWgradArgs a) {
+  __shared__ __align__(16) float sums[4][kWgradTile][kWgradTile];
+  __shared__ float dz_sum[4][kWgradTile];
   touch_args(a);
-  __shared__ __align__(16) float xs[kWgradStage][kWgradTile], zs[kWgradStage][kWgradTile];
   int ji = 0;
-  while (ji + 1 < a.n_jobs && (int)blockIdx.x >= a.job[ji + 1].block0) ++ji;
+#pragma unroll
+  for (int i = 1; i < kWgradJobs; ++i) ji += i < a.n_jobs && (int)blockIdx.x >= a.job[i].block0 ? 1 : 0;
   const SmallWgradJob &j = a.job[ji];
   int q = (int)blockIdx.x - j.block0;
   const int f0 = (q % j.tiles_f) * kWgradTile;
@@ -64,60 +66,95 @@ __global__ __launch_bounds__(256) void small_wgrad_kernel(const SmallWgradArgs a
   const int k0 = (q % j.tiles_k) * kWgradTile, chunk = q / j.tiles_k;
   const int64_t r0 = (int64_t)chunk * j.rows_per_chunk;
   const int64_t r1 = r0 + j.rows_per_chunk < j.n_rows ? r0 + j.rows_per_chunk : j.n_rows;
-  const int t = threadIdx.x, tk = 4 * (t >> 4), tf = 4 * (t & 15);
-  const int col = t & 63, row4 = t >> 6;                    // staging: column `col` of rows row4, row4 + 4, ..
-  const int k = k0 + col, f = f0 + col;
-  const bool in_x = k < j.d_in, in_f = f < j.d_out;
-  const float *xp = k < j.w1 ? j.x1 + k : (in_x ? j.x2 + (k - j.w1) : j.x1);
-  const int xstride = k < j.w1 ? j.w1 : j.w2;
-  const float xelse = k == j.d_in ? 1.f : 0.f;
-  float xv[kWgradStage / 4], zv[kWgradStage / 4];
-  auto request = [&](int64_t r) {
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), c16 = lane & 15, q4 = lane >> 4;
+  const int quarter = (int)((r1 - r0 + 15) >> 4) << 2;      // rows of a wave, a multiple of four
+  const int64_t w0 = r0 + wave * quarter, w1 = w0 + quarter < r1 ? w0 + quarter : r1;
+  const int k = k0 + 4 * c16, f = f0 + 4 * c16;
+  // (whole tiles of aligned rows 16 bytes a lane, others element by element; every load under no condition, its join would wait for it)
+  const bool x_whole = k0 + kWgradTile <= j.w1 && (j.w1 & 3) == 0 && ((uintptr_t)j.x1 & 15) == 0;
+  const bool z_whole = f0 + kWgradTile <= j.d_out && (j.d_out & 3) == 0;
+  // what is there already, where the sums are added to it: requested with the rows
+  const int col = t & 63, fo = f0 + col, rows = j.d_in - k0 < kWgradTile ? j.d_in - k0 : kWgradTile;
+  const bool direct = !j.partial;
+  float *dst = direct ? j.dW + (size_t)k0 * j.d_out + fo : j.partial + ((size_t)chunk * (j.d_in + 1) + k0) * j.d_out + fo;
+  float *bias = direct ? j.db + fo : j.partial + ((size_t)chunk * (j.d_in + 1) + j.d_in) * j.d_out + fo;
+  float old[kWgradTile / 4], old_bias = 0.f;
 #pragma unroll
-    for (int i = 0; i < kWgradStage / 4; ++i) {
-      const int64_t ri = r + row4 + 4 * i;
-      const bool on = ri < r1;
-      const int64_t rc = on ? ri : r1 - 1;
-      const float x = in_x ? xp[rc * xstride] : xelse;
-      const float z = in_f ? j.dz[rc * j.d_out + f] : 0.f;
-      xv[i] = on ? x : 0.f;
-      zv[i] = on ? z : 0.f;
+  for (int i = 0; i < kWgradTile / 4; ++i) {
+    const int m = (t >> 6) + 4 * i;
+    old[i] = 0.f;
+    if (direct && fo < j.d_out && m < rows) old[i] = dst[(size_t)m * j.d_out];
+  }
+  if (direct && k0 == 0 && t < 64 && fo < j.d_out) old_bias = *bias;
+  f32x4 acc[4][4], dzs = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int m = 0; m < 4; ++m)
+#pragma unroll
+    for (int n = 0; n < 4; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto run = [&](auto xw, auto zw) {
+    constexpr bool XW = decltype(xw)::value, ZW = decltype(zw)::value;
+    for (int64_t r = w0; r < w1; r += 4 * kWgradFly) {
+      f32x4 xv[kWgradFly], zv[kWgradFly];
+#pragma unroll
+      for (int i = 0; i < kWgradFly; ++i) {
+        const int64_t ri = r + 4 * i + q4, rc = ri < w1 ? ri : w1 - 1;
+        if constexpr (XW) {
+          xv[i] = *(const f32x4 *)(j.x1 + rc * j.w1 + k);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int kc = k + e < j.d_in ? k + e : j.d_in - 1;
+            xv[i][e] = *(kc < j.w1 ? j.x1 + rc * j.w1 + kc : j.x2 + rc * j.w2 + (kc - j.w1));
+          }
+        }
+        if constexpr (ZW) {
+          zv[i] = *(const f32x4 *)(j.dz + rc * j.d_out + f);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) zv[i][e] = j.dz[rc * j.d_out + (f + e < j.d_out ? f + e : j.d_out - 1)];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < kWgradFly; ++i) {
+        const bool on = r + 4 * i + q4 < w1;                       // (columns past the last are not stored)
+        xv[i] = on ? xv[i] : zero;
+        zv[i] = on ? zv[i] : zero;
+        dzs += zv[i];
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+          for (int n = 0; n < 4; ++n) acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[i][m], zv[i][n], acc[m][n], 0, 0, 0);
+      }
     }
   };
-  float acc[4][4];
+  typedef std::integral_constant<bool, true> yes;
+  typedef std::integral_constant<bool, false> no;
+  if (x_whole && z_whole) run(yes(), yes());
+  else if (x_whole) run(yes(), no());
+  else run(no(), no());
+  // register i of tile (m, n): row 4 (4 q4 + i) + m, column 4 c16 + n
 #pragma unroll
   for (int m = 0; m < 4; ++m)
 #pragma unroll
-    for (int n = 0; n < 4; ++n) acc[m][n] = 0.f;
-  request(r0);
-  for (int64_t r = r0; r < r1; r += kWgradStage) {
-#pragma unroll
-    for (int i = 0; i < kWgradStage / 4; ++i) {
-      xs[row4 + 4 * i][col] = xv[i];
-      zs[row4 + 4 * i][col] = zv[i];
-    }
-    __syncthreads();
-    if (r + kWgradStage < r1) request(r + kWgradStage);
-#pragma unroll
-    for (int i = 0; i < kWgradStage; ++i) {
-      const f32x4 x = *(const f32x4 *)&xs[i][tk], z = *(const f32x4 *)&zs[i][tf];
-#pragma unroll
-      for (int m = 0; m < 4; ++m)
-#pragma unroll
-        for (int n = 0; n < 4; ++n) acc[m][n] = fmaf(x[m], z[n], acc[m][n]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int m = 0; m < 4; ++m)
+    for (int i = 0; i < 4; ++i)
+      *(f32x4 *)&sums[wave][16 * q4 + 4 * i + m][4 * c16] = f32x4{acc[m][0][i], acc[m][1][i], acc[m][2][i], acc[m][3][i]};
+  if (k0 == 0) {
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
-      const int ko = k0 + tk + m, fo = f0 + tf + n;
-      if (ko > j.d_in || fo >= j.d_out) continue;
-      if (j.partial) j.partial[((size_t)chunk * (j.d_in + 1) + ko) * j.d_out + fo] = acc[m][n];
-      else if (ko == j.d_in) j.db[fo] += acc[m][n];
-      else j.dW[(size_t)ko * j.d_out + fo] += acc[m][n];
+      dzs[n] += __shfl_xor(dzs[n], 16);
+      dzs[n] += __shfl_xor(dzs[n], 32);
     }
+    if (q4 == 0) *(f32x4 *)&dz_sum[wave][4 * c16] = dzs;
+  }
+  __syncthreads();
+  if (fo >= j.d_out) return;
+#pragma unroll
+  for (int i = 0; i < kWgradTile / 4; ++i) {
+    const int m = (t >> 6) + 4 * i;
+    if (m < rows) dst[(size_t)m * j.d_out] = old[i] + ((sums[0][m][col] + sums[1][m][col]) + (sums[2][m][col] + sums[3][m][col]));
+  }
+  if (k0 == 0 && t < 64) *bias = old_bias + ((dz_sum[0][col] + dz_sum[1][col]) + (dz_sum[2][col] + dz_sum[3][col]));
 }
 // dW / db += the chunks' sums, every entry in chunk order (eight loads in flight); layers of one chunk have no blocks
 __global__ __launch_bounds__(256) void small_wgrad_reduce_kernel(const SmallWgradArgs a) {

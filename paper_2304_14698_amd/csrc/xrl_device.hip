@@ -1611,7 +1611,7 @@ int launch_readout_backward(xrl_ctx *c, const RowBwdArgs &a) {
 // dW, db of every layer of one or two small row-MLPs in one launch (and one reduction): x of layer 0 is
 // [x1 | x2], of layer l > 0 act[l-1]. Rows are cut into chunks of kSmallWgradRows, fewer and larger ones
 // where `partial` (partial_floats long) has no room for as many.
-constexpr int kSmallWgradRows = 64;
+constexpr int kSmallWgradRows = 128;
 struct SmallWgradMlp {
   const MlpRef *r;
   const float *x1, *x2;
@@ -1633,6 +1633,13 @@ int launch_small_wgrads(xrl_ctx *c, const SmallWgradMlp *mlps, int n_mlps, float
   memset(&a, 0, sizeof(a));
   int blocks = 0, entries = 0;
   size_t used = 0;
+  auto tiles = [](int n) { return (n + kWgradTile - 1) / kWgradTile; };
+  // (as many chunks as give each compute unit the two blocks it has room for: 4624 rows, H = 256, in chunks of 128 31 us,
+  // so 27 and a reduction of 5 in place of 7)
+  int many = 0;
+  for (int i = 0; i < n_mlps; ++i)
+    for (int l = 0; l < mlps[i].r->n_layers && mlps[i].n_rows > kSmallWgradRows; ++l) many += tiles(mlps[i].r->d_in[l]) * tiles(mlps[i].r->d_out[l]);
+  const int64_t most_chunks = std::max(1, 2 * c->n_cu / std::max(1, many));
   for (int i = 0; i < n_mlps; ++i) {
     const SmallWgradMlp &m = mlps[i];
     if (m.n_rows <= 0) continue;
@@ -1646,13 +1653,13 @@ int launch_small_wgrads(xrl_ctx *c, const SmallWgradMlp *mlps, int n_mlps, float
       j.dz = m.dz[l];
       j.n_rows = m.n_rows;
       const size_t n = (size_t)(j.d_in + 1) * j.d_out;
-      int64_t nc = small_wgrad_chunks(m.n_rows);
+      int64_t nc = std::min(small_wgrad_chunks(m.n_rows), most_chunks);
       if (partial && used + (size_t)nc * n > partial_floats) nc = (int64_t)((partial_floats - used) / n);
       if (!partial || nc < 2) nc = 1;
       j.rows_per_chunk = (int)((m.n_rows + nc - 1) / nc);
       j.n_chunks = (int)((m.n_rows + j.rows_per_chunk - 1) / j.rows_per_chunk);
-      j.tiles_k = (j.d_in + 1 + kWgradTile - 1) / kWgradTile;
-      j.tiles_f = (j.d_out + kWgradTile - 1) / kWgradTile;
+      j.tiles_k = tiles(j.d_in);
+      j.tiles_f = tiles(j.d_out);
       j.block0 = blocks;
       j.entry0 = entries;
       j.dW = dweights + m.r->w[l];

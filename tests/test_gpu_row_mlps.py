@@ -1,5 +1,6 @@
 """The row-MLPs (readout, heads) where their launches and loops change: widths that are no multiples of sixteen, one tile, more
-tiles than waves, as wide as they go; states that share a block of the value head, more states than there are slot counters; graphs
+tiles than waves, as wide as they go; states that share a block of the value head, more states than there are slot counters; one
+and several chunks of rows in the weight gradients; graphs
 up to one a compute unit (readout in one launch) and beyond (sum and MLP apart, two block sizes), wide and no global attributes.
 Against the float64 oracle with the heads' criterion of test_gpu_head_gradients.py and the forward's fp32 tolerance; a graph's
 embedding and a state's outputs are the same bits whatever the batch around them."""
@@ -16,7 +17,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("hidden,heads,n_states,n_cand", [
     (64, (16, 16), 2, 20), (128, (17, 3), 3, 42), (64, (129, 64), 2, 70), (256, (512, 512), 2, 30), (128, (1, 1), 1, 16),
-    (64, (256, 64), 300, 1), (64, (40, 12), 4100, 0)])
+    (64, (256, 64), 300, 1), (64, (40, 12), 4100, 0),
+    (64, (256, 64), 1, 127), (128, (256, 64), 1, 128), (128, (100, 36), 3, 170), (64, (65, 66), 9, 255)])   # a chunk of rows, and more
 def test_heads_of_any_width(hidden, heads, n_states, n_cand):
     import torch
     import paper_2304_14698_amd as xrl
