@@ -292,6 +292,7 @@ struct LevelFillArgs {
   const float *edge_feat, *node_dense;
   int De, Dd;
   int32_t *o_ptr, *o_src, *o_dst, *o_agg_src, *o_self, *o_op;
+  int32_t *o_below_src, *o_below_dst;       // nullable
   float *o_feat, *o_dense;
   int32_t *receivers;                       // classes with in-edges, counted
 };
@@ -310,6 +311,10 @@ __global__ __launch_bounds__(256) void level_fill_kernel(const LevelFillArgs a) 
     for (int k = 0; k < d; ++k) {
       a.o_src[p0 + k] = a.cls[a.in_src[e0 + k]];
       a.o_dst[p0 + k] = (int32_t)c;
+      if (a.o_below_src) {
+        a.o_below_src[p0 + k] = a.prev[a.in_src[e0 + k]];
+        a.o_below_dst[p0 + k] = a.prev[r];
+      }
     }
   } else {
     a.o_op[c] = a.node_op[r];

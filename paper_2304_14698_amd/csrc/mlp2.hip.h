@@ -59,7 +59,7 @@ struct Mlp2Args {
   // kernels instantiated for a level whose size the host does not know: its counts on the device, and the row
   // of h of each edge's receiver (EDGE; in_src: of its sender) or of each node (NODE)
   const unsigned long long *level_counts;
-  const int32_t *h_row;
+  const int32_t *h_row;    // (the split kernels: nullptr, or the same of a level whose rows of h are the classes below)
 };
 // Counts of a level in one word (what the blocks that make it take at once from one counter)
 constexpr int kCountBits = 21;
@@ -501,10 +501,11 @@ __global__ __launch_bounds__(2 * H) void mlp2_split_kernel(const Mlp2Args a) {
     const T *pa, *pb;
     if constexpr (KIND == KIND_EDGE) {
       meta = load_edge_meta(a.in_dst, a.n_rows, row0, nv, l32);
+      const int32_t *recv = a.h_row ? a.h_row : a.in_dst;
       pa = (const T *)a.h + (size_t)a.in_src[row] * H + g * V;
-      pb = (const T *)a.h + (size_t)meta.dst * H + g * V;
+      pb = (const T *)a.h + (size_t)recv[row] * H + g * V;
     } else {
-      pa = (const T *)a.h + (size_t)row * H + g * V;
+      pa = (const T *)a.h + (size_t)(a.h_row ? a.h_row[row] : row) * H + g * V;
       const int64_t ar = a.agg_src ? (int64_t)a.agg_src[row] : row;
       pb = ar < 0 ? (const T *)a.zero_row + g * V : (const T *)a.agg + (size_t)ar * H + g * V;
     }
@@ -659,10 +660,11 @@ __global__ __launch_bounds__(2 * H) void mlp2_split3_kernel(const Mlp2Args a) {
   [[maybe_unused]] EdgeTileMeta meta;
   if constexpr (KIND == KIND_EDGE) {
     meta = load_edge_meta(a.in_dst, a.n_rows, row0, nv, l32);
+    const int32_t *recv = a.h_row ? a.h_row : a.in_dst;
     pa = (const float *)a.h + (size_t)a.in_src[row] * H + g * 8;
-    pb = (const float *)a.h + (size_t)meta.dst * H + g * 8;
+    pb = (const float *)a.h + (size_t)recv[row] * H + g * 8;
   } else {
-    pa = (const float *)a.h + (size_t)row * H + g * 8;
+    pa = (const float *)a.h + (size_t)(a.h_row ? a.h_row[row] : row) * H + g * 8;
     const int64_t ar = a.agg_src ? (int64_t)a.agg_src[row] : row;
     pb = ar < 0 ? (const float *)a.zero_row + g * 8 : (const float *)a.agg + (size_t)ar * H + g * 8;
   }
@@ -750,7 +752,8 @@ __global__ __launch_bounds__(2 * H) void mlp2_split3_kernel(const Mlp2Args a) {
   for (unsigned rows = (unsigned)(lanes | lanes >> 32); rows; rows &= rows - 1) {
     const int r = __builtin_ctz(rows);
     const int64_t ro = row0 + r;
-    const int64_t first = KIND == KIND_EDGE ? a.in_src[ro] : ro, second = KIND == KIND_EDGE ? a.in_dst[ro] : a.agg_src ? a.agg_src[ro] : ro;
+    const int64_t first = KIND == KIND_EDGE ? a.in_src[ro] : a.h_row ? a.h_row[ro] : ro;
+    const int64_t second = KIND == KIND_EDGE ? (a.h_row ? a.h_row : a.in_dst)[ro] : a.agg_src ? a.agg_src[ro] : ro;
     const float *xa = (const float *)a.h + (size_t)first * H, *xe = a.edge_feat + (KIND == KIND_EDGE ? (size_t)ro * a.De : 0);
     const float *xb = second < 0 ? (const float *)a.zero_row : (const float *)(KIND == KIND_EDGE ? a.h : a.agg) + (size_t)second * H;
     const int K = KIND == KIND_EDGE ? 2 * H + a.De : 2 * H;

@@ -1,0 +1,42 @@
+"""fp32 encodes of a reduced batch, forward only, read the states of the level below by index: the same bits as from a copy of each
+class's state (the saving encode of the same batch) and as the whole batch, rows that are computed once more without parts
+among them (H = 128: values next to the largest float and beyond)."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("scale", [1.0, 1e34, 1e36])
+@pytest.mark.parametrize("hidden,rounds", [(64, 3), (128, 5), (256, 2)])
+def test_states_of_the_level_below(hidden, rounds, scale, monkeypatch):
+    import torch
+
+    import paper_2304_14698_amd as xrl
+    rng = np.random.Generator(np.random.PCG64(hidden))
+    model, _ = synth.make_config(1)
+    model.update(hidden=hidden, precision="fp32", rounds=rounds)
+    base = synth.transformer_dag(rng, 3)
+    state = synth.concat_states([synth.make_state(rng, base, 40, by_block=True)])
+    layout = xrl.weight_layout(model)
+    w = synth.init_weights(rng, layout, bias_range=0.1)
+    at = 0
+    for name, shape in layout:
+        n = int(np.prod(shape))
+        if name == "embed.W1":
+            w[at:at + n] *= np.float32(scale)
+        at += n
+    embs = []
+    for min_us in ("-1", "0"):
+        monkeypatch.setenv("XRL_DISTINCT_MIN_US", min_us)
+        enc = xrl.Encoder(model, w)
+        batch = enc.pack(state)
+        embs += [enc.encode(batch, save_for_backward=save).clone() for save in (False, True, False)]
+        assert (enc.batch_level(batch, rounds)[0] < len(state["node_op"]) // 2) == (min_us == "0")
+        batch.free()
+        enc.close()
+    nan = torch.isnan(embs[0])
+    for e in embs[1:]:
+        assert torch.equal(torch.isnan(e), nan) and torch.equal(e[~nan], embs[0][~nan])
