@@ -218,7 +218,7 @@ int xrl_batch_free(xrl_batch *b);   /* frees host and device copies; NULL is acc
  * where more has been refused, or captured calls hold addresses in a smaller workspace);
  * XRL_RESIDENT_MAX_GRAPHS (default 256; 0 = never) and XRL_RESIDENT_MAX_TILES (default 4) =
  * largest batch, in graphs and in 32-row tiles of nodes or edges per graph, that xrl_encode runs
- * as one launch with a block per graph (message-passing rounds of the MLP kind, rows of at most
+ * up to the readout as one launch with a block per graph (message-passing rounds of the MLP kind, rows of at most
  * 256 bytes, no receiver of more than 32 in-edges; results identical to the other path's) when it
  * saves for the backward pass -- and otherwise too if XRL_RESIDENT_MAX_GRAPHS is set: forward
  * only, a launch per layer is the faster way;
@@ -380,7 +380,7 @@ int xrl_mlp_backward(xrl_ctx *ctx, const xrl_batch *b, int32_t kind, int32_t rou
  * recorded since the last read for `kernel` and forgets them. Forward: {"embed", "edge",
  * "edge_fixup", "node", "pool", "readout", "heads"} (the steps of Section 3.4 / 3.3.2 in
  * execution order; "gat_linear", "gat_aggregate" with XRL_ROUND_GAT; "round" = a whole round of a small
- * batch in one launch, "resident" = its whole encoder; "levels" = the making of the levels of a batch that is
+ * batch in one launch, "resident" = its encoder up to the readout; "levels" = the making of the levels of a batch that is
  * reduced for one encode, R + 2 of them). Backward (Section 3.3.4):
  * {"bwd_edge", "bwd_node", "bwd_embed"} = gradients through the fused MLPs, "wgrad" = the weight
  * gradients of as many MLPs as one launch takes, with their reductions (a single product through

@@ -92,3 +92,45 @@ def test_readout_at_graph_counts(hidden, d_global, precision, readout):
             check_emb(got, O.encode(om, w, st), model, "emb")
         assert np.array_equal(got[:7], alone), n
         batch.free()
+
+
+@pytest.mark.parametrize("hidden,heads", [(256, (256, 64)), (128, (512, 200))])
+def test_heads_and_readout_under_capture(hidden, heads):
+    """Both heads forward and back and the readout's backward pass in a captured graph (launches with more LDS than one may have by itself):
+    every replay, with eager passes between, gives the eager bits."""
+    import torch
+    import paper_2304_14698_amd as xrl
+    model, state = synth.make_config(1, n_cand=40)
+    model.update(hidden=hidden, precision="fp32", rounds=1, head_hidden=heads)
+    side = torch.cuda.Stream()
+    enc = xrl.Encoder(model, weights_for(model), stream=side)
+    batch = enc.pack(state)
+    g = torch.Generator(device="cpu").manual_seed(3)
+    G = len(state["slot_mask"])
+    dl, ds = torch.randn(G, generator=g).cuda(), torch.randn(1, generator=g).cuda()
+
+    def step(dw):
+        emb = enc.encode(batch, save_for_backward=True)
+        pv = enc.policy_value(batch, emb)
+        demb = enc.policy_value_backward(batch, emb, dl, ds, ds, dw)
+        enc.encode_backward(batch, demb, dw)
+        return pv["logp"], pv["value"], demb
+    with torch.cuda.stream(side):
+        want_dw = torch.zeros(enc.n_weights, device="cuda")
+        want = step(want_dw)
+        torch.cuda.synchronize()
+        dw = torch.zeros_like(want_dw)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side, capture_error_mode="relaxed"):
+            dw.zero_()
+            out = step(dw)
+        for _ in range(3):
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(dw, want_dw) and all(torch.equal(a, b) for a, b in zip(out, want))
+            eager = torch.zeros_like(want_dw)
+            assert all(torch.equal(a, b) for a, b in zip(step(eager), want)) and torch.equal(eager, want_dw)
+            torch.cuda.synchronize()
+            dw.fill_(7.0)
+    batch.free()
+    enc.close()
