@@ -787,10 +787,12 @@ __global__ __launch_bounds__(256) void class_sum_kernel(const ClassSumArgs a) {
 // made three times, row g of window w the sum of rows g .. g + w - 1 (w = 1, 4, 16), and a run of consecutive graphs is read sixteen
 // of them at a time, four or one: 11 reads for 64 places of 16 transformer states, 16 of as many residual networks'. A wave takes 64
 // places, a row's columns over its lanes, so that what it reads next is the same for all of them; eight reads are in flight. us of
-// class_sum_kernel / of this kernel and the tables, H = 256: 4.35 M places 282 / 155 + 9, 15.9 M 979 / 856 + 14 (the classes of an
+// class_sum_kernel / of this kernel and the tables, H = 256: 4.35 M places 282 / 151 + 9, 15.9 M 979 / 857 + 14 (the classes of an
 // episode's states are shared, and the tables of 8 states are more than an XCD's L2); H = 128, 351 k places 22 / 28 + 7: below
-// 4096 places a compute unit a wave's chain of reads is the longer way. (256 places a wave 202 in place of 155, an XCD to consecutive
-// places 215: the states' shares differ.)
+// 4096 places a compute unit a wave's chain of reads is the longer way. 4.35 M places are bound by the instructions of a read, 15.9 M by
+// the 6 GB that come from behind the L2. (256 places a wave 202 in place of 155, an XCD to consecutive places 215: the states' shares differ.
+// The columns in two slices, on four XCDs each, 236 and 833, in four 440 and 1602, though the 6 GB become 2: a read costs
+// the same instructions for fewer columns.)
 constexpr int kWindows = 3;
 __host__ __device__ constexpr int window_size(int w) { return w == 0 ? 1 : w == 1 ? 4 : 16; }
 constexpr int kWindowStrip = 8;                // rows a thread makes, of four columns
@@ -832,98 +834,95 @@ template <int VEC> struct FloatVec;
 template <> struct FloatVec<1> { typedef float type; };
 template <> struct FloatVec<2> { typedef f32x2 type; };
 template <> struct FloatVec<4> { typedef f32x4 type; };
-// a.vals: the window tables, a.perm: the places' graphs; a.group: a multiple of 64
+// a.vals: the window tables, a.perm: the places' graphs; a.group: kPoolPlaces
+constexpr int kPoolPlaces = 64;                // places a wave takes, one a lane
 template <typename TOut, int H>
 __global__ __launch_bounds__(256) void pool_class_sum_kernel(const ClassSumArgs a, const int64_t G) {
   constexpr int VEC = H / 64, FLY = 8;
   typedef typename FloatVec<VEC>::type vec;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  // an XCD takes consecutive places, i.e. one state's graphs after the other's, whose part of the tables its L2 holds
-  const int64_t block = blockIdx.x, st = block * 4 + wave;
-  const int64_t p0 = st * a.group, p1 = p0 + a.group < a.n_rows ? p0 + a.group : a.n_rows;
+  const int64_t st = (int64_t)blockIdx.x * 4 + wave;
+  const int64_t p0 = st * kPoolPlaces;
   if (p0 >= a.n_rows) return;
+  const int n = a.n_rows - p0 < kPoolPlaces ? (int)(a.n_rows - p0) : kPoolPlaces;
   const int c = lane * VEC, c4 = c & ~3;
   const float *table = (const float *)a.vals + c;
   const bool masked = a.ymask != nullptr;
-  const int before = p0 > 0 ? a.seg[p0 - 1] : -1, behind = p1 < a.n_rows ? a.seg[p1] : -1;
-  auto place = [&](int64_t p) { return p + lane < p1 ? p + lane : p1 - 1; };
-  int next_g = a.perm[place(p0)], next_s = a.seg[place(p0)];
-  bool begun = __builtin_amdgcn_readfirstlane(next_s) == before;
+  const int64_t place = p0 + (lane < n ? lane : n - 1);
+  const int g = a.perm[place], s = a.seg[place];
+  const int seg_before = a.seg[p0 > 0 ? p0 - 1 : 0], seg_behind = a.seg[p0 + n < a.n_rows ? p0 + n : a.n_rows - 1];
+  const int before = p0 > 0 ? seg_before : -1, behind = p0 + n < a.n_rows ? seg_behind : -1;
+  bool begun = __builtin_amdgcn_readfirstlane(s) == before;
   float acc[VEC];
 #pragma unroll
   for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
-  for (int64_t q0 = p0; q0 < p1; q0 += 64) {
-    const int n = p1 - q0 < 64 ? (int)(p1 - q0) : 64;
-    const int g = next_g, s = next_s;
-    next_g = a.perm[place(q0 + 64)];
-    next_s = a.seg[place(q0 + 64)];
-    const int gl = __shfl_up(g, 1), sl = __shfl_up(s, 1);
-    const unsigned long long in = n < 64 ? (1ull << n) - 1 : ~0ull;
-    const unsigned long long starts = __ballot(lane == 0 || s != sl || g != gl + 1) & in;
-    // the lane's run [first, end), what of it goes by sixteen, by four, by one, and whether this place begins such a read
-    const unsigned long long upto = lane < 63 ? (2ull << lane) - 1 : ~0ull;
-    const int first = 63 - __builtin_clzll((starts & upto) | 1ull);
-    const unsigned long long later = starts & ~upto;
-    const int end = later ? __builtin_ctzll(later) : n, len = end - first, o = lane - first;
-    const int n16 = len & ~15, n4 = n16 + ((len - n16) & ~3);
-    const int w = o < n16 ? 2 : o < n4 ? 1 : 0;
-    const bool head = lane < n && (w == 2 ? (o & 15) == 0 : w == 1 ? ((o - n16) & 3) == 0 : true);
-    const unsigned row = (unsigned)(w * G) + (unsigned)g;        // of the three tables, one behind the other
-    // (a read is its class's last one where the place behind it is another class's: the first of the next 64, or of the next group)
-    const int then = q0 + 64 < p1 ? __builtin_amdgcn_readfirstlane(next_s) : behind;
-    const int next = __shfl_down(s, 1), of_next = lane + 1 < n ? next : then;
-    const unsigned long long ends = __ballot(lane < n && s != of_next);
-    unsigned long long todo = __ballot(head);
-    int l = 0;
-    while (todo) {
-      vec v[FLY];
-      unsigned word[FLY];
-      int of[FLY];
-      const int m = __popcll(todo) < FLY ? __popcll(todo) : FLY;
-      unsigned last = 0;                           // bit i: read i is its class's last
+  const int gl = __shfl_up(g, 1), sl = __shfl_up(s, 1);
+  const unsigned long long in = n < 64 ? (1ull << n) - 1 : ~0ull;
+  const unsigned long long starts = __ballot(lane == 0 || s != sl || g != gl + 1) & in;
+  // the lane's run [first, end), what of it goes by sixteen, by four, by one, and whether this place begins such a read
+  const unsigned long long upto = lane < 63 ? (2ull << lane) - 1 : ~0ull;
+  const int first = 63 - __builtin_clzll((starts & upto) | 1ull);
+  const unsigned long long later = starts & ~upto;
+  const int end = later ? __builtin_ctzll(later) : n, len = end - first, o = lane - first;
+  const int n16 = len & ~15, n4 = n16 + ((len - n16) & ~3);
+  const int w = o < n16 ? 2 : o < n4 ? 1 : 0;
+  const bool head = lane < n && (w == 2 ? (o & 15) == 0 : w == 1 ? ((o - n16) & 3) == 0 : true);
+  const unsigned row = (unsigned)(w * G) + (unsigned)g;        // of the three tables, one behind the other
+  // (a read is its class's last one where the place behind it is another class's)
+  const int next = __shfl_down(s, 1), of_next = lane + 1 < n ? next : behind;
+  const unsigned long long ends = __ballot(lane < n && s != of_next);
+  unsigned long long todo = __ballot(head);
+  int l = 0;
+  while (todo) {
+    vec v[FLY];
+    unsigned word[FLY], r[FLY];
+    int of[FLY];
+    const int m = __popcll(todo) < FLY ? __popcll(todo) : FLY;
+    unsigned last = 0;                           // bit i: read i is its class's last
 #pragma unroll
-      for (int i = 0; i < FLY; ++i) {              // (past the end the last read again, left out of the sums)
-        l = todo ? __builtin_ctzll(todo) : l;
-        todo &= todo - 1;
-        const unsigned r = (unsigned)__builtin_amdgcn_readlane((int)row, l);
-        of[i] = __builtin_amdgcn_readlane(s, l);
-        v[i] = *(const vec *)(table + (size_t)r * H);
-        const int stop = todo ? __builtin_ctzll(todo) : n;       // the read's places: l .. stop - 1
-        last |= (unsigned)((ends >> (stop - 1)) & 1) << i;
+    for (int i = 0; i < FLY; ++i) {              // (past the end the last read again, left out of the sums)
+      l = todo ? __builtin_ctzll(todo) : l;
+      todo &= todo - 1;
+      r[i] = (unsigned)__builtin_amdgcn_readlane((int)row, l);
+      of[i] = __builtin_amdgcn_readlane(s, l);
+      const int stop = todo ? __builtin_ctzll(todo) : n;       // the read's places: l .. stop - 1
+      last |= (unsigned)((ends >> (stop - 1)) & 1) << i;
+    }
+    // (the mask bits before the rows: loads return in order, so no wait for them later stands behind a class's store)
+    if (masked) {
+#pragma unroll
+      for (int i = 0; i < FLY; ++i)
+        if ((last >> i) & 1) word[i] = mask_word(a.ymask, of[i], H, c4);
+    }
+#pragma unroll
+    for (int i = 0; i < FLY; ++i) v[i] = *(const vec *)(table + (size_t)r[i] * H);
+#pragma unroll
+    for (int i = 0; i < FLY; ++i) {
+      if (i >= m) break;
+      if constexpr (VEC == 1) acc[0] += v[i];
+      else {
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) acc[j] += v[i][j];
       }
-      if (masked) {
+      const bool complete = (last >> i) & 1, group_ends = i == m - 1 && !todo;
+      if (complete || group_ends) {
+        if (begun || !complete) {
+          vec x;
+          if constexpr (VEC == 1) x = acc[0];
+          else for (int j = 0; j < VEC; ++j) x[j] = acc[j];
+          *(vec *)(a.carry + ((size_t)st * 2 + (begun ? 0 : 1)) * H + c) = x;
+        } else {
+          const unsigned bits = masked ? word[i] >> (4 * (c4 % 32 / 8)) >> (c & 3) : 0xfu;
 #pragma unroll
-        for (int i = 0; i < FLY; ++i)
-          if ((last >> i) & 1) word[i] = mask_word(a.ymask, of[i], H, c4);
-      }
-#pragma unroll
-      for (int i = 0; i < FLY; ++i) {
-        if (i >= m) break;
-        if constexpr (VEC == 1) acc[0] += v[i];
-        else {
-#pragma unroll
-          for (int j = 0; j < VEC; ++j) acc[j] += v[i][j];
+          for (int j = 0; j < VEC; ++j) acc[j] = (bits >> j) & 1u ? acc[j] : 0.f;
+          TOut *p = (TOut *)a.out + (size_t)of[i] * H + c;
+          if constexpr (VEC == 4) store4<TOut>(p, acc);
+          else if constexpr (VEC == 2 && sizeof(TOut) == 2) *(unsigned *)p = cvt_pk_bf16(acc[0], acc[1]);
+          else for (int j = 0; j < VEC; ++j) p[j] = (TOut)acc[j];
         }
-        const bool complete = (last >> i) & 1, group_ends = i == m - 1 && !todo && q0 + 64 >= p1;
-        if (complete || group_ends) {
-          if (begun || !complete) {
-            vec x;
-            if constexpr (VEC == 1) x = acc[0];
-            else for (int j = 0; j < VEC; ++j) x[j] = acc[j];
-            *(vec *)(a.carry + ((size_t)st * 2 + (begun ? 0 : 1)) * H + c) = x;
-          } else {
-            const unsigned bits = masked ? word[i] >> (4 * (c4 % 32 / 8)) >> (c & 3) : 0xfu;
+        begun = false;
 #pragma unroll
-            for (int j = 0; j < VEC; ++j) acc[j] = (bits >> j) & 1u ? acc[j] : 0.f;
-            TOut *p = (TOut *)a.out + (size_t)of[i] * H + c;
-            if constexpr (VEC == 4) store4<TOut>(p, acc);
-            else if constexpr (VEC == 2 && sizeof(TOut) == 2) *(unsigned *)p = cvt_pk_bf16(acc[0], acc[1]);
-            else for (int j = 0; j < VEC; ++j) p[j] = (TOut)acc[j];
-          }
-          begun = false;
-#pragma unroll
-          for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
-        }
+        for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
       }
     }
   }

@@ -2431,7 +2431,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
           rdx, d.graph_node_ptr, m.readout == XRL_READOUT_MEAN, G, H, dpool_rows);
       ClassSumArgs s;
       s.vals = dpool_rows; s.zero_row = c->zero_row; s.perm = q->mem_graph; s.seg = q->mem_seg; s.ptr = q->mem_ptr; s.n_rows = N; s.D = H;
-      s.ymask = mask; s.out = out; s.carry = ccarry; s.slices = 1; s.group = 64;
+      s.ymask = mask; s.out = out; s.carry = ccarry; s.slices = 1; s.group = kPoolPlaces;
       const int64_t groups = (N + s.group - 1) / s.group;
       const dim3 grid((unsigned)((groups + 3) / 4));
       if (H == 64) pool_class_sum_kernel<T, 64><<<grid, dim3(256), 0, c->stream>>>(s, G);
