@@ -636,17 +636,18 @@ inline size_t row_bwd_lds_floats(const RowBwdArgs &a) {
 }
 
 // Two rows a wave of a [*, w] array, row_of(r) for the block's row r < n (the last again past them): the first 256 columns
-// requested together, before any is waited for (16 bytes a lane where the width is a multiple of four, else four loads)
+// requested together, before any is waited for (16 bytes a lane where every row is aligned to that -- a caller's array need not be -- else
+// four loads)
 struct RowPiece {
   f32x4 v[2];
   template <typename RowOf>
-  __device__ __forceinline__ void request(const float *src, int w, int n, RowOf row_of) {
+  __device__ __forceinline__ void request(const float *src, int w, int n, RowOf row_of, bool aligned = true) {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int r = 2 * (threadIdx.x >> 6) + i;
       const float *q = src + (int64_t)row_of(r < n ? r : n - 1) * w;
-      if ((w & 3) == 0) {
+      if ((w & 3) == 0 && aligned) {
         v[i] = *(const f32x4 *)(q + (4 * lane < w ? 4 * lane : 0));
       } else {
 #pragma unroll
@@ -695,7 +696,7 @@ __device__ __forceinline__ void row_backward(const RowBwdArgs &a, int64_t row0, 
         __syncthreads();
         pm.request(a.dmean, wl, n, of_state);
       }
-      pd.request(a.dout, w, n, own);
+      pd.request(a.dout, w, n, own, ((uintptr_t)a.dout & 15) == 0);
       p0.store(a.act[L - 2], w0, n, own, [&](int r, int f, float v) { below0[r * pitch0 + f] = v; });
       if (L > 2) p1.store(a.act[0], w1, n, own, [&](int r, int f, float v) { below1[r * pitch1 + f] = v; });
       if (MASKED) pm.store(a.dmean, wl, n, of_state, [&](int r, int f, float v) { belowl[r * pitchl + f] = v; });

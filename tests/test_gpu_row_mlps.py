@@ -134,3 +134,29 @@ def test_heads_and_readout_under_capture(hidden, heads):
             dw.fill_(7.0)
     batch.free()
     enc.close()
+
+
+@pytest.mark.parametrize("hidden", [64, 128, 256])
+def test_upstream_gradient_of_any_alignment(hidden):
+    """A caller's gradient of the embeddings may begin at any fp32 address: the same bits as from an aligned copy, over 17 rows (a tile and
+    one row more)."""
+    import torch
+    import paper_2304_14698_amd as xrl
+    model, state = synth.make_config(1, n_cand=16)
+    model.update(hidden=hidden, precision="fp32", rounds=1)
+    enc = xrl.Encoder(model, weights_for(model))
+    batch = enc.pack(state)
+    enc.encode(batch, save_for_backward=True)
+    room = torch.randn(17 * hidden + 4, generator=torch.Generator().manual_seed(5)).cuda()
+    up = room[:17 * hidden].clone()
+    got = []
+    for offset in range(4):
+        at = room[offset:offset + 17 * hidden].view(17, hidden)
+        at.copy_(up.view(17, hidden))
+        assert at.data_ptr() % 16 == 4 * offset
+        dw = torch.zeros(enc.n_weights, device="cuda")
+        enc.encode_backward(batch, at, dw)
+        got.append(dw)
+    assert got[0].any() and all(torch.equal(got[0], g) for g in got[1:])
+    batch.free()
+    enc.close()
