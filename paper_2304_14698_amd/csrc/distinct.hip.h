@@ -790,7 +790,11 @@ __global__ __launch_bounds__(256) void class_sum_kernel(const ClassSumArgs a) {
 // class_sum_kernel / of this kernel and the tables, H = 256: 4.35 M places 282 / 151 + 9, 15.9 M 979 / 857 + 14 (the classes of an
 // episode's states are shared, and the tables of 8 states are more than an XCD's L2); H = 128, 351 k places 22 / 28 + 7: below
 // 4096 places a compute unit a wave's chain of reads is the longer way. 4.35 M places are bound by the instructions of a read, 15.9 M by
-// the 6 GB that come from behind the L2. (256 places a wave 202 in place of 155, an XCD to consecutive places 215: the states' shares differ.
+// the 6 GB that come from behind the L2. For H = 256 alone, where a row is 16 bytes a lane. There short runs cost nothing, us of a backward pass
+// of one round by class sums / by windows, graphs alike in runs of 1, 4, 16: 1.1 M places 245 / 239, 245 / 205, 246 / 197, 4.3 M 493 / 445,
+// 490 / 325, 489 / 306, 7.7 M 868 / 765, 867 / 548, 863 / 504. Of narrower rows a wave reads half and a quarter as much at a time: H = 128, 4.3 M
+// places in runs of 1, 7, 16 246 / 313, 245 / 245, 243 / 167, in a minibatch's own runs, five rounds, 845 / 842, 632 / 625, 809 / 809; H = 64
+// 158 / 281, 157 / 214, 156 / 135 and 523 / 542, 411 / 435, 510 / 529. (256 places a wave 202 in place of 155, an XCD to consecutive places 215: the states' shares differ.
 // The columns in two slices, on four XCDs each, 236 and 833, in four 440 and 1602, though the 6 GB become 2: a read costs
 // the same instructions for fewer columns.)
 constexpr int kWindows = 3;
@@ -830,22 +834,18 @@ __global__ __launch_bounds__(256) void pool_windows_kernel(const float *dx, cons
     *(f32x4 *)(rows + 2 * table + (size_t)(g0 + k) * H + c) = (x[k] + x[k + 4]) + (x[k + 8] + x[k + 12]);
   }
 }
-template <int VEC> struct FloatVec;
-template <> struct FloatVec<1> { typedef float type; };
-template <> struct FloatVec<2> { typedef f32x2 type; };
-template <> struct FloatVec<4> { typedef f32x4 type; };
 // a.vals: the window tables, a.perm: the places' graphs; a.group: kPoolPlaces
 constexpr int kPoolPlaces = 64;                // places a wave takes, one a lane
-template <typename TOut, int H>
+constexpr int kPoolWidth = 256;                // columns of a row, four a lane
+template <typename TOut>
 __global__ __launch_bounds__(256) void pool_class_sum_kernel(const ClassSumArgs a, const int64_t G) {
-  constexpr int VEC = H / 64, FLY = 8;
-  typedef typename FloatVec<VEC>::type vec;
+  constexpr int H = kPoolWidth, FLY = 8;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t st = (int64_t)blockIdx.x * 4 + wave;
   const int64_t p0 = st * kPoolPlaces;
   if (p0 >= a.n_rows) return;
   const int n = a.n_rows - p0 < kPoolPlaces ? (int)(a.n_rows - p0) : kPoolPlaces;
-  const int c = lane * VEC, c4 = c & ~3;
+  const int c = lane * 4;
   const float *table = (const float *)a.vals + c;
   const bool masked = a.ymask != nullptr;
   const int64_t place = p0 + (lane < n ? lane : n - 1);
@@ -853,9 +853,7 @@ __global__ __launch_bounds__(256) void pool_class_sum_kernel(const ClassSumArgs 
   const int seg_before = a.seg[p0 > 0 ? p0 - 1 : 0], seg_behind = a.seg[p0 + n < a.n_rows ? p0 + n : a.n_rows - 1];
   const int before = p0 > 0 ? seg_before : -1, behind = p0 + n < a.n_rows ? seg_behind : -1;
   bool begun = __builtin_amdgcn_readfirstlane(s) == before;
-  float acc[VEC];
-#pragma unroll
-  for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
   const int gl = __shfl_up(g, 1), sl = __shfl_up(s, 1);
   const unsigned long long in = n < 64 ? (1ull << n) - 1 : ~0ull;
   const unsigned long long starts = __ballot(lane == 0 || s != sl || g != gl + 1) & in;
@@ -874,7 +872,7 @@ __global__ __launch_bounds__(256) void pool_class_sum_kernel(const ClassSumArgs 
   unsigned long long todo = __ballot(head);
   int l = 0;
   while (todo) {
-    vec v[FLY];
+    f32x4 v[FLY];
     unsigned word[FLY], r[FLY];
     int of[FLY];
     const int m = __popcll(todo) < FLY ? __popcll(todo) : FLY;
@@ -892,37 +890,24 @@ __global__ __launch_bounds__(256) void pool_class_sum_kernel(const ClassSumArgs 
     if (masked) {
 #pragma unroll
       for (int i = 0; i < FLY; ++i)
-        if ((last >> i) & 1) word[i] = mask_word(a.ymask, of[i], H, c4);
+        if ((last >> i) & 1) word[i] = mask_word(a.ymask, of[i], H, c);
     }
 #pragma unroll
-    for (int i = 0; i < FLY; ++i) v[i] = *(const vec *)(table + (size_t)r[i] * H);
+    for (int i = 0; i < FLY; ++i) v[i] = *(const f32x4 *)(table + (size_t)r[i] * H);
 #pragma unroll
     for (int i = 0; i < FLY; ++i) {
       if (i >= m) break;
-      if constexpr (VEC == 1) acc[0] += v[i];
-      else {
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) acc[j] += v[i][j];
-      }
+      acc += v[i];
       const bool complete = (last >> i) & 1, group_ends = i == m - 1 && !todo;
       if (complete || group_ends) {
         if (begun || !complete) {
-          vec x;
-          if constexpr (VEC == 1) x = acc[0];
-          else for (int j = 0; j < VEC; ++j) x[j] = acc[j];
-          *(vec *)(a.carry + ((size_t)st * 2 + (begun ? 0 : 1)) * H + c) = x;
+          *(f32x4 *)(a.carry + ((size_t)st * 2 + (begun ? 0 : 1)) * H + c) = acc;
         } else {
-          const unsigned bits = masked ? word[i] >> (4 * (c4 % 32 / 8)) >> (c & 3) : 0xfu;
-#pragma unroll
-          for (int j = 0; j < VEC; ++j) acc[j] = (bits >> j) & 1u ? acc[j] : 0.f;
-          TOut *p = (TOut *)a.out + (size_t)of[i] * H + c;
-          if constexpr (VEC == 4) store4<TOut>(p, acc);
-          else if constexpr (VEC == 2 && sizeof(TOut) == 2) *(unsigned *)p = cvt_pk_bf16(acc[0], acc[1]);
-          else for (int j = 0; j < VEC; ++j) p[j] = (TOut)acc[j];
+          float y[4] = {acc[0], acc[1], acc[2], acc[3]};
+          store_masked4<TOut>((TOut *)a.out + (size_t)of[i] * H + c, y, masked, masked ? word[i] : 0u, c);
         }
         begun = false;
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) acc[j] = 0.f;
+        acc = f32x4{0.f, 0.f, 0.f, 0.f};
       }
     }
   }

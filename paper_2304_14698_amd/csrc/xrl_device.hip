@@ -190,7 +190,7 @@ struct xrl_ctx {
   int64_t p_min_rows = 8192;    // smallest row count for the persistent kernels (XRL_PERSISTENT_MIN_ROWS) when saving
   int64_t p_min_rows_forward = 8192;   // for the backward pass, and when not
   int64_t wide_min_rows = 1 << 18;   // rows of a launch's products from which 256-column weight-gradient tiles are used (XRL_WGRAD_WIDE_MIN_ROWS)
-  int64_t pool_window_nodes = 4096;  // nodes per compute unit from which the pool's gradient goes by windows of graphs (XRL_POOL_WINDOW_NODES)
+  int64_t pool_window_nodes = 4096;  // nodes per compute unit from which the pool's gradient of H = 256 goes by windows of graphs (XRL_POOL_WINDOW_NODES)
   int sum_steps = 0;                 // steps of a group of class_sum_kernel, 0: by the rows (XRL_SUM_STEPS)
   size_t grad_room = kGradRoom;      // XRL_GRAD_ROOM
   int64_t round_blocks = 0;          // blocks per compute unit up to which a round is one launch, see mlp2_round_kernel (XRL_ROUND_BLOCKS)
@@ -2325,9 +2325,11 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   // time, the sort that makes the groupings these sums go by (in the same place)
   size_t sort_bytes = 0;
   const size_t o_reduced = need;
+  const bool pool_windows = q && H == kPoolWidth && N >= c->pool_window_nodes * c->n_cu;      // (see pool_class_sum_kernel)
+  const size_t pool_rows = (size_t)(pool_windows ? kWindows : 1) * G * H;
   if (q) {
     acc((size_t)((std::max(N, max_rows) + kSumRows - 1) / kSumRows) * 2 * H * 4);
-    acc((size_t)kWindows * G * H * 4);
+    acc(pool_rows * 4);
     sort_bytes = q->grouped && q->grouped_fold == fold ? 0 : grouping_bytes(b, q, fold);
     need = std::max(need, sort_bytes);
   }
@@ -2360,7 +2362,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
   }
   bump.off = o_reduced;
   float *ccarry = q ? bump.take<float>((size_t)((std::max(N, max_rows) + kSumRows - 1) / kSumRows) * 2 * H) : nullptr;
-  float *dpool_rows = q ? bump.take<float>((size_t)kWindows * G * H) : nullptr;
+  float *dpool_rows = q ? bump.take<float>(pool_rows) : nullptr;
   WgradQueue wq;
   wq.partial = partial; wq.partial_floats = part;
   char *const room_base = c->bws + o_room;
@@ -2426,7 +2428,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
     const uint16_t *mask = kept ? c->ym_node[R - 1] : nullptr;
     dz2_given = mask != nullptr;
     T *const out = mask ? node_grads.dz2 : dhA;
-    if (N >= c->pool_window_nodes * c->n_cu) {                      // (see pool_class_sum_kernel)
+    if (pool_windows) {
       pool_windows_kernel<<<dim3((unsigned)(((G + kWindowStrip - 1) / kWindowStrip * (H / 4) + 255) / 256)), dim3(256), 0, c->stream>>>(
           rdx, d.graph_node_ptr, m.readout == XRL_READOUT_MEAN, G, H, dpool_rows);
       ClassSumArgs s;
@@ -2434,9 +2436,7 @@ int encode_backward_impl(xrl_ctx *c, const xrl_batch *b, const float *d_demb, fl
       s.ymask = mask; s.out = out; s.carry = ccarry; s.slices = 1; s.group = kPoolPlaces;
       const int64_t groups = (N + s.group - 1) / s.group;
       const dim3 grid((unsigned)((groups + 3) / 4));
-      if (H == 64) pool_class_sum_kernel<T, 64><<<grid, dim3(256), 0, c->stream>>>(s, G);
-      else if (H == 128) pool_class_sum_kernel<T, 128><<<grid, dim3(256), 0, c->stream>>>(s, G);
-      else pool_class_sum_kernel<T, 256><<<grid, dim3(256), 0, c->stream>>>(s, G);
+      pool_class_sum_kernel<T><<<grid, dim3(256), 0, c->stream>>>(s, G);
       class_sum_carried_kernel<T><<<dim3((unsigned)((groups + 4 * kCarryGroups - 1) / (4 * kCarryGroups))), dim3(256), 0, c->stream>>>(s);
       HIP_TRY(hipGetLastError());
     } else {

@@ -13,6 +13,36 @@ import synth
 pytestmark = pytest.mark.gpu
 
 
+def states_of_repeated_graphs(rng):
+    """Three base graphs over and over, by themselves and in runs; one that holds the first twice; a few of their own."""
+    base = [synth.layered_dag(rng, n) for n in (11, 7, 5)]
+    b, n = base[0], base[0].n_nodes
+    two = lambda x: np.concatenate([x, x])
+    twice = dataclasses.replace(b, op=two(b.op), dense=two(b.dense), layer=two(b.layer), block=two(b.block), efeat=two(b.efeat),
+                                src=np.concatenate([b.src, b.src + n]), dst=np.concatenate([b.dst, b.dst + n]))
+    graphs = [base[0]] * 333 + [base[int(i)] for i in rng.integers(0, 3, 200)] + [base[i % 17 == 0] for i in range(163)]
+    graphs[40] = graphs[41] = graphs[350] = twice                # classes with two places in a graph
+    graphs += [synth.layered_dag(rng, 6) for _ in range(9)]      # classes of one graph
+    return synth.concat_states([(graphs, np.ones(len(graphs), np.uint8))])
+
+
+def gradients(model, w, state, up, window_nodes, monkeypatch):
+    import torch
+
+    import paper_2304_14698_amd as xrl
+    monkeypatch.setenv("XRL_DISTINCT_MIN_US", "0")
+    monkeypatch.setenv("XRL_POOL_WINDOW_NODES", window_nodes)
+    enc = xrl.Encoder(model, w)
+    batch = enc.pack(state)
+    enc.encode(batch, save_for_backward=True)
+    assert enc.batch_level(batch, model["rounds"])[0] < len(state["node_op"]) // 4
+    dw = torch.zeros(enc.n_weights, device="cuda")
+    enc.encode_backward(batch, up, dw)
+    batch.free()
+    enc.close()
+    return dw
+
+
 @pytest.mark.parametrize("readout", ["sum", "mean"])
 @pytest.mark.parametrize("hidden,precision", [(64, "fp32"), (128, "fp32"), (256, "fp32"), (64, "bf16"), (128, "bf16"), (256, "bf16")])
 def test_pool_gradient_by_windows(hidden, precision, readout, monkeypatch):
@@ -22,29 +52,25 @@ def test_pool_gradient_by_windows(hidden, precision, readout, monkeypatch):
     rng = np.random.Generator(np.random.PCG64(hidden))
     model, _ = synth.make_config(1)
     model.update(hidden=hidden, precision=precision, rounds=2, readout=readout)
-    base = [synth.layered_dag(rng, n) for n in (11, 7, 5)]
-    b, n = base[0], base[0].n_nodes
-    two = lambda x: np.concatenate([x, x])
-    twice = dataclasses.replace(b, op=two(b.op), dense=two(b.dense), layer=two(b.layer), block=two(b.block), efeat=two(b.efeat),
-                                src=np.concatenate([b.src, b.src + n]), dst=np.concatenate([b.dst, b.dst + n]))
-    graphs = [base[0]] * 333 + [base[int(i)] for i in rng.integers(0, 3, 200)] + [base[i % 17 == 0] for i in range(163)]
-    graphs[40] = graphs[41] = graphs[350] = twice                # classes with two places in a graph
-    graphs += [synth.layered_dag(rng, 6) for _ in range(9)]      # classes of one graph
-    state = synth.concat_states([(graphs, np.ones(len(graphs), np.uint8))])
+    state = states_of_repeated_graphs(rng)
     w = synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1)
-    up = torch.randn(len(graphs), hidden, generator=torch.Generator().manual_seed(1)).cuda()
-    monkeypatch.setenv("XRL_DISTINCT_MIN_US", "0")
-    got = []
-    for nodes in ("0", "1000000000"):
-        monkeypatch.setenv("XRL_POOL_WINDOW_NODES", nodes)
-        enc = xrl.Encoder(model, w)
-        batch = enc.pack(state)
-        enc.encode(batch, save_for_backward=True)
-        assert enc.batch_level(batch, 2)[0] < len(state["node_op"]) // 4
-        dw = torch.zeros(enc.n_weights, device="cuda")
-        enc.encode_backward(batch, up, dw)
-        got.append(dw.double())
-        batch.free()
-        enc.close()
+    up = torch.randn(len(state["slot_mask"]), hidden, generator=torch.Generator().manual_seed(1)).cuda()
+    got = [gradients(model, w, state, up, nodes, monkeypatch).double() for nodes in ("0", "1000000000")]
     assert float(got[1].norm()) > 0
     assert float((got[0] - got[1]).norm() / got[1].norm()) <= (1e-5 if precision == "fp32" else 2e-2)
+
+
+@pytest.mark.parametrize("hidden", [64, 128])
+def test_narrow_rows_go_by_class_sums(hidden, monkeypatch):
+    """Windows are for rows of 256 columns: narrower ones take the class sums' order whatever the threshold, so the same bits."""
+    import torch
+
+    import paper_2304_14698_amd as xrl
+    rng = np.random.Generator(np.random.PCG64(hidden))
+    model, _ = synth.make_config(1)
+    model.update(hidden=hidden, precision="fp32", rounds=2)
+    state = states_of_repeated_graphs(rng)
+    w = synth.init_weights(rng, xrl.weight_layout(model), bias_range=0.1)
+    up = torch.randn(len(state["slot_mask"]), hidden, generator=torch.Generator().manual_seed(1)).cuda()
+    got = [gradients(model, w, state, up, nodes, monkeypatch) for nodes in ("0", "1000000000")]
+    assert got[0].any() and torch.equal(got[0], got[1])
