@@ -1272,17 +1272,26 @@ int launch_gat_round(xrl_ctx *c, const GatArgs &a, const GatNext &next) {
   return c->m.hidden == 64 ? launch_gat_round_h<T, 64>(c, a, next) : launch_gat_round_h<T, 128>(c, a, next);
 }
 
-// (Beyond 64 KB, with what a kernel holds besides, a launch has to be allowed its LDS: heads 512 wide, hundreds of global attributes.)
-template <typename Kernel>
-int allow_row_lds(Kernel kern, size_t lds) {
-  if (lds > 40 * 1024) HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+// Beyond 64 KB, with what a kernel holds besides, a launch has to be allowed its LDS: 71 KB for the backward pass of heads of 256 and 64 at
+// H = 256, more for wider ones and for hundreds of global attributes. The permission is the process's, one per kernel, while the size is a
+// context's; so it is given once, for the most that any model needs: rows of 512 forward, heads of 512 and 512 at H = 256 back.
+constexpr int kRowWidest = 512;
+const size_t kRowForwardMost = row_lds_floats(row_pitch(kRowWidest)) * sizeof(float);
+const size_t kRowBackwardMost = sizeof(float) * kRowTile * (4 * row_pitch(kRowWidest) + row_pitch(256));
+template <auto KERN>
+int allow_row_lds(size_t most) {
+  static std::atomic<bool> allowed{false};
+  if (!allowed.load(std::memory_order_relaxed)) {
+    HIP_TRY(hipFuncSetAttribute((const void *)KERN, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most));
+    allowed.store(true, std::memory_order_relaxed);
+  }
   return XRL_OK;
 }
-template <typename Kernel, typename Args>
-int launch_rows(Kernel kern, const Args &a, int64_t blocks, size_t lds_floats, hipStream_t stream) {
+template <auto KERN, typename... Args>
+int launch_rows(size_t most, int64_t blocks, size_t lds_floats, hipStream_t stream, const Args &...args) {
   const size_t lds = lds_floats * sizeof(float);
-  if (int rc = allow_row_lds(kern, lds)) return rc;
-  kern<<<dim3((unsigned)blocks), dim3(kRowThreads), lds, stream>>>(a);
+  if (int rc = allow_row_lds<KERN>(most)) return rc;
+  KERN<<<dim3((unsigned)blocks), dim3(kRowThreads), lds, stream>>>(args...);
   HIP_TRY(hipGetLastError());
   return XRL_OK;
 }
@@ -1325,7 +1334,7 @@ RowFwdArgs row_fwd_args(const xrl_ctx *c, const MlpRef &r, bool relu_last, const
 int launch_readout(xrl_ctx *c, const RowFwdArgs &a) {
   if (a.n_rows <= 0) return XRL_OK;
   return with_readout_widths(c, [&](auto fwd, auto) {
-    return launch_rows(row_forward_kernel<decltype(fwd)>, a, row_blocks(a.n_rows), row_lds_floats(a.pitch), c->stream);
+    return launch_rows<row_forward_kernel<decltype(fwd)>>(kRowForwardMost, row_blocks(a.n_rows), row_lds_floats(a.pitch), c->stream, a);
   });
 }
 
@@ -1350,7 +1359,7 @@ int launch_heads(xrl_ctx *c, const xrl_batch *b, const float *d_emb, float *logi
   a.counter = counter; a.logp = counted ? logp : nullptr; a.entropy = entropy; a.action = action; a.zmean = zmean;
   const int64_t blocks = row_blocks(b->G) + (b->S + a.value_rows - 1) / a.value_rows;
   const int rc = with_head_widths(c, [&](auto fwd, auto) {
-    return launch_rows(heads_kernel<decltype(fwd)>, a, blocks, row_lds_floats(a.policy.pitch), c->stream);
+    return launch_rows<heads_kernel<decltype(fwd)>>(kRowForwardMost, blocks, row_lds_floats(a.policy.pitch), c->stream, a);
   });
   if (rc) {
     // (a launch that the runtime rejected has not run; one that failed later may have left
@@ -1605,7 +1614,7 @@ RowBwdArgs row_bwd_args(const xrl_ctx *c, const MlpRef &r, bool relu_last, float
 int launch_readout_backward(xrl_ctx *c, const RowBwdArgs &a) {
   if (a.n_rows <= 0) return XRL_OK;
   return with_readout_widths(c, [&](auto, auto bwd) {
-    return launch_rows(row_backward_kernel<decltype(bwd), false>, a, row_blocks(a.n_rows), row_bwd_lds_floats(a), c->stream);
+    return launch_rows<row_backward_kernel<decltype(bwd), false>>(kRowBackwardMost, row_blocks(a.n_rows), row_bwd_lds_floats(a), c->stream, a);
   });
 }
 
@@ -2789,12 +2798,11 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
       if (G == 0) return XRL_OK;
       Timed t(c, TK_POOL);
       return with_readout_widths(c, [&](auto fwd, auto) -> int {
-        auto kern = cls ? graph_readout_kernel<decltype(fwd), T, PV, true> : graph_readout_kernel<decltype(fwd), T, PV, false>;
-        const size_t lds = row_lds_floats(ra.pitch) * sizeof(float);
-        if (int rc2 = allow_row_lds(kern, lds)) return rc2;
-        kern<<<dim3((unsigned)G), dim3(kRowThreads), lds, c->stream>>>(hlast, d.graph_node_ptr, cls, mean, c->pool, ra);
-        HIP_TRY(hipGetLastError());
-        return XRL_OK;
+        auto go = [&](auto mapped) {
+          return launch_rows<graph_readout_kernel<decltype(fwd), T, PV, decltype(mapped)::value>>(
+              kRowForwardMost, G, row_lds_floats(ra.pitch), c->stream, hlast, d.graph_node_ptr, cls, mean, c->pool, ra);
+        };
+        return cls ? go(std::true_type()) : go(std::false_type());
       });
     }
     { Timed t(c, TK_POOL);
@@ -3508,9 +3516,9 @@ int policy_value_backward_run(xrl_ctx *c, const xrl_batch *b, const float *d_emb
   RowBwdArgs pb = row_bwd_args(c, c->L.policy, false, pact, dlogit, G, pdz, d_demb);
   pb.mask = d.mask; pb.state_graph_ptr = d.state_graph_ptr; pb.dmean = dzs; pb.inv_valid = inv_n; pb.S = (int)S;
   rc = with_head_widths(c, [&](auto, auto bwd) {
-    if (int rc2 = launch_rows(heads_state_bwd_kernel<decltype(bwd)>, sb, (S + sb.value_rows - 1) / sb.value_rows,
-                              row_bwd_lds_floats(sb.value), c->stream)) return rc2;
-    return launch_rows(row_backward_kernel<decltype(bwd), true>, pb, row_blocks(G), row_bwd_lds_floats(pb), c->stream);
+    if (int rc2 = launch_rows<heads_state_bwd_kernel<decltype(bwd)>>(kRowBackwardMost, (S + sb.value_rows - 1) / sb.value_rows, row_bwd_lds_floats(sb.value),
+                                                                     c->stream, sb)) return rc2;
+    return launch_rows<row_backward_kernel<decltype(bwd), true>>(kRowBackwardMost, row_blocks(G), row_bwd_lds_floats(pb), c->stream, pb);
   });
   if (rc) return rc;
   const SmallWgradMlp heads[2] = {{&c->L.policy, d_emb, nullptr, H, 0, pact, pdz, G}, {&c->L.value, zmean, nullptr, H, 0, vact, vdz, S}};

@@ -160,3 +160,52 @@ def test_upstream_gradient_of_any_alignment(hidden):
     assert got[0].any() and all(torch.equal(got[0], g) for g in got[1:])
     batch.free()
     enc.close()
+
+
+def test_models_of_other_sizes_in_other_threads():
+    """Heads that need more and less LDS than a launch may have by itself, of the same kernels, called from two threads on streams of their own:
+    every pass gives the bits of a pass alone."""
+    import threading
+
+    import torch
+    import paper_2304_14698_amd as xrl
+    work = []
+    for heads in ((512, 512), (300, 100)):
+        model, state = synth.make_config(1, n_cand=20)
+        model.update(hidden=128, precision="fp32", rounds=1, head_hidden=heads)
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            enc = xrl.Encoder(model, weights_for(model), stream=stream)
+            batch = enc.pack(state)
+            emb = torch.randn(21, 128, generator=torch.Generator().manual_seed(1)).cuda()
+            d = torch.randn(21, generator=torch.Generator().manual_seed(2)).cuda()
+            dw = torch.zeros(enc.n_weights, device="cuda")
+            torch.cuda.synchronize()
+
+        def step(enc=enc, batch=batch, emb=emb, d=d, dw=dw):
+            pv = enc.policy_value(batch, emb)
+            return [pv["logp"], pv["value"], enc.policy_value_backward(batch, emb, d, d[:1], d[:1], dw)]
+        with torch.cuda.stream(stream):
+            want = [x.clone() for x in step()]
+            torch.cuda.synchronize()
+        work.append((enc, batch, stream, step, want))
+    failed = []
+
+    def run(stream, step, want):
+        try:
+            with torch.cuda.stream(stream):
+                for _ in range(30):
+                    got = step()
+                    stream.synchronize()
+                    assert all(torch.equal(a, b) for a, b in zip(got, want))
+        except BaseException as e:
+            failed.append(e)
+    threads = [threading.Thread(target=run, args=w[2:]) for w in work]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for w in work:
+        w[1].free()
+        w[0].close()
+    assert not failed, failed
