@@ -52,10 +52,58 @@ struct SmallWgradArgs {
   int n_jobs;
   SmallWgradJob job[kWgradJobs];
 };
-__global__ __launch_bounds__(256) void small_wgrad_kernel(const SmallWgradArgs a) {
+// What a slot's gradient lacks of the mean embedding's, kMeanRows slots a block: demb[j] = mask[j] ? demb[j] + dmean[s] * inv_valid[s] : 0,
+// s the slot's state. Nothing of the weight gradients depends on it, nor it on them.
+constexpr int kMeanRows = 64;
+struct MeanShareArgs {
+  float *demb;                   // [G, H]
+  const float *dmean, *inv_valid;
+  const uint8_t *mask;
+  const int32_t *state_graph_ptr;
+  int G, S, H;
+  int block0;                    // the launch's first block of these
+};
+__device__ __forceinline__ void add_mean_share(const MeanShareArgs &a, int j0, int *state, float *share) {
+  const int t = threadIdx.x, n = a.G - j0 < kMeanRows ? a.G - j0 : kMeanRows;
+  if (t < n) {
+    int lo = 0, hi = a.S;                     // state_graph_ptr[lo] <= j0 + t < state_graph_ptr[hi]
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (a.state_graph_ptr[mid] <= j0 + t) lo = mid; else hi = mid;
+    }
+    state[t] = lo;
+    share[t] = a.mask[j0 + t] ? a.inv_valid[lo] : -1.f;
+  }
+  __syncthreads();
+  const int q = a.H / 4, step = 256 / q, c = (t % q) * 4;
+  for (int r = t / q; r < n; r += 4 * step) {
+    f32x4 m[4], d[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {             // (past the last row the last again, not stored)
+      const int k = r + i * step < n ? r + i * step : n - 1;
+      m[i] = *(const f32x4 *)(a.dmean + (size_t)state[k] * a.H + c);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d[i][e] = a.demb[(size_t)(j0 + k) * a.H + c + e];      // (a caller's array: of any alignment)
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int k = r + i * step;
+      if (k >= n) break;
+      const float w = share[k];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a.demb[(size_t)(j0 + k) * a.H + c + e] = w >= 0.f ? d[i][e] + m[i][e] * w : 0.f;
+    }
+  }
+}
+__global__ __launch_bounds__(256) void small_wgrad_kernel(const SmallWgradArgs a, const MeanShareArgs mean) {
   __shared__ __align__(16) float sums[4][kWgradTile][kWgradTile];
   __shared__ float dz_sum[4][kWgradTile];
   touch_args(a);
+  touch_args(mean);
+  if ((int)blockIdx.x >= mean.block0) {
+    add_mean_share(mean, ((int)blockIdx.x - mean.block0) * kMeanRows, (int *)sums, dz_sum[0]);
+    return;
+  }
   int ji = 0;
 #pragma unroll
   for (int i = 1; i < kWgradJobs; ++i) ji += i < a.n_jobs && (int)blockIdx.x >= a.job[i].block0 ? 1 : 0;

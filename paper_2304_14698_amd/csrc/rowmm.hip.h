@@ -618,20 +618,12 @@ struct RowBwdArgs {
   int64_t n_rows;
   float *dz[3];            // [n_rows, width of layer l]
   float *dx;               // [n_rows, d_in]
-  int pitch;
-  // the policy head's dx also takes its state's share of the gradient of the mean embedding, and nothing where a slot
-  // is masked: dx[j] = mask[j] ? dx[j] + dmean[s] * inv_valid[s] : 0 (mask null: neither)
-  const uint8_t *mask;
-  const int32_t *state_graph_ptr;
-  const float *dmean, *inv_valid;
-  int S;
+  int n_layers, pitch;
 };
-// LDS of a backward block: x, x2 and, of every layer below the last, the outputs whose ReLU the gradient passes (below the first: the
-// states' gradients of the mean embedding)
+// LDS of a backward block: x, x2 and, of every layer but the last, the outputs whose ReLU the gradient passes
 inline size_t row_bwd_lds_floats(const RowBwdArgs &a) {
   size_t n = 2 * a.pitch;
-  for (const RowMap &m : a.map)
-    if (m.w) n += row_pitch(m.n_out);
+  for (int m = 0; m + 1 < a.n_layers; ++m) n += row_pitch(a.map[m].n_out);
   return kRowTile * n;
 }
 
@@ -669,37 +661,27 @@ struct RowPiece {
     }
   }
 };
-// The sixteen rows from row0, of which those below row_end exist (at least one); state, share (LDS, with MASKED only): the slots'
-// states and factors of the mean embedding's gradient, -1 where masked. first() writes them, and dout where that is this block's to write.
-template <typename W, bool MASKED, typename First>
-__device__ __forceinline__ void row_backward(const RowBwdArgs &a, int64_t row0, int64_t row_end, float *x, int pitch, const int *state,
-                                             const float *share, First first) {
+// The sixteen rows from row0, of which those below row_end exist (at least one).
+template <typename W>
+__device__ __forceinline__ void row_backward(const RowBwdArgs &a, int64_t row0, int64_t row_end, float *x, int pitch) {
   constexpr int L = W::N;
   static_assert(L == 2 || L == 3, "row-MLPs of two or three layers");
   const int lane = threadIdx.x & 63, q4 = lane >> 4;
   const int n = (int)(row_end - row0 < kRowTile ? row_end - row0 : kRowTile);
   // what post takes, of each map
-  const int pitch0 = row_pitch(W::template out<0>(a.map)), pitch1 = row_pitch(W::template out<1>(a.map)), pitchl = row_pitch(W::template out<L - 1>(a.map));
-  float *const below0 = x + 2 * kRowTile * pitch, *const below1 = below0 + kRowTile * pitch0, *const below2 = below1 + kRowTile * pitch1;
-  float *const belowl = L > 2 ? below2 : below1;
+  const int pitch0 = row_pitch(W::template out<0>(a.map)), pitch1 = row_pitch(W::template out<1>(a.map));
+  float *const below0 = x + 2 * kRowTile * pitch, *const below1 = below0 + kRowTile * pitch0;
   (void)row_maps<W>(a.map, x, x + kRowTile * pitch, pitch,
     [&]() {
       auto own = [&](int r) { return row0 + r; };
-      auto of_state = [&](int r) { return state[r]; };
-      const int w = W::template in<0>(a.map), w0 = W::template out<0>(a.map), w1 = W::template out<1>(a.map), wl = W::template out<L - 1>(a.map);
-      RowPiece p0, p1, pr, pm, pd;
+      const int w = W::template in<0>(a.map), w0 = W::template out<0>(a.map), w1 = W::template out<1>(a.map);
+      RowPiece p0, p1, pr, pd;
       p0.request(a.act[L - 2], w0, n, own);
       if (L > 2) p1.request(a.act[0], w1, n, own);
       if (a.relu_last) pr.request(a.act[L - 1], w, n, own);
-      first();
-      if constexpr (MASKED) {
-        __syncthreads();
-        pm.request(a.dmean, wl, n, of_state);
-      }
       pd.request(a.dout, w, n, own, ((uintptr_t)a.dout & 15) == 0);
       p0.store(a.act[L - 2], w0, n, own, [&](int r, int f, float v) { below0[r * pitch0 + f] = v; });
       if (L > 2) p1.store(a.act[0], w1, n, own, [&](int r, int f, float v) { below1[r * pitch1 + f] = v; });
-      if (MASKED) pm.store(a.dmean, wl, n, of_state, [&](int r, int f, float v) { belowl[r * pitchl + f] = v; });
       if (a.relu_last) pr.store(a.act[L - 1], w, n, own, [&](int r, int f, float v) { x[r * pitch + f] = v; });
       float *dz = a.dz[L - 1] + row0 * w;
       pd.store(a.dout, w, n, own, [&](int r, int f, float v) {
@@ -723,78 +705,76 @@ __device__ __forceinline__ void row_backward(const RowBwdArgs &a, int64_t row0, 
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int r = 4 * q4 + i;
-        if (M + 1 < L) {
-          if (!((M ? below1[r * pitch1 + f] : below0[r * pitch0 + f]) > 0.f)) y[i] = 0.f;
-        } else if (MASKED) {
-          const float k = r < n ? share[r] : -1.f;
-          y[i] = k >= 0.f ? y[i] + belowl[r * pitchl + f] * k : 0.f;
-        }
+        if (M + 1 < L && !((M ? below1[r * pitch1 + f] : below0[r * pitch0 + f]) > 0.f)) y[i] = 0.f;
         if (r < n) to[r * w + f] = y[i];
         else y[i] = 0.f;
       }
     });
 }
-template <typename W, bool MASKED>
+template <typename W>
 __global__ __launch_bounds__(kRowThreads, W::waves) void row_backward_kernel(const RowBwdArgs a) {
   extern __shared__ __align__(16) float sm[];
-  __shared__ int state[kRowTile];
-  __shared__ float share[kRowTile];
-  const int64_t row0 = (int64_t)blockIdx.x * kRowTile;
   touch_args(a);
-  row_backward<W, MASKED>(a, row0, a.n_rows, sm, a.pitch, state, share, [&]() {
-    if constexpr (MASKED) {
-      for (int s = threadIdx.x; s < a.S; s += kRowThreads) {
-        const int64_t p0 = a.state_graph_ptr[s] - row0, p1 = a.state_graph_ptr[s + 1] - row0;
-        for (int64_t r = p0 > 0 ? p0 : 0; r < kRowTile && r < p1; ++r) {
-          state[r] = s;
-          share[r] = a.mask[row0 + r] ? a.inv_valid[s] : -1.f;
-        }
-      }
-    }
-  });
+  row_backward<W>(a, (int64_t)blockIdx.x * kRowTile, a.n_rows, sm, a.pitch);
 }
 
-// Backward of what a state's slots have in common, value_rows states per block: from the logits and the outputs' gradients
+// Backward of the masked log-softmax, states_per_block states per block: from the logits and the outputs' gradients
 //   dlogit_k = c_k - p_k * sum_valid c  -  dent * p_k * (logp_k + entropy),  c = dlogp      (0 when masked)
-// and the value head's backward pass (whose dx is the gradient of the mean embedding).
-struct HeadsStateBwdArgs {
-  RowBwdArgs value;
+// and one over the number of the state's valid slots.
+struct HeadsSoftmaxBwdArgs {
   const float *logit;
   const uint8_t *mask;
   const int32_t *state_graph_ptr;
   const float *dlogp, *dentropy;
   float *dlogit, *inv_valid;
-  int S, value_rows;
+  int S, states_per_block;
+};
+__global__ __launch_bounds__(kRowThreads) void heads_softmax_bwd_kernel(const HeadsSoftmaxBwdArgs a) {
+  __shared__ float red[2 * kRowWaves];
+  touch_args(a);
+  const int t = threadIdx.x, s0 = blockIdx.x * a.states_per_block, s1 = s0 + a.states_per_block < a.S ? s0 + a.states_per_block : a.S;
+  auto ld = [&](int j) { return a.logit[j]; };
+  for (int s = s0; s < s1; ++s) {
+    const int j0 = a.state_graph_ptr[s], j1 = a.state_graph_ptr[s + 1];
+    auto slots = [&](auto wide) {
+      using Softmax = StateSoftmax<decltype(wide)::value>;
+      const int at = j0 + (int)(t & (Softmax::STEP - 1));
+      const float first = at < j1 ? a.dlogp[at] : 0.f, de = a.dentropy[s];
+      const Softmax m(ld, a.mask, j0, j1, red);
+      auto c = [&](int j) { return j == m.first ? first : a.dlogp[j]; };
+      float cs = 0.f;
+      m.each(ld, a.mask, [&](int j, float) { cs += c(j); });
+      cs = Softmax::sum(cs, 0.f, red).x;
+      for (int j = m.first; j < j1; j += Softmax::STEP)
+        if (j == m.first ? !m.on : !a.mask[j]) a.dlogit[j] = 0.f;
+      m.each(ld, a.mask, [&](int j, float x) {
+        const float lp = x - m.lse, p = expf(lp);
+        a.dlogit[j] = c(j) - p * cs - de * p * (lp + m.entropy);
+      });
+      if (m.first == j0) a.inv_valid[s] = 1.f / m.n_valid;
+    };
+    if (j1 - j0 > 64) slots(MapIndex<1>());
+    else if ((s - s0) % kRowWaves == t >> 6) slots(MapIndex<0>());    // (the same choice for all threads of a wave)
+  }
+}
+
+// Both heads' MLPs back, in one launch: the value head's rows (value_rows states a block; its dx is the gradient of the mean
+// embedding) in the first blocks, the policy head's in the others. A slot's dx still lacks its state's share of the mean embedding's
+// gradient: the last blocks of small_wgrad_kernel's launch add it. Where few slots leave the chip empty, a launch is as long as one tile's way through
+// the layers, so the two heads beside each other are what counts: us of a call with the value head in front of the policy head, in the softmax's
+// launch / so, 15 slots, heads of 128 and 64, H = 64 36.8 / 28.4, H = 256 43.8 / 33.2, of 512 and 512 127 / 88 and 153 / 108; at 4624 slots of
+// H = 256 and heads of 256 and 64 the launches 13.1 + 22.4 / 4.7 + 19.0.
+struct HeadsBwdArgs {
+  RowBwdArgs value, policy;          // of the same widths
+  int value_rows, value_blocks;
 };
 template <typename W>
-__global__ __launch_bounds__(kRowThreads, W::waves) void heads_state_bwd_kernel(const HeadsStateBwdArgs a) {
+__global__ __launch_bounds__(kRowThreads, W::waves) void heads_backward_kernel(const HeadsBwdArgs a) {
   extern __shared__ __align__(16) float sm[];
-  __shared__ float red[2 * kRowWaves];
-  const int t = threadIdx.x, s0 = blockIdx.x * a.value_rows, s1 = s0 + a.value_rows < a.S ? s0 + a.value_rows : a.S;
   touch_args(a);
-  row_backward<W, false>(a.value, s0, s1, sm, a.value.pitch, nullptr, nullptr, [&]() {
-    auto ld = [&](int j) { return a.logit[j]; };
-    for (int s = s0; s < s1; ++s) {
-      const int j0 = a.state_graph_ptr[s], j1 = a.state_graph_ptr[s + 1];
-      auto slots = [&](auto wide) {
-        using Softmax = StateSoftmax<decltype(wide)::value>;
-        const int at = j0 + (int)(t & (Softmax::STEP - 1));
-        const float first = at < j1 ? a.dlogp[at] : 0.f, de = a.dentropy[s];
-        const Softmax m(ld, a.mask, j0, j1, red);
-        auto c = [&](int j) { return j == m.first ? first : a.dlogp[j]; };
-        float cs = 0.f;
-        m.each(ld, a.mask, [&](int j, float) { cs += c(j); });
-        cs = Softmax::sum(cs, 0.f, red).x;
-        for (int j = m.first; j < j1; j += Softmax::STEP)
-          if (j == m.first ? !m.on : !a.mask[j]) a.dlogit[j] = 0.f;
-        m.each(ld, a.mask, [&](int j, float x) {
-          const float lp = x - m.lse, p = expf(lp);
-          a.dlogit[j] = c(j) - p * cs - de * p * (lp + m.entropy);
-        });
-        if (m.first == j0) a.inv_valid[s] = 1.f / m.n_valid;
-      };
-      if (j1 - j0 > 64) slots(MapIndex<1>());
-      else if ((s - s0) % kRowWaves == t >> 6) slots(MapIndex<0>());    // (the same choice for all threads of a wave)
-    }
-  });
+  const bool is_value = (int)blockIdx.x < a.value_blocks;
+  const RowBwdArgs &mlp = is_value ? a.value : a.policy;            // (one copy of the layers' code for both)
+  const int rows = is_value ? a.value_rows : kRowTile;
+  const int64_t row0 = (int64_t)(is_value ? (int)blockIdx.x : (int)blockIdx.x - a.value_blocks) * rows;
+  row_backward<W>(mlp, row0, row0 + rows < mlp.n_rows ? row0 + rows : mlp.n_rows, sm, a.policy.pitch);
 }

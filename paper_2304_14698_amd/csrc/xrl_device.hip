@@ -1274,10 +1274,10 @@ int launch_gat_round(xrl_ctx *c, const GatArgs &a, const GatNext &next) {
 
 // Beyond 64 KB, with what a kernel holds besides, a launch has to be allowed its LDS: 71 KB for the backward pass of heads of 256 and 64 at
 // H = 256, more for wider ones and for hundreds of global attributes. The permission is the process's, one per kernel, while the size is a
-// context's; so it is given once, for the most that any model needs: rows of 512 forward, heads of 512 and 512 at H = 256 back.
+// context's; so it is given once, for the most that any model needs: rows of 512 forward, heads of 512 and 512 back.
 constexpr int kRowWidest = 512;
 const size_t kRowForwardMost = row_lds_floats(row_pitch(kRowWidest)) * sizeof(float);
-const size_t kRowBackwardMost = sizeof(float) * kRowTile * (4 * row_pitch(kRowWidest) + row_pitch(256));
+const size_t kRowBackwardMost = sizeof(float) * kRowTile * 4 * row_pitch(kRowWidest);
 template <auto KERN>
 int allow_row_lds(size_t most) {
   static std::atomic<bool> allowed{false};
@@ -1608,18 +1608,19 @@ RowBwdArgs row_bwd_args(const xrl_ctx *c, const MlpRef &r, bool relu_last, float
     widest = std::max(widest, r.d_out[l]);
   }
   a.dout = dout; a.n_rows = n_rows; a.dx = dx;
+  a.n_layers = r.n_layers;
   a.pitch = row_pitch(widest);
   return a;
 }
 int launch_readout_backward(xrl_ctx *c, const RowBwdArgs &a) {
   if (a.n_rows <= 0) return XRL_OK;
   return with_readout_widths(c, [&](auto, auto bwd) {
-    return launch_rows<row_backward_kernel<decltype(bwd), false>>(kRowBackwardMost, row_blocks(a.n_rows), row_bwd_lds_floats(a), c->stream, a);
+    return launch_rows<row_backward_kernel<decltype(bwd)>>(kRowBackwardMost, row_blocks(a.n_rows), row_bwd_lds_floats(a), c->stream, a);
   });
 }
 
 // dW, db of every layer of one or two small row-MLPs in one launch (and one reduction): x of layer 0 is
-// [x1 | x2], of layer l > 0 act[l-1]. Rows are cut into chunks of kSmallWgradRows, fewer and larger ones
+// [x1 | x2], of layer l > 0 act[l-1]. mean: what else the launch does (see MeanShareArgs). Rows are cut into chunks of kSmallWgradRows, fewer and larger ones
 // where `partial` (partial_floats long) has no room for as many.
 constexpr int kSmallWgradRows = 128;
 struct SmallWgradMlp {
@@ -1638,7 +1639,8 @@ inline size_t small_wgrad_partial_floats(const MlpRef &r, int64_t n_rows) {
   const int64_t nc = small_wgrad_chunks(n_rows);
   return nc > 1 ? n * (size_t)nc : 0;
 }
-int launch_small_wgrads(xrl_ctx *c, const SmallWgradMlp *mlps, int n_mlps, float *dweights, float *partial, size_t partial_floats) {
+int launch_small_wgrads(xrl_ctx *c, const SmallWgradMlp *mlps, int n_mlps, float *dweights, float *partial, size_t partial_floats,
+                        const MeanShareArgs *mean = nullptr) {
   SmallWgradArgs a;
   memset(&a, 0, sizeof(a));
   int blocks = 0, entries = 0;
@@ -1683,7 +1685,11 @@ int launch_small_wgrads(xrl_ctx *c, const SmallWgradMlp *mlps, int n_mlps, float
     }
   }
   if (blocks == 0) return XRL_OK;
-  small_wgrad_kernel<<<dim3((unsigned)blocks), dim3(256), 0, c->stream>>>(a);
+  MeanShareArgs m = {};
+  if (mean) m = *mean;
+  m.block0 = blocks;
+  blocks += (m.G + kMeanRows - 1) / kMeanRows;
+  small_wgrad_kernel<<<dim3((unsigned)blocks), dim3(256), 0, c->stream>>>(a, m);
   if (entries > 0) small_wgrad_reduce_kernel<<<dim3((unsigned)entries), dim3(256), 0, c->stream>>>(a);
   HIP_TRY(hipGetLastError());
   return XRL_OK;
@@ -3508,21 +3514,25 @@ int policy_value_backward_run(xrl_ctx *c, const xrl_batch *b, const float *d_emb
   const xrl_batch_device &d = b->dev;
   // forward of the heads, keeping every layer's output
   if ((rc = launch_heads(c, b, d_emb, logit, nullptr, nullptr, nullptr, zmean, value, pact, vact, c->d_counter))) return rc;
-  // backward: what belongs to a state (the softmax, the value head), then the slots' policy MLP
-  HeadsStateBwdArgs sb;
-  sb.value = row_bwd_args(c, c->L.value, false, vact, d_dvalue, S, vdz, dzs);
+  // backward: the softmax of each state, both heads' MLPs, then their weight gradients and the slots' share of the mean embedding's gradient
+  HeadsSoftmaxBwdArgs sb;
   sb.logit = logit; sb.mask = d.mask; sb.state_graph_ptr = d.state_graph_ptr; sb.dlogp = d_dlogp; sb.dentropy = d_dentropy;
-  sb.dlogit = dlogit; sb.inv_valid = inv_n; sb.S = (int)S; sb.value_rows = value_rows(c, S);
-  RowBwdArgs pb = row_bwd_args(c, c->L.policy, false, pact, dlogit, G, pdz, d_demb);
-  pb.mask = d.mask; pb.state_graph_ptr = d.state_graph_ptr; pb.dmean = dzs; pb.inv_valid = inv_n; pb.S = (int)S;
+  sb.dlogit = dlogit; sb.inv_valid = inv_n; sb.S = (int)S; sb.states_per_block = value_rows(c, S);
+  const int64_t state_blocks = (S + sb.states_per_block - 1) / sb.states_per_block;
+  heads_softmax_bwd_kernel<<<dim3((unsigned)state_blocks), dim3(kRowThreads), 0, c->stream>>>(sb);
+  HeadsBwdArgs hb;
+  hb.value = row_bwd_args(c, c->L.value, false, vact, d_dvalue, S, vdz, dzs);
+  hb.policy = row_bwd_args(c, c->L.policy, false, pact, dlogit, G, pdz, d_demb);
+  hb.value_rows = sb.states_per_block; hb.value_blocks = (int)state_blocks;
   rc = with_head_widths(c, [&](auto, auto bwd) {
-    if (int rc2 = launch_rows<heads_state_bwd_kernel<decltype(bwd)>>(kRowBackwardMost, (S + sb.value_rows - 1) / sb.value_rows, row_bwd_lds_floats(sb.value),
-                                                                     c->stream, sb)) return rc2;
-    return launch_rows<row_backward_kernel<decltype(bwd), true>>(kRowBackwardMost, row_blocks(G), row_bwd_lds_floats(pb), c->stream, pb);
+    return launch_rows<heads_backward_kernel<decltype(bwd)>>(kRowBackwardMost, state_blocks + row_blocks(G), row_bwd_lds_floats(hb.policy), c->stream, hb);
   });
   if (rc) return rc;
   const SmallWgradMlp heads[2] = {{&c->L.policy, d_emb, nullptr, H, 0, pact, pdz, G}, {&c->L.value, zmean, nullptr, H, 0, vact, vdz, S}};
-  if ((rc = launch_small_wgrads(c, heads, 2, d_dweights, spart, spart_floats))) return rc;
+  MeanShareArgs mean;
+  mean.demb = d_demb; mean.dmean = dzs; mean.inv_valid = inv_n; mean.mask = d.mask; mean.state_graph_ptr = d.state_graph_ptr;
+  mean.G = (int)G; mean.S = (int)S; mean.H = H;
+  if ((rc = launch_small_wgrads(c, heads, 2, d_dweights, spart, spart_floats, &mean))) return rc;
   HIP_TRY(hipGetLastError());
   return XRL_OK;
 }

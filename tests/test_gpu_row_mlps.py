@@ -209,3 +209,37 @@ def test_models_of_other_sizes_in_other_threads():
         w[1].free()
         w[0].close()
     assert not failed, failed
+
+
+@pytest.mark.parametrize("hidden", [64, 256])
+def test_slots_share_of_the_mean_gradient(hidden):
+    """The embeddings' gradient where its last step -- the mean embedding's share, 64 slots a block -- has full blocks, a remainder, states that
+    cross blocks, masked slots, and an output that begins at any fp32 address."""
+    import torch
+    import paper_2304_14698_amd as xrl
+    model, _ = synth.make_config(1)
+    model.update(hidden=hidden, precision="fp32")
+    rng = np.random.Generator(np.random.PCG64(hidden))
+    state = heads_only_state(rng, model, 13, 24)
+    G, S, w, om = len(state["slot_mask"]), 13, weights_for(model), oracle_model(model)
+    assert G > 64 and G % 64
+    emb = rng.standard_normal((G, hidden)).astype(np.float32)
+    dlogp = (rng.standard_normal(G) * state["slot_mask"]).astype(np.float32)
+    dvalue, dentropy = (rng.standard_normal(S).astype(np.float32) for _ in range(2))
+    ref, _ = O.policy_value_backward(om, w, emb.astype(np.float64), state, dlogp, dvalue, dentropy)
+    enc = xrl.Encoder(model, w)
+    batch = enc.pack(state)
+    t = lambda x: torch.from_numpy(x).cuda()
+    args, dw, got = [t(x) for x in (emb, dlogp, dvalue, dentropy)], torch.zeros(enc.n_weights, device="cuda"), []
+    for offset in (0, 1, 2):
+        room = torch.full((G * hidden + 4,), 7.0, device="cuda")
+        at = room[offset:offset + G * hidden]
+        enc._empty = lambda shape, dtype=None: at.view(shape)
+        assert enc.policy_value_backward(batch, *args, dw).data_ptr() == at.data_ptr()
+        got.append(at.view(G, hidden).cpu().numpy())
+        assert (room[:offset] == 7.0).all() and (room[offset + G * hidden:] == 7.0).all()
+    assert np.linalg.norm(got[0] - ref) <= 1e-5 * np.linalg.norm(ref)
+    assert not got[0][state["slot_mask"] == 0].any()
+    assert all(np.array_equal(got[0], g) for g in got[1:])
+    batch.free()
+    enc.close()
