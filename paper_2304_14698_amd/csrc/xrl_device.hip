@@ -2973,7 +2973,7 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
     set_graph(g);
     a.agg_src = g.agg_src;
     if (!q && r == 0 && !save) one_launch = b->n_split_tiles == 0 && round_applies<T>(c, g, b->at<int32_t>(b->o_in_ptr));
-    if (q && !save) one_launch = round_applies<T>(c, g, nullptr);
+    if (q && !save) one_launch = !below && round_applies<T>(c, g, nullptr);     // (a round in one launch reads copied states)
     if (one_launch) {
       RoundArgs ra;
       set_w(c->edge[r]);
