@@ -2631,6 +2631,9 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   const LevelGraph whole = batch_graph(b);
   auto lev = [&](int l) -> const LevelGraph & { return q ? q->lv[l] : whole; };
   c->min_rows_now = !save ? c->p_min_rows_forward : (q && c->p_min_rows <= kPersistentMinRows ? 1 : c->p_min_rows);
+  // A level's classes split those of the level below. fp32 kernels read the states there by index; others, and the backward
+  // pass, go by a copy of the state each. (Re-evaluation of 73 k nodes in five levels, H = 128: 217 -> 203 us.)
+  const bool below = q && !save && sizeof(T) == 4;
   // ---- workspace plan
   const int nh = save ? R + 1 : (R > 0 ? 2 : 1), nagg = save ? R : (R > 0 ? 1 : 0);
   int64_t maxN = 0, max_tiles = 0;
@@ -2643,7 +2646,7 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   const bool gat = m.round_kind == XRL_ROUND_GAT;
   for (int i = 0; i < nh; ++i) acc(h_rows(i) * H * sizeof(T));
   for (int i = 0; i < nagg; ++i) acc(a_rows(i) * H * sizeof(T));        // (GAT: the agg slot holds z)
-  for (int i = 0; q && i < nagg; ++i) acc(a_rows(i) * H * sizeof(T));
+  for (int i = 0; q && !below && i < nagg; ++i) acc(a_rows(i) * H * sizeof(T));
   const xrl_batch_device &d = b->dev;
   const bool resident_ok = !gat && !q && H * sizeof(T) <= 256 && d.graph_tile_ptr && R <= kResidentMaxRounds;
   const int64_t resident_max = save ? c->resident_max_graphs : c->resident_max_forward;
@@ -2738,7 +2741,7 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   c->hx.assign(R + 1, nullptr);
   for (int i = 0; i < nh; ++i) hb[i] = bump.take<T>(h_rows(i) * H);
   for (int i = 0; i < nagg; ++i) ab[i] = bump.take<T>(a_rows(i) * H);
-  for (int i = 0; q && i < nagg; ++i) xb[i] = bump.take<T>(a_rows(i) * H);
+  for (int i = 0; q && !below && i < nagg; ++i) xb[i] = bump.take<T>(a_rows(i) * H);
   c->gat_ss.assign(R, nullptr);
   c->gat_sd.assign(R, nullptr);
   for (int i = 0; i < n_gs; ++i) {
@@ -2929,9 +2932,6 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
     T *hnext = save ? hb[r + 1] : hb[(r + 1) & 1];
     const LevelGraph &g = lev(r + 1);
     const int64_t N = g.N, E = g.E;
-    // The level's classes split those of the level below. fp32 kernels read the states there by index; others, and the backward
-    // pass, go by a copy of the state each. (Re-evaluation of 73 k nodes in five levels, H = 128: 217 -> 203 us.)
-    const bool below = q && !save && sizeof(T) == 4;
     if (q && !below) {
       T *x = save ? xb[r] : xb[0];
       const int pieces = H / PV;

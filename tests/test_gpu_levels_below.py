@@ -40,3 +40,31 @@ def test_states_of_the_level_below(hidden, rounds, scale, monkeypatch):
     nan = torch.isnan(embs[0])
     for e in embs[1:]:
         assert torch.equal(torch.isnan(e), nan) and torch.equal(e[~nan], embs[0][~nan])
+
+
+def test_levels_read_by_index_need_no_room_for_copies(monkeypatch):
+    """The encode that reduces a batch to levels as large as the batch itself -- no two nodes alike, H = 256, one round -- takes the levels' own
+    memory, 303 bytes a node, and no more workspace than the whole batch had (copies of the states would be 1 KB a node, of which the whole
+    batch's plan has room for 440 bytes: 887 in all)."""
+    import torch
+
+    import paper_2304_14698_amd as xrl
+    monkeypatch.setenv("XRL_DISTINCT_MIN_US", "0")
+    rng = np.random.Generator(np.random.PCG64(1))
+    model, _ = synth.make_config(1)
+    model.update(hidden=256, precision="fp32", rounds=1)
+    graphs = [synth.layered_dag(rng, 50) for _ in range(1900)]
+    state = synth.concat_states([(graphs, np.ones(len(graphs), np.uint8))])
+    n = len(state["node_op"])
+    enc = xrl.Encoder(model, synth.init_weights(rng, xrl.weight_layout(model)))
+    batch = enc.pack(state)
+    free, embs = [], []
+    for _ in range(2):
+        embs.append(enc.encode(batch))
+        torch.cuda.synchronize()
+        free.append(torch.cuda.mem_get_info()[0])
+        level = enc.batch_level(batch, 1)[0]
+    assert level > 0.9 * n and torch.equal(*embs)
+    assert free[0] - free[1] < 450 * n, (free, n)
+    batch.free()
+    enc.close()
