@@ -1,7 +1,8 @@
-"""Both heads where a policy block takes one, two or four slots: the last block partly filled, states of one slot (several
-in a block), states that begin or end inside a block, widths of 16-byte columns and of single ones. Against the float64
+"""Both heads at the edges of a policy block's sixteen slots: the last block full, of one slot and of fifteen, states of one slot (several
+in a block), states that begin or end inside a block or fill it, states of 64 slots (a wave's softmax) and of 65 (the block's), several states
+to a block of the value head, widths of 16-byte columns and of single ones. Against the float64
 oracle: a dot of n fp32 terms errs by at most n * 2^-24 of the sum of their absolute values, here three layers of at most 512
-terms, and by far less as it is summed in slices: 2e-5 of the largest value. A state's results do not depend on the batch around it."""
+terms, and by far less as it is summed in four chains: 2e-5 of the largest value. A state's results do not depend on the batch around it."""
 import numpy as np
 import pytest
 
@@ -13,8 +14,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("hidden,heads,n_states,n_cand", [
-    (128, None, 127, 0), (64, None, 43, 4), (256, None, 1, 128), (128, (100, 35), 3, 42),      # one slot a block, then two
-    (64, None, 1023, 0), (128, None, 93, 10), (128, (100, 35), 206, 4), (256, None, 6, 205)])  # two, then four, with remainders
+    (128, None, 127, 0), (64, None, 43, 4), (256, None, 1, 128), (128, (100, 35), 3, 42),
+    (64, None, 1023, 0), (128, None, 93, 10), (128, (100, 35), 206, 4), (256, None, 6, 205),
+    (128, None, 4, 15), (64, None, 2, 16), (256, None, 2, 63), (64, (100, 35), 2, 64), (256, None, 1040, 0)])
 def test_heads_at_rows_per_block(hidden, heads, n_states, n_cand):
     import torch
     import paper_2304_14698_amd as xrl

@@ -58,15 +58,15 @@ def test_heads_of_any_width(hidden, heads, n_states, n_cand):
             assert np.linalg.norm(dw[sl] - ref_dw[sl]) <= tol, name
 
 
-def first_graphs(state, n):
-    """The state's first n graphs, as one state."""
-    N, E = state["graph_node_ptr"][n], state["graph_edge_ptr"][n]
-    out = {k: state[k][:N] for k in ("node_op", "node_dense")}
-    out.update({k: state[k][:E] for k in ("edge_src", "edge_dst", "edge_feat")})
-    out.update({k: state[k][:n + 1] for k in ("graph_node_ptr", "graph_edge_ptr")})
+def some_graphs(state, a, z):
+    """The state's graphs a .. z - 1, as one state."""
+    n0, n1, e0, e1 = (int(state[k][g]) for k in ("graph_node_ptr", "graph_edge_ptr") for g in (a, z))
+    out = {k: state[k][n0:n1] for k in ("node_op", "node_dense")}
+    out.update({k: state[k][e0:e1] for k in ("edge_src", "edge_dst", "edge_feat")})
+    out.update({k: state[k][a:z + 1] - state[k][a] for k in ("graph_node_ptr", "graph_edge_ptr")})
     if state.get("graph_global") is not None:
-        out["graph_global"] = state["graph_global"][:n]
-    return dict(out, n_states=1, state_graph_ptr=np.array([0, n], np.int32), slot_mask=state["slot_mask"][:n])
+        out["graph_global"] = state["graph_global"][a:z]
+    return dict(out, n_states=1, state_graph_ptr=np.array([0, z - a], np.int32), slot_mask=state["slot_mask"][a:z])
 
 
 @pytest.mark.parametrize("readout", ["sum", "mean"])
@@ -81,17 +81,21 @@ def test_readout_at_graph_counts(hidden, d_global, precision, readout):
     w, om = weights_for(model), oracle_model(model)
     enc = xrl.Encoder(model, w)
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
-    alone = None
-    for n in (7, n_cu, n_cu + 1, 2 * n_cu - 1, 2 * n_cu):
-        n = min(n, 531)
-        st = first_graphs(state, n)
-        batch = enc.pack(st)
-        got = enc.encode(batch).cpu().numpy()
-        if alone is None:
-            alone = got
-            check_emb(got, O.encode(om, w, st), model, "emb")
-        assert np.array_equal(got[:7], alone), n
+
+    def encoded(a, z):
+        batch = enc.pack(some_graphs(state, a, z))
+        out = enc.encode(batch).cpu().numpy()
         batch.free()
+        return out
+    # every graph's row where a block makes it alone, a few of them against the oracle
+    pieces = [(a, min(a + n_cu, 531)) for a in range(0, 531, n_cu)]
+    alone = np.concatenate([encoded(*p) for p in pieces])
+    assert np.array_equal(encoded(0, 7), alone[:7])
+    for a in (0, 524):
+        check_emb(alone[a:a + 7], O.encode(om, w, some_graphs(state, a, a + 7)), model, "emb")
+    for n in (n_cu, n_cu + 1, n_cu + 16, 2 * n_cu - 1, 2 * n_cu, 531):
+        n = min(n, 531)
+        assert np.array_equal(encoded(0, n), alone[:n]), n
 
 
 @pytest.mark.parametrize("hidden,heads", [(256, (256, 64)), (128, (512, 200))])
