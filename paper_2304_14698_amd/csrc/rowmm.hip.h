@@ -288,13 +288,13 @@ __global__ __launch_bounds__(kRowThreads, W::waves) void row_forward_kernel(cons
 }
 
 // ---- readout: the sum (or mean) of a graph's node states by a block, stored as pool[g, :] and left in row (LDS; nullable).
-// H / VEC lanes cover a node's row with 16-byte loads. The nodes are dealt over 512 / (H / VEC) groups, of which a thread of a block of
+// (row: column k at (k % 4) * quarter + k / 4, see RowVector.) H / VEC lanes cover a node's row with 16-byte loads. The nodes are dealt over 512 / (H / VEC) groups, of which a thread of a block of
 // THREADS threads holds V = 512 / THREADS (eight loads in flight in all), and the groups' sums are added in an order that does not
-// depend on THREADS: a graph's sum is the same bits in a batch of any size.
+// depend on THREADS: a graph's sum is the same bits in every batch that comes here (of at most 4096 nodes a graph on average, see the readout's dispatch).
 // MAPPED: row_of[n] is the row of h that holds node n's state (else row n); it is read a step ahead. part: THREADS * VEC floats of LDS.
 template <typename T, int VEC, int H, bool MAPPED, int THREADS>
 __device__ __forceinline__ void graph_pool(const T *h, const int32_t *graph_node_ptr, const int32_t *row_of, int g, int mean, float *pool,
-                                           float *part, float *row) {
+                                           float *part, float *row, int quarter) {
   constexpr int tpr = H / VEC, Q = 256 / tpr, B = THREADS / tpr, NG = 2 * Q, V = 512 / THREADS, UF = 8 / V;
   const int t = threadIdx.x, c0 = (t % tpr) * VEC, q = t / tpr, n0 = graph_node_ptr[g], n1 = graph_node_ptr[g + 1];
   float acc[V][VEC];
@@ -347,33 +347,134 @@ __device__ __forceinline__ void graph_pool(const T *h, const int32_t *graph_node
     }
     if (mean) a *= 1.f / (float)(n1 - n0 > 1 ? n1 - n0 : 1);
     pool[(size_t)g * H + t] = a;
-    if (row) row[t] = a;
+    if (row) row[(t & 3) * quarter + (t >> 2)] = a;
   }
 }
 // Many graphs: a block sums one, the readout MLP follows in a launch of its own (row_forward_kernel), whose blocks
-// share the weights among sixteen graphs.
-template <typename T, int VEC, int H, bool MAPPED, int THREADS>
-__global__ __launch_bounds__(THREADS) void graph_pool_kernel(const T *h, const int32_t *graph_node_ptr, const int32_t *row_of, int mean, float *pool) {
-  __shared__ __align__(16) float part[THREADS * VEC];
-  graph_pool<T, VEC, H, MAPPED, THREADS>(h, graph_node_ptr, row_of, blockIdx.x, mean, pool, part, nullptr);
+// share the weights among sixteen graphs. (1040 graphs of 338 nodes, by 512 threads a graph 13.8 us, by 256 11.4.)
+constexpr int kPoolThreads = 256;
+template <typename T, int VEC, int H, bool MAPPED>
+__global__ __launch_bounds__(kPoolThreads) void graph_pool_kernel(const T *h, const int32_t *graph_node_ptr, const int32_t *row_of, int mean, float *pool) {
+  __shared__ __align__(16) float part[kPoolThreads * VEC];
+  graph_pool<T, VEC, H, MAPPED, kPoolThreads>(h, graph_node_ptr, row_of, blockIdx.x, mean, pool, part, nullptr, 0);
 }
-// Few graphs: both in one launch, a block per graph, the MLP's first weights requested ahead of the sum.
-template <typename W, typename T, int VEC, bool MAPPED>
+// Few graphs: both in one launch, a block per graph, which has one row for the MLP: the matrix instruction would spend its time on fifteen
+// that are not there (H = 256: 3.6 us a layer, of one block on a compute unit). v_mfma_f32_16x16x4_f32 adds its four products to a sum one after
+// the other, as four fmaf do (1M outputs each of ordinary, wide, subnormal and infinite operands: no bit differs); so a lane takes one of an
+// output's four sums (RowMaps) through the same products in the same order, and a graph's embedding is the same bits either way.
+// Lane 4 * c + j of a wave has sum j of output 16 * tile + c: of a tile's fragments it reads every 64th float, the wave 256 bytes at a time, one
+// stream per tile. x lies in LDS by quarters, contraction index k at (k % 4) * quarter + k / 4, so that a lane reads a group's four at once.
+template <int H>
+struct RowVector {
+  static constexpr int TILES = H / 16, PER = TILES > kRowWaves ? 2 : 1, RING = PER == 2 ? 6 : 12;    // tiles a wave; groups in flight
+  float w[RING][4][PER];
+  int lane, wave, groups, half;                       // of the map at hand (see RowMaps)
+  const float *p[PER];
+  int g0, g1;                                         // this wave's groups; none: no tile
+  bool upper;
+  __device__ __forceinline__ int tile(int i) const { return half ? wave >> 1 : wave * PER + i; }
+  __device__ __forceinline__ void begin(const RowMap &map, int n_in) {
+    groups = (n_in + 15) >> 4;
+    half = TILES <= kRowWaves / 2 && groups > kRowFrags / 2 ? (groups + 1) >> 1 : 0;
+    upper = half && (wave & 1);
+    g0 = upper ? half : 0;
+    g1 = tile(0) >= TILES ? g0 : half && !upper ? half : groups;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) p[i] = (const float *)(map.w + (unsigned)((tile(0) < TILES ? tile(i) : 0) * groups + g0) * 64u) + lane;
+  }
+  // groups FROM .. TO - 1 of those in flight
+  template <int FROM, int TO> __device__ __forceinline__ void request() {
+#pragma unroll
+    for (int r = FROM; r < TO; ++r)
+      if (g0 + r < g1) load(r, r);
+  }
+  __device__ __forceinline__ void load(int r, int g) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int i = 0; i < PER; ++i) w[r][q][i] = p[i][(unsigned)g * 256u + q * 64];
+  }
+  // the sums of this wave's outputs, from `from` on (the first one's; a tile's lower half's), complete in all four lanes
+  __device__ __forceinline__ void run(const float *x, int quarter, const float *from, float *extra, float *y) {
+    float s[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) s[i] = (lane & 3) == 0 && !upper ? from[i] : 0.f;
+    const float *xl = x + (lane & 3) * quarter + 4 * g0;
+    const int n = g1 - g0;
+    for (int g = 0; g < n; g += RING) {
+#pragma unroll
+      for (int r = 0; r < RING; ++r) {
+        if (g + r >= n) break;
+        const f32x4 v = *(const f32x4 *)(xl + 4 * (g + r));
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int i = 0; i < PER; ++i) s[i] = fmaf(v[q], w[r][q][i], s[i]);
+        if (g + r + RING < n) load(r, g + r + RING);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      s[i] += __shfl_xor(s[i], 2);                    // (s0 + s2) + (s1 + s3)
+      y[i] = s[i] + __shfl_xor(s[i], 1);
+    }
+    if (half) {
+      if (upper && (lane & 3) == 0) extra[16 * tile(0) + (lane >> 2)] = y[0];
+      __syncthreads();
+      if (!upper && g1 > g0) y[0] += extra[16 * tile(0) + (lane >> 2)];
+    }
+  }
+  __device__ __forceinline__ bool owns() const { return g1 > g0 && !upper && (lane & 3) == 0; }   // a lane that has outputs to store
+};
+// floats a quarter of the widest row takes, its lanes' 16-byte reads in different banks
+constexpr int kRowQuarter = 512 / 4 + 8;
+template <typename T, int VEC, int H, bool MAPPED>
 __global__ __launch_bounds__(kRowThreads, 4) void graph_readout_kernel(const T *h, const int32_t *graph_node_ptr, const int32_t *row_of, int mean,
                                                                        float *pool, const RowFwdArgs a) {
-  constexpr int H = W::w[1];
-  extern __shared__ __align__(16) float sm[];
-  __shared__ __align__(16) float part[kRowThreads * VEC];
+  using V = RowVector<H>;
+  __shared__ __align__(16) float part[kRowThreads * VEC], x[2][4 * kRowQuarter], extra[H];
   touch_args(a);
-  const int g = blockIdx.x, t = threadIdx.x, pitch = a.pitch;
-  (void)row_forward<W, false>(a, g, g + 1, sm, pitch, [&]() {
-    RowBiases<W> b;
-    b.request(a);
-    for (int i = t; i < kRowTile * pitch; i += kRowThreads)        // row 0: the pool (below), the global attributes
-      if (i >= H) sm[i] = i < H + a.w2 ? a.in2[(size_t)g * a.w2 + (i - H)] : 0.f;
-    b.store(a, sm, pitch);
-    graph_pool<T, VEC, H, MAPPED, kRowThreads>(h, graph_node_ptr, row_of, g, mean, pool, part, sm);
-  });
+  const int g = blockIdx.x, t = threadIdx.x, n_in = H + a.w2;
+  V m;
+  m.lane = t & 63;
+  m.wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  m.begin(a.map[0], n_in);
+  m.template request<0, V::RING / 2>();
+  float from[V::PER];
+  int f[V::PER];
+  auto outputs = [&](const float *bias) {             // this wave's of the map at hand, and what their sums start from
+#pragma unroll
+    for (int i = 0; i < V::PER; ++i) {
+      f[i] = 16 * m.tile(i) + (m.lane >> 2);
+      from[i] = bias[f[i] < H ? f[i] : H - 1];
+    }
+  };
+  outputs(a.b[0]);
+  for (int k = H + t; k < ((n_in + 15) & ~15); k += kRowThreads) x[0][(k & 3) * kRowQuarter + (k >> 2)] = k < n_in ? a.in2[(size_t)g * a.w2 + (k - H)] : 0.f;
+  graph_pool<T, VEC, H, MAPPED, kRowThreads>(h, graph_node_ptr, row_of, g, mean, pool, part, x[0], kRowQuarter);
+  m.template request<V::RING / 2, V::RING>();
+  __syncthreads();
+#pragma unroll
+  for (int l = 0; l < 2; ++l) {
+    float y[V::PER];
+    m.run(x[l], kRowQuarter, from, extra, y);
+    float *to = a.act[l];
+    if (m.owns()) {
+#pragma unroll
+      for (int i = 0; i < V::PER; ++i) {
+        if (l == 0 || a.relu_last) y[i] = fmaxf(y[i], 0.f);
+        if (l == 0) x[1][(f[i] & 3) * kRowQuarter + (f[i] >> 2)] = y[i];
+        else a.out[(size_t)g * H + f[i]] = y[i];
+        if (to) to[(size_t)g * H + f[i]] = y[i];
+      }
+    }
+    if (l == 0) {
+      m.begin(a.map[1], H);
+      m.template request<0, V::RING>();
+      outputs(a.b[1]);
+      __syncthreads();
+    }
+  }
 }
 
 // ---- reductions over a wave or the block, in a fixed order

@@ -2780,25 +2780,20 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
   auto readout = [&](const T *hlast, const int32_t *cls) -> int {
     int rc = XRL_OK;
     if (N <= 4096 * G) {
-      // Many graphs of moderate size: a block per graph. Where each has a compute unit to itself the readout MLP follows in the same
-      // launch; a block more, and every unit's way to the weights and its matrix cores are shared by MLPs of one row in sixteen: us in
-      // one launch / two, 9 graphs of 50 nodes, H = 64 5.7 / 6.8, 15 of 338, H = 128 8.1 / 9.8, 129 of 565 10.3 / 12.4, 257 of 1253,
-      // H = 256 38 / 33, 1040 of 338, H = 128 31 / 18, 2080 58 / 39, 4624 of 940, H = 256 334 / 145. (Sums by 512 threads a graph until two
-      // blocks meet on a unit, 257 graphs 22 / 18, then 256: 1040 graphs 13.8 / 11.4.)
+      // Many graphs of moderate size: a block per graph. The readout MLP follows in the same launch where two blocks lie on a compute unit at
+      // most, of the narrower rows three come one after the other; beyond, in a launch of its own, where sixteen graphs share the weights' way from L2.
+      // us of a bf16 encode of one round, graphs of 50 nodes, in one launch / two: H = 64, 257 graphs 17.6 / 21.1, 512 24.1 / 26.9, 768 30.4 / 30.9,
+      // 1040 36.4 / 34.8; H = 128 24.1 / 27.4, 37.9 / 40.6, 47.9 / 47.9, 56.7 / 52.8; H = 256 59.6 / 63.4, 74.6 / 77.1, 98.1 / 94.2, 123 / 110.
       const RowFwdArgs ra = row_fwd_args(c, c->L.readout, true, c->pool, H, d.graph_global, m.d_global, G, d_emb, c->ro_act);
       const int mean = m.readout == XRL_READOUT_MEAN ? 1 : 0;
-      if (G > c->n_cu) {
+      if (G > (H == 256 ? 2 : 3) * c->n_cu) {
         { Timed t(c, TK_POOL);
           rc = with_readout_widths(c, [&](auto fwd, auto) -> int {
             constexpr int HH = decltype(fwd)::w[1];
-            auto go = [&](auto threads) -> int {
-              constexpr int THREADS = decltype(threads)::value;
-              auto kern = cls ? graph_pool_kernel<T, PV, HH, true, THREADS> : graph_pool_kernel<T, PV, HH, false, THREADS>;
-              kern<<<dim3((unsigned)G), dim3(THREADS), 0, c->stream>>>(hlast, d.graph_node_ptr, cls, mean, c->pool);
-              HIP_TRY(hipGetLastError());
-              return XRL_OK;
-            };
-            return G < 2 * c->n_cu ? go(std::integral_constant<int, 512>()) : go(std::integral_constant<int, 256>());
+            auto kern = cls ? graph_pool_kernel<T, PV, HH, true> : graph_pool_kernel<T, PV, HH, false>;
+            kern<<<dim3((unsigned)G), dim3(kPoolThreads), 0, c->stream>>>(hlast, d.graph_node_ptr, cls, mean, c->pool);
+            HIP_TRY(hipGetLastError());
+            return XRL_OK;
           }); }
         if (rc) return rc;
         Timed t(c, TK_READOUT);
@@ -2807,11 +2802,11 @@ int encode_impl(xrl_ctx *c, const xrl_batch *b, float *d_emb, int save) {
       if (G == 0) return XRL_OK;
       Timed t(c, TK_POOL);
       return with_readout_widths(c, [&](auto fwd, auto) -> int {
-        auto go = [&](auto mapped) {
-          return launch_rows<graph_readout_kernel<decltype(fwd), T, PV, decltype(mapped)::value>>(
-              kRowForwardMost, G, row_lds_floats(ra.pitch), c->stream, hlast, d.graph_node_ptr, cls, mean, c->pool, ra);
-        };
-        return cls ? go(std::true_type()) : go(std::false_type());
+        constexpr int HH = decltype(fwd)::w[1];
+        auto kern = cls ? graph_readout_kernel<T, PV, HH, true> : graph_readout_kernel<T, PV, HH, false>;
+        kern<<<dim3((unsigned)G), dim3(kRowThreads), 0, c->stream>>>(hlast, d.graph_node_ptr, cls, mean, c->pool, ra);
+        HIP_TRY(hipGetLastError());
+        return XRL_OK;
       });
     }
     { Timed t(c, TK_POOL);

@@ -1,7 +1,8 @@
 """The row-MLPs (readout, heads) where their launches and loops change: widths that are no multiples of sixteen, one tile, more
 tiles than waves, as wide as they go; states that share a block of the value head, more states than there are slot counters; one
 and several chunks of rows in the weight gradients; graphs
-up to one a compute unit (readout in one launch) and beyond (sum and MLP apart, two block sizes), wide and no global attributes.
+up to two or three a compute unit (readout in one launch, vector instructions) and beyond (sum and MLP apart, matrix instructions), wide and no
+global attributes.
 Against the float64 oracle with the heads' criterion of test_gpu_head_gradients.py and the forward's fp32 tolerance; a graph's
 embedding and a state's outputs are the same bits whatever the batch around them."""
 import numpy as np
@@ -70,14 +71,15 @@ def some_graphs(state, a, z):
 
 
 @pytest.mark.parametrize("readout", ["sum", "mean"])
-@pytest.mark.parametrize("hidden,d_global,precision", [(64, 0, "fp32"), (128, 100, "fp32"), (256, 1, "fp32"), (128, 3, "bf16")])
+@pytest.mark.parametrize("hidden,d_global,precision", [(64, 0, "fp32"), (128, 100, "fp32"), (256, 1, "fp32"), (128, 3, "bf16"),
+                                                       (64, 1, "bf16"), (64, 256, "fp32"), (128, 256, "bf16"), (256, 256, "fp32")])
 def test_readout_at_graph_counts(hidden, d_global, precision, readout):
     import torch
     import paper_2304_14698_amd as xrl
-    model, state = synth.make_config(1, n_cand=530)
+    model, state = synth.make_config(1, n_cand=790)
     model.update(hidden=hidden, precision=precision, rounds=1, d_global=d_global, readout=readout)
     rng = np.random.Generator(np.random.PCG64(hidden))
-    state["graph_global"] = rng.standard_normal((531, d_global)).astype(np.float32) if d_global else None
+    state["graph_global"] = rng.standard_normal((791, d_global)).astype(np.float32) if d_global else None
     w, om = weights_for(model), oracle_model(model)
     enc = xrl.Encoder(model, w)
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
@@ -87,14 +89,14 @@ def test_readout_at_graph_counts(hidden, d_global, precision, readout):
         out = enc.encode(batch).cpu().numpy()
         batch.free()
         return out
-    # every graph's row where a block makes it alone, a few of them against the oracle
-    pieces = [(a, min(a + n_cu, 531)) for a in range(0, 531, n_cu)]
+    # every graph's row from batches of few graphs, some of them against the oracle
+    pieces = [(a, min(a + n_cu, 791)) for a in range(0, 791, n_cu)]
     alone = np.concatenate([encoded(*p) for p in pieces])
     assert np.array_equal(encoded(0, 7), alone[:7])
-    for a in (0, 524):
+    for a in (0, 784):
         check_emb(alone[a:a + 7], O.encode(om, w, some_graphs(state, a, a + 7)), model, "emb")
-    for n in (n_cu, n_cu + 1, n_cu + 16, 2 * n_cu - 1, 2 * n_cu, 531):
-        n = min(n, 531)
+    for n in (n_cu + 1, 2 * n_cu, 2 * n_cu + 1, 3 * n_cu, 3 * n_cu + 1, 3 * n_cu + 16, 791):
+        n = min(n, 791)
         assert np.array_equal(encoded(0, n), alone[:n]), n
 
 
