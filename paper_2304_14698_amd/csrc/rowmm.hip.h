@@ -4,8 +4,8 @@
 // What bounds them: every block reads all the weights from L2 (320 KB for a head at H = 256), and a row is too few products
 // to hide that behind; so sixteen rows share a fragment (v_mfma_f32_16x16x4_f32, full fp32 operands and sums), the weights lie in
 // fragment order (a fragment of 16 outputs by 16 contraction indices is one coalesced 1 KB load), and the eight waves of a
-// block own different outputs, so that a layer costs one barrier. A wave requests the fragments of its next step -- across
-// the barrier between two layers -- before the products of this one: at H = 256 a step's 32 instructions take longer than
+// block own different outputs, so that a layer costs one barrier. A wave requests half of the fragments of its next step -- across
+// the barrier between two layers -- as soon as that half of this one's is used: at H = 256 a step's 32 instructions take longer than
 // the L2's answer. Both halves of a layer's widths are padded to sixteen with zeros in the fragments; any width fits.
 #pragma once
 #include <hip/hip_runtime.h>
@@ -23,14 +23,17 @@ struct RowMap {
   const f32x4 *w;
   int n_in, n_out;
 };
-// The widths of an MLP from its input on, where the kernel is made for them (0: known at run time only). These launches are chains of a
-// few round trips, and every width that has to be asked for first lengthens them.
+// The widths of an MLP from its input on, where the kernel is made for them (kAnyWidth, kNarrow: known at run time only, at most 512 and 128).
+// These launches are chains of a few round trips, and every width that has to be asked for first lengthens them.
+constexpr int kAnyWidth = 0, kNarrow = -1;
 template <int... W>
 struct RowWidths {
   static constexpr int N = sizeof...(W) - 1;                       // maps
   static constexpr int w[N + 1] = {W...};
-  static constexpr bool known = ((W > 0) && ...);                  // (else with registers of two waves per SIMD: it would spill)
-  static constexpr int waves = known || N == 2 ? 4 : 2;
+  // (any width: two waves per SIMD, whose registers hold twice the fragments in flight: at most 16 KB a wave, as a layer of 512 by 512 is 1 MB)
+  static constexpr bool wide = N > 2 && ((W == kAnyWidth) || ...);
+  static constexpr int waves = wide ? 2 : 4, frags = wide ? 2 * kRowFrags : kRowFrags;
+  template <int M> static constexpr bool few = w[M + 1] == kNarrow || (w[M + 1] > 0 && w[M + 1] <= 16 * kRowWaves);   // at most a tile per wave
   template <int M> static __device__ __forceinline__ int in(const RowMap *map) { if constexpr (w[M] > 0) return w[M]; else return map[M].n_in; }
   template <int M> static __device__ __forceinline__ int out(const RowMap *map) { if constexpr (w[M + 1] > 0) return w[M + 1]; else return map[M].n_out; }
 };
@@ -45,39 +48,46 @@ __host__ __device__ inline int row_pitch(int width) { return ((width + 15) >> 4)
 // map's x (zeros in padding columns). Returns the x that holds the last results, after a barrier.
 template <typename W>
 struct RowMaps {
-  static constexpr int HALF = kRowFrags / 2;
+  static constexpr int FRAGS = W::frags, HALF = FRAGS / 2;
   const RowMap *map;
   int lane, wave, c16, q4, pitch;
-  f32x4 next[kRowFrags];                             // of the wave's next step
+  f32x4 frag[FRAGS];                             // of the wave's step; as soon as a half is used, that of the next step is requested in its place
 
-  // A step is kRowFrags fragments of one output tile (a unit) or, where there are more tiles than waves, of two; where there are
+  // A step is FRAGS fragments of one output tile (a unit) or, where there are more tiles than waves, of two; where there are
   // at most half as many tiles as waves, of one half of a tile's contraction (a unit too: the halves are added in LDS).
   template <int M> __device__ __forceinline__ int groups() const { return (W::template in<M>(map) + 15) >> 4; }
   template <int M> __device__ __forceinline__ int tiles() const { return (W::template out<M>(map) + 15) >> 4; }
-  template <int M> __device__ __forceinline__ bool two() const { return tiles<M>() > kRowWaves; }
+  template <int M> __device__ __forceinline__ bool two() const { if constexpr (W::template few<M>) return false; else return tiles<M>() > kRowWaves; }
   template <int M> __device__ __forceinline__ int half() const {   // groups of the first half, or 0
-    return tiles<M>() <= kRowWaves / 2 && groups<M>() > HALF ? (groups<M>() + 1) >> 1 : 0;
+    return tiles<M>() <= kRowWaves / 2 && groups<M>() > kRowFrags / 2 ? (groups<M>() + 1) >> 1 : 0;
   }
   template <int M> __device__ __forceinline__ int units() const { return two<M>() ? (tiles<M>() + 1) >> 1 : half<M>() ? 2 * tiles<M>() : tiles<M>(); }
   template <int M> __device__ __forceinline__ int steps() const {
     const int g = half<M>() ? half<M>() : groups<M>();
-    return two<M>() ? (g + HALF - 1) / HALF : (g + kRowFrags - 1) / kRowFrags;
+    return two<M>() ? (g + HALF - 1) / HALF : (g + FRAGS - 1) / FRAGS;
   }
-  template <int M> __device__ __forceinline__ void request(int u, int s) {   // (past the end the last fragment again: its products are left out)
+  struct Step { const f32x4 *w0, *w1; int g0, last; bool two; };   // the tiles' fragments, its first group and the map's last
+  template <int M> __device__ __forceinline__ Step step(int u, int s) const {
     const int G = groups<M>(), last = tiles<M>() - 1, t0 = two<M>() ? 2 * u : half<M>() ? u >> 1 : u, t1 = t0 < last ? t0 + 1 : last;
-    const f32x4 *w0 = map[M].w + (unsigned)(t0 * G) * 64u, *w1 = map[M].w + (unsigned)(t1 * G) * 64u;
-    const int g0 = s * (two<M>() ? HALF : kRowFrags) + (u & 1 ? half<M>() : 0);
+    return Step{map[M].w + (unsigned)(t0 * G) * 64u, map[M].w + (unsigned)(t1 * G) * 64u,
+                s * (two<M>() ? HALF : FRAGS) + (u & 1 ? half<M>() : 0), G - 1, two<M>()};
+  }
+  // one half of a step's fragments (past the end the last one again: its products are left out)
+  template <int PART> __device__ __forceinline__ void request(const Step &st) {
 #pragma unroll
-    for (int i = 0; i < kRowFrags; ++i) {
-      int g = g0 + (two<M>() ? i >> 1 : i);
-      g = g < G ? g : G - 1;
-      const f32x4 *p = (two<M>() && (i & 1) ? w1 : w0) + (unsigned)g * 64u;   // (the same for all lanes)
-      next[i] = p[lane];
+    for (int i = PART * HALF; i < PART * HALF + HALF; ++i) {
+      int g = st.g0 + (st.two ? i >> 1 : i);
+      g = g < st.last ? g : st.last;
+      frag[i] = ((st.two && (i & 1) ? st.w1 : st.w0) + (unsigned)g * 64u)[lane];   // (the same for all lanes)
     }
   }
   template <int M> __device__ __forceinline__ void request_first() {
     if constexpr (M < W::N)
-      if (wave < units<M>()) request<M>(wave, 0);
+      if (wave < units<M>()) {
+        const Step st = step<M>(wave, 0);
+        request<0>(st);
+        request<1>(st);
+      }
   }
   template <int M, typename Pre, typename Post>
   __device__ __forceinline__ void run(float *x, float *x2, Pre &pre, Post &post) {
@@ -102,42 +112,45 @@ struct RowMaps {
         for (int j = 1; j < 4; ++j) sum[k][j] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
       for (int s = 0; s < n_steps; ++s) {
-        f32x4 w[kRowFrags], a[HALF];
+        Step next;
+        bool more = true;
+        if (s + 1 < n_steps) next = step<M>(u, s + 1);
+        else if (u + kRowWaves < n_units) next = step<M>(u + kRowWaves, 0);
+        else if constexpr (M + 1 < W::N) {
+          next = step<M + 1>(wave, 0);
+          more = wave < units<M + 1>();
+        } else more = false;
+        const int g0 = s * (two<M>() ? HALF : FRAGS) + (upper ? half<M>() : 0);
+        auto part = [&](auto which) {
+          constexpr int PART = decltype(which)::value;
+          const int gp = g0 + PART * (two<M>() ? HALF / 2 : HALF);
+          f32x4 a[HALF];
+          if (two<M>()) {
 #pragma unroll
-        for (int i = 0; i < kRowFrags; ++i) w[i] = next[i];
-        if (s + 1 < n_steps) request<M>(u, s + 1);
-        else if (u + kRowWaves < n_units) request<M>(u + kRowWaves, 0);
-        else request_first<M + 1>();
-        int g0 = s * (two<M>() ? HALF : kRowFrags) + (upper ? half<M>() : 0);
-        auto rows = [&]() {
+            for (int i = 0; i < HALF / 2; ++i) a[i] = *(const f32x4 *)(xr + 16 * (gp + i < gend ? gp + i : gend - 1));
 #pragma unroll
-          for (int i = 0; i < HALF; ++i) a[i] = *(const f32x4 *)(xr + 16 * (g0 + i < gend ? g0 + i : gend - 1));
-        };
-        rows();
-        if (two<M>()) {
+            for (int i = 0; i < HALF / 2; ++i) {
+              if (gp + i >= gend) break;
 #pragma unroll
-          for (int i = 0; i < HALF; ++i) {
-            if (g0 + i >= gend) break;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              sum[0][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j], w[2 * i][j], sum[0][j], 0, 0, 0);
-              sum[1][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j], w[2 * i + 1][j], sum[1][j], 0, 0, 0);
+              for (int j = 0; j < 4; ++j) {
+                sum[0][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j], frag[PART * HALF + 2 * i][j], sum[0][j], 0, 0, 0);
+                sum[1][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j], frag[PART * HALF + 2 * i + 1][j], sum[1][j], 0, 0, 0);
+              }
             }
-          }
-        } else {
+          } else {
 #pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            if (g0 >= gend) break;
-            if (h == 1) rows();
+            for (int i = 0; i < HALF; ++i) a[i] = *(const f32x4 *)(xr + 16 * (gp + i < gend ? gp + i : gend - 1));
 #pragma unroll
             for (int i = 0; i < HALF; ++i) {
-              if (g0 + i >= gend) break;
+              if (gp + i >= gend) break;
 #pragma unroll
-              for (int j = 0; j < 4; ++j) sum[0][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j], w[h * HALF + i][j], sum[0][j], 0, 0, 0);
+              for (int j = 0; j < 4; ++j) sum[0][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][j], frag[PART * HALF + i][j], sum[0][j], 0, 0, 0);
             }
-            g0 += HALF;
           }
-        }
+          if (more) request<PART>(next);
+        };
+        part(MapIndex<0>());
+        part(MapIndex<1>());
       }
       f32x4 acc[2];
 #pragma unroll
@@ -620,13 +633,12 @@ __global__ __launch_bounds__(kRowThreads, W::waves) void heads_kernel(const Head
       return;
     }
     // the mean embedding of the valid slots: H / 4 threads cover a row with 16-byte loads, the 2048 / H thread groups
-    // take every (2048 / H)-th slot, eight or (H = 256) sixteen loads in flight each; the groups' sums are added in order
-    constexpr int U = H > 128 ? 16 : 8;
+    // take every (2048 / H)-th slot, eight or (H = 256) twelve or sixteen loads in flight each; the groups' sums are added in order
+    constexpr int U = H <= 128 ? 8 : W::w[1] == kNarrow ? 12 : 16;
     const float *emb = a.policy.in1;
     const int tpr = H / 4, ng = kRowThreads / tpr, c4 = (t % tpr) * 4, q = t / tpr; 
     for (int i = t; i < kRowTile * pitch; i += kRowThreads) sm[i] = 0.f;
     biases.request(mlp);
-    biases.store(mlp, sm, pitch);
     for (int s = s0; s < s1; ++s) {
       const int j0 = a.state_graph_ptr[s], j1 = a.state_graph_ptr[s + 1];
       f32x4 p = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -659,6 +671,7 @@ __global__ __launch_bounds__(kRowThreads, W::waves) void heads_kernel(const Head
       }
       __syncthreads();
     }
+    biases.store(mlp, sm, pitch);
   });
   if (is_value) return;
   if (!a.logp) return;

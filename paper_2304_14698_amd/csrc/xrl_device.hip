@@ -1298,21 +1298,27 @@ int launch_rows(size_t most, int64_t blocks, size_t lds_floats, hipStream_t stre
 inline int64_t row_blocks(int64_t n) { return (n + kRowTile - 1) / kRowTile; }
 
 // go(forward widths, backward widths) of the heads and of the readout MLP: the paper's head widths are known to the kernels, any
-// others asked for; the readout's backward pass stops at the pool (the global attributes are inputs)
+// others asked for; the readout's backward pass stops at the pool (the global attributes are inputs). Others of up to 128 have a kernel
+// that never takes two tiles a wave, of half the registers, two blocks on a compute unit: us forward / forward and backward at H = 128, by vector
+// code / with one kernel for all widths / so: heads of 17 and 3, 20 k slots 46 / 59 / 33 and 137 / 106 / 71, of 128 and 64 72 / 75 / 43 and 227 / 140 / 97,
+// 15 slots 14.2 / 13.5 / 13.0 and 34 / 30 / 28. Wider: of 512 and 512, 4624 slots 189 / 87 / 75 and 553 / 230 / 209, 257 slots 43 / 45 / 39 and
+// 141 / 109 / 98, 15 slots 31 / 43 / 37 and 85 / 94 / 85 (the fp32 matrix rate of the one compute unit that has the sixteen rows).
 template <typename Go>
 int with_head_widths(const xrl_ctx *c, Go go) {
-  const bool paper = c->m.head_hidden[0] == 256 && c->m.head_hidden[1] == 64;
+  const bool paper = c->m.head_hidden[0] == 256 && c->m.head_hidden[1] == 64, narrow = std::max(c->m.head_hidden[0], c->m.head_hidden[1]) <= 16 * kRowWaves;
   auto of = [&](auto h) -> int {
     constexpr int H = decltype(h)::value;
-    return paper ? go(RowWidths<H, 256, 64, 1>(), RowWidths<1, 64, 256, H>()) : go(RowWidths<H, 0, 0, 1>(), RowWidths<1, 0, 0, H>());
+    return paper ? go(RowWidths<H, 256, 64, 1>(), RowWidths<1, 64, 256, H>()) :
+           narrow ? go(RowWidths<H, kNarrow, kNarrow, 1>(), RowWidths<1, kNarrow, kNarrow, H>()) :
+                    go(RowWidths<H, kAnyWidth, kAnyWidth, 1>(), RowWidths<1, kAnyWidth, kAnyWidth, H>());
   };
   return c->m.hidden == 64 ? of(std::integral_constant<int, 64>()) : c->m.hidden == 128 ? of(std::integral_constant<int, 128>()) :
                                                                                          of(std::integral_constant<int, 256>());
 }
 template <typename Go>
 int with_readout_widths(const xrl_ctx *c, Go go) {
-  return c->m.hidden == 64 ? go(RowWidths<0, 64, 64>(), RowWidths<64, 64, 64>()) :
-         c->m.hidden == 128 ? go(RowWidths<0, 128, 128>(), RowWidths<128, 128, 128>()) : go(RowWidths<0, 256, 256>(), RowWidths<256, 256, 256>());
+  return c->m.hidden == 64 ? go(RowWidths<kAnyWidth, 64, 64>(), RowWidths<64, 64, 64>()) :
+         c->m.hidden == 128 ? go(RowWidths<kAnyWidth, 128, 128>(), RowWidths<128, 128, 128>()) : go(RowWidths<kAnyWidth, 256, 256>(), RowWidths<256, 256, 256>());
 }
 
 RowFwdArgs row_fwd_args(const xrl_ctx *c, const MlpRef &r, bool relu_last, const float *in1, int w1, const float *in2, int w2,
