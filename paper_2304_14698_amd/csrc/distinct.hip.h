@@ -797,10 +797,9 @@ __global__ __launch_bounds__(256) void class_sum_kernel(const ClassSumArgs a) {
 // 158 / 281, 157 / 214, 156 / 135 and 523 / 542, 411 / 435, 510 / 529. (256 places a wave 202 in place of 155, an XCD to consecutive places 215: the states' shares differ.
 // The columns in two slices, on four XCDs each, 236 and 833, in four 440 and 1602, though the 6 GB become 2: a read costs
 // the same instructions for fewer columns.)
-constexpr int kWindows = 3;
-__host__ __device__ constexpr int window_size(int w) { return w == 0 ? 1 : w == 1 ? 4 : 16; }
+constexpr int kWindows = 3;                    // of 1, 4 and 16 graphs
 constexpr int kWindowStrip = 8;                // rows a thread makes, of four columns
-// rows[w][g, :] = sum of dx[g .. g + window_size(w) - 1, :], each divided by its graph's node count for the mean readout (rows past the
+// rows[w][g, :] = sum of dx[g .. g + 4^w - 1, :], each divided by its graph's node count for the mean readout (rows past the
 // last graph count as zeros: no run reads such a sum)
 __global__ __launch_bounds__(256) void pool_windows_kernel(const float *dx, const int32_t *graph_node_ptr, int mean, int64_t G, int H, float *rows) {
   constexpr int N = kWindowStrip + 15;
