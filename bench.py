@@ -30,27 +30,27 @@ PEAK_HBM_GBS = 8000.0
 TRAFFIC = {
     # configuration 2 (profiles/forward_config2_bf16_hbm_traffic.md): persistent forward kernels, weights in LDS
     (2, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2p.hip.h"), sha256_16="9c42e854a36c15c0",
-                              bytes_per_launch=(11148.7 * 2.000 + 11599.5 * 1.000) * 1024),
+                              bytes_per_launch=(11148.6 * 2.000 + 11599.5 * 1.000) * 1024),
     (2, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2p.hip.h"), sha256_16="9c42e854a36c15c0",
-                              bytes_per_launch=(15502.6 * 2.000 + 18218.2 * 1.000) * 1024),
+                              bytes_per_launch=(15507.0 * 2.000 + 18218.2 * 1.000) * 1024),
     # configuration 4 (profiles/forward_config4_bf16_kernel_stats_and_traffic.md): register-stationary forward kernels on the
     # levels of the reduced batch, mean over the rounds (so the sources that decide the levels belong to it)
-    (4, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="b81627a2f86264e5",
-                              bytes_per_launch=(20798.4 * 2.000 + 25991.7 * 1.000) * 1024),
-    (4, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="b81627a2f86264e5",
-                              bytes_per_launch=(27931.3 * 2.000 + 26453.7 * 1.000) * 1024),
+    (4, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="416fe5d8d01159b3",
+                              bytes_per_launch=(20797.1 * 2.000 + 25991.7 * 1.000) * 1024),
+    (4, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="416fe5d8d01159b3",
+                              bytes_per_launch=(27931.2 * 2.000 + 26453.7 * 1.000) * 1024),
     # configuration 5 (profiles/step_config5_bf16_hbm_traffic.md): the same, saving, and the backward kernels
-    (5, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="b81627a2f86264e5",
-                              bytes_per_launch=(58006.7 * 2.000 + 248146.9 * 1.000) * 1024),
-    (5, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="b81627a2f86264e5",
+    (5, "bf16", "edge"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="416fe5d8d01159b3",
+                              bytes_per_launch=(58008.5 * 2.000 + 248146.9 * 1.000) * 1024),
+    (5, "bf16", "node"): dict(sources=("mma.hip.h", "mlp2.hip.h", "mlp2r.hip.h", "distinct.hip.h"), sha256_16="416fe5d8d01159b3",
                               bytes_per_launch=(81359.8 * 2.000 + 172861.0 * 1.000) * 1024),
-    (5, "bf16", "bwd_edge"): dict(sources=("mma.hip.h", "mlp2_bwd.hip.h", "mlp2_bwdz.hip.h", "distinct.hip.h"), sha256_16="b7a9eb2d17c7d20f",
-                                  bytes_per_launch=(57260.7 * 2.000 + 533222.0 * 1.000) * 1024),
-    (5, "bf16", "bwd_node"): dict(sources=("mma.hip.h", "mlp2_bwd.hip.h", "mlp2_bwdz.hip.h", "distinct.hip.h"), sha256_16="b7a9eb2d17c7d20f",
-                                  bytes_per_launch=(47995.5 * 2.000 + 240256.7 * 1.000) * 1024),
+    (5, "bf16", "bwd_edge"): dict(sources=("mma.hip.h", "mlp2_bwd.hip.h", "mlp2_bwdz.hip.h", "distinct.hip.h"), sha256_16="b73d92b57674aba0",
+                                  bytes_per_launch=(57257.3 * 2.000 + 533106.1 * 1.000) * 1024),
+    (5, "bf16", "bwd_node"): dict(sources=("mma.hip.h", "mlp2_bwd.hip.h", "mlp2_bwdz.hip.h", "distinct.hip.h"), sha256_16="b73d92b57674aba0",
+                                  bytes_per_launch=(47995.2 * 2.000 + 240258.9 * 1.000) * 1024),
     # (the products of a launch and the sums of its slices)
-    (5, "bf16", "wgrad"): dict(sources=("mma.hip.h", "wgrad.hip.h", "distinct.hip.h"), sha256_16="bbabb328c220c932",
-                               bytes_per_launch=((1455839.0 + 25414.8) * 2.000 + (67488.0 + 2680.7) * 1.000) * 1024),
+    (5, "bf16", "wgrad"): dict(sources=("mma.hip.h", "wgrad.hip.h", "distinct.hip.h"), sha256_16="a55924cbd2e52e61",
+                               bytes_per_launch=((1452934.6 + 25414.9) * 2.000 + (67488.0 + 2680.7) * 1.000) * 1024),
 }
 
 
