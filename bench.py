@@ -281,7 +281,7 @@ def main():
                      bytes=NH + n_edge * De * 4 + idx_e + n_recv * H * b + zk * (EH + 2 * mask_e)),
         "node": dict(kernel="node MLP (one launch per round)", flops=2.0 * n_node * H * 3 * H,
                      bytes=(2 + zk) * NH + n_recv * H * b + 4 * n_node + zk * 2 * mask_n),   # received sums: nodes with in-edges only
-        "pool": dict(kernel="per-graph readout sum (with the readout MLP up to a graph per compute unit)", flops=0.0,
+        "pool": dict(kernel="per-graph readout sum (with the readout MLP up to two or three graphs per compute unit)", flops=0.0,
                      bytes=levels[R][0] * H * b + (4 * N if reduced else 0) + 4 * (G + 1) + G * H * 4),
         "grad_gather": dict(kernel="per-node sum of the per-edge gradients (receiver and sender side)", flops=0.0,
                             # (reduced: the three kinds of rows summed per distinct node of the round below, stored

@@ -214,6 +214,10 @@ int xrl_batch_free(xrl_batch *b);   /* frees host and device copies; NULL is acc
  * have more than 72 in-edges; 0 = never; same bits);
  * XRL_WGRAD_WIDE_MIN_ROWS = rows of the products of one weight-gradient launch, added up, from which it uses
  * 256-column tiles at hidden = 256 in bf16 (default 2^18; same sums in a different, equally fixed order);
+ * XRL_SUM_STEPS = steps of sixteen rows a group of lanes takes in the class sums of a reduced batch's backward pass (1, 2 or 4;
+ * default by the rows; same sums in a different, equally fixed order);
+ * XRL_POOL_WINDOW_NODES = nodes per compute unit of a reduced batch at hidden = 256 from which the pool's gradient is summed by
+ * 1, 4 and 16 consecutive graphs at a time (default 4096; same sums in a different, equally fixed order);
  * XRL_GRAD_ROOM = bytes of gradients kept for one such launch (default 2^31; always at least one MLP's; what is there
  * where more has been refused, or captured calls hold addresses in a smaller workspace);
  * XRL_RESIDENT_MAX_GRAPHS (default 256; 0 = never) and XRL_RESIDENT_MAX_TILES (default 4) =
