@@ -300,6 +300,142 @@ __global__ __launch_bounds__(kRowThreads, W::waves) void row_forward_kernel(cons
   });
 }
 
+// One row a block: the matrix instruction would spend its time on fifteen that are not there (H = 256: 3.6 us a layer of the readout, of one
+// block on a compute unit). v_mfma_f32_16x16x4_f32 adds its four products to a sum one after
+// the other, as four fmaf do (1M outputs each of ordinary, wide, subnormal and infinite operands: no bit differs); so a lane takes one of an
+// output's four sums (RowMaps) through the same products in the same order, and a row's results are the same bits either way.
+// Lane 4 * c + j of a wave has sum j of output 16 * tile + c: of a tile's fragments it reads every 64th float, the wave 256 bytes at a time, one
+// stream per tile. x lies in LDS by quarters, contraction index k at (k % 4) * quarter + k / 4, so that a lane reads a group's four at once.
+// floats a quarter of the widest row takes, its lanes' 16-byte reads in different banks; of two rows and the halves of a tile's contraction
+constexpr int kRowQuarter = 512 / 4 + 8, kRowOneFloats = 2 * 4 * kRowQuarter + 16 * kRowWaves / 2;
+template <typename W>
+struct RowVector {
+  static constexpr int most_tiles() {
+    int n = 0;
+    for (int k = 1; k <= W::N; ++k) {
+      const int t = (W::w[k] > 0 ? W::w[k] + 15 : W::w[k] == kNarrow ? 16 * kRowWaves : 512) / 16;
+      n = t > n ? t : n;
+    }
+    return n;
+  }
+  static constexpr int PER = (most_tiles() + kRowWaves - 1) / kRowWaves;       // tiles a wave, one in every kRowWaves
+  static constexpr int RING = PER == 1 ? 12 : PER == 2 ? 6 : 4;                // groups in flight
+  float w[RING][4][PER], from[PER];                   // fragments; what the sums start from
+  const RowMap *map;
+  int lane, wave;
+  const float *p[PER];                                // of the map at hand: the tiles' streams
+  int half, n, count;                                 // see RowMaps; this wave's groups (0: no tile) and tiles
+  bool upper;
+  template <int M> __device__ __forceinline__ int tiles() const { return (W::template out<M>(map) + 15) >> 4; }
+  template <int M> __device__ __forceinline__ int tile(int i) const { return half ? wave >> 1 : wave + kRowWaves * i; }
+  template <int M> __device__ __forceinline__ void begin(const float *bias) {
+    const int G = (W::template in<M>(map) + 15) >> 4, T = tiles<M>(), n_out = W::template out<M>(map);
+    half = T <= kRowWaves / 2 && G > kRowFrags / 2 ? (G + 1) >> 1 : 0;
+    upper = half && (wave & 1);
+    count = PER == 1 || half ? 1 : (T + kRowWaves - 1) / kRowWaves;
+    const int g0 = upper ? half : 0;
+    n = tile<M>(0) >= T ? 0 : half && !upper ? half : G - g0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int t = tile<M>(i) < T ? tile<M>(i) : T - 1, f = 16 * t + (lane >> 2);
+      p[i] = (const float *)(map[M].w + (unsigned)(t * G + g0) * 64u) + lane;
+      from[i] = (lane & 3) == 0 && !upper ? bias[f < n_out ? f : n_out - 1] : 0.f;
+    }
+  }
+  // groups FROM .. TO - 1 of those in flight
+  template <int FROM, int TO> __device__ __forceinline__ void request() {
+#pragma unroll
+    for (int r = FROM; r < TO; ++r)
+      if (r < n) load(r, r);
+  }
+  __device__ __forceinline__ void load(int r, int g) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      if (i >= count) break;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) w[r][q][i] = p[i][(unsigned)g * 256u + q * 64];
+    }
+  }
+  // the map's results, passed through post(M, f, y) in the lane that has output f, to x2 (zeros in padding columns)
+  template <int M, typename Post>
+  __device__ __forceinline__ float *run(const RowFwdArgs &a, float *x, float *x2, float *extra, Post &post) {
+    float s[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) s[i] = from[i];
+    const float *xl = x + (lane & 3) * kRowQuarter + (upper ? 4 * half : 0);
+    for (int g = 0; g < n; g += RING) {
+#pragma unroll
+      for (int r = 0; r < RING; ++r) {
+        if (g + r >= n) break;
+        const f32x4 v = *(const f32x4 *)(xl + 4 * (g + r));
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+          if (i >= count) break;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) s[i] = fmaf(v[q], w[r][q][i], s[i]);
+        }
+        if (g + r + RING < n) load(r, g + r + RING);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      s[i] += __shfl_xor(s[i], 2);                    // (s0 + s2) + (s1 + s3)
+      s[i] += __shfl_xor(s[i], 1);
+    }
+    const int T = tiles<M>(), n_out = W::template out<M>(map);
+    const bool owns = n > 0 && !upper && (lane & 3) == 0;
+    if (half) {
+      const int f = 16 * tile<M>(0) + (lane >> 2);
+      if (upper && n > 0 && (lane & 3) == 0) extra[f] = s[0];
+      __syncthreads();
+      if (owns) s[0] += extra[f];
+    }
+    if (owns) {
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        if (i >= count || tile<M>(i) >= T) break;
+        const int f = 16 * tile<M>(i) + (lane >> 2);
+        if (f < n_out) post(MapIndex<M>(), f, s[i]);
+        else s[i] = 0.f;
+        x2[(f & 3) * kRowQuarter + (f >> 2)] = s[i];
+      }
+    }
+    if constexpr (M + 1 < W::N) {
+      begin<M + 1>(a.b[M + 1]);
+      request<0, RING>();
+    }
+    __syncthreads();
+    if constexpr (M + 1 < W::N) return run<M + 1>(a, x2, x, extra, post);
+    else return x2;
+  }
+};
+// The layers of `a` on one row, which stage() writes to x (kRowOneFloats of LDS; zeros in padding columns); as row_forward otherwise.
+template <typename W, bool COHERENT_OUT, typename Stage>
+__device__ __forceinline__ float *row_forward_one(const RowFwdArgs &a, int64_t row, float *x, Stage stage) {
+  RowVector<W> m;
+  constexpr int RING = RowVector<W>::RING;
+  m.map = a.map;
+  m.lane = threadIdx.x & 63;
+  m.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool relu_last = a.relu_last;
+  m.template begin<0>(a.b[0]);
+  m.template request<0, RING / 2>();
+  stage();
+  m.template request<RING / 2, RING>();
+  __syncthreads();
+  auto post = [&](auto map, int f, float &y) {
+    constexpr int M = decltype(map)::value;
+    const int64_t at = row * W::template out<M>(a.map) + f;
+    if (M + 1 < W::N || relu_last) y = fmaxf(y, 0.f);
+    if (a.act[M]) a.act[M][at] = y;
+    if constexpr (M + 1 == W::N) {
+      if constexpr (COHERENT_OUT) __hip_atomic_store(a.out + at, y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else a.out[at] = y;
+    }
+  };
+  return m.template run<0>(a, x, x + 4 * kRowQuarter, x + 8 * kRowQuarter, post);
+}
+
 // ---- readout: the sum (or mean) of a graph's node states by a block, stored as pool[g, :] and left in row (LDS; nullable).
 // (row: column k at (k % 4) * quarter + k / 4, see RowVector.) H / VEC lanes cover a node's row with 16-byte loads. The nodes are dealt over 512 / (H / VEC) groups, of which a thread of a block of
 // THREADS threads holds V = 512 / THREADS (eight loads in flight in all), and the groups' sums are added in an order that does not
@@ -371,123 +507,18 @@ __global__ __launch_bounds__(kPoolThreads) void graph_pool_kernel(const T *h, co
   __shared__ __align__(16) float part[kPoolThreads * VEC];
   graph_pool<T, VEC, H, MAPPED, kPoolThreads>(h, graph_node_ptr, row_of, blockIdx.x, mean, pool, part, nullptr, 0);
 }
-// Few graphs: both in one launch, a block per graph, which has one row for the MLP: the matrix instruction would spend its time on fifteen
-// that are not there (H = 256: 3.6 us a layer, of one block on a compute unit). v_mfma_f32_16x16x4_f32 adds its four products to a sum one after
-// the other, as four fmaf do (1M outputs each of ordinary, wide, subnormal and infinite operands: no bit differs); so a lane takes one of an
-// output's four sums (RowMaps) through the same products in the same order, and a graph's embedding is the same bits either way.
-// Lane 4 * c + j of a wave has sum j of output 16 * tile + c: of a tile's fragments it reads every 64th float, the wave 256 bytes at a time, one
-// stream per tile. x lies in LDS by quarters, contraction index k at (k % 4) * quarter + k / 4, so that a lane reads a group's four at once.
-template <int H>
-struct RowVector {
-  static constexpr int TILES = H / 16, PER = TILES > kRowWaves ? 2 : 1, RING = PER == 2 ? 6 : 12;    // tiles a wave; groups in flight
-  float w[RING][4][PER];
-  int lane, wave, groups, half;                       // of the map at hand (see RowMaps)
-  const float *p[PER];
-  int g0, g1;                                         // this wave's groups; none: no tile
-  bool upper;
-  __device__ __forceinline__ int tile(int i) const { return half ? wave >> 1 : wave * PER + i; }
-  __device__ __forceinline__ void begin(const RowMap &map, int n_in) {
-    groups = (n_in + 15) >> 4;
-    half = TILES <= kRowWaves / 2 && groups > kRowFrags / 2 ? (groups + 1) >> 1 : 0;
-    upper = half && (wave & 1);
-    g0 = upper ? half : 0;
-    g1 = tile(0) >= TILES ? g0 : half && !upper ? half : groups;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) p[i] = (const float *)(map.w + (unsigned)((tile(0) < TILES ? tile(i) : 0) * groups + g0) * 64u) + lane;
-  }
-  // groups FROM .. TO - 1 of those in flight
-  template <int FROM, int TO> __device__ __forceinline__ void request() {
-#pragma unroll
-    for (int r = FROM; r < TO; ++r)
-      if (g0 + r < g1) load(r, r);
-  }
-  __device__ __forceinline__ void load(int r, int g) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int i = 0; i < PER; ++i) w[r][q][i] = p[i][(unsigned)g * 256u + q * 64];
-  }
-  // the sums of this wave's outputs, from `from` on (the first one's; a tile's lower half's), complete in all four lanes
-  __device__ __forceinline__ void run(const float *x, int quarter, const float *from, float *extra, float *y) {
-    float s[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) s[i] = (lane & 3) == 0 && !upper ? from[i] : 0.f;
-    const float *xl = x + (lane & 3) * quarter + 4 * g0;
-    const int n = g1 - g0;
-    for (int g = 0; g < n; g += RING) {
-#pragma unroll
-      for (int r = 0; r < RING; ++r) {
-        if (g + r >= n) break;
-        const f32x4 v = *(const f32x4 *)(xl + 4 * (g + r));
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-          for (int i = 0; i < PER; ++i) s[i] = fmaf(v[q], w[r][q][i], s[i]);
-        if (g + r + RING < n) load(r, g + r + RING);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      s[i] += __shfl_xor(s[i], 2);                    // (s0 + s2) + (s1 + s3)
-      y[i] = s[i] + __shfl_xor(s[i], 1);
-    }
-    if (half) {
-      if (upper && (lane & 3) == 0) extra[16 * tile(0) + (lane >> 2)] = y[0];
-      __syncthreads();
-      if (!upper && g1 > g0) y[0] += extra[16 * tile(0) + (lane >> 2)];
-    }
-  }
-  __device__ __forceinline__ bool owns() const { return g1 > g0 && !upper && (lane & 3) == 0; }   // a lane that has outputs to store
-};
-// floats a quarter of the widest row takes, its lanes' 16-byte reads in different banks
-constexpr int kRowQuarter = 512 / 4 + 8;
+// Few graphs: both in one launch, a block per graph, the MLP's first weights requested ahead of the sum.
 template <typename T, int VEC, int H, bool MAPPED>
 __global__ __launch_bounds__(kRowThreads, 4) void graph_readout_kernel(const T *h, const int32_t *graph_node_ptr, const int32_t *row_of, int mean,
                                                                        float *pool, const RowFwdArgs a) {
-  using V = RowVector<H>;
-  __shared__ __align__(16) float part[kRowThreads * VEC], x[2][4 * kRowQuarter], extra[H];
+  __shared__ __align__(16) float part[kRowThreads * VEC], x[kRowOneFloats];
   touch_args(a);
-  const int g = blockIdx.x, t = threadIdx.x, n_in = H + a.w2;
-  V m;
-  m.lane = t & 63;
-  m.wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  m.begin(a.map[0], n_in);
-  m.template request<0, V::RING / 2>();
-  float from[V::PER];
-  int f[V::PER];
-  auto outputs = [&](const float *bias) {             // this wave's of the map at hand, and what their sums start from
-#pragma unroll
-    for (int i = 0; i < V::PER; ++i) {
-      f[i] = 16 * m.tile(i) + (m.lane >> 2);
-      from[i] = bias[f[i] < H ? f[i] : H - 1];
-    }
-  };
-  outputs(a.b[0]);
-  for (int k = H + t; k < ((n_in + 15) & ~15); k += kRowThreads) x[0][(k & 3) * kRowQuarter + (k >> 2)] = k < n_in ? a.in2[(size_t)g * a.w2 + (k - H)] : 0.f;
-  graph_pool<T, VEC, H, MAPPED, kRowThreads>(h, graph_node_ptr, row_of, g, mean, pool, part, x[0], kRowQuarter);
-  m.template request<V::RING / 2, V::RING>();
-  __syncthreads();
-#pragma unroll
-  for (int l = 0; l < 2; ++l) {
-    float y[V::PER];
-    m.run(x[l], kRowQuarter, from, extra, y);
-    float *to = a.act[l];
-    if (m.owns()) {
-#pragma unroll
-      for (int i = 0; i < V::PER; ++i) {
-        if (l == 0 || a.relu_last) y[i] = fmaxf(y[i], 0.f);
-        if (l == 0) x[1][(f[i] & 3) * kRowQuarter + (f[i] >> 2)] = y[i];
-        else a.out[(size_t)g * H + f[i]] = y[i];
-        if (to) to[(size_t)g * H + f[i]] = y[i];
-      }
-    }
-    if (l == 0) {
-      m.begin(a.map[1], H);
-      m.template request<0, V::RING>();
-      outputs(a.b[1]);
-      __syncthreads();
-    }
-  }
+  const int g = blockIdx.x, n_in = H + a.w2;
+  (void)row_forward_one<RowWidths<kAnyWidth, H, H>, false>(a, g, x, [&]() {
+    for (int k = H + threadIdx.x; k < ((n_in + 15) & ~15); k += kRowThreads)
+      x[(k & 3) * kRowQuarter + (k >> 2)] = k < n_in ? a.in2[(size_t)g * a.w2 + (k - H)] : 0.f;
+    graph_pool<T, VEC, H, MAPPED, kRowThreads>(h, graph_node_ptr, row_of, g, mean, pool, part, x, kRowQuarter);
+  });
 }
 
 // ---- reductions over a wave or the block, in a fixed order
@@ -600,35 +631,43 @@ struct HeadsArgs {
   int32_t *action;
   float *zmean;
 };
-template <typename W>
+// ONE: a slot or state a block (value_rows 1), by vector instructions.
+template <typename W, bool ONE>
 __global__ __launch_bounds__(kRowThreads, W::waves) void heads_kernel(const HeadsArgs a) {
+  constexpr int ROWS = ONE ? 1 : kRowTile;
   extern __shared__ __align__(16) float sm[];
   __shared__ float red[2 * kRowWaves];
-  __shared__ int sh_state[kRowTile], sh_done[kRowTile], sh_n_done;
+  __shared__ int sh_state[ROWS], sh_done[ROWS], sh_n_done;
   __shared__ __align__(16) f32x4 part[kRowThreads];
   __shared__ int n_valid[kRowThreads];
   touch_args(a);
   constexpr int H = W::w[0];
-  const int t = threadIdx.x, policy_blocks = (a.G + kRowTile - 1) / kRowTile, pitch = a.policy.pitch;
+  const int t = threadIdx.x, policy_blocks = (a.G + ROWS - 1) / ROWS, pitch = a.policy.pitch;
   const bool is_value = (int)blockIdx.x >= policy_blocks;
   const RowFwdArgs &mlp = is_value ? a.value : a.policy;            // (one copy of the layers' code for both)
-  const int slot0 = blockIdx.x * kRowTile;
+  const int slot0 = blockIdx.x * ROWS;
   const int s0 = ((int)blockIdx.x - policy_blocks) * a.value_rows, s1 = s0 + a.value_rows < a.S ? s0 + a.value_rows : a.S;
-  const float *y = row_forward<W, true>(mlp, is_value ? s0 : slot0, is_value ? s1 : a.G, sm, pitch, [&]() {
+  auto stage = [&]() {
     RowBiases<W> biases;
     if (!is_value) {
       // the block's slots; meanwhile find their states
-      RowInputs in;
-      in.request(mlp, H, slot0);
-      biases.request(mlp);
-      if (a.logp && t < kRowTile) sh_state[t] = -1;
-      __syncthreads();
-      in.store(mlp, H, H, slot0, sm, pitch);
-      biases.store(mlp, sm, pitch);
+      if constexpr (ONE) {
+        if (t < H) sm[(t & 3) * kRowQuarter + (t >> 2)] = mlp.in1[(size_t)slot0 * H + t];
+        if (a.logp && t < ROWS) sh_state[t] = -1;
+        __syncthreads();
+      } else {
+        RowInputs in;
+        in.request(mlp, H, slot0);
+        biases.request(mlp);
+        if (a.logp && t < ROWS) sh_state[t] = -1;
+        __syncthreads();
+        in.store(mlp, H, H, slot0, sm, pitch);
+        biases.store(mlp, sm, pitch);
+      }
       if (!a.logp) return;
       for (int s = t; s < a.S; s += kRowThreads) {
         const int p0 = a.state_graph_ptr[s], p1 = a.state_graph_ptr[s + 1];
-        for (int r = p0 > slot0 ? p0 - slot0 : 0; r < kRowTile && slot0 + r < p1; ++r) sh_state[r] = s;
+        for (int r = p0 > slot0 ? p0 - slot0 : 0; r < ROWS && slot0 + r < p1; ++r) sh_state[r] = s;
       }
       return;
     }
@@ -637,8 +676,10 @@ __global__ __launch_bounds__(kRowThreads, W::waves) void heads_kernel(const Head
     constexpr int U = H <= 128 ? 8 : W::w[1] == kNarrow ? 12 : 16;
     const float *emb = a.policy.in1;
     const int tpr = H / 4, ng = kRowThreads / tpr, c4 = (t % tpr) * 4, q = t / tpr; 
-    for (int i = t; i < kRowTile * pitch; i += kRowThreads) sm[i] = 0.f;
-    biases.request(mlp);
+    if constexpr (!ONE) {
+      for (int i = t; i < kRowTile * pitch; i += kRowThreads) sm[i] = 0.f;
+      biases.request(mlp);
+    }
     for (int s = s0; s < s1; ++s) {
       const int j0 = a.state_graph_ptr[s], j1 = a.state_graph_ptr[s + 1];
       f32x4 p = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -667,23 +708,29 @@ __global__ __launch_bounds__(kRowThreads, W::waves) void heads_kernel(const Head
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[i] /= nv;
         *(f32x4 *)(a.zmean + (size_t)s * H + c4) = acc;
-        *(f32x4 *)(sm + (s - s0) * pitch + c4) = acc;
+        if constexpr (ONE) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sm[i * kRowQuarter + (c4 >> 2)] = acc[i];
+        } else *(f32x4 *)(sm + (s - s0) * pitch + c4) = acc;
       }
       __syncthreads();
     }
-    biases.store(mlp, sm, pitch);
-  });
+    if constexpr (!ONE) biases.store(mlp, sm, pitch);
+  };
+  const float *y;
+  if constexpr (ONE) y = row_forward_one<W, true>(mlp, is_value ? s0 : slot0, sm, stage);
+  else y = row_forward<W, true>(mlp, is_value ? s0 : slot0, is_value ? s1 : a.G, sm, pitch, stage);
   if (is_value) return;
   if (!a.logp) return;
   __builtin_amdgcn_s_waitcnt(0x0F70);                              // vmcnt(0): this wave's logit stores have completed
   __syncthreads();
-  if (t < kRowTile) {
+  if (t < ROWS) {
     // one thread per slot; that of a state's first slot here speaks for the state (the sixteen lanes are one wave's)
     const int s = sh_state[t];
     bool done = false;
     if (s >= 0 && (t == 0 || sh_state[t - 1] != s)) {
       int k = 1;
-      while (t + k < kRowTile && sh_state[t + k] == s) ++k;
+      while (t + k < ROWS && sh_state[t + k] == s) ++k;
       const int slots = a.state_graph_ptr[s + 1] - a.state_graph_ptr[s];
       done = k == slots;
       if (!done && atomicAdd(&a.counter[s], k) + k == slots) {
@@ -698,7 +745,7 @@ __global__ __launch_bounds__(kRowThreads, W::waves) void heads_kernel(const Head
   __syncthreads();
   const float *logit = a.policy.out;
   auto with_logits = [&](int j0, int j1, auto go) {                // its own logits are still in LDS
-    if (j0 >= slot0 && j1 <= slot0 + kRowTile) go([&](int j) { return y[(j - slot0) * pitch]; });
+    if (j0 >= slot0 && j1 <= slot0 + ROWS) go([&](int j) { return y[(j - slot0) * pitch]; });
     else go([&](int j) { return __hip_atomic_load(logit + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); });
   };
   const int n_done = sh_n_done;

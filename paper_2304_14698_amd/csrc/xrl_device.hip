@@ -1302,7 +1302,7 @@ inline int64_t row_blocks(int64_t n) { return (n + kRowTile - 1) / kRowTile; }
 // that never takes two tiles a wave, of half the registers, two blocks on a compute unit: us forward / forward and backward at H = 128, by vector
 // code / with one kernel for all widths / so: heads of 17 and 3, 20 k slots 46 / 59 / 33 and 137 / 106 / 71, of 128 and 64 72 / 75 / 43 and 227 / 140 / 97,
 // 15 slots 14.2 / 13.5 / 13.0 and 34 / 30 / 28. Wider: of 512 and 512, 4624 slots 189 / 87 / 75 and 553 / 230 / 209, 257 slots 43 / 45 / 39 and
-// 141 / 109 / 98, 15 slots 31 / 43 / 37 and 85 / 94 / 85 (the fp32 matrix rate of the one compute unit that has the sixteen rows).
+// 141 / 109 / 98 (with few slots they go by launch_heads' rule).
 template <typename Go>
 int with_head_widths(const xrl_ctx *c, Go go) {
   const bool paper = c->m.head_hidden[0] == 256 && c->m.head_hidden[1] == 64, narrow = std::max(c->m.head_hidden[0], c->m.head_hidden[1]) <= 16 * kRowWaves;
@@ -1365,7 +1365,13 @@ int launch_heads(xrl_ctx *c, const xrl_batch *b, const float *d_emb, float *logi
   a.counter = counter; a.logp = counted ? logp : nullptr; a.entropy = entropy; a.action = action; a.zmean = zmean;
   const int64_t blocks = row_blocks(b->G) + (b->S + a.value_rows - 1) / a.value_rows;
   const int rc = with_head_widths(c, [&](auto fwd, auto) {
-    return launch_rows<heads_kernel<decltype(fwd)>>(kRowForwardMost, blocks, row_lds_floats(a.policy.pitch), c->stream, a);
+    using W = decltype(fwd);
+    // (heads wider than 128: a slot or state a block, by vector instructions, where each block has a compute unit to itself, of H <= 128 half of one.
+    // us by vector code of another order / sixteen slots a block / so: heads of 512 and 512, H = 256, 15 slots 34 / 42 / 22, 254 47 / 44 / 27, 258 47 / 44 / 44;
+    // H = 128 31 / 37 / 20, 42 / 39 / 25, 42 / 39 / 31, 701 47 / 41 / 52; of 300 and 100, H = 128, 15 slots 16 / 18 / 13, 258 19 / 20 / 16, 511 25 / 20 / 20.)
+    if constexpr (W::wide)
+      if (b->G + b->S <= (H == 256 ? 1 : 2) * c->n_cu) return launch_rows<heads_kernel<W, true>>(kRowForwardMost, b->G + b->S, kRowOneFloats, c->stream, a);
+    return launch_rows<heads_kernel<W, false>>(kRowForwardMost, blocks, row_lds_floats(a.policy.pitch), c->stream, a);
   });
   if (rc) {
     // (a launch that the runtime rejected has not run; one that failed later may have left

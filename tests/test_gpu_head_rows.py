@@ -16,7 +16,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("hidden,heads,n_states,n_cand", [
     (128, None, 127, 0), (64, None, 43, 4), (256, None, 1, 128), (128, (100, 35), 3, 42),
     (64, None, 1023, 0), (128, None, 93, 10), (128, (100, 35), 206, 4), (256, None, 6, 205),
-    (128, None, 4, 15), (64, None, 2, 16), (256, None, 2, 63), (64, (100, 35), 2, 64), (256, None, 1040, 0)])
+    (128, None, 4, 15), (64, None, 2, 16), (256, None, 2, 63), (64, (100, 35), 2, 64), (256, None, 1040, 0),
+    (64, (300, 140), 6, 60), (256, (512, 512), 14, 20), (128, (40, 200), 4, 70)])    # alone a slot a block, with the others sixteen
 def test_heads_at_rows_per_block(hidden, heads, n_states, n_cand):
     import torch
     import paper_2304_14698_amd as xrl

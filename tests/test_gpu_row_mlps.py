@@ -20,6 +20,7 @@ pytestmark = pytest.mark.gpu
     (64, (16, 16), 2, 20), (128, (17, 3), 3, 42), (64, (129, 64), 2, 70), (256, (512, 512), 2, 30), (128, (1, 1), 1, 16),
     (64, (256, 64), 300, 1), (64, (40, 12), 4100, 0),
     (64, (128, 128), 2, 20), (256, (113, 128), 2, 30), (128, (512, 17), 2, 40), (64, (128, 130), 2, 15),
+    (256, (17, 512), 2, 40), (128, (200, 300), 1, 254), (64, (129, 64), 9, 40), (256, (512, 512), 2, 150),
     (64, (256, 64), 1, 127), (128, (256, 64), 1, 128), (128, (100, 36), 3, 170), (64, (65, 66), 9, 255)])   # a chunk of rows, and more
 def test_heads_of_any_width(hidden, heads, n_states, n_cand):
     import torch
