@@ -1,5 +1,5 @@
 // Row-MLPs on the fp32 matrix cores: sixteen rows of per-graph or per-state data per block through the readout MLP of the
-// global-update layer (Section 3.4) or the policy and value heads (Section 3.3.2), and back.
+// global-update layer (Section 3.4) or the policy and value heads (Section 3.3.2), and back; where a block has one row, by vector instructions (RowVector).
 //
 // What bounds them: every block reads all the weights from L2 (320 KB for a head at H = 256), and a row is too few products
 // to hide that behind; so sixteen rows share a fragment (v_mfma_f32_16x16x4_f32, full fp32 operands and sums), the weights lie in
